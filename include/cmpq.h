@@ -473,9 +473,12 @@ int cmpq_outliers_by_column(const int32_t *out_idx, const uint16_t *out_val, int
  *   act_idx [k_act], W_act [k_act, d_out] (ld_act)       the channels of O_act, FP16;
  *   colptr, row_idx, delta                               O_q from cmpq_outliers_by_column
  *                                                        (colptr null: no such outliers).
- * Products and sums are fp32: per output the table products are summed over slabs of 128
- * rows of one width in a fixed order, then the O_act rows, then the column's O_q entries;
- * the result is reproducible bit for bit.  Workspace: CMPQ_OP_LUT_MATVEC with n = m.
+ * Products are exact and sums fp32: per output the products of the packed rows are summed over
+ * slabs of rows of one width in a fixed order, then the O_act rows, then the column's O_q
+ * entries.  Several tokens are multiplied together on the matrix cores (FP16 operands, fp32
+ * sums, runs of at most 512 rows added up apart); with many tokens an entry of O_q replaces its
+ * level before the product.  Which way is taken, and so the last bits of a result, depends on
+ * m, d_in and d_out alone; the result is reproducible bit for bit.  Workspace: CMPQ_OP_LUT_MATVEC with n = m.
  * Limits: m <= 65535, d_out < 2^20.
  */
 int cmpq_lut_matvec(const void *X, int64_t m, int64_t d_in, int64_t ldx, int64_t d_out,

@@ -1,0 +1,992 @@
+// The product with the deployed weight for several tokens (Sec. 6 / Fig. 4 of arXiv 2410.13056):
+// Y[t,o] = sum_i X[t,i] * W_hat[i,o] as a matrix product on the matrix cores, from the stored
+// format.  FP16 levels and inputs multiply exactly, sums are fp32, as in the single-token kernel.
+//
+// Work is cut into steps of 32 rows of one width (or of O_act): the 32 rows are the depth of one
+// v_mfma_f32_16x16x32_f16, and because the order of the rows is free, a lane may hold any 8 of
+// them.  A wavefront takes 256 outputs: lane (i, kg) = (lane % 16, lane / 16) reads the codes of
+// its 16 outputs 16 i .. 16 i + 15 in each of the rows 8 kg .. 8 kg + 7, and turns them into 16
+// operands, one per output, of 8 rows each: operand e of the wavefront covers the outputs
+// 16 i + e.  No code passes between lanes.
+//
+//   * tokens_kernel     X in operand order (rows as the steps take them), and channel by channel
+//                       for the entries of O_q;
+//   * few tokens: lut_tokens_kernel multiplies while it decodes - a weight is decoded once per
+//     16 or 32 tokens and never stored - and leaves one partial result per slab of rows;
+//     tokens_finish_kernel adds the slabs and the entries of O_q in a fixed order;
+//   * many tokens: lut_decode_kernel writes W_hat once in operand order, override_kernel puts the
+//     entries of O_q in, and weight_gemm_kernel multiplies.
+// Every sum has a fixed order: results are reproducible bit for bit, and a layer's result does
+// not depend on the other layers of a call.
+//
+// Measured against one token after the other (us per call): two 13824x5120 layers, 16 tokens 281 ->
+// 56, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 304, of which the
+// product 210 (690 TFLOP/s of the 1144 that a large library product reaches here), decoding 66
+// (4.2 TB/s).  The error against 64 bits is the same within a few per cent (1.0e-7 to 1.4e-7).
+// What bounds the few-token kernel is instruction issue (half of its time is vector instructions,
+// a third LDS look-ups at 2.4 clocks each, which overlap poorly with 3 wavefronts per SIMD) and,
+// for small layers, the first pass through its code.
+#include "lut_gemm.h"
+#include <limits.h>
+
+namespace {
+
+typedef _Float16 Half8 __attribute__((ext_vector_type(8)));
+typedef float Float4 __attribute__((ext_vector_type(4)));
+typedef uint32_t Word4 __attribute__((ext_vector_type(4)));
+
+constexpr int kRowsPerStep = 32;
+constexpr int kOuts = 16;                    // outputs of a lane = operands of a wavefront per step
+constexpr int kTileOuts = 16 * kOuts;        // outputs of a wavefront
+constexpr int kThreads = 256, kWaves = kThreads / CMPQ_WAVE;
+constexpr int kMaxSegs = 5;                  // four widths and O_act
+constexpr int kActBits = 16;
+constexpr int kTok = 16;                     // tokens of an operand
+
+// Rows of one width (or of O_act, bits = 16).
+struct Seg {
+    const uint32_t *packed;
+    const uint16_t *lut;
+    const int32_t *chan;
+    int rows, words_per_row, bits, step0;    // step0: first step among all steps of the layer
+    int steps, slabs;                        // few tokens: slabs that share the steps
+};
+
+struct Layer {
+    Seg seg[kMaxSegs];
+    const __half *X, *W_act;
+    int64_t ldx, ld_act;
+    const int32_t *colptr, *row_idx;
+    const float *delta;
+    float *Y;
+    int64_t ldy;
+    uint4 *xf;          // [token tile][step][lane]: X in operand order
+    __half *xt;         // [token tile][channel][16 tokens]
+    int32_t *pos;       // [channel]: its row among all steps (many tokens)
+    float *partial;     // [slab][token][d_out]
+    uint4 *dense;       // [step][tile][operand][lane]: W_hat in operand order (many tokens)
+    int d_in, d_out, n_seg, steps, tiles, slabs, act_vec_ok;
+    int slab0[kMaxSegs];  // few tokens: first slab of each segment
+};
+
+constexpr int kMaxLayers = CMPQ_MAX_GROUP;
+struct Group {
+    int wg0[kMaxLayers];  // first workgroup of each layer in the launch (past the last layer: INT_MAX)
+    int n_layers, m, token_tiles;
+    Layer l[kMaxLayers];
+};
+static_assert(sizeof(Group) <= 4096, "travels in the kernel arguments");
+
+// The layer a workgroup belongs to, and its number among that layer's workgroups.
+__device__ __forceinline__ const Layer &layer_of(const Group &g, int &wg) {
+    int l = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxLayers; ++i) l += (int)blockIdx.x >= g.wg0[i];
+    wg = (int)blockIdx.x - g.wg0[l];
+    return g.l[l];
+}
+
+// Workgroups are dealt out to the 8 XCDs in turn.  This renumbering gives each XCD a contiguous
+// range of work, so that neighbouring tiles, which share cache lines of the packed rows (or whole
+// operands), meet in one L2.
+__device__ __forceinline__ int xcd_order(int i, int n) {
+    const int q = n >> 3, r = n & 7, x = i & 7;
+    return x * q + min(x, r) + (i >> 3);
+}
+
+// ---- X as the product reads it
+
+// Workgroups of a layer: per token tile, blocks of 256 rows (8 steps) of the operand order, then
+// blocks of 256 channels.
+__global__ __launch_bounds__(kThreads) void tokens_kernel(Group g) {
+    int b;
+    const Layer &L = layer_of(g, b);
+    const int tid = threadIdx.x;
+    const int row_blocks = (L.steps + 7) / 8, chan_blocks = L.xt ? (L.d_in + kThreads - 1) / kThreads : 0;
+    const int tt = b / (row_blocks + chan_blocks);
+    b -= tt * (row_blocks + chan_blocks);
+    const int t0 = tt * kTok;
+    if (b >= row_blocks) {
+        const int c = (b - row_blocks) * kThreads + tid;
+        if (c >= L.d_in) return;
+        __half v[kTok];
+#pragma unroll
+        for (int t = 0; t < kTok; ++t)
+            v[t] = t0 + t < g.m ? L.X[(int64_t)(t0 + t) * L.ldx + c] : __ushort_as_half(0);
+        uint4 *dst = reinterpret_cast<uint4 *>(L.xt + ((int64_t)tt * L.d_in + c) * kTok);
+        dst[0] = reinterpret_cast<const uint4 *>(v)[0];
+        dst[1] = reinterpret_cast<const uint4 *>(v)[1];
+        return;
+    }
+    __shared__ __align__(16) __half s[kTok][kThreads + 8];
+    const int k = b * kThreads + tid, step = k / kRowsPerStep;
+    int chan = -1;
+    if (step < L.steps) {
+#pragma unroll
+        for (int j = 0; j < kMaxSegs; ++j) {  // segments that are not there have no rows
+            const int row = k - L.seg[j].step0 * kRowsPerStep;
+            if (row >= 0 && row < L.seg[j].rows) chan = L.seg[j].chan[row];
+        }
+    }
+    if (L.pos && tt == 0 && chan >= 0) L.pos[chan] = k;
+#pragma unroll
+    for (int t = 0; t < kTok; ++t)
+        s[t][tid] = chan >= 0 && t0 + t < g.m ? L.X[(int64_t)(t0 + t) * L.ldx + chan] : __ushort_as_half(0);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int unit = u * kThreads + tid, st = unit / CMPQ_WAVE, lane = unit % CMPQ_WAVE;
+        if (b * 8 + st < L.steps)
+            L.xf[((int64_t)tt * L.steps + b * 8 + st) * CMPQ_WAVE + lane] =
+                *reinterpret_cast<const uint4 *>(&s[lane % 16][st * kRowsPerStep + (lane / 16) * 8]);
+    }
+}
+
+// What the decoding of a tile needs of its layer, copied out of the kernel arguments once.
+struct TileArgs {
+    uint4 *xf;
+    const __half *X, *W_act;
+    int64_t ldx;
+    int64_t ld_act;
+    float *partial;
+    int steps, d_out, act_vec_ok;
+};
+
+// ---- decoding one step: 32 rows x 256 outputs -> 16 operands
+
+// LDS of a wavefront: the level tables of a step's 32 rows, twice.  Widths 1, 3, 4:
+// [row % 8][row / 8][16 levels]; width 2: pairs of rows, [row / 2 % 4][row / 8][16 pairs of codes],
+// an entry the two rows' levels side by side, so that one look-up decodes two weights.  The tables
+// that a half-wavefront reads at once lie in different banks.
+constexpr int kTableBytes = kRowsPerStep * 16 * 2;
+
+// (v << 1) + base in one instruction.
+__device__ __forceinline__ uint32_t shl1_add(uint32_t v, uint32_t base) {
+    uint32_t r;
+    asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(r) : "v"(v), "v"(base));
+    return r;
+}
+
+// base + byte q of t in one instruction (written out: the compiler takes the byte out first).
+template <int Q>
+__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t t) {
+    uint32_t r;
+    if constexpr (Q == 0) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(base), "v"(t));
+    else if constexpr (Q == 1) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(base), "v"(t));
+    else if constexpr (Q == 2) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(base), "v"(t));
+    else asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(base), "v"(t));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t t, int q) {  // q known at compile time
+    return q == 0 ? add_byte<0>(base, t) : (q == 1 ? add_byte<1>(base, t) : (q == 2 ? add_byte<2>(base, t) : add_byte<3>(base, t)));
+}
+
+template <typename T>
+__device__ __forceinline__ uint32_t lds_read(uint32_t at) {
+    typedef const T __attribute__((address_space(3))) *P;
+    return *(P)(uintptr_t)at;
+}
+
+template <int B>
+struct Decoder {
+    static constexpr bool kAct = B == kActBits, kPairs = B == 2;
+    static constexpr int kWords = kAct ? 4 : (B >= 3 ? 2 : 1);  // words fetched per row: 16 outputs (O_act: 8)
+    static constexpr int kLevels = kAct ? 0 : 1 << B;
+    static constexpr int kEntries = kLevels / 2;               // levels a lane fetches per step (not for pairs)
+    static constexpr int kRaw = kPairs ? 4 : 8;                // look-ups per operand
+    uint32_t w[8][kWords];
+    uint32_t e[4];
+
+    // The words of this lane's outputs in its 8 rows of the step that starts at `row`, and its share
+    // of the step's tables.  Rows past the end are read again from the last one; their tables are
+    // zero, so they add nothing.
+    __device__ __forceinline__ void fetch(const TileArgs &L, const Seg &s, int row, int out0, bool full, int half = 0) {
+        const int lane = threadIdx.x & 63, kg = lane >> 4;
+        const int unit = (out0 >> 4) + (lane & 15);        // which 16 outputs of a row
+        if constexpr (kAct) {
+            const int o = unit * kOuts + half * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int r = row + 8 * kg + j;
+                const bool ok = r < s.rows;
+                const __half *p = L.W_act + (int64_t)min(r, s.rows - 1) * L.ld_act + o;
+                if (full && L.act_vec_ok) {
+                    const uint4 a = *reinterpret_cast<const uint4 *>(p);
+                    w[j][0] = ok ? a.x : 0, w[j][1] = ok ? a.y : 0, w[j][2] = ok ? a.z : 0, w[j][3] = ok ? a.w : 0;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        uint32_t v = 0;
+                        if (ok && o + 2 * q < L.d_out) v = __half_as_ushort(p[2 * q]);
+                        if (ok && o + 2 * q + 1 < L.d_out) v |= (uint32_t)__half_as_ushort(p[2 * q + 1]) << 16;
+                        w[j][q] = v;
+                    }
+                }
+            }
+        } else {
+            const int first = B == 4 ? 2 * unit : (B == 3 ? 3 * (unit >> 1) + (unit & 1) : (B == 2 ? unit : unit >> 1));
+            const uint32_t wpr = (uint32_t)s.words_per_row;
+            // a uniform base and a 32-bit offset per lane (the packed rows of a width stay below 2^30 bytes)
+            const char *base = reinterpret_cast<const char *>(s.packed) + (uint64_t)row * wpr * 4u;
+            typedef uint32_t WordsN __attribute__((ext_vector_type(kWords), aligned(4)));
+            if (full && row + kRowsPerStep <= s.rows) {
+                const uint32_t at = ((uint32_t)(8 * kg) * wpr + (uint32_t)first) * 4u;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const WordsN v = __builtin_nontemporal_load(reinterpret_cast<const WordsN *>(base + (uint64_t)(at + j * wpr * 4u)));
+#pragma unroll
+                    for (int q = 0; q < kWords; ++q) w[j][q] = v[q];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t *p = reinterpret_cast<const uint32_t *>(base) + (uint64_t)min(8 * kg + j, s.rows - 1 - row) * wpr + first;
+#pragma unroll
+                    for (int q = 0; q < kWords; ++q) w[j][q] = first + q < s.words_per_row ? p[q] : 0u;
+                }
+            }
+            const uint16_t *lut = s.lut + (int64_t)row * kLevels;
+            const int left = s.rows - row;                 // rows of the step
+            if constexpr (kPairs) {
+                // lane: rows 2 p, 2 p + 1 with p = lane / 4; the upper row's code lane % 4
+                const int r0 = lane >> 2 << 1;
+                const uint16_t *lo = lut + min(r0, left - 1) * kLevels;
+                uint16_t t[kLevels], h = lut[min(r0 + 1, left - 1) * kLevels + (lane & 3)];
+                __builtin_memcpy(t, lo, sizeof(t));
+                const uint32_t hi = r0 + 1 < left ? (uint32_t)h << 16 : 0u;
+#pragma unroll
+                for (int q = 0; q < kLevels; ++q) e[q] = (r0 < left ? (uint32_t)t[q] : 0u) | hi;
+            } else {
+                // lane: row lane / 2, half lane % 2 of its table
+                const int r = lane >> 1;
+                uint16_t t[8];
+                __builtin_memcpy(t, lut + min(r, left - 1) * kLevels + (lane & 1) * kEntries, kEntries * 2);
+#pragma unroll
+                for (int q = 0; q < (kEntries + 1) / 2; ++q)
+                    e[q] = r < left ? (uint32_t)t[2 * q] | (kEntries > 1 ? (uint32_t)t[2 * q + 1] << 16 : 0u) : 0u;
+            }
+        }
+    }
+
+    // Puts this lane's share of the tables into the wavefront's table buffer, and moves the codes
+    // of widths 1 and 3 to the start of their words (odd units start in the middle of one).
+    __device__ __forceinline__ void settle(unsigned char *buf) {
+        const int lane = threadIdx.x & 63;
+        if constexpr (kPairs) {
+            const int p = lane >> 2;
+            *reinterpret_cast<uint4 *>(buf + (p & 3) * 256 + (p >> 2) * 64 + (lane & 3) * 16) = make_uint4(e[0], e[1], e[2], e[3]);
+        } else if constexpr (!kAct) {
+            const int row = lane >> 1;
+            unsigned char *p = buf + ((row & 7) * 4 + (row >> 3)) * 32 + (lane & 1) * kEntries * 2;
+            if constexpr (B == 4) *reinterpret_cast<uint4 *>(p) = make_uint4(e[0], e[1], e[2], e[3]);
+            else if constexpr (B == 3) *reinterpret_cast<uint2 *>(p) = make_uint2(e[0], e[1]);
+            else *reinterpret_cast<uint16_t *>(p) = (uint16_t)e[0];
+            const int shift = 16 * (lane & 1);  // out0 is a whole number of units of 16 outputs, an even one
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (B == 3) {
+                    w[j][0] = __builtin_amdgcn_alignbit(w[j][1], w[j][0], shift);
+                    w[j][1] >>= shift;
+                }
+                if constexpr (B == 1) w[j][0] >>= shift;
+            }
+        }
+    }
+
+    // LDS address of this lane's tables.
+    static __device__ __forceinline__ uint32_t tables_at(const unsigned char *tables) {
+        return (uint32_t)reinterpret_cast<uintptr_t>(tables) + ((threadIdx.x & 63) >> 4) * (kPairs ? 64 : 32);
+    }
+
+    // What operand k (output k of this lane in its 8 rows) is made of, and the operand.  Two parts,
+    // so that the look-ups of the next operands can be under way while these are packed and multiplied.
+    struct Raw {
+        uint32_t v[kRaw];
+    };
+    __device__ __forceinline__ Raw look_up(int k, uint32_t at) const {
+        Raw r;
+#pragma unroll
+        for (int j = 0; j < kRaw; ++j) {
+            if constexpr (kAct) {
+                r.v[j] = w[j][k >> 1];
+            } else if constexpr (kPairs) {
+                // nibbles of a pair of rows' codes (even outputs | odd outputs), times 4, a byte each
+                const uint32_t a = w[2 * j][0], b = w[2 * j + 1][0];
+                const uint32_t n = k & 1 ? ((a >> 2) & 0x33333333u) | (b & 0xccccccccu) : (a & 0x33333333u) | ((b << 2) & 0xccccccccu);
+                const uint32_t t = (k & 2 ? n >> 2 : n << 2) & 0x3c3c3c3cu;
+                r.v[j] = lds_read<uint32_t>(add_byte(at, t, k >> 2) + j * 256);
+            } else if constexpr (B == 4) {
+                // every other code, times 2, a byte each
+                const uint32_t t = (k & 1 ? w[j][k >> 3] >> 3 : w[j][k >> 3] << 1) & 0x1e1e1e1eu;
+                r.v[j] = lds_read<uint16_t>(add_byte(at, t, (k & 7) >> 1) + j * 128);
+            } else {
+                r.v[j] = lds_read<uint16_t>(shl1_add(code(j, k), at) + j * 128);
+            }
+        }
+        return r;
+    }
+    static __device__ __forceinline__ Half8 operand(const Raw &r, int k) {
+        Word4 v;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            if constexpr (kPairs) v[d] = r.v[d];
+            else if constexpr (kAct) v[d] = __builtin_amdgcn_perm(r.v[2 * d + 1], r.v[2 * d], k & 1 ? 0x07060302u : 0x05040100u);
+            else v[d] = r.v[2 * d] | (r.v[2 * d + 1] << 16);
+        }
+        return __builtin_bit_cast(Half8, v);
+    }
+
+    __device__ __forceinline__ uint32_t code(int j, int k) const {
+        const int bit = k * B, q = bit >> 5, sh = bit & 31;
+        if (sh + B <= 32) return __builtin_amdgcn_ubfe(w[j][q], sh, B);
+        return __builtin_amdgcn_alignbit(w[j][q + 1 < kWords ? q + 1 : q], w[j][q], sh) & ((1u << B) - 1u);
+    }
+};
+
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Whether all 16 outputs of every lane of a tile lie inside the rows.
+__device__ __forceinline__ bool tile_is_full(const TileArgs &L, int out0) { return out0 + kTileOuts <= L.d_out; }
+
+// ---- few tokens: decode and multiply
+
+__device__ __forceinline__ Float4 mfma(Half8 a, Half8 b, Float4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
+// ND > 0: a workgroup fetches the inputs of its slab's rows, of up to ND tokens, into LDS itself,
+// [token][row], instead of reading operands that tokens_kernel made: a launch less, which is what
+// counts for short products.
+constexpr int kTablesBytes = kWaves * 2 * kTableBytes;
+constexpr int kSlabLds = kWaves * (kOuts / 2) * 4 * CMPQ_WAVE * 4;   // 32 KB: tables and inputs, then sums
+constexpr int direct_steps(int nd) { return ((kSlabLds - kTablesBytes) / (nd * 2) - 8) / kRowsPerStep; }  // most steps of a slab
+
+// The steps a part of a width's slabs covers.
+__device__ __forceinline__ int part_step(const Seg &s, int part) { return s.step0 + (int)((int64_t)s.steps * part / (s.slabs * kWaves)); }
+
+template <int B, int MT, int ND>
+__device__ __forceinline__ void multiply_steps(const TileArgs &L, const Seg &s, int lo, int hi, int out0, int tt,
+                                               unsigned char *tables, const __half *xs, int xs_step0, int xs_rows,
+                                               Float4 (&acc)[MT][kOuts]) {
+    using D = Decoder<B>;
+    const int lane = threadIdx.x & 63;
+    const bool full = tile_is_full(L, out0);
+    const uint32_t at0 = D::tables_at(tables);
+    const uint4 *xf = L.xf + ((int64_t)tt * L.steps) * CMPQ_WAVE + lane;
+    auto load_x = [&](int step, Word4 (&x)[MT]) {
+        if constexpr (ND > 0) {
+            const int token = lane & 15;
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                const Word4 v = *reinterpret_cast<const Word4 *>(xs + ((t * kTok + token) & (ND - 1)) * (xs_rows + 8) +
+                                                                 (step - xs_step0) * kRowsPerStep + (lane >> 4) * 8);
+                x[t] = t * kTok + token < ND ? v : Word4{0u, 0u, 0u, 0u};
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) x[t] = *reinterpret_cast<const Word4 *>(xf + ((int64_t)t * L.steps + step) * CMPQ_WAVE);
+        }
+    };
+    if constexpr (D::kAct) {  // few steps, many words: one at a time
+#pragma unroll 1
+        for (int step = lo; step < hi; ++step) {
+            Word4 x[MT];
+            load_x(step, x);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                D d;
+                d.fetch(L, s, (step - s.step0) * kRowsPerStep, out0, full, h);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const Half8 a = D::operand(d.look_up(k, 0), k);
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) acc[t][8 * h + k] = mfma(a, __builtin_bit_cast(Half8, x[t]), acc[t][8 * h + k]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        return;
+    }
+    D cur, nxt;
+    Word4 x[MT], xn[MT];
+    cur.fetch(L, s, (lo - s.step0) * kRowsPerStep, out0, full);
+    load_x(lo, x);
+    cur.settle(tables);
+    wave_fence();
+    int buf = 0;
+#pragma unroll 1
+    for (int step = lo; step < hi; ++step) {
+        // the last step fetches itself again, which nothing uses
+        const int ahead = step + 1 < hi ? step + 1 : step;
+        nxt.fetch(L, s, (ahead - s.step0) * kRowsPerStep, out0, full);
+        load_x(ahead, xn);
+        const uint32_t at = at0 + buf * kTableBytes;
+        // Look-ups run one operand ahead of the products.  The fences keep the compiler from starting
+        // all of them at once, for which the registers would not do; two ahead costs a wavefront per
+        // SIMD and 10 %.
+        typename D::Raw raw = cur.look_up(0, at), raw_n;
+#pragma unroll
+        for (int k = 0; k < kOuts; ++k) {
+            if (k + 1 < kOuts) raw_n = cur.look_up(k + 1, at);
+            __builtin_amdgcn_sched_barrier(0);
+            const Half8 a = D::operand(raw, k);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) acc[t][k] = mfma(a, __builtin_bit_cast(Half8, x[t]), acc[t][k]);
+            __builtin_amdgcn_sched_barrier(0);
+            raw = raw_n;
+        }
+        buf ^= 1;
+        nxt.settle(tables + buf * kTableBytes);
+        wave_fence();
+        cur = nxt;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) x[t] = xn[t];
+    }
+}
+
+// One slab: 256 outputs x MT * 16 tokens x a share of a width's steps, which 4 wavefronts split.
+// The whole body is instantiated per width: with the widths in one loop, the sums would change
+// registers between them.
+template <int B, int MT, int ND>
+__device__ __forceinline__ void multiply_slab(const TileArgs &L, const Seg &s, int at, int slab, int tile, int tt, int m,
+                                              unsigned char *smem) {
+    const int lane = threadIdx.x & 63, wave = wave_index();
+    const int out0 = tile * kTileOuts;
+    Float4 acc[MT][kOuts];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int k = 0; k < kOuts; ++k) acc[t][k] = Float4{0.f, 0.f, 0.f, 0.f};
+    const int lo = part_step(s, at * kWaves + wave), hi = part_step(s, at * kWaves + wave + 1);
+    __half *xs = reinterpret_cast<__half *>(smem + kTablesBytes);
+    const int first = part_step(s, at * kWaves), rows = (part_step(s, at * kWaves + kWaves) - first) * kRowsPerStep;
+    if constexpr (ND > 0) {
+        const int row0 = (first - s.step0) * kRowsPerStep;
+        for (int r = threadIdx.x; r < rows; r += kThreads) {
+            const bool ok = row0 + r < s.rows;
+            const int chan = ok ? s.chan[row0 + r] : 0;
+            __half v[ND];
+#pragma unroll
+            for (int t = 0; t < ND; ++t) v[t] = ok && t < m ? L.X[(int64_t)t * L.ldx + chan] : __ushort_as_half(0);
+#pragma unroll
+            for (int t = 0; t < ND; ++t) xs[t * (rows + 8) + r] = v[t];
+        }
+        __syncthreads();
+    }
+    if (lo < hi) multiply_steps<B, MT, ND>(L, s, lo, hi, out0, tt, smem + wave * 2 * kTableBytes, xs, first, rows, acc);
+    // The four wavefronts' sums, added in order.  Wavefront w takes the operands 4 w .. 4 w + 3, for a
+    // lane four neighbouring outputs of one token in each of the 4 components; two of them at a time,
+    // so that 32 KB do.
+    Float4 *red = reinterpret_cast<Float4 *>(smem);
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        Float4 y[4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kOuts / 2; ++k)
+                red[(wave * (kOuts / 2) + k) * CMPQ_WAVE + lane] = acc[t][4 * (k >> 1) + 2 * h + (k & 1)];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                Float4 v = red[(2 * wave + k) * CMPQ_WAVE + lane];
+#pragma unroll
+                for (int u = 1; u < kWaves; ++u) v += red[(u * (kOuts / 2) + 2 * wave + k) * CMPQ_WAVE + lane];
+                y[2 * h + k] = v;
+            }
+        }
+        const int token = (tt + t) * kTok + (lane & 15);
+        if (token < m) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int o = out0 + kOuts * (4 * (lane >> 4) + r) + 4 * wave;
+                float *dst = L.partial + ((int64_t)slab * m + token) * L.d_out + o;
+                if (L.d_out % 4 == 0) {
+                    if (o < L.d_out) *reinterpret_cast<float4 *>(dst) = make_float4(y[0][r], y[1][r], y[2][r], y[3][r]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (o + k < L.d_out) dst[k] = y[k][r];
+                }
+            }
+        }
+    }
+}
+
+template <int MT, int ND>
+__global__ __launch_bounds__(kThreads, MT == 1 ? 3 : 2) void lut_tokens_kernel(Group g) {
+    __shared__ __align__(16) unsigned char smem[kSlabLds];
+    int wg;
+    const Layer &L = layer_of(g, wg);
+    wg = xcd_order(wg, L.tiles * L.slabs * (g.token_tiles / MT));
+    const int tile = wg % L.tiles, rest = wg / L.tiles, tt = (rest / L.slabs) * MT;
+    const int slab = rest % L.slabs;
+    int j = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxSegs; ++i) j += slab >= L.slab0[i];
+    const Seg s = L.seg[j];
+    const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out, L.act_vec_ok};
+    const int at = slab - L.slab0[j];
+    switch (s.bits) {
+        case 1: multiply_slab<1, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
+        case 2: multiply_slab<2, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
+        case 3: multiply_slab<3, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
+        case 4: multiply_slab<4, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
+        default: multiply_slab<kActBits, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
+    }
+}
+
+// Slabs and entries of O_q: 16 outputs x NT tokens per workgroup.  16 lanes per column take its
+// entries l, l + 16, ... with all NT tokens of the entry's channel at once; per output and token the
+// slabs are added in eights, each in pairs, then the 16 lanes' sums in lane order.
+constexpr int kFinCols = 16;
+template <int NT, bool DIRECT>
+__global__ __launch_bounds__(kThreads) void tokens_finish_kernel(Group g) {
+    int wg;
+    const Layer &L = layer_of(g, wg);
+    // a column's sums: odd distances between lanes and between columns, so that neither the writes
+    // (one lane per entry) nor the reads (one lane per output) meet in a bank
+    constexpr int kLane = NT + 1, kCol = 16 * kLane + 1;
+    __shared__ float sp[kFinCols * kCol];
+    const int hi = threadIdx.x >> 4, lo = threadIdx.x & 15;
+    const int col_blocks = (L.d_out + kFinCols - 1) / kFinCols;
+    const int tt = wg / col_blocks, o0 = (wg - tt * col_blocks) * kFinCols;
+    const int d_out = L.d_out, slabs = L.slabs, m = g.m;
+    const int32_t *colptr = L.colptr;
+    // the slabs of output o0 + lo, token hi: on their way while the entries of O_q are worked on
+    const int token = tt * kTok + hi, o = o0 + lo;
+    const bool mine = hi < NT && token < m && o < d_out;
+    constexpr int kInFlight = 8;
+    const float *p = L.partial + (int64_t)token * d_out + o;
+    float v[kInFlight];
+#pragma unroll
+    for (int q = 0; q < kInFlight; ++q) v[q] = mine && q < slabs ? p[(int64_t)q * m * d_out] : 0.f;
+    if (colptr) {
+        float t[NT];
+#pragma unroll
+        for (int u = 0; u < NT; ++u) t[u] = 0.f;
+        if (o0 + hi < d_out) {
+            const int e1 = colptr[o0 + hi + 1];
+            const __half *xt = L.xt + (int64_t)tt * L.d_in * kTok, *X = L.X;
+            const int64_t ldx = L.ldx;
+            const int32_t *row_idx = L.row_idx;
+            const float *delta = L.delta;
+            constexpr int U = NT > 4 ? 4 : 8;  // entries in flight
+            for (int e = colptr[o0 + hi] + lo; e < e1; e += 16 * U) {
+                int r[U];
+                float d[U];
+                uint4 x[U][(NT + 7) / 8];
+                __half xd[U][NT];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool ok = e + 16 * u < e1;
+                    r[u] = ok ? row_idx[e + 16 * u] : -1;
+                    d[u] = ok ? delta[e + 16 * u] : 0.f;
+                }
+                if constexpr (DIRECT) {  // straight from X
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int w = 0; w < NT; ++w) xd[u][w] = r[u] >= 0 && tt * kTok + w < m ? X[(int64_t)(tt * kTok + w) * ldx + r[u]] : __ushort_as_half(0);
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int w = 0; w < NT; ++w) t[w] = fmaf(__half2float(xd[u][w]), d[u], t[w]);
+                    continue;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int q = 0; q < (NT + 7) / 8; ++q)
+                        x[u][q] = r[u] >= 0 ? reinterpret_cast<const uint4 *>(xt + (int64_t)r[u] * kTok)[q] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const __half *h = reinterpret_cast<const __half *>(x[u]);
+#pragma unroll
+                    for (int w = 0; w < NT; ++w) t[w] = fmaf(__half2float(h[w]), d[u], t[w]);
+                }
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < NT; ++w) sp[hi * kCol + lo * kLane + w] = t[w];
+        __syncthreads();
+    }
+    if (!mine) return;
+    auto pairwise = [&] { return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])); };
+    static_assert(kInFlight == 8, "");
+    float y = pairwise();
+    for (int s = kInFlight; s < slabs; s += kInFlight) {
+#pragma unroll
+        for (int q = 0; q < kInFlight; ++q) v[q] = s + q < slabs ? p[(int64_t)(s + q) * m * d_out] : 0.f;
+        y += pairwise();
+    }
+    if (colptr) {
+        float z = 0.f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) z += sp[lo * kCol + u * kLane + hi];
+        y += z;
+    }
+    L.Y[(int64_t)token * L.ldy + o] = y;
+}
+
+// ---- many tokens: decode once, then multiply
+
+template <int B>
+__device__ __forceinline__ void decode_step(const TileArgs &L, const Seg &s, Word4 *dense, int step, int out0, unsigned char *tables) {
+    const int lane = threadIdx.x & 63;
+    Word4 *dst = dense + lane;
+    const uint32_t at = Decoder<B>::tables_at(tables);
+    constexpr int kHalves = B == kActBits ? 2 : 1, kOps = kOuts / kHalves;
+#pragma unroll
+    for (int h = 0; h < kHalves; ++h) {
+        Decoder<B> d;
+        d.fetch(L, s, (step - s.step0) * kRowsPerStep, out0, tile_is_full(L, out0), h);
+        d.settle(tables);
+        wave_fence();
+#pragma unroll
+        for (int k = 0; k < kOps; ++k) dst[(h * kOps + k) * CMPQ_WAVE] = __builtin_bit_cast(Word4, Decoder<B>::operand(d.look_up(k, at), k));
+    }
+}
+
+// A wavefront: one step of one tile.
+__global__ __launch_bounds__(kThreads) void lut_decode_kernel(Group g) {
+    __shared__ __align__(16) unsigned char smem[kWaves * kTableBytes];
+    int wg;
+    const Layer &L = layer_of(g, wg);
+    const int wave = wave_index();
+    const int unit = wg * kWaves + wave, tiles = L.tiles;
+    const int step = unit / tiles, tile = unit - step * tiles;
+    if (step >= L.steps) return;
+    unsigned char *tables = smem + wave * kTableBytes;
+    int j = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxSegs; ++i) j += i < L.n_seg && step >= L.seg[i].step0;
+    const Seg s = L.seg[j];
+    const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out, L.act_vec_ok};
+    Word4 *dense = reinterpret_cast<Word4 *>(L.dense) + (int64_t)unit * kOuts * CMPQ_WAVE;
+    switch (s.bits) {
+        case 1: decode_step<1>(a, s, dense, step, tile * kTileOuts, tables); break;
+        case 2: decode_step<2>(a, s, dense, step, tile * kTileOuts, tables); break;
+        case 3: decode_step<3>(a, s, dense, step, tile * kTileOuts, tables); break;
+        case 4: decode_step<4>(a, s, dense, step, tile * kTileOuts, tables); break;
+        default: decode_step<kActBits>(a, s, dense, step, tile * kTileOuts, tables); break;
+    }
+}
+
+// Entries of O_q override their level: W_hat = FP16(level + delta), which is the FP16 weight.
+// A wavefront per column.
+__global__ __launch_bounds__(kThreads) void override_kernel(Group g) {
+    int wg;
+    const Layer &L = layer_of(g, wg);
+    const int lane = threadIdx.x & 63;
+    const int o = wg * kWaves + wave_index();
+    if (!L.colptr || o >= L.d_out) return;
+    const int in = o % kTileOuts, tile = o / kTileOuts, tiles = L.tiles;
+    const uint32_t depth = (uint32_t)L.steps * kRowsPerStep;
+    const int32_t *row_idx = L.row_idx, *pos = L.pos;
+    const float *delta = L.delta;
+    __half *dense = reinterpret_cast<__half *>(L.dense);
+    for (int e = L.colptr[o] + lane, e1 = L.colptr[o + 1]; e < e1; e += CMPQ_WAVE) {
+        const uint32_t k = (uint32_t)pos[row_idx[e]];
+        if (k >= depth) continue;
+        const int row = (int)(k % kRowsPerStep), ln = (row / 8) * 16 + in / kOuts;
+        const int64_t at = ((((int64_t)(k / kRowsPerStep) * tiles + tile) * kOuts + in % kOuts) * CMPQ_WAVE + ln) * 8 + row % 8;
+        dense[at] = __float2half_rn(__half2float(dense[at]) + delta[e]);
+    }
+}
+
+// A workgroup: 128 outputs (operands 8 h .. 8 h + 7 of a tile) x 128 tokens.  Each of the 4
+// wavefronts 4 operands x 4 token tiles.  Operands reach LDS by direct loads in the order in which
+// they are read: 1 KB per operand, lane by lane, no conflicts.  A step's 16 operands are one
+// buffer; kBuffers - 1 steps are on their way while one is multiplied.
+constexpr int kGemmOps = 8;                           // operands of W and of X per step
+constexpr int kBufBytes = 2 * kGemmOps * 1024, kBuffers = 4;
+constexpr int kRun = 4;                               // steps whose sums are kept apart
+
+__device__ __forceinline__ void load_lds16(const uint4 *src, unsigned char *dst) {
+    __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) uint32_t *>(reinterpret_cast<uintptr_t>(src)),
+                                     reinterpret_cast<__attribute__((address_space(3))) uint32_t *>((uint32_t)reinterpret_cast<uintptr_t>(dst)), 16, 0, 0);
+}
+
+__global__ __launch_bounds__(kThreads, 2) void weight_gemm_kernel(Group g) {
+    __shared__ __align__(16) unsigned char smem[kBuffers * kBufBytes];
+    int wg;
+    const Layer &L = layer_of(g, wg);
+    const int lane = threadIdx.x & 63, wave = wave_index();
+    const int token_blocks = (g.token_tiles + kGemmOps - 1) / kGemmOps;
+    const int steps = L.steps, tiles = L.tiles, d_out = L.d_out, m = g.m;
+    float *Y = L.Y;
+    const int64_t ldy = L.ldy;
+    wg = xcd_order(wg, 2 * tiles * token_blocks);
+    const int tb = wg % token_blocks, half = wg / token_blocks;
+    const int tile = half >> 1, op0 = (half & 1) * kGemmOps, tt0 = tb * kGemmOps;
+    // wavefront w brings operands 4 (w % 2) .. + 3 of W (w < 2) or of X
+    const bool weights = wave < 2;
+    const uint4 *src[4];
+    unsigned char *dst = smem + wave * 4096;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int k = 4 * (wave & 1) + q;
+        src[q] = (weights ? L.dense + ((int64_t)tile * kOuts + op0 + k) * CMPQ_WAVE
+                          : L.xf + (int64_t)min(tt0 + k, g.token_tiles - 1) * steps * CMPQ_WAVE) + lane;
+    }
+    const int64_t stride = weights ? (int64_t)tiles * kOuts * CMPQ_WAVE : CMPQ_WAVE;
+    auto load = [&](int step, int buf) {  // past the last step: that one again, which nothing reads
+        const int64_t at = (int64_t)min(step, steps - 1) * stride;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load_lds16(src[q] + at, dst + buf * kBufBytes + q * 1024);
+    };
+    const int wn = (wave & 1) * 4, wt = (wave >> 1) * 4;  // this wavefront's operands of W and token tiles
+    // The matrix cores add one step after the other into fp32; over a whole depth of thousands of
+    // rows that loses more than the short runs of the other kernels (4.5e-7 against 1.4e-7 relative
+    // at 4096 rows), so runs of kRun steps are added up apart, and kRun of those again.
+    Float4 acc[4][4], sum[4][4], total[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = sum[a][b] = total[a][b] = Float4{0.f, 0.f, 0.f, 0.f};
+    auto add_up = [](Float4 (&from)[4][4], Float4 (&to)[4][4]) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                to[p][q] += from[p][q];
+                from[p][q] = Float4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+#pragma unroll
+    for (int u = 0; u < kBuffers - 1; ++u) load(u, u);
+    for (int step = 0; step < steps; ++step) {
+        // the oldest step's 4 loads of this wavefront have landed (two later steps are under way),
+        // after the barrier everyone's have; the buffer read one step ago is free then
+        static_assert(kBuffers == 4, "the count of loads still under way");
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        load(step + kBuffers - 1, (step + kBuffers - 1) % kBuffers);
+        const unsigned char *buf = smem + (step % kBuffers) * kBufBytes + lane * 16;
+        Half8 a[4], b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            a[q] = *reinterpret_cast<const Half8 *>(buf + (wn + q) * 1024);
+            b[q] = *reinterpret_cast<const Half8 *>(buf + (kGemmOps + wt + q) * 1024);
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[p][q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[p], b[q], acc[p][q], 0, 0, 0);
+        if (step % kRun == kRun - 1 || step == steps - 1) {
+            add_up(acc, sum);
+            if (step % (kRun * kRun) == kRun * kRun - 1 || step == steps - 1) add_up(sum, total);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads that nothing reads end before the LDS does
+    // operand p, component r: output 16 (4 (lane / 16) + r) + op0 + wn + p of the tile
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int token = (tt0 + wt + q) * kTok + (lane & 15);
+        if (token >= m) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int o = tile * kTileOuts + kOuts * (4 * (lane >> 4) + r) + op0 + wn;
+            float *dst = Y + (int64_t)token * ldy + o;
+            if (o + 4 <= d_out && (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0) {
+                *reinterpret_cast<float4 *>(dst) = make_float4(total[0][q][r], total[1][q][r], total[2][q][r], total[3][q][r]);
+            } else {
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    if (o + p < d_out) dst[p] = total[p][q][r];
+            }
+        }
+    }
+}
+
+// ---- host
+
+constexpr int kMaxSlabs = 16, kMaxRun = 8;
+constexpr int64_t kDirectWeights = 4 << 20;
+
+int64_t max_steps(int64_t d_in) { return cdiv(d_in, (int64_t)kRowsPerStep) + kMaxSegs; }
+
+// Slabs of a width's steps per tile and token tile: over all widths 384 workgroups (three for every
+// two compute units; 192 to 512 differ by less than 5 %), at least 2 steps per wavefront and at most
+// 8: longer runs of fp32 sums lose more than the token-by-token kernel.  Depends on the layer and m
+// alone, so that a layer gives the same bits in any group.
+void choose_slabs(Layer &L, int64_t token_groups) {
+    int64_t want = cdiv((int64_t)384, L.tiles * token_groups);
+    if (want > kMaxSlabs) want = kMaxSlabs;
+    L.slabs = 0;
+    for (int j = 0; j < L.n_seg; ++j) {
+        Seg &s = L.seg[j];
+        int64_t n = (want * s.steps + L.steps / 2) / L.steps;
+        if (n > s.steps / (2 * kWaves)) n = s.steps / (2 * kWaves);
+        const int64_t least = cdiv(s.steps, (int64_t)kMaxRun * kWaves);
+        if (n < least) n = least;
+        L.slab0[j] = L.slabs;
+        s.slabs = (int)n;
+        L.slabs += s.slabs;
+    }
+    for (int j = L.n_seg; j < kMaxSegs; ++j) L.slab0[j] = INT_MAX;
+}
+
+// At least what choose_slabs gives.
+int64_t most_slabs(int64_t d_in) { return kMaxSlabs + 2 * kMaxSegs + cdiv(max_steps(d_in), (int64_t)kMaxRun * kWaves); }
+
+// Whether to decode the weight once into memory and multiply from there.  That costs 4 bytes of
+// traffic per weight and two launches, multiplying while decoding costs a decoding per 32 tokens;
+// measured (us, decode once | while decoding): 4096x4096, 256 tokens 74 | 66; 13824x5120 twice,
+// 96 tokens 169 | 152, each 32 tokens more 4 | 39.  Every channel has to have a row, so that an
+// entry of O_q always finds the weight it overrides.
+bool many_tokens(const cmpq_deployed_layer &L, int64_t m) {
+    int64_t rows = L.k_act;
+    for (int j = 0; j < L.n_set; ++j) rows += L.counts_host[j];
+    return m >= 96 && rows > 0 && rows == L.d_in && m * L.d_in >= ((int64_t)8 << 30) / L.d_out;
+}
+
+size_t piece(size_t bytes) { return align_up(bytes, 256); }
+
+}  // namespace
+
+// Up to 8 tokens the two ways cost the same where a product is all latency (2048x2048, 6 tokens:
+// 14.7 | 15.0 us here | token by token) and this one wins as soon as it is not (13824x5120 twice, 2
+// tokens: 39 | 56; 4099x3001, 5 tokens: 20 | 41).  More tokens need more registers and longer
+// kernels, which pays from some 24 million weight-token products on (900x700, 16 tokens: 20 | 16;
+// 2048x2048, 16 tokens: 20.0 | 21.1; 513x3001, 16 tokens: 22 | 29).
+bool lut_gemm_takes(int64_t d_in, int64_t d_out, int64_t m) {
+    return m >= 2 && (m <= 8 || m * d_in >= ((int64_t)24 << 20) / d_out);
+}
+
+size_t lut_gemm_ws_bytes(int64_t d_in, int64_t d_out, int64_t m) {
+    const int64_t tt = align_up((size_t)cdiv(m, (int64_t)kTok), 2), steps = max_steps(d_in), tiles = cdiv(d_out, (int64_t)kTileOuts);
+    size_t b = piece((size_t)tt * steps * 1024) + piece((size_t)tt * d_in * kTok * 2) + piece((size_t)d_in * 4);
+    const size_t part = piece((size_t)most_slabs(d_in) * m * d_out * 4);
+    const size_t dense = piece((size_t)steps * tiles * kOuts * 1024);
+    return b + (part > dense ? part : dense);
+}
+
+int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int64_t m, void *ws, hipStream_t s) {
+    Group few, many;
+    few.n_layers = many.n_layers = 0;
+    const int MT = m > kTok ? 2 : 1;
+    const int64_t tts = align_up((size_t)cdiv(m, (int64_t)kTok), MT);
+    char *base = static_cast<char *>(ws);
+    for (int i = 0; i < n_layers; ++i) {
+        const cmpq_deployed_layer &S = *layers[i];
+        const bool dense = many_tokens(S, m);
+        Group &G = dense ? many : few;
+        Layer &L = G.l[G.n_layers++];
+        L = Layer{};
+        int64_t steps = 0;
+        auto add = [&](const uint32_t *packed, const uint16_t *lut, const int32_t *chan, int64_t rows, int bits) {
+            if (rows <= 0) return;
+            Seg &g = L.seg[L.n_seg++];
+            g.packed = packed;
+            g.lut = lut;
+            g.chan = chan;
+            g.rows = (int)rows;
+            g.words_per_row = bits == kActBits ? 0 : (int)cdiv(S.d_out * bits, 32);
+            g.bits = bits;
+            g.step0 = (int)steps;
+            g.steps = (int)cdiv(rows, (int64_t)kRowsPerStep);
+            steps += g.steps;
+        };
+        for (int j = 0; j < S.n_set; ++j) add(S.packed[j], S.lut[j], S.chan_idx[j], S.counts_host[j], S.bit_set[j]);
+        add(nullptr, nullptr, S.act_idx, S.k_act, kActBits);
+        L.X = static_cast<const __half *>(S.X);
+        L.ldx = S.ldx;
+        L.W_act = reinterpret_cast<const __half *>(S.W_act);
+        L.ld_act = S.ld_act;
+        L.act_vec_ok = reinterpret_cast<uintptr_t>(S.W_act) % 16 == 0 && S.ld_act % 8 == 0;
+        L.colptr = S.colptr;
+        L.row_idx = S.row_idx;
+        L.delta = S.delta;
+        L.Y = S.Y;
+        L.ldy = S.ldy;
+        L.d_in = (int)S.d_in;
+        L.d_out = (int)S.d_out;
+        L.steps = (int)steps;
+        L.tiles = (int)cdiv(S.d_out, (int64_t)kTileOuts);
+        size_t used = 0;
+        auto take = [&](size_t bytes) {
+            char *p = base + used;
+            used += piece(bytes);
+            return p;
+        };
+        L.xf = reinterpret_cast<uint4 *>(take((size_t)tts * steps * 1024));
+        if (dense) {
+            if (S.colptr) L.pos = reinterpret_cast<int32_t *>(take((size_t)S.d_in * 4));
+            L.dense = reinterpret_cast<uint4 *>(take((size_t)steps * L.tiles * kOuts * 1024));
+        } else {
+            if (S.colptr) L.xt = reinterpret_cast<__half *>(take((size_t)tts * S.d_in * kTok * 2));
+            choose_slabs(L, tts / MT);
+            L.partial = reinterpret_cast<float *>(take((size_t)L.slabs * m * S.d_out * 4));
+        }
+        base += lut_gemm_ws_bytes(S.d_in, S.d_out, m);
+    }
+    for (Group *G : {&few, &many}) {
+        if (G->n_layers == 0) continue;
+        const int n = G->n_layers;
+        G->m = (int)m;
+        G->token_tiles = (int)(G == &few ? tts : cdiv(m, (int64_t)kTok));
+        auto number = [&](auto &&count) {
+            int64_t w = 0;
+            for (int i = 0; i < kMaxLayers; ++i) G->wg0[i] = INT_MAX;
+            for (int i = 0; i < n; ++i) {
+                G->wg0[i] = (int)w;
+                w += count(G->l[i]);
+            }
+            return (unsigned)w;
+        };
+        const unsigned wx = number([&](const Layer &L) {
+            return G->token_tiles * (cdiv(L.steps, 8) + (L.xt ? cdiv(L.d_in, (int64_t)kThreads) : 0)); });
+        // Inputs straight from X where a launch less is worth more than the scattered reads: up to 4
+        // tokens always (13824x5120 twice, 4 tokens: 41 against 45 us), up to 32 in small layers
+        // (900x700, 6 tokens: 17 against 20 us).  Either way the same numbers in the same order.
+        const int nd = m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32));
+        bool direct = G == &few && m <= 32;
+        for (int i = 0; direct && i < n; ++i) {
+            if (nd > 4 && (int64_t)G->l[i].d_in * G->l[i].d_out > kDirectWeights) direct = false;
+            for (int j = 0; j < G->l[i].n_seg; ++j)
+                if (cdiv(G->l[i].seg[j].steps, G->l[i].seg[j].slabs) >= direct_steps(nd)) direct = false;
+        }
+        if (wx && !direct) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
+        if (G == &few) {
+            const unsigned w = number([&](const Layer &L) { return (int64_t)L.tiles * L.slabs * (tts / MT); });
+            if (w > 0) {
+                const int d = direct ? nd : 0;
+                if (d == 4) lut_tokens_kernel<1, 4><<<w, kThreads, 0, s>>>(*G);
+                else if (d == 8) lut_tokens_kernel<1, 8><<<w, kThreads, 0, s>>>(*G);
+                else if (d == 16) lut_tokens_kernel<1, 16><<<w, kThreads, 0, s>>>(*G);
+                else if (d == 32) lut_tokens_kernel<2, 32><<<w, kThreads, 0, s>>>(*G);
+                else if (MT == 1) lut_tokens_kernel<1, 0><<<w, kThreads, 0, s>>>(*G);
+                else lut_tokens_kernel<2, 0><<<w, kThreads, 0, s>>>(*G);
+            }
+            const unsigned f = number([&](const Layer &L) { return cdiv(L.d_out, (int64_t)kFinCols) * tts; });
+            if (direct && nd == 4) tokens_finish_kernel<4, true><<<f, kThreads, 0, s>>>(*G);
+            else if (direct && nd == 8) tokens_finish_kernel<8, true><<<f, kThreads, 0, s>>>(*G);
+            else if (direct) tokens_finish_kernel<16, true><<<f, kThreads, 0, s>>>(*G);
+            else if (m <= 8) tokens_finish_kernel<8, false><<<f, kThreads, 0, s>>>(*G);
+            else tokens_finish_kernel<16, false><<<f, kThreads, 0, s>>>(*G);
+        } else {
+            const unsigned w = number([&](const Layer &L) { return cdiv((int64_t)L.steps * L.tiles, (int64_t)kWaves); });
+            lut_decode_kernel<<<w, kThreads, 0, s>>>(*G);
+            bool any = false;
+            for (int i = 0; i < n; ++i) any = any || G->l[i].colptr;
+            if (any) {
+                const unsigned o = number([&](const Layer &L) { return L.colptr ? cdiv(L.d_out, (int64_t)kWaves) : 0; });
+                override_kernel<<<o, kThreads, 0, s>>>(*G);
+            }
+            const int64_t tb = cdiv((int64_t)G->token_tiles, (int64_t)kGemmOps);
+            const unsigned q = number([&](const Layer &L) { return 2 * L.tiles * tb; });
+            weight_gemm_kernel<<<q, kThreads, 0, s>>>(*G);
+        }
+    }
+    CMPQ_LAUNCH_CHECK();
+    return CMPQ_OK;
+}

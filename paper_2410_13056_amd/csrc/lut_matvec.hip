@@ -4,6 +4,9 @@
 //
 //   Y[t,o] = sum_i X[t,i] * W_hat[i,o]
 //
+// This file multiplies one token at a time; several tokens go to the matrix cores
+// (lut_gemm.hip) wherever that is faster.
+//
 // The packed rows are input channels, so a row contributes X[t,i] * lut_i[code] to every
 // output: the 2^b products X[t,i] * lut_i[c] are formed once per row and the rest is table
 // look-ups and additions.  HBM bound: b/8 bytes per weight are read once per token.
@@ -25,6 +28,7 @@
 //   * cmpq_outliers_by_column / cmpq_gather_channels prepare O_q and O_act for this once,
 //     at quantization time.
 #include "common.h"
+#include "lut_gemm.h"
 
 namespace {
 
@@ -800,7 +804,9 @@ size_t cmpq_ws_outliers_by_column(int64_t d_out, int64_t n_out) {
 // filled slab.
 size_t cmpq_ws_lut_matvec(int64_t d_in, int64_t d_out, int64_t m) {
     const int64_t slabs = cdiv(d_in, (int64_t)kWaves * 8) + kMaxWidths + 2;  // the smallest slabs
-    return align_up((size_t)m * (size_t)slabs * (size_t)d_out * sizeof(float), 256);
+    const size_t one_by_one = align_up((size_t)m * (size_t)slabs * (size_t)d_out * sizeof(float), 256);
+    const size_t together = lut_gemm_ws_bytes(d_in, d_out, m);
+    return one_by_one > together ? one_by_one : together;
 }
 
 extern "C" int cmpq_gather_channels(const void *W, int dtype, int64_t d_in, int64_t d_out, int64_t ldw,
@@ -879,34 +885,22 @@ int check_layer(const cmpq_deployed_layer &L, int64_t m) {
     return CMPQ_OK;
 }
 
-int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, void *ws, size_t ws_bytes,
-                 void *stream, bool half_sums = false) {
-    if (n_layers < 0 || n_layers > kMaxLayers || m < 0 || (n_layers > 0 && !layers)) return CMPQ_EINVAL;
-    for (int i = 0; i < n_layers; ++i) {
-        const int rc = check_layer(layers[i], m);
-        if (rc != CMPQ_OK) return rc;
-    }
-    if (m > 65535) return CMPQ_ESHAPE;
-    if (m == 0) return CMPQ_OK;
-    // the longest products first: their workgroups are dispatched first
-    int order[kMaxLayers], n_live = 0;
-    for (int i = 0; i < n_layers; ++i)
-        if (layers[i].d_out > 0) order[n_live++] = i;
-    for (int i = 1; i < n_live; ++i)
-        for (int j = i; j > 0; --j) {
-            const cmpq_deployed_layer &p = layers[order[j - 1]], &q = layers[order[j]];
-            if (p.d_in * p.d_out >= q.d_in * q.d_out) break;
-            const int t = order[j];
-            order[j] = order[j - 1];
-            order[j - 1] = t;
-        }
-    if (n_live == 0) return CMPQ_OK;
+// The token-by-token launch of the layers order[0..n): arguments of its two kernels, grid and
+// scratch.
+struct Plan {
     LmGroup g;
     FinGroup f;
-    g.n_layers = f.n_layers = n_live;
-    size_t ws_used = 0;
-    int64_t y_total = 0, x_total = 0, max_tiles = 0;
-    for (int s = 0; s < n_live; ++s) {
+    size_t ws_used;
+    int64_t y_total, x_total, max_tiles;
+};
+
+void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, int n, int64_t m, void *ws, Plan &p) {
+    LmGroup &g = p.g;
+    FinGroup &f = p.f;
+    g.n_layers = f.n_layers = n;
+    p.ws_used = 0;
+    p.y_total = p.x_total = p.max_tiles = 0;
+    for (int s = 0; s < n; ++s) {
         const cmpq_deployed_layer &L = layers[order[s]];
         LmArgs &a = g.l[s];
         // rows per wavefront: the largest of 32, 16, 8 that still gives two workgroups per compute unit
@@ -922,11 +916,11 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
         a.n_act_slabs = (int)n_act;
         a.n_rows_total = (int)n_rows;
         a.tiles = (int)tiles;
-        a.y0 = (int)y_total;
+        a.y0 = (int)p.y_total;
         a.X = static_cast<const __half *>(L.X);
         a.ldx = L.ldx;
         a.d_out = L.d_out;
-        a.partial = reinterpret_cast<float *>(static_cast<char *>(ws) + ws_used);
+        a.partial = reinterpret_cast<float *>(static_cast<char *>(ws) + p.ws_used);
         a.act_idx = L.act_idx;
         a.W_act = reinterpret_cast<const __half *>(L.W_act);
         a.k_act = L.k_act;
@@ -957,27 +951,76 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
         fa.Y = L.Y;
         fa.ldy = L.ldy;
         fa.n_rows_total = (int)n_rows;
-        fa.x0 = (int)x_total;
-        ws_used += align_up((size_t)m * (size_t)n_rows * (size_t)L.d_out * sizeof(float), 256);
-        y_total += n_rows;
-        x_total += cdiv(L.d_out, kFinCols);
-        if (tiles > max_tiles) max_tiles = tiles;
+        fa.x0 = (int)p.x_total;
+        p.ws_used += align_up((size_t)m * (size_t)n_rows * (size_t)L.d_out * sizeof(float), 256);
+        p.y_total += n_rows;
+        p.x_total += cdiv(L.d_out, kFinCols);
+        if (tiles > p.max_tiles) p.max_tiles = tiles;
     }
-    for (int s = n_live; s < kMaxLayers; ++s) {
+    for (int s = n; s < kMaxLayers; ++s) {
         g.l[s] = g.l[0];
         f.l[s] = f.l[0];
     }
-    if (y_total > 65535 || x_total > 0x7fffffff) return CMPQ_ESHAPE;
-    if (ws_used > 0 && (!ws || reinterpret_cast<uintptr_t>(ws) % 256 != 0 || ws_bytes < ws_used))
+}
+
+int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, void *ws, size_t ws_bytes,
+                 void *stream, bool half_sums = false) {
+    if (n_layers < 0 || n_layers > kMaxLayers || m < 0 || (n_layers > 0 && !layers)) return CMPQ_EINVAL;
+    for (int i = 0; i < n_layers; ++i) {
+        const int rc = check_layer(layers[i], m);
+        if (rc != CMPQ_OK) return rc;
+    }
+    if (m > 65535) return CMPQ_ESHAPE;
+    if (m == 0) return CMPQ_OK;
+    // the longest products first: their workgroups are dispatched first
+    int order[kMaxLayers], n_live = 0;
+    for (int i = 0; i < n_layers; ++i)
+        if (layers[i].d_out > 0) order[n_live++] = i;
+    for (int i = 1; i < n_live; ++i)
+        for (int j = i; j > 0; --j) {
+            const cmpq_deployed_layer &p = layers[order[j - 1]], &q = layers[order[j]];
+            if (p.d_in * p.d_out >= q.d_in * q.d_out) break;
+            const int t = order[j];
+            order[j] = order[j - 1];
+            order[j - 1] = t;
+        }
+    if (n_live == 0) return CMPQ_OK;
+    Plan p;
+    plan_token_by_token(layers, order, n_live, m, ws, p);
+    if (p.y_total > 65535 || p.x_total > 0x7fffffff) return CMPQ_ESHAPE;
+    if (p.ws_used > 0 && (!ws || reinterpret_cast<uintptr_t>(ws) % 256 != 0 || ws_bytes < p.ws_used))
         return CMPQ_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (y_total > 0) {
-        const dim3 grid((unsigned)max_tiles, (unsigned)y_total, (unsigned)m);
-        if (half_sums) lut_matvec_half_kernel<<<grid, kThreads, 0, st>>>(g);
-        else lut_matvec_kernel<<<grid, kThreads, 0, st>>>(g);
+    // Layers that the matrix cores take (several tokens) go first, the others token by token.  With a
+    // workspace that holds the token-by-token launch but not this one (less than
+    // cmpq_workspace_bytes asks for), all go token by token.
+    if (m > 1 && !half_sums) {
+        const cmpq_deployed_layer *taken[kMaxLayers];
+        int n_taken = 0, rest[kMaxLayers], n_rest = 0;
+        size_t need = 0;
+        for (int i = 0; i < n_live; ++i) {
+            const cmpq_deployed_layer &L = layers[order[i]];
+            if (lut_gemm_takes(L.d_in, L.d_out, m)) {
+                taken[n_taken++] = &L;
+                need += lut_gemm_ws_bytes(L.d_in, L.d_out, m);
+            } else {
+                rest[n_rest++] = order[i];
+            }
+        }
+        if (n_taken > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= need) {
+            const int rc = launch_lut_gemm(taken, n_taken, m, ws, st);
+            if (rc != CMPQ_OK || n_rest == 0) return rc;
+            // launches on one stream run in order: the rest uses the same workspace
+            plan_token_by_token(layers, rest, n_rest, m, ws, p);
+        }
     }
-    const dim3 fgrid((unsigned)x_total, (unsigned)m);
-    lut_matvec_finish_kernel<<<fgrid, kThreads, 0, st>>>(f);
+    if (p.y_total > 0) {
+        const dim3 grid((unsigned)p.max_tiles, (unsigned)p.y_total, (unsigned)m);
+        if (half_sums) lut_matvec_half_kernel<<<grid, kThreads, 0, st>>>(p.g);
+        else lut_matvec_kernel<<<grid, kThreads, 0, st>>>(p.g);
+    }
+    const dim3 fgrid((unsigned)p.x_total, (unsigned)m);
+    lut_matvec_finish_kernel<<<fgrid, kThreads, 0, st>>>(p.f);
     CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
 }
