@@ -231,8 +231,8 @@ int cmpq_extract_outliers(int mode, int score, int scope, const float *sumsq, co
  *   centroids   [d_in, 16] fp32 out (in/out with CMPQ_INIT_GIVEN): K levels, then +infinity;
  *               all +infinity for a channel with bits outside 1..4.
  *   codes       [d_in, d_out] uint8 out (0 for such a channel).  May be null for inputs the
- *               histogram kernel takes (fp16, unit importance, rows of whole groups of 4
- *               entries, 8-byte aligned): the call then leaves the levels alone and skips the
+ *               histogram kernel takes as aligned groups (fp16, unit importance, rows of whole groups of
+ *               4 entries, 8-byte aligned): the call then leaves the levels alone and skips the
  *               last assignment, which is all the preliminary quantization of Sec. 3.2.2
  *               needs when cmpq_extract_outliers is given no codes.  Null otherwise: CMPQ_EINVAL.
  * Assignment: the nearest level in exact arithmetic, equal distances to the smaller level
@@ -279,9 +279,11 @@ int cmpq_select_by_width(const uint8_t *bits, int64_t d_in, int64_t d_out, const
  *               unit importance.  Both give identical levels and codes: CMPQ_KMEANS_HISTOGRAM
  *               reads cumulative tables of the channel, CMPQ_KMEANS_DIRECT revisits every
  *               weight (K-1 compares, 2 accumulations; kept as the independent second
- *               implementation).  Other inputs (fp32, elem_weight, rows that are not a whole
- *               number of 4 entries) run on the general kernel whatever is named here, and so
- *               does init = CMPQ_INIT_GIVEN with CMPQ_KMEANS_DIRECT (on the histogram kernel).
+ *               implementation).  fp32 weights and elem_weight run on the general kernel
+ *               whatever is named here; rows that are not a whole number of 4 entries, or not
+ *               8-byte aligned, run on the histogram kernel with CMPQ_KMEANS_HISTOGRAM and on the
+ *               general one with CMPQ_KMEANS_DIRECT; init = CMPQ_INIT_GIVEN with
+ *               CMPQ_KMEANS_DIRECT runs on the histogram kernel where rows are aligned groups of 4.
  *   bit_set ... err_total   (all null / 0: not asked for.)  Sec. 3.2.2's final quantization is
  *               followed by the stored format (Sec. 5.1) and the error (App. B.3) of the very
  *               codes it produces; with these fields set, the call leaves what

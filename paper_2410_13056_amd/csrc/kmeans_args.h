@@ -24,6 +24,9 @@ struct KmArgs {
     // App. B.3) instead of by a pass of their own: where the rows go, the row of each channel
     // inside its width group, and the per-channel squared error.  Unused unless `fused`.
     int fused;
+    // Rows of no whole number of groups of 4 weights, or not on 8 bytes (bucket kernel; no kept
+    // arrangement then, and `codes` must be given).
+    int ragged;
     PackPtrs pack;
     const int32_t *row_of;
     double *err_ch;

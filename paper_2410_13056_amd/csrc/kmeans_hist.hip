@@ -46,6 +46,41 @@ __host__ __device__ inline size_t bucket_arr_bytes(int64_t d_out, int lb) {
     return ((size_t)(d_out + pad) + 15) & ~(size_t)15;
 }
 
+// RAGGED: rows that are no whole number of groups of 4 weights, or do not start on 8 bytes.  A
+// group is then fetched and its codes are stored at any alignment; the last one may hold 1 to 3
+// weights, and what fills it up is marked as removed.
+template <bool RAGGED>
+__device__ __forceinline__ uint2 load_group(const __half *row, int g, int n_groups, int d_out) {
+    uint2 v = make_uint2(0, 0);
+    if (g >= n_groups) return v;
+    if constexpr (!RAGGED) return reinterpret_cast<const uint2 *>(row)[g];
+    const __half *p = row + 4 * (int64_t)g;
+    const int n = d_out - 4 * g;
+    if (n >= 4) {
+        __builtin_memcpy(&v, p, 8);
+    } else {
+        v.x = __half_as_ushort(p[0]);
+        if (n > 1) v.x |= (uint32_t)__half_as_ushort(p[1]) << 16;
+        if (n > 2) v.y = __half_as_ushort(p[2]);
+    }
+    return v;
+}
+template <bool RAGGED>
+__device__ __forceinline__ void store_codes(uint8_t *row, int g, int d_out, uint32_t word) {
+    if constexpr (!RAGGED) {
+        reinterpret_cast<uint32_t *>(row)[g] = word;
+    } else {
+        const int n = d_out - 4 * g;
+        if (n >= 4) __builtin_memcpy(row + 4 * (int64_t)g, &word, 4);
+        else for (int e = 0; e < n; ++e) row[4 * (int64_t)g + e] = (uint8_t)(word >> (8 * e));
+    }
+}
+template <bool RAGGED, int T>
+__device__ __forceinline__ void zero_codes(uint8_t *row, int n_groups, int d_out) {
+    if (!row) return;
+    for (int g = threadIdx.x; g < n_groups; g += T) store_codes<RAGGED>(row, g, d_out, 0);
+}
+
 template <int LB>
 struct BucketShared {
     static constexpr int kBuckets = 1 << (16 - LB);
@@ -218,7 +253,7 @@ __device__ __forceinline__ uint32_t code_from_entry(uint32_t ent, uint32_t kk, i
 // channel's row of the bit stream, which is built in the place array the rounds no longer need.
 // A rolled loop: its fp64 temporaries would not fit the register budget of the unrolled one.
 // Returns the lane's share of the error.  Contains a barrier: called by all threads.
-template <int G, int K, int T, int LB>
+template <int G, int K, int T, int LB, bool RAGGED>
 __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, BucketShared<LB> &sm,
                                                     unsigned char *arr, uint32_t *tbl, const uint32_t *removed,
                                                     int n_ex, int n_groups, int par) {
@@ -240,8 +275,9 @@ __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, 
     if constexpr (kTable) multi = build_code_table<K, T, LB>(thr, sm.code_of, sm.tk[par], tbl);
     const bool any_multi = __syncthreads_or(multi) != 0;  // also the barrier before the groups below
     const uint32_t tbl_at = lds_address(tbl);
-    const uint2 *wrow = reinterpret_cast<const uint2 *>(static_cast<const __half *>(a.W) + i * a.ldw);
-    uint32_t *crow = a.codes ? reinterpret_cast<uint32_t *>(a.codes + i * a.d_out) : nullptr;
+    const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
+    const int d_out = (int)a.d_out;
+    uint8_t *crow = a.codes ? a.codes + i * a.d_out : nullptr;
     double err = 0.0;
     const int n_steps = (n_groups + T - 1) / T;  // the same for every lane: the neighbour exchange below needs all of them
     // the weights of the next few groups are fetched while the current ones are worked on: this
@@ -254,8 +290,7 @@ __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, 
     uint2 nxt[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-        const int g = u * T + tid;
-        nxt[u] = g < n_groups ? wrow[g] : make_uint2(0, 0);
+        nxt[u] = load_group<RAGGED>(wrow, u * T + tid, n_groups, d_out);
     }
 #pragma unroll 1
     for (int step0 = 0; step0 < n_steps; step0 += kAhead) {
@@ -263,8 +298,7 @@ __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, 
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             chunk[u] = nxt[u];
-            const int gn = (step0 + kAhead + u) * T + tid;
-            nxt[u] = gn < n_groups ? wrow[gn] : make_uint2(0, 0);
+            nxt[u] = load_group<RAGGED>(wrow, (step0 + kAhead + u) * T + tid, n_groups, d_out);
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
@@ -285,12 +319,13 @@ __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, 
                     code[e] = sm.code_of[cell_of<K>((kk[e >> 1] >> (16 * (e & 1))) & 0xffffu, thr)];
                 }
             }
-            const uint32_t word = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);  // one code per byte
-            if (in && crow) crow[g] = word;
+            uint32_t word = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);  // one code per byte
+            if (RAGGED && d_out - 4 * g < 4) word &= (1u << (8 * (d_out & 3))) - 1u;  // the stream ends in zeros
+            if (in && crow) store_codes<RAGGED>(crow, g, d_out, word);
             // (w - level)^2 of the four entries; an entry of O_q (restored to its FP16 weight) and a
             // lane past the end add an exact zero: their difference is masked bit by bit
             uint32_t kept = in ? 0xfu : 0u;
-            if (n_ex > 0 && in) kept = ~(removed[g >> 3] >> ((g & 7) * 4)) & 0xfu;
+            if ((RAGGED || n_ex > 0) && in) kept = ~(removed[g >> 3] >> ((g & 7) * 4)) & 0xfu;
             const uint32_t hw[2] = {cur.x, cur.y};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -331,7 +366,7 @@ __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, 
     return err;
 }
 
-template <int G, int K, int T, int LB, bool FUSED>
+template <int G, int K, int T, int LB, bool FUSED, bool RAGGED>
 __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketShared<LB> &sm,
                                              unsigned char *arr, uint32_t *tbl, const uint32_t *removed, int n_ex,
                                              const uint32_t (&keys)[2 * G], int n_groups, uint32_t M,
@@ -512,7 +547,7 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
 
     __builtin_amdgcn_s_setprio(0);
     if constexpr (FUSED) {
-        err_out = coding_pass_fused<G, K, T, LB>(a, i, sm, arr, tbl, removed, n_ex, n_groups, par);
+        err_out = coding_pass_fused<G, K, T, LB, RAGGED>(a, i, sm, arr, tbl, removed, n_ex, n_groups, par);
         return;
     }
     if (!a.codes) {  // the caller wants the levels alone
@@ -526,18 +561,17 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
     uint32_t thr[CMPQ_KMAX];
 #pragma unroll
     for (int p = 0; p < K - 1; ++p) thr[p] = (uint32_t)__builtin_amdgcn_readlane((int)tk_fin, p);
-    uint32_t *crow = reinterpret_cast<uint32_t *>(a.codes + i * a.d_out);
+    uint8_t *crow = a.codes + i * a.d_out;
+    const int d_out = (int)a.d_out;
     // Workgroups of 512 lanes fetch their weights again here (from cache) instead of holding
     // them in registers through the rounds: a third workgroup then fits a compute unit.
     constexpr bool kReload = T >= 512;
     uint32_t again[2 * G];
     if constexpr (kReload) {
-        const uint2 *wrow = reinterpret_cast<const uint2 *>(static_cast<const __half *>(a.W) + i * a.ldw);
+        const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            const int g = k * T + tid;
-            uint2 raw = make_uint2(0, 0);
-            if (g < n_groups) raw = wrow[g];
+            const uint2 raw = load_group<RAGGED>(wrow, k * T + tid, n_groups, d_out);
             again[2 * k] = keys_of_half2(raw.x);
             again[2 * k + 1] = keys_of_half2(raw.y);
         }
@@ -565,7 +599,7 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
                     const uint32_t kk = pair_at(k, e);
                     word |= code_from_entry(table_entry<LB>(tbl_at, kk, e & 1), kk, e & 1) << (8 * e);
                 }
-                if (g < n_groups) crow[g] = word;
+                if (g < n_groups) store_codes<RAGGED>(crow, g, d_out, word);
             }
         } else {
 #pragma unroll
@@ -580,7 +614,7 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
                     if (ent & kTblMulti) code = sm.code_of[cell_of<K>(key_at(k, e), thr)];
                     word |= code << (8 * e);
                 }
-                if (g < n_groups) crow[g] = word;
+                if (g < n_groups) store_codes<RAGGED>(crow, g, d_out, word);
             }
         }
     } else {
@@ -595,7 +629,7 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
                 if (!ident) pos = (uint32_t)__shfl(own_fin, (int)pos, CMPQ_WAVE);
                 word |= pos << (8 * e);
             }
-            if (g < n_groups) crow[g] = word;
+            if (g < n_groups) store_codes<RAGGED>(crow, g, d_out, word);
         }
     }
     __syncthreads();
@@ -665,12 +699,14 @@ __device__ __forceinline__ void blank_one_place(uint32_t *words, uint32_t w0, ui
 // variant keeps the occupancy it has always run at, 7 wavefronts per SIMD (72 registers; 7
 // workgroups of 256 lanes per compute unit).  Measured against budgets of 77 / 72 registers: the
 // kernel alone 3-4 % shorter, the whole step with three streams 5 %.
-constexpr int waves_per_simd(int G, int T, int MODE) {
-    return G == 16 && T == 512 && MODE != kModeFused ? 8 : 7;
+// Rows of any length and alignment need a few registers more: 5 there for the longest channels, so
+// that nothing spills.
+constexpr int waves_per_simd(int G, int T, int MODE, bool RAGGED) {
+    return G == 16 && T == 512 ? (RAGGED ? 5 : (MODE != kModeFused ? 8 : 7)) : 7;
 }
-template <int G, int T, int LB, int MODE>
+template <int G, int T, int LB, int MODE, bool RAGGED>
 __global__ __launch_bounds__(T)
-    __attribute__((amdgpu_waves_per_eu(waves_per_simd(G, T, MODE), waves_per_simd(G, T, MODE))))
+    __attribute__((amdgpu_waves_per_eu(waves_per_simd(G, T, MODE, RAGGED), waves_per_simd(G, T, MODE, RAGGED))))
 void kmeans_bucket_kernel(KmArgs a) {
     constexpr int kBuckets = 1 << (16 - LB);
     constexpr bool kCodesFused = MODE != kModePlain;
@@ -681,15 +717,12 @@ void kmeans_bucket_kernel(KmArgs a) {
     __shared__ BucketShared<LB> sm;
     const int64_t i = blockIdx.x;
     const int tid = threadIdx.x;
-    const int d_out = (int)a.d_out, n_groups = d_out >> 2;
+    const int d_out = (int)a.d_out, n_groups = RAGGED ? (d_out + 3) >> 2 : d_out >> 2;
     const int b = a.bits[i];
     float *crow = a.centroids + i * CMPQ_KMAX;
     if (b < 1 || b > 4) {  // a channel of O_act: no levels, no codes, no row; kept whole in FP16: no error
         if (tid < CMPQ_KMAX) crow[tid] = INFINITY;
-        if (a.codes) {
-            uint32_t *c32 = reinterpret_cast<uint32_t *>(a.codes + i * a.d_out);
-            for (int g = tid; g < n_groups; g += T) c32[g] = 0;
-        }
+        zero_codes<RAGGED, T>(a.codes ? a.codes + i * a.d_out : nullptr, n_groups, d_out);
         if (kCodesFused && a.err_ch && tid == 0) a.err_ch[i] = 0.0;
         return;
     }
@@ -713,7 +746,6 @@ void kmeans_bucket_kernel(KmArgs a) {
     const int n_words = (d_out + 31) >> 5;
     uint32_t *cursor = removed + ((n_words + 3) & ~3);
     const __half *wrow_h = static_cast<const __half *>(a.W) + i * a.ldw;
-    const uint2 *wrow = reinterpret_cast<const uint2 *>(wrow_h);
     // the arrangement this run leaves (any mode but reuse) or starts from (reuse)
     unsigned char *keep = nullptr;
     if (MODE != kModeReuse && a.arr_keep) keep = static_cast<unsigned char *>(a.arr_keep) + i * a.arr_stride;
@@ -729,7 +761,8 @@ void kmeans_bucket_kernel(KmArgs a) {
         const int64_t lo = a.seg ? a.seg[i + 1] : 0;
         sm.n_excl = (int)lo - sm.seg_lo;
     }
-    for (int s = tid; s < n_words; s += T) removed[s] = 0;
+    for (int s = tid; s < n_words; s += T)  // what fills up the last group counts as removed
+        removed[s] = RAGGED && s == d_out >> 5 && (d_out & 3) ? ((1u << (4 - (d_out & 3))) - 1u) << (d_out & 31) : 0u;
     if constexpr (MODE == kModeReuse) {
         // ---- the kept arrangement: header, bucket table, place array
         const unsigned char *src = static_cast<const unsigned char *>(a.arr_reuse) + i * a.arr_stride;
@@ -758,9 +791,7 @@ void kmeans_bucket_kernel(KmArgs a) {
         uint32_t nonfinite = 0;
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            const int g = k * T + tid;
-            uint2 raw = make_uint2(0, 0);
-            if (g < n_groups) raw = wrow[g];
+            const uint2 raw = load_group<RAGGED>(wrow_h, k * T + tid, n_groups, d_out);
             nonfinite |= nonfinite_of_half2(raw.x) | nonfinite_of_half2(raw.y);
             keys[2 * k] = keys_of_half2(raw.x);
             keys[2 * k + 1] = keys_of_half2(raw.y);
@@ -782,10 +813,7 @@ void kmeans_bucket_kernel(KmArgs a) {
         // a clustering of NaNs
         if (tid == 0 && a.status) atomicOr(a.status, (int)(input_ok ? CMPQ_STATUS_NONFINITE : bad_status));
         if (tid < CMPQ_KMAX) crow[tid] = tid < K ? 0.0f : INFINITY;
-        if (a.codes) {
-            uint32_t *c32 = reinterpret_cast<uint32_t *>(a.codes + i * a.d_out);
-            for (int g = tid; g < n_groups; g += T) c32[g] = 0;
-        }
+        zero_codes<RAGGED, T>(a.codes ? a.codes + i * a.d_out : nullptr, n_groups, d_out);
         if constexpr (kCodesFused) {  // the row of all-zero codes, the table of zero levels, no number for the error
             if (row_dst) for (int w = tid; w < row_words; w += T) row_dst[w] = 0;
             if (lut_dst && tid < K) lut_dst[tid] = 0;
@@ -814,7 +842,7 @@ void kmeans_bucket_kernel(KmArgs a) {
 
     // ---- bucket tables: counts and sums of places of the kept weights
     if constexpr (MODE != kModeReuse) {
-        if (n_ex > 0) count_buckets<G, T, LB, true>(keys, removed, sm.scum, n_groups);
+        if (RAGGED || n_ex > 0) count_buckets<G, T, LB, true>(keys, removed, sm.scum, n_groups);
         else count_buckets<G, T, LB, false>(keys, removed, sm.scum, n_groups);
         __syncthreads();
     }
@@ -882,7 +910,7 @@ void kmeans_bucket_kernel(KmArgs a) {
         }
     } else {
         // ---- scatter the places of the kept weights, ordered by bucket
-        if (n_ex > 0) scatter_places<G, T, LB, true>(keys, removed, cursor, arr, n_groups);
+        if (RAGGED || n_ex > 0) scatter_places<G, T, LB, true>(keys, removed, cursor, arr, n_groups);
         else scatter_places<G, T, LB, false>(keys, removed, cursor, arr, n_groups);
     }
     __syncthreads();
@@ -895,10 +923,10 @@ void kmeans_bucket_kernel(KmArgs a) {
 
     double err = 0.0;
     switch (K) {
-        case 2: lloyd_bucket<G, 2, T, LB, kCodesFused>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-        case 4: lloyd_bucket<G, 4, T, LB, kCodesFused>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-        case 8: lloyd_bucket<G, 8, T, LB, kCodesFused>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-        default: lloyd_bucket<G, 16, T, LB, kCodesFused>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
+        case 2: lloyd_bucket<G, 2, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
+        case 4: lloyd_bucket<G, 4, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
+        case 8: lloyd_bucket<G, 8, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
+        default: lloyd_bucket<G, 16, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
     }
     if (tid < CMPQ_KMAX) crow[tid] = tid < K ? sm.cent[tid] : INFINITY;
     if constexpr (kCodesFused) {
@@ -930,8 +958,9 @@ size_t bucket_dyn_lds(int64_t d_out, int lb) {
 
 template <int G, int T, int LB>
 int launch_variant(const KmArgs &a, hipStream_t s) {
-    auto kern = a.arr_reuse ? kmeans_bucket_kernel<G, T, LB, kModeReuse>
-                            : (a.fused ? kmeans_bucket_kernel<G, T, LB, kModeFused> : kmeans_bucket_kernel<G, T, LB, kModePlain>);
+    auto kern = a.arr_reuse ? kmeans_bucket_kernel<G, T, LB, kModeReuse, false>
+                            : (a.fused ? kmeans_bucket_kernel<G, T, LB, kModeFused, false> : kmeans_bucket_kernel<G, T, LB, kModePlain, false>);
+    if (a.ragged) kern = a.fused ? kmeans_bucket_kernel<G, T, LB, kModeFused, true> : kmeans_bucket_kernel<G, T, LB, kModePlain, true>;
     const size_t lds = bucket_dyn_lds(a.d_out, LB);
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
@@ -996,7 +1025,7 @@ int launch_kmeans_hist(const KmArgs &a, hipStream_t s) {
     // longest channels (two workgroups of 512 share a compute unit where one of 1024
     // would leave it idle at every barrier).
     int T, G, LB;
-    hist_variant(a.d_out, T, G, LB);
+    hist_variant((a.d_out + 3) / 4 * 4, T, G, LB);
     if (T == 0) return CMPQ_ESHAPE;
     if (G == 16) return launch_variant<16, 512, CMPQ_LB512>(a, s);
     if (G == 8) {
