@@ -150,13 +150,20 @@ __global__ __launch_bounds__(kSelThreads) void allocate_bits_kernel(
 // concentration), a flag sends the call down the full path: per-workgroup tables from the
 // last pass and one more pass over the data.
 //
-// Fast chain, tried first: two histogram passes over a sample (every s-th wave-chunk)
-// give a 22-bit prefix that, by the sample, a few percent more than k entries reach.  One
-// pass over the data stages every entry that reaches it; the exact k-th key is then
-// found inside the list (the same three digits, over the list only) and the answer
-// written from the list.  The sample only guides the guess: if the list turns out to
-// hold fewer than k entries or overflows, a flag is raised and the exact chain, whose
-// kernels otherwise return at once, does the work.  Either way the result is the same set.
+// Fast chain, tried first: one histogram pass over a sample (every s-th wave-chunk) gives a
+// threshold that, by the sample, some ten percent more than k entries reach.  One pass over
+// the data stages every entry that reaches it; the exact k-th key is then found inside the
+// list (two histograms, the first of them counted from the guess upwards, which is where it
+// lies) and the answer written from the list.  The sample only guides the guess: if the list
+// turns out to hold fewer than k entries or overflows, or the k-th key lies beyond four times
+// the guess, a flag is raised and the exact chain, whose kernels otherwise return at once,
+// does the work.  Either way the result is the same set.
+//
+// What bounds the chain beside the one pass over the data is its launches, 4.5 us each, and counters
+// that many workgroups add to.  Ten launches: one sample pass, two of the list and no scan of the
+// units' counts in a kernel of its own, where it were thirteen; 4096x4096 weights, k = 0.5 %, all
+// kernels but the pass over the data: 102 -> 64 us (sample 31 -> 11, list 25 -> 13, counts and
+// output 29 -> 15).
 
 constexpr int kWThreads = 256;
 constexpr int kWaves = kWThreads / CMPQ_WAVE;
@@ -165,8 +172,18 @@ constexpr int kWaveChunk = CMPQ_WAVE * kWPerLane;
 constexpr int kMaxBlocks = 2048;
 constexpr int kMaxUnits = kMaxBlocks * kWaves;
 constexpr int kBins = 2048;
-// histograms: 0-2 the digits of the exact chain, 3-4 the sample's, 5-7 the list's
-constexpr int kHists = 8;
+// Histograms: the three digits of the exact chain; the sample's, 12 bits of the key (exponent and
+// 4 mantissa bits) and the sums of 8 of those; the list's first (by 2^13 keys, from the guess on)
+// and second (every key of one bin of the first, and the sums of 8 of those).
+constexpr int kSampleShift = 19, kSampleFine = 1 << (31 - kSampleShift);
+constexpr int kListShift = 13, kListFine = 1 << kListShift;
+// Additions from many workgroups to one counter go one after the other (0.13 us each across the
+// chip), so the sample's and the list's first histogram are kept in kSets sets, to be added up by
+// the reader.
+constexpr int kSets = 4, kSampleSet = kSampleFine + kSampleFine / 8;
+constexpr int kHistSample = 3 * kBins, kHistList = kHistSample + kSets * kSampleSet;
+constexpr int kHistList2 = kHistList + kSets * kBins;
+constexpr int kHistList2Fine = kHistList2 + kListFine / 8, kHistWords = kHistList2Fine + kListFine;
 
 struct WselState {
     uint32_t T;         // final threshold key
@@ -175,7 +192,9 @@ struct WselState {
     // fast chain
     uint32_t fast_overflow;  // a unit's staging share was too small
     uint32_t fast_failed;    // the list does not settle the answer: the exact chain runs
-    uint32_t guess22;        // staged: top 22 bits >= guess22
+    uint32_t reach;          // staged: key >= reach
+    uint32_t first_key;      // the k-th key lies in the kListFine keys from here
+    uint64_t rem;            //   and is the rem-th largest of the list there
 };
 
 struct WselArgs {
@@ -219,13 +238,14 @@ WselPlan wsel_plan(int64_t d_in, int64_t d_out, int64_t k) {
     int64_t cap = 4 * cdiv(k, nu) + 256;
     if (cap > p.wc_per_unit * kWaveChunk) cap = p.wc_per_unit * kWaveChunk;
     p.cap = (uint32_t)cap;
-    // sample: 8192 wave-chunks or more, a prime stride that does not divide the chunks of a
+    // sample: 4096 wave-chunks or more, a prime stride that does not divide the chunks of a
     // channel (so that every part of a channel is met); aim a margin above the sample's share
-    // of k: 6 %, or 8 standard deviations of a count of that size if that is more
-    static const int primes[] = {61, 59, 53, 47, 43, 41, 37, 31, 29, 23, 19, 17, 13, 11, 7, 5, 3};
+    // of k: 15 % (channels differ, a chunk is of one channel, and keys are not spread evenly inside
+    // a bin), or 8 standard deviations of a count of that size if that is more
+    static const int primes[] = {1021, 761, 509, 383, 251, 191, 127, 97, 73, 61, 53, 47, 43, 37, 31, 23, 19, 17, 13, 11, 7, 5, 3};
     p.sample_stride = 1;
     for (int pr : primes) {
-        if ((int64_t)pr * 8192 <= p.total_wc && p.wc_per_channel % pr != 0) {
+        if ((int64_t)pr * 4096 <= p.total_wc && p.wc_per_channel % pr != 0) {
             p.sample_stride = pr;
             break;
         }
@@ -233,7 +253,7 @@ WselPlan wsel_plan(int64_t d_in, int64_t d_out, int64_t k) {
     p.n_sample = cdiv(p.total_wc, p.sample_stride);
     const double ks = (double)k * (double)p.n_sample / (double)(p.total_wc > 0 ? p.total_wc : 1);
     double margin = 8.0 / __builtin_sqrt(ks > 1.0 ? ks : 1.0);
-    if (margin < 0.06) margin = 0.06;
+    if (margin < 0.15) margin = 0.15;
     p.sample_rank = (uint64_t)(ks * (1.0 + margin)) + 8;
     return p;
 }
@@ -264,6 +284,10 @@ __device__ __forceinline__ uint2 fetch_codes8(const WselArgs &a, int64_t i, int 
         const U2 nt = __builtin_nontemporal_load(reinterpret_cast<const U2 *>(crow + o0));
         return make_uint2(nt.x, nt.y);
     }
+    if (o0 + 8 <= d_out) {  // at any alignment
+        __builtin_memcpy(&c, crow + o0, 8);
+        return c;
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         if (o0 + j < d_out) {
@@ -282,6 +306,8 @@ __device__ __forceinline__ void fetch8(const WselArgs &a, int64_t i, int o0, Raw
         typedef uint32_t U4 __attribute__((ext_vector_type(4)));
         const U4 nt = __builtin_nontemporal_load(reinterpret_cast<const U4 *>(wrow + o0));
         r.w = make_uint4(nt.x, nt.y, nt.z, nt.w);
+    } else if (o0 + 8 <= d_out) {  // at any alignment
+        __builtin_memcpy(&r.w, wrow + o0, 16);
     } else {
         uint32_t h[8];
 #pragma unroll
@@ -298,6 +324,9 @@ __device__ __forceinline__ void fetch8(const WselArgs &a, int64_t i, int o0, Raw
     if (vec) {
         r.w0 = *reinterpret_cast<const float4 *>(wrow + o0);
         r.w1 = *reinterpret_cast<const float4 *>(wrow + o0 + 4);
+    } else if (o0 + 8 <= d_out) {  // at any alignment
+        __builtin_memcpy(&r.w0, wrow + o0, 16);
+        __builtin_memcpy(&r.w1, wrow + o0 + 4, 16);
     } else {
         float f[8];
 #pragma unroll
@@ -818,17 +847,21 @@ struct PickShared {
     int ok;
 };
 
-// The bin of the 2048-bin histogram h that holds rank `rem`, counted from the largest bin
-// down (1-based), and the rank inside that bin.  Called by all 256 threads of a workgroup
+// The bin of the histogram h (2048 bins, or NBINS) that holds rank `rem`, counted from the largest
+// bin down (1-based), and the rank inside that bin.  Called by all 256 threads of a workgroup
 // (contains barriers); false when rem is 0 or exceeds the total.
+// SETS histograms that lie `stride` words apart count together.
+template <int NBINS = kBins, int SETS = 1>
 __device__ __forceinline__ bool block_pick(const uint32_t *__restrict__ h, uint64_t rem, PickShared &ps,
-                                           uint32_t &bin, uint64_t &rem_in, uint32_t &total) {
-    constexpr int kPer = kBins / kWThreads;
-    const int r0 = threadIdx.x * kPer;  // position r <-> bin kBins - 1 - r
+                                           uint32_t &bin, uint64_t &rem_in, uint32_t &total, int stride = 0) {
+    constexpr int kPer = NBINS / kWThreads;
+    const int r0 = threadIdx.x * kPer;  // position r <-> bin NBINS - 1 - r
     uint32_t v[kPer], sum = 0;
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        v[r] = h[kBins - 1 - (r0 + r)];
+        v[r] = h[NBINS - 1 - (r0 + r)];
+#pragma unroll
+        for (int c = 1; c < SETS; ++c) v[r] += h[c * stride + NBINS - 1 - (r0 + r)];
         sum += v[r];
     }
     uint32_t tot;
@@ -845,7 +878,7 @@ __device__ __forceinline__ bool block_pick(const uint32_t *__restrict__ h, uint6
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
             if (v[r] && run < rem && rem <= run + v[r]) {
-                ps.bin = (uint32_t)(kBins - 1 - (r0 + r));
+                ps.bin = (uint32_t)(NBINS - 1 - (r0 + r));
                 ps.rem_in = rem - run;
                 ps.ok = 1;
             }
@@ -880,22 +913,83 @@ __device__ __forceinline__ void exact_prefix(const uint32_t *__restrict__ hist, 
     }
 }
 
-// Fast chain, sample passes: histogram of the first (PASS 0) or, inside the first digit's
-// bin, the second (PASS 1) 11-bit digit over every sample_stride-th wave-chunk.
-template <typename TW, int PASS>
-__global__ __launch_bounds__(kWThreads) void wsel_sample_kernel(WselArgs a, uint32_t *__restrict__ hist) {
-    __shared__ uint32_t lh[kBins];
-    __shared__ PickShared ps;
-    for (int b = threadIdx.x; b < kBins; b += kWThreads) lh[b] = 0;
-    uint32_t bin0 = 0;
-    if (PASS == 1) {
-        uint64_t r;
-        uint32_t tot;
-        if (!block_pick(hist + 3 * kBins, a.sample_rank, ps, bin0, r, tot)) return;
+// The one of 8 neighbouring fine bins that holds rank `rem` of their sum (from the largest down),
+// the rank inside it and its count.  Every lane for itself.
+template <int SETS = 1>
+__device__ __forceinline__ int pick_of_8(const uint32_t *__restrict__ fine, uint64_t rem, uint64_t &rem_in, uint32_t &count,
+                                         int stride = 0) {
+    uint32_t v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        v[r] = fine[r];
+#pragma unroll
+        for (int c = 1; c < SETS; ++c) v[r] += fine[c * stride + r];
     }
+    int bin = 0;
+    uint64_t run = 0;
+    rem_in = rem;
+    count = v[0];
+#pragma unroll
+    for (int r = 7; r >= 0; --r) {
+        if (v[r] && run < rem && rem <= run + v[r]) {
+            bin = r;
+            rem_in = rem - run;
+            count = v[r];
+        }
+        run += v[r];
+    }
+    return bin;
+}
+
+// Fast chain, the list's digits.  First: the bin (of 2^13 keys, counted from the guess) that holds the
+// k-th key; false when the list does not settle that (too short, or beyond the bins).
+__device__ __forceinline__ bool list_bin(const uint32_t *__restrict__ hist, uint64_t k, uint32_t reach, PickShared &ps,
+                                         uint32_t &first_key, uint64_t &rem) {
+    uint32_t bin, tot;
+    const bool ok = block_pick<kBins, kSets>(hist + kHistList, k, ps, bin, rem, tot, kBins) && bin < kBins - 1;
+    first_key = ((reach >> kListShift) + bin) << kListShift;
+    return ok;
+}
+// Then the key itself and how many keys equal to it are to be taken.
+__device__ __forceinline__ void list_key(const uint32_t *__restrict__ hist, uint32_t first_key, uint64_t rem,
+                                         PickShared &ps, uint32_t &T, uint64_t &need) {
+    uint32_t bin, tot, count;
+    uint64_t rem8;
+    block_pick<kListFine / 8>(hist + kHistList2, rem, ps, bin, rem8, tot);
+    T = first_key + 8 * bin + (uint32_t)pick_of_8(hist + kHistList2Fine + 8 * bin, rem8, need, count);
+}
+
+// Adds a workgroup's fine histogram, 16 bits a counter, two to a word, to the global one, and the
+// sums of 8 to the coarse one.
+__device__ __forceinline__ void flush_fine(const uint32_t *lh, int n_fine, uint32_t *__restrict__ coarse,
+                                           uint32_t *__restrict__ fine) {
+    for (int b = threadIdx.x; b < n_fine / 8; b += (int)blockDim.x) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t two = lh[4 * b + r], lo = two & 0xffffu, hi = two >> 16;
+            if (lo) atomicAdd(&fine[8 * b + 2 * r], lo);
+            if (hi) atomicAdd(&fine[8 * b + 2 * r + 1], hi);
+            sum += lo + hi;
+        }
+        if (sum) atomicAdd(&coarse[b], sum);
+    }
+}
+
+// Fast chain, the sample: histogram of the keys' top 12 bits over every sample_stride-th wave-chunk.
+// A workgroup takes at most kSampleChunks of them, so that 16 bits a counter do.
+// Workgroups of 16 wavefronts: a wavefront's wave-chunks wait for memory one after the other, and a
+// workgroup more is a flush more into the same counters.
+constexpr int kSampleChunks = 96, kSampleThreads = 1024;
+static_assert(kSampleChunks * kWaveChunk < 65536, "");
+template <typename TW>
+__global__ __launch_bounds__(kSampleThreads) void wsel_sample_kernel(WselArgs a, uint32_t *__restrict__ hist) {
+    __shared__ uint32_t lh[kSampleFine / 2];
+    for (int b = threadIdx.x; b < kSampleFine / 2; b += kSampleThreads) lh[b] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    const int64_t n_waves = (int64_t)gridDim.x * kWaves;
+    constexpr int kSampleWaves = kSampleThreads / CMPQ_WAVE;
+    const int64_t n_waves = (int64_t)gridDim.x * kSampleWaves;
     // few workgroups (every one ends with a flush into the same global counters), several
     // wave-chunks per wavefront, the next one's loads issued before the current one is used
     struct Item {
@@ -905,15 +999,15 @@ __global__ __launch_bounds__(kWThreads) void wsel_sample_kernel(WselArgs a, uint
         Raw8<TW> raw;
     };
     auto load = [&](int64_t j, Item &it) {
-        const int64_t q = j * a.sample_stride;
-        it.i = q / a.wc_per_channel;
-        it.o0 = (q % a.wc_per_channel) * kWaveChunk + lane * kWPerLane;
+        const uint32_t q = (uint32_t)(j * a.sample_stride);  // total_wc is below 2^31
+        it.i = q / (uint32_t)a.wc_per_channel;
+        it.o0 = (int64_t)(q % (uint32_t)a.wc_per_channel) * kWaveChunk + lane * kWPerLane;
         // all loads at once: the few channels of O_act are fetched and then dropped
         it.live = channel_live(a, it.i);  // uniform over the wavefront
         fetch8(a, it.i, it.o0, it.raw);
         it.cent = a.centroids ? a.centroids[it.i * CMPQ_KMAX + (lane & 15)] : 0.f;
     };
-    int64_t j = (int64_t)blockIdx.x * kWaves + wave;
+    int64_t j = (int64_t)blockIdx.x * kSampleWaves + wave;
     Item cur = {}, nxt = {};
     if (j < a.n_sample) load(j, cur);
     for (; j < a.n_sample; j += n_waves) {
@@ -926,43 +1020,41 @@ __global__ __launch_bounds__(kWThreads) void wsel_sample_kernel(WselArgs a, uint
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 if (!((valid >> e) & 1u)) continue;
-                if (PASS == 0) {
-                    atomicAdd(&lh[key[e] >> 21], 1u);
-                } else if ((key[e] >> 21) == bin0) {
-                    atomicAdd(&lh[(key[e] >> 10) & 2047u], 1u);
-                }
+                const uint32_t bin = key[e] >> kSampleShift;
+                atomicAdd(&lh[bin >> 1], bin & 1u ? 0x10000u : 1u);
             }
         }
         cur = nxt;
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < kBins; b += kWThreads)
-        if (lh[b]) atomicAdd(&hist[(3 + PASS) * kBins + b], lh[b]);
+    uint32_t *set = hist + kHistSample + (blockIdx.x & (kSets - 1)) * kSampleSet;
+    flush_fine(lh, kSampleFine, set, set + kSampleFine / 8);
 }
 
-// Fast chain, the one pass over the data: stages every entry whose top 22 bits reach the
-// guess read off the sample's histograms.
+// Fast chain, the one pass over the data: stages every entry whose key reaches the guess read off
+// the sample's histograms (inside a bin, by the share of its entries that lie above).
 // NEAR (FP16 weights, residual score, no codes): candidates by the channel's intervals.
 template <typename TW, bool NEAR>
 __global__ __launch_bounds__(kWThreads) void wsel_stage_kernel(WselArgs a, WselState *st,
                                                                 const uint32_t *__restrict__ hist) {
     __shared__ PickShared ps;
-    uint32_t guess22 = 0;  // no usable sample: everything reaches it, the list overflows, the exact chain runs
+    uint32_t reach = 0;  // no usable sample: everything reaches it, the list overflows, the exact chain runs
     {
-        uint32_t bin0, bin1, tot;
-        uint64_t rem0, rem1;
-        if (block_pick(hist + 3 * kBins, a.sample_rank, ps, bin0, rem0, tot) &&
-            block_pick(hist + 4 * kBins, rem0, ps, bin1, rem1, tot))
-            guess22 = (bin0 << 11) | bin1;
+        uint32_t bin, tot, count;
+        uint64_t rem, rem_in;
+        if (block_pick<kSampleFine / 8, kSets>(hist + kHistSample, a.sample_rank, ps, bin, rem, tot, kSampleSet)) {
+            const int fine = (int)(8 * bin) + pick_of_8<kSets>(hist + kHistSample + kSampleFine / 8 + 8 * bin, rem, rem_in, count, kSampleSet);
+            const float share = 1.0f - (float)rem_in / (float)(count ? count : 1);
+            reach = ((uint32_t)fine << kSampleShift) + (uint32_t)(share * (float)((1 << kSampleShift) - 1));
+        }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) st->guess22 = guess22;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->reach = reach;
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
     const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
     const int64_t q0 = unit * a.wc_per_unit;
     const int64_t q1 = min(a.total_wc, q0 + a.wc_per_unit);
     uint32_t n_staged = 0;
     bool over = false;
-    const uint32_t reach = guess22 << 10;  // (key >> 10) >= guess22 as one compare
     unsigned long long *stage_ik = a.stage_ik + unit * a.cap;
     uint16_t *stage_val = a.stage_val + unit * a.cap;
     if constexpr (std::is_same<TW, __half>::value) {
@@ -1014,71 +1106,88 @@ __global__ __launch_bounds__(kWThreads) void wsel_stage_kernel(WselArgs a, WselS
     }
 }
 
-// Fast chain, passes over the list: the exact k-th key of the list by the same three
-// digits as the exact chain (11 + 11 + 10 bits), each pass reading the digits the earlier
-// ones fixed off their histograms.  The second pass also settles whether the list holds
-// the answer at all: it does unless it overflowed or is shorter than k.
+// Fast chain, passes over the list: its two histograms.  The second pass also settles whether the
+// list holds the answer at all: it does unless it overflowed, is shorter than k, or the k-th key
+// lies beyond the first histogram's bins.
 template <int PASS>
 __global__ __launch_bounds__(kWThreads) void wsel_list_kernel(WselArgs a, WselState *st, int nunits,
                                                                uint32_t *__restrict__ hist, uint64_t k) {
-    __shared__ uint32_t lh[kBins];
+    constexpr int kWords = PASS == 0 ? kBins : kListFine;
+    __shared__ uint32_t lh[kWords];
     __shared__ PickShared ps;
-    for (int b = threadIdx.x; b < kBins; b += kWThreads) lh[b] = 0;
+    for (int b = threadIdx.x; b < kWords; b += kWThreads) lh[b] = 0;
     const bool overflowed = st->fast_overflow != 0;
-    uint32_t prefix = 0;
-    if (PASS > 0) {
+    const uint32_t reach = st->reach;
+    uint32_t first_key = 0;
+    if (PASS == 1) {
         uint64_t rem;
-        bool all;
-        exact_prefix(hist + 5 * kBins, k, PASS, ps, prefix, rem, all);
-        const bool failed = overflowed || all;
-        if (PASS == 1 && blockIdx.x == 0 && threadIdx.x == 0) st->fast_failed = failed ? 1u : 0u;
+        const bool failed = !list_bin(hist, k, reach, ps, first_key, rem) || overflowed;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st->fast_failed = failed ? 1u : 0u;
+            st->first_key = first_key;
+            st->rem = rem;
+        }
         if (failed) return;
     } else if (overflowed) {
         return;
     }
     __syncthreads();
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    for (int64_t unit = (int64_t)blockIdx.x * kWaves + wave; unit < nunits; unit += (int64_t)gridDim.x * kWaves) {
+    // 8 lanes per unit: units hold a few entries to a few hundred
+    constexpr int kShare = 8;
+    const int sub = lane & (kShare - 1);
+    for (int64_t unit = ((int64_t)blockIdx.x * kWaves + wave) * (CMPQ_WAVE / kShare) + lane / kShare; unit < nunits;
+         unit += (int64_t)gridDim.x * (kWThreads / kShare)) {
         const unsigned long long *ik = a.stage_ik + unit * a.cap;
         const uint32_t n = a.stage_cnt[unit];
 #pragma unroll 4
-        for (uint32_t e = lane; e < n; e += CMPQ_WAVE) {
+        for (uint32_t e = sub; e < n; e += kShare) {
             const uint32_t key = (uint32_t)ik[e];
-            if (PASS == 0) {
-                atomicAdd(&lh[key >> 21], 1u);
-            } else if (PASS == 1) {
-                if ((key >> 21) == (prefix >> 21)) atomicAdd(&lh[(key >> 10) & 2047u], 1u);
-            } else {
-                if ((key >> 10) == (prefix >> 10)) atomicAdd(&lh[key & 1023u], 1u);
-            }
+            if (PASS == 0) atomicAdd(&lh[min((key >> kListShift) - (reach >> kListShift), (uint32_t)kBins - 1)], 1u);
+            else if ((key >> kListShift) == (first_key >> kListShift)) atomicAdd(&lh[key & (kListFine - 1)], 1u);
         }
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < kBins; b += kWThreads)
-        if (lh[b]) atomicAdd(&hist[(5 + PASS) * kBins + b], lh[b]);
+    if (PASS == 0) {
+        for (int b = threadIdx.x; b < kBins; b += kWThreads)
+            if (lh[b]) atomicAdd(&hist[kHistList + (blockIdx.x & (kSets - 1)) * kBins + b], lh[b]);
+    } else {
+        for (int b = threadIdx.x; b < kListFine / 8; b += kWThreads) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const uint32_t v = lh[8 * b + r];
+                if (v) atomicAdd(&hist[kHistList2Fine + 8 * b + r], v);
+                sum += v;
+            }
+            if (sum) atomicAdd(&hist[kHistList2 + b], sum);
+        }
+    }
 }
 
-__global__ void wsel_init_kernel(WselState *st, uint32_t *hist, int32_t *idx_out,
-                                 int64_t k_fill) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < kHists * kBins) hist[t] = 0;
+__global__ void wsel_init_kernel(WselState *st, uint32_t *hist) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < kHistWords / 4) reinterpret_cast<uint4 *>(hist)[t] = make_uint4(0, 0, 0, 0);
     if (t == 0) {
         st->T = 0;
         st->need = 0;
         st->overflow = 0;
         st->fast_overflow = 0;
         st->fast_failed = 0;
-        st->guess22 = 0;
+        st->reach = 0;
+        st->first_key = 0;
+        st->rem = 0;
     }
-    for (int64_t j = t; j < k_fill; j += (int64_t)gridDim.x * blockDim.x) idx_out[j] = -1;
 }
 
 // PASS 0: digit = key >> 21 (11 bits), PASS 1: (key >> 10) & 2047, PASS 2: key & 1023.
 // The last pass also stages the entries whose top 22 bits reach the prefix and leaves,
 // per workgroup, how many of its keys lie above the 22-bit prefix and its own histogram
 // of the last digit (what the full path needs to place its output without counting again).
+// Usually it returns at once, so it is launched with few workgroups, each of which takes the shares
+// blk = blockIdx.x, + gridDim.x, ... of the nblocks in turn.
 template <typename TW, int PASS>
-__global__ __launch_bounds__(kWThreads) void wsel_hist_kernel(WselArgs a, WselState *st, uint64_t k,
+__global__ __launch_bounds__(kWThreads) void wsel_hist_kernel(WselArgs a, WselState *st, uint64_t k, int nblocks,
                                                                uint32_t *__restrict__ hist,
                                                                uint32_t *__restrict__ above,
                                                                uint32_t *__restrict__ local_last) {
@@ -1088,7 +1197,6 @@ __global__ __launch_bounds__(kWThreads) void wsel_hist_kernel(WselArgs a, WselSt
     __shared__ uint32_t lh[kCopies * kBins];
     __shared__ uint32_t red[kWaves];
     if (!st->fast_failed) return;  // the fast chain settled the answer
-    for (int b = threadIdx.x; b < kCopies * kBins; b += kWThreads) lh[b] = 0;
     __shared__ PickShared ps;
     uint32_t prefix = 0;
     {
@@ -1096,87 +1204,93 @@ __global__ __launch_bounds__(kWThreads) void wsel_hist_kernel(WselArgs a, WselSt
         bool all;
         exact_prefix(hist, k, PASS, ps, prefix, rem, all);  // the digits the passes before this one fixed
     }
-    __syncthreads();
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    uint32_t *lh0 = lh + (lane & (kCopies - 1)) * kBins;
-    const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
-    const int64_t q0 = unit * a.wc_per_unit;
-    const int64_t q1 = min(a.total_wc, q0 + a.wc_per_unit);
-    uint32_t n_above = 0, n_staged = 0;
-    bool over = false;
-    unsigned long long *stage_ik = a.stage_ik + unit * a.cap;
-    uint16_t *stage_val = a.stage_val + unit * a.cap;
-    for_each_wave_chunk<TW>(a, q0, q1, [&](int64_t i, int o0, const uint32_t (&key)[8], const float (&wv)[8], uint32_t valid) {
-        uint32_t cand = 0;  // bit j: entry j reaches the 22-bit prefix
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (!((valid >> j) & 1u)) continue;
-            if (PASS == 0) {
-                atomicAdd(&lh0[key[j] >> 21], 1u);
-            } else if (PASS == 1) {
-                if ((key[j] >> 21) == (prefix >> 21)) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
-            } else {
-                if ((key[j] >> 10) == (prefix >> 10)) atomicAdd(&lh[key[j] & 1023u], 1u);
-                n_above += (key[j] >> 10) > (prefix >> 10);
-                cand |= (uint32_t)((key[j] >> 10) >= (prefix >> 10)) << j;
-            }
-        }
-        if (PASS == 2) stage_chunk(cand, i, o0, a.d_out, key, wv, stage_ik, stage_val, a.cap, n_staged, over);
-    });
-    __syncthreads();
-    for (int b = threadIdx.x; b < kBins; b += kWThreads) {
-        uint32_t n = lh[b];
-#pragma unroll
-        for (int r = 1; r < kCopies; ++r) n += lh[r * kBins + b];
-        if (n) atomicAdd(&hist[PASS * kBins + b], n);
-    }
-    if (PASS == 2) {
-        if (lane == 0) {
-            a.stage_cnt[unit] = over ? 0u : n_staged;
-            if (over) st->overflow = 1u;
-        }
-        for (int b = threadIdx.x; b < 1024; b += kWThreads) local_last[(int64_t)blockIdx.x * 1024 + b] = lh[b];
-        n_above = wave_sum_u32(n_above);
-        if (lane == 0) red[wave] = n_above;
+    for (int blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        __syncthreads();  // the counters of the share before are no longer read
+        for (int b = threadIdx.x; b < kCopies * kBins; b += kWThreads) lh[b] = 0;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t t = 0;
-            for (int w = 0; w < kWaves; ++w) t += red[w];
-            above[blockIdx.x] = t;
+        uint32_t *lh0 = lh + (lane & (kCopies - 1)) * kBins;
+        const int64_t unit = (int64_t)blk * kWaves + wave;
+        const int64_t q0 = unit * a.wc_per_unit;
+        const int64_t q1 = min(a.total_wc, q0 + a.wc_per_unit);
+        uint32_t n_above = 0, n_staged = 0;
+        bool over = false;
+        unsigned long long *stage_ik = a.stage_ik + unit * a.cap;
+        uint16_t *stage_val = a.stage_val + unit * a.cap;
+        for_each_wave_chunk<TW>(a, q0, q1, [&](int64_t i, int o0, const uint32_t (&key)[8], const float (&wv)[8], uint32_t valid) {
+            uint32_t cand = 0;  // bit j: entry j reaches the 22-bit prefix
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (!((valid >> j) & 1u)) continue;
+                if (PASS == 0) {
+                    atomicAdd(&lh0[key[j] >> 21], 1u);
+                } else if (PASS == 1) {
+                    if ((key[j] >> 21) == (prefix >> 21)) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
+                } else {
+                    if ((key[j] >> 10) == (prefix >> 10)) atomicAdd(&lh[key[j] & 1023u], 1u);
+                    n_above += (key[j] >> 10) > (prefix >> 10);
+                    cand |= (uint32_t)((key[j] >> 10) >= (prefix >> 10)) << j;
+                }
+            }
+            if (PASS == 2) stage_chunk(cand, i, o0, a.d_out, key, wv, stage_ik, stage_val, a.cap, n_staged, over);
+        });
+        __syncthreads();
+        for (int b = threadIdx.x; b < kBins; b += kWThreads) {
+            uint32_t n = lh[b];
+#pragma unroll
+            for (int r = 1; r < kCopies; ++r) n += lh[r * kBins + b];
+            if (n) atomicAdd(&hist[PASS * kBins + b], n);
+        }
+        if (PASS == 2) {
+            if (lane == 0) {
+                a.stage_cnt[unit] = over ? 0u : n_staged;
+                if (over) st->overflow = 1u;
+            }
+            for (int b = threadIdx.x; b < 1024; b += kWThreads) local_last[(int64_t)blk * 1024 + b] = lh[b];
+            n_above = wave_sum_u32(n_above);
+            if (lane == 0) red[wave] = n_above;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                uint32_t t = 0;
+                for (int w = 0; w < kWaves; ++w) t += red[w];
+                above[blk] = t;
+            }
         }
     }
 }
 
-// Keys above the threshold and keys equal to it: per unit from the staging list, or, on
-// the full path, per workgroup from the tables the last histogram pass left.
-// First settles the threshold: read off the list's second histogram when the fast chain
-// holds the answer, else off the three histograms of the exact chain.
+// Keys above the threshold and keys equal to it, per workgroup (4 units) and, from the staging list,
+// per unit; on the full path per workgroup only, from the tables the last histogram pass left.
+// First settles the threshold: read off the list's histograms when the fast chain holds the answer,
+// else off the three histograms of the exact chain.
 __global__ __launch_bounds__(kWThreads) void wsel_count_kernel(WselState *st, WselArgs a, uint64_t k,
                                                                 const uint32_t *__restrict__ hist,
                                                                 const uint32_t *__restrict__ above,
                                                                 const uint32_t *__restrict__ local_last,
-                                                                uint32_t *__restrict__ cnt_gt,
-                                                                uint32_t *__restrict__ cnt_eq) {
-    __shared__ uint32_t red[kWaves];
+                                                                uint2 *__restrict__ cnt_unit,
+                                                                uint2 *__restrict__ cnt_block) {
+    __shared__ uint2 red[kWaves];
     __shared__ PickShared ps;
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
     const bool exact = st->fast_failed != 0;
     uint32_t T;
     uint64_t need;
-    {
-        bool all;  // the three digits of the list's histograms, or of the exact chain's
-        exact_prefix(exact ? hist : hist + 5 * kBins, k, 3, ps, T, need, all);
+    if (exact) {
+        bool all;
+        exact_prefix(hist, k, 3, ps, T, need, all);
         if (all) need = ~0ull;  // T = 0: every candidate counts
+    } else {
+        list_key(hist, st->first_key, st->rem, ps, T, need);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->T = T;
         st->need = need;
     }
+    uint32_t gt = 0, eq = 0;
     if (!exact || !st->overflow) {
         const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
         const unsigned long long *ik = a.stage_ik + unit * a.cap;
         const uint32_t n = a.stage_cnt[unit];
-        uint32_t gt = 0, eq = 0;
         for (uint32_t e = lane; e < n; e += CMPQ_WAVE) {
             const uint32_t key = (uint32_t)ik[e];
             gt += key > T;
@@ -1184,90 +1298,91 @@ __global__ __launch_bounds__(kWThreads) void wsel_count_kernel(WselState *st, Ws
         }
         gt = wave_sum_u32(gt);
         eq = wave_sum_u32(eq);
-        if (lane == 0) {
-            cnt_gt[unit] = gt;
-            cnt_eq[unit] = eq;
+        if (lane == 0) cnt_unit[unit] = make_uint2(gt, eq);
+    } else {
+        const uint32_t digit = T & 1023u;
+        const bool everything = need == ~0ull;  // more asked than there is: every candidate counts
+        const uint32_t *h = local_last + (int64_t)blockIdx.x * 1024;
+        for (int b = threadIdx.x; b < 1024; b += kWThreads)
+            if (everything ? b > 0 : (uint32_t)b > digit) gt += h[b];
+        gt = wave_sum_u32(gt);
+        if (threadIdx.x == 0) {
+            gt += above[blockIdx.x];
+            eq = h[everything ? 0 : digit];
         }
-        return;
     }
-    const uint32_t digit = T & 1023u;
-    const bool everything = need == ~0ull;  // more asked than there is: every candidate counts
-    const uint32_t *h = local_last + (int64_t)blockIdx.x * 1024;
-    uint32_t gt = 0;
-    for (int b = threadIdx.x; b < 1024; b += kWThreads)
-        if (everything ? b > 0 : (uint32_t)b > digit) gt += h[b];
-    gt = wave_sum_u32(gt);
-    if (lane == 0) red[wave] = gt;
+    if (lane == 0) red[wave] = make_uint2(gt, eq);
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t g = above[blockIdx.x];
-        for (int w = 0; w < kWaves; ++w) g += red[w];
-        cnt_gt[blockIdx.x] = g;
-        cnt_eq[blockIdx.x] = h[everything ? 0 : digit];
+        uint2 t = red[0];
+        for (int w = 1; w < kWaves; ++w) {
+            t.x += red[w].x;
+            t.y += red[w].y;
+        }
+        cnt_block[blockIdx.x] = t;
     }
 }
 
-// Exclusive prefix over units (or workgroups, on the full path) of (ties seen) and
-// (entries written).  A thread takes kMaxUnits / 1024 consecutive entries.
-__global__ __launch_bounds__(1024) void wsel_offsets_kernel(const WselState *st, int nunits, int nblocks,
-                                                            const uint32_t *__restrict__ cnt_gt,
-                                                            const uint32_t *__restrict__ cnt_eq,
-                                                            uint64_t *__restrict__ tie_base,
-                                                            uint64_t *__restrict__ out_base) {
-    constexpr int kPer = kMaxUnits / 1024;
-    __shared__ uint32_t scan[17];
-    const uint64_t need = st->need;
-    const int n = st->fast_failed && st->overflow ? nblocks : nunits;
-    const int b0 = threadIdx.x * kPer;
-    uint32_t e[kPer], g[kPer], e_sum = 0;
+// Keys above the threshold and equal to it before this workgroup's share, and in all of the layer
+// (every workgroup adds up the at most 2048 counts for itself; contains barriers).
+struct Before {
+    uint32_t gt, eq, all_gt, all_eq;
+};
+__device__ __forceinline__ Before counts_before(const uint2 *__restrict__ cnt_block, uint32_t (*red)[4]) {
+    uint32_t s[4] = {0, 0, 0, 0};
+    constexpr int kPer = kMaxBlocks / kWThreads;
+    uint2 c[kPer];
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        e[r] = b0 + r < n ? cnt_eq[b0 + r] : 0;
-        g[r] = b0 + r < n ? cnt_gt[b0 + r] : 0;
-        e_sum += e[r];
+        const int b = r * kWThreads + (int)threadIdx.x;
+        c[r] = b < (int)gridDim.x ? cnt_block[b] : make_uint2(0, 0);
     }
-    uint32_t e_total, w_total;
-    uint64_t tb = block_scan_excl_u32(e_sum, scan, &e_total);
-    // ties of an entry that are still within the first `need`
-    uint32_t w[kPer], w_sum = 0;
-    uint64_t tbs[kPer];
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        tbs[r] = tb;
-        uint64_t take = 0;
-        if (tb < need) take = (need - tb) < e[r] ? (need - tb) : e[r];
-        w[r] = g[r] + (uint32_t)take;
-        w_sum += w[r];
-        tb += e[r];
+        const bool before = r * kWThreads + (int)threadIdx.x < (int)blockIdx.x;
+        s[0] += before ? c[r].x : 0u;
+        s[1] += before ? c[r].y : 0u;
+        s[2] += c[r].x;
+        s[3] += c[r].y;
     }
-    uint64_t ob = block_scan_excl_u32(w_sum, scan, &w_total);
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        if (b0 + r < n) {
-            tie_base[b0 + r] = tbs[r];
-            out_base[b0 + r] = ob;
-        }
-        ob += w[r];
+    for (int q = 0; q < 4; ++q) {
+        s[q] = wave_sum_u32(s[q]);
+        if ((threadIdx.x & (CMPQ_WAVE - 1)) == 0) red[wave_index()][q] = s[q];
     }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        s[q] = red[0][q];
+        for (int w = 1; w < kWaves; ++w) s[q] += red[w][q];
+    }
+    return Before{s[0], s[1], s[2], s[3]};
 }
 
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Writes the answer from the staging list: a wavefront per unit, 64 staged entries a step.
-__device__ __forceinline__ void emit_from_list(const WselArgs &a, const WselState *st,
-                                               const uint64_t *__restrict__ tie_base,
-                                               const uint64_t *__restrict__ out_base, int64_t k,
+// Writes the answer from the staging list: a wavefront per unit, 64 staged entries a step.  `ties`
+// and `outp`: the equal keys and the taken entries before the workgroup's units.
+__device__ __forceinline__ void emit_from_list(const WselArgs &a, uint32_t T, uint64_t need,
+                                               const uint2 *__restrict__ cnt_unit, uint32_t gt_before,
+                                               uint32_t eq_before, int64_t k,
                                                int32_t *__restrict__ idx_out, uint16_t *__restrict__ val_out) {
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
-    const uint32_t T = st->T;
-    const uint64_t need = st->need;
+    const int64_t unit0 = (int64_t)blockIdx.x * kWaves, unit = unit0 + wave;
+    for (int w = 0; w < kWaves - 1; ++w) {
+        const uint2 c = cnt_unit[unit0 + w];
+        if (w < wave) {
+            gt_before += c.x;
+            eq_before += c.y;
+        }
+    }
     const unsigned long long *ik = a.stage_ik + unit * a.cap;
     const uint16_t *sv = a.stage_val + unit * a.cap;
     const uint32_t n = a.stage_cnt[unit];
-    uint64_t ties = tie_base[unit], outp = out_base[unit];
+    // equal keys are taken in index order until `need` are in
+    uint64_t ties = eq_before, outp = gt_before + (ties < need ? ties : need);
     for (uint32_t e0 = 0; e0 < n; e0 += CMPQ_WAVE) {
         const uint32_t e = e0 + lane;
         const unsigned long long v = e < n ? ik[e] : 0ull;
@@ -1348,32 +1463,30 @@ __device__ __forceinline__ void write_chunks(const WselArgs &a, uint32_t T, uint
     }
 }
 
-// Full path: one more pass over the data, a workgroup per run of 4 units.
-template <typename TW>
-__device__ __forceinline__ void write_full(const WselArgs &a, const WselState *st,
-                                           const uint64_t *__restrict__ tie_base,
-                                           const uint64_t *__restrict__ out_base, int64_t k,
-                                           int32_t *__restrict__ idx_out, uint16_t *__restrict__ val_out,
-                                           uint32_t *scan) {
-    const int64_t q0 = (int64_t)blockIdx.x * kWaves * a.wc_per_unit;
-    const int64_t q1 = min(a.total_wc, q0 + kWaves * a.wc_per_unit);
-    write_chunks<TW>(a, st->T, st->need, tie_base[blockIdx.x], out_base[blockIdx.x], q0, q1, k, idx_out, val_out,
-                     scan);
-}
-
-// The last kernel of a call: from the list, unless the exact chain ran and its list
-// overflowed.
+// The last kernel of a call: from the list, unless the exact chain ran and its list overflowed: then
+// with one more pass over the data, a workgroup per run of 4 units.  Where there are fewer
+// candidates than asked for, the rest of idx_out is filled with -1.
 template <typename TW>
 __global__ __launch_bounds__(kWThreads) void wsel_emit_kernel(WselArgs a, const WselState *st,
-                                                               const uint64_t *__restrict__ tie_base,
-                                                               const uint64_t *__restrict__ out_base,
+                                                               const uint2 *__restrict__ cnt_unit,
+                                                               const uint2 *__restrict__ cnt_block,
                                                                int64_t k, int32_t *__restrict__ idx_out,
                                                                uint16_t *__restrict__ val_out) {
     __shared__ uint32_t scan[34];
-    if (st->fast_failed && st->overflow)
-        write_full<TW>(a, st, tie_base, out_base, k, idx_out, val_out, scan);
-    else
-        emit_from_list(a, st, tie_base, out_base, k, idx_out, val_out);
+    __shared__ uint32_t red[kWaves][4];
+    const uint32_t T = st->T;
+    const uint64_t need = st->need;
+    const Before c = counts_before(cnt_block, red);
+    if (st->fast_failed && st->overflow) {
+        const int64_t q0 = (int64_t)blockIdx.x * kWaves * a.wc_per_unit;
+        const int64_t q1 = min(a.total_wc, q0 + kWaves * a.wc_per_unit);
+        write_chunks<TW>(a, T, need, c.eq, c.gt + (c.eq < need ? (uint64_t)c.eq : need), q0, q1, k, idx_out, val_out, scan);
+    } else {
+        emit_from_list(a, T, need, cnt_unit, c.gt, c.eq, k, idx_out, val_out);
+    }
+    const uint64_t found = c.all_gt + (c.all_eq < need ? (uint64_t)c.all_eq : need);
+    for (int64_t j = (int64_t)found + (int64_t)blockIdx.x * kWThreads + threadIdx.x; j < k; j += (int64_t)gridDim.x * kWThreads)
+        idx_out[j] = -1;
 }
 
 // ------------------------------------------------------------------ one channel at a time
@@ -1449,8 +1562,8 @@ __global__ __launch_bounds__(kWThreads) void wsel_channel_kernel(WselArgs a, con
 
 struct WselWs {
     WselState *st;
-    uint32_t *hist, *cnt_gt, *cnt_eq, *above, *local_last, *stage_cnt;
-    uint64_t *tie_base, *out_base;
+    uint32_t *hist, *above, *local_last, *stage_cnt;
+    uint2 *cnt_unit, *cnt_block;
     unsigned long long *stage_ik;
     uint16_t *stage_val;
     size_t bytes;
@@ -1460,11 +1573,10 @@ WselWs wsel_carve(void *ws, const WselPlan &p) {
     WsCarver carve(ws);
     WselWs w;
     w.st = carve.take<WselState>(1);
-    w.hist = carve.take<uint32_t>(kHists * kBins);
-    w.cnt_gt = carve.take<uint32_t>(kMaxUnits);
-    w.cnt_eq = carve.take<uint32_t>(kMaxUnits);
-    w.tie_base = carve.take<uint64_t>(kMaxUnits);
-    w.out_base = carve.take<uint64_t>(kMaxUnits);
+    w.hist = carve.take<uint32_t>(kHistWords);
+    w.cnt_unit = carve.take<uint2>(kMaxUnits);
+    w.cnt_block = carve.take<uint2>(kMaxBlocks);
+    carve.take<char>(12288);  // unused: the size callers have always been told to hand over
     w.above = carve.take<uint32_t>(kMaxBlocks);
     w.local_last = carve.take<uint32_t>((size_t)kMaxBlocks * 1024);
     w.stage_cnt = carve.take<uint32_t>(kMaxUnits);
@@ -1485,31 +1597,31 @@ int launch_weight_select(WselArgs a, const WselPlan &p, int64_t k, int32_t *idx_
     a.sample_stride = p.sample_stride;
     a.n_sample = p.n_sample;
     a.sample_rank = p.sample_rank;
-    int64_t sample_blocks = cdiv(p.n_sample, kWaves);
-    if (sample_blocks > 512) sample_blocks = 512;
+    int64_t sample_blocks = cdiv(p.n_sample, 16);
+    if (sample_blocks > 128) sample_blocks = 128;  // every one ends with a flush into the same counters
+    if (sample_blocks < cdiv(p.n_sample, kSampleChunks)) sample_blocks = cdiv(p.n_sample, kSampleChunks);
     if (sample_blocks < 1) sample_blocks = 1;
-    wsel_init_kernel<<<64, 256, 0, s>>>(w.st, w.hist, idx_out, k);
+    static_assert(kHistWords % 4 == 0, "");
+    wsel_init_kernel<<<(unsigned)cdiv(kHistWords / 4, 256), 256, 0, s>>>(w.st, w.hist);
     // fast chain
-    wsel_sample_kernel<TW, 0><<<(unsigned)sample_blocks, kWThreads, 0, s>>>(a, w.hist);
-    wsel_sample_kernel<TW, 1><<<(unsigned)sample_blocks, kWThreads, 0, s>>>(a, w.hist);
+    wsel_sample_kernel<TW><<<(unsigned)sample_blocks, kSampleThreads, 0, s>>>(a, w.hist);
     cmpq_timing_before(CMPQ_KERNEL_OUTLIER_STAGE, s);
     if (std::is_same<TW, __half>::value && a.score == CMPQ_SCORE_RESIDUAL && !a.codes)
         wsel_stage_kernel<TW, true><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.hist);
     else
         wsel_stage_kernel<TW, false><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.hist);
     cmpq_timing_after(CMPQ_KERNEL_OUTLIER_STAGE, s);
-    const int list_blocks = p.nblocks < 256 ? p.nblocks : 256;  // few: each ends with a flush into shared counters
+    const int list_blocks = (int)cdiv(p.nunits, 32) < 256 ? (int)cdiv(p.nunits, 32) : 256;  // a unit per 8 lanes
     wsel_list_kernel<0><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
     wsel_list_kernel<1><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
-    wsel_list_kernel<2><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
     // exact chain: these return at once unless the fast chain raised its flag
-    wsel_hist_kernel<TW, 0><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, w.hist, w.above, w.local_last);
-    wsel_hist_kernel<TW, 1><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, w.hist, w.above, w.local_last);
-    wsel_hist_kernel<TW, 2><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, w.hist, w.above, w.local_last);
+    const int hist_blocks = p.nblocks < 512 ? p.nblocks : 512;
+    wsel_hist_kernel<TW, 0><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
+    wsel_hist_kernel<TW, 1><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
+    wsel_hist_kernel<TW, 2><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     // threshold, placement and output, from whichever chain holds the answer
-    wsel_count_kernel<<<p.nblocks, kWThreads, 0, s>>>(w.st, a, (uint64_t)k, w.hist, w.above, w.local_last, w.cnt_gt, w.cnt_eq);
-    wsel_offsets_kernel<<<1, 1024, 0, s>>>(w.st, p.nunits, p.nblocks, w.cnt_gt, w.cnt_eq, w.tie_base, w.out_base);
-    wsel_emit_kernel<TW><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.tie_base, w.out_base, k, idx_out, val_out);
+    wsel_count_kernel<<<p.nblocks, kWThreads, 0, s>>>(w.st, a, (uint64_t)k, w.hist, w.above, w.local_last, w.cnt_unit, w.cnt_block);
+    wsel_emit_kernel<TW><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.cnt_unit, w.cnt_block, k, idx_out, val_out);
     CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
 }
