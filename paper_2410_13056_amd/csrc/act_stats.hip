@@ -142,8 +142,20 @@ __global__ __launch_bounds__(kThreads) void act_stats_finish_kernel(
     const int per = (splits + kWaves - 1) / kWaves;
     const int s0 = wave * per, s1 = min(splits, s0 + per);
     double t = 0.0;
-    if (col < d_in)
-        for (int sidx = s0; sidx < s1; ++sidx) t = combine<NORM>(t, partial[(int64_t)sidx * d_in + col]);
+    // 16 partials on their way at a time, added in split order all the same (4096 columns, 256 splits:
+    // 20.8 us one load after the other, 5.7 us so)
+    if (col < d_in) {
+        constexpr int U = 16;
+        int sidx = s0;
+        for (; sidx + U <= s1; sidx += U) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = partial[(int64_t)(sidx + u) * d_in + col];
+#pragma unroll
+            for (int u = 0; u < U; ++u) t = combine<NORM>(t, v[u]);
+        }
+        for (; sidx < s1; ++sidx) t = combine<NORM>(t, partial[(int64_t)sidx * d_in + col]);
+    }
     red[wave][lane] = t;
     __syncthreads();
     if (wave == 0 && col < d_in) {
