@@ -135,6 +135,185 @@ __global__ __launch_bounds__(kSelThreads) void allocate_bits_kernel(
     }
 }
 
+// The same two rankings for up to 8192 channels: every thread keeps PER consecutive keys in
+// registers, so the statistic is read once, a digit is 11 bits (three passes, and fewer lanes on one
+// counter), and the output takes one scan instead of one per 1024 channels.  These kernels are one
+// workgroup's chain of dependent steps: what counts is how many there are (8192 channels: top
+// channels 16.4 -> 6.8 us, allocation 20.8 -> 7.4 us; 512 threads of 16 keys 7.9 and 11.1, 256 of 32
+// keys 12.2 and 17.8).  1024 threads of 32 keys, for 32768 channels, need 116 registers and waited
+// 0.8 ms for a compute unit that K-means on other streams had left empty, so larger counts stay with
+// the kernels above.
+constexpr int kRankThreads = 1024, kRankPer = 8;
+
+struct RankShared {
+    uint32_t hist[2048];
+    uint32_t scan[34];
+    uint32_t prefix, rem;
+};
+
+template <int PER>
+struct RankKeys {
+    uint32_t key[PER];
+    uint32_t live;  // bit r: entry r takes part
+
+    __device__ __forceinline__ void load(const float *__restrict__ stat, const uint8_t *__restrict__ skip, int d) {
+        const int i0 = (int)threadIdx.x * PER;
+        float f[PER];
+        uint8_t m[PER];
+        const bool whole = i0 + PER <= d;
+        if (whole && reinterpret_cast<uintptr_t>(stat) % 16 == 0) {
+#pragma unroll
+            for (int q = 0; q < PER / 4; ++q) {
+                const float4 v = reinterpret_cast<const float4 *>(stat + i0)[q];
+                f[4 * q] = v.x, f[4 * q + 1] = v.y, f[4 * q + 2] = v.z, f[4 * q + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < PER; ++r) f[r] = i0 + r < d ? stat[i0 + r] : 0.f;
+        }
+        if (!skip) {
+#pragma unroll
+            for (int r = 0; r < PER; ++r) m[r] = 0;
+        } else if (whole && reinterpret_cast<uintptr_t>(skip) % 8 == 0) {
+#pragma unroll
+            for (int q = 0; q < PER / 8; ++q) reinterpret_cast<uint2 *>(m)[q] = reinterpret_cast<const uint2 *>(skip + i0)[q];
+        } else {
+#pragma unroll
+            for (int r = 0; r < PER; ++r) m[r] = i0 + r < d ? skip[i0 + r] : 0;
+        }
+        live = 0;
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            key[r] = stat_key(f[r]);
+            live |= (uint32_t)(i0 + r < d && !m[r]) << r;
+        }
+    }
+
+    // block_kth_largest over the live keys.
+    __device__ __forceinline__ void kth_largest(uint32_t k, RankShared &sh, uint32_t &T, uint32_t &need) const {
+        if (k == 0) {  // nothing: no key exceeds the all-ones pattern
+            T = 0xffffffffu;
+            need = 0;
+            return;
+        }
+        uint32_t prefix = 0, have = 0, rem = k;
+#pragma unroll
+        for (int pass = 0; pass < 3; ++pass) {
+            const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+            const uint32_t digit_mask = pass == 2 ? 1023u : 2047u;
+            constexpr int kBinsPer = 2048 / kRankThreads;
+#pragma unroll
+            for (int q = 0; q < kBinsPer; ++q) sh.hist[threadIdx.x + q * kRankThreads] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < PER; ++r)
+                if (((live >> r) & 1u) && (key[r] & have) == prefix) atomicAdd(&sh.hist[(key[r] >> shift) & digit_mask], 1u);
+            __syncthreads();
+            // thread t looks at the digits 2047 - 8 t and down, and owns the one the rank falls in
+            const int top = 2047 - kBinsPer * (int)threadIdx.x;
+            uint32_t v[kBinsPer], sum = 0, total;
+#pragma unroll
+            for (int q = 0; q < kBinsPer; ++q) sum += v[q] = sh.hist[top - q];
+            uint32_t before = block_scan_excl_u32(sum, sh.scan, &total);
+#pragma unroll
+            for (int q = 0; q < kBinsPer; ++q) {
+                if (before < rem && rem <= before + v[q]) {
+                    sh.rem = rem - before;
+                    sh.prefix = prefix | ((uint32_t)(top - q) << shift);
+                }
+                before += v[q];
+            }
+            have |= digit_mask << shift;
+            __syncthreads();
+            prefix = sh.prefix;
+            rem = sh.rem;
+            __syncthreads();
+        }
+        T = prefix;
+        need = rem;
+    }
+};
+
+// PER bytes of this thread's channels, at any alignment and up to the last channel.
+template <int PER>
+__device__ __forceinline__ void store_bytes(uint8_t *__restrict__ dst, const uint8_t (&v)[PER], int d) {
+    const int i0 = (int)threadIdx.x * PER;
+    if (i0 + PER <= d && reinterpret_cast<uintptr_t>(dst) % 8 == 0) {
+#pragma unroll
+        for (int q = 0; q < PER / 8; ++q) reinterpret_cast<uint2 *>(dst + i0)[q] = reinterpret_cast<const uint2 *>(v)[q];
+    } else {
+#pragma unroll
+        for (int r = 0; r < PER; ++r)
+            if (i0 + r < d) dst[i0 + r] = v[r];
+    }
+}
+
+template <int PER>
+__global__ __launch_bounds__(kRankThreads) void top_channels_reg_kernel(const float *__restrict__ sumsq, int d_in,
+                                                                        uint32_t k, int32_t *__restrict__ idx_out,
+                                                                        uint8_t *__restrict__ mask_out) {
+    __shared__ RankShared sh;
+    RankKeys<PER> a;
+    a.load(sumsq, nullptr, d_in);
+    uint32_t T, need;
+    a.kth_largest(k, sh, T, need);
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const uint32_t in = (a.live >> r) & 1u;
+        gt += in && a.key[r] > T;
+        eq += in && a.key[r] == T;
+    }
+    uint32_t gt_before, eq_before, gt_all, eq_all;
+    block_scan_excl_2xu32(gt, eq, sh.scan, gt_before, eq_before, gt_all, eq_all);
+    // equal keys are taken in index order until `need` are in
+    uint32_t pos = gt_before + min(eq_before, need);
+    __align__(8) uint8_t taken[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const bool in = (a.live >> r) & 1u, tie = in && a.key[r] == T;
+        const bool sel = (in && a.key[r] > T) || (tie && eq_before < need);
+        eq_before += tie;
+        if (sel && idx_out) idx_out[pos] = (int)threadIdx.x * PER + r;
+        pos += sel;
+        taken[r] = sel;
+    }
+    if (mask_out) store_bytes<PER>(mask_out, taken, d_in);
+}
+
+template <int PER>
+__global__ __launch_bounds__(kRankThreads) void allocate_bits_reg_kernel(
+    const float *__restrict__ sumsq, int d_in, const uint8_t *__restrict__ chan_mask, uint32_t k_hi, uint32_t k_mid,
+    int all_mid, int w_hi, int w_mid, int w_lo, uint8_t *__restrict__ bits) {
+    __shared__ RankShared sh;
+    RankKeys<PER> a;
+    a.load(sumsq, chan_mask, d_in);
+    uint32_t T1, need1, T2 = 0, need2 = 0;
+    a.kth_largest(k_hi, sh, T1, need1);
+    if (!all_mid) a.kth_largest(k_mid, sh, T2, need2);
+    uint32_t eq1 = 0, eq2 = 0;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const uint32_t in = (a.live >> r) & 1u;
+        eq1 += in && a.key[r] == T1;
+        eq2 += in && !all_mid && a.key[r] == T2;
+    }
+    uint32_t before1, before2, all1, all2;
+    block_scan_excl_2xu32(eq1, eq2, sh.scan, before1, before2, all1, all2);
+    __align__(8) uint8_t w[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const bool in = (a.live >> r) & 1u, tie1 = in && a.key[r] == T1, tie2 = in && !all_mid && a.key[r] == T2;
+        if (!in) w[r] = CMPQ_PROTECTED;
+        else if (a.key[r] > T1 || (tie1 && before1 < need1)) w[r] = (uint8_t)w_hi;
+        else if (all_mid || a.key[r] > T2 || (tie2 && before2 < need2)) w[r] = (uint8_t)w_mid;
+        else w[r] = (uint8_t)w_lo;
+        before1 += tie1;
+        before2 += tie2;
+    }
+    store_bytes<PER>(bits, w, d_in);
+}
+
 // ------------------------------------------------------------------ whole layer, d_in*d_out keys
 //
 // Top-k of the scores of a whole layer, written in ascending linear index.  The data is
@@ -1694,8 +1873,13 @@ extern "C" int cmpq_allocate_bits(const float *sumsq, int64_t d_in, const uint8_
         if (d_eff - k_mid > 0) counts_host[w_lo - lo] += d_eff - k_mid;
     }
     if (d_in == 0) return CMPQ_OK;
-    allocate_bits_kernel<<<1, kSelThreads, 0, static_cast<hipStream_t>(stream)>>>(
-        sumsq, d_in, chan_mask, (uint32_t)k_hi, (uint32_t)k_mid, all_mid, w_hi, w_mid, w_lo, bits);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (d_in <= kRankPer * kRankThreads)
+        allocate_bits_reg_kernel<kRankPer><<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, chan_mask, (uint32_t)k_hi,
+                                                                       (uint32_t)k_mid, all_mid, w_hi, w_mid, w_lo, bits);
+    else
+        allocate_bits_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, chan_mask, (uint32_t)k_hi, (uint32_t)k_mid, all_mid,
+                                                       w_hi, w_mid, w_lo, bits);
     CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
 }
@@ -1713,7 +1897,10 @@ extern "C" int cmpq_extract_outliers(int mode, int score, int scope, const float
         if (d_in >= (int64_t)1 << 31) return CMPQ_ESHAPE;
         if (k > d_in) return CMPQ_ECOUNT;
         if (d_in == 0) return CMPQ_OK;
-        top_channels_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, (uint32_t)k, idx_out, chan_mask_out);
+        if (d_in <= kRankPer * kRankThreads)
+            top_channels_reg_kernel<kRankPer><<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, (uint32_t)k, idx_out, chan_mask_out);
+        else
+            top_channels_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, (uint32_t)k, idx_out, chan_mask_out);
         CMPQ_LAUNCH_CHECK();
         return CMPQ_OK;
     }
