@@ -81,13 +81,25 @@ __device__ __forceinline__ void zero_codes(uint8_t *row, int n_groups, int d_out
     for (int g = threadIdx.x; g < n_groups; g += T) store_codes<RAGGED>(row, g, d_out, 0);
 }
 
+// One word per bucket (dynamic LDS): where the bucket's stretch of the byte array begins, and above
+// it the exclusive prefix over buckets of the counts (both stay below 2^16).  While the places are
+// scattered the low half is the bucket's cursor; after the rounds the words hold the coding table.
+// The last bucket lies past the finite values: it is empty, and stretch_end() asks for no entry past
+// the table.  (Two 16-bit tables and a cursor of their own, 4 bytes a bucket more, let a compute unit hold 13
+// workgroups of 64 lanes at 1024 weights where these let it hold 16: the layer of 8192 such channels
+// took 331 us and takes 316, 4096x4096 took 605 and takes 599.)
+__device__ __forceinline__ uint32_t stretch_of(uint32_t word) { return word & 0xffffu; }
+__device__ __forceinline__ uint32_t before_of(uint32_t word) { return word >> 16; }
+template <int LB>
+__device__ __forceinline__ uint32_t stretch_end(const uint32_t *words, uint32_t bucket) {
+    return stretch_of(words[min(bucket + 1u, (1u << (16 - LB)) - 1u)]);
+}
+
 template <int LB>
 struct BucketShared {
     static constexpr int kBuckets = 1 << (16 - LB);
     long long scum[kBuckets + 1];   // count << 32 | sum of places; then the exclusive prefix
                                     // over buckets of sum(x * 2^24)
-    uint16_t ncum[kBuckets + 2];    // exclusive prefix over buckets of the counts
-    uint16_t start[kBuckets + 2];   // where a bucket's stretch of the byte array begins
     uint32_t part_n[2][CMPQ_KMAX];  // by round parity, per boundary: kept weights of its bucket
     uint32_t part_l[2][CMPQ_KMAX];  //   not above it, and the sum of their places
     float cent[CMPQ_KMAX];          // levels by level index
@@ -97,6 +109,7 @@ struct BucketShared {
     uint32_t scan32[17];
     unsigned long long scan64[17];
     int seg_lo, n_excl;
+    uint32_t kept;                  // weights that take part
     double cent64[CMPQ_KMAX];       // final levels by level index, as the error sum reads them
 };
 
@@ -179,7 +192,7 @@ __device__ __forceinline__ void scatter_places(const uint32_t (&keys)[2 * G], co
             for (int e = 0; e < 4; ++e) {
                 if (!MASKED || ((kept >> e) & 1u)) {
                     const uint32_t key = elem_key<G>(keys, k, e);
-                    const uint32_t pos = atomicAdd(&cursor[key >> LB], 1u);
+                    const uint32_t pos = stretch_of(atomicAdd(&cursor[key >> LB], 1u));
                     arr[pos] = (unsigned char)(key & ((1u << LB) - 1));
                 }
             }
@@ -396,14 +409,14 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
                 while (lo < hi_b) {
                     const int step = (hi_b - lo + L - 1) / L;
                     const int probe = min(lo + (sub + 1) * step, hi_b);
-                    const unsigned long long pass = __ballot(sm.ncum[probe] <= r) >> g0;
+                    const unsigned long long pass = __ballot(before_of(tbl[probe]) <= r) >> g0;
                     const int c_pass = __popcll(L < 64 ? pass & ((1ull << L) - 1) : pass);
                     const int nlo = c_pass > 0 ? min(lo + c_pass * step, hi_b) : lo;
                     if (c_pass < L) hi_b = min(lo + (c_pass + 1) * step, hi_b) - 1;
                     lo = nlo;
                 }
-                const uint32_t b = (uint32_t)lo, r_in = r - sm.ncum[b];
-                const uint32_t begin = sm.start[b], end = sm.start[b + 1];
+                const uint32_t b = (uint32_t)lo, word = tbl[b], r_in = r - before_of(word);
+                const uint32_t begin = stretch_of(word), end = stretch_end<LB>(tbl, b);
                 // smallest place with more than r_in weights at or below it: bisection on the place.
                 // The bucket's words are fetched once (4 per lane) when they fit; the counting
                 // scans of the bisection then run on registers.
@@ -494,7 +507,7 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
             uint32_t n = 0, l = 0;
             if (t != kKeyInf) {
                 const uint32_t b = t >> kLowBits;
-                scan_bucket<LR, UR>(arr, sm.start[b], sm.start[b + 1], t & (kLows - 1), n, l);
+                scan_bucket<LR, UR>(arr, stretch_of(tbl[b]), stretch_end<LB>(tbl, b), t & (kLows - 1), n, l);
             }
             if ((tid & (LR - 1)) == 0) {
                 sm.part_n[par][p_mine] = n;
@@ -510,7 +523,7 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
         if (lane < K - 1 && tk != kKeyInf) {
             const uint32_t b = tk >> kLowBits;
             const uint32_t cnt = sm.part_n[par][lane];
-            n_below = sm.ncum[b] + cnt;
+            n_below = before_of(tbl[b]) + cnt;
             s_below = sm.scum[b] + bucket_sum<LB>(b, cnt, sm.part_l[par][lane]);
         }
         // sorted positions live in lanes 0..15, one DPP row: neighbours come by row shifts
@@ -712,7 +725,7 @@ void kmeans_bucket_kernel(KmArgs a) {
     constexpr bool kCodesFused = MODE != kModePlain;
     // dynamic LDS: places of the kept weights, ordered by bucket (a byte each; the bucket
     // follows from the position) | removed-entry bitmap (one bit per weight) | the scatter
-    // cursors, later the coding table
+    // words of the buckets, later the coding table
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ BucketShared<LB> sm;
     const int64_t i = blockIdx.x;
@@ -878,9 +891,7 @@ void kmeans_bucket_kernel(KmArgs a) {
                     const uint32_t n = (uint32_t)(packed >> 32);
                     const uint32_t n_place = MODE == kModeReuse ? n_orig[r] : n;
                     const long long sb = bucket_sum<LB>((uint32_t)(b0 + r), n, (uint32_t)packed);
-                    sm.ncum[b0 + r] = (uint16_t)(n_run & 0xffffu);
-                    sm.start[b0 + r] = (uint16_t)(n_run >> 16);
-                    cursor[b0 + r] = n_run >> 16;  // where the next place of the bucket goes
+                    cursor[b0 + r] = (n_run << 16) | (n_run >> 16);
                     sm.scum[b0 + r] = s_run;
                     n_run += n | (((n_place + 3) & ~3u) << 16);
                     s_run += sb;
@@ -888,13 +899,12 @@ void kmeans_bucket_kernel(KmArgs a) {
             }
         }
         if (tid == 0) {
-            sm.ncum[kBuckets] = (uint16_t)(n_tot & 0xffffu);
-            sm.start[kBuckets] = (uint16_t)(n_tot >> 16);
+            sm.kept = n_tot & 0xffffu;
             sm.scum[kBuckets] = (long long)s_tot;
         }
     }
     __syncthreads();
-    const uint32_t M = sm.ncum[kBuckets];
+    const uint32_t M = sm.kept;
     if constexpr (MODE == kModeReuse) {
         // ---- one place byte per entry of O_q becomes a filler
         if (n_ex > 0) {
@@ -904,7 +914,8 @@ void kmeans_bucket_kernel(KmArgs a) {
                 const uint32_t key =
                     e == tid ? first_key : key_of_half(__half_as_ushort(wrow_h[ex_idx[e] - chan_base]));
                 const uint32_t bk = key >> LB;
-                blank_one_place(reinterpret_cast<uint32_t *>(arr), sm.start[bk] >> 2, sm.start[bk + 1] >> 2,
+                blank_one_place(reinterpret_cast<uint32_t *>(arr), stretch_of(cursor[bk]) >> 2,
+                                stretch_end<LB>(cursor, bk) >> 2,
                                 key & ((1u << LB) - 1));
             }
         }
@@ -912,6 +923,20 @@ void kmeans_bucket_kernel(KmArgs a) {
         // ---- scatter the places of the kept weights, ordered by bucket
         if (RAGGED || n_ex > 0) scatter_places<G, T, LB, true>(keys, removed, cursor, arr, n_groups);
         else scatter_places<G, T, LB, false>(keys, removed, cursor, arr, n_groups);
+        __syncthreads();
+        // the cursors go back to where their stretches begin (a neighbour may read a word while its low
+        // half changes: it wants the upper half)
+        if (b0 < kBuckets) {
+            uint32_t word = cursor[b0];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                if (r < per) {
+                    const uint32_t next = b0 + r + 1 < kBuckets ? cursor[b0 + r + 1] : word;
+                    cursor[b0 + r] = word - (before_of(next) - before_of(word));
+                    word = next;
+                }
+            }
+        }
     }
     __syncthreads();
     if (keep) {  // the arrangement as it stands, for a later run on this channel
