@@ -224,16 +224,44 @@ __device__ void quantile_start(KmSmall &sm, int K, int d_out, const TW *xs, cons
                 if (sm.q_leader[j] == j && sm.q_prefix[j] == hi) atomicAdd(&hist[j * 256 + digit], 1u);
         }
         __syncthreads();
-        if (tid < K) {
-            const uint32_t *h = hist + sm.q_leader[tid] * 256;
-            uint32_t rank = sm.q_rank[tid], cum = 0;
+        // 16 lanes per rank, 16 digits each: where the running count passes the rank.  (One lane
+        // per rank and a chain of up to 255 dependent LDS reads in each of the four passes took
+        // more than half the time of a short fp32 channel: 256 channels of 512 weights, 10 rounds,
+        // took 94 us and take 40.)
+        static_assert(kT == 16 * CMPQ_KMAX, "16 lanes for every rank");
+        const int j = tid >> 4, sub = tid & 15;
+        const uint4 *h = reinterpret_cast<const uint4 *>(hist + (j < K ? sm.q_leader[j] : 0) * 256) + 4 * sub;
+        const uint32_t rank = j < K ? sm.q_rank[j] : 0u;
+        const uint32_t prefix = j < K ? sm.q_prefix[j] : 0u;
+        uint32_t n[16];  // running count, this lane's digits
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint4 v = h[e];
+            n[4 * e] = v.x + (e > 0 ? n[4 * e - 1] : 0u);
+            n[4 * e + 1] = v.y + n[4 * e];
+            n[4 * e + 2] = v.z + n[4 * e + 1];
+            n[4 * e + 3] = v.w + n[4 * e + 2];
+        }
+        uint32_t upto = n[15];
+#pragma unroll
+        for (int s = 1; s < 16; s <<= 1) {
+            const uint32_t below = __shfl_up(upto, s, 16);
+            if (sub >= s) upto += below;
+        }
+        const uint32_t before = upto - n[15];
+        __syncthreads();  // every lane has read its rank and prefix
+        if (j < K && before <= rank && rank < upto) {
+            uint32_t cum = before;
             int b = 0;
-            for (; b < 255; ++b) {
-                if (cum + h[b] > rank) break;
-                cum += h[b];
+#pragma unroll
+            for (int e = 0; e < 15; ++e) {
+                if (before + n[e] <= rank) {
+                    cum = before + n[e];
+                    b = e + 1;
+                }
             }
-            sm.q_rank[tid] = rank - cum;
-            sm.q_prefix[tid] = (sm.q_prefix[tid] << 8) | (uint32_t)b;
+            sm.q_rank[j] = rank - cum;
+            sm.q_prefix[j] = (prefix << 8) | (uint32_t)(16 * sub + b);
         }
         __syncthreads();
     }
