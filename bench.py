@@ -34,7 +34,7 @@ HBM_PEAK_GBS = 8000.0
 # mean HBM bytes per k-means launch (FETCH_SIZE + WRITE_SIZE scaled by a plain copy of known
 # size) and mean vector-ALU instructions per k-means launch (SQ_INSTS_VALU, per wavefront).
 KMEANS_TRAFFIC_BYTES = {"block70b": 583.6e6}
-KMEANS_VALU_WAVE_INSTS_PER_STEP = {"block70b": 1.85e9}     # 14 launches
+KMEANS_VALU_WAVE_INSTS_PER_STEP = {"block70b": 1.87e9}     # 14 launches
 KMEANS_COUNTERS_FILE = "profiles/kmeans_bucket_block70b_counters.txt"
 
 
