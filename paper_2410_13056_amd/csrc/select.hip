@@ -1225,6 +1225,9 @@ __global__ __launch_bounds__(kWThreads) void wsel_stage_kernel(WselArgs a, WselS
             const int fine = (int)(8 * bin) + pick_of_8<kSets>(hist + kHistSample + kSampleFine / 8 + 8 * bin, rem, rem_in, count, kSampleSet);
             const float share = 1.0f - (float)rem_in / (float)(count ? count : 1);
             reach = ((uint32_t)fine << kSampleShift) + (uint32_t)(share * (float)((1 << kSampleShift) - 1));
+            // At most infinity: as the pattern of a NaN it would not stand in the floats' order below, and
+            // the list would hold keys beneath it, which its histogram has no place for.
+            reach = min(reach, 0x7f800000u);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) st->reach = reach;
