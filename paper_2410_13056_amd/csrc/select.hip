@@ -209,12 +209,18 @@ struct RankKeys {
             for (int r = 0; r < PER; ++r)
                 if (((live >> r) & 1u) && (key[r] & have) == prefix) atomicAdd(&sh.hist[(key[r] >> shift) & digit_mask], 1u);
             __syncthreads();
-            // thread t looks at the digits 2047 - 8 t and down, and owns the one the rank falls in
+            // thread t looks at the digits 2047 - 2 t and 2046 - 2 t, and owns the one the rank falls in
             const int top = 2047 - kBinsPer * (int)threadIdx.x;
             uint32_t v[kBinsPer], sum = 0, total;
 #pragma unroll
             for (int q = 0; q < kBinsPer; ++q) sum += v[q] = sh.hist[top - q];
             uint32_t before = block_scan_excl_u32(sum, sh.scan, &total);
+            // a rank past the last live key falls in no digit: digit 0 and the rank stay, and every live
+            // key is taken in the end, as in block_kth_largest
+            if (threadIdx.x == 0 && rem > total) {
+                sh.rem = rem;
+                sh.prefix = prefix;
+            }
 #pragma unroll
             for (int q = 0; q < kBinsPer; ++q) {
                 if (before < rem && rem <= before + v[q]) {

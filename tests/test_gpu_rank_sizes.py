@@ -56,3 +56,27 @@ def test_rankings_at_the_edges(d_in):
 
 def mask_of(want):
     return torch.from_numpy(want).to(DEV)
+
+
+@pytest.mark.parametrize("d_in", [300, 8192, 9000])
+def test_fewer_free_channels_than_ranks_asked_for(d_in):
+    """A mask that protects more channels than `n_protected` says leaves fewer channels than the counts
+    of the budget: ranks past the last free channel are not there, whichever kernel ranks (the register
+    kernel up to 8192 channels, the other beyond)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2410_13056_amd import binding as B
+    ws = B.Workspace(DEV)
+    stat = torch.arange(1, d_in + 1, dtype=torch.float32, device=DEV)
+    mask = torch.zeros(d_in, dtype=torch.uint8, device=DEV)
+    free = d_in // 4
+    mask[free:] = 1
+    order = np.argsort(-stat.cpu().numpy()[:free], kind="stable")
+    for avg in (3.5, 3.0):
+        bits = torch.zeros(d_in, dtype=torch.uint8, device=DEV)
+        B.allocate_bits(stat, mask, 2, (2, 3, 4), avg, bits, ws)
+        want = np.full(d_in, B.PROTECTED, np.uint8)
+        n_hi = free if avg > 3 else int(np.ceil(0.01 * (d_in - 2 - 1) - 1e-12))   # counted without the mask
+        want[order[:n_hi]] = 4
+        want[order[n_hi:]] = 3                                       # the second rank lies past the last
+        assert np.array_equal(bits.cpu().numpy(), want), avg
