@@ -73,3 +73,38 @@ def test_selection_among_nans(score, share_nan):
         taken = h.ravel()[want]
         exact = (taken & 0x7fff) <= 0x7c00
         assert np.array_equal(val.cpu().numpy().view(np.uint16)[exact], taken[exact]), k
+
+
+@pytest.mark.parametrize("dtype,d_in,d_out,codes", [(np.float16, 512, 2048, False), (np.float16, 300, 1027, True),
+                                                    (np.float32, 200, 1000, False)])
+@pytest.mark.parametrize("far", [1.5, 3.0, 20.0, 1e4])
+def test_selection_at_a_cliff(dtype, d_in, d_out, codes, far):
+    """As many far weights as are asked for, a few more and a few less: the k-th key lies on the cliff
+    or below it, `far` times the sampled guess (the list's histogram has fine bins up to twice the
+    guess and coarse ones beyond); the far weights are spread over a binary octave or all but tied."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle as orc
+    from paper_2410_13056_amd import binding as B
+    ws = B.Workspace(DEV)
+    rng = np.random.default_rng(d_in)
+    n = d_in * d_out
+    n_far = n // 100
+    W = rng.uniform(-0.02, 0.02, n)
+    at = rng.choice(n, n_far, replace=False)
+    for spread in (1.0, 0.001):
+        W[at] = np.sign(W[at]) * 0.02 * far * (1 + spread * rng.random(n_far))
+        Wt = W.astype(dtype).reshape(d_in, d_out)
+        bits = np.full(d_in, 2, np.uint8)
+        cent = np.full((d_in, 16), np.inf, np.float32)
+        cent[:, :4] = [-0.01, 0.0, 0.01, 1e-3]
+        code = np.abs(Wt[..., None].astype(np.float32) - cent[:, None, :4]).argmin(-1).astype(np.uint8) if codes else None
+        Wd, cd, bd = (torch.from_numpy(x).to(DEV) for x in (Wt, cent, bits))
+        kd = torch.from_numpy(code).to(DEV) if codes else None
+        for k in (n_far - 50, n_far - n_far // 20, n_far, n_far + 7, n_far // 8):
+            idx = torch.full((k,), -7, dtype=torch.int32, device=DEV)
+            val = torch.zeros(k, dtype=torch.float16, device=DEV)
+            B.extract_weight_outliers(Wd, cd, kd, bd, k, idx, val, ws)
+            oidx, oval = orc.weight_outliers(Wt, cent, code, bits, k)
+            assert np.array_equal(idx.cpu().numpy().astype(np.int64), oidx), (spread, k)
+            assert np.array_equal(val.cpu().numpy().view(np.uint16), oval), (spread, k)
