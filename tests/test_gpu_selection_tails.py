@@ -108,3 +108,29 @@ def test_selection_at_a_cliff(dtype, d_in, d_out, codes, far):
             oidx, oval = orc.weight_outliers(Wt, cent, code, bits, k)
             assert np.array_equal(idx.cpu().numpy().astype(np.int64), oidx), (spread, k)
             assert np.array_equal(val.cpu().numpy().view(np.uint16), oval), (spread, k)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(512, 2048), (300, 1027)])
+@pytest.mark.parametrize("step", [0.02 / 4, 0.02 / 16])
+def test_selection_among_few_values(d_in, d_out, step):
+    """Weights on a coarse grid: the k-th key is tied with many others and stands alone in its bin of
+    the sample, above an empty one or beside its neighbour on the grid."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2410_13056_amd import binding as B
+    ws = B.Workspace(DEV)
+    rng = np.random.default_rng(d_out)
+    W = (np.round(rng.normal(0, 0.02, (d_in, d_out)) / step) * step).astype(np.float16)
+    bits = torch.full((d_in,), 3, dtype=torch.uint8, device=DEV)
+    cent = torch.full((d_in, 16), float("inf"), device=DEV)
+    cent[:, :8] = torch.linspace(-0.04, 0.04, 8, device=DEV)
+    for score, key in ((B.SCORE_MAGNITUDE, np.abs(W.astype(np.float32))),
+                       (B.SCORE_RESIDUAL, np.abs(W.astype(np.float32)[..., None] - cent[0, :8].cpu().numpy()).min(-1))):
+        order = np.argsort(-key.ravel(), kind="stable")
+        for k in (W.size // 2000, W.size // 200, W.size // 100, W.size // 20):
+            idx = torch.full((k,), -7, dtype=torch.int32, device=DEV)
+            val = torch.zeros(k, dtype=torch.float16, device=DEV)
+            B.extract_weight_outliers(torch.from_numpy(W).to(DEV), cent, None, bits, k, idx, val, ws, score=score)
+            want = np.sort(order[:k])
+            assert np.array_equal(idx.cpu().numpy(), want), k
+            assert np.array_equal(val.cpu().numpy(), W.ravel()[want]), k
