@@ -762,10 +762,12 @@ __global__ __launch_bounds__(kThreads, 2) void weight_gemm_kernel(Group g) {
 #pragma unroll
     for (int u = 0; u < kBuffers - 1; ++u) load(u, u);
     for (int step = 0; step < steps; ++step) {
-        // the oldest step's 4 loads of this wavefront have landed (two later steps are under way),
-        // after the barrier everyone's have; the buffer read one step ago is free then
+        // The oldest step's 4 loads of this wavefront have landed (two later steps, 8 loads, are under
+        // way; any other load between them would only make the wait longer) and its LDS reads of the
+        // step before have returned.  After the barrier both hold for every wavefront: this step's
+        // buffer is full, and the one read a step ago, which is loaded next, is free.
         static_assert(kBuffers == 4, "the count of loads still under way");
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         load(step + kBuffers - 1, (step + kBuffers - 1) % kBuffers);

@@ -129,3 +129,19 @@ def test_kmeans_kernel_indices_stay_in_bounds_on_adversarial_channels():
         B.kmeans_launch_shape(32772)
     with np.testing.assert_raises(Exception):
         B.kmeans_launch_shape(6)
+
+
+def test_bare_barriers_state_both_waits():
+    """A bare s_barrier (unlike __syncthreads) waits for nothing: where buffers change hands at one, the
+    line before it has to wait for the wavefront's loads into LDS and for its reads from LDS."""
+    import glob
+    import re
+    csrc = os.path.join(ROOT, "paper_2410_13056_amd", "csrc")
+    found = 0
+    for path in glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.h")):
+        lines = open(path).read().splitlines()
+        for n, line in enumerate(lines):
+            if "__builtin_amdgcn_s_barrier()" in line:
+                found += 1
+                assert re.search(r'"s_waitcnt vmcnt\(\d+\) lgkmcnt\(0\)" ::: "memory"', lines[n - 1]), f"{path}:{n + 1}"
+    assert found == 1
