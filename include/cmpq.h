@@ -478,9 +478,14 @@ int cmpq_outliers_by_column(const int32_t *out_idx, const uint16_t *out_val, int
  * Products are exact and sums fp32: per output the products of the packed rows are summed over
  * slabs of rows of one width in a fixed order, then the O_act rows, then the column's O_q
  * entries.  Several tokens are multiplied together on the matrix cores (FP16 operands, fp32
- * sums, runs of at most 512 rows added up apart); with many tokens an entry of O_q replaces its
- * level before the product.  Which way is taken, and so the last bits of a result, depends on
- * m, d_in and d_out alone; the result is reproducible bit for bit.  Workspace: CMPQ_OP_LUT_MATVEC with n = m.
+ * sums, runs of at most 512 rows added up apart); with many tokens, where every channel is
+ * stored, an entry of O_q replaces its level before the product.  Which way is taken, and so the
+ * last bits of a result, depends on m, the layer's sizes and its counts of rows alone; the result
+ * is reproducible bit for bit.
+ * Workspace: CMPQ_OP_LUT_MATVEC with n = m (for one token its partial rows, for many tokens about
+ * the weight in FP16).  Less is enough where it holds what this layer takes, or the partial rows of
+ * every token; a layer that would be multiplied together but finds no room for it then goes token
+ * by token, which changes its last bits.
  * Limits: m <= 65535, d_out < 2^20.
  */
 int cmpq_lut_matvec(const void *X, int64_t m, int64_t d_in, int64_t ldx, int64_t d_out,
@@ -529,7 +534,7 @@ int cmpq_lut4_quantize(int mode, const float *centroids, const uint8_t *bits, in
  * launch and first-load latency; grouped, the short layers run beside the long ones.
  * Every field has the meaning of the argument of the same name of cmpq_lut_matvec; all
  * products of a group share the number of tokens m.  Results are bit-identical to one
- * cmpq_lut_matvec call per layer.
+ * cmpq_lut_matvec call per layer with the same workspace.
  * Workspace: the sum over the layers of cmpq_workspace_bytes(CMPQ_OP_LUT_MATVEC, d_in, d_out, m)
  * is always enough.  Limits: n_layers <= CMPQ_MAX_GROUP; those of cmpq_lut_matvec per layer; the
  * partial rows of all layers together stay below 65536 (CMPQ_ESHAPE beyond).
@@ -560,7 +565,8 @@ int cmpq_lut_matvec_group(const cmpq_deployed_layer *layers, int n_layers, int64
 /*
  * The same products with the packed rows added up in FP16 (Sec. 6 / Fig. 4: the paper's
  * kernel keeps FP16 throughout; cmpq_lut_matvec_group above adds in fp32).  Arguments, limits,
- * workspace and errors are those of cmpq_lut_matvec_group.  What differs:
+ * workspace and errors are those of cmpq_lut_matvec_group (the tokens go through the workspace as
+ * many at a time as it holds, one at least, with the same results).  What differs:
  *   - a product X[t,i] * level is rounded to FP16 (to nearest even);
  *   - the products of a run of R consecutive packed rows of one width (in the order of that
  *     width's chan_idx; R = 32, halved while that leaves fewer than 512 workgroups, down to

@@ -816,13 +816,20 @@ constexpr int64_t kDirectWeights = 4 << 20;
 
 int64_t max_steps(int64_t d_in) { return cdiv(d_in, (int64_t)kRowsPerStep) + kMaxSegs; }
 
+// Token tiles of a launch that multiplies while it decodes, and how many a wavefront takes at a time.
+int tiles_at_once(int64_t m) { return m > kTok ? 2 : 1; }
+int64_t padded_token_tiles(int64_t m) { return align_up((size_t)cdiv(m, (int64_t)kTok), tiles_at_once(m)); }
+
 // Slabs of a width's steps per tile and token tile: over all widths 384 workgroups (three for every
 // two compute units; 192 to 512 differ by less than 5 %), at least 2 steps per wavefront and at most
 // 8: longer runs of fp32 sums lose more than the token-by-token kernel.  Depends on the layer and m
 // alone, so that a layer gives the same bits in any group.
-void choose_slabs(Layer &L, int64_t token_groups) {
-    int64_t want = cdiv((int64_t)384, L.tiles * token_groups);
-    if (want > kMaxSlabs) want = kMaxSlabs;
+int64_t wanted_slabs(int64_t d_out, int64_t m) {
+    const int64_t want = cdiv((int64_t)384, cdiv(d_out, (int64_t)kTileOuts) * (padded_token_tiles(m) / tiles_at_once(m)));
+    return want < kMaxSlabs ? want : kMaxSlabs;
+}
+void choose_slabs(Layer &L, int64_t m) {
+    const int64_t want = wanted_slabs(L.d_out, m);
     L.slabs = 0;
     for (int j = 0; j < L.n_seg; ++j) {
         Seg &s = L.seg[j];
@@ -837,18 +844,39 @@ void choose_slabs(Layer &L, int64_t token_groups) {
     for (int j = L.n_seg; j < kMaxSegs; ++j) L.slab0[j] = INT_MAX;
 }
 
-// At least what choose_slabs gives.
-int64_t most_slabs(int64_t d_in) { return kMaxSlabs + 2 * kMaxSegs + cdiv(max_steps(d_in), (int64_t)kMaxRun * kWaves); }
+// At least what choose_slabs gives for any widths: the shares of `want`, rounded, and the least of each.
+int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
+    return wanted_slabs(d_out, m) + kMaxSegs + cdiv(max_steps(d_in), (int64_t)kMaxRun * kWaves) + kMaxSegs;
+}
 
 // Whether to decode the weight once into memory and multiply from there.  That costs 4 bytes of
 // traffic per weight and two launches, multiplying while decoding costs a decoding per 32 tokens;
 // measured (us, decode once | while decoding): 4096x4096, 256 tokens 74 | 66; 13824x5120 twice,
 // 96 tokens 169 | 152, each 32 tokens more 4 | 39.  Every channel has to have a row, so that an
 // entry of O_q always finds the weight it overrides.
+constexpr int64_t kManyTokens = 96, kManyProducts = (int64_t)8 << 30;
+bool enough_for_many(int64_t d_in, int64_t d_out, int64_t m) {
+    return m >= kManyTokens && m * d_in >= kManyProducts / d_out;
+}
 bool many_tokens(const cmpq_deployed_layer &L, int64_t m) {
     int64_t rows = L.k_act;
     for (int j = 0; j < L.n_set; ++j) rows += L.counts_host[j];
-    return m >= 96 && rows > 0 && rows == L.d_in && m * L.d_in >= ((int64_t)8 << 30) / L.d_out;
+    return rows > 0 && rows == L.d_in && enough_for_many(L.d_in, L.d_out, m);
+}
+
+// Tokens of a launch that multiplies while it decodes.  Past the line above (layers that are not
+// stored whole) the tokens go in parts of about the line, so that the partial results stay the size
+// they have there; and no grid or row of partial results grows past 2^28 for one layer.
+int64_t part_tokens(int64_t d_in, int64_t d_out, int64_t m) {
+    int64_t c = m;
+    if (enough_for_many(d_in, d_out, m)) {
+        c = (int64_t)align_up((size_t)cdiv(cdiv(kManyProducts, d_in), d_out), 32);
+        if (c < kManyTokens) c = kManyTokens;
+    }
+    int64_t most = ((int64_t)1 << 28) / (d_in > d_out ? d_in : d_out) / 32 * 32;
+    if (most < 32) most = 32;
+    if (c > most) c = most;
+    return c < m ? c : m;
 }
 
 size_t piece(size_t bytes) { return align_up(bytes, 256); }
@@ -865,71 +893,113 @@ bool lut_gemm_takes(int64_t d_in, int64_t d_out, int64_t m) {
 }
 
 size_t lut_gemm_ws_bytes(int64_t d_in, int64_t d_out, int64_t m) {
-    const int64_t tt = align_up((size_t)cdiv(m, (int64_t)kTok), 2), steps = max_steps(d_in), tiles = cdiv(d_out, (int64_t)kTileOuts);
-    size_t b = piece((size_t)tt * steps * 1024) + piece((size_t)tt * d_in * kTok * 2) + piece((size_t)d_in * 4);
-    const size_t part = piece((size_t)most_slabs(d_in) * m * d_out * 4);
-    const size_t dense = piece((size_t)steps * tiles * kOuts * 1024);
-    return b + (part > dense ? part : dense);
+    const int64_t steps = max_steps(d_in), tiles = cdiv(d_out, (int64_t)kTileOuts), part = part_tokens(d_in, d_out, m);
+    auto few = [&](int64_t n) -> size_t {
+        if (n == 0) return 0;
+        const int64_t tt = padded_token_tiles(n);
+        return piece((size_t)tt * steps * 1024) + piece((size_t)tt * d_in * kTok * 2) +
+               piece((size_t)most_slabs(d_in, d_out, n) * n * d_out * 4);
+    };
+    size_t b = few(part), last = few(m % part);
+    if (last > b) b = last;
+    if (enough_for_many(d_in, d_out, m)) {
+        const size_t dense = piece((size_t)cdiv(m, (int64_t)kTok) * steps * 1024) + piece((size_t)d_in * 4) +
+                             piece((size_t)steps * tiles * kOuts * 1024);
+        if (dense > b) b = dense;
+    }
+    return b;
+}
+
+namespace {
+
+// A layer as the kernels see it, its scratch from `base` on; returns the bytes of that.
+size_t plan_layer(const cmpq_deployed_layer &S, int64_t m, bool dense, char *base, Layer &L) {
+    L = Layer{};
+    int64_t steps = 0;
+    auto add = [&](const uint32_t *packed, const uint16_t *lut, const int32_t *chan, int64_t rows, int bits) {
+        if (rows <= 0) return;
+        Seg &g = L.seg[L.n_seg++];
+        g.packed = packed;
+        g.lut = lut;
+        g.chan = chan;
+        g.rows = (int)rows;
+        g.words_per_row = bits == kActBits ? 0 : (int)cdiv(S.d_out * bits, 32);
+        g.bits = bits;
+        g.step0 = (int)steps;
+        g.steps = (int)cdiv(rows, (int64_t)kRowsPerStep);
+        steps += g.steps;
+    };
+    for (int j = 0; j < S.n_set; ++j) add(S.packed[j], S.lut[j], S.chan_idx[j], S.counts_host[j], S.bit_set[j]);
+    add(nullptr, nullptr, S.act_idx, S.k_act, kActBits);
+    L.X = static_cast<const __half *>(S.X);
+    L.ldx = S.ldx;
+    L.W_act = reinterpret_cast<const __half *>(S.W_act);
+    L.ld_act = S.ld_act;
+    L.act_vec_ok = reinterpret_cast<uintptr_t>(S.W_act) % 16 == 0 && S.ld_act % 8 == 0;
+    L.colptr = S.colptr;
+    L.row_idx = S.row_idx;
+    L.delta = S.delta;
+    L.Y = S.Y;
+    L.ldy = S.ldy;
+    L.d_in = (int)S.d_in;
+    L.d_out = (int)S.d_out;
+    L.steps = (int)steps;
+    L.tiles = (int)cdiv(S.d_out, (int64_t)kTileOuts);
+    size_t used = 0;
+    auto take = [&](size_t bytes) {
+        char *p = base + used;
+        used += piece(bytes);
+        return p;
+    };
+    if (dense) {
+        L.xf = reinterpret_cast<uint4 *>(take((size_t)cdiv(m, (int64_t)kTok) * steps * 1024));
+        if (S.colptr) L.pos = reinterpret_cast<int32_t *>(take((size_t)S.d_in * 4));
+        L.dense = reinterpret_cast<uint4 *>(take((size_t)steps * L.tiles * kOuts * 1024));
+    } else {
+        const int64_t tts = padded_token_tiles(m);
+        L.xf = reinterpret_cast<uint4 *>(take((size_t)tts * steps * 1024));
+        if (S.colptr) L.xt = reinterpret_cast<__half *>(take((size_t)tts * S.d_in * kTok * 2));
+        choose_slabs(L, m);
+        L.partial = reinterpret_cast<float *>(take((size_t)L.slabs * m * S.d_out * 4));
+    }
+    return used;
+}
+
+}  // namespace
+
+size_t lut_gemm_need(const cmpq_deployed_layer &S, int64_t m) {
+    Layer L;
+    if (many_tokens(S, m)) return plan_layer(S, m, true, nullptr, L);
+    const int64_t part = part_tokens(S.d_in, S.d_out, m);
+    const size_t first = plan_layer(S, part, false, nullptr, L);
+    const size_t last = m % part ? plan_layer(S, m % part, false, nullptr, L) : 0;
+    return first > last ? first : last;
 }
 
 int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int64_t m, void *ws, hipStream_t s) {
     Group few, many;
     few.n_layers = many.n_layers = 0;
-    const int MT = m > kTok ? 2 : 1;
-    const int64_t tts = align_up((size_t)cdiv(m, (int64_t)kTok), MT);
+    const int MT = tiles_at_once(m);
+    const int64_t tts = padded_token_tiles(m);
     char *base = static_cast<char *>(ws);
     for (int i = 0; i < n_layers; ++i) {
         const cmpq_deployed_layer &S = *layers[i];
         const bool dense = many_tokens(S, m);
-        Group &G = dense ? many : few;
-        Layer &L = G.l[G.n_layers++];
-        L = Layer{};
-        int64_t steps = 0;
-        auto add = [&](const uint32_t *packed, const uint16_t *lut, const int32_t *chan, int64_t rows, int bits) {
-            if (rows <= 0) return;
-            Seg &g = L.seg[L.n_seg++];
-            g.packed = packed;
-            g.lut = lut;
-            g.chan = chan;
-            g.rows = (int)rows;
-            g.words_per_row = bits == kActBits ? 0 : (int)cdiv(S.d_out * bits, 32);
-            g.bits = bits;
-            g.step0 = (int)steps;
-            g.steps = (int)cdiv(rows, (int64_t)kRowsPerStep);
-            steps += g.steps;
-        };
-        for (int j = 0; j < S.n_set; ++j) add(S.packed[j], S.lut[j], S.chan_idx[j], S.counts_host[j], S.bit_set[j]);
-        add(nullptr, nullptr, S.act_idx, S.k_act, kActBits);
-        L.X = static_cast<const __half *>(S.X);
-        L.ldx = S.ldx;
-        L.W_act = reinterpret_cast<const __half *>(S.W_act);
-        L.ld_act = S.ld_act;
-        L.act_vec_ok = reinterpret_cast<uintptr_t>(S.W_act) % 16 == 0 && S.ld_act % 8 == 0;
-        L.colptr = S.colptr;
-        L.row_idx = S.row_idx;
-        L.delta = S.delta;
-        L.Y = S.Y;
-        L.ldy = S.ldy;
-        L.d_in = (int)S.d_in;
-        L.d_out = (int)S.d_out;
-        L.steps = (int)steps;
-        L.tiles = (int)cdiv(S.d_out, (int64_t)kTileOuts);
-        size_t used = 0;
-        auto take = [&](size_t bytes) {
-            char *p = base + used;
-            used += piece(bytes);
-            return p;
-        };
-        L.xf = reinterpret_cast<uint4 *>(take((size_t)tts * steps * 1024));
-        if (dense) {
-            if (S.colptr) L.pos = reinterpret_cast<int32_t *>(take((size_t)S.d_in * 4));
-            L.dense = reinterpret_cast<uint4 *>(take((size_t)steps * L.tiles * kOuts * 1024));
-        } else {
-            if (S.colptr) L.xt = reinterpret_cast<__half *>(take((size_t)tts * S.d_in * kTok * 2));
-            choose_slabs(L, tts / MT);
-            L.partial = reinterpret_cast<float *>(take((size_t)L.slabs * m * S.d_out * 4));
+        const int64_t part = dense ? m : part_tokens(S.d_in, S.d_out, m);
+        if (part < m) {  // on its own, a part of the tokens after the other in the same scratch
+            for (int64_t t = 0; t < m; t += part) {
+                cmpq_deployed_layer P = S;
+                P.X = static_cast<const __half *>(S.X) + t * S.ldx;
+                P.Y = S.Y + t * S.ldy;
+                const cmpq_deployed_layer *one = &P;
+                const int rc = launch_lut_gemm(&one, 1, m - t < part ? m - t : part, base, s);
+                if (rc != CMPQ_OK) return rc;
+            }
+            base += lut_gemm_need(S, m);
+            continue;
         }
-        base += lut_gemm_ws_bytes(S.d_in, S.d_out, m);
+        Group &G = dense ? many : few;
+        base += plan_layer(S, m, dense, base, G.l[G.n_layers++]);
     }
     for (Group *G : {&few, &many}) {
         if (G->n_layers == 0) continue;

@@ -800,13 +800,22 @@ size_t cmpq_ws_outliers_by_column(int64_t d_out, int64_t n_out) {
     return align_up((size_t)(d_out + 1) * sizeof(int32_t), 256) * 2 + align_up((size_t)n_out * 4, 256) * 2;
 }
 
-// Upper bound without the per-width counts: every width and O_act may end with a partly
-// filled slab.
-size_t cmpq_ws_lut_matvec(int64_t d_in, int64_t d_out, int64_t m) {
+// Token by token.  Upper bound without the per-width counts: every width and O_act may end with a
+// partly filled slab.
+static size_t ws_token_by_token(int64_t d_in, int64_t d_out, int64_t m) {
     const int64_t slabs = cdiv(d_in, (int64_t)kWaves * 8) + kMaxWidths + 2;  // the smallest slabs
-    const size_t one_by_one = align_up((size_t)m * (size_t)slabs * (size_t)d_out * sizeof(float), 256);
+    return align_up((size_t)m * (size_t)slabs * (size_t)d_out * sizeof(float), 256);
+}
+
+// Where several tokens go to the matrix cores: what they need there, and room for a few tokens of
+// the product with FP16 sums, which has to work through them in parts (one at least; 32 MB of
+// partial rows keep the chip busy however many tokens there are).
+size_t cmpq_ws_lut_matvec(int64_t d_in, int64_t d_out, int64_t m) {
+    if (m < 2 || d_in <= 0 || d_out <= 0 || !lut_gemm_takes(d_in, d_out, m)) return ws_token_by_token(d_in, d_out, m);
+    const int64_t fit = ((int64_t)32 << 20) / (int64_t)ws_token_by_token(d_in, d_out, 1);
+    const size_t parts = ws_token_by_token(d_in, d_out, fit < 1 ? 1 : (fit < m ? fit : m));
     const size_t together = lut_gemm_ws_bytes(d_in, d_out, m);
-    return one_by_one > together ? one_by_one : together;
+    return parts > together ? parts : together;
 }
 
 extern "C" int cmpq_gather_channels(const void *W, int dtype, int64_t d_in, int64_t d_out, int64_t ldw,
@@ -885,8 +894,8 @@ int check_layer(const cmpq_deployed_layer &L, int64_t m) {
     return CMPQ_OK;
 }
 
-// The token-by-token launch of the layers order[0..n): arguments of its two kernels, grid and
-// scratch.
+// The token-by-token launch of the layers order[0..n), `tokens` of the call's m at a time: arguments
+// of its two kernels, grid and scratch.
 struct Plan {
     LmGroup g;
     FinGroup f;
@@ -894,7 +903,8 @@ struct Plan {
     int64_t y_total, x_total, max_tiles;
 };
 
-void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, int n, int64_t m, void *ws, Plan &p) {
+void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, int n, int64_t m, int64_t tokens, void *ws,
+                         Plan &p) {
     LmGroup &g = p.g;
     FinGroup &f = p.f;
     g.n_layers = f.n_layers = n;
@@ -952,7 +962,7 @@ void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, in
         fa.ldy = L.ldy;
         fa.n_rows_total = (int)n_rows;
         fa.x0 = (int)p.x_total;
-        p.ws_used += align_up((size_t)m * (size_t)n_rows * (size_t)L.d_out * sizeof(float), 256);
+        p.ws_used += align_up((size_t)tokens * (size_t)n_rows * (size_t)L.d_out * sizeof(float), 256);
         p.y_total += n_rows;
         p.x_total += cdiv(L.d_out, kFinCols);
         if (tiles > p.max_tiles) p.max_tiles = tiles;
@@ -961,6 +971,18 @@ void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, in
         g.l[s] = g.l[0];
         f.l[s] = f.l[0];
     }
+}
+
+int launch_token_by_token(const Plan &p, int64_t tokens, bool half_sums, hipStream_t st) {
+    if (p.y_total > 0) {
+        const dim3 grid((unsigned)p.max_tiles, (unsigned)p.y_total, (unsigned)tokens);
+        if (half_sums) lut_matvec_half_kernel<<<grid, kThreads, 0, st>>>(p.g);
+        else lut_matvec_kernel<<<grid, kThreads, 0, st>>>(p.g);
+    }
+    const dim3 fgrid((unsigned)p.x_total, (unsigned)tokens);
+    lut_matvec_finish_kernel<<<fgrid, kThreads, 0, st>>>(p.f);
+    CMPQ_LAUNCH_CHECK();
+    return CMPQ_OK;
 }
 
 int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, void *ws, size_t ws_bytes,
@@ -985,44 +1007,73 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
             order[j - 1] = t;
         }
     if (n_live == 0) return CMPQ_OK;
-    Plan p;
-    plan_token_by_token(layers, order, n_live, m, ws, p);
-    if (p.y_total > 65535 || p.x_total > 0x7fffffff) return CMPQ_ESHAPE;
-    if (p.ws_used > 0 && (!ws || reinterpret_cast<uintptr_t>(ws) % 256 != 0 || ws_bytes < p.ws_used))
-        return CMPQ_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Layers that the matrix cores take (several tokens) go first, the others token by token.  With a
-    // workspace that holds the token-by-token launch but not this one (less than
-    // cmpq_workspace_bytes asks for), all go token by token.
-    if (m > 1 && !half_sums) {
-        const cmpq_deployed_layer *taken[kMaxLayers];
-        int n_taken = 0, rest[kMaxLayers], n_rest = 0;
-        size_t need = 0;
-        for (int i = 0; i < n_live; ++i) {
-            const cmpq_deployed_layer &L = layers[order[i]];
-            if (lut_gemm_takes(L.d_in, L.d_out, m)) {
-                taken[n_taken++] = &L;
-                need += lut_gemm_ws_bytes(L.d_in, L.d_out, m);
-            } else {
-                rest[n_rest++] = order[i];
+    const size_t have = ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 ? ws_bytes : 0;
+    Plan p;
+    plan_token_by_token(layers, order, n_live, m, m, ws, p);
+    if (p.y_total > 65535 || p.x_total > 0x7fffffff) return CMPQ_ESHAPE;
+    if (half_sums) {
+        // as many tokens at a time as the workspace holds, the same numbers however many
+        int64_t tokens = m;
+        if (p.ws_used > have) {
+            plan_token_by_token(layers, order, n_live, m, 1, ws, p);
+            if (p.ws_used > have) return CMPQ_EWORKSPACE;
+            tokens = (int64_t)(have / p.ws_used);  // a token's rows fill whole 256 bytes at most once over
+        }
+        plan_token_by_token(layers, order, n_live, m, tokens, ws, p);
+        for (int64_t t = 0; t < m; t += tokens) {
+            const int rc = launch_token_by_token(p, m - t < tokens ? m - t : tokens, true, st);
+            if (rc != CMPQ_OK) return rc;
+            for (int i = 0; i < n_live; ++i) {
+                p.g.l[i].X += tokens * p.g.l[i].ldx;
+                p.f.l[i].X += tokens * p.f.l[i].ldx;
+                p.f.l[i].Y += tokens * p.f.l[i].ldy;
             }
         }
-        if (n_taken > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= need) {
-            const int rc = launch_lut_gemm(taken, n_taken, m, ws, st);
-            if (rc != CMPQ_OK || n_rest == 0) return rc;
-            // launches on one stream run in order: the rest uses the same workspace
-            plan_token_by_token(layers, rest, n_rest, m, ws, p);
+        return CMPQ_OK;
+    }
+    // Layers that the matrix cores take (several tokens) go first, the others token by token.  A
+    // workspace is enough if it holds either launch, or the token-by-token launch of all layers (which
+    // is what calls had to bring before there were others): a layer whose plan does not fit into the
+    // workspace goes token by token then, whatever else is in the group.
+    size_t need[kMaxLayers], sum = 0;
+    bool fits[kMaxLayers];
+    int rest[kMaxLayers], n_rest = 0;
+    Plan q;
+    for (int i = 0; i < n_live; ++i) {
+        const cmpq_deployed_layer &L = layers[order[i]];
+        fits[i] = m > 1 && lut_gemm_takes(L.d_in, L.d_out, m);
+        need[i] = fits[i] ? lut_gemm_need(L, m) : 0;
+        sum += need[i];
+        if (!fits[i]) rest[n_rest++] = order[i];
+    }
+    q.ws_used = 0;
+    if (n_rest > 0) plan_token_by_token(layers, rest, n_rest, m, m, ws, q);
+    if (p.ws_used > have && (sum > have || q.ws_used > have)) return CMPQ_EWORKSPACE;
+    const cmpq_deployed_layer *batch[kMaxLayers];
+    int n_batch = 0;
+    n_rest = 0;
+    char *at = static_cast<char *>(ws);
+    size_t used = 0;
+    for (int i = 0; i <= n_live; ++i) {
+        if (i < n_live && !(fits[i] && need[i] <= have)) {
+            rest[n_rest++] = order[i];
+            continue;
+        }
+        if (n_batch > 0 && (i == n_live || used + need[i] > have)) {  // (launches on one stream run in order)
+            const int rc = launch_lut_gemm(batch, n_batch, m, at, st);
+            if (rc != CMPQ_OK) return rc;
+            n_batch = 0;
+            used = 0;
+        }
+        if (i < n_live) {
+            batch[n_batch++] = &layers[order[i]];
+            used += need[i];
         }
     }
-    if (p.y_total > 0) {
-        const dim3 grid((unsigned)p.max_tiles, (unsigned)p.y_total, (unsigned)m);
-        if (half_sums) lut_matvec_half_kernel<<<grid, kThreads, 0, st>>>(p.g);
-        else lut_matvec_kernel<<<grid, kThreads, 0, st>>>(p.g);
-    }
-    const dim3 fgrid((unsigned)p.x_total, (unsigned)m);
-    lut_matvec_finish_kernel<<<fgrid, kThreads, 0, st>>>(p.f);
-    CMPQ_LAUNCH_CHECK();
-    return CMPQ_OK;
+    if (n_rest == 0) return CMPQ_OK;
+    plan_token_by_token(layers, rest, n_rest, m, m, ws, q);
+    return launch_token_by_token(q, m, false, st);
 }
 
 }  // namespace

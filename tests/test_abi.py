@@ -215,3 +215,20 @@ def test_product_package_does_not_reach_the_oracle():
                 assert "import oracle" not in text and "from oracle" not in text and "orc_" not in text, f
     src = open(os.path.join(ROOT, "oracle", "__init__.py")).read() + open(os.path.join(ROOT, "oracle", "cmpq_oracle.c")).read()
     assert "paper_2410_13056_amd" not in src and "cmpq.h" not in src
+
+
+def test_scratch_of_a_product_follows_the_plan_that_runs(L):
+    """One token asks for its partial rows, a few tokens for no more than those of two, many tokens for
+    about the decoded weight: neither the decoded weight where it is not made nor a row per slab and
+    token where tokens are multiplied together."""
+    from paper_2410_13056_amd import binding as B
+    need = lambda *a: B.workspace_bytes(B.OP_LUT_MATVEC, *a)
+    one = need(8192, 28672, 1)
+    assert one <= 31 << 20
+    assert need(512, 256, 1) <= 32 << 10
+    assert need(8192, 28672, 2) <= 2 * one and need(8192, 28672, 16) <= 2 * one
+    weight = 2 * 8192 * 28672
+    assert weight <= need(8192, 28672, 512) <= 1.1 * weight
+    assert need(8192, 28672, 2048) <= 1.2 * weight
+    assert need(4096, 11008, 512) <= 2 * 2 * 4096 * 11008
+    assert need(4096, 11008, 4096) <= 2 * 2 * 4096 * 11008
