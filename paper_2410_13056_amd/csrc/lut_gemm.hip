@@ -883,13 +883,27 @@ size_t piece(size_t bytes) { return align_up(bytes, 256); }
 
 }  // namespace
 
-// Up to 8 tokens the two ways cost the same where a product is all latency (2048x2048, 6 tokens:
-// 14.7 | 15.0 us here | token by token) and this one wins as soon as it is not (13824x5120 twice, 2
-// tokens: 39 | 56; 4099x3001, 5 tokens: 20 | 41).  More tokens need more registers and longer
-// kernels, which pays from some 24 million weight-token products on (900x700, 16 tokens: 20 | 16;
-// 2048x2048, 16 tokens: 20.0 | 21.1; 513x3001, 16 tokens: 22 | 29).
+// All in us, this way | token by token.  A launch of this kind costs 1 to 6 us more to get going
+// (bigger kernels, colder code), a token in it next to nothing; so the line lies where the tokens'
+// work outweighs the start.  It is drawn by d_in first, without d_out, so that the layers of a group,
+// which read the same input, go the same way: a group split over both ways pays for both
+// (2048 -> 2048, 512, 512, 12 tokens: 42 split, 20 | 37; 1000 -> 1024, 300, 32 tokens: 42, 23 | 30).
+//   * up to 8 tokens (one answer for all of them, so that a token's bits do not depend on how many
+//     come with it) from 960 channels: 300x2048, 4 tokens 15.5 | 12.6; 700x700 16.2 | 14.5;
+//     600 -> 600, 700, 800 16.8 | 16.0.  Above the line a layer of its own still loses 1 to 3 us
+//     (1000x1024, 4 tokens 15.4 | 13.5; 2048x2048 15.9 | 14.0), groups win (2048 -> 2048, 512, 512
+//     16.5 | 18.2; 4096 -> 4096, 512, 512, 2 tokens 20 | 27), and so do outputs that are no multiple
+//     of 32 beside rows of O_act (3001x513, 2 tokens 17 | 25).  Below it from 4 million weights:
+//     700 -> 3000, 200, 8 tokens 17.2 | 17.9; 300x8192 16.2 | 16.6.
+//   * up to 16 tokens, m * d_in from 16384: 2048x512, 9 tokens 18.0 | 15.4; 2048 -> 2048, 512, 512
+//     19 | 29.
+//   * more, with kernels of 32 tokens, from 24576: 512x512, 32 tokens 19 | 15, 64 tokens 20.5 | 21.3;
+//     1024 -> 1024, 256, 256, 24 tokens 19 | 32.
+//   * or, past 8 tokens, 24 million weight-token products: 300x8192, 16 tokens 19 | 26.
 bool lut_gemm_takes(int64_t d_in, int64_t d_out, int64_t m) {
-    return m >= 2 && (m <= 8 || m * d_in >= ((int64_t)24 << 20) / d_out);
+    if (m < 2) return false;
+    if (m <= 8) return d_in >= 960 || d_in >= ((int64_t)4 << 20) / d_out;
+    return m * d_in >= (m <= 16 ? 16384 : 24576) || m * d_in >= ((int64_t)24 << 20) / d_out;
 }
 
 size_t lut_gemm_ws_bytes(int64_t d_in, int64_t d_out, int64_t m) {

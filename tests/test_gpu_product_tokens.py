@@ -88,3 +88,23 @@ def test_a_workspace_for_single_tokens_only_still_serves(env):
         torch.cuda.synchronize()
         if rc == 0:
             _check(Y, X, What)
+
+
+@pytest.mark.parametrize("d_in,m,wide", [(959, 8, 2050), (960, 8, 2050), (500, 8, 8380), (500, 8, 8400),
+                                         (1820, 9, 2050), (1821, 9, 2050), (1023, 16, 2050), (1024, 16, 2050),
+                                         (1445, 17, 2050), (1446, 17, 2050), (511, 48, 2050), (512, 48, 2050),
+                                         (64, 384, 2050)])
+def test_both_sides_of_the_lines_to_the_matrix_cores(env, d_in, m, wide):
+    """Layers of one input, narrow and wide, at the lines from which tokens are multiplied together: right
+    on both sides, in a group as alone, and up to 8 tokens the same however many come together."""
+    P, ws = env["P"], env["ws"]
+    layers = [_layer(env, d_in + o, d_in, o, (2, 3, 4), 3.0) for o in (1, 40, 257, wide)]
+    deps = [d for d, _ in layers]
+    X = torch.randn((m, d_in), generator=torch.Generator(device=DEV).manual_seed(m), device=DEV).to(torch.float16)
+    Ys = [torch.full((m, d.d_out), float("nan"), device=DEV) for d in deps]
+    P.group_products(deps)([X] * len(deps), Ys, ws)
+    for (dep, What), Y in zip(layers, Ys):
+        _check(Y, X, What)
+        assert torch.equal(Y, P.lut_matvec(dep, X, ws))
+        if m <= 8 and d_in >= 960:
+            assert torch.equal(Y[:2], P.lut_matvec(dep, X[:2], ws))
