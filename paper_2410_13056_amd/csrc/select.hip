@@ -1863,7 +1863,12 @@ int launch_weight_select(WselArgs a, const WselPlan &p, int64_t k, int32_t *idx_
     wsel_list_kernel<0><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
     wsel_list_kernel<1><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
     // exact chain: these return at once unless the fast chain raised its flag
-    const int hist_blocks = p.nblocks < 512 ? p.nblocks : 512;
+    // (Workgroups that return at once still cost: three launches of 1024 0.1 us, of 1536 0.5 us more than
+    // of 512.  Where they do work they hide its latency: channels of different scale, 8192x28672
+    // weights, 512 workgroups 1300 us for the call, 1024 1067, 1536 988, 2048 999; 4096x4096 186, 168,
+    // 163, 167.)
+    const int most_blocks = p.wc_per_unit >= 16 ? 1536 : 1024;
+    const int hist_blocks = p.nblocks < most_blocks ? p.nblocks : most_blocks;
     wsel_hist_kernel<TW, 0><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     wsel_hist_kernel<TW, 1><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     wsel_hist_kernel<TW, 2><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
