@@ -376,7 +376,8 @@ constexpr int kSets = 4, kSampleSet = kSampleFine + kSampleFine / 8;
 constexpr int kHistSample = 3 * kBins, kHistList = kHistSample + kSets * kSampleSet;
 constexpr int kHistList2 = kHistList + kSets * kBins;
 constexpr int kHistList2Fine = kHistList2 + kListFine / 8, kHistList3 = kHistList2Fine + kListFine;
-constexpr int kHistWords = kHistList3 + (1 << kListFarShift);
+constexpr int kHistTop = kHistList3 + (1 << kListFarShift);  // the sample's largest key, in kSets sets too
+constexpr int kHistWords = kHistTop + kSets;
 
 struct WselState {
     uint32_t T;         // final threshold key
@@ -447,7 +448,7 @@ WselPlan wsel_plan(int64_t d_in, int64_t d_out, int64_t k) {
     p.n_sample = cdiv(p.total_wc, p.sample_stride);
     const double ks = (double)k * (double)p.n_sample / (double)(p.total_wc > 0 ? p.total_wc : 1);
     double margin = 8.0 / __builtin_sqrt(ks > 1.0 ? ks : 1.0);
-    if (margin < 0.15) margin = 0.15;
+    if (margin < 0.10) margin = 0.10;
     p.sample_rank = (uint64_t)(ks * (1.0 + margin)) + 8;
     return p;
 }
@@ -1107,38 +1108,23 @@ __device__ __forceinline__ void exact_prefix(const uint32_t *__restrict__ hist, 
     }
 }
 
-// The one of 8 neighbouring fine bins that holds rank `rem64` of their sum (from the largest down),
-// the rank inside it, its count, and whether the bins of the 8 beside it are empty.  Every lane for
-// itself, so in 32 bits (a sum of the bins fits).
-template <int SETS = 1>
-__device__ __forceinline__ int pick_of_8(const uint32_t *__restrict__ fine, uint64_t rem64, uint64_t &rem_in, uint32_t &count,
-                                         bool &alone, int stride = 0) {
-    uint32_t v[8];
+// The one of 8 neighbouring fine bins that holds rank `rem` of their sum (from the largest down) and
+// the rank inside it.  Every lane for itself, so in 32 bits (a sum of the bins fits).
+__device__ __forceinline__ int pick_of_8(const uint32_t *__restrict__ fine, uint32_t rem, uint64_t &rem_in) {
+    uint32_t v[8], run = 0, before = 0;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        v[r] = fine[r];
-#pragma unroll
-        for (int c = 1; c < SETS; ++c) v[r] += fine[c * stride + r];
-    }
-    const uint32_t rem = (uint32_t)rem64;
-    uint32_t run = 0, before = 0, filled = 0;
+    for (int r = 0; r < 8; ++r) v[r] = fine[r];
     int bin = -1;
 #pragma unroll
     for (int r = 7; r >= 0; --r) {
         run += v[r];
-        filled |= v[r] ? 1u << r : 0u;
         if (bin < 0 && rem <= run) {
             bin = r;
             before = run - v[r];
         }
     }
-    bin = bin < 0 ? 0 : bin;
-    count = v[0];
-#pragma unroll
-    for (int r = 1; r < 8; ++r) count = bin == r ? v[r] : count;
     rem_in = rem - before;
-    alone = ((filled << 1) & (5u << bin)) == 0;
-    return bin;
+    return bin < 0 ? 0 : bin;
 }
 
 // Fast chain, the list's digits.  First: the bin that holds the k-th key; false when the list is too
@@ -1159,11 +1145,10 @@ __device__ __forceinline__ bool list_bin(const uint32_t *__restrict__ hist, uint
 // Then the key (the first of 2^shift) and how many keys equal to it (in them) are to be taken.
 __device__ __forceinline__ void list_key(const uint32_t *__restrict__ hist, uint32_t first_key, uint32_t shift, uint64_t rem,
                                          PickShared &ps, uint32_t &T, uint64_t &need) {
-    uint32_t bin, tot, count;
+    uint32_t bin, tot;
     uint64_t rem8;
-    bool alone;
     block_pick<kListFine / 8>(hist + kHistList2, rem, ps, bin, rem8, tot);
-    T = first_key + ((8 * bin + (uint32_t)pick_of_8(hist + kHistList2Fine + 8 * bin, rem8, need, count, alone)) << shift);
+    T = first_key + ((8 * bin + (uint32_t)pick_of_8(hist + kHistList2Fine + 8 * bin, (uint32_t)rem8, need)) << shift);
 }
 
 // Calls body(key) for the listed entries of this workgroup's share of the units.
@@ -1207,8 +1192,9 @@ constexpr int kSampleChunks = 96, kSampleThreads = 1024;
 static_assert(kSampleChunks * kWaveChunk < 65536, "");
 template <typename TW>
 __global__ __launch_bounds__(kSampleThreads) void wsel_sample_kernel(WselArgs a, uint32_t *__restrict__ hist) {
-    __shared__ uint32_t lh[kSampleFine / 2];
+    __shared__ uint32_t lh[kSampleFine / 2], largest;
     for (int b = threadIdx.x; b < kSampleFine / 2; b += kSampleThreads) lh[b] = 0;
+    if (threadIdx.x == 0) largest = 0;
     __syncthreads();
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
     constexpr int kSampleWaves = kSampleThreads / CMPQ_WAVE;
@@ -1231,6 +1217,7 @@ __global__ __launch_bounds__(kSampleThreads) void wsel_sample_kernel(WselArgs a,
         it.cent = a.centroids ? a.centroids[it.i * CMPQ_KMAX + (lane & 15)] : 0.f;
     };
     int64_t j = (int64_t)blockIdx.x * kSampleWaves + wave;
+    uint32_t top = 0;
     Item cur = {}, nxt = {};
     if (j < a.n_sample) load(j, cur);
     for (; j < a.n_sample; j += n_waves) {
@@ -1243,43 +1230,96 @@ __global__ __launch_bounds__(kSampleThreads) void wsel_sample_kernel(WselArgs a,
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 if (!((valid >> e) & 1u)) continue;
+                top = max(top, key[e]);
                 const uint32_t bin = key[e] >> kSampleShift;
                 atomicAdd(&lh[bin >> 1], bin & 1u ? 0x10000u : 1u);
             }
         }
         cur = nxt;
     }
+#pragma unroll
+    for (int d = CMPQ_WAVE / 2; d > 0; d >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d, CMPQ_WAVE));
+    if (lane == 0) atomicMax(&largest, top);
     __syncthreads();
+    if (threadIdx.x == 0) atomicMax(&hist[kHistTop + (blockIdx.x & (kSets - 1))], largest);
     uint32_t *set = hist + kHistSample + (blockIdx.x & (kSets - 1)) * kSampleSet;
     flush_fine(lh, kSampleFine, set, set + kSampleFine / 8);
+}
+
+// The guess: the key that `rank` entries of the sample reach, placed inside its fine bin.  0 where
+// there is no usable sample: then everything reaches it, the list overflows and the exact chain runs.
+// Called by all threads of a workgroup, every lane for itself.
+//   * The topmost bin ends at the sample's largest key, not at its edge: scores with a bound, weights
+//     drawn uniformly or clipped.  (4096x4096 such weights, 1 % by magnitude: 58 us, 165
+//     by the edge.)
+//   * Between empty bins a bin most likely holds one value, weights on a coarse grid: the whole bin.
+//     (On a grid of a quarter of their deviation 58 us, 149 with a guess inside.)
+//   * Elsewhere the density of the scores is taken to change evenly across the bin, as the bins beside
+//     it say; with an even density the list came out short where the scores thin out quickly.
+// At most infinity: as the pattern of a NaN the guess would not stand in the floats' order by which
+// FP16 weights are staged, and the list would hold keys beneath it, which its histogram has no place
+// for.
+__device__ __forceinline__ uint32_t sample_guess(const uint32_t *__restrict__ hist, uint64_t rank, PickShared &ps) {
+    uint32_t coarse, tot;
+    uint64_t rem64;
+    if (!block_pick<kSampleFine / 8, kSets>(hist + kHistSample, rank, ps, coarse, rem64, tot, kSampleSet)) return 0;
+    const int first = 8 * (int)coarse;
+    const uint32_t rem = (uint32_t)rem64;
+    const uint32_t *fine = hist + kHistSample + kSampleFine / 8;
+    uint32_t v[10];  // the 8 bins and one on either side (none past the ends)
+    const int before = first > 0 ? first - 1 : 0, after = first + 8 < kSampleFine ? first + 8 : first + 7;
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        const int b = r == 0 ? before : (r == 9 ? after : first + r - 1);
+        v[r] = 0;
+#pragma unroll
+        for (int c = 0; c < kSets; ++c) v[r] += fine[c * kSampleSet + b];
+    }
+    if (before == first) v[0] = 0;
+    if (after < first + 8) v[9] = 0;
+    uint32_t run = 0, in = 1, count = 1, below = 0, above = 0;
+    int at = 0;
+#pragma unroll
+    for (int r = 8; r >= 1; --r) {
+        run += v[r];
+        if (at == 0 && rem <= run) {
+            at = r;
+            in = rem - (run - v[r]);
+            count = v[r], below = v[r - 1], above = v[r + 1];
+        }
+    }
+    const uint32_t lower = (uint32_t)(first - 1 + at) << kSampleShift;
+    float from_top, width = (float)((1 << kSampleShift) - 1);
+    if (in == rank) {
+        uint32_t top = hist[kHistTop];
+#pragma unroll
+        for (int c = 1; c < kSets; ++c) top = max(top, hist[kHistTop + c]);
+        width = (float)(top - lower);
+        from_top = (float)in / (float)count;
+    } else if ((below | above) == 0) {
+        return min(lower, 0x7f800000u);
+    } else {
+        // densities l at the lower edge and h at the upper one, (l + h) / 2 = count; the guess lies t
+        // below the upper edge, h t + (l - h) t^2 / 2 = in
+        const float n = (float)count, l0 = (float)below + n, h0 = (float)above + n, scale = 2.f * n / (l0 + h0);
+        const float l = l0 * scale, h = h0 * scale, i = (float)in;
+        from_top = 2.f * i / (h + __builtin_sqrtf(h * h + 2.f * (l - h) * i));
+    }
+    const float share = fminf(fmaxf(1.f - from_top, 0.f), 1.f);
+    return min(lower + (uint32_t)(share * width), 0x7f800000u);
 }
 
 // Fast chain, the one pass over the data: stages every entry whose key reaches the guess read off
 // the sample's histograms (inside a bin, by the share of its entries that lie above).
 // NEAR (FP16 weights, residual score, no codes): candidates by the channel's intervals.
+// At most 80 scalar registers: with more a SIMD holds a wavefront less, whatever the vector registers
+// allow, and this pass lives on wavefronts in flight (8192x28672 weights, k = 1 %, whole selection:
+// 236 -> 208 us, by magnitude 217 with 87 registers, 193 with 80).
 template <typename TW, bool NEAR>
-__global__ __launch_bounds__(kWThreads) void wsel_stage_kernel(WselArgs a, WselState *st,
+__global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_num_sgpr(80))) void wsel_stage_kernel(WselArgs a, WselState *st,
                                                                 const uint32_t *__restrict__ hist) {
     __shared__ PickShared ps;
-    uint32_t reach = 0;  // no usable sample: everything reaches it, the list overflows, the exact chain runs
-    {
-        uint32_t bin, tot, count;
-        uint64_t rem, rem_in;
-        if (block_pick<kSampleFine / 8, kSets>(hist + kHistSample, a.sample_rank, ps, bin, rem, tot, kSampleSet)) {
-            bool alone;
-            const int fine = (int)(8 * bin) + pick_of_8<kSets>(hist + kHistSample + kSampleFine / 8 + 8 * bin, rem, rem_in, count, alone, kSampleSet);
-            // Scores of few values (weights on a coarse grid): between empty bins the bin most likely
-            // holds one value, which a guess inside the bin may miss: then the whole bin.  (Not where
-            // it is the topmost: a narrow distribution looks the same.)  4096x4096 weights on a grid of
-            // a quarter of their deviation, 1 % by magnitude: 58 us, 149 with the guess inside.
-            const float share = 1.0f - (float)rem_in / (float)(count ? count : 1);
-            reach = ((uint32_t)fine << kSampleShift) + (uint32_t)(share * (float)((1 << kSampleShift) - 1));
-            if (alone && rem_in < a.sample_rank) reach = (uint32_t)fine << kSampleShift;
-            // At most infinity: as the pattern of a NaN it would not stand in the floats' order below, and
-            // the list would hold keys beneath it, which its histogram has no place for.
-            reach = min(reach, 0x7f800000u);
-        }
-    }
+    const uint32_t reach = sample_guess(hist, a.sample_rank, ps);
     if (blockIdx.x == 0 && threadIdx.x == 0) st->reach = reach;
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
     const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;

@@ -134,3 +134,31 @@ def test_selection_among_few_values(d_in, d_out, step):
             want = np.sort(order[:k])
             assert np.array_equal(idx.cpu().numpy(), want), k
             assert np.array_equal(val.cpu().numpy(), W.ravel()[want]), k
+
+
+@pytest.mark.parametrize("d_in,d_out", [(512, 2048), (300, 1027)])
+def test_selection_among_bounded_scores(d_in, d_out):
+    """Scores that end at a bound, inside the topmost bin of the sample, or thin out quickly above the
+    k-th (weights drawn uniformly; clipped, so that many are tied at the bound)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle as orc
+    from paper_2410_13056_amd import binding as B
+    ws = B.Workspace(DEV)
+    rng = np.random.default_rng(d_out)
+    bits = np.full(d_in, 3, np.uint8)
+    for W in (rng.uniform(-0.02, 0.02, (d_in, d_out)), rng.normal(0, 0.02, (d_in, d_out)).clip(-0.05, 0.05)):
+        W = W.astype(np.float16)
+        cent = np.full((d_in, 16), np.inf, np.float32)
+        cent[:, :8] = np.quantile(W.astype(np.float32), np.linspace(0.06, 0.94, 8), axis=1).T
+        Wd, cd, bd = (torch.from_numpy(x).to(DEV) for x in (W, cent, bits))
+        for k in (3, W.size // 2000, W.size // 200, W.size // 100, W.size // 20):
+            idx = torch.full((k,), -7, dtype=torch.int32, device=DEV)
+            val = torch.zeros(k, dtype=torch.float16, device=DEV)
+            B.extract_weight_outliers(Wd, cd, None, bd, k, idx, val, ws)
+            oidx, oval = orc.weight_outliers(W, cent, None, bits, k)
+            assert np.array_equal(idx.cpu().numpy().astype(np.int64), oidx), k
+            assert np.array_equal(val.cpu().numpy().view(np.uint16), oval), k
+            B.extract_weight_outliers(Wd, cd, None, bd, k, idx, val, ws, score=B.SCORE_MAGNITUDE)
+            want = np.sort(np.argsort(-np.abs(W.astype(np.float32)).ravel(), kind="stable")[:k])
+            assert np.array_equal(idx.cpu().numpy(), want), k
