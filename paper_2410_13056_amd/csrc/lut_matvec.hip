@@ -807,15 +807,20 @@ static size_t ws_token_by_token(int64_t d_in, int64_t d_out, int64_t m) {
     return align_up((size_t)m * (size_t)slabs * (size_t)d_out * sizeof(float), 256);
 }
 
-// Where several tokens go to the matrix cores: what they need there, and room for a few tokens of
-// the product with FP16 sums, which has to work through them in parts (one at least; 32 MB of
-// partial rows keep the chip busy however many tokens there are).
+// Where several tokens go to the matrix cores: what they need there, and room for the product with
+// FP16 sums, which works through its tokens in as many parts as that makes: one token at least, up to
+// 32 MB of tokens with the smallest slabs (which it cuts where there is little work) and up to 128 MB
+// with the largest (8192x28672, 16 tokens: 418 us in one part, 436 in two, 472 in six).
 size_t cmpq_ws_lut_matvec(int64_t d_in, int64_t d_out, int64_t m) {
     if (m < 2 || d_in <= 0 || d_out <= 0 || !lut_gemm_takes(d_in, d_out, m)) return ws_token_by_token(d_in, d_out, m);
-    const int64_t fit = ((int64_t)32 << 20) / (int64_t)ws_token_by_token(d_in, d_out, 1);
-    const size_t parts = ws_token_by_token(d_in, d_out, fit < 1 ? 1 : (fit < m ? fit : m));
+    auto tokens = [&](int64_t room, int64_t token) { return room / token < 1 ? 1 : (room / token < m ? room / token : m); };
+    const int64_t slabs = cdiv(d_in, (int64_t)kWaves * kMaxRowsPerWave) + kMaxWidths + 2;
+    const int64_t token = slabs * d_out * (int64_t)sizeof(float);
+    size_t b = ws_token_by_token(d_in, d_out, tokens((int64_t)32 << 20, (int64_t)ws_token_by_token(d_in, d_out, 1)));
+    const size_t large = align_up((size_t)token * (size_t)tokens((int64_t)128 << 20, token), 256);
     const size_t together = lut_gemm_ws_bytes(d_in, d_out, m);
-    return parts > together ? parts : together;
+    if (large > b) b = large;
+    return together > b ? together : b;
 }
 
 extern "C" int cmpq_gather_channels(const void *W, int dtype, int64_t d_in, int64_t d_out, int64_t ldw,
@@ -1018,9 +1023,10 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
         if (p.ws_used > have) {
             plan_token_by_token(layers, order, n_live, m, 1, ws, p);
             if (p.ws_used > have) return CMPQ_EWORKSPACE;
-            tokens = (int64_t)(have / p.ws_used);  // a token's rows fill whole 256 bytes at most once over
+            // (a token's rows fill whole 256 bytes at most once over; parts of even size)
+            tokens = cdiv(m, cdiv(m, (int64_t)(have / p.ws_used)));
+            plan_token_by_token(layers, order, n_live, m, tokens, ws, p);
         }
-        plan_token_by_token(layers, order, n_live, m, tokens, ws, p);
         for (int64_t t = 0; t < m; t += tokens) {
             const int rc = launch_token_by_token(p, m - t < tokens ? m - t : tokens, true, st);
             if (rc != CMPQ_OK) return rc;
@@ -1039,7 +1045,6 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
     size_t need[kMaxLayers], sum = 0;
     bool fits[kMaxLayers];
     int rest[kMaxLayers], n_rest = 0;
-    Plan q;
     for (int i = 0; i < n_live; ++i) {
         const cmpq_deployed_layer &L = layers[order[i]];
         fits[i] = m > 1 && lut_gemm_takes(L.d_in, L.d_out, m);
@@ -1047,9 +1052,12 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
         sum += need[i];
         if (!fits[i]) rest[n_rest++] = order[i];
     }
-    q.ws_used = 0;
-    if (n_rest > 0) plan_token_by_token(layers, rest, n_rest, m, m, ws, q);
-    if (p.ws_used > have && (sum > have || q.ws_used > have)) return CMPQ_EWORKSPACE;
+    if (n_rest == n_live) return p.ws_used > have ? CMPQ_EWORKSPACE : launch_token_by_token(p, m, false, st);
+    if (p.ws_used > have) {
+        if (sum > have) return CMPQ_EWORKSPACE;
+        if (n_rest > 0) plan_token_by_token(layers, rest, n_rest, m, m, ws, p);
+        if (n_rest > 0 && p.ws_used > have) return CMPQ_EWORKSPACE;
+    }
     const cmpq_deployed_layer *batch[kMaxLayers];
     int n_batch = 0;
     n_rest = 0;
@@ -1072,8 +1080,8 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
         }
     }
     if (n_rest == 0) return CMPQ_OK;
-    plan_token_by_token(layers, rest, n_rest, m, m, ws, q);
-    return launch_token_by_token(q, m, false, st);
+    plan_token_by_token(layers, rest, n_rest, m, m, ws, p);
+    return launch_token_by_token(p, m, false, st);
 }
 
 }  // namespace

@@ -226,7 +226,7 @@ def test_scratch_of_a_product_follows_the_plan_that_runs(L):
     one = need(8192, 28672, 1)
     assert one <= 31 << 20
     assert need(512, 256, 1) <= 32 << 10
-    assert need(8192, 28672, 2) <= 2 * one and need(8192, 28672, 16) <= 2 * one
+    assert need(8192, 28672, 2) <= one and need(8192, 28672, 16) <= 128 << 20
     weight = 2 * 8192 * 28672
     assert weight <= need(8192, 28672, 512) <= 1.1 * weight
     assert need(8192, 28672, 2048) <= 1.2 * weight
