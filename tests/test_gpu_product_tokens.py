@@ -108,3 +108,48 @@ def test_both_sides_of_the_lines_to_the_matrix_cores(env, d_in, m, wide):
         assert torch.equal(Y, P.lut_matvec(dep, X, ws))
         if m <= 8 and d_in >= 960:
             assert torch.equal(Y[:2], P.lut_matvec(dep, X[:2], ws))
+
+
+@pytest.mark.parametrize("m", [95, 96, 520])
+def test_layers_of_every_plan_in_one_group(env, m):
+    """One call with layers that are decoded once (two of them; one without entries of O_q, one without
+    outliers of either kind), one too small for that, one that is not stored whole and one that goes token
+    by token: each right, and the same as alone.  95 and 96 tokens: the line to decoding once (from 96
+    tokens and 8 * 2^30 products on; the wide layer passes it at 96)."""
+    P, B, ws = env["P"], env["B"], env["ws"]
+    wide = (8192, 11008) if m < 520 else (4096, 4100)
+    specs = [(*wide, 10000, 10000), (*wide, 10000, 0), (4096, 4360, 0, 0), (1000, 700, 10000, 10000),
+             (4096, 4099, 20000, 5000), (40, 33, 30000, 10000)]
+    layers = [_layer(env, 70 + i, d_in, d_out, (2, 3, 4), 3.1, a, q) for i, (d_in, d_out, a, q) in enumerate(specs)]
+    gen = torch.Generator(device=DEV).manual_seed(m)
+    Xs = [torch.randn((m, d.d_in), generator=gen, device=DEV).to(torch.float16) for d, _ in layers]
+    part = layers[4][0]
+    Xs[4][:, part.act_idx.long()] = 0                             # the rows of O_act that the call leaves out
+    calls = [d.call() for d, _ in layers]
+    calls[4] = B.LutMatvecCall(part.d_in, part.d_out, part.bit_set, part.counts, part.packed, part.chan_idx, part.lut,
+                               None, None, part.colptr, part.row_idx, part.delta)
+    Ys = [torch.full((m, d.d_out), float("nan"), device=DEV) for d, _ in layers]
+    B.LutMatvecGroupCall(calls)(Xs, Ys, ws)
+    for call, (_, What), X, Y in zip(calls, layers, Xs, Ys):
+        _check(Y, X, What)
+        alone = torch.empty_like(Y)
+        call(X, alone, ws)
+        assert torch.equal(Y, alone)
+
+
+@pytest.mark.parametrize("m,d_in,d_out", [(3, 1000, 300), (20, 1300, 513), (40, 2048, 700), (513, 4100, 4099)])
+def test_infinities_and_nans_stay_with_their_token(env, m, d_in, d_out):
+    """An infinity or NaN in one token's inputs reaches all its outputs (no weight of the layer is zero
+    for certain, so: none of them is finite where the 64-bit product is not) and no other token's."""
+    dep, What = _layer(env, d_in, d_in, d_out, (2, 3, 4), 3.1, 10000, 10000)
+    gen = torch.Generator(device=DEV).manual_seed(m)
+    X = torch.randn((m, d_in), generator=gen, device=DEV).to(torch.float16)
+    bad = X.clone()
+    bad[m // 2, d_in // 3], bad[m - 1, d_in - 1] = float("inf"), float("nan")
+    Y, Z = env["P"].lut_matvec(dep, X, env["ws"]), env["P"].lut_matvec(dep, bad, env["ws"])
+    rows = torch.ones(m, dtype=torch.bool, device=DEV)
+    rows[[m // 2, m - 1]] = False
+    assert torch.equal(Y[rows], Z[rows])
+    ref = bad[~rows].double() @ What
+    assert not Z[~rows][~torch.isfinite(ref)].isfinite().any()
+    _check(Y, X, What)
