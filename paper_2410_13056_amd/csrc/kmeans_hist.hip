@@ -403,8 +403,8 @@ __device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketS
             if (M > 0) {
                 const uint32_t r = (uint32_t)(((uint64_t)(2 * j + 1) * M) / (uint64_t)(2 * K));
                 const int g0 = lane & ~(L - 1);  // first lane of this group inside its wavefront
-                // largest b with ncum[b] <= r: the L lanes probe L evenly spaced buckets at a time
-                // (ncum does not decrease, so the probes that pass come first)
+                // largest b with at most r weights below it: the L lanes probe L evenly spaced buckets
+                // at a time (the counts below do not decrease, so the probes that pass come first)
                 int lo = 0, hi_b = kBuckets - 1;
                 while (lo < hi_b) {
                     const int step = (hi_b - lo + L - 1) / L;

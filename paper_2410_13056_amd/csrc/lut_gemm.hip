@@ -17,7 +17,8 @@
 //   * many tokens: lut_decode_kernel writes W_hat once in operand order, override_kernel puts the
 //     entries of O_q in, and weight_gemm_kernel multiplies.
 // Every sum has a fixed order: results are reproducible bit for bit, and a layer's result does
-// not depend on the other layers of a call.
+// not depend on the other layers of a call (a workspace too small for a layer's plan aside, which
+// sends that layer token by token).
 //
 // Measured against one token after the other (us per call): two 13824x5120 layers, 16 tokens 281 ->
 // 56, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 304, of which the
@@ -25,7 +26,9 @@
 // (4.2 TB/s).  The error against 64 bits is the same within a few per cent (1.0e-7 to 1.4e-7).
 // What bounds the few-token kernel is instruction issue (half of its time is vector instructions,
 // a third LDS look-ups at 2.4 clocks each, which overlap poorly with 3 wavefronts per SIMD) and,
-// for small layers, the first pass through its code.
+// for small layers, the first pass through its code: 52 to 85 KB, a body for each width.  Registers
+// are all in use: the variants of 4, 8 and 16 tokens keep one vector register in memory, those of
+// 16 and 32 move 28 and 303 scalar registers through lanes of vector registers.
 #include "lut_gemm.h"
 #include <limits.h>
 

@@ -117,12 +117,13 @@ __global__ __launch_bounds__(kT) void rtn_kernel(const TW *__restrict__ W, int64
             zero[i * n_groups + g] = lo;
         }
         if (!kept && delta != 0.f) {
-            // The correctly rounded quotient (w - lo) / delta.  With delta well inside the
-            // normal range this is the usual division sequence - reciprocal estimate, one
-            // Newton step, then two residual corrections of the quotient - with the part that
-            // only depends on delta done once per step instead of once per weight; no
-            // intermediate can leave the normal range for a quotient that rounds to a code
-            // above 0.  Other steps (tiny or huge delta) divide in the ordinary way.
+            // The correctly rounded quotient (w - lo) / delta by Markstein's method (Computation of
+            // elementary functions on the IBM RISC System/6000 processor, 1990): the reciprocal by a
+            // Newton step from an estimate, the quotient from it, then its residual, exact in a fused
+            // multiply-add, as a correction - twice, since the reciprocal may be off by an ulp.  What
+            // depends on delta alone is done once per step instead of once per weight; no intermediate
+            // can leave the normal range, with delta well inside it, for a quotient that rounds to a
+            // code above 0.  Other steps (tiny or huge delta) divide in the ordinary way.
             float quo[kPer];
             if (delta >= 0x1p-60f && delta <= 0x1p60f) {
                 const float y0 = __builtin_amdgcn_rcpf(delta);

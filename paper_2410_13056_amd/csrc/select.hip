@@ -1894,8 +1894,9 @@ int launch_weight_select(WselArgs a, const WselPlan &p, int64_t k, int32_t *idx_
     // fast chain
     wsel_sample_kernel<TW><<<(unsigned)sample_blocks, kSampleThreads, 0, s>>>(a, w.hist);
     cmpq_timing_before(CMPQ_KERNEL_OUTLIER_STAGE, s);
-    if (std::is_same<TW, __half>::value && a.score == CMPQ_SCORE_RESIDUAL && !a.codes)
-        wsel_stage_kernel<TW, true><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.hist);
+    constexpr bool kHalf = std::is_same<TW, __half>::value;
+    if (kHalf && a.score == CMPQ_SCORE_RESIDUAL && !a.codes)
+        wsel_stage_kernel<TW, kHalf><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.hist);
     else
         wsel_stage_kernel<TW, false><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.hist);
     cmpq_timing_after(CMPQ_KERNEL_OUTLIER_STAGE, s);
