@@ -204,6 +204,12 @@ struct RankKeys {
             constexpr int kBinsPer = 2048 / kRankThreads;
 #pragma unroll
             for (int q = 0; q < kBinsPer; ++q) sh.hist[threadIdx.x + q * kRankThreads] = 0;
+            // a rank past the last live key falls in no digit: digit 0 and the rank stay, and every live
+            // key is taken in the end, as in block_kth_largest
+            if (threadIdx.x == 0) {
+                sh.rem = rem;
+                sh.prefix = prefix;
+            }
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < PER; ++r)
@@ -215,12 +221,6 @@ struct RankKeys {
 #pragma unroll
             for (int q = 0; q < kBinsPer; ++q) sum += v[q] = sh.hist[top - q];
             uint32_t before = block_scan_excl_u32(sum, sh.scan, &total);
-            // a rank past the last live key falls in no digit: digit 0 and the rank stay, and every live
-            // key is taken in the end, as in block_kth_largest
-            if (threadIdx.x == 0 && rem > total) {
-                sh.rem = rem;
-                sh.prefix = prefix;
-            }
 #pragma unroll
             for (int q = 0; q < kBinsPer; ++q) {
                 if (before < rem && rem <= before + v[q]) {
@@ -1237,9 +1237,14 @@ __global__ __launch_bounds__(kSampleThreads) void wsel_sample_kernel(WselArgs a,
         }
         cur = nxt;
     }
-#pragma unroll
-    for (int d = CMPQ_WAVE / 2; d > 0; d >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d, CMPQ_WAVE));
-    if (lane == 0) atomicMax(&largest, top);
+    // the largest of the wavefront ends up in its last lane (steps of wave_scan_incl_u32)
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x111, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x112, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x114, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x118, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x142, 0xA, 0xF, false));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x143, 0xC, 0xF, false));
+    if (lane == CMPQ_WAVE - 1) atomicMax(&largest, top);
     __syncthreads();
     if (threadIdx.x == 0) atomicMax(&hist[kHistTop + (blockIdx.x & (kSets - 1))], largest);
     uint32_t *set = hist + kHistSample + (blockIdx.x & (kSets - 1)) * kSampleSet;
@@ -1295,15 +1300,15 @@ __device__ __forceinline__ uint32_t sample_guess(const uint32_t *__restrict__ hi
 #pragma unroll
         for (int c = 1; c < kSets; ++c) top = max(top, hist[kHistTop + c]);
         width = (float)(top - lower);
-        from_top = (float)in / (float)count;
+        from_top = (float)in * __builtin_amdgcn_rcpf((float)count);
     } else if ((below | above) == 0) {
         return min(lower, 0x7f800000u);
     } else {
         // densities l at the lower edge and h at the upper one, (l + h) / 2 = count; the guess lies t
         // below the upper edge, h t + (l - h) t^2 / 2 = in
-        const float n = (float)count, l0 = (float)below + n, h0 = (float)above + n, scale = 2.f * n / (l0 + h0);
-        const float l = l0 * scale, h = h0 * scale, i = (float)in;
-        from_top = 2.f * i / (h + __builtin_sqrtf(h * h + 2.f * (l - h) * i));
+        const float n = (float)count, l0 = (float)below + n, h0 = (float)above + n;
+        const float scale = 2.f * n * __builtin_amdgcn_rcpf(l0 + h0), l = l0 * scale, h = h0 * scale, i = (float)in;
+        from_top = 2.f * i * __builtin_amdgcn_rcpf(h + __builtin_amdgcn_sqrtf(fmaxf(h * h + 2.f * (l - h) * i, 0.f)));
     }
     const float share = fminf(fmaxf(1.f - from_top, 0.f), 1.f);
     return min(lower + (uint32_t)(share * width), 0x7f800000u);
