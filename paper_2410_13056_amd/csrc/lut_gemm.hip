@@ -21,12 +21,13 @@
 // sends that layer token by token).
 //
 // Measured against one token after the other (us per call): two 13824x5120 layers, 16 tokens 281 ->
-// 56, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 304, of which the
-// product 210 (690 TFLOP/s of the 1144 that a large library product reaches here), decoding 66
-// (4.2 TB/s).  The error against 64 bits is the same within a few per cent (1.0e-7 to 1.4e-7).
-// What bounds the few-token kernel is instruction issue (half of its time is vector instructions,
-// a third LDS look-ups at 2.4 clocks each, which overlap poorly with 3 wavefronts per SIMD) and,
-// for small layers, the first pass through its code: 52 to 85 KB, a body for each width.  Registers
+// 56, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 312, of which, under
+// the profiler, the product 226 (636 TFLOP/s of the 1144 that a large library product reaches here),
+// decoding 65 (4.3 TB/s written).  The error against 64 bits is the same within a few per cent
+// (1.0e-7 to 1.4e-7).  What bounds the few-token kernel is its decoding (of its 37 us at 16 tokens 39 %
+// is issue of vector instructions, a quarter LDS look-ups, 7 % matrix cores; they overlap poorly with
+// 3 wavefronts per SIMD) and, for small layers, the first pass through its code: 52 to 85 KB, a body
+// for each width.  Registers
 // are all in use: the variants of 4, 8 and 16 tokens keep one vector register in memory, those of
 // 16 and 32 move 28 and 303 scalar registers through lanes of vector registers.
 #include "lut_gemm.h"
