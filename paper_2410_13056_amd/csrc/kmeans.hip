@@ -409,11 +409,20 @@ size_t cmpq_ws_kmeans_arrangement(int64_t d_in, int64_t d_out) {
     return align_up((size_t)(d_in > 0 ? d_in : 0) * kmeans_hist_arrangement_stride(d_out), 256);
 }
 
-size_t cmpq_ws_kmeans(int64_t d_in, int64_t) {
-    // ... | each channel's row in its width group | what cmpq_pack_with_error needs when the
-    // stored format is asked for and the histogram kernel does not take the input
-    return ws_kmeans_base(d_in) + align_up((size_t)(d_in > 0 ? d_in : 1) * sizeof(int32_t), 256) +
-           cmpq_ws_pack_with_error(d_in);
+// ... | each channel's row in its width group
+static size_t ws_kmeans_rows(int64_t d_in) {
+    return ws_kmeans_base(d_in) + align_up((size_t)(d_in > 0 ? d_in : 1) * sizeof(int32_t), 256);
+}
+
+// What every call needs: ... | what cmpq_pack_with_error needs when the stored format is asked for and the
+// histogram kernels do not take the input.
+static size_t ws_kmeans_least(int64_t d_in) { return ws_kmeans_rows(d_in) + cmpq_ws_pack_with_error(d_in); }
+
+size_t cmpq_ws_kmeans(int64_t d_in, int64_t d_out) {
+    // in the place of the latter, the channels' tables where the histogram kernels run (with less they run
+    // a part of the channels at a time)
+    const size_t least = ws_kmeans_least(d_in), hist = ws_kmeans_rows(d_in) + align_up(kmeans_hist_scratch(d_in, d_out), 256);
+    return least > hist ? least : hist;
 }
 
 extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, size_t ws_bytes, void *stream) {
@@ -462,10 +471,11 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
     a.arr_reuse = nullptr;
     a.arr_stride = 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!ws || reinterpret_cast<uintptr_t>(ws) % 256 != 0 || ws_bytes < cmpq_ws_kmeans(d_in, d_out))
+    if (!ws || reinterpret_cast<uintptr_t>(ws) % 256 != 0 || ws_bytes < ws_kmeans_least(d_in))
         return CMPQ_EWORKSPACE;
     char *ws_row_of = static_cast<char *>(ws) + ws_kmeans_base(d_in);
-    char *ws_tail = ws_row_of + align_up((size_t)d_in * sizeof(int32_t), 256);
+    char *ws_tail = static_cast<char *>(ws) + ws_kmeans_rows(d_in);
+    const size_t tail_bytes = ws_bytes - ws_kmeans_rows(d_in);
     const bool hist_takes_it = kmeans_fast_eligible(a, j.dtype) && (j.algorithm != CMPQ_KMEANS_DIRECT || a.start_given);
     // Rows of other lengths and alignments run on the histogram kernel as well (4099x3001 weights, both
     // quantizations with packing and error: 0.15 ms there, 2.24 ms on the general kernels), but keep no
@@ -514,7 +524,7 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
         // the bucket kernel takes every channel itself
         // (so does a run from given levels, whichever implementation is named)
         if (hist_takes_it) {
-            if (const int rc = launch_kmeans_hist(a, s)) return rc;
+            if (const int rc = launch_kmeans_hist(a, ws_tail, tail_bytes, s)) return rc;
             return a.fused ? launch_error_totals(j.err_ch, j.sumsq, d_in, j.err_total, s) : CMPQ_OK;
         }
         a.deferred = static_cast<uint8_t *>(ws);
@@ -524,7 +534,7 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
     }
     if (ragged) {
         a.ragged = 1;
-        if (const int rc = launch_kmeans_hist(a, s)) return rc;
+        if (const int rc = launch_kmeans_hist(a, ws_tail, tail_bytes, s)) return rc;
         return a.fused ? launch_error_totals(j.err_ch, j.sumsq, d_in, j.err_total, s) : CMPQ_OK;
     }
     if (j.dtype == CMPQ_F16)

@@ -40,7 +40,10 @@ struct KmArgs {
 
 // Histogram k-means (kmeans_hist.hip) and fixed-point brute-force k-means
 // (kmeans_fast.hip), both for fp16 weights with unit importance.
-int launch_kmeans_hist(const KmArgs &a, hipStream_t s);  // honours a.fused, a.arr_keep, a.arr_reuse
+// Honours a.fused, a.arr_keep, a.arr_reuse.  With less scratch than kmeans_hist_scratch() the channels are worked
+// on in parts; CMPQ_EWORKSPACE where not even one fits.
+int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hipStream_t s);
+size_t kmeans_hist_scratch(int64_t d_in, int64_t d_out);
 // Bytes per channel of the arrangement for channels of d_out weights (0: the kernel does not take them).
 size_t kmeans_hist_arrangement_stride(int64_t d_out);
 int launch_kmeans_fast(const KmArgs &a, hipStream_t s);

@@ -2,24 +2,42 @@
 // importance (Sec. 3.2.1 of arXiv 2410.13056; entries of O_q removed as in Sec. 3.2.2).
 //
 // A Lloyd round on a line only needs, for each boundary between two neighbouring
-// levels, how many weights lie below it and what they sum to.  The kernel arranges the
-// channel once so that each round reads these numbers instead of recounting them:
+// levels, how many weights lie below it and what they sum to.  Three kernels:
 //
-//   * every weight becomes its 16-bit order key (unsigned order = value order); the top
-//     bits name a bucket (1024 buckets of 64 places, or 512 of 128 for short channels),
-//     the low bits the place inside it;
-//   * one pass counts the buckets and sums the places, a scan turns this into exclusive
-//     prefixes of the count and of the exact integer sum of x*2^24 (inside a bucket
-//     x*2^24 is affine in the place: sign, exponent and top mantissa bits are shared);
-//   * a second pass scatters the places into an LDS byte array ordered by bucket (any
-//     order inside a bucket); a bucket's stretch starts on a 4-byte boundary and its
-//     unused tail holds a filler above every place, so a scan reads whole words;
-//   * a round then costs, per boundary, the prefix of its bucket plus a scan of that one
-//     bucket (a group of lanes per boundary, four places per word compared at once), a
-//     cell is the difference of two boundaries, and the new level is the exact integer sum
-//     divided in fp64 and rounded once to fp32 - the value an fp64 reference computes;
-//   * when no boundary moved the iteration has reached its fixed point and the remaining
-//     rounds, which would repeat it, are skipped.
+//   * kmeans_build_kernel arranges a channel once so that a round reads these numbers instead of
+//     recounting them.  Every weight becomes its 16-bit order key (unsigned order = value order); the
+//     top bits name a bucket (1024 of 64 places for long channels, 512 of 128 otherwise), the low bits
+//     the place inside it.  One pass counts the buckets and sums the places, a scan turns this into
+//     exclusive prefixes of the count and of the exact integer sum of x*2^24 (inside a bucket x*2^24 is
+//     affine in the place: sign, exponent and top mantissa bits are shared), a second pass scatters the
+//     places into an LDS byte array ordered by bucket (any order inside a bucket; a bucket's stretch
+//     starts on a whole word and its unused tail holds a filler above every place).  The tables go to
+//     memory;
+//   * kmeans_rounds_kernel runs start-up and rounds from the tables: per boundary the prefix of its
+//     bucket plus a scan of that one bucket; a cell is the difference of two boundaries, and the new
+//     level is the exact integer sum divided in fp64 and rounded once to fp32 - the value an fp64
+//     reference computes.  When no boundary moved the iteration has reached its fixed point and the
+//     remaining rounds, which would repeat it, are skipped;
+//   * kmeans_code_kernel codes the weights with the final boundaries, and writes the stored format and
+//     the error where they are asked for.
+//
+// A quantization without entries of O_q can leave its tables to a later one with them.  That one has
+// kmeans_removed_kernel arrange the removed entries alone, in the same form, and its rounds take
+// (all) - (removed) at every boundary.
+//
+// Why three kernels.  A round is a chain of some 200 dependent instructions and two table look-ups, 20
+// times over, which one wavefront can run for several channels at once - while a channel's tables take
+// 5 to 36 KB to build in LDS.  In one kernel the rounds, half of a channel's time, hold that LDS and all
+// wavefronts of the channel, and leave a compute unit with 3 to 16 channels to hide the chain behind (2400
+// cycles a round at 28672 weights, where a wavefront alone needs 1400).  On their own they hold 4 to 9 KB a
+// channel and one wavefront for 1 to 4.  Both quantizations of a layer, widths 2 to 4 at 3.5 on average, 1 %
+// in O_q, us in one kernel -> now (first + final):
+//   8192 x 28672  471 + 594 -> 360 + 459      4096 x 11008  192 + 244 -> 99 + 169
+//   28672 x 8192  574 + 751 -> 459 + 606      8192 x 1024    98 + 133 -> 62 + 124
+//   4096 x 4096    82 + 112 ->  63 + 100
+// Tried on the way, same results: rounds of 4 / 2 / 1 channels on one wavefront inside the one kernel (1024
+// weights 98 -> 70, 8192 weights 574 -> 630), all tables of the rounds in LDS (28672 x 8192 528: too few
+// channels at a time), none of them (gate-shaped 373, the records' lines do not stay in L2).
 //
 // All sums are integers, so the result is reproducible bit for bit and identical to the
 // brute-force kernels.  Boundaries are exact: between distinct neighbouring levels
@@ -28,10 +46,7 @@
 // index) whenever their order may have changed; they need not stay ascending because a
 // level without members keeps a stale value.
 //
-// The kernel is bound by instruction issue, not by latency: the serial part of a round
-// runs on one wavefront while the others sleep at barriers, and several workgroups share
-// a compute unit.  A channel with NaN or infinity raises the status flag and gets levels 0
-// and codes 0.
+// A channel with NaN or infinity raises the status flag and gets levels 0 and codes 0.
 #include <type_traits>
 
 #include "kmeans_args.h"
@@ -76,47 +91,40 @@ __device__ __forceinline__ void store_codes(uint8_t *row, int g, int d_out, uint
     }
 }
 template <bool RAGGED, int T>
-__device__ __forceinline__ void zero_codes(uint8_t *row, int n_groups, int d_out) {
+__device__ __forceinline__ void zero_codes(uint8_t *row, int tid, int n_groups, int d_out) {
     if (!row) return;
-    for (int g = threadIdx.x; g < n_groups; g += T) store_codes<RAGGED>(row, g, d_out, 0);
+    for (int g = tid; g < n_groups; g += T) store_codes<RAGGED>(row, g, d_out, 0);
 }
 
-// One word per bucket (dynamic LDS): where the bucket's stretch of the byte array begins, and above
-// it the exclusive prefix over buckets of the counts (both stay below 2^16).  While the places are
-// scattered the low half is the bucket's cursor; after the rounds the words hold the coding table.
-// The last bucket lies past the finite values: it is empty, and stretch_end() asks for no entry past
-// the table.  (Two 16-bit tables and a cursor of their own, 4 bytes a bucket more, let a compute unit hold 13
-// workgroups of 64 lanes at 1024 weights where these let it hold 16: the layer of 8192 such channels
-// took 331 us and takes 316, 4096x4096 took 605 and takes 599.)
-__device__ __forceinline__ uint32_t stretch_of(uint32_t word) { return word & 0xffffu; }
-__device__ __forceinline__ uint32_t before_of(uint32_t word) { return word >> 16; }
-template <int LB>
-__device__ __forceinline__ uint32_t stretch_end(const uint32_t *words, uint32_t bucket) {
-    return stretch_of(words[min(bucket + 1u, (1u << (16 - LB)) - 1u)]);
-}
-
-template <int LB>
-struct BucketShared {
-    static constexpr int kBuckets = 1 << (16 - LB);
-    long long scum[kBuckets + 1];   // count << 32 | sum of places; then the exclusive prefix
-                                    // over buckets of sum(x * 2^24)
-    uint32_t part_n[2][CMPQ_KMAX];  // by round parity, per boundary: kept weights of its bucket
-    uint32_t part_l[2][CMPQ_KMAX];  //   not above it, and the sum of their places
-    float cent[CMPQ_KMAX];          // levels by level index
-    uint32_t tk[2][CMPQ_KMAX];      // by round parity: boundary keys by sorted position
-    uint32_t code_of[CMPQ_KMAX];    // level index that each sorted position stands for
-    int go[2];                      // by round parity: another round follows
-    uint32_t scan32[17];
-    unsigned long long scan64[17];
-    int seg_lo, n_excl;
-    uint32_t kept;                  // weights that take part
-    double cent64[CMPQ_KMAX];       // final levels by level index, as the error sum reads them
+// A channel's tables in memory: head | one record per bucket | the place array.
+struct TableHead {
+    uint32_t magic;      // kTableMagic + 1: tables follow; + 2: the channel held a non-finite weight
+    uint32_t kept;       // weights that take part
+    uint32_t d_out, quads;  // row length; groups of 16 bytes of the place array that hold stretches
+    // exact sum of x * 2^24 over the keys below key k << 10 (64 runs of 1024 keys: one sign and exponent
+    // each); [64] is the sum over all
+    long long base[65];
+    uint32_t unused2[2];
+    uint32_t fill[4];    // filler
 };
+constexpr uint32_t kTableMagic = 0xC3A77B00u;
+// Record of a bucket: .x = word of the place array where its stretch begins | weights below it << 16; .y =
+// sum over the buckets below it that share its sign and exponent, in units of that exponent's spacing
+// (|.y| <= 2047 * 32768).  A stretch ends where the next one begins.
+static_assert(sizeof(TableHead) == 560, "records start on 16 bytes");
+// 16 bytes more than the place array: scans read whole groups of 4 words.
+__host__ __device__ inline size_t table_bytes(int64_t d_out, int lb) {
+    return sizeof(TableHead) + ((size_t)8 << (16 - lb)) + bucket_arr_bytes(d_out, lb) + 16;
+}
 
-// Two order keys in one word -> the two fp16 patterns they stand for (inverse of keys_of_half2).
-__device__ __forceinline__ uint32_t halves_of_keys2(uint32_t kk) {
-    const uint32_t pos = (kk >> 15) & 0x00010001u;  // key of a non-negative value: only the sign bit was flipped
-    return kk ^ (0xffffffffu ^ __umul24(pos, 0x7fffu));
+// Of bucket b: mantissa of its first key with the sign, and the exponent's shift: x * 2^24 = (mantissa + place) << sh.
+template <int LB>
+__device__ __forceinline__ void bucket_scale(uint32_t b, int &mant, uint32_t &sh) {
+    const uint32_t h = half_of_key(b << LB);
+    const uint32_t e = (h >> 10) & 31u;
+    const int mag = (int)((e ? 1024u : 0u) + (h & 1023u));
+    sh = (e > 1 ? e : 1) - 1;
+    mant = (h & 0x8000u) ? -mag : mag;
 }
 
 template <int G>
@@ -124,41 +132,15 @@ __device__ __forceinline__ uint32_t elem_key(const uint32_t (&keys)[2 * G], int 
     return (keys[2 * k + (e >> 1)] >> (16 * (e & 1))) & 0xffffu;
 }
 
-// A group of L lanes: among the places of one bucket, arr[begin, end) with begin and end
-// multiples of 4 and filler in the unused tail, how many are <= pl, and their sum (U words
-// per lane in flight).  Four places per word are compared at once: a byte plus (127 - pl) reaches bit 7 exactly when
-// it is above pl (places and pl are at most 127, the filler is 128: no carry leaves a
-// byte).  The inverted bits 7 are counted, and a dot product of the word's bytes with them
-// gives 128 times the sum of the places they mark (below 2^32 for any channel: at most
-// 32 768 places of at most 127).  Result valid in every lane of the group.
-template <int L, int U = 4>
-__device__ __forceinline__ void scan_bucket(const unsigned char *arr, uint32_t begin, uint32_t end,
-                                            uint32_t pl, uint32_t &n, uint32_t &l) {
-    const int sub = threadIdx.x & (L - 1);
-    const uint32_t *words = reinterpret_cast<const uint32_t *>(arr);
-    const uint32_t w_end = end >> 2;
-    const uint32_t bias = 0x7f7f7f7fu - pl * 0x01010101u;
-    uint32_t cn = 0, cl7 = 0;
-    for (uint32_t j = (begin >> 2) + sub; j < w_end; j += U * L) {  // U reads in flight
-        uint32_t x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = j + u * L < w_end ? words[j + u * L] : kFill4;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t le7 = ~(x[u] + bias) & 0x80808080u;  // bit 7 per byte <= pl
-            cn += (uint32_t)__builtin_popcount(le7);
-            cl7 = __builtin_amdgcn_udot4(x[u], le7, cl7, false);
-        }
-    }
-    n = group_sum<L>(cn);
-    l = group_sum<L>(cl7) >> 7;
-}
-
-// Counts the buckets and sums the places of the kept weights (packed 64-bit LDS atomics).
-template <int G, int T, int LB, bool MASKED>
-__device__ __forceinline__ void count_buckets(const uint32_t (&keys)[2 * G], const uint32_t *removed,
-                                              long long *scum, int n_groups) {
-    const int tid = threadIdx.x;
+// Counts the buckets and sums the places of the kept weights with packed LDS atomics: `n << kShift |
+// sum of places`.  In 32 bits the sum of a bucket may run over into its count (channels of more than
+// 4096 weights); every such carry makes the counts add up to more than the weights, which is how the
+// caller finds out that it has to count again in 64 bits.
+template <int T>
+constexpr int count_shift() { return T >= 512 ? 16 : (T == 256 ? 18 : (T == 128 ? 19 : 20)); }
+template <int G, int T, int LB, bool MASKED, int kShift, typename Word>
+__device__ __forceinline__ void count_buckets(const uint32_t (&keys)[2 * G], const uint32_t *removed, Word *table,
+                                              int tid, int n_groups) {
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int g = k * T + tid;
@@ -169,8 +151,7 @@ __device__ __forceinline__ void count_buckets(const uint32_t (&keys)[2 * G], con
             for (int e = 0; e < 4; ++e) {
                 if (!MASKED || ((kept >> e) & 1u)) {
                     const uint32_t key = elem_key<G>(keys, k, e);
-                    atomicAdd(reinterpret_cast<unsigned long long *>(&scum[key >> LB]),
-                              (1ull << 32) | (key & ((1u << LB) - 1)));
+                    atomicAdd(&table[key >> LB], ((Word)1 << kShift) | (key & ((1u << LB) - 1)));
                 }
             }
         }
@@ -180,8 +161,7 @@ __device__ __forceinline__ void count_buckets(const uint32_t (&keys)[2 * G], con
 // Puts the place of every kept weight into its bucket's stretch of the byte array.
 template <int G, int T, int LB, bool MASKED>
 __device__ __forceinline__ void scatter_places(const uint32_t (&keys)[2 * G], const uint32_t *removed,
-                                               uint32_t *cursor, unsigned char *arr, int n_groups) {
-    const int tid = threadIdx.x;
+                                               uint32_t *cursor, unsigned char *arr, int tid, int n_groups) {
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int g = k * T + tid;
@@ -192,11 +172,692 @@ __device__ __forceinline__ void scatter_places(const uint32_t (&keys)[2 * G], co
             for (int e = 0; e < 4; ++e) {
                 if (!MASKED || ((kept >> e) & 1u)) {
                     const uint32_t key = elem_key<G>(keys, k, e);
-                    const uint32_t pos = stretch_of(atomicAdd(&cursor[key >> LB], 1u));
+                    const uint32_t pos = atomicAdd(&cursor[key >> LB], 1u);
                     arr[pos] = (unsigned char)(key & ((1u << LB) - 1));
                 }
             }
         }
+    }
+}
+
+// The exclusive prefix over the kBuckets buckets of a channel: every lane hands over the counts n and sums of
+// places l of its `per` buckets from b0 on (lanes past the buckets: none).  Writes the records and the head's
+// sums to memory; start[r] becomes the byte where the bucket's stretch begins.  Returns the number of weights
+// counted.  All T lanes call it; contains barriers.
+template <int T>
+struct PrefixShared {
+    uint32_t wave_n[T / CMPQ_WAVE + 1];
+    long long run[64];  // per sign and exponent: sum of x * 2^24
+};
+template <int T, int LB>
+__device__ __forceinline__ uint32_t write_records(PrefixShared<T> &sm, const uint32_t *n, const uint32_t *l,
+                                                  uint32_t *start, TableHead *head, uint2 *rec, uint32_t *total_n) {
+    constexpr int kBuckets = 1 << (16 - LB), kPer = kBuckets / T > 0 ? kBuckets / T : 1;
+    constexpr int kSeg = T >= 64 ? (T / 64 < kBuckets / 64 ? T / 64 : kBuckets / 64) : 1;  // lanes that share a sign and exponent
+    static_assert(kBuckets >= T, "a lane owns whole buckets");
+    constexpr int kWaves = T / CMPQ_WAVE;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b0 = tid * kPer;
+    uint32_t n_loc = 0;  // count | padded count << 16: both stay below 2^16
+    int u_loc = 0, mant;
+    uint32_t sh;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        n_loc += n[r] | (((n[r] + 3) & ~3u) << 16);
+        bucket_scale<LB>((uint32_t)(b0 + r), mant, sh);
+        u_loc += __mul24(mant, (int)n[r]) + (int)l[r];
+    }
+    // sums inside a run of equal sign and exponent (its kSeg lanes are neighbours)
+    int u_incl = u_loc;
+#pragma unroll
+    for (int d = 1; d < kSeg; d <<= 1) {
+        const int up = __shfl_up(u_incl, d, CMPQ_WAVE);
+        if ((lane & (kSeg - 1)) >= d) u_incl += up;
+    }
+    if ((lane & (kSeg - 1)) == kSeg - 1) {
+        bucket_scale<LB>((uint32_t)b0, mant, sh);
+        sm.run[(b0 << LB) >> 10] = (long long)((unsigned long long)(long long)u_incl << sh);
+    }
+    uint32_t n_incl = wave_scan_incl_u32(n_loc);
+    if (lane == 63) sm.wave_n[wave] = n_incl;
+    __syncthreads();
+    uint32_t n_run = n_incl - n_loc, n_tot = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t t = sm.wave_n[w];
+        if (w < wave) n_run += t;
+        n_tot += t;
+    }
+    if (wave == 0) {
+        const unsigned long long v = (unsigned long long)sm.run[lane];
+        const unsigned long long incl = wave_scan_incl_u64(v);
+        head->base[lane] = (long long)(incl - v);
+        if (lane == 63) head->base[64] = (long long)incl;
+        if (lane < 4) head->fill[lane] = kFill4;
+    }
+    int u_run = u_incl - u_loc;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        start[r] = n_run >> 16;
+        rec[b0 + r] = make_uint2((n_run >> 18) | (n_run << 16), (uint32_t)u_run);
+        bucket_scale<LB>((uint32_t)(b0 + r), mant, sh);
+        n_run += n[r] | (((n[r] + 3) & ~3u) << 16);
+        u_run += __mul24(mant, (int)n[r]) + (int)l[r];
+    }
+    *total_n = n_tot;
+    return n_tot & 0xffffu;
+}
+
+// The tables of one channel, built in LDS.  Bound by LDS (an atomic, a returning atomic and a byte store to
+// scattered addresses per weight: 6.7 clocks a wavefront instruction, two thirds of them bank conflicts) and
+// by what it reads and writes: 2 B a weight in, 1.1 B and 8 B a bucket out.  8192 x 28672 in 219 us = 3.9 TB/s,
+// LDS busy 61 % of the time.  64 registers: 8 wavefronts a SIMD, so that one workgroup's fetch runs beside the
+// others' LDS passes.  Counting in 32 bits where that is enough halves the LDS words of a count.
+template <int G, int T, int LB, bool MASKED, bool RAGGED>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void kmeans_build_kernel(KmArgs a, int64_t i0, unsigned char *tables, int64_t stride) {
+    constexpr int kBuckets = 1 << (16 - LB), kPer = kBuckets / T, kShift = count_shift<T>();
+    // dynamic LDS: places of the kept weights, ordered by bucket | removed-entry bitmap (one bit per weight;
+    // MASKED) | a word per bucket: count and sum of places, then the cursor of its stretch
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ PrefixShared<T> sm;
+    __shared__ uint32_t flag[T / CMPQ_WAVE];
+    const int64_t i = i0 + blockIdx.x;
+    const int b = a.bits[i];
+    if (b < 1 || b > 4) return;
+    const int tid = threadIdx.x;
+    const int d_out = (int)a.d_out, n_groups = RAGGED ? (d_out + 3) >> 2 : d_out >> 2;
+    const size_t arr_bytes = bucket_arr_bytes(d_out, LB);
+    const int n_words = MASKED ? (d_out + 31) >> 5 : 0;
+    unsigned char *arr = dyn;
+    uint32_t *removed = reinterpret_cast<uint32_t *>(dyn + arr_bytes);
+    uint32_t *cursor = removed + ((n_words + 3) & ~3);
+    const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
+    TableHead *head = reinterpret_cast<TableHead *>(tables + blockIdx.x * stride);
+    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
+
+    // lane owns groups g = k*T + tid of 4 weights, kept as packed 16-bit keys
+    uint32_t keys[2 * G];
+    uint32_t nonfinite = 0;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        const uint2 raw = load_group<RAGGED>(wrow, k * T + tid, n_groups, d_out);
+        keys[2 * k] = raw.x;
+        keys[2 * k + 1] = raw.y;
+    }
+    const uint4 fill = make_uint4(kFill4, kFill4, kFill4, kFill4);
+    for (int s = tid; s < (int)(arr_bytes >> 4); s += T) reinterpret_cast<uint4 *>(arr)[s] = fill;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) cursor[r * T + tid] = 0;
+    for (int s = tid; s < n_words; s += T)  // what fills up the last group counts as removed
+        removed[s] = RAGGED && s == d_out >> 5 && (d_out & 3) ? ((1u << (4 - (d_out & 3))) - 1u) << (d_out & 31) : 0u;
+#pragma unroll
+    for (int k = 0; k < 2 * G; ++k) {
+        nonfinite |= nonfinite_of_half2(keys[k]);
+        keys[k] = keys_of_half2(keys[k]);
+    }
+    const bool bad = __ballot((nonfinite & 0x80008000u) != 0u) != 0ull;
+    if ((tid & 63) == 0) flag[tid >> 6] = bad;
+    __syncthreads();
+    {
+        uint32_t any = 0;
+#pragma unroll
+        for (int w = 0; w < T / CMPQ_WAVE; ++w) any |= flag[w];
+        if (any) {  // the same for all lanes
+            if (tid == 0) head->magic = kTableMagic + 2u, head->d_out = (uint32_t)d_out;
+            return;
+        }
+    }
+    int n_ex = 0;
+    if constexpr (MASKED) {  // entries of O_q do not take part in the clustering
+        const int lo = a.seg ? a.seg[i] : 0;
+        n_ex = a.seg ? a.seg[i + 1] - lo : 0;
+        const int32_t chan_base = (int32_t)(i * a.d_out);
+        for (int e = tid; e < n_ex; e += T) {
+            const int o = a.out_idx[lo + e] - chan_base;
+            atomicOr(&removed[o >> 5], 1u << (o & 31));
+        }
+        __syncthreads();
+    }
+    count_buckets<G, T, LB, MASKED, kShift>(keys, removed, cursor, tid, n_groups);
+    __syncthreads();
+    uint32_t n[kPer], l[kPer], start[kPer], total;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const uint32_t w = cursor[tid * kPer + r];
+        n[r] = w >> kShift;
+        l[r] = w & ((1u << kShift) - 1u);
+    }
+    uint32_t kept = write_records<T, LB>(sm, n, l, start, head, rec, &total);
+    if constexpr (T >= 256) {
+        if (kept != (uint32_t)(d_out - n_ex)) {  // a sum of places ran over into a count (the same for all lanes):
+            unsigned long long *wide = reinterpret_cast<unsigned long long *>(arr);  // again, in 64 bits
+            __syncthreads();
+            for (int s = tid; s < kBuckets; s += T) wide[s] = 0;
+            __syncthreads();
+            count_buckets<G, T, LB, MASKED, 32>(keys, removed, wide, tid, n_groups);
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) {
+                const unsigned long long w = wide[tid * kPer + r];
+                n[r] = (uint32_t)(w >> 32);
+                l[r] = (uint32_t)w;
+            }
+            __syncthreads();
+            for (int s = tid; s < (int)(arr_bytes >> 4); s += T) reinterpret_cast<uint4 *>(arr)[s] = fill;
+            kept = write_records<T, LB>(sm, n, l, start, head, rec, &total);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) cursor[tid * kPer + r] = start[r];
+    __syncthreads();
+    scatter_places<G, T, LB, MASKED>(keys, removed, cursor, arr, tid, n_groups);
+    __syncthreads();
+    // the stretches, up to the last one's end; what a scan may read past it is defined too
+    const int used = min((int)(((total >> 16) + 15) >> 4) + 1, (int)(arr_bytes >> 4));
+    uint4 *dst = reinterpret_cast<uint4 *>(rec + kBuckets);
+    for (int s = tid; s < used; s += T) dst[s] = reinterpret_cast<const uint4 *>(arr)[s];
+    if (tid == 0) {
+        head->magic = kTableMagic + 1u;
+        head->kept = kept;
+        head->d_out = (uint32_t)d_out;
+        head->quads = (uint32_t)used;
+    }
+}
+
+// The removed entries of one channel (slice of out_idx), in the form of the tables above.  About 1 % of the
+// channel: bound by latency (a gather of their weights) and by the records.
+constexpr int kRemovedLanes = 256;
+template <int LB>
+__global__ __launch_bounds__(kRemovedLanes) void kmeans_removed_kernel(KmArgs a, int64_t i0, unsigned char *tables,
+                                                                      int64_t stride) {
+    constexpr int T = kRemovedLanes, kBuckets = 1 << (16 - LB), kPer = kBuckets / T;
+    __shared__ PrefixShared<T> sm;
+    __shared__ unsigned long long count[kBuckets];  // count << 32 | sum of places, then the cursors
+    const int64_t i = i0 + blockIdx.x;
+    const int b = a.bits[i];
+    if (b < 1 || b > 4) return;
+    const int tid = threadIdx.x;
+    const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
+    TableHead *head = reinterpret_cast<TableHead *>(tables + blockIdx.x * stride);
+    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
+    const int lo = a.seg[i], n_ex = min(a.seg[i + 1] - lo, (int)a.d_out);
+    if (n_ex <= 0) {
+        if (tid == 0) head->kept = 0;
+        return;
+    }
+    const int32_t chan_base = (int32_t)(i * a.d_out);
+    constexpr int kHeld = 2;  // entries whose keys a lane keeps for the second visit
+    uint32_t held[kHeld];
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const int e = u * T + tid;
+        held[u] = e < n_ex ? key_of_half(__half_as_ushort(wrow[a.out_idx[lo + e] - chan_base])) : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) count[r * T + tid] = 0;
+    __syncthreads();
+    auto each = [&](auto &&visit) {
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u)
+            if (u * T + tid < n_ex) visit(held[u]);
+        for (int e = kHeld * T + tid; e < n_ex; e += T) visit(key_of_half(__half_as_ushort(wrow[a.out_idx[lo + e] - chan_base])));
+    };
+    each([&](uint32_t key) { atomicAdd(&count[key >> LB], (1ull << 32) | (key & ((1u << LB) - 1))); });
+    __syncthreads();
+    uint32_t n[kPer], l[kPer], start[kPer], total;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const unsigned long long w = count[tid * kPer + r];
+        n[r] = (uint32_t)(w >> 32);
+        l[r] = (uint32_t)w;
+    }
+    write_records<T, LB>(sm, n, l, start, head, rec, &total);
+    unsigned char *arr = reinterpret_cast<unsigned char *>(rec + kBuckets);
+    uint32_t *cursor = reinterpret_cast<uint32_t *>(count);
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {  // (a lane's words lie in its own entries of `count`)
+        cursor[2 * (tid * kPer + r)] = start[r];
+        for (uint32_t s = start[r] + n[r]; s < ((start[r] + n[r] + 3) & ~3u); ++s) arr[s] = 0x80;
+    }
+    if (tid < 4) reinterpret_cast<uint32_t *>(arr + (total >> 16))[tid] = kFill4;  // a scan may read past the last stretch
+    __syncthreads();
+    each([&](uint32_t key) { arr[atomicAdd(&cursor[2 * (key >> LB)], 1u)] = (unsigned char)(key & ((1u << LB) - 1)); });
+    if (tid == 0) {
+        head->magic = kTableMagic + 1u;
+        head->kept = total & 0xffffu;
+    }
+}
+
+// What the rounds leave for the coding pass.
+struct ChannelFinal {
+    uint16_t tk[CMPQ_KMAX];      // boundary keys by sorted position
+    uint8_t code_of[CMPQ_KMAX];  // level index that each sorted position stands for
+    uint32_t ok;                 // 0: the channel was flagged, its codes are zero
+    uint32_t unused[3];
+};
+static_assert(sizeof(ChannelFinal) == 64, "one line of memory");
+
+// Sum over the R = 1, 2 or 4 rows of 16 lanes that share a channel; every row gets it.
+template <int R>
+__device__ __forceinline__ uint32_t row_group_sum(uint32_t v) {
+    if constexpr (R >= 2) {
+        const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = s[0] + s[1];
+    }
+    if constexpr (R >= 4) {
+        const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = s[0] + s[1];
+    }
+    return v;
+}
+
+// Value that lane `l` of the caller's row of 16 lanes holds.
+__device__ __forceinline__ float from_row_lane(float v, int l) {
+    return __shfl(v, (threadIdx.x & 48) | l, CMPQ_WAVE);
+}
+__device__ __forceinline__ int from_row_lane(int v, int l) {
+    return __shfl(v, (threadIdx.x & 48) | l, CMPQ_WAVE);
+}
+
+// Levels by level index (lane j of a row of 16 lanes holds c for j < K, infinity above) -> per sorted
+// position p (lane p): value, owning level, next distinct value above and the owners for the tie rule.
+// Handles repeated values and any order.  K may differ from row to row.
+__device__ __forceinline__ void rank_levels_in_rows(float c, int K, float &sorted, int &own, float &hi, int &owner_lo,
+                                                    int &owner_hi, bool &have_hi) {
+    const int j = threadIdx.x & 15;
+    int rank = 0;
+#pragma unroll 1
+    for (int l = 0; l < CMPQ_KMAX; ++l) {
+        const float cl = from_row_lane(c, l);
+        rank += (cl < c) || (cl == c && l < j);
+    }
+    sorted = INFINITY;
+    own = j;
+#pragma unroll 1
+    for (int l = 0; l < CMPQ_KMAX; ++l) {
+        const int rl = from_row_lane(rank, l);
+        const float cl = from_row_lane(c, l);
+        if (rl == j) {
+            sorted = cl;
+            own = l;
+        }
+    }
+    hi = INFINITY;
+    owner_lo = own;
+    owner_hi = 0;
+    bool have_lo = false;
+    have_hi = false;
+#pragma unroll 1
+    for (int l = 0; l < CMPQ_KMAX; ++l) {
+        const float sl = from_row_lane(sorted, l);
+        const int pl = from_row_lane(own, l);
+        if (!have_lo && sl == sorted) {
+            owner_lo = pl;
+            have_lo = true;
+        }
+        if (!have_hi && l > j && l < K && sl > sorted) {
+            hi = sl;
+            owner_hi = pl;
+            have_hi = true;
+        }
+    }
+    if (j >= K - 1) have_hi = false;
+}
+
+__device__ __forceinline__ uint4 load_words4(const uint32_t *p) {  // 4-byte aligned
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+// Keeps the compiler from moving the load of v past this point: it would otherwise wait for one group of
+// words, or put a load under the condition of its use, and pay several trips to memory for one.
+__device__ __forceinline__ void loaded(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+
+// A channel's sums per run and records in LDS (what the removed entries add to both taken off), and where its
+// place arrays lie in memory; with removed entries, also where the stretches of theirs begin.
+// No key that is looked up lies in the first or the last 8 * 128 keys but one: those buckets are left out.
+template <int LB, bool REM>
+struct ChannelView {
+    static constexpr uint32_t kBuckets = 1u << (16 - LB), kFirst = (0x0400u >> LB) - 1u, kLast = (0xfbffu >> LB) + 1u;
+    static constexpr uint32_t kRecs = (kLast - kFirst + 2u) & ~1u;
+    static constexpr uint32_t kBytes = (520 + 8 * kRecs + (REM ? 2 * kRecs : 0) + 15u) & ~15u;
+    unsigned char *at;
+    const uint32_t *arr, *rem_arr, *fill;  // memory
+    __device__ __forceinline__ long long *base() const { return reinterpret_cast<long long *>(at); }
+    __device__ __forceinline__ uint2 *rec() const { return reinterpret_cast<uint2 *>(at + 520); }  // [bucket - kFirst]
+    __device__ __forceinline__ uint16_t *rem_start() const { return reinterpret_cast<uint16_t *>(at + 520 + 8 * kRecs); }
+};
+
+// Sums of absolute differences of the bytes of a stretch of the place array (`len` words) to pl and to pl + 1,
+// over the words that row r of the channel's R rows takes: whole groups of 4 words in turn, then the 0 to 3
+// words after them; what a row lacks is filler, so that no lane has a condition to pass.  AHEAD groups are on
+// their way at a time.
+template <int R, int AHEAD>
+struct Stretch {
+    const uint32_t *src, *fill;
+    uint32_t len, r;
+    uint4 tail, x[AHEAD];
+    __device__ __forceinline__ const uint32_t *group(uint32_t q) const { return q < (len >> 2) ? src + 4 * q : fill; }
+    __device__ __forceinline__ void fetch(const uint32_t *from, uint32_t n_words, uint32_t row, const uint32_t *filler) {
+        src = from, len = n_words, r = row, fill = filler;
+        tail = load_words4((len & 3u) ? src + (len & ~3u) : fill);
+#pragma unroll
+        for (uint32_t u = 0; u < AHEAD; ++u) x[u] = load_words4(group(r + u * R));
+    }
+    __device__ __forceinline__ void wait() {
+        loaded(tail);
+#pragma unroll
+        for (uint32_t u = 0; u < AHEAD; ++u) loaded(x[u]);
+    }
+    // N bytes are looked at in all rows together.  Leaves the first groups in place: the sums can be taken again
+    // for another pl.
+    __device__ __forceinline__ void sums(uint32_t pl, uint32_t &A, uint32_t &B, uint32_t &N) const {
+        const uint32_t pl4 = pl * 0x01010101u, pu4 = pl4 + 0x01010101u;
+        const uint32_t m = (R == 1 || ((len >> 2) & (R - 1)) == r) ? len & 3u : 0u;
+        const uint32_t end[3] = {m > 0 ? tail.x : kFill4, m > 1 ? tail.y : kFill4, m > 2 ? tail.z : kFill4};
+        A = B = 0;
+        auto add = [&](uint32_t v) {
+            A = __builtin_amdgcn_sad_u8(v, pl4, A);
+            B = __builtin_amdgcn_sad_u8(v, pu4, B);
+        };
+#pragma unroll
+        for (int e = 0; e < 3; ++e) add(end[e]);
+#pragma unroll
+        for (uint32_t u = 0; u < AHEAD; ++u) add(x[u].x), add(x[u].y), add(x[u].z), add(x[u].w);
+        N = (16 * AHEAD + 12) * R;
+        for (uint32_t q = AHEAD * R; __ballot(q < (len >> 2)) != 0ull; q += AHEAD * R) {
+            uint4 y[AHEAD];
+#pragma unroll
+            for (uint32_t u = 0; u < AHEAD; ++u) y[u] = load_words4(group(q + r + u * R));
+#pragma unroll
+            for (uint32_t u = 0; u < AHEAD; ++u) loaded(y[u]);
+#pragma unroll
+            for (uint32_t u = 0; u < AHEAD; ++u) add(y[u].x), add(y[u].y), add(y[u].z), add(y[u].w);
+            N += 16 * AHEAD * R;
+        }
+    }
+};
+
+// The stretch of one bucket, less that of the removed entries in it.
+template <int R, int LB, int AHEAD, bool REM>
+struct BucketPlaces {
+    Stretch<R, AHEAD> all;
+    Stretch<R, 1> rem;
+    bool any_rem;
+    // b: the bucket, counted from kFirst
+    __device__ __forceinline__ void fetch(const ChannelView<LB, REM> &ch, uint32_t b, uint32_t x0, uint32_t x1, bool in, uint32_t r) {
+        const uint32_t w0 = x0 & 0xffffu;
+        all.fetch(ch.arr + (in ? w0 : 0u), in ? (x1 & 0xffffu) - w0 : 0u, r, ch.fill);
+        if constexpr (REM) {
+            const uint32_t v0 = ch.rem_start()[b], v1 = ch.rem_start()[b + 1];
+            const uint32_t len = in ? v1 - v0 : 0u;
+            any_rem = __ballot(len != 0) != 0ull;
+            rem.fetch(ch.rem_arr + (len ? v0 : 0u), len, r, ch.fill);
+            rem.wait();
+        }
+        all.wait();
+    }
+    // N + D = twice the number of places at or below pl; A as in below_key.
+    __device__ __forceinline__ void sums(uint32_t pl, int &A, int &D, int &N) const {
+        uint32_t a, b, n;
+        all.sums(pl, a, b, n);
+        A = (int)a, D = (int)(b - a), N = (int)n;
+        if constexpr (REM) {
+            if (any_rem) {
+                rem.sums(pl, a, b, n);
+                A -= (int)a, D -= (int)(b - a), N -= (int)n;
+            }
+        }
+        if constexpr (R > 1) {
+            A = (int)row_group_sum<R>((uint32_t)A);
+            D = (int)row_group_sum<R>((uint32_t)D);
+        }
+    }
+};
+
+// How many of a channel's weights have a key up to tk, and their exact sum of x * 2^24 (nothing to look up
+// and both 0 where `inside` is false).  Called by all lanes.
+//
+// The part of a bucket at or below place pl comes from two sums of absolute differences over the
+// stretch's bytes x (v_sad_u8, four bytes an instruction): with A = sum |x - pl| and B = sum |x - pl - 1|
+// over N bytes, B - A = #(x <= pl) - #(x > pl), and A gives the sum of the places at or below pl once the
+// sum of all bytes is known - which the records tell, filler included.  (Places and pl are at most 127, the
+// filler is 128.)  Every term is linear in the bytes, so what the removed entries add is taken off term by
+// term.
+template <int R, int LB, int AHEAD, bool REM>
+__device__ __forceinline__ void below_key(const ChannelView<LB, REM> &ch, uint32_t tk, bool inside, uint32_t r,
+                                          uint32_t &n_below, long long &s_below) {
+    constexpr uint32_t kPerRun = 1u << (10 - LB);  // buckets that share sign and exponent
+    // a boundary key is that of a finite value: its bucket is not the last one, nor is its run of buckets
+    const uint32_t b = inside ? tk >> LB : ch.kFirst, run = b / kPerRun;
+    const uint2 r0 = ch.rec()[b - ch.kFirst], r1 = ch.rec()[b - ch.kFirst + 1];
+    const long long base0 = ch.base()[run], base1 = ch.base()[run + 1];
+    BucketPlaces<R, LB, AHEAD, REM> places;
+    places.fetch(ch, b - ch.kFirst, r0.x, r1.x, inside, r);
+    const int pl = (int)(tk & ((1u << LB) - 1));
+    int A, D, N;
+    places.sums((uint32_t)pl, A, D, N);
+    const int n_b = (int)((r1.x >> 16) - (r0.x >> 16));  // places in the bucket
+    const int n = (N + D) >> 1;                          // those at or below pl
+    int mant;
+    uint32_t sh;
+    bucket_scale<LB>(b, mant, sh);
+    const int u0 = (int)r0.y;
+    const int u1 = (b & (kPerRun - 1)) == kPerRun - 1 ? (int)((base1 - base0) >> sh) : (int)r1.y;
+    const int bytes = u1 - u0 - __mul24(mant, n_b) + 128 * (N - n_b);  // sum of all bytes
+    const int l = (bytes + __mul24(pl, 2 * n - N) - A) >> 1;
+    n_below = inside ? (r0.x >> 16) + (uint32_t)n : 0u;
+    s_below = inside ? base0 + (long long)((unsigned long long)(long long)(u0 + __mul24(mant, n) + l) << sh) : 0ll;
+}
+
+// Start-up: level j = order statistic floor((2j+1)M/(2K)) of the kept weights.  The bucket by bisection on
+// the counts below, then the place by bisection with counting scans of that bucket.
+template <int R, int LB, int AHEAD, bool REM>
+__device__ __forceinline__ float quantile_start(const ChannelView<LB, REM> &ch, int K, uint32_t M, uint32_t r) {
+    using View = ChannelView<LB, REM>;
+    const int p = threadIdx.x & 15;
+    const bool mine = p < K && M > 0;
+    const uint32_t rank = mine ? (uint32_t)(2 * p + 1) * M >> __ffs(K) : 0u;  // K is a power of two
+    uint32_t b = 0;  // largest bucket with at most `rank` weights below it
+#pragma unroll 1
+    for (uint32_t s = View::kBuckets / 2; s > 0; s >>= 1)
+        if ((ch.rec()[min(max(b + s, View::kFirst), View::kLast) - View::kFirst].x >> 16) <= rank) b += s;
+    b = mine ? min(max(b, View::kFirst), View::kLast - 1u) : View::kFirst;
+    const uint32_t x0 = ch.rec()[b - View::kFirst].x, x1 = ch.rec()[b - View::kFirst + 1].x, in = rank - (x0 >> 16);
+    BucketPlaces<R, LB, AHEAD, REM> places;
+    places.fetch(ch, b - View::kFirst, x0, x1, mine, r);
+    uint32_t pl = 0;  // smallest place with more than `in` weights at or below it
+#pragma unroll 1
+    for (uint32_t s = (1u << LB) / 2; s > 0; s >>= 1) {
+        int A, D, N;
+        places.sums(pl + s - 1, A, D, N);
+        if ((uint32_t)((N + D) >> 1) <= in) pl += s;
+    }
+    const float c = mine ? value_of_key((b << LB) | pl) : 0.0f;
+    return c == 0.0f ? 0.0f : c;  // a level never starts as -0
+}
+
+// (s * 2^-24) / n in fp64, rounded once more to fp32.  The quotient is IEEE's: the reciprocal refined twice, one
+// correction of the quotient by its exact remainder - the steps of the compiler's own division without its
+// rescaling, which no |s| < 2^56 and 1 <= n <= 32768 asks for (with n = 0 the value is not used).  The reciprocal
+// is ready before the sum is.
+__device__ __forceinline__ float mean_of_cell(long long s, uint32_t n) {
+    const double d = ldexp((double)n, 24);
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    const double x = (double)s, q = x * r;
+    return (float)fma(fma(-d, q, x), r, q);
+}
+
+// Start-up and rounds of 4 / R channels on one wavefront.  A channel has R rows of 16 lanes; lane p of a
+// row carries the level at sorted position p and the boundary above it.  All rows of a channel hold the same
+// state; they share out the words of a boundary's bucket.  Sharing a wavefront is what makes a round
+// cheap: its ~200 dependent instructions per boundary key and level cost the same for one channel and for four.
+// REM: `removed` holds the tables of the entries that do not take part.
+// Bound by that chain: about 1400 cycles of instructions and a trip to memory for the words of a bucket (800
+// cycles; the records come from LDS, 150).
+template <int R, int LB, int AHEAD, bool REM>
+__global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int64_t i0, int64_t n_chan,
+                                                                 const unsigned char *tables, int64_t stride,
+                                                                 const unsigned char *removed, ChannelFinal *fin) {
+    const int lane = threadIdx.x, p = lane & 15;
+    const uint32_t r = (uint32_t)((lane >> 4) & (R - 1));
+    const int64_t at = (int64_t)blockIdx.x * (4 / R) + (lane >> 4) / R;
+    const bool exists = at < n_chan;
+    const int64_t j = exists ? at : n_chan - 1, i = i0 + j;
+    const int b = exists ? a.bits[i] : 0;
+    const bool coded = b >= 1 && b <= 4;
+    float *crow = a.centroids + i * CMPQ_KMAX;
+    const TableHead *head = reinterpret_cast<const TableHead *>(tables + j * stride);
+    const TableHead *rem = reinterpret_cast<const TableHead *>(REM ? removed + j * stride : nullptr);
+    // ---- sums per run and records into LDS, what the removed entries add taken off.  All loads go out before
+    //      the first is looked at: each trip to another kernel's output costs about 2000 cycles.
+    extern __shared__ __align__(16) unsigned char dyn[];
+    using View = ChannelView<LB, REM>;
+    constexpr int kLanes = 16 * R, kPairs = (int)View::kRecs / 2, kHeld = (kPairs + kLanes - 1) / kLanes;
+    constexpr int kRuns = (65 + kLanes - 1) / kLanes;
+    const int at0 = lane & (kLanes - 1);
+    View ch;
+    ch.at = dyn + (lane >> 4) / R * View::kBytes;
+    const uint2 *src = reinterpret_cast<const uint2 *>(head + 1), *src_rem = reinterpret_cast<const uint2 *>(rem + 1);
+    ch.arr = reinterpret_cast<const uint32_t *>(src + View::kBuckets);
+    ch.rem_arr = REM ? reinterpret_cast<const uint32_t *>(src_rem + View::kBuckets) : nullptr;
+    ch.fill = head->fill;
+    uint4 two[kHeld], two_rem[REM ? kHeld : 1];
+    long long run[kRuns], run_rem[REM ? kRuns : 1];
+    const uint32_t magic = head->magic, len = head->d_out, kept_all = head->kept, n_rem = REM ? rem->kept : 0u;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const int s = min(at0 + u * kLanes, kPairs - 1);
+        __builtin_memcpy(&two[u], src + View::kFirst + 2 * s, 16);
+        if constexpr (REM) __builtin_memcpy(&two_rem[u], src_rem + View::kFirst + 2 * s, 16);
+    }
+#pragma unroll
+    for (int u = 0; u < kRuns; ++u) {
+        const int s = min(at0 + u * kLanes, 64);
+        run[u] = head->base[s];
+        if constexpr (REM) run_rem[u] = rem->base[s];
+    }
+    const bool has_rem = n_rem > 0;  // without, the removed entries' records were not written
+    if (!has_rem) ch.rem_arr = ch.arr;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const int s = at0 + u * kLanes;
+        uint4 v = two[u];
+        loaded(v);
+        if constexpr (REM) {
+            uint4 w = two_rem[u];
+            loaded(w);
+            if (!has_rem) w = make_uint4(0, 0, 0, 0);
+            v.x -= w.x & 0xffff0000u, v.z -= w.z & 0xffff0000u;
+            v.y -= w.y, v.w -= w.w;
+            if (s < kPairs) ch.rem_start()[2 * s] = (uint16_t)w.x, ch.rem_start()[2 * s + 1] = (uint16_t)w.z;
+        }
+        if (s < kPairs) ch.rec()[2 * s] = make_uint2(v.x, v.y), ch.rec()[2 * s + 1] = make_uint2(v.z, v.w);
+    }
+#pragma unroll
+    for (int u = 0; u < kRuns; ++u) {
+        const int s = at0 + u * kLanes;
+        if (s < 65) ch.base()[s] = REM && has_rem ? run[u] - run_rem[u] : run[u];
+    }
+    int K = coded ? 1 << b : 0;
+    // a non-finite weight or starting level, or no usable tables: the caller's status word says so; the
+    // channel gets defined outputs (all levels 0, all codes 0) instead of a clustering of NaNs
+    uint32_t why = 0;
+    if (coded && (magic != kTableMagic + 1u || len != (uint32_t)a.d_out))
+        why = magic == kTableMagic + 2u ? CMPQ_STATUS_NONFINITE : CMPQ_STATUS_ARRANGEMENT;
+    float c0 = INFINITY;
+    if (a.start_given) {  // the caller's levels, in level order; -0 is taken as +0
+        if (p < K) c0 = crow[p];
+        const uint64_t odd = __ballot(p < K && !isfinite(c0));
+        if (((odd >> (lane & 48)) & 0xffffu) && !why) why = CMPQ_STATUS_NONFINITE;
+        c0 = c0 == 0.0f ? 0.0f : c0;
+    }
+    const int K_out = K;
+    if (why) K = 0;
+    const uint32_t M = K ? kept_all - n_rem : 0u;
+    __syncthreads();
+    const long long s_all = K ? ch.base()[64] : 0ll;
+    if (!a.start_given) {
+        const float start = quantile_start<R, LB, AHEAD, REM>(ch, K, M, r);
+        c0 = p < K ? start : INFINITY;
+    }
+
+    // lane p of a row: the level at sorted position p, which level that is, the next distinct level above it
+    // (there is none for have_hi = false) and whether a weight half way belongs to the upper one
+    float c_sorted, hi;
+    int own;
+    bool have_hi, tie_up;
+    auto rank = [&](float c_level) {
+        int owner_lo, owner_hi;
+        rank_levels_in_rows(c_level, K, c_sorted, own, hi, owner_lo, owner_hi, have_hi);
+        tie_up = owner_hi < owner_lo;
+    };
+    {
+        // starting levels that ascend strictly (the usual outcome of the quantile start) are
+        // in sorted order already: each level's upper neighbour sits one lane up
+        const float c0_up = __uint_as_float(row_from_above(__float_as_uint(c0)));
+        if (__ballot(p < K - 1 && !(c0 < c0_up)) == 0ull) {
+            c_sorted = c0;
+            own = p;
+            hi = c0_up;
+            have_hi = p < K - 1;
+            tie_up = false;
+        } else {
+            rank(c0);
+        }
+    }
+    uint32_t tk = 0xffffffffu;
+#pragma unroll 1
+    for (int round = 0;; ++round) {
+        const uint32_t tk_prev = tk;
+        tk = boundary_key(c_sorted, hi, __ballot(have_hi && tie_up) != 0ull && tie_up);
+        if (!have_hi) tk = kKeyInf;
+        // no boundary moved: the iteration sits on its fixed point
+        if (round == a.iters || __ballot(p < K - 1 && tk != tk_prev) == 0ull) break;
+        // cumulative count and sum at each boundary; the last position takes everything
+        uint32_t n_below;
+        long long s_below;
+        below_key<R, LB, AHEAD, REM>(ch, tk, have_hi, r, n_below, s_below);
+        if (!have_hi) {
+            n_below = M;
+            s_below = s_all;
+        }
+        // sorted positions live in one DPP row: neighbours come by row shifts
+        const uint32_t n_cell = n_below - row_from_below(n_below);
+        const long long s_cell = s_below - (long long)(((unsigned long long)row_from_below((uint32_t)((unsigned long long)s_below >> 32)) << 32) |
+                                                       row_from_below((uint32_t)s_below));
+        const float mean = mean_of_cell(s_cell, n_cell);
+        const float c = p < K && n_cell > 0 ? mean : c_sorted;
+        // usual case: the levels are still strictly ascending in the old order
+        const float c_up = __uint_as_float(row_from_above(__float_as_uint(c)));
+        const int own_up = (int)row_from_above((uint32_t)own);
+        if (__ballot(p < K - 1 && !(c < c_up)) == 0ull) {
+            c_sorted = c;
+            hi = c_up;
+            have_hi = p < K - 1;
+            tie_up = own_up < own;
+        } else {
+            // bring the values back to level order and rank them again
+            float c_level = INFINITY;
+#pragma unroll 1
+            for (int l = 0; l < CMPQ_KMAX; ++l) {
+                const int ol = from_row_lane(own, l);
+                const float cl = from_row_lane(c, l);
+                if (ol == p) c_level = cl;
+            }
+            rank(c_level);
+        }
+    }
+    if (!exists || r != 0) return;
+    if (why && p == 0 && a.status) atomicOr(a.status, (int)why);
+    if (p >= K_out) crow[p] = INFINITY;
+    else if (why) crow[p] = 0.0f;
+    else crow[own] = c_sorted;
+    if (fin && coded) {
+        fin[j].tk[p] = (uint16_t)tk;
+        fin[j].code_of[p] = (uint8_t)own;
+        if (p == 0) fin[j].ok = why == 0;
     }
 }
 
@@ -210,10 +871,10 @@ constexpr uint32_t kTblMulti = 0x1000000u;
 
 template <int K, int T, int LB>
 __device__ __forceinline__ int build_code_table(const uint32_t (&thr)[CMPQ_KMAX], const uint32_t *code_of,
-                                                const uint32_t *tk, uint32_t *tbl) {
+                                                const uint32_t *tk, uint32_t *tbl, int tid) {
     constexpr int kLows = 1 << LB, kBuckets = 1 << (16 - LB);
     int multi = 0;
-    for (int bk = threadIdx.x; bk < kBuckets; bk += T) {
+    for (int bk = tid; bk < kBuckets; bk += T) {
         const uint32_t first = (uint32_t)bk << LB;
         const uint32_t p0 = cell_of<K>(first, thr), p1 = cell_of<K>(first + kLows - 1, thr);
         uint32_t ent = code_of[p0] | (code_of[p1] << 16);
@@ -259,34 +920,75 @@ __device__ __forceinline__ uint32_t code_from_entry(uint32_t ent, uint32_t kk, i
     return low > ((ent >> 8) & 0xffu) ? (ent >> 16) & 0xffu : ent & 0xffu;
 }
 
+// Words of the coding table (0: no number of levels uses one).
+constexpr int code_table_words(int T, int G, int LB) { return G * T >= 2 * (1 << (16 - LB)) ? 1 << (16 - LB) : 0; }
+
+struct CodeShared {
+    float cent[CMPQ_KMAX];        // levels by level index
+    uint32_t tk[CMPQ_KMAX];       // final boundary keys by sorted position
+    uint32_t code_of[CMPQ_KMAX];  // level index that each sorted position stands for
+    uint32_t flag[8];             // per wavefront
+    double cent64[CMPQ_KMAX];     // levels by level index, as the error sum reads them
+    double red[8];
+};
+
+// A table over the buckets replaces the search in the coding pass where there are many levels; worth it
+// for long channels only.
+template <int G, int K, int T, int LB>
+constexpr bool kCodeTable = K >= 8 && G * T >= 2 * (1 << (16 - LB));
+
+// The final boundaries as wave-uniform values.
+template <int K>
+__device__ __forceinline__ void final_boundaries(const CodeShared &sm, uint32_t (&thr)[CMPQ_KMAX]) {
+    const uint32_t tk_fin = sm.tk[threadIdx.x & (CMPQ_KMAX - 1)];
+#pragma unroll
+    for (int p = 0; p < K - 1; ++p) thr[p] = (uint32_t)__builtin_amdgcn_readlane((int)tk_fin, p);
+}
+
+// What the coding pass needs before the channel's lanes may start on their groups: the coding table, the
+// levels in fp64, zeros in the bytes of the row of the bit stream that no group writes.
+template <int G, int K, int T, int LB, bool FUSED>
+__device__ __forceinline__ void coding_prepare(const KmArgs &a, CodeShared &sm, unsigned char *arr, uint32_t *tbl,
+                                               int tid, int n_groups) {
+    if constexpr (FUSED) {
+        constexpr int B = K == 2 ? 1 : (K == 4 ? 2 : (K == 8 ? 3 : 4));
+        if (tid < CMPQ_KMAX) sm.cent64[tid] = (double)sm.cent[tid];
+        const int row_bytes = (int)(((int64_t)a.d_out * B + 31) / 32) * 4;
+        const int coded = B == 4 ? 2 * n_groups : (B == 2 ? n_groups : (B == 3 ? 3 * ((n_groups + 1) >> 1) : (n_groups + 1) >> 1));
+        for (int x = coded + tid; x < row_bytes; x += T) arr[x] = 0;
+    }
+    if constexpr (kCodeTable<G, K, T, LB>) {
+        uint32_t thr[CMPQ_KMAX];
+        final_boundaries<K>(sm, thr);
+        const int multi = build_code_table<K, T, LB>(thr, sm.code_of, sm.tk, tbl, tid);
+        const bool any = __ballot(multi) != 0ull;
+        if ((tid & 63) == 0) sm.flag[tid >> 6] = any;
+    }
+}
+template <int T>
+__device__ __forceinline__ bool any_flag(const CodeShared &sm) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int w = 0; w < T / CMPQ_WAVE; ++w) any |= sm.flag[w];
+    return __builtin_amdgcn_readfirstlane((int)any) != 0;
+}
+
 // The coding pass with the stored format and the error folded in (Sec. 5.1; App. B.3): every
 // lane takes groups g = tid, tid + T, ... of 4 weights (fetched again: the place array cannot
 // give a weight's position back), finds their codes, adds (w - level)^2 in fp64 - nothing for an
 // entry of O_q, whose FP16 weight is restored - and puts the group's 4 * B code bits into the
 // channel's row of the bit stream, which is built in the place array the rounds no longer need.
 // A rolled loop: its fp64 temporaries would not fit the register budget of the unrolled one.
-// Returns the lane's share of the error.  Contains a barrier: called by all threads.
+// Returns the lane's share of the error.
 template <int G, int K, int T, int LB, bool RAGGED>
-__device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, BucketShared<LB> &sm,
+__device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, CodeShared &sm,
                                                     unsigned char *arr, uint32_t *tbl, const uint32_t *removed,
-                                                    int n_ex, int n_groups, int par) {
-    constexpr int kLowBits = LB, kLows = 1 << LB, kBuckets = 1 << (16 - LB);
+                                                    int n_ex, int tid, int n_groups) {
     constexpr int B = K == 2 ? 1 : (K == 4 ? 2 : (K == 8 ? 3 : 4));
-    const int tid = threadIdx.x, lane = tid & 63;
-    const uint32_t tk_fin = sm.tk[par][lane & (CMPQ_KMAX - 1)];
+    constexpr bool kTable = kCodeTable<G, K, T, LB>;
     uint32_t thr[CMPQ_KMAX];
-#pragma unroll
-    for (int p = 0; p < K - 1; ++p) thr[p] = (uint32_t)__builtin_amdgcn_readlane((int)tk_fin, p);
-    if (tid < CMPQ_KMAX) sm.cent64[tid] = (double)sm.cent[tid];
-    // bytes of the row that the groups below do not write: zero, up to whole words
-    const int row_bytes = (int)(((int64_t)a.d_out * B + 31) / 32) * 4;
-    const int coded = B == 4 ? 2 * n_groups : (B == 2 ? n_groups : (B == 3 ? 3 * ((n_groups + 1) >> 1) : (n_groups + 1) >> 1));
-    for (int x = coded + tid; x < row_bytes; x += T) arr[x] = 0;
-    // a table over the buckets replaces the search where there are many levels
-    constexpr bool kTable = K >= 8 && G * T >= 2 * kBuckets;  // worth it for long channels only
-    int multi = 0;
-    if constexpr (kTable) multi = build_code_table<K, T, LB>(thr, sm.code_of, sm.tk[par], tbl);
-    const bool any_multi = __syncthreads_or(multi) != 0;  // also the barrier before the groups below
+    final_boundaries<K>(sm, thr);
+    const bool any_multi = kTable && any_flag<T>(sm);
     const uint32_t tbl_at = lds_address(tbl);
     const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
     const int d_out = (int)a.d_out;
@@ -375,375 +1077,74 @@ __device__ __forceinline__ double coding_pass_fused(const KmArgs &a, int64_t i, 
     };
     if (any_multi) all_groups(std::true_type{});
     else all_groups(std::false_type{});
-    __syncthreads();
     return err;
 }
 
-template <int G, int K, int T, int LB, bool FUSED, bool RAGGED>
-__device__ __forceinline__ void lloyd_bucket(const KmArgs &a, int64_t i, BucketShared<LB> &sm,
-                                             unsigned char *arr, uint32_t *tbl, const uint32_t *removed, int n_ex,
-                                             const uint32_t (&keys)[2 * G], int n_groups, uint32_t M,
-                                             double &err_out) {
-    constexpr int L = T / 16;  // lanes that share one boundary in a round
-    constexpr int kLowBits = LB, kLows = 1 << LB, kBuckets = 1 << (16 - LB);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    // Start-up and rounds are a chain of short dependent steps (half the lifetime of a
-    // workgroup): they go first at instruction issue, ahead of the wide, latency-tolerant
-    // passes of the other workgroups on the compute unit.
-    __builtin_amdgcn_s_setprio(3);
-    // ---- start-up: level j = order statistic floor((2j+1)M/(2K)) of the kept weights.
-    //      L lanes per rank: locate the bucket by its prefix, then bisect on the place
-    //      with counting scans of that bucket.  Not when the caller gave the levels: they
-    //      are in place already.
-    if (!a.start_given) {
-        const int j = tid / L, sub = tid & (L - 1);
-        if (j < K) {
-            float c = 0.0f;
-            if (M > 0) {
-                const uint32_t r = (uint32_t)(((uint64_t)(2 * j + 1) * M) / (uint64_t)(2 * K));
-                const int g0 = lane & ~(L - 1);  // first lane of this group inside its wavefront
-                // largest b with at most r weights below it: the L lanes probe L evenly spaced buckets
-                // at a time (the counts below do not decrease, so the probes that pass come first)
-                int lo = 0, hi_b = kBuckets - 1;
-                while (lo < hi_b) {
-                    const int step = (hi_b - lo + L - 1) / L;
-                    const int probe = min(lo + (sub + 1) * step, hi_b);
-                    const unsigned long long pass = __ballot(before_of(tbl[probe]) <= r) >> g0;
-                    const int c_pass = __popcll(L < 64 ? pass & ((1ull << L) - 1) : pass);
-                    const int nlo = c_pass > 0 ? min(lo + c_pass * step, hi_b) : lo;
-                    if (c_pass < L) hi_b = min(lo + (c_pass + 1) * step, hi_b) - 1;
-                    lo = nlo;
-                }
-                const uint32_t b = (uint32_t)lo, word = tbl[b], r_in = r - before_of(word);
-                const uint32_t begin = stretch_of(word), end = stretch_end<LB>(tbl, b);
-                // smallest place with more than r_in weights at or below it: bisection on the place.
-                // The bucket's words are fetched once (4 per lane) when they fit; the counting
-                // scans of the bisection then run on registers.
-                const uint32_t w_begin = begin >> 2, w_end = end >> 2;
-                const bool fits = w_end - w_begin <= 4u * L;
-                const uint32_t *words = reinterpret_cast<const uint32_t *>(arr);
-                uint32_t x[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t at = w_begin + sub + u * L;
-                    x[u] = at < w_end ? words[at] : kFill4;
-                }
-                int pl = 0, ph = kLows - 1;
-                while (pl < ph) {
-                    const int mid = (pl + ph) >> 1;
-                    uint32_t n, l;
-                    if (fits) {
-                        const uint32_t bias = 0x7f7f7f7fu - (uint32_t)mid * 0x01010101u;
-                        uint32_t cn = 0;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) cn += (uint32_t)__builtin_popcount(~(x[u] + bias) & 0x80808080u);
-                        n = group_sum<L>(cn);
-                    } else {
-                        scan_bucket<L>(arr, begin, end, (uint32_t)mid, n, l);
-                    }
-                    if (n > r_in) ph = mid; else pl = mid + 1;
-                }
-                c = value_of_key((b << kLowBits) | (uint32_t)pl);
-                if (c == 0.0f) c = 0.0f;  // a level never starts as -0
-            }
-            if (sub == 0) sm.cent[j] = c;
-        }
-    }
-    __syncthreads();
-
-    // ---- rounds.  Wavefront 0 alone carries the levels (lane p = sorted position p) and
-    //      does the serial part of a round; the others only join in the per-boundary bucket
-    //      scans and otherwise sleep at the two barriers, leaving the issue slots to the
-    //      other workgroups of the compute unit.
-    float c_sorted = 0.0f, hi = 0.0f;
-    int own = lane, owner_lo = 0, owner_hi = 0;
-    bool have_hi = false;
-    if (wave == 0) {
-        // starting levels that ascend strictly (the usual outcome of the quantile start) are
-        // in sorted order already: each level's upper neighbour sits one lane up
-        const float c0 = lane < K ? sm.cent[lane] : INFINITY;
-        const float c0_up = __uint_as_float(row_from_above(__float_as_uint(c0)));
-        if (__ballot(lane < K - 1 && !(c0 < c0_up)) == 0ull) {
-            c_sorted = c0;
-            hi = c0_up;
-            owner_lo = lane;
-            owner_hi = lane + 1;
-            have_hi = lane < K - 1;
-        } else {
-            rank_levels<K>(c0, c_sorted, own, hi, owner_lo, owner_hi, have_hi);
-        }
-    }
-    uint32_t tk_prev = 0xffffffffu;
-    // lanes per boundary in the rounds, and words each of them has in flight: the 512-lane
-    // workgroups give a boundary 16 lanes with 8 words (fewer wavefronts then execute the scan;
-    // measured 2 % faster there, 3 % slower for 256 lanes)
-    constexpr int LR = T >= 512 ? T / 32 : L;
-    constexpr int UR = 4 * (L / LR);
-    const int p_mine = tid / LR;  // the boundary this lane helps with
-    int par = 0;
-
-    for (int round = 0;; ++round) {
-        par = round & 1;
-        if (wave == 0) {
-            uint32_t tk = kKeyInf;
-            if (have_hi) tk = boundary_key(c_sorted, hi, owner_lo, owner_hi);
-            // no boundary moved: the iteration sits on its fixed point
-            const bool moved = __ballot(lane < K - 1 && tk != tk_prev) != 0ull;
-            tk_prev = tk;
-            const bool go = round != a.iters && moved;
-            if (lane < CMPQ_KMAX) sm.tk[par][lane] = tk;
-            if (lane == 0) sm.go[par] = go;
-            if (!go) {  // results: the position -> level map and the levels by level index
-                if (lane < CMPQ_KMAX) sm.code_of[lane] = (uint32_t)own;
-                if (lane < K) sm.cent[own] = c_sorted;
-            }
-        }
-        __syncthreads();
-        if (!sm.go[par]) break;
-        // L lanes per boundary: the part of its bucket that lies below it
-        if (p_mine < K - 1) {
-            const uint32_t t = sm.tk[par][p_mine];
-            uint32_t n = 0, l = 0;
-            if (t != kKeyInf) {
-                const uint32_t b = t >> kLowBits;
-                scan_bucket<LR, UR>(arr, stretch_of(tbl[b]), stretch_end<LB>(tbl, b), t & (kLows - 1), n, l);
-            }
-            if ((tid & (LR - 1)) == 0) {
-                sm.part_n[par][p_mine] = n;
-                sm.part_l[par][p_mine] = l;
-            }
-        }
-        __syncthreads();
-        if (wave != 0) continue;
-        // cumulative count and sum at each boundary; the last position takes everything
-        const uint32_t tk = tk_prev;
-        uint32_t n_below = M;
-        long long s_below = sm.scum[kBuckets];
-        if (lane < K - 1 && tk != kKeyInf) {
-            const uint32_t b = tk >> kLowBits;
-            const uint32_t cnt = sm.part_n[par][lane];
-            n_below = before_of(tbl[b]) + cnt;
-            s_below = sm.scum[b] + bucket_sum<LB>(b, cnt, sm.part_l[par][lane]);
-        }
-        // sorted positions live in lanes 0..15, one DPP row: neighbours come by row shifts
-        const uint32_t n_prev = row_from_below(n_below);
-        const long long s_prev = (long long)(((unsigned long long)row_from_below((uint32_t)((unsigned long long)s_below >> 32)) << 32) |
-                                             row_from_below((uint32_t)s_below));
-        const uint32_t n_cell = n_below - n_prev;
-        const long long s_cell = s_below - s_prev;
-        float c = c_sorted;
-        if (lane < K && n_cell > 0)
-            c = (float)(((double)s_cell * 5.9604644775390625e-08) / (double)n_cell);
-        // usual case: the levels are still strictly ascending in the old order
-        const float c_up = __uint_as_float(row_from_above(__float_as_uint(c)));
-        const int own_up = (int)row_from_above((uint32_t)own);
-        const unsigned long long bad = __ballot(lane < K - 1 && !(c < c_up));
-        if (bad == 0ull) {
-            c_sorted = c;
-            hi = c_up;
-            owner_lo = own;
-            owner_hi = own_up;
-            have_hi = lane < K - 1;
-        } else {
-            // bring the values back to level order and rank them again
-            float c_level = INFINITY;
-#pragma unroll
-            for (int l = 0; l < K; ++l) {
-                const int ol = __shfl(own, l, CMPQ_WAVE);
-                const float cl = __shfl(c, l, CMPQ_WAVE);
-                if (ol == lane) c_level = cl;
-            }
-            rank_levels<K>(c_level, c_sorted, own, hi, owner_lo, owner_hi, have_hi);
-        }
-    }
-
-    __builtin_amdgcn_s_setprio(0);
-    if constexpr (FUSED) {
-        err_out = coding_pass_fused<G, K, T, LB, RAGGED>(a, i, sm, arr, tbl, removed, n_ex, n_groups, par);
-        return;
-    }
-    if (!a.codes) {  // the caller wants the levels alone
-        __syncthreads();
-        return;
-    }
-    // ---- final coding: 4 codes per lane and store.  Every wavefront fetches the final
-    //      boundaries and the position -> level map left by wavefront 0.
-    const uint32_t tk_fin = sm.tk[par][lane & (CMPQ_KMAX - 1)];
-    const int own_fin = (int)sm.code_of[lane & (CMPQ_KMAX - 1)];
+// Codes alone: 4 per lane and store.  The weights are fetched again (from cache) instead of being held in
+// registers through the rounds.
+template <int G, int K, int T, int LB, bool RAGGED>
+__device__ __forceinline__ void coding_pass_plain(const KmArgs &a, int64_t i, CodeShared &sm, uint32_t *tbl,
+                                                  int tid, int n_groups) {
+    constexpr bool kTable = kCodeTable<G, K, T, LB>;
     uint32_t thr[CMPQ_KMAX];
-#pragma unroll
-    for (int p = 0; p < K - 1; ++p) thr[p] = (uint32_t)__builtin_amdgcn_readlane((int)tk_fin, p);
+    final_boundaries<K>(sm, thr);
+    const bool any_multi = kTable && any_flag<T>(sm);
+    const uint32_t tbl_at = lds_address(tbl);
+    const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
     uint8_t *crow = a.codes + i * a.d_out;
     const int d_out = (int)a.d_out;
-    // Workgroups of 512 lanes fetch their weights again here (from cache) instead of holding
-    // them in registers through the rounds: a third workgroup then fits a compute unit.
-    constexpr bool kReload = T >= 512;
-    uint32_t again[2 * G];
-    if constexpr (kReload) {
-        const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            const uint2 raw = load_group<RAGGED>(wrow, k * T + tid, n_groups, d_out);
-            again[2 * k] = keys_of_half2(raw.x);
-            again[2 * k + 1] = keys_of_half2(raw.y);
-        }
-    }
-    auto key_at = [&](int k, int e) -> uint32_t {
-        if constexpr (kReload) return elem_key<G>(again, k, e);
-        else return elem_key<G>(keys, k, e);
-    };
-    // Many weights per lane and many levels: a table over the buckets replaces the search.
-    constexpr bool kTable = K >= 8 && G * T >= 2 * kBuckets;
-    if constexpr (kTable) {
-        const int multi = build_code_table<K, T, LB>(thr, sm.code_of, sm.tk[par], tbl);
-        const uint32_t tbl_at = lds_address(tbl);
-        auto pair_at = [&](int k, int e) -> uint32_t {
-            if constexpr (kReload) return again[2 * k + (e >> 1)];
-            else return keys[2 * k + (e >> 1)];
-        };
-        if (!__syncthreads_or(multi)) {
-#pragma unroll
-            for (int k = 0; k < G; ++k) {
-                const int g = k * T + tid;
-                uint32_t word = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t kk = pair_at(k, e);
-                    word |= code_from_entry(table_entry<LB>(tbl_at, kk, e & 1), kk, e & 1) << (8 * e);
-                }
-                if (g < n_groups) store_codes<RAGGED>(crow, g, d_out, word);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < G; ++k) {
-                const int g = k * T + tid;
-                uint32_t word = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t kk = pair_at(k, e);
-                    const uint32_t ent = table_entry<LB>(tbl_at, kk, e & 1);
-                    uint32_t code = code_from_entry(ent, kk, e & 1);
-                    if (ent & kTblMulti) code = sm.code_of[cell_of<K>(key_at(k, e), thr)];
-                    word |= code << (8 * e);
-                }
-                if (g < n_groups) store_codes<RAGGED>(crow, g, d_out, word);
-            }
-        }
-    } else {
-        const bool ident = __ballot(lane < K && own_fin != lane) == 0ull;
-#pragma unroll
+    auto all_groups = [&](auto with_search) {
+        constexpr bool kSearch = decltype(with_search)::value;
+#pragma unroll 4
         for (int k = 0; k < G; ++k) {
             const int g = k * T + tid;
+            if (g >= n_groups) break;
+            const uint2 raw = load_group<RAGGED>(wrow, g, n_groups, d_out);
+            const uint32_t kk[2] = {keys_of_half2(raw.x), keys_of_half2(raw.y)};
             uint32_t word = 0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {  // all lanes take part: the level look-up crosses lanes
-                uint32_t pos = cell_of<K>(key_at(k, e), thr);
-                if (!ident) pos = (uint32_t)__shfl(own_fin, (int)pos, CMPQ_WAVE);
-                word |= pos << (8 * e);
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t key = (kk[e >> 1] >> (16 * (e & 1))) & 0xffffu;
+                uint32_t code;
+                if constexpr (kTable) {
+                    const uint32_t ent = table_entry<LB>(tbl_at, kk[e >> 1], e & 1);
+                    code = code_from_entry(ent, kk[e >> 1], e & 1);
+                    if (kSearch && (ent & kTblMulti)) code = sm.code_of[cell_of<K>(key, thr)];
+                } else {
+                    code = sm.code_of[cell_of<K>(key, thr)];
+                }
+                word |= code << (8 * e);
             }
-            if (g < n_groups) store_codes<RAGGED>(crow, g, d_out, word);
+            store_codes<RAGGED>(crow, g, d_out, word);
         }
-    }
-    __syncthreads();
+    };
+    if (any_multi) all_groups(std::true_type{});
+    else all_groups(std::false_type{});
 }
 
-// What a run may leave behind for a later run on the same channel (the final quantization of
-// Sec. 3.2.2 differs from the preliminary one by the few entries of O_q): per channel a header
-// word, the per-bucket (count << 32 | sum of places) table and the place array, as built from
-// ALL weights of the channel.  The later run loads them instead of fetching, keying, counting
-// and scattering the weights again, takes the entries of O_q out of the table and blanks one
-// byte of the place array per such entry.
-constexpr uint32_t kArrMagic = 0xC3A77A00u;  // + 1: an arrangement follows; + 2: the channel held a non-finite weight
-__host__ __device__ inline size_t arrangement_stride(int64_t d_out, int lb) {
-    return 16 + ((size_t)8 << (16 - lb)) + bucket_arr_bytes(d_out, lb);
-}
-
-constexpr int kModePlain = 0;  // codes only
-constexpr int kModeFused = 1;  // the coding pass also writes the row of the stored format and the error
-constexpr int kModeReuse = 2;  // starts from a kept arrangement; codes like kModeFused (outputs optional)
-
-// One of the place bytes of bucket stretch [w0, w1) (words) that equals `place` becomes a filler.
-// Lanes that remove equal values race for the bytes: compare-and-swap, try the next on a loss.
-__device__ __forceinline__ void blank_one_place(uint32_t *words, uint32_t w0, uint32_t w1, uint32_t place) {
-    const uint32_t pat = place * 0x01010101u;
-    uint32_t j = w0;
-    while (j < w1) {
-        // The search and the exchange are separate loops: lanes of a wavefront find their
-        // words after different numbers of steps, and an exchange inside the search would put
-        // its round trip into every step that any lane ends on.
-        uint32_t x = 0, zero = 0;
-        for (; j < w1; j += 4) {  // four words per step, the last one again past the end
-            uint32_t xs[4], zs[4];
-#pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) xs[u] = words[min(j + u, w1 - 1)];
-#pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) {
-                const uint32_t t = xs[u] ^ pat;
-                zs[u] = (t - 0x01010101u) & ~t & 0x80808080u;  // lowest flag marks a byte that matches
-            }
-            if (zs[0] | zs[1] | zs[2] | zs[3]) {
-                const uint32_t u = zs[0] ? 0u : (zs[1] ? 1u : (zs[2] ? 2u : 3u));
-                x = zs[0] ? xs[0] : (zs[1] ? xs[1] : (zs[2] ? xs[2] : xs[3]));
-                zero = zs[0] ? zs[0] : (zs[1] ? zs[1] : (zs[2] ? zs[2] : zs[3]));
-                j = min(j + u, w1 - 1);
-                break;
-            }
-        }
-        if (!zero) return;
-        for (;;) {
-            const uint32_t sh = (uint32_t)(__ffs(zero) - 8);  // bit offset of that byte
-            const uint32_t nw = (x & ~(0xffu << sh)) | (0x80u << sh);
-            const uint32_t old = atomicCAS(&words[j], x, nw);
-            if (old == x) return;
-            x = old;  // another lane changed the word: look at it again
-            const uint32_t t = x ^ pat;
-            zero = (t - 0x01010101u) & ~t & 0x80808080u;
-            if (!zero) break;
-        }
-        ++j;
-    }
-}
-
-// Registers and occupancy.  The longest channels (16 groups a lane, 512 lanes) are bound by LDS:
-// 3 workgroups = 6 wavefronts per SIMD at d_out = 28 672 whatever the registers; their budget is
-// 64 per lane (72 for the fused final pass, which would spill at 64), so that what they leave
-// free lets a wavefront of a memory-bound kernel on another stream in beside them.  Every other
-// variant keeps the occupancy it has always run at, 7 wavefronts per SIMD (72 registers; 7
-// workgroups of 256 lanes per compute unit).  Measured against budgets of 77 / 72 registers: the
-// kernel alone 3-4 % shorter, the whole step with three streams 5 %.
-// Rows of any length and alignment need a few registers more: 5 there for the longest channels, so
-// that nothing spills.
-constexpr int waves_per_simd(int G, int T, int MODE, bool RAGGED) {
-    return G == 16 && T == 512 ? (RAGGED ? 5 : (MODE != kModeFused ? 8 : 7)) : 7;
-}
-template <int G, int T, int LB, int MODE, bool RAGGED>
-__global__ __launch_bounds__(T)
-    __attribute__((amdgpu_waves_per_eu(waves_per_simd(G, T, MODE, RAGGED), waves_per_simd(G, T, MODE, RAGGED))))
-void kmeans_bucket_kernel(KmArgs a) {
-    constexpr int kBuckets = 1 << (16 - LB);
-    constexpr bool kCodesFused = MODE != kModePlain;
-    // dynamic LDS: places of the kept weights, ordered by bucket (a byte each; the bucket
-    // follows from the position) | removed-entry bitmap (one bit per weight) | the scatter
-    // words of the buckets, later the coding table
+// Codes of a channel's weights with its final boundaries, and, FUSED, the row of the stored format, the FP16
+// table and the channel's error.
+template <int G, int T, int LB, bool FUSED, bool RAGGED>
+__global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, const ChannelFinal *fin) {
+    // dynamic LDS: coding table | removed-entry bitmap | the row of the bit stream
     extern __shared__ __align__(16) unsigned char dyn[];
-    __shared__ BucketShared<LB> sm;
-    const int64_t i = blockIdx.x;
+    __shared__ CodeShared sm;
+    const int64_t i = i0 + blockIdx.x;
     const int tid = threadIdx.x;
     const int d_out = (int)a.d_out, n_groups = RAGGED ? (d_out + 3) >> 2 : d_out >> 2;
     const int b = a.bits[i];
-    float *crow = a.centroids + i * CMPQ_KMAX;
-    if (b < 1 || b > 4) {  // a channel of O_act: no levels, no codes, no row; kept whole in FP16: no error
-        if (tid < CMPQ_KMAX) crow[tid] = INFINITY;
-        zero_codes<RAGGED, T>(a.codes ? a.codes + i * a.d_out : nullptr, n_groups, d_out);
-        if (kCodesFused && a.err_ch && tid == 0) a.err_ch[i] = 0.0;
+    uint8_t *codes_row = a.codes ? a.codes + i * a.d_out : nullptr;
+    if (b < 1 || b > 4) {  // a channel of O_act: no codes, no row; kept whole in FP16: no error
+        zero_codes<RAGGED, T>(codes_row, tid, n_groups, d_out);
+        if (FUSED && a.err_ch && tid == 0) a.err_ch[i] = 0.0;
         return;
     }
+    const int K = 1 << b;
     // where the channel's row of the stored format goes
     uint32_t *row_dst = nullptr;
     uint16_t *lut_dst = nullptr;
     const int row_words = (int)(((int64_t)d_out * b + 31) / 32);
-    if (kCodesFused && a.fused) {
+    if (FUSED) {
         const int32_t row = a.row_of[i];
         int j = 0;
         while (j < a.pack.n_set && a.pack.width[j] != b) ++j;
@@ -752,223 +1153,79 @@ void kmeans_bucket_kernel(KmArgs a) {
             if (a.pack.lut[j]) lut_dst = a.pack.lut[j] + ((int64_t)row << b);
         }
     }
-    const int K = 1 << b;
-    unsigned char *arr = dyn;
-    const size_t arr_bytes = bucket_arr_bytes(d_out, LB);
-    uint32_t *removed = reinterpret_cast<uint32_t *>(dyn + arr_bytes);
-    const int n_words = (d_out + 31) >> 5;
-    uint32_t *cursor = removed + ((n_words + 3) & ~3);
-    const __half *wrow_h = static_cast<const __half *>(a.W) + i * a.ldw;
-    // the arrangement this run leaves (any mode but reuse) or starts from (reuse)
-    unsigned char *keep = nullptr;
-    if (MODE != kModeReuse && a.arr_keep) keep = static_cast<unsigned char *>(a.arr_keep) + i * a.arr_stride;
-    const int per = kBuckets / T > 0 ? kBuckets / T : 1;  // buckets a lane owns in the prefix pass (T is a power of two)
-    const int b0 = tid * per;
-
-    uint32_t keys[2 * G];
-    uint32_t n_orig[8];  // reuse: the kept arrangement's count of each bucket this lane owns (per <= 8)
-    bool input_ok = true;
-    uint32_t bad_status = CMPQ_STATUS_NONFINITE;
-    if (tid == 0) {  // the slice of out_idx inside this channel
-        sm.seg_lo = a.seg ? a.seg[i] : 0;
-        const int64_t lo = a.seg ? a.seg[i + 1] : 0;
-        sm.n_excl = (int)lo - sm.seg_lo;
-    }
-    for (int s = tid; s < n_words; s += T)  // what fills up the last group counts as removed
-        removed[s] = RAGGED && s == d_out >> 5 && (d_out & 3) ? ((1u << (4 - (d_out & 3))) - 1u) << (d_out & 31) : 0u;
-    if constexpr (MODE == kModeReuse) {
-        // ---- the kept arrangement: header, bucket table, place array
-        const unsigned char *src = static_cast<const unsigned char *>(a.arr_reuse) + i * a.arr_stride;
-        const uint32_t head = *reinterpret_cast<const uint32_t *>(src);
-        if (head != kArrMagic + 1u) {
-            input_ok = false;  // the earlier run flagged the channel, or this is no arrangement at all
-            if (head != kArrMagic + 2u) bad_status = CMPQ_STATUS_ARRANGEMENT;
-        } else {
-            const unsigned long long *tsrc = reinterpret_cast<const unsigned long long *>(src + 16);
-            if (b0 < kBuckets) {
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    if (r < per) {
-                        const unsigned long long packed = tsrc[b0 + r];
-                        n_orig[r] = (uint32_t)(packed >> 32);
-                        sm.scum[b0 + r] = (long long)packed;
-                    }
-                }
-            }
-            const uint4 *asrc = reinterpret_cast<const uint4 *>(src + 16 + (size_t)kBuckets * 8);
-            uint4 *a4 = reinterpret_cast<uint4 *>(arr);
-            for (int s = tid; s < (int)(arr_bytes >> 4); s += T) a4[s] = asrc[s];
-        }
-    } else {
-        // ---- load: lane owns groups g = k*T + tid of 4 weights, kept as packed 16-bit keys
-        uint32_t nonfinite = 0;
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            const uint2 raw = load_group<RAGGED>(wrow_h, k * T + tid, n_groups, d_out);
-            nonfinite |= nonfinite_of_half2(raw.x) | nonfinite_of_half2(raw.y);
-            keys[2 * k] = keys_of_half2(raw.x);
-            keys[2 * k + 1] = keys_of_half2(raw.y);
-        }
-        input_ok = (nonfinite & 0x80008000u) == 0u;
-        for (int s = tid; s < kBuckets; s += T) sm.scum[s] = 0;  // first: count << 32 | sum of places
-        uint4 *a4 = reinterpret_cast<uint4 *>(arr);
-        for (int s = tid; s < (int)(arr_bytes >> 4); s += T) a4[s] = make_uint4(kFill4, kFill4, kFill4, kFill4);
-    }
-    bool bad_start = false;
-    if (a.start_given && tid < K) {  // the caller's levels, in level order; -0 is taken as +0
-        const float given = crow[tid];
-        bad_start = !isfinite(given);
-        sm.cent[tid] = given == 0.0f ? 0.0f : given;
-    }
-    if (!__syncthreads_and(input_ok && !bad_start)) {
-        // a non-finite weight or starting level (or no usable arrangement): the caller's status
-        // word says so; the channel gets defined outputs (all levels 0, all codes 0) instead of
-        // a clustering of NaNs
-        if (tid == 0 && a.status) atomicOr(a.status, (int)(input_ok ? CMPQ_STATUS_NONFINITE : bad_status));
-        if (tid < CMPQ_KMAX) crow[tid] = tid < K ? 0.0f : INFINITY;
-        zero_codes<RAGGED, T>(a.codes ? a.codes + i * a.d_out : nullptr, n_groups, d_out);
-        if constexpr (kCodesFused) {  // the row of all-zero codes, the table of zero levels, no number for the error
+    const ChannelFinal &f = fin[blockIdx.x];
+    if (!f.ok) {
+        zero_codes<RAGGED, T>(codes_row, tid, n_groups, d_out);
+        if constexpr (FUSED) {  // the row of all-zero codes, the table of zero levels, no number for the error
             if (row_dst) for (int w = tid; w < row_words; w += T) row_dst[w] = 0;
             if (lut_dst && tid < K) lut_dst[tid] = 0;
             if (a.err_ch && tid == 0) a.err_ch[i] = __longlong_as_double(0x7ff8000000000000ll);
         }
-        if (keep && tid == 0) *reinterpret_cast<uint32_t *>(keep) = kArrMagic + 2u;
         return;
     }
-    const int n_ex = sm.n_excl;
-    uint32_t first_key = 0;  // reuse: the key of entry `tid` of O_q, for the second visit below
-    if (n_ex > 0) {  // entries of O_q do not take part in the clustering
-        const int32_t *ex_idx = a.out_idx + sm.seg_lo;
+    uint32_t *tbl = reinterpret_cast<uint32_t *>(dyn);
+    const int n_words = FUSED ? (d_out + 31) >> 5 : 0;
+    uint32_t *removed = tbl + code_table_words(T, G, LB);
+    unsigned char *arr = reinterpret_cast<unsigned char *>(removed + ((n_words + 3) & ~3));
+    if (tid < CMPQ_KMAX) {
+        const float c = a.centroids[i * CMPQ_KMAX + tid];
+        sm.tk[tid] = f.tk[tid];
+        sm.code_of[tid] = f.code_of[tid];
+        sm.cent[tid] = c;
+        sm.cent64[tid] = (double)c;
+    }
+    int n_ex = 0;
+    if constexpr (FUSED) {
+        const int lo = a.seg ? a.seg[i] : 0;
+        n_ex = a.seg ? a.seg[i + 1] - lo : 0;
+        if (RAGGED || n_ex > 0) {
+            for (int s = tid; s < n_words; s += T)  // what fills up the last group counts as removed
+                removed[s] = RAGGED && s == d_out >> 5 && (d_out & 3) ? ((1u << (4 - (d_out & 3))) - 1u) << (d_out & 31) : 0u;
+        }
+        __syncthreads();
         const int32_t chan_base = (int32_t)(i * a.d_out);
-        for (int e = tid; e < n_ex; e += T) {
-            const int o = ex_idx[e] - chan_base;
+        for (int e = tid; e < n_ex; e += T) {  // entries of O_q are restored to their FP16 weight: no error
+            const int o = a.out_idx[lo + e] - chan_base;
             atomicOr(&removed[o >> 5], 1u << (o & 31));
-            if constexpr (MODE == kModeReuse) {  // out of its bucket's count and sum of places
-                const uint32_t key = key_of_half(__half_as_ushort(wrow_h[o]));
-                if (e == tid) first_key = key;
-                atomicAdd(reinterpret_cast<unsigned long long *>(&sm.scum[key >> LB]),
-                          0ull - ((1ull << 32) | (key & ((1u << LB) - 1))));
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- bucket tables: counts and sums of places of the kept weights
-    if constexpr (MODE != kModeReuse) {
-        if (RAGGED || n_ex > 0) count_buckets<G, T, LB, true>(keys, removed, sm.scum, n_groups);
-        else count_buckets<G, T, LB, false>(keys, removed, sm.scum, n_groups);
-        __syncthreads();
-    }
-    // ---- exclusive prefixes over buckets of count and exact sum; where each bucket's
-    //      stretch of the byte array begins (counts rounded up to whole words; with a kept
-    //      arrangement the stretches are those of its counts, the prefixes those of what is left)
-    {
-        unsigned long long *keep_tbl = keep ? reinterpret_cast<unsigned long long *>(keep + 16) : nullptr;
-        uint32_t n_loc = 0;  // count | padded count << 16: both stay below 2^16
-        long long s_loc = 0;
-        if (b0 < kBuckets) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if (r < per) {
-                    const unsigned long long packed = (unsigned long long)sm.scum[b0 + r];
-                    const uint32_t n = (uint32_t)(packed >> 32);
-                    const uint32_t n_place = MODE == kModeReuse ? n_orig[r] : n;
-                    n_loc += n | (((n_place + 3) & ~3u) << 16);
-                    s_loc += bucket_sum<LB>((uint32_t)(b0 + r), n, (uint32_t)packed);
-                    if (keep_tbl) keep_tbl[b0 + r] = packed;
-                }
-            }
-        }
-        uint32_t n_run, n_tot;
-        unsigned long long s_run_u, s_tot;
-        block_scan_excl_pair(n_loc, (unsigned long long)s_loc, sm.scan32, sm.scan64, n_run, s_run_u, n_tot, s_tot);
-        long long s_run = (long long)s_run_u;
-        if (b0 < kBuckets) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if (r < per) {
-                    const unsigned long long packed = (unsigned long long)sm.scum[b0 + r];
-                    const uint32_t n = (uint32_t)(packed >> 32);
-                    const uint32_t n_place = MODE == kModeReuse ? n_orig[r] : n;
-                    const long long sb = bucket_sum<LB>((uint32_t)(b0 + r), n, (uint32_t)packed);
-                    cursor[b0 + r] = (n_run << 16) | (n_run >> 16);
-                    sm.scum[b0 + r] = s_run;
-                    n_run += n | (((n_place + 3) & ~3u) << 16);
-                    s_run += sb;
-                }
-            }
-        }
-        if (tid == 0) {
-            sm.kept = n_tot & 0xffffu;
-            sm.scum[kBuckets] = (long long)s_tot;
-        }
-    }
-    __syncthreads();
-    const uint32_t M = sm.kept;
-    if constexpr (MODE == kModeReuse) {
-        // ---- one place byte per entry of O_q becomes a filler
-        if (n_ex > 0) {
-            const int32_t *ex_idx = a.out_idx + sm.seg_lo;
-            const int32_t chan_base = (int32_t)(i * a.d_out);
-            for (int e = tid; e < n_ex; e += T) {
-                const uint32_t key =
-                    e == tid ? first_key : key_of_half(__half_as_ushort(wrow_h[ex_idx[e] - chan_base]));
-                const uint32_t bk = key >> LB;
-                blank_one_place(reinterpret_cast<uint32_t *>(arr), stretch_of(cursor[bk]) >> 2,
-                                stretch_end<LB>(cursor, bk) >> 2,
-                                key & ((1u << LB) - 1));
-            }
         }
     } else {
-        // ---- scatter the places of the kept weights, ordered by bucket
-        if (RAGGED || n_ex > 0) scatter_places<G, T, LB, true>(keys, removed, cursor, arr, n_groups);
-        else scatter_places<G, T, LB, false>(keys, removed, cursor, arr, n_groups);
         __syncthreads();
-        // the cursors go back to where their stretches begin (a neighbour may read a word while its low
-        // half changes: it wants the upper half)
-        if (b0 < kBuckets) {
-            uint32_t word = cursor[b0];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if (r < per) {
-                    const uint32_t next = b0 + r + 1 < kBuckets ? cursor[b0 + r + 1] : word;
-                    cursor[b0 + r] = word - (before_of(next) - before_of(word));
-                    word = next;
-                }
-            }
-        }
+    }
+    switch (K) {
+        case 2: coding_prepare<G, 2, T, LB, FUSED>(a, sm, arr, tbl, tid, n_groups); break;
+        case 4: coding_prepare<G, 4, T, LB, FUSED>(a, sm, arr, tbl, tid, n_groups); break;
+        case 8: coding_prepare<G, 8, T, LB, FUSED>(a, sm, arr, tbl, tid, n_groups); break;
+        default: coding_prepare<G, 16, T, LB, FUSED>(a, sm, arr, tbl, tid, n_groups); break;
     }
     __syncthreads();
-    if (keep) {  // the arrangement as it stands, for a later run on this channel
-        const uint4 *a4 = reinterpret_cast<const uint4 *>(arr);
-        uint4 *adst = reinterpret_cast<uint4 *>(keep + 16 + (size_t)kBuckets * 8);
-        for (int s = tid; s < (int)(arr_bytes >> 4); s += T) adst[s] = a4[s];
-        if (tid == 0) *reinterpret_cast<uint32_t *>(keep) = kArrMagic + 1u;
-    }
-
-    double err = 0.0;
-    switch (K) {
-        case 2: lloyd_bucket<G, 2, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-        case 4: lloyd_bucket<G, 4, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-        case 8: lloyd_bucket<G, 8, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-        default: lloyd_bucket<G, 16, T, LB, kCodesFused, RAGGED>(a, i, sm, arr, cursor, removed, n_ex, keys, n_groups, M, err); break;
-    }
-    if (tid < CMPQ_KMAX) crow[tid] = tid < K ? sm.cent[tid] : INFINITY;
-    if constexpr (kCodesFused) {
-        // the row is complete in the place array (the coding pass ends with a barrier): copy it
-        // out, the table in FP16 beside it, and add the lanes' error sums in a fixed order
+    if constexpr (!FUSED) {
+        switch (K) {
+            case 2: coding_pass_plain<G, 2, T, LB, RAGGED>(a, i, sm, tbl, tid, n_groups); break;
+            case 4: coding_pass_plain<G, 4, T, LB, RAGGED>(a, i, sm, tbl, tid, n_groups); break;
+            case 8: coding_pass_plain<G, 8, T, LB, RAGGED>(a, i, sm, tbl, tid, n_groups); break;
+            default: coding_pass_plain<G, 16, T, LB, RAGGED>(a, i, sm, tbl, tid, n_groups); break;
+        }
+    } else {
+        double err;
+        switch (K) {
+            case 2: err = coding_pass_fused<G, 2, T, LB, RAGGED>(a, i, sm, arr, tbl, removed, n_ex, tid, n_groups); break;
+            case 4: err = coding_pass_fused<G, 4, T, LB, RAGGED>(a, i, sm, arr, tbl, removed, n_ex, tid, n_groups); break;
+            case 8: err = coding_pass_fused<G, 8, T, LB, RAGGED>(a, i, sm, arr, tbl, removed, n_ex, tid, n_groups); break;
+            default: err = coding_pass_fused<G, 16, T, LB, RAGGED>(a, i, sm, arr, tbl, removed, n_ex, tid, n_groups); break;
+        }
+        // the lanes' error sums, added in a fixed order
+        err = wave_sum_f64(err);
+        if ((tid & 63) == 0) sm.red[tid >> 6] = err;
+        __syncthreads();
+        // the row is complete: copy it out, the table in FP16 beside it
         if (row_dst) {
             const uint32_t *stage = reinterpret_cast<const uint32_t *>(arr);
             for (int w = tid; w < row_words; w += T) row_dst[w] = stage[w];
         }
         if (lut_dst && tid < K) lut_dst[tid] = __half_as_ushort(__float2half_rn(sm.cent[tid]));
-        err = wave_sum_f64(err);
-        double *red = reinterpret_cast<double *>(sm.scan64);
-        if ((tid & 63) == 0) red[tid >> 6] = err;
-        __syncthreads();
         if (tid == 0 && a.err_ch) {
             double t = 0.0;
-            for (int w = 0; w < T / CMPQ_WAVE; ++w) t += red[w];
+            for (int w = 0; w < T / CMPQ_WAVE; ++w) t += sm.red[w];
             a.err_ch[i] = t;
         }
     }
@@ -981,21 +1238,79 @@ size_t bucket_dyn_lds(int64_t d_out, int lb) {
     return b;
 }
 
-template <int G, int T, int LB>
-int launch_variant(const KmArgs &a, hipStream_t s) {
-    auto kern = a.arr_reuse ? kmeans_bucket_kernel<G, T, LB, kModeReuse, false>
-                            : (a.fused ? kmeans_bucket_kernel<G, T, LB, kModeFused, false> : kmeans_bucket_kernel<G, T, LB, kModePlain, false>);
-    if (a.ragged) kern = a.fused ? kmeans_bucket_kernel<G, T, LB, kModeFused, true> : kmeans_bucket_kernel<G, T, LB, kModePlain, true>;
-    const size_t lds = bucket_dyn_lds(a.d_out, LB);
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+template <typename Kern>
+int allow_lds(Kern kern, size_t lds) {
+    if (lds <= 64 * 1024) return CMPQ_OK;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
         (void)hipGetLastError();
         return CMPQ_EHIP;
     }
-    cmpq_timing_before(CMPQ_KERNEL_KMEANS, s);
-    kern<<<dim3((unsigned)a.d_in), dim3((unsigned)T), lds, s>>>(a);
-    cmpq_timing_after(CMPQ_KERNEL_KMEANS, s);
+    return CMPQ_OK;
+}
+
+// Rows of 16 lanes per channel in the rounds.  More rows shorten the scan of a bucket and put more wavefronts on
+// the chip, fewer share the rest of the chain: first quantization with 1 / 2 / 4 rows, us: 8192 x 1024 62 / 76 /
+// 100, 4096 x 4096 69 / 63 / 76, 28672 x 8192 552 / 459 / 456, 8192 x 28672 433 / 395 / 360.
+template <int T>
+constexpr int kRows = T == 64 ? 1 : (T < 512 ? 2 : 4);
+template <int R, int LB, int AHEAD>
+int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *tables, int64_t stride,
+                   const unsigned char *removed, ChannelFinal *fin, hipStream_t s) {
+    const unsigned grid = (unsigned)cdiv(n, 4 / R);
+    const size_t lds = 4 / R * (removed ? ChannelView<LB, true>::kBytes : ChannelView<LB, false>::kBytes);
+    auto kern = removed ? kmeans_rounds_kernel<R, LB, AHEAD, true> : kmeans_rounds_kernel<R, LB, AHEAD, false>;
+    if (const int rc = allow_lds(kern, lds)) return rc;
+    kern<<<grid, CMPQ_WAVE, lds, s>>>(a, i0, n, tables, stride, removed, fin);
     CMPQ_LAUNCH_CHECK();
+    return CMPQ_OK;
+}
+
+// One quantization, a run of channels at a time (as many as the scratch holds tables for).
+template <int G, int T, int LB>
+int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes, hipStream_t s) {
+    const int64_t stride = (int64_t)table_bytes(a.d_out, LB);
+    const bool want_codes = a.codes || a.fused;
+    // scratch per channel: tables of all weights, or of the removed ones beside kept tables; what the rounds leave
+    const bool own_tables = !a.arr_keep && !a.arr_reuse, rem_tables = a.arr_reuse && a.n_out > 0;
+    const int64_t per_chan = (own_tables || rem_tables ? stride : 0) + (want_codes ? (int64_t)sizeof(ChannelFinal) : 0);
+    int64_t step = a.d_in;
+    if (per_chan > 0 && (int64_t)(scratch_bytes / per_chan) < step) step = (int64_t)(scratch_bytes / per_chan);
+    if (step < 1) return CMPQ_EWORKSPACE;
+    ChannelFinal *fin = want_codes ? reinterpret_cast<ChannelFinal *>(scratch) : nullptr;
+    unsigned char *side = scratch + (want_codes ? step * (int64_t)sizeof(ChannelFinal) : 0);
+    cmpq_timing_before(CMPQ_KERNEL_KMEANS, s);
+    for (int64_t i0 = 0; i0 < a.d_in; i0 += step) {
+        const int64_t n = a.d_in - i0 < step ? a.d_in - i0 : step;
+        unsigned char *tables = a.arr_keep ? static_cast<unsigned char *>(a.arr_keep) + i0 * stride : side;
+        const unsigned char *src = tables;
+        if (a.arr_reuse) {
+            src = static_cast<const unsigned char *>(a.arr_reuse) + i0 * stride;
+            if (rem_tables) {
+                kmeans_removed_kernel<LB><<<(unsigned)n, kRemovedLanes, 0, s>>>(a, i0, side, stride);
+                CMPQ_LAUNCH_CHECK();
+            }
+        } else {
+            const bool masked = a.n_out > 0 || a.ragged;
+            auto kern = a.ragged ? kmeans_build_kernel<G, T, LB, true, true>
+                                 : (masked ? kmeans_build_kernel<G, T, LB, true, false> : kmeans_build_kernel<G, T, LB, false, false>);
+            const size_t lds = bucket_arr_bytes(a.d_out, LB) + (masked ? (size_t)((((a.d_out + 31) >> 5) + 3) & ~3) * 4 : 0) +
+                               ((size_t)4 << (16 - LB));
+            if (const int rc = allow_lds(kern, lds)) return rc;
+            kern<<<(unsigned)n, T, lds, s>>>(a, i0, tables, stride);
+            CMPQ_LAUNCH_CHECK();
+        }
+        if (const int rc = launch_rounds<kRows<T>, LB, G == 16 ? 8 : 4>(a, i0, n, src, stride, rem_tables ? side : nullptr, fin, s)) return rc;
+        if (want_codes) {
+            auto kern = a.fused ? (a.ragged ? kmeans_code_kernel<G, T, LB, true, true> : kmeans_code_kernel<G, T, LB, true, false>)
+                                : (a.ragged ? kmeans_code_kernel<G, T, LB, false, true> : kmeans_code_kernel<G, T, LB, false, false>);
+            size_t lds = (size_t)code_table_words(T, G, LB) * 4;
+            if (a.fused) lds += (size_t)((((a.d_out + 31) >> 5) + 3) & ~3) * 4 + (size_t)(a.d_out / 2 + 16);
+            if (const int rc = allow_lds(kern, lds)) return rc;
+            kern<<<(unsigned)n, T, lds, s>>>(a, i0, fin);
+            CMPQ_LAUNCH_CHECK();
+        }
+    }
+    cmpq_timing_after(CMPQ_KERNEL_KMEANS, s);
     return CMPQ_OK;
 }
 
@@ -1007,7 +1322,7 @@ int launch_variant(const KmArgs &a, hipStream_t s) {
 #ifndef CMPQ_LB256
 #define CMPQ_LB256 7
 #endif
-// The launch shape launch_kmeans_hist picks for a channel length: lanes per workgroup, groups of
+// The launch shape for a channel length: lanes per workgroup, groups of
 // 4 weights per lane, low bits of a key that name the place inside a bucket.  0 lanes: too long.
 static void hist_variant(int64_t d_out, int &T_out, int &G_out, int &LB_out) {
     const int64_t groups = d_out / 4;
@@ -1024,44 +1339,53 @@ static void hist_variant(int64_t d_out, int &T_out, int &G_out, int &LB_out) {
     else G_out = 1;
 }
 
+// Rows of any length: up to whole groups of 4.
+static bool table_shape(int64_t d_out, int &T, int &G, int &LB) {
+    hist_variant((d_out + 3) / 4 * 4, T, G, LB);
+    return T != 0;
+}
+
 size_t kmeans_hist_arrangement_stride(int64_t d_out) {
-    if (d_out < 4 || d_out % 4 != 0) return 0;
     int T, G, LB;
-    hist_variant(d_out, T, G, LB);
-    return T == 0 ? 0 : arrangement_stride(d_out, LB);
+    if (d_out < 4 || d_out % 4 != 0 || !table_shape(d_out, T, G, LB)) return 0;
+    return table_bytes(d_out, LB);
+}
+
+size_t kmeans_hist_scratch(int64_t d_in, int64_t d_out) {
+    int T, G, LB;
+    if (d_in < 1 || d_out < 1 || !table_shape(d_out, T, G, LB)) return 0;
+    return (size_t)d_in * (table_bytes(d_out, LB) + sizeof(ChannelFinal));
 }
 
 extern "C" int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape) {
     if (!shape || d_out < 4 || d_out % 4 != 0) return CMPQ_EINVAL;
     int T, G, LB;
-    hist_variant(d_out, T, G, LB);
-    if (T == 0) return CMPQ_ESHAPE;
+    if (!table_shape(d_out, T, G, LB)) return CMPQ_ESHAPE;
     shape[0] = T;
     shape[1] = G;
     shape[2] = LB;
     shape[3] = (int64_t)bucket_arr_bytes(d_out, LB);
     shape[4] = (int64_t)bucket_dyn_lds(d_out, LB);
-    shape[5] = LB == 6 ? (int64_t)sizeof(BucketShared<6>) : (int64_t)sizeof(BucketShared<7>);
+    shape[5] = (int64_t)sizeof(PrefixShared<512>) + 8 * 4;
     return CMPQ_OK;
 }
 
-int launch_kmeans_hist(const KmArgs &a, hipStream_t s) {
+int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hipStream_t s) {
     // A power-of-two workgroup of at most 512 lanes: up to 32 weights per lane, 64 for the
-    // longest channels (two workgroups of 512 share a compute unit where one of 1024
-    // would leave it idle at every barrier).
+    // longest channels.
     int T, G, LB;
-    hist_variant((a.d_out + 3) / 4 * 4, T, G, LB);
-    if (T == 0) return CMPQ_ESHAPE;
-    if (G == 16) return launch_variant<16, 512, CMPQ_LB512>(a, s);
+    if (!table_shape(a.d_out, T, G, LB)) return CMPQ_ESHAPE;
+    unsigned char *sc = static_cast<unsigned char *>(scratch);
+    if (G == 16) return launch_variant<16, 512, CMPQ_LB512>(a, sc, scratch_bytes, s);
     if (G == 8) {
         switch (T) {
-            case 512: return launch_variant<8, 512, CMPQ_LB512>(a, s);
-            case 256: return launch_variant<8, 256, CMPQ_LB256>(a, s);
-            case 128: return launch_variant<8, 128, 7>(a, s);
-            default: return launch_variant<8, 64, 7>(a, s);
+            case 512: return launch_variant<8, 512, CMPQ_LB512>(a, sc, scratch_bytes, s);
+            case 256: return launch_variant<8, 256, CMPQ_LB256>(a, sc, scratch_bytes, s);
+            case 128: return launch_variant<8, 128, 7>(a, sc, scratch_bytes, s);
+            default: return launch_variant<8, 64, 7>(a, sc, scratch_bytes, s);
         }
     }
-    if (G == 4) return launch_variant<4, 64, 7>(a, s);
-    if (G == 2) return launch_variant<2, 64, 7>(a, s);
-    return launch_variant<1, 64, 7>(a, s);
+    if (G == 4) return launch_variant<4, 64, 7>(a, sc, scratch_bytes, s);
+    if (G == 2) return launch_variant<2, 64, 7>(a, sc, scratch_bytes, s);
+    return launch_variant<1, 64, 7>(a, sc, scratch_bytes, s);
 }

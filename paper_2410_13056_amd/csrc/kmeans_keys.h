@@ -153,36 +153,28 @@ __device__ __forceinline__ uint32_t cell_of(uint32_t q, const uint32_t (&t)[CMPQ
     }
 }
 
-// The largest fp16 value that is not above x (x finite, |x| < 65504), as its bit pattern: the
-// two narrowing conversions run with the rounding mode set to "towards minus infinity" (both
-// precision groups of the mode register), which is put back to "nearest even" - the mode this
-// library's kernels run in - before the block ends.  Rounding down twice is rounding down once.
-__device__ __forceinline__ uint32_t floor_half_of_double(double x) {
+// Key of the largest fp16 value that belongs to `lo` rather than `hi` (lo < hi): values below the midpoint,
+// and the midpoint itself unless `tie_up` (the upper level has the smaller index).  Never the key of -0: a
+// boundary there would part the two zeros.  Values that are no levels give some key.
+//
+// The midpoint narrowed to fp32 (nearest) and then to fp16 (towards zero) is the largest fp16 value not
+// above it or the next one, as neither step can pass an fp16 value: one comparison tells which.
+// (A midpoint between -2^-24 and 0 comes out as -0, which is above it: the key below is that of -2^-24.)
+__device__ __forceinline__ uint32_t boundary_key(float lo, float hi, bool tie_up) {
+    const double twice = (double)lo + (double)hi;  // exact
+    typedef __fp16 Half2 __attribute__((ext_vector_type(2)));
+    const Half2 narrow = __builtin_amdgcn_cvt_pkrtz((float)twice * 0.5f, 0.0f);  // (upper half +0)
     uint32_t h;
-    float f;
-    asm volatile(
-        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0xa\n\t"
-        "s_nop 1\n\t"
-        "v_cvt_f32_f64 %1, %2\n\t"
-        "s_nop 0\n\t"
-        "v_cvt_f16_f32 %0, %1\n\t"
-        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0x0\n\t"
-        "s_nop 1"
-        : "=v"(h), "=&v"(f)
-        : "v"(x));
-    return h & 0xffffu;
-}
-
-// Key of the largest fp16 value that belongs to `lo` rather than `hi` (lo < hi): values
-// below the midpoint, and the midpoint itself when lo has the smaller level index.
-// Never the key of -0: a boundary there would part the two zeros.
-__device__ __forceinline__ uint32_t boundary_key(float lo, float hi, int owner_lo, int owner_hi) {
-    const double mid = ((double)lo + (double)hi) * 0.5;  // exact
-    uint32_t h = floor_half_of_double(mid);
-    h = h == 0x8000u ? 0u : h;  // -0 is +0 here
-    uint32_t key = key_of_half(h);
-    key -= ((double)value_of_key(key) == mid && owner_hi < owner_lo) ? 1u : 0u;
-    return key == 0x7fffu ? 0x7ffeu : key;
+    __builtin_memcpy(&h, &narrow, 4);
+    const float at = __half2float(__ushort_as_half((unsigned short)h));
+    const double at2 = (double)(at + at);
+    uint32_t key = (h ^ (0x8000u | (uint32_t)__builtin_amdgcn_sbfe((int)h, 15, 1))) & 0xffffu;
+    key -= at2 > twice ? 1u : 0u;
+    if (tie_up && at2 == twice) {
+        key -= 1u;
+        key = key == 0x7fffu ? 0x7ffeu : key;
+    }
+    return key;
 }
 
 // Wave 0: levels by level index (lane j holds c for j < K) -> per sorted position p

@@ -201,7 +201,7 @@ __global__ __launch_bounds__(1024) void lut4_cluster_kernel(const uint32_t *__re
     uint32_t tk_prev = 0xffffffffu;
     for (int round = 0;; ++round) {
         uint32_t tk = kKeyInf;
-        if (have_hi) tk = boundary_key(c_sorted, hi_v, owner_lo, owner_hi);
+        if (have_hi) tk = boundary_key(c_sorted, hi_v, owner_hi < owner_lo);
         const bool moved = __ballot(lane < CMPQ_KMAX - 1 && tk != tk_prev) != 0ull;
         tk_prev = tk;
         if (round == iters || !moved) break;  // a fixed point repeats itself

@@ -1,0 +1,106 @@
+"""The K-means kernels that build, share and read per-channel tables, at the edges of their forms: counts
+that do not fit the packed 32-bit word, buckets longer than one fetch of words, groups of channels that
+end in the middle of a wavefront, scratch for a few channels only, tables of another row length."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def env():
+    import oracle as orc
+    from paper_2410_13056_amd import binding as B
+    B.lib()
+    return dict(B=B, orc=orc, ws=B.Workspace(DEV))
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+def _crowded(rng, d_in, d_out):
+    """Rows whose weights share a bucket or a few: around 1, with the highest places alone, one value, zeros
+    of both signs, a wide row beside them."""
+    W = (1.0 + 0.06 * rng.random((d_in, d_out))).astype(np.float16)
+    W[1 % d_in] = np.float16(1.0) + np.float16(2 ** -10) * (60 + rng.integers(0, 4, d_out))
+    W[2 % d_in] = np.float16(-0.7)
+    W[3 % d_in] = np.where(rng.random(d_out) < 0.5, 0.0, -0.0)
+    W[4 % d_in] = rng.normal(0, 0.02, d_out)
+    return W.astype(np.float16)
+
+
+@pytest.mark.parametrize("d_out", [64, 1024, 4096, 4100, 8192, 28672, 32768])
+@pytest.mark.parametrize("d_in", [1, 6])
+def test_crowded_buckets_match_the_oracle(env, d_out, d_in):
+    B, ws, orc = env["B"], env["ws"], env["orc"]
+    rng = np.random.default_rng(d_out + d_in)
+    W = _crowded(rng, d_in, d_out)
+    bits = np.array([4, 4, 3, 2, 3, 16][:d_in], np.uint8)
+    excl = np.sort(rng.choice(d_in * d_out, max(1, d_in * d_out // 50), replace=False)).astype(np.int32)
+    dW, db, de = _dev(W), _dev(bits), _dev(excl)
+    tables = torch.empty(B.arrangement_bytes(d_in, d_out), dtype=torch.uint8, device=DEV)
+    cent = torch.empty((d_in, 16), dtype=torch.float32, device=DEV)
+    codes = torch.empty((d_in, d_out), dtype=torch.uint8, device=DEV)
+    B.kmeans_quantize(dW, db, None, 0, None, 6, cent, codes, ws, arrangement=tables, arrangement_use=B.ARRANGEMENT_KEEP)
+    oc, ok = orc.kmeans(W, bits, iters=6)
+    assert np.array_equal(_np(cent), oc) and np.array_equal(_np(codes), ok)
+    oc, ok = orc.kmeans(W, bits, out_idx=excl.astype(np.int64), iters=6)
+    for use in (B.ARRANGEMENT_NONE, B.ARRANGEMENT_REUSE):
+        cent.fill_(7.0), codes.fill_(255)
+        B.kmeans_quantize(dW, db, de, len(excl), None, 6, cent, codes, ws,
+                          arrangement=tables if use else None, arrangement_use=use)
+        assert np.array_equal(_np(cent), oc) and np.array_equal(_np(codes), ok)
+
+
+class _Limited:
+    """A workspace of a given size, whatever is asked for."""
+
+    def __init__(self, nbytes):
+        self.buf = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+
+    def get(self, nbytes):
+        return self.buf
+
+
+@pytest.mark.parametrize("d_out", [1024, 4098, 8192])
+def test_scratch_for_a_few_channels_gives_the_same_bits(env, d_out):
+    B, ws = env["B"], env["ws"]
+    rng = np.random.default_rng(3)
+    d_in = 23
+    W = rng.normal(0, 0.02, (d_in, d_out)).astype(np.float16)
+    bits = rng.choice(np.array([2, 3, 4, 16], np.uint8), d_in)
+    excl = _dev(np.sort(rng.choice(d_in * d_out, d_in * d_out // 80, replace=False)).astype(np.int32))
+    dW, db = _dev(W), _dev(bits)
+    cent = torch.empty((d_in, 16), dtype=torch.float32, device=DEV)
+    codes = torch.empty((d_in, d_out), dtype=torch.uint8, device=DEV)
+    B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, ws)
+    full = B.workspace_bytes(B.OP_KMEANS, d_in, d_out)
+    one = (full - B.workspace_bytes(B.OP_KMEANS, 1, d_out)) // (d_in - 1)
+    for channels in (1, 5, d_in - 1):
+        c2, k2 = torch.full_like(cent, 7.0), torch.full_like(codes, 255)
+        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, c2, k2, _Limited(full - (d_in - channels) * one + 512))
+        assert torch.equal(c2, cent) and torch.equal(k2, codes)
+    with pytest.raises(B.CmpqError):
+        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, _Limited(256))
+
+
+def test_tables_of_another_row_length_are_flagged(env):
+    B, ws = env["B"], env["ws"]
+    rng = np.random.default_rng(5)
+    W = rng.normal(0, 0.02, (3, 4096)).astype(np.float16)
+    db = _dev(np.full(3, 3, np.uint8))
+    tables = torch.zeros(B.arrangement_bytes(3, 4096), dtype=torch.uint8, device=DEV)
+    cent = torch.empty((3, 16), dtype=torch.float32, device=DEV)
+    B.kmeans_quantize(_dev(W), db, None, 0, None, 3, cent, None, ws, arrangement=tables, arrangement_use=B.ARRANGEMENT_KEEP)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    codes = torch.full((3, 2048), 9, dtype=torch.uint8, device=DEV)
+    B.kmeans_quantize(_dev(W[:, :2048]), db, None, 0, None, 3, cent, codes, ws, st, arrangement=tables,
+                      arrangement_use=B.ARRANGEMENT_REUSE)
+    assert st.item() == B.STATUS_ARRANGEMENT and not codes.any() and not cent[:, :8].any()
