@@ -3,12 +3,16 @@
 // Delta = (max - min) / (2^N - 1), per group of consecutive outputs of an input channel, with
 // the channel's width N from Algorithm 1.
 //
-// HBM bound: 2 (or 4) bytes of W read, 1 byte of code written per weight, two floats per
-// group.  One workgroup per channel; a lane takes 8 consecutive weights per step (one 16-byte
-// load, one 8-byte store), so a group of g weights is g / 8 neighbouring lanes and its range
-// is found with a butterfly of lane exchanges - min and max do not depend on the order.  The
-// code is decided in fp32 from the correctly rounded quotient (w - min) / Delta; the squared
-// error is summed in fp64 per lane and reduced in a fixed order.
+// One workgroup per channel; a lane takes 8 consecutive weights per step (one 16-byte load a step ahead, one
+// 8-byte store), so a group of g weights is g / 8 neighbouring lanes and its range is found with exchanges
+// between them - min and max do not depend on the order.  The code is the whole number nearest to the correctly
+// rounded fp32 quotient (w - min) / Delta; the squared error is summed in fp64 per lane and reduced in a fixed
+// order.
+//
+// Bound by instruction issue and HBM alike: 3 B a weight (FP16; 5120 x 13824 in 56 us = 3.8 TB/s, a plain copy
+// here 4.8) and 25 vector instructions, 46 us of it.  It took 77 us with 36: a division in 64 bits for the
+// group's number, the group's range exchanged through LDS float by float, the quotient carried to its last bit
+// for every weight.
 #include "common.h"
 
 namespace {
@@ -16,34 +20,10 @@ namespace {
 constexpr int kT = 256;
 constexpr int kPer = 8;  // weights per lane and step
 
-// Eight consecutive weights of one channel, by a vector load when the addresses allow it.
+// Eight consecutive weights of one channel at any alignment and end.
 // Returns the mask of entries that exist (o0 + j < d_out).
 template <typename TW>
-__device__ __forceinline__ uint32_t load8w(const TW *__restrict__ wrow, int64_t o0, int64_t d_out, bool vec_ok,
-                                           float (&w)[kPer]) {
-    if (o0 >= d_out) {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) w[j] = 0.f;
-        return 0u;
-    }
-    if (vec_ok && o0 + kPer <= d_out) {
-        if constexpr (sizeof(TW) == 2) {
-            const uint4 raw = load16_stream(wrow + o0);
-            const __half2 *h = reinterpret_cast<const __half2 *>(&raw);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float2 t = __half22float2(h[j]);
-                w[2 * j] = t.x;
-                w[2 * j + 1] = t.y;
-            }
-        } else {
-            const float4 r0 = *reinterpret_cast<const float4 *>(wrow + o0);
-            const float4 r1 = *reinterpret_cast<const float4 *>(wrow + o0 + 4);
-            w[0] = r0.x, w[1] = r0.y, w[2] = r0.z, w[3] = r0.w;
-            w[4] = r1.x, w[5] = r1.y, w[6] = r1.z, w[7] = r1.w;
-        }
-        return 0xffu;
-    }
+__device__ __forceinline__ uint32_t load8w(const TW *__restrict__ wrow, int64_t o0, int64_t d_out, float (&w)[kPer]) {
     uint32_t valid = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
@@ -56,6 +36,96 @@ __device__ __forceinline__ uint32_t load8w(const TW *__restrict__ wrow, int64_t 
     return valid;
 }
 
+// The 8 weights of a lane as they lie in memory (16-byte aligned), and as floats.
+template <typename TW>
+struct Piece {
+    uint4 v[sizeof(TW) / 2];
+    __device__ __forceinline__ void fetch(const TW *p, bool there) {
+#pragma unroll
+        for (int q = 0; q < (int)(sizeof(TW) / 2); ++q) v[q] = there ? load16_stream(p + q * (16 / sizeof(TW))) : make_uint4(0, 0, 0, 0);
+    }
+    __device__ __forceinline__ void floats(float (&w)[kPer]) const {
+        if constexpr (sizeof(TW) == 2) {
+            const __half2 *h = reinterpret_cast<const __half2 *>(&v[0]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float2 t = __half22float2(h[j]);
+                w[2 * j] = t.x;
+                w[2 * j + 1] = t.y;
+            }
+        } else {
+            __builtin_memcpy(w, v, sizeof(w));
+        }
+    }
+};
+
+// Packed FP16 minimum (the compiler's own form first quiets both operands).
+__device__ __forceinline__ uint32_t pk_min_f16(uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t min_step(uint32_t x) {
+    return pk_min_f16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true));
+}
+// FP16: range of the group from a lane's 8 weights, and whether one of these is not finite.  Smallest and
+// negated largest travel as one pair: 2 instructions an exchange where single floats take 8.
+__device__ __forceinline__ void range_of_halves(const uint4 &v, bool there, int lanes, float &lo, float &hi, bool &bad) {
+    typedef unsigned short Bits2 __attribute__((ext_vector_type(2)));
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    Bits2 m = __builtin_bit_cast(Bits2, d[0] & 0x7fff7fffu);
+#pragma unroll
+    for (int q = 1; q < 4; ++q) m = __builtin_elementwise_max(m, __builtin_bit_cast(Bits2, d[q] & 0x7fff7fffu));
+    bad |= (m.x > m.y ? m.x : m.y) >= 0x7c00;
+    const uint32_t mn = pk_min_f16(pk_min_f16(d[0], d[1]), pk_min_f16(d[2], d[3]));
+    const uint32_t s = 0x80008000u;
+    const uint32_t mx = pk_min_f16(pk_min_f16(d[0] ^ s, d[1] ^ s), pk_min_f16(d[2] ^ s, d[3] ^ s));
+    uint32_t x = pk_min_f16(__builtin_amdgcn_perm(mx, mn, 0x05040100u), __builtin_amdgcn_perm(mx, mn, 0x07060302u));
+    if (!there) x = 0x7c007c00u;  // a lane past the end (its weights read as 0) brings nothing into its group
+    if (lanes >= 2) x = min_step<0xB1>(x);    // quad_perm [1,0,3,2]
+    if (lanes >= 4) x = min_step<0x4E>(x);    // quad_perm [2,3,0,1]
+    if (lanes >= 8) x = min_step<0x141>(x);   // row_half_mirror
+    if (lanes >= 16) x = min_step<0x140>(x);  // row_mirror
+    if (lanes >= 32) {
+        const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = pk_min_f16(a[0], a[1]);
+    }
+    if (lanes >= 64) {
+        const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        x = pk_min_f16(a[0], a[1]);
+    }
+    lo = __half2float(__ushort_as_half((unsigned short)x));
+    hi = -__half2float(__ushort_as_half((unsigned short)(x >> 16)));
+}
+
+// Smallest lo and largest hi over aligned groups of `lanes` lanes (a power of two, the same for all), in every
+// lane of a group.  On the DPP path inside a row of 16 lanes, by row swaps across rows: as exchanges through
+// LDS these were 8 trips of some 130 cycles one after the other for a group of 128 weights.
+template <int CTRL>
+__device__ __forceinline__ void range_step(float &lo, float &hi) {
+    lo = fminf(lo, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(lo), CTRL, 0xF, 0xF, true)));
+    hi = fmaxf(hi, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(hi), CTRL, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ void range_of_group(float &lo, float &hi, int lanes) {
+    if (lanes >= 2) range_step<0xB1>(lo, hi);    // quad_perm [1,0,3,2]
+    if (lanes >= 4) range_step<0x4E>(lo, hi);    // quad_perm [2,3,0,1]
+    if (lanes >= 8) range_step<0x141>(lo, hi);   // row_half_mirror
+    if (lanes >= 16) range_step<0x140>(lo, hi);  // row_mirror
+    if (lanes >= 32) {
+        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(lo), false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(hi), __float_as_uint(hi), false, false);
+        lo = fminf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        hi = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    }
+    if (lanes >= 64) {
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(lo), false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(hi), __float_as_uint(hi), false, false);
+        lo = fminf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        hi = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    }
+}
+
 // lanes_per_group: a power of two in 1..64 (group / 8).  VEC: rows are read and written in
 // whole 8-weight pieces (aligned, d_out a multiple of 8), so a lane's piece exists entirely
 // or not at all and no entry needs a test of its own.
@@ -65,7 +135,6 @@ __global__ __launch_bounds__(kT) void rtn_kernel(const TW *__restrict__ W, int64
                                                   int64_t n_groups, uint8_t *__restrict__ codes,
                                                   float *__restrict__ scale, float *__restrict__ zero,
                                                   double *__restrict__ err_ch, int32_t *__restrict__ status) {
-    constexpr int vec_ok = VEC ? 1 : 0;
     __shared__ double red[kT / CMPQ_WAVE];
     const int64_t i = blockIdx.x;
     const int tid = threadIdx.x;
@@ -74,26 +143,46 @@ __global__ __launch_bounds__(kT) void rtn_kernel(const TW *__restrict__ W, int64
     const float top = (float)((1 << (kept ? 1 : N)) - 1);
     const TW *wrow = W + i * ldw;
     uint8_t *crow = codes + i * d_out;
+    const int group_shift = __ffs(lanes_per_group * kPer) - 1;  // (a division in 64 bits is 130 instructions)
     double s = 0.0;
     bool bad = false;
+    Piece<TW> next;
+    if constexpr (VEC) next.fetch(wrow + (int64_t)tid * kPer, (int64_t)tid * kPer < d_out);
     for (int64_t base = 0; base < d_out; base += (int64_t)kT * kPer) {
         const int64_t o0 = base + (int64_t)tid * kPer;
         float w[kPer];
-        const uint32_t valid = load8w<TW>(wrow, o0, d_out, vec_ok, w);
-        auto has = [&](int j) -> bool { return VEC ? valid != 0u : ((valid >> j) & 1u) != 0u; };
+        uint32_t valid;
         float lo = INFINITY, hi = -INFINITY;
+        if constexpr (VEC) {  // the next step's weights are on their way while these are worked on
+            const Piece<TW> piece = next;
+            valid = o0 < d_out ? 0xffu : 0u;
+            next.fetch(wrow + o0 + (int64_t)kT * kPer, o0 + (int64_t)kT * kPer < d_out);
+            piece.floats(w);
+            if constexpr (sizeof(TW) == 2) {
+                bool odd = false;
+                range_of_halves(piece.v[0], valid != 0, lanes_per_group, lo, hi, odd);
+                bad |= odd;
+            } else if (valid) {
 #pragma unroll
-        for (int j = 0; j < kPer; ++j)
-            if (has(j)) {
-                lo = fminf(lo, w[j]);
-                hi = fmaxf(hi, w[j]);
-                bad |= !isfinite(w[j]);
+                for (int j = 0; j < kPer; ++j) {
+                    lo = fminf(lo, w[j]);
+                    hi = fmaxf(hi, w[j]);
+                    bad |= !isfinite(w[j]);
+                }
             }
-        // range of the group: every lane of the wavefront takes part, also those past the end
-        for (int off = 1; off < lanes_per_group; off <<= 1) {
-            lo = fminf(lo, __shfl_xor(lo, off));
-            hi = fmaxf(hi, __shfl_xor(hi, off));
+        } else {
+            valid = load8w<TW>(wrow, o0, d_out, w);
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                if ((valid >> j) & 1u) {
+                    lo = fminf(lo, w[j]);
+                    hi = fmaxf(hi, w[j]);
+                    bad |= !isfinite(w[j]);
+                }
         }
+        auto has = [&](int j) -> bool { return VEC ? valid != 0u : ((valid >> j) & 1u) != 0u; };
+        // range of the group: every lane of the wavefront takes part, also those past the end
+        if constexpr (!(VEC && sizeof(TW) == 2)) range_of_group(lo, hi, lanes_per_group);
         if (!valid) continue;
         float r[kPer];
 #pragma unroll
@@ -112,36 +201,31 @@ __global__ __launch_bounds__(kT) void rtn_kernel(const TW *__restrict__ W, int64
         }
         const float delta = (hi - lo) / top;
         if ((tid & (lanes_per_group - 1)) == 0) {
-            const int64_t g = o0 / ((int64_t)lanes_per_group * kPer);
+            const int64_t g = o0 >> group_shift;
             scale[i * n_groups + g] = delta;
             zero[i * n_groups + g] = lo;
         }
         if (!kept && delta != 0.f) {
-            // The correctly rounded quotient (w - lo) / delta by Markstein's method (Computation of
-            // elementary functions on the IBM RISC System/6000 processor, 1990): the reciprocal by a
-            // Newton step from an estimate, the quotient from it, then its residual, exact in a fused
-            // multiply-add, as a correction - twice, since the reciprocal may be off by an ulp.  What
-            // depends on delta alone is done once per step instead of once per weight; no intermediate
-            // can leave the normal range, with delta well inside it, for a quotient that rounds to a
-            // code above 0.  Other steps (tiny or huge delta) divide in the ordinary way.
-            float quo[kPer];
+            // The code is the whole number nearest to the correctly rounded quotient (w - lo) / delta.  A product
+            // with the reciprocal is within 2^-17 of that quotient (16 * 2^-21): where none of the 8 comes
+            // closer than 2^-16 to half way between two codes, it rounds to the same number.  Otherwise (one
+            // wavefront step in 60), and for tiny or huge delta, the quotient itself.
+            float farthest = 1.f;
             if (delta >= 0x1p-60f && delta <= 0x1p60f) {
                 const float y0 = __builtin_amdgcn_rcpf(delta);
                 const float y = fmaf(fmaf(-delta, y0, 1.f), y0, y0);
+                farthest = 0.f;
 #pragma unroll
                 for (int j = 0; j < kPer; ++j) {
-                    const float a = w[j] - lo;
-                    const float m = a * y;
-                    const float q1 = fmaf(fmaf(-delta, m, a), y, m);
-                    quo[j] = fmaf(fmaf(-delta, q1, a), y, q1);
+                    const float q = (w[j] - lo) * y;
+                    r[j] = rintf(q);
+                    farthest = fmaxf(farthest, fabsf(q - r[j]));
                 }
-            } else {
-#pragma unroll
-                for (int j = 0; j < kPer; ++j) quo[j] = (w[j] - lo) / delta;
             }
+            if (farthest > 0.5f - 0x1p-16f) {
 #pragma unroll
-            for (int j = 0; j < kPer; ++j)
-                if (has(j)) r[j] = fminf(fmaxf(rintf(quo[j]), 0.f), top);
+                for (int j = 0; j < kPer; ++j) r[j] = fminf(fmaxf(rintf((w[j] - lo) / delta), 0.f), top);
+            }
         }
         if (WITH_ERR && !kept) {
 #pragma unroll
