@@ -25,6 +25,15 @@ static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 __device__ __forceinline__ size_t align_up_dev(size_t x) { return (x + 15) & ~(size_t)15; }
 
+// Number of entries of the ascending list idx[0..n) below `first`.
+__device__ __forceinline__ int32_t entries_below(const int32_t *__restrict__ idx, int64_t n, int64_t first) {
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)idx[mid] < first) lo = mid + 1; else hi = mid;
+    }
+    return (int32_t)lo;
+}
 // seg[i] = number of entries of the ascending list idx[0..n) below i*d_out, i = 0..d_in.
 int launch_segment_offsets(const int32_t *idx, int64_t n, int64_t d_in, int64_t d_out, int32_t *seg,
                            hipStream_t s);
@@ -49,8 +58,15 @@ struct PackPtrs {
 // Checks the host arrays of cmpq_pack and gathers the device pointers.
 int gather_pack_ptrs(int64_t d_in, int64_t d_out, const int32_t *bit_set, int n_set, const int64_t *counts_host,
                      uint32_t *const *packed, int32_t *const *chan_idx, uint16_t *const *lut, PackPtrs &p);
-// row_of[i] = row of channel i inside its width group (-1: it stores no row); fills the channel lists.
-int launch_pack_index(const uint8_t *bits, int64_t d_in, const PackPtrs &p, int32_t *row_of, hipStream_t s);
+// row_of[i] = row of channel i inside its width group (-1: it stores no row); fills the channel lists.  With
+// n_out > 0 the same launch leaves what launch_segment_offsets would in `seg`.
+int launch_pack_index(const uint8_t *bits, int64_t d_in, const PackPtrs &p, int32_t *row_of, const int32_t *out_idx,
+                      int64_t n_out, int64_t d_out, int32_t *seg, hipStream_t s);
+// The stored format and the error (cmpq_pack_with_error) behind launch_pack_index; `slices` as above.
+int launch_pack_error(const void *W, int dtype, int64_t d_in, int64_t d_out, int64_t ldw, const uint8_t *codes,
+                      const uint8_t *bits, const float *centroids, const PackPtrs &p, const int32_t *row_of,
+                      const int32_t *out_idx, const int32_t *slices, const float *sumsq, double *err_ch,
+                      double *err_total, hipStream_t s);
 
 // Carves aligned pieces out of the caller's workspace; `need` ends up as the total.
 struct WsCarver {

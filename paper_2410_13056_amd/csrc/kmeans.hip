@@ -414,13 +414,12 @@ static size_t ws_kmeans_rows(int64_t d_in) {
     return ws_kmeans_base(d_in) + align_up((size_t)(d_in > 0 ? d_in : 1) * sizeof(int32_t), 256);
 }
 
-// What every call needs: ... | what cmpq_pack_with_error needs when the stored format is asked for and the
-// histogram kernels do not take the input.
+// The least that a call takes: ... | room of cmpq_pack_with_error's size, in which the histogram kernels work a
+// part of the channels at a time.
 static size_t ws_kmeans_least(int64_t d_in) { return ws_kmeans_rows(d_in) + cmpq_ws_pack_with_error(d_in); }
 
 size_t cmpq_ws_kmeans(int64_t d_in, int64_t d_out) {
-    // in the place of the latter, the channels' tables where the histogram kernels run (with less they run
-    // a part of the channels at a time)
+    // in the place of the latter, the tables of all channels where the histogram kernels run
     const size_t least = ws_kmeans_least(d_in), hist = ws_kmeans_rows(d_in) + align_up(kmeans_hist_scratch(d_in, d_out), 256);
     return least > hist ? least : hist;
 }
@@ -492,34 +491,22 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
         if (j.arrangement_use == CMPQ_ARRANGEMENT_KEEP) a.arr_keep = j.arrangement;
         else a.arr_reuse = j.arrangement;
     }
+    int32_t *seg = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + align_up((size_t)d_in, 256));
+    int32_t *row_of = reinterpret_cast<int32_t *>(ws_row_of);
     if (want_format) {
         if (d_out > 1 << 20) return CMPQ_ESHAPE;
         if (const int rc = gather_pack_ptrs(d_in, d_out, j.bit_set, j.n_set, j.counts_host, j.packed, j.chan_idx, j.lut, a.pack))
             return rc;
         if (!hist_takes_it && d_out > 0 && !j.codes) return CMPQ_EINVAL;
-        if (!hist_takes_it && !ragged) {
-            // the general kernels write dense codes; the stored format follows in a pass of its own
-            cmpq_kmeans_job plain = j;
-            plain.bit_set = nullptr, plain.n_set = 0, plain.counts_host = nullptr, plain.packed = nullptr;
-            plain.chan_idx = nullptr, plain.lut = nullptr, plain.sumsq = nullptr, plain.err_ch = nullptr;
-            plain.err_total = nullptr;
-            if (const int rc = cmpq_kmeans_quantize_job(&plain, ws, ws_bytes, stream)) return rc;
-            return cmpq_pack_with_error(j.W, j.dtype, d_in, d_out, j.ldw, j.codes, j.bits, j.centroids, j.bit_set,
-                                        j.n_set, j.counts_host, j.packed, j.chan_idx, j.lut, j.out_idx, j.n_out,
-                                        j.sumsq, j.err_ch, j.err_total, ws_tail, cmpq_ws_pack_with_error(d_in), stream);
-        }
-        int32_t *row_of = reinterpret_cast<int32_t *>(ws_row_of);
-        if (const int rc = launch_pack_index(j.bits, d_in, a.pack, row_of, s)) return rc;
-        a.fused = 1;
+        // the general kernels write dense codes; the stored format follows in a pass of its own
+        a.fused = hist_takes_it || ragged;
         a.row_of = row_of;
         a.err_ch = j.err_ch;
+        if (const int rc = launch_pack_index(j.bits, d_in, a.pack, row_of, j.out_idx, j.n_out, d_out, seg, s)) return rc;
+    } else if (j.n_out > 0) {
+        if (const int rc = launch_segment_offsets(j.out_idx, j.n_out, d_in, d_out, seg, s)) return rc;
     }
-    if (j.n_out > 0) {
-        int32_t *seg = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + align_up((size_t)d_in, 256));
-        const int rc = launch_segment_offsets(j.out_idx, j.n_out, d_in, d_out, seg, s);
-        if (rc != CMPQ_OK) return rc;
-        a.seg = seg;
-    }
+    if (j.n_out > 0) a.seg = seg;
     if (kmeans_fast_eligible(a, j.dtype)) {
         // the bucket kernel takes every channel itself
         // (so does a run from given levels, whichever implementation is named)
@@ -528,18 +515,21 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
             return a.fused ? launch_error_totals(j.err_ch, j.sumsq, d_in, j.err_total, s) : CMPQ_OK;
         }
         a.deferred = static_cast<uint8_t *>(ws);
-        const int rc = launch_kmeans_fast(a, s);
-        if (rc != CMPQ_OK) return rc;
-        return launch_kmeans<__half, false>(a, s);  // only the channels the first kernel deferred
-    }
-    if (ragged) {
+        if (const int rc = launch_kmeans_fast(a, s)) return rc;
+        if (const int rc = launch_kmeans<__half, false>(a, s)) return rc;  // only the channels the first kernel deferred
+    } else if (ragged) {
         a.ragged = 1;
         if (const int rc = launch_kmeans_hist(a, ws_tail, tail_bytes, s)) return rc;
         return a.fused ? launch_error_totals(j.err_ch, j.sumsq, d_in, j.err_total, s) : CMPQ_OK;
+    } else {
+        const bool half = j.dtype == CMPQ_F16;
+        if (const int rc = j.elem_weight ? (half ? launch_kmeans<__half, true>(a, s) : launch_kmeans<float, true>(a, s))
+                                         : (half ? launch_kmeans<__half, false>(a, s) : launch_kmeans<float, false>(a, s)))
+            return rc;
     }
-    if (j.dtype == CMPQ_F16)
-        return j.elem_weight ? launch_kmeans<__half, true>(a, s) : launch_kmeans<__half, false>(a, s);
-    return j.elem_weight ? launch_kmeans<float, true>(a, s) : launch_kmeans<float, false>(a, s);
+    if (!want_format) return CMPQ_OK;
+    return launch_pack_error(j.W, j.dtype, d_in, d_out, j.ldw, j.codes, j.bits, j.centroids, a.pack, row_of, j.out_idx,
+                             a.seg, j.sumsq, j.err_ch, j.err_total, s);
 }
 
 extern "C" int cmpq_kmeans_quantize(const void *W, int dtype, int64_t d_in, int64_t d_out,

@@ -12,9 +12,19 @@ namespace {
 // row_of[i] = row of channel i inside its width group, -1 when it stores no row.  One pass: the
 // flags of up to four widths are scanned together, two 16-bit fields to a word (a step covers
 // 1024 channels, so no field overflows).
+//
+// That is the first workgroup.  Those behind it, if any, find the slices of an ascending list of entries, a
+// channel a lane: the two jobs are 3 us each and share nothing, and a launch of its own cost a layer some 5 us.
 __global__ __launch_bounds__(1024) void pack_index_kernel(const uint8_t *__restrict__ bits,
                                                           int64_t d_in, PackPtrs p,
-                                                          int32_t *__restrict__ row_of) {
+                                                          int32_t *__restrict__ row_of,
+                                                          const int32_t *__restrict__ out_idx, int64_t n_out,
+                                                          int64_t d_out, int32_t *__restrict__ seg) {
+    if (blockIdx.x > 0) {
+        const int64_t i = (int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
+        if (i <= d_in) seg[i] = entries_below(out_idx, n_out, i * d_out);
+        return;
+    }
     __shared__ uint32_t scan[34];
     uint32_t run[4] = {0, 0, 0, 0};
     for (int64_t base = 0; base < d_in; base += blockDim.x) {
@@ -302,8 +312,10 @@ int gather_pack_ptrs(int64_t d_in, int64_t d_out, const int32_t *bit_set, int n_
     return CMPQ_OK;
 }
 
-int launch_pack_index(const uint8_t *bits, int64_t d_in, const PackPtrs &p, int32_t *row_of, hipStream_t s) {
-    pack_index_kernel<<<1, 1024, 0, s>>>(bits, d_in, p, row_of);
+int launch_pack_index(const uint8_t *bits, int64_t d_in, const PackPtrs &p, int32_t *row_of, const int32_t *out_idx,
+                      int64_t n_out, int64_t d_out, int32_t *seg, hipStream_t s) {
+    const unsigned slices = n_out > 0 ? (unsigned)cdiv(d_in + 1, 1024) : 0u;
+    pack_index_kernel<<<1 + slices, 1024, 0, s>>>(bits, d_in, p, row_of, out_idx, n_out, d_out, seg);
     CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
 }
@@ -326,7 +338,7 @@ extern "C" int cmpq_pack(const uint8_t *codes, int64_t d_in, int64_t d_out, cons
         return CMPQ_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     int32_t *row_of = static_cast<int32_t *>(ws);
-    pack_index_kernel<<<1, 1024, 0, s>>>(bits, d_in, p, row_of);
+    pack_index_kernel<<<1, 1024, 0, s>>>(bits, d_in, p, row_of, nullptr, 0, d_out, nullptr);
     const int vec_ok = reinterpret_cast<uintptr_t>(codes) % 16 == 0 && d_out % 16 == 0;
     int64_t gy = cdiv(cdiv(d_out, 32), 256);
     if (gy < 1) gy = 1;
@@ -335,6 +347,41 @@ extern "C" int cmpq_pack(const uint8_t *codes, int64_t d_in, int64_t d_out, cons
     pack_codes_kernel<<<grid, 256, 0, s>>>(codes, d_out, bits, centroids, row_of, p, vec_ok);
     CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
+}
+
+int launch_pack_error(const void *W, int dtype, int64_t d_in, int64_t d_out, int64_t ldw, const uint8_t *codes,
+                      const uint8_t *bits, const float *centroids, const PackPtrs &p, const int32_t *row_of,
+                      const int32_t *out_idx, const int32_t *slices, const float *sumsq, double *err_ch,
+                      double *err_total, hipStream_t s) {
+    const int esz = dtype == CMPQ_F16 ? 2 : 4;
+    const bool one_pass = d_out > 0 && d_out % 32 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
+                          (ldw * esz) % 16 == 0 && reinterpret_cast<uintptr_t>(codes) % 16 == 0;
+    if (one_pass) {
+        const size_t lds = (size_t)(d_out / 32) * 4;
+        cmpq_timing_before(CMPQ_KERNEL_PACK_ERROR, s);
+        if (dtype == CMPQ_F16)
+            pack_error_kernel<__half><<<(unsigned)d_in, kPeT, lds, s>>>(
+                static_cast<const __half *>(W), d_out, ldw, codes, bits, centroids, row_of, p, out_idx, slices,
+                err_ch);
+        else
+            pack_error_kernel<float><<<(unsigned)d_in, kPeT, lds, s>>>(
+                static_cast<const float *>(W), d_out, ldw, codes, bits, centroids, row_of, p, out_idx, slices,
+                err_ch);
+        cmpq_timing_after(CMPQ_KERNEL_PACK_ERROR, s);
+        CMPQ_LAUNCH_CHECK();
+    } else {  // ragged or unaligned rows: the kernels of the two separate calls
+        const int vec_ok = reinterpret_cast<uintptr_t>(codes) % 16 == 0 && d_out % 16 == 0;
+        int64_t gy = cdiv(cdiv(d_out, 32), 256);
+        if (gy < 1) gy = 1;
+        if (gy > 64) gy = 64;
+        pack_codes_kernel<<<dim3((unsigned)d_in, (unsigned)gy), 256, 0, s>>>(codes, d_out, bits, centroids,
+                                                                              row_of, p, vec_ok);
+        CMPQ_LAUNCH_CHECK();
+        if (const int rc = launch_dequant_error_rows(W, dtype, d_in, d_out, ldw, centroids, codes, bits,
+                                                     out_idx, slices, err_ch, s))
+            return rc;
+    }
+    return launch_error_totals(err_ch, sumsq, d_in, err_total, s);
 }
 
 size_t cmpq_ws_pack_with_error(int64_t d_in) {
@@ -364,42 +411,10 @@ extern "C" int cmpq_pack_with_error(const void *W, int dtype, int64_t d_in, int6
             return CMPQ_EWORKSPACE;
         int32_t *row_of = static_cast<int32_t *>(ws);
         int32_t *seg = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + align_up((size_t)d_in * sizeof(int32_t), 256));
-        pack_index_kernel<<<1, 1024, 0, s>>>(bits, d_in, p, row_of);
-        CMPQ_LAUNCH_CHECK();
-        const int32_t *slices = nullptr;
-        if (n_out > 0) {
-            const int rc = launch_segment_offsets(out_idx, n_out, d_in, d_out, seg, s);
-            if (rc != CMPQ_OK) return rc;
-            slices = seg;
-        }
-        const int esz = dtype == CMPQ_F16 ? 2 : 4;
-        const bool one_pass = d_out > 0 && d_out % 32 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
-                              (ldw * esz) % 16 == 0 && reinterpret_cast<uintptr_t>(codes) % 16 == 0;
-        if (one_pass) {
-            const size_t lds = (size_t)(d_out / 32) * 4;
-            cmpq_timing_before(CMPQ_KERNEL_PACK_ERROR, s);
-            if (dtype == CMPQ_F16)
-                pack_error_kernel<__half><<<(unsigned)d_in, kPeT, lds, s>>>(
-                    static_cast<const __half *>(W), d_out, ldw, codes, bits, centroids, row_of, p, out_idx, slices,
-                    err_ch);
-            else
-                pack_error_kernel<float><<<(unsigned)d_in, kPeT, lds, s>>>(
-                    static_cast<const float *>(W), d_out, ldw, codes, bits, centroids, row_of, p, out_idx, slices,
-                    err_ch);
-            cmpq_timing_after(CMPQ_KERNEL_PACK_ERROR, s);
-            CMPQ_LAUNCH_CHECK();
-        } else {  // ragged or unaligned rows: the kernels of the two separate calls
-            const int vec_ok = reinterpret_cast<uintptr_t>(codes) % 16 == 0 && d_out % 16 == 0;
-            int64_t gy = cdiv(cdiv(d_out, 32), 256);
-            if (gy < 1) gy = 1;
-            if (gy > 64) gy = 64;
-            pack_codes_kernel<<<dim3((unsigned)d_in, (unsigned)gy), 256, 0, s>>>(codes, d_out, bits, centroids,
-                                                                                  row_of, p, vec_ok);
-            CMPQ_LAUNCH_CHECK();
-            if (const int rc = launch_dequant_error_rows(W, dtype, d_in, d_out, ldw, centroids, codes, bits,
-                                                         out_idx, slices, err_ch, s))
-                return rc;
-        }
+        const int32_t *slices = n_out > 0 ? seg : nullptr;
+        if (const int rc = launch_pack_index(bits, d_in, p, row_of, out_idx, n_out, d_out, seg, s)) return rc;
+        return launch_pack_error(W, dtype, d_in, d_out, ldw, codes, bits, centroids, p, row_of, out_idx, slices, sumsq,
+                                 err_ch, err_total, s);
     }
     return launch_error_totals(err_ch, sumsq, d_in, err_total, s);
 }

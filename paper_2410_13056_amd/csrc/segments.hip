@@ -10,13 +10,7 @@ __global__ __launch_bounds__(256) void segment_offsets_kernel(const int32_t *__r
                                                               int32_t *__restrict__ seg) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i > d_in) return;
-    const int64_t first = i * d_out;
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)idx[mid] < first) lo = mid + 1; else hi = mid;
-    }
-    seg[i] = (int32_t)lo;
+    seg[i] = entries_below(idx, n, i * d_out);
 }
 
 }  // namespace
