@@ -174,7 +174,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle alone: as torch.cuda.current_stream().cuda_stream each call takes the host about 2 us longer
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _rows(t: torch.Tensor):
