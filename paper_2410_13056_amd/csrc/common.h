@@ -98,9 +98,37 @@ __device__ __forceinline__ int wave_index() {
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CMPQ_WAVE));
 }
 
+// Value of the lane `N` above inside a row of 16 lanes (0 past the row's end).
+template <int N>
+__device__ __forceinline__ double row_up_f64(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x100 + N, 0xF, 0xF, true);  // row_shl:N
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x100 + N, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double join_f64(uint32_t lo, uint32_t hi) {
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sum over the wavefront, valid in lane 0: lanes 32 apart first, then 16, 8, 4, 2 and 1.  Row swaps and the
+// DPP path: as six exchanges through LDS it took some 900 cycles.  Called by all lanes.
 __device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s, CMPQ_WAVE);
+    {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v = join_f64(lo[0], hi[0]) + join_f64(lo[1], hi[1]);
+    }
+    {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v = join_f64(lo[0], hi[0]) + join_f64(lo[1], hi[1]);
+    }
+    v += row_up_f64<8>(v);
+    v += row_up_f64<4>(v);
+    v += row_up_f64<2>(v);
+    v += row_up_f64<1>(v);
     return v;
 }
 

@@ -16,6 +16,10 @@
 // table in LDS, the table is reduced per cell in a fixed order, and the new level is
 // the fp64 quotient rounded once to fp32.  For fp16 inputs with 0/1 weights these
 // sums are exact, so the result does not depend on the lane layout.
+//
+// A short channel is bound by the chain of one round, not by its weights (256 channels of 512 fp32 weights, a
+// channel a CU: 33 us for 10 rounds; 40 with the fp64 sums taken through LDS exchanges, the counts summed in fp64
+// as well and the start's prefixes read from LDS for every weight).
 #include "kmeans_args.h"
 
 namespace {
@@ -168,17 +172,20 @@ __device__ void lloyd_rounds(const KmArgs &a, int64_t i, KmSmall &sm, const TW *
         }
         __syncthreads();
         for (int p = wave; p < K; p += kWavesPerBlock) {
-            double s = 0.0, m = 0.0;
+            double s = 0.0;
+            MassT m = (MassT)0;
 #pragma unroll
             for (int r = 0; r < kWavesPerBlock; ++r) {
                 s += sums[p * kT + r * 64 + lane];
-                m += (double)mass[p * kT + r * 64 + lane];
+                m += mass[p * kT + r * 64 + lane];
             }
             s = wave_sum_f64(s);
-            m = wave_sum_f64(m);
+            double m_all;
+            if constexpr (WEIGHTED) m_all = wave_sum_f64(m);
+            else m_all = (double)(uint32_t)__builtin_amdgcn_readlane((int)wave_scan_incl_u32(m), CMPQ_WAVE - 1);
             if (lane == 0) {
                 sm.tot_sum[p] = s;
-                sm.tot_mass[p] = m;
+                sm.tot_mass[p] = m_all;
             }
         }
         __syncthreads();
@@ -215,19 +222,29 @@ __device__ void quantile_start(KmSmall &sm, int K, int d_out, const TW *xs, cons
         }
         for (int b = tid; b < K * 256; b += kT) hist[b] = 0;
         __syncthreads();
+        // the leading ranks' prefixes in registers: read inside the loop, each is a trip to LDS per weight
+        uint32_t lead = 0, prefix_of[CMPQ_KMAX];
+#pragma unroll
+        for (int j = 0; j < CMPQ_KMAX; ++j) {
+            prefix_of[j] = j < K ? sm.q_prefix[j] : 0u;
+            lead |= (j < K && sm.q_leader[j] == j ? 1u : 0u) << j;
+        }
         for (int o = tid; o < d_out; o += kT) {
             if (!((incl[o >> 5] >> (o & 31)) & 1u)) continue;
             const uint32_t key = Elem<TW>::key(xs[o]);
             const uint32_t hi = shift + 8 >= kBits ? 0u : key >> (shift + 8);
             const uint32_t digit = (key >> shift) & 255u;
-            for (int j = 0; j < K; ++j)
-                if (sm.q_leader[j] == j && sm.q_prefix[j] == hi) atomicAdd(&hist[j * 256 + digit], 1u);
+            int at = -1;  // leading prefixes differ: at most one is the weight's
+#pragma unroll
+            for (int j = 0; j < CMPQ_KMAX; ++j)
+                if (((lead >> j) & 1u) && prefix_of[j] == hi) at = j;
+            if (at >= 0) atomicAdd(&hist[at * 256 + digit], 1u);
         }
         __syncthreads();
         // 16 lanes per rank, 16 digits each: where the running count passes the rank.  (One lane
         // per rank and a chain of up to 255 dependent LDS reads in each of the four passes took
         // more than half the time of a short fp32 channel: 256 channels of 512 weights, 10 rounds,
-        // took 94 us and take 40.)
+        // took 94 us instead of 40.)
         static_assert(kT == 16 * CMPQ_KMAX, "16 lanes for every rank");
         const int j = tid >> 4, sub = tid & 15;
         const uint4 *h = reinterpret_cast<const uint4 *>(hist + (j < K ? sm.q_leader[j] : 0) * 256) + 4 * sub;
