@@ -1253,6 +1253,11 @@ int allow_lds(Kern kern, size_t lds) {
 // 100, 4096 x 4096 69 / 63 / 76, 28672 x 8192 552 / 459 / 456, 8192 x 28672 433 / 395 / 360.
 template <int T>
 constexpr int kRows = T == 64 ? 1 : (T < 512 ? 2 : 4);
+// Up to this many channels the rounds leave SIMDs without a wavefront (there are 1024 of them, and a wavefront
+// takes 4 / R channels), and a round's own length is what counts: twice the rows then.  First and final
+// quantization, us: 1024 x 8192 52 + 74 -> 40 + 66, 1024 x 4096 38 + 58 -> 33 + 57, 2048 x 4608 48 + 74 -> 45 + 73,
+// 2048 x 2048 43 + 68 -> 40 + 64; past it the order turns: 3000 x 4099 69 + 96 with 2 rows, 82 + 113 with 4.
+constexpr int64_t kFewChannels = 2048;
 template <int R, int LB, int AHEAD>
 int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *tables, int64_t stride,
                    const unsigned char *removed, ChannelFinal *fin, hipStream_t s) {
@@ -1266,7 +1271,7 @@ int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *t
 }
 
 // One quantization, a run of channels at a time (as many as the scratch holds tables for).
-template <int G, int T, int LB>
+template <int G, int T, int LB, int R = kRows<T>>
 int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes, hipStream_t s) {
     const int64_t stride = (int64_t)table_bytes(a.d_out, LB);
     const bool want_codes = a.codes || a.fused;
@@ -1299,7 +1304,7 @@ int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes
             kern<<<(unsigned)n, T, lds, s>>>(a, i0, tables, stride);
             CMPQ_LAUNCH_CHECK();
         }
-        if (const int rc = launch_rounds<kRows<T>, LB, G == 16 ? 8 : 4>(a, i0, n, src, stride, rem_tables ? side : nullptr, fin, s)) return rc;
+        if (const int rc = launch_rounds<R, LB, G == 16 ? 8 : 4>(a, i0, n, src, stride, rem_tables ? side : nullptr, fin, s)) return rc;
         if (want_codes) {
             auto kern = a.fused ? (a.ragged ? kmeans_code_kernel<G, T, LB, true, true> : kmeans_code_kernel<G, T, LB, true, false>)
                                 : (a.ragged ? kmeans_code_kernel<G, T, LB, false, true> : kmeans_code_kernel<G, T, LB, false, false>);
@@ -1377,6 +1382,11 @@ int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hip
     if (!table_shape(a.d_out, T, G, LB)) return CMPQ_ESHAPE;
     unsigned char *sc = static_cast<unsigned char *>(scratch);
     if (G == 16) return launch_variant<16, 512, CMPQ_LB512>(a, sc, scratch_bytes, s);
+    if (a.d_in <= kFewChannels && T < 512) {
+        if (T == 256) return launch_variant<8, 256, CMPQ_LB256, 4>(a, sc, scratch_bytes, s);
+        if (T == 128) return launch_variant<4, 256, 7, 4>(a, sc, scratch_bytes, s);  // 2304 weights: 42 us, 44 on 128 lanes
+        if (G == 8) return launch_variant<8, 64, 7, 2>(a, sc, scratch_bytes, s);
+    }
     if (G == 8) {
         switch (T) {
             case 512: return launch_variant<8, 512, CMPQ_LB512>(a, sc, scratch_bytes, s);

@@ -104,3 +104,33 @@ def test_tables_of_another_row_length_are_flagged(env):
     B.kmeans_quantize(_dev(W[:, :2048]), db, None, 0, None, 3, cent, codes, ws, st, arrangement=tables,
                       arrangement_use=B.ARRANGEMENT_REUSE)
     assert st.item() == B.STATUS_ARRANGEMENT and not codes.any() and not cent[:, :8].any()
+
+
+@pytest.mark.parametrize("d_out", [1028, 1999, 2052, 4095, 4100, 8192])
+def test_many_channels_get_the_bits_of_few(env, d_out):
+    """2049 channels in one call, and the same rows as 2048 and 1: other numbers of lanes per channel."""
+    B, ws = env["B"], env["ws"]
+    g = torch.Generator(device=DEV).manual_seed(d_out)
+    d_in = 2049
+    W = (torch.randn(d_in, d_out, generator=g, device=DEV) * 0.02).half()
+    bits = torch.randint(1, 5, (d_in,), generator=g, device=DEV).to(torch.uint8)
+    excl = torch.arange(0, d_in * d_out, 97, dtype=torch.int32, device=DEV)
+
+    def run(lo, hi, out_idx, use, tables):
+        cent = torch.full((hi - lo, 16), 7.0, device=DEV)
+        codes = torch.full((hi - lo, d_out), 255, dtype=torch.uint8, device=DEV)
+        B.kmeans_quantize(W[lo:hi], bits[lo:hi], out_idx, out_idx.numel() if out_idx is not None else 0, None, 4, cent, codes,
+                          ws, arrangement=tables, arrangement_use=use)
+        return cent, codes
+
+    def both(lo, hi):
+        e = excl[(excl >= lo * d_out) & (excl < hi * d_out)] - lo * d_out
+        n = B.arrangement_bytes(hi - lo, d_out) if d_out % 4 == 0 else 0
+        tables = torch.empty(n, dtype=torch.uint8, device=DEV) if n else None
+        first = run(lo, hi, None, B.ARRANGEMENT_KEEP if n else B.ARRANGEMENT_NONE, tables)
+        final = run(lo, hi, e, B.ARRANGEMENT_REUSE if n else B.ARRANGEMENT_NONE, tables)
+        return first + final + run(lo, hi, e, B.ARRANGEMENT_NONE, None)
+
+    whole, head, tail = both(0, d_in), both(0, 2048), both(2048, d_in)
+    for w, h, t in zip(whole, head, tail):
+        assert torch.equal(w, torch.cat([h, t]))
