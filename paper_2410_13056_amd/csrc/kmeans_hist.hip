@@ -702,7 +702,11 @@ __global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int6
                                                                  const unsigned char *removed, ChannelFinal *fin) {
     const int lane = threadIdx.x, p = lane & 15;
     const uint32_t r = (uint32_t)((lane >> 4) & (R - 1));
-    const int64_t at = (int64_t)blockIdx.x * (4 / R) + (lane >> 4) / R;
+    // Channels 8 apart: workgroups go to the 8 XCDs in turn, and a channel's tables are best read on the XCD that
+    // built them, whose L2 may still hold them.  First and final quantization, us, neighbouring channels together
+    // and 8 apart: 3001 x 1031 51 + 69 and 45 + 63, 3001 x 2049 58 + 79 and 52 + 72, 28672 x 8192 459 + 606 and
+    // 455 + 595.
+    const int64_t at = (int64_t)(blockIdx.x >> 3) * (8 * (4 / R)) + (blockIdx.x & 7) + (lane >> 4) / R * 8;
     const bool exists = at < n_chan;
     const int64_t j = exists ? at : n_chan - 1, i = i0 + j;
     const int b = exists ? a.bits[i] : 0;
@@ -1261,7 +1265,7 @@ constexpr int64_t kFewChannels = 2048;
 template <int R, int LB, int AHEAD>
 int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *tables, int64_t stride,
                    const unsigned char *removed, ChannelFinal *fin, hipStream_t s) {
-    const unsigned grid = (unsigned)cdiv(n, 4 / R);
+    const unsigned grid = (unsigned)cdiv(n, 8 * (4 / R)) * 8;
     const size_t lds = 4 / R * (removed ? ChannelView<LB, true>::kBytes : ChannelView<LB, false>::kBytes);
     auto kern = removed ? kmeans_rounds_kernel<R, LB, AHEAD, true> : kmeans_rounds_kernel<R, LB, AHEAD, false>;
     if (const int rc = allow_lds(kern, lds)) return rc;
