@@ -136,11 +136,18 @@ def _histogram_kernel_takes(Wt: torch.Tensor) -> bool:
     return B.arrangement_bytes(d_in, d_out) > 0
 
 
+# Up to this many weights a channel the final K-means builds its tables again: taking the removed entries from
+# kept ones means a second set of tables per channel, which costs more than counting so few weights twice.  Final
+# quantization from kept and from new tables, us: 8192 x 1024 118 and 94, 8192 x 2048 130 and 116, 4096 x 2048 82
+# and 82, 4096 x 4096 93 and 98, 28672 x 8192 595 and 692.
+SHORT_CHANNEL = 2048
+
+
 def _shared_tables(Wt: torch.Tensor) -> Optional[torch.Tensor]:
     """The buffer through which the preliminary K-means of a layer hands its per-channel tables
     to the final one (`cmpq_kmeans_job.arrangement`), or None where the histogram kernel would
-    not take the input."""
-    if not _histogram_kernel_takes(Wt):
+    not take the input or the channels are short."""
+    if not _histogram_kernel_takes(Wt) or Wt.shape[1] <= SHORT_CHANNEL:
         return None
     return torch.empty(B.arrangement_bytes(*Wt.shape), dtype=torch.uint8, device=Wt.device)
 
@@ -235,9 +242,10 @@ def quantize_layer(W: torch.Tensor, sumsq: torch.Tensor, bit_set: Sequence[int],
     the same widths, so a block ranks and allocates once per input.
 
     ``share_tables`` (on by default): the preliminary K-means leaves its per-channel tables for
-    the final one (`cmpq_kmeans_job.arrangement`), which then does not build them again.  Same
+    the final one (`cmpq_kmeans_job.arrangement`), which then does not build them again (for
+    channels of more than 2048 weights; shorter ones are the faster built anew).  Same
     results, one buffer of about `d_in * (d_out + 8 KiB)` bytes more while the layer is in work;
-    measured, the final pass is 10 % shorter and the whole step 2 %.
+    measured, the final pass is 14 to 34 % shorter on channels of 8192 and 28 672 weights.
 
     ``iters_final_from_prelim`` (a variant; the paper names no start for either K-means of
     Sec. 3.2.2): the final quantization starts from the levels of the preliminary one and runs
