@@ -44,37 +44,12 @@ __device__ __forceinline__ void bucket_affine(uint32_t b, long long &q0, long lo
     q0 = (h & 0x8000u) ? -mag : mag;
 }
 
-// Sum of x*2^24 over n keys of bucket b whose places add up to l (n <= 32768, places <= 127):
-// (n * q0 + step * l) of bucket_affine, formed as a 32-bit product and one 64-bit shift
-// (|mantissa * n| < 2^26 and l < 2^23, so their sum fits 32 bits).
-template <int LB>
-__device__ __forceinline__ long long bucket_sum(uint32_t b, uint32_t n, uint32_t l) {
-    const uint32_t h = half_of_key(b << LB);
-    const uint32_t e = (h >> 10) & 31u;
-    const uint32_t sh = (e > 1 ? e : 1) - 1;
-    const int mant = (int)((e ? 1024u : 0u) + (h & 1023u));
-    const int t = __mul24((h & 0x8000u) ? -mant : mant, (int)n) + (int)l;
-    return (long long)((unsigned long long)(long long)t << sh);
-}
-
 // Value of the lane below / above inside a row of 16 lanes; 0 at the row's edge.
 __device__ __forceinline__ uint32_t row_from_below(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);  // row_shr:1
 }
 __device__ __forceinline__ uint32_t row_from_above(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x101, 0xF, 0xF, true);  // row_shl:1
-}
-
-// Sum over aligned groups of L lanes (L a power of two, 4..64); every lane gets its group's sum.
-template <int L>
-__device__ __forceinline__ uint32_t group_sum(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
-    if constexpr (L >= 8) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);  // row_half_mirror
-    if constexpr (L >= 16) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false); // row_mirror
-    if constexpr (L >= 32) v += __shfl_xor(v, 16, CMPQ_WAVE);
-    if constexpr (L >= 64) v += __shfl_xor(v, 32, CMPQ_WAVE);
-    return v;
 }
 
 __device__ __forceinline__ unsigned long long wave_scan_incl_u64(unsigned long long v) {
