@@ -31,11 +31,11 @@ FP32_PEAK_TFLOPS = 157.3
 ISSUE_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 HBM_PEAK_GBS = 8000.0
 # Constants taken from the kept rocprofv3 --pmc summaries (bench.py cannot collect counters):
-# mean HBM bytes per k-means launch (FETCH_SIZE + WRITE_SIZE scaled by a plain copy of known
-# size) and mean vector-ALU instructions per k-means launch (SQ_INSTS_VALU, per wavefront).
-KMEANS_TRAFFIC_BYTES = {"block70b": 583.6e6}
-KMEANS_VALU_WAVE_INSTS_PER_STEP = {"block70b": 1.87e9}     # 14 launches
-KMEANS_COUNTERS_FILE = "profiles/kmeans_bucket_block70b_counters.txt"
+# mean HBM bytes per k-means call, all its kernels (FETCH_SIZE + WRITE_SIZE scaled by a plain copy of known
+# size) and vector-ALU instructions of the k-means calls of a step (SQ_INSTS_VALU, per wavefront).
+KMEANS_TRAFFIC_BYTES = {"block70b": 778.8e6}
+KMEANS_VALU_WAVE_INSTS_PER_STEP = {"block70b": 1.302e9}     # 14 calls
+KMEANS_COUNTERS_FILE = "profiles/kmeans_block70b_counters.txt"
 
 
 def measured_shader_clock(B, dev):
@@ -422,7 +422,7 @@ def main():
     avg_launch_s = ms_km / 1e3 / max(n_km, 1)
     achieved = flops / max(n_km, 1) / avg_launch_s / 1e12
     ms_km_timed = per_step(stages, "kmeans_prelim", args.steps)[1] + per_step(stages, "kmeans_final", args.steps)[1]
-    roofline = {"kernel": "kmeans_bucket_kernel", "bound": "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS,
+    roofline = {"kernel": "kmeans_build/removed/rounds/code_kernel", "bound": "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
                 "traffic": KMEANS_TRAFFIC_BYTES.get(wl.name),
                 "what": "credited work (per weight and round K-1 compares + 2 accumulations, K-1 for the coding "

@@ -239,7 +239,8 @@ int cmpq_extract_outliers(int mode, int score, int scope, const float *sumsq, co
  * index.  Update: level = sum(m*x)/sum(m) of its members, accumulated in fp64 and rounded
  * once to fp32; a level without members keeps its value.  -0.0 reads as +0.0.
  * Limits: d_out <= 32768 for CMPQ_F16, <= 16384 for CMPQ_F32 (CMPQ_ESHAPE beyond).
- * Workspace: CMPQ_OP_KMEANS.  Status: CMPQ_STATUS_NONFINITE (the levels and codes of a channel
+ * Workspace: CMPQ_OP_KMEANS (room for the per-channel tables of all channels; a smaller one works
+ * through the channels in parts).  Status: CMPQ_STATUS_NONFINITE (the levels and codes of a channel
  * that holds a non-finite weight, or is given a non-finite starting level, are unspecified, its
  * codes stay below K; the other channels are not affected).
  */
@@ -347,10 +348,10 @@ typedef struct cmpq_kmeans_job {
 int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, size_t ws_bytes, void *stream);
 
 /*
- * Introspection for host-side checks: the launch shape the histogram K-means kernel uses for
- * fp16 channels of d_out weights (d_out a multiple of 4, at most 32768).  shape [6], host, out:
- * lanes per workgroup, groups of 4 weights per lane, low key bits that name the place inside a
- * bucket (64 or 128 places; 2^(16 - bits) buckets), bytes of the per-channel place array, bytes
+ * Introspection for host-side checks: the launch shape the histogram K-means builds the tables of
+ * many fp16 channels of d_out weights with (few channels get more lanes; d_out a multiple of 4, at
+ * most 32768).  shape [6], host, out: lanes per workgroup, groups of 4 weights per lane, low key
+ * bits that name the place inside a bucket (64 or 128 places; 2^(16 - bits) buckets), bytes of the per-channel place array, bytes
  * of dynamic LDS per workgroup, bytes of static LDS per workgroup.  Launches nothing.
  * CMPQ_EINVAL for a null pointer or a length that is no positive multiple of 4, CMPQ_ESHAPE
  * beyond the limit.

@@ -131,7 +131,7 @@ def count_ppm(ppm: int, n: int) -> int:
 
 def kmeans_launch_shape(d_out: int):
     """(lanes, groups of 4 per lane, place bits, place-array bytes, dynamic LDS, static LDS) of the
-    histogram K-means kernel for channels of `d_out` fp16 weights."""
+    histogram K-means table build for channels of `d_out` fp16 weights, many of them (few get more lanes)."""
     shape = (_i64 * 6)()
     _check(lib().cmpq_kmeans_launch_shape(int(d_out), shape), "cmpq_kmeans_launch_shape")
     return tuple(int(v) for v in shape)

@@ -525,7 +525,7 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
     }
     if (j.n_out > 0) a.seg = seg;
     if (kmeans_fast_eligible(a, j.dtype)) {
-        // the bucket kernel takes every channel itself
+        // the bucket kernels take every channel themselves
         // (so does a run from given levels, whichever implementation is named)
         if (hist_takes_it) {
             if (const int rc = launch_kmeans_hist(a, ws_tail, tail_bytes, s)) return rc;

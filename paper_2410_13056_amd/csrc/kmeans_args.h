@@ -20,7 +20,7 @@ struct KmArgs {
     uint8_t *deferred;
     // seg[i]..seg[i+1]: the slice of out_idx inside channel i (null when n_out is 0).
     const int32_t *seg;
-    // Stored format and error written by the coding pass of the bucket kernel (Sec. 5.1;
+    // Stored format and error written by the coding pass of the bucket kernels (Sec. 5.1;
     // App. B.3) instead of by a pass of their own: where the rows go, the row of each channel
     // inside its width group, and the per-channel squared error.  Unused unless `fused`.
     int fused;
@@ -30,7 +30,7 @@ struct KmArgs {
     PackPtrs pack;
     const int32_t *row_of;
     double *err_ch;
-    // The bucket kernel's per-channel arrangement (bucket table and place array built from all
+    // The bucket kernels' per-channel arrangement (bucket table and place array built from all
     // weights of a channel): written for a later run (arr_keep) or taken from an earlier one
     // instead of building it again (arr_reuse).  arr_stride bytes per channel.
     void *arr_keep;
