@@ -349,14 +349,23 @@ int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, size_t ws_byt
 
 /*
  * Introspection for host-side checks: the launch shape the histogram K-means builds the tables of
- * many fp16 channels of d_out weights with (few channels get more lanes; d_out a multiple of 4, at
- * most 32768).  shape [6], host, out: lanes per workgroup, groups of 4 weights per lane, low key
- * bits that name the place inside a bucket (64 or 128 places; 2^(16 - bits) buckets), bytes of the per-channel place array, bytes
- * of dynamic LDS per workgroup, bytes of static LDS per workgroup.  Launches nothing.
- * CMPQ_EINVAL for a null pointer or a length that is no positive multiple of 4, CMPQ_ESHAPE
- * beyond the limit.
+ * many fp16 channels of d_out weights with (d_out a multiple of 4, at most 32768).  shape [6],
+ * host, out: lanes per workgroup, groups of 4 weights per lane, low key bits that name the place
+ * inside a bucket (64 or 128 places; 2^(16 - bits) buckets), bytes of the per-channel place array,
+ * most bytes of dynamic LDS per workgroup (with entries removed), bytes of static LDS.  Launches
+ * nothing.  CMPQ_EINVAL for a null pointer or a length that is no positive multiple of 4,
+ * CMPQ_ESHAPE beyond the limit.
  */
 int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape);
+
+/*
+ * The same for d_in channels of any length (few channels get more lanes).  shape [8]: as above, then
+ * the bytes of LDS that the place array lies in, which also hold the bucket counts (8 bytes a
+ * bucket) where they are taken again in 64 bits, and the bits of a bucket's 32-bit word
+ * that its sum of places has: they are taken again when the sum of some bucket reaches 2^bits.
+ * CMPQ_EINVAL for a null pointer, no channels or no weights, CMPQ_ESHAPE beyond the limit.
+ */
+int cmpq_kmeans_build_shape(int64_t d_in, int64_t d_out, int64_t *shape);
 
 /*
  * Sec. 5.1 / Fig. 4, the stored format: one code matrix per width.  For j < n_set and

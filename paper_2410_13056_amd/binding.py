@@ -40,7 +40,7 @@ EXPORTS = ("cmpq_workspace_bytes", "cmpq_strerror", "cmpq_count_ppm", "cmpq_act_
            "cmpq_gather_channels", "cmpq_outliers_by_column", "cmpq_lut_matvec", "cmpq_act_stats_norm",
            "cmpq_rtn_quantize", "cmpq_select_by_width", "cmpq_lut_matvec_group", "cmpq_lut4_quantize",
            "cmpq_pack_with_error", "cmpq_time_kernel", "cmpq_act_stats_static", "cmpq_kmeans_launch_shape",
-           "cmpq_shader_clock_probe", "cmpq_lut_matvec_group_fp16acc")
+           "cmpq_shader_clock_probe", "cmpq_lut_matvec_group_fp16acc", "cmpq_kmeans_build_shape")
 
 _i64, _i32, _int, _vp, _dbl, _sz = (ctypes.c_int64, ctypes.c_int32, ctypes.c_int, ctypes.c_void_p,
                                     ctypes.c_double, ctypes.c_size_t)
@@ -103,6 +103,7 @@ def lib() -> ctypes.CDLL:
         L.cmpq_kmeans_quantize_job.argtypes = [ctypes.POINTER(KmeansJob), _vp, _sz, _vp]
         L.cmpq_time_kernel.argtypes = [_int, _vp, _vp]
         L.cmpq_kmeans_launch_shape.argtypes = [_i64, _vp]
+        L.cmpq_kmeans_build_shape.argtypes = [_i64, _i64, _vp]
         L.cmpq_shader_clock_probe.argtypes = [_int, _int, _vp, _vp, _vp]
         L.cmpq_act_stats_static.argtypes = [_vp, _int, _i64, _i64, _i64, _vp, _vp, _int, _vp, _vp]
         L.cmpq_act_stats_norm.argtypes = [_vp, _int, _i64, _i64, _i64, _int, _vp, _vp, _int, _vp, _sz, _vp, _vp]
@@ -131,9 +132,17 @@ def count_ppm(ppm: int, n: int) -> int:
 
 def kmeans_launch_shape(d_out: int):
     """(lanes, groups of 4 per lane, place bits, place-array bytes, dynamic LDS, static LDS) of the
-    histogram K-means table build for channels of `d_out` fp16 weights, many of them (few get more lanes)."""
+    histogram K-means table build for many channels of `d_out` fp16 weights."""
     shape = (_i64 * 6)()
     _check(lib().cmpq_kmeans_launch_shape(int(d_out), shape), "cmpq_kmeans_launch_shape")
+    return tuple(int(v) for v in shape)
+
+
+def kmeans_build_shape(d_in: int, d_out: int):
+    """`kmeans_launch_shape` for `d_in` channels of any length, then the bytes of LDS the place array lies in and
+    the bits of a bucket's word that hold its sum of places."""
+    shape = (_i64 * 8)()
+    _check(lib().cmpq_kmeans_build_shape(int(d_in), int(d_out), shape), "cmpq_kmeans_build_shape")
     return tuple(int(v) for v in shape)
 
 

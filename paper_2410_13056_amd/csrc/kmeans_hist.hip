@@ -136,8 +136,24 @@ __device__ __forceinline__ uint32_t elem_key(const uint32_t (&keys)[2 * G], int 
 // sum of places`.  In 32 bits the sum of a bucket may run over into its count (channels of more than
 // 4096 weights); every such carry makes the counts add up to more than the weights, which is how the
 // caller finds out that it has to count again in 64 bits.
-template <int T>
-constexpr int count_shift() { return T >= 512 ? 16 : (T == 256 ? 18 : (T == 128 ? 19 : 20)); }
+//
+// Low bits of the word that the sum of places has: the count's need room for all 4 * G * T weights that a
+// workgroup can take.
+template <int G, int T>
+constexpr int count_shift() {
+    int shift = 31;
+    for (int n = 4 * G * T; n > 1; n >>= 1) --shift;
+    return shift;
+}
+template <int G, int T, int LB>
+constexpr bool kMayCarry = (int64_t)4 * G * T * ((1 << LB) - 1) >= (int64_t)1 << count_shift<G, T>();
+// LDS of the place array.  The 64-bit count lies there before the places do, and the bitmap behind it has to
+// outlive that count.
+template <int G, int T, int LB>
+__host__ __device__ inline size_t place_area_bytes(int64_t d_out) {
+    const size_t arr = bucket_arr_bytes(d_out, LB), wide = kMayCarry<G, T, LB> ? (size_t)8 << (16 - LB) : 0;
+    return arr > wide ? arr : wide;
+}
 template <int G, int T, int LB, bool MASKED, int kShift, typename Word>
 __device__ __forceinline__ void count_buckets(const uint32_t (&keys)[2 * G], const uint32_t *removed, Word *table,
                                               int tid, int n_groups) {
@@ -254,7 +270,7 @@ __device__ __forceinline__ uint32_t write_records(PrefixShared<T> &sm, const uin
 // others' LDS passes.  Counting in 32 bits where that is enough halves the LDS words of a count.
 template <int G, int T, int LB, bool MASKED, bool RAGGED>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void kmeans_build_kernel(KmArgs a, int64_t i0, unsigned char *tables, int64_t stride) {
-    constexpr int kBuckets = 1 << (16 - LB), kPer = kBuckets / T, kShift = count_shift<T>();
+    constexpr int kBuckets = 1 << (16 - LB), kPer = kBuckets / T, kShift = count_shift<G, T>();
     // dynamic LDS: places of the kept weights, ordered by bucket | removed-entry bitmap (one bit per weight;
     // MASKED) | a word per bucket: count and sum of places, then the cursor of its stretch
     extern __shared__ __align__(16) unsigned char dyn[];
@@ -268,7 +284,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
     const size_t arr_bytes = bucket_arr_bytes(d_out, LB);
     const int n_words = MASKED ? (d_out + 31) >> 5 : 0;
     unsigned char *arr = dyn;
-    uint32_t *removed = reinterpret_cast<uint32_t *>(dyn + arr_bytes);
+    uint32_t *removed = reinterpret_cast<uint32_t *>(dyn + place_area_bytes<G, T, LB>(d_out));
     uint32_t *cursor = removed + ((n_words + 3) & ~3);
     const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
     TableHead *head = reinterpret_cast<TableHead *>(tables + blockIdx.x * stride);
@@ -327,7 +343,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
         l[r] = w & ((1u << kShift) - 1u);
     }
     uint32_t kept = write_records<T, LB>(sm, n, l, start, head, rec, &total);
-    if constexpr (T >= 256) {
+    if constexpr (kMayCarry<G, T, LB>) {
         if (kept != (uint32_t)(d_out - n_ex)) {  // a sum of places ran over into a count (the same for all lanes):
             unsigned long long *wide = reinterpret_cast<unsigned long long *>(arr);  // again, in 64 bits
             __syncthreads();
@@ -1235,11 +1251,12 @@ __global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, co
     }
 }
 
-size_t bucket_dyn_lds(int64_t d_out, int lb) {
-    size_t b = bucket_arr_bytes(d_out, lb);
-    b += (size_t)((((d_out + 31) >> 5) + 3) & ~3) * 4;
-    b += ((size_t)1 << (16 - lb)) * 4;
-    return b;
+// Dynamic LDS of a table build.
+template <int G, int T, int LB>
+size_t build_lds(int64_t d_out, bool masked) {
+    size_t b = place_area_bytes<G, T, LB>(d_out);
+    if (masked) b += (size_t)((((d_out + 31) >> 5) + 3) & ~3) * 4;
+    return b + ((size_t)4 << (16 - LB));
 }
 
 template <typename Kern>
@@ -1252,11 +1269,11 @@ int allow_lds(Kern kern, size_t lds) {
     return CMPQ_OK;
 }
 
-// Rows of 16 lanes per channel in the rounds.  More rows shorten the scan of a bucket and put more wavefronts on
-// the chip, fewer share the rest of the chain: first quantization with 1 / 2 / 4 rows, us: 8192 x 1024 62 / 76 /
-// 100, 4096 x 4096 69 / 63 / 76, 28672 x 8192 552 / 459 / 456, 8192 x 28672 433 / 395 / 360.
-template <int T>
-constexpr int kRows = T == 64 ? 1 : (T < 512 ? 2 : 4);
+// Rows of 16 lanes per channel in the rounds (1 for channels built by 64 lanes, 2 by 128 and 256, 4 by 512).  More
+// rows shorten the scan of a bucket and put more wavefronts on the chip, fewer share the rest of the chain: first
+// quantization with 1 / 2 / 4 rows, us: 8192 x 1024 62 / 76 / 100, 4096 x 4096 69 / 63 / 76, 28672 x 8192 552 / 459
+// / 456, 8192 x 28672 433 / 395 / 360.
+//
 // Up to this many channels the rounds leave SIMDs without a wavefront (there are 1024 of them, and a wavefront
 // takes 4 / R channels), and a round's own length is what counts: twice the rows then.  First and final
 // quantization, us: 1024 x 8192 52 + 74 -> 40 + 66, 1024 x 4096 38 + 58 -> 33 + 57, 2048 x 4608 48 + 74 -> 45 + 73,
@@ -1275,7 +1292,7 @@ int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *t
 }
 
 // One quantization, a run of channels at a time (as many as the scratch holds tables for).
-template <int G, int T, int LB, int R = kRows<T>>
+template <int G, int T, int LB, int R>
 int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes, hipStream_t s) {
     const int64_t stride = (int64_t)table_bytes(a.d_out, LB);
     const bool want_codes = a.codes || a.fused;
@@ -1302,8 +1319,7 @@ int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes
             const bool masked = a.n_out > 0 || a.ragged;
             auto kern = a.ragged ? kmeans_build_kernel<G, T, LB, true, true>
                                  : (masked ? kmeans_build_kernel<G, T, LB, true, false> : kmeans_build_kernel<G, T, LB, false, false>);
-            const size_t lds = bucket_arr_bytes(a.d_out, LB) + (masked ? (size_t)((((a.d_out + 31) >> 5) + 3) & ~3) * 4 : 0) +
-                               ((size_t)4 << (16 - LB));
+            const size_t lds = build_lds<G, T, LB>(a.d_out, masked);
             if (const int rc = allow_lds(kern, lds)) return rc;
             kern<<<(unsigned)n, T, lds, s>>>(a, i0, tables, stride);
             CMPQ_LAUNCH_CHECK();
@@ -1331,75 +1347,83 @@ int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes
 #ifndef CMPQ_LB256
 #define CMPQ_LB256 7
 #endif
-// The launch shape for a channel length: lanes per workgroup, groups of
-// 4 weights per lane, low bits of a key that name the place inside a bucket.  0 lanes: too long.
-static void hist_variant(int64_t d_out, int &T_out, int &G_out, int &LB_out) {
-    const int64_t groups = d_out / 4;
+namespace {
+
+// A shape of the launches: groups of 4 weights per lane, lanes per workgroup, low bits of a key that name the
+// place inside a bucket, rows of 16 lanes per channel in the rounds.
+template <int G_, int T_, int LB_, int R_>
+struct Shape {
+    static constexpr int G = G_, T = T_, LB = LB_, R = R_;
+};
+
+// Calls f with the shape for d_in channels of d_out weights (rows of any length: up to whole groups of 4).  A
+// power-of-two workgroup of at most 512 lanes: up to 32 weights per lane, 64 for the longest channels.
+// CMPQ_ESHAPE: too long.
+template <typename F>
+int with_shape(int64_t d_in, int64_t d_out, F &&f) {
+    const int64_t groups = (d_out + 3) / 4;
     int64_t T = 64;
     while (T < 512 && T * 8 < groups) T <<= 1;
     const int64_t per_lane = cdiv(groups, T);
-    T_out = (int)T;
-    LB_out = T == 512 ? CMPQ_LB512 : (T == 256 ? CMPQ_LB256 : 7);
-    if (per_lane > 16) T_out = 0, G_out = 0;
-    else if (per_lane > 8) G_out = 16, LB_out = CMPQ_LB512;
-    else if (per_lane > 4) G_out = 8;
-    else if (per_lane > 2) G_out = 4;
-    else if (per_lane > 1) G_out = 2;
-    else G_out = 1;
+    const bool few = d_in <= kFewChannels;
+    if (per_lane > 16) return CMPQ_ESHAPE;
+    if (per_lane > 8) return f(Shape<16, 512, CMPQ_LB512, 4>{});
+    if (T == 512) return f(Shape<8, 512, CMPQ_LB512, 4>{});
+    if (T == 256) return few ? f(Shape<8, 256, CMPQ_LB256, 4>{}) : f(Shape<8, 256, CMPQ_LB256, 2>{});
+    // 2304 weights: 42 us, 44 on 128 lanes
+    if (T == 128) return few ? f(Shape<4, 256, 7, 4>{}) : f(Shape<8, 128, 7, 2>{});
+    if (per_lane > 4) return few ? f(Shape<8, 64, 7, 2>{}) : f(Shape<8, 64, 7, 1>{});
+    if (per_lane > 2) return f(Shape<4, 64, 7, 1>{});
+    if (per_lane > 1) return f(Shape<2, 64, 7, 1>{});
+    return f(Shape<1, 64, 7, 1>{});
 }
 
-// Rows of any length: up to whole groups of 4.
-static bool table_shape(int64_t d_out, int &T, int &G, int &LB) {
-    hist_variant((d_out + 3) / 4 * 4, T, G, LB);
-    return T != 0;
+// Bytes of a channel's tables: the same for few channels and for many.  0: too long.
+size_t table_bytes_of(int64_t d_out) {
+    size_t bytes = 0;
+    (void)with_shape(INT64_MAX, d_out, [&](auto s) {
+        bytes = table_bytes(d_out, s.LB);
+        return CMPQ_OK;
+    });
+    return bytes;
 }
+
+}  // namespace
 
 size_t kmeans_hist_arrangement_stride(int64_t d_out) {
-    int T, G, LB;
-    if (d_out < 4 || d_out % 4 != 0 || !table_shape(d_out, T, G, LB)) return 0;
-    return table_bytes(d_out, LB);
+    return d_out < 4 || d_out % 4 != 0 ? 0 : table_bytes_of(d_out);
 }
 
 size_t kmeans_hist_scratch(int64_t d_in, int64_t d_out) {
-    int T, G, LB;
-    if (d_in < 1 || d_out < 1 || !table_shape(d_out, T, G, LB)) return 0;
-    return (size_t)d_in * (table_bytes(d_out, LB) + sizeof(ChannelFinal));
+    const size_t tables = d_in < 1 || d_out < 1 ? 0 : table_bytes_of(d_out);
+    return tables ? (size_t)d_in * (tables + sizeof(ChannelFinal)) : 0;
+}
+
+extern "C" int cmpq_kmeans_build_shape(int64_t d_in, int64_t d_out, int64_t *shape) {
+    if (!shape || d_in < 1 || d_out < 1) return CMPQ_EINVAL;
+    return with_shape(d_in, d_out, [&](auto s) {
+        shape[0] = s.T;
+        shape[1] = s.G;
+        shape[2] = s.LB;
+        shape[3] = (int64_t)bucket_arr_bytes(d_out, s.LB);
+        shape[4] = (int64_t)build_lds<s.G, s.T, s.LB>(d_out, true);
+        shape[5] = (int64_t)(sizeof(PrefixShared<s.T>) + s.T / CMPQ_WAVE * sizeof(uint32_t));
+        shape[6] = (int64_t)place_area_bytes<s.G, s.T, s.LB>(d_out);
+        shape[7] = count_shift<s.G, s.T>();
+        return CMPQ_OK;
+    });
 }
 
 extern "C" int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape) {
     if (!shape || d_out < 4 || d_out % 4 != 0) return CMPQ_EINVAL;
-    int T, G, LB;
-    if (!table_shape(d_out, T, G, LB)) return CMPQ_ESHAPE;
-    shape[0] = T;
-    shape[1] = G;
-    shape[2] = LB;
-    shape[3] = (int64_t)bucket_arr_bytes(d_out, LB);
-    shape[4] = (int64_t)bucket_dyn_lds(d_out, LB);
-    shape[5] = (int64_t)sizeof(PrefixShared<512>) + 8 * 4;
-    return CMPQ_OK;
+    int64_t all[8];
+    const int rc = cmpq_kmeans_build_shape(INT64_MAX, d_out, all);
+    for (int k = 0; rc == CMPQ_OK && k < 6; ++k) shape[k] = all[k];
+    return rc;
 }
 
 int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hipStream_t s) {
-    // A power-of-two workgroup of at most 512 lanes: up to 32 weights per lane, 64 for the
-    // longest channels.
-    int T, G, LB;
-    if (!table_shape(a.d_out, T, G, LB)) return CMPQ_ESHAPE;
-    unsigned char *sc = static_cast<unsigned char *>(scratch);
-    if (G == 16) return launch_variant<16, 512, CMPQ_LB512>(a, sc, scratch_bytes, s);
-    if (a.d_in <= kFewChannels && T < 512) {
-        if (T == 256) return launch_variant<8, 256, CMPQ_LB256, 4>(a, sc, scratch_bytes, s);
-        if (T == 128) return launch_variant<4, 256, 7, 4>(a, sc, scratch_bytes, s);  // 2304 weights: 42 us, 44 on 128 lanes
-        if (G == 8) return launch_variant<8, 64, 7, 2>(a, sc, scratch_bytes, s);
-    }
-    if (G == 8) {
-        switch (T) {
-            case 512: return launch_variant<8, 512, CMPQ_LB512>(a, sc, scratch_bytes, s);
-            case 256: return launch_variant<8, 256, CMPQ_LB256>(a, sc, scratch_bytes, s);
-            case 128: return launch_variant<8, 128, 7>(a, sc, scratch_bytes, s);
-            default: return launch_variant<8, 64, 7>(a, sc, scratch_bytes, s);
-        }
-    }
-    if (G == 4) return launch_variant<4, 64, 7>(a, sc, scratch_bytes, s);
-    if (G == 2) return launch_variant<2, 64, 7>(a, sc, scratch_bytes, s);
-    return launch_variant<1, 64, 7>(a, sc, scratch_bytes, s);
+    return with_shape(a.d_in, a.d_out, [&](auto shape) {
+        return launch_variant<shape.G, shape.T, shape.LB, shape.R>(a, static_cast<unsigned char *>(scratch), scratch_bytes, s);
+    });
 }

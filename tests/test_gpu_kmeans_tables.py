@@ -134,3 +134,30 @@ def test_many_channels_get_the_bits_of_few(env, d_out):
     whole, head, tail = both(0, d_in), both(0, 2048), both(2048, d_in)
     for w, h, t in zip(whole, head, tail):
         assert torch.equal(w, torch.cat([h, t]))
+
+
+@pytest.mark.parametrize("d_out", [2053, 2068, 2101, 2304, 2541, 2543, 2544, 2548, 4095, 4099, 8191, 8196, 28671])
+def test_counts_that_run_over_with_entries_removed(env, d_out):
+    """Rows of one value with the highest place of its bucket, so that the bucket's sum of places leaves its part
+    of the 32-bit word wherever it can; some entries are removed, and rows of no whole number of groups of 4 are
+    filled up."""
+    B, ws, orc = env["B"], env["ws"], env["orc"]
+    rng = np.random.default_rng(d_out)
+    d_in = 5
+    W = np.empty((d_in, d_out), np.float16)
+    W[0] = np.uint16(0x3C7F).view(np.float16)
+    W[1] = -0.0
+    W[2] = np.uint16(0xBC80).view(np.float16)  # of negative values the smallest magnitude has the highest place
+    W[3] = np.where(rng.random(d_out) < 0.97, W[0], rng.normal(0, 0.02, d_out).astype(np.float16))
+    W[4] = rng.normal(0, 0.02, d_out)
+    far = rng.choice(d_out, 12, replace=False)
+    W[:3, far] = np.float16(-7.5)              # few enough for the sum to run over, far enough to move the levels
+    bits = np.array([2, 3, 4, 4, 1], np.uint8)
+    excl = np.sort((np.arange(d_in)[:, None] * d_out + far[None, :9]).ravel()).astype(np.int32)
+    dW, db, de = _dev(W), _dev(bits), _dev(excl)
+    for out_idx in (None, de):
+        cent = torch.full((d_in, 16), 7.0, device=DEV)
+        codes = torch.full((d_in, d_out), 255, dtype=torch.uint8, device=DEV)
+        B.kmeans_quantize(dW, db, out_idx, 0 if out_idx is None else len(excl), None, 6, cent, codes, ws)
+        oc, ok = orc.kmeans(W, bits, out_idx=None if out_idx is None else excl.astype(np.int64), iters=6)
+        assert np.array_equal(_np(cent), oc) and np.array_equal(_np(codes), ok)

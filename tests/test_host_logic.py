@@ -96,19 +96,19 @@ def _arrangement_bounds(d_out, keys, kept, shape):
 
 
 def test_kmeans_kernel_indices_stay_in_bounds_on_adversarial_channels():
-    """The two builds of the K-means kernel that faulted on the GPU differed from the shipped one
-    only in register allocation; a cause in the shared index arithmetic would show here.  Every
-    launch shape, its extreme channel lengths, and key layouts that push each table to its
-    limit: all keys in one bucket, every bucket occupied, counts of 1 mod 4 everywhere (most
-    padding), everything removed, the largest channel."""
+    """Every launch shape of the table build, for many channels and for few, its extreme channel
+    lengths, and key layouts that push each table to its limit: all keys in one bucket, every bucket
+    occupied, counts of 1 mod 4 everywhere (most padding), everything removed, the largest channel."""
     from paper_2410_13056_amd import binding as B
     B.lib()
     rng = np.random.default_rng(0)
     lengths = sorted({4, 8, 252, 256, 260, 512, 1024, 2044, 2048, 2052, 4096, 4100, 5120, 8192, 8196, 11008,
                       13824, 16384, 16388, 28672, 32764, 32768})
     worst = 0
-    for d_out in lengths:
-        shape = B.kmeans_launch_shape(d_out)
+    for d_out, d_in in [(n, m) for n in lengths for m in (1, 2048, 2049)]:
+        shape = B.kmeans_build_shape(d_in, d_out)[:6]
+        if d_in > 2048:
+            assert shape == B.kmeans_launch_shape(d_out)
         LB = shape[2]
         buckets = 1 << (16 - LB)
         layouts = {
@@ -129,6 +129,26 @@ def test_kmeans_kernel_indices_stay_in_bounds_on_adversarial_channels():
         B.kmeans_launch_shape(32772)
     with np.testing.assert_raises(Exception):
         B.kmeans_launch_shape(6)
+
+
+def test_kmeans_bucket_counts_fit_their_words_or_are_taken_again_in_place():
+    """A bucket's 32-bit word holds its count above its sum of places.  Where a sum can run over, the
+    counts still fit beside the carries, and the array that takes the second, 64-bit count lies inside
+    the place area: behind that lies the bitmap of removed entries, which is still read.  Every length."""
+    from paper_2410_13056_amd import binding as B
+    for d_in in (1, 2048, 2049):
+        for d_out in range(1, 32769):
+            T, G, LB, arr_bytes, _, _, area, sum_bits = B.kmeans_build_shape(d_in, d_out)
+            places = (1 << LB) - 1
+            assert d_out <= 4 * G * T and arr_bytes <= area and area % 16 == 0
+            carries = d_out * places >> sum_bits
+            assert d_out + carries < 1 << (32 - sum_bits), (d_in, d_out)
+            if 4 * G * T * places >> sum_bits:
+                assert 8 << (16 - LB) <= area, (d_in, d_out)
+    with np.testing.assert_raises(Exception):
+        B.kmeans_build_shape(1, 32769)
+    with np.testing.assert_raises(Exception):
+        B.kmeans_build_shape(0, 64)
 
 
 def test_bare_barriers_state_both_waits():
