@@ -239,8 +239,9 @@ int cmpq_extract_outliers(int mode, int score, int scope, const float *sumsq, co
  * index.  Update: level = sum(m*x)/sum(m) of its members, accumulated in fp64 and rounded
  * once to fp32; a level without members keeps its value.  -0.0 reads as +0.0.
  * Limits: d_out <= 32768 for CMPQ_F16, <= 16384 for CMPQ_F32 (CMPQ_ESHAPE beyond).
- * Workspace: CMPQ_OP_KMEANS (room for the per-channel tables of all channels; a smaller one works
- * through the channels in parts).  Status: CMPQ_STATUS_NONFINITE (the levels and codes of a channel
+ * Workspace: CMPQ_OP_KMEANS, which for fp16 has room for the tables of all channels (d_out + 5 to
+ * 12 KiB each).  Less will do, down to what cmpq_workspace_bytes(CMPQ_OP_KMEANS, d_in, 0, 0) gives
+ * (some 20 bytes a channel): the channels then go in parts, or their tables stay in LDS.  Status: CMPQ_STATUS_NONFINITE (the levels and codes of a channel
  * that holds a non-finite weight, or is given a non-finite starting level, are unspecified, its
  * codes stay below K; the other channels are not affected).
  */

@@ -98,14 +98,14 @@ __device__ __forceinline__ void zero_codes(uint8_t *row, int tid, int n_groups, 
 
 // A channel's tables in memory: head | one record per bucket | the place array.
 struct TableHead {
-    uint32_t magic;      // kTableMagic + 1: tables follow; + 2: the channel held a non-finite weight
-    uint32_t kept;       // weights that take part
-    uint32_t d_out, quads;  // row length; groups of 16 bytes of the place array that hold stretches
+    uint32_t magic;          // kTableMagic + 1: tables follow; + 2: the channel held a non-finite weight
+    uint32_t kept;           // weights that take part
+    uint32_t d_out, unused;  // row length
     // exact sum of x * 2^24 over the keys below key k << 10 (64 runs of 1024 keys: one sign and exponent
     // each); [64] is the sum over all
     long long base[65];
     uint32_t unused2[2];
-    uint32_t fill[4];    // filler
+    uint32_t fill[4];        // filler
 };
 constexpr uint32_t kTableMagic = 0xC3A77B00u;
 // Record of a bucket: .x = word of the place array where its stretch begins | weights below it << 16; .y =
@@ -263,22 +263,19 @@ __device__ __forceinline__ uint32_t write_records(PrefixShared<T> &sm, const uin
     return n_tot & 0xffffu;
 }
 
-// The tables of one channel, built in LDS.  Bound by LDS (an atomic, a returning atomic and a byte store to
-// scattered addresses per weight: 6.7 clocks a wavefront instruction, two thirds of them bank conflicts) and
-// by what it reads and writes: 2 B a weight in, 1.1 B and 8 B a bucket out.  8192 x 28672 in 219 us = 3.9 TB/s,
-// LDS busy 61 % of the time.  64 registers: 8 wavefronts a SIMD, so that one workgroup's fetch runs beside the
-// others' LDS passes.  Counting in 32 bits where that is enough halves the LDS words of a count.
+// Tables of channel i: head and records where the caller wants them, the place array at the start of `dyn`.  Dynamic
+// LDS: places of the kept weights, ordered by bucket | removed-entry bitmap (one bit per weight; MASKED) | a word per
+// bucket: count and sum of places, then the cursor of its stretch.  Returns the bytes of the place array that hold
+// stretches, -1 for a channel with a non-finite weight (the same for all lanes); ends in a barrier.
+template <int T>
+struct BuildShared {
+    PrefixShared<T> prefix;
+    uint32_t flag[T / CMPQ_WAVE];
+};
 template <int G, int T, int LB, bool MASKED, bool RAGGED>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void kmeans_build_kernel(KmArgs a, int64_t i0, unsigned char *tables, int64_t stride) {
+__device__ __forceinline__ int build_tables(const KmArgs &a, int64_t i, unsigned char *dyn, BuildShared<T> &sm,
+                                            TableHead *head, uint2 *rec) {
     constexpr int kBuckets = 1 << (16 - LB), kPer = kBuckets / T, kShift = count_shift<G, T>();
-    // dynamic LDS: places of the kept weights, ordered by bucket | removed-entry bitmap (one bit per weight;
-    // MASKED) | a word per bucket: count and sum of places, then the cursor of its stretch
-    extern __shared__ __align__(16) unsigned char dyn[];
-    __shared__ PrefixShared<T> sm;
-    __shared__ uint32_t flag[T / CMPQ_WAVE];
-    const int64_t i = i0 + blockIdx.x;
-    const int b = a.bits[i];
-    if (b < 1 || b > 4) return;
     const int tid = threadIdx.x;
     const int d_out = (int)a.d_out, n_groups = RAGGED ? (d_out + 3) >> 2 : d_out >> 2;
     const size_t arr_bytes = bucket_arr_bytes(d_out, LB);
@@ -287,8 +284,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
     uint32_t *removed = reinterpret_cast<uint32_t *>(dyn + place_area_bytes<G, T, LB>(d_out));
     uint32_t *cursor = removed + ((n_words + 3) & ~3);
     const __half *wrow = static_cast<const __half *>(a.W) + i * a.ldw;
-    TableHead *head = reinterpret_cast<TableHead *>(tables + blockIdx.x * stride);
-    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
 
     // lane owns groups g = k*T + tid of 4 weights, kept as packed 16-bit keys
     uint32_t keys[2 * G];
@@ -311,15 +306,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
         keys[k] = keys_of_half2(keys[k]);
     }
     const bool bad = __ballot((nonfinite & 0x80008000u) != 0u) != 0ull;
-    if ((tid & 63) == 0) flag[tid >> 6] = bad;
+    if ((tid & 63) == 0) sm.flag[tid >> 6] = bad;
     __syncthreads();
     {
         uint32_t any = 0;
 #pragma unroll
-        for (int w = 0; w < T / CMPQ_WAVE; ++w) any |= flag[w];
-        if (any) {  // the same for all lanes
+        for (int w = 0; w < T / CMPQ_WAVE; ++w) any |= sm.flag[w];
+        if (any) {
             if (tid == 0) head->magic = kTableMagic + 2u, head->d_out = (uint32_t)d_out;
-            return;
+            return -1;
         }
     }
     int n_ex = 0;
@@ -342,7 +337,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
         n[r] = w >> kShift;
         l[r] = w & ((1u << kShift) - 1u);
     }
-    uint32_t kept = write_records<T, LB>(sm, n, l, start, head, rec, &total);
+    uint32_t kept = write_records<T, LB>(sm.prefix, n, l, start, head, rec, &total);
     if constexpr (kMayCarry<G, T, LB>) {
         if (kept != (uint32_t)(d_out - n_ex)) {  // a sum of places ran over into a count (the same for all lanes):
             unsigned long long *wide = reinterpret_cast<unsigned long long *>(arr);  // again, in 64 bits
@@ -359,7 +354,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
             }
             __syncthreads();
             for (int s = tid; s < (int)(arr_bytes >> 4); s += T) reinterpret_cast<uint4 *>(arr)[s] = fill;
-            kept = write_records<T, LB>(sm, n, l, start, head, rec, &total);
+            kept = write_records<T, LB>(sm.prefix, n, l, start, head, rec, &total);
         }
     }
 #pragma unroll
@@ -367,16 +362,38 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void 
     __syncthreads();
     scatter_places<G, T, LB, MASKED>(keys, removed, cursor, arr, tid, n_groups);
     __syncthreads();
-    // the stretches, up to the last one's end; what a scan may read past it is defined too
-    const int used = min((int)(((total >> 16) + 15) >> 4) + 1, (int)(arr_bytes >> 4));
-    uint4 *dst = reinterpret_cast<uint4 *>(rec + kBuckets);
-    for (int s = tid; s < used; s += T) dst[s] = reinterpret_cast<const uint4 *>(arr)[s];
     if (tid == 0) {
         head->magic = kTableMagic + 1u;
         head->kept = kept;
         head->d_out = (uint32_t)d_out;
-        head->quads = (uint32_t)used;
     }
+    return (int)(total >> 16);
+}
+
+// The stretches to memory, up to the last one's end; what a scan may read past it is defined too.
+template <int T>
+__device__ __forceinline__ void store_places(void *to, const unsigned char *arr, int bytes, size_t arr_bytes) {
+    const int quads = min(((bytes + 15) >> 4) + 1, (int)(arr_bytes >> 4));
+    for (int s = threadIdx.x; s < quads; s += T)
+        reinterpret_cast<uint4 *>(to)[s] = reinterpret_cast<const uint4 *>(arr)[s];
+}
+
+// The tables of one channel, built in LDS.  Bound by LDS (an atomic, a returning atomic and a byte store to
+// scattered addresses per weight: 6.7 clocks a wavefront instruction, two thirds of them bank conflicts) and
+// by what it reads and writes: 2 B a weight in, 1.1 B and 8 B a bucket out.  8192 x 28672 in 219 us = 3.9 TB/s,
+// LDS busy 61 % of the time.  64 registers: 8 wavefronts a SIMD, so that one workgroup's fetch runs beside the
+// others' LDS passes.  Counting in 32 bits where that is enough halves the LDS words of a count.
+template <int G, int T, int LB, bool MASKED, bool RAGGED>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void kmeans_build_kernel(KmArgs a, int64_t i0, unsigned char *tables, int64_t stride) {
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ BuildShared<T> sm;
+    const int64_t i = i0 + blockIdx.x;
+    const int b = a.bits[i];
+    if (b < 1 || b > 4) return;
+    TableHead *head = reinterpret_cast<TableHead *>(tables + blockIdx.x * stride);
+    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
+    const int bytes = build_tables<G, T, LB, MASKED, RAGGED>(a, i, dyn, sm, head, rec);
+    if (bytes >= 0) store_places<T>(rec + (1 << (16 - LB)), dyn, bytes, bucket_arr_bytes((int)a.d_out, LB));
 }
 
 // The removed entries of one channel (slice of out_idx), in the form of the tables above.  About 1 % of the
@@ -437,10 +454,7 @@ __global__ __launch_bounds__(kRemovedLanes) void kmeans_removed_kernel(KmArgs a,
     if (tid < 4) reinterpret_cast<uint32_t *>(arr + (total >> 16))[tid] = kFill4;  // a scan may read past the last stretch
     __syncthreads();
     each([&](uint32_t key) { arr[atomicAdd(&cursor[2 * (key >> LB)], 1u)] = (unsigned char)(key & ((1u << LB) - 1)); });
-    if (tid == 0) {
-        head->magic = kTableMagic + 1u;
-        head->kept = total & 0xffffu;
-    }
+    if (tid == 0) head->kept = total & 0xffffu;
 }
 
 // What the rounds leave for the coding pass.
@@ -533,6 +547,8 @@ __device__ __forceinline__ void loaded(uint4 &v) { asm volatile("" : "+v"(v.x), 
 // No key that is looked up lies in the first or the last 8 * 128 keys but one: those buckets are left out.
 template <int LB, bool REM>
 struct ChannelView {
+    static constexpr int kLB = LB;
+    static constexpr bool kRem = REM;
     static constexpr uint32_t kBuckets = 1u << (16 - LB), kFirst = (0x0400u >> LB) - 1u, kLast = (0xfbffu >> LB) + 1u;
     static constexpr uint32_t kRecs = (kLast - kFirst + 2u) & ~1u;
     static constexpr uint32_t kBytes = (520 + 8 * kRecs + (REM ? 2 * kRecs : 0) + 15u) & ~15u;
@@ -594,13 +610,14 @@ struct Stretch {
 };
 
 // The stretch of one bucket, less that of the removed entries in it.
-template <int R, int LB, int AHEAD, bool REM>
+template <int R, int AHEAD, typename View>
 struct BucketPlaces {
+    static constexpr bool REM = View::kRem;
     Stretch<R, AHEAD> all;
     Stretch<R, 1> rem;
     bool any_rem;
     // b: the bucket, counted from kFirst
-    __device__ __forceinline__ void fetch(const ChannelView<LB, REM> &ch, uint32_t b, uint32_t x0, uint32_t x1, bool in, uint32_t r) {
+    __device__ __forceinline__ void fetch(const View &ch, uint32_t b, uint32_t x0, uint32_t x1, bool in, uint32_t r) {
         const uint32_t w0 = x0 & 0xffffu;
         all.fetch(ch.arr + (in ? w0 : 0u), in ? (x1 & 0xffffu) - w0 : 0u, r, ch.fill);
         if constexpr (REM) {
@@ -639,15 +656,16 @@ struct BucketPlaces {
 // sum of all bytes is known - which the records tell, filler included.  (Places and pl are at most 127, the
 // filler is 128.)  Every term is linear in the bytes, so what the removed entries add is taken off term by
 // term.
-template <int R, int LB, int AHEAD, bool REM>
-__device__ __forceinline__ void below_key(const ChannelView<LB, REM> &ch, uint32_t tk, bool inside, uint32_t r,
-                                          uint32_t &n_below, long long &s_below) {
+template <int R, int AHEAD, typename View>
+__device__ __forceinline__ void below_key(const View &ch, uint32_t tk, bool inside, uint32_t r, uint32_t &n_below,
+                                          long long &s_below) {
+    constexpr int LB = View::kLB;
     constexpr uint32_t kPerRun = 1u << (10 - LB);  // buckets that share sign and exponent
     // a boundary key is that of a finite value: its bucket is not the last one, nor is its run of buckets
     const uint32_t b = inside ? tk >> LB : ch.kFirst, run = b / kPerRun;
     const uint2 r0 = ch.rec()[b - ch.kFirst], r1 = ch.rec()[b - ch.kFirst + 1];
     const long long base0 = ch.base()[run], base1 = ch.base()[run + 1];
-    BucketPlaces<R, LB, AHEAD, REM> places;
+    BucketPlaces<R, AHEAD, View> places;
     places.fetch(ch, b - ch.kFirst, r0.x, r1.x, inside, r);
     const int pl = (int)(tk & ((1u << LB) - 1));
     int A, D, N;
@@ -667,9 +685,9 @@ __device__ __forceinline__ void below_key(const ChannelView<LB, REM> &ch, uint32
 
 // Start-up: level j = order statistic floor((2j+1)M/(2K)) of the kept weights.  The bucket by bisection on
 // the counts below, then the place by bisection with counting scans of that bucket.
-template <int R, int LB, int AHEAD, bool REM>
-__device__ __forceinline__ float quantile_start(const ChannelView<LB, REM> &ch, int K, uint32_t M, uint32_t r) {
-    using View = ChannelView<LB, REM>;
+template <int R, int AHEAD, typename View>
+__device__ __forceinline__ float quantile_start(const View &ch, int K, uint32_t M, uint32_t r) {
+    constexpr int LB = View::kLB;
     const int p = threadIdx.x & 15;
     const bool mine = p < K && M > 0;
     const uint32_t rank = mine ? (uint32_t)(2 * p + 1) * M >> __ffs(K) : 0u;  // K is a power of two
@@ -679,7 +697,7 @@ __device__ __forceinline__ float quantile_start(const ChannelView<LB, REM> &ch, 
         if ((ch.rec()[min(max(b + s, View::kFirst), View::kLast) - View::kFirst].x >> 16) <= rank) b += s;
     b = mine ? min(max(b, View::kFirst), View::kLast - 1u) : View::kFirst;
     const uint32_t x0 = ch.rec()[b - View::kFirst].x, x1 = ch.rec()[b - View::kFirst + 1].x, in = rank - (x0 >> 16);
-    BucketPlaces<R, LB, AHEAD, REM> places;
+    BucketPlaces<R, AHEAD, View> places;
     places.fetch(ch, b - View::kFirst, x0, x1, mine, r);
     uint32_t pl = 0;  // smallest place with more than `in` weights at or below it
 #pragma unroll 1
@@ -705,6 +723,122 @@ __device__ __forceinline__ float mean_of_cell(long long s, uint32_t n) {
     return (float)fma(fma(-d, q, x), r, q);
 }
 
+// What the rounds leave in lane p of a row: the level at sorted position p, which level that is, the key of the
+// boundary above it.
+struct Rounds {
+    float c_sorted;
+    int own;
+    uint32_t tk;
+};
+// Start-up (unless the caller gave the levels: lane p's is c0) and rounds of the channels whose rows of 16 lanes these
+// are.  M weights take part, their sum of x * 2^24 is s_all.
+template <int R, int AHEAD, typename View>
+__device__ __forceinline__ Rounds run_rounds(const View &ch, int K, uint32_t M, long long s_all, bool start_given, float c0,
+                                             int iters, uint32_t r) {
+    const int p = threadIdx.x & 15;
+    if (!start_given) {
+        const float start = quantile_start<R, AHEAD>(ch, K, M, r);
+        c0 = p < K ? start : INFINITY;
+    }
+
+    // lane p of a row: the level at sorted position p, which level that is, the next distinct level above it
+    // (there is none for have_hi = false) and whether a weight half way belongs to the upper one
+    float c_sorted, hi;
+    int own;
+    bool have_hi, tie_up;
+    auto rank = [&](float c_level) {
+        int owner_lo, owner_hi;
+        rank_levels_in_rows(c_level, K, c_sorted, own, hi, owner_lo, owner_hi, have_hi);
+        tie_up = owner_hi < owner_lo;
+    };
+    {
+        // starting levels that ascend strictly (the usual outcome of the quantile start) are
+        // in sorted order already: each level's upper neighbour sits one lane up
+        const float c0_up = __uint_as_float(row_from_above(__float_as_uint(c0)));
+        if (__ballot(p < K - 1 && !(c0 < c0_up)) == 0ull) {
+            c_sorted = c0;
+            own = p;
+            hi = c0_up;
+            have_hi = p < K - 1;
+            tie_up = false;
+        } else {
+            rank(c0);
+        }
+    }
+    uint32_t tk = 0xffffffffu;
+#pragma unroll 1
+    for (int round = 0;; ++round) {
+        const uint32_t tk_prev = tk;
+        tk = boundary_key(c_sorted, hi, __ballot(have_hi && tie_up) != 0ull && tie_up);
+        if (!have_hi) tk = kKeyInf;
+        // no boundary moved: the iteration sits on its fixed point
+        if (round == iters || __ballot(p < K - 1 && tk != tk_prev) == 0ull) break;
+        // cumulative count and sum at each boundary; the last position takes everything
+        uint32_t n_below;
+        long long s_below;
+        below_key<R, AHEAD>(ch, tk, have_hi, r, n_below, s_below);
+        if (!have_hi) {
+            n_below = M;
+            s_below = s_all;
+        }
+        // sorted positions live in one DPP row: neighbours come by row shifts
+        const uint32_t n_cell = n_below - row_from_below(n_below);
+        const long long s_cell = s_below - (long long)(((unsigned long long)row_from_below((uint32_t)((unsigned long long)s_below >> 32)) << 32) |
+                                                       row_from_below((uint32_t)s_below));
+        const float mean = mean_of_cell(s_cell, n_cell);
+        const float c = p < K && n_cell > 0 ? mean : c_sorted;
+        // usual case: the levels are still strictly ascending in the old order
+        const float c_up = __uint_as_float(row_from_above(__float_as_uint(c)));
+        const int own_up = (int)row_from_above((uint32_t)own);
+        if (__ballot(p < K - 1 && !(c < c_up)) == 0ull) {
+            c_sorted = c;
+            hi = c_up;
+            have_hi = p < K - 1;
+            tie_up = own_up < own;
+        } else {
+            // bring the values back to level order and rank them again
+            float c_level = INFINITY;
+#pragma unroll 1
+            for (int l = 0; l < CMPQ_KMAX; ++l) {
+                const int ol = from_row_lane(own, l);
+                const float cl = from_row_lane(c, l);
+                if (ol == p) c_level = cl;
+            }
+            rank(c_level);
+        }
+    }
+    return {c_sorted, own, tk};
+}
+// The levels of a channel, lane p's share: why != 0 is the status of a flagged one.
+__device__ __forceinline__ void store_levels(const KmArgs &a, int64_t i, int K, uint32_t why, const Rounds &res) {
+    const int p = threadIdx.x & 15;
+    float *crow = a.centroids + i * CMPQ_KMAX;
+    if (why && p == 0 && a.status) atomicOr(a.status, (int)why);
+    if (p >= K) crow[p] = INFINITY;
+    else if (why) crow[p] = 0.0f;
+    else crow[res.own] = res.c_sorted;
+}
+__device__ __forceinline__ void store_final(ChannelFinal &fin, uint32_t why, const Rounds &res) {
+    const int p = threadIdx.x & 15;
+    fin.tk[p] = (uint16_t)res.tk;
+    fin.code_of[p] = (uint8_t)res.own;
+    if (p == 0) fin.ok = why == 0;
+}
+
+// The caller's level p of channel i in lane p (infinity: no such level; -0 is taken as +0); a non-finite one raises
+// `why`.
+__device__ __forceinline__ float given_level(const KmArgs &a, int64_t i, int K, uint32_t &why) {
+    const int p = threadIdx.x & 15;
+    float c = INFINITY;
+    if (a.start_given) {
+        if (p < K) c = a.centroids[i * CMPQ_KMAX + p];
+        const uint64_t odd = __ballot(p < K && !isfinite(c));
+        if (((odd >> (threadIdx.x & 48)) & 0xffffu) && !why) why = CMPQ_STATUS_NONFINITE;
+        c = c == 0.0f ? 0.0f : c;
+    }
+    return c;
+}
+
 // Start-up and rounds of 4 / R channels on one wavefront.  A channel has R rows of 16 lanes; lane p of a
 // row carries the level at sorted position p and the boundary above it.  All rows of a channel hold the same
 // state; they share out the words of a boundary's bucket.  Sharing a wavefront is what makes a round
@@ -716,7 +850,7 @@ template <int R, int LB, int AHEAD, bool REM>
 __global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int64_t i0, int64_t n_chan,
                                                                  const unsigned char *tables, int64_t stride,
                                                                  const unsigned char *removed, ChannelFinal *fin) {
-    const int lane = threadIdx.x, p = lane & 15;
+    const int lane = threadIdx.x;
     const uint32_t r = (uint32_t)((lane >> 4) & (R - 1));
     // Channels 8 apart: workgroups go to the 8 XCDs in turn, and a channel's tables are best read on the XCD that
     // built them, whose L2 may still hold them.  First and final quantization, us, neighbouring channels together
@@ -727,7 +861,6 @@ __global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int6
     const int64_t j = exists ? at : n_chan - 1, i = i0 + j;
     const int b = exists ? a.bits[i] : 0;
     const bool coded = b >= 1 && b <= 4;
-    float *crow = a.centroids + i * CMPQ_KMAX;
     const TableHead *head = reinterpret_cast<const TableHead *>(tables + j * stride);
     const TableHead *rem = reinterpret_cast<const TableHead *>(REM ? removed + j * stride : nullptr);
     // ---- sums per run and records into LDS, what the removed entries add taken off.  All loads go out before
@@ -786,99 +919,77 @@ __global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int6
     uint32_t why = 0;
     if (coded && (magic != kTableMagic + 1u || len != (uint32_t)a.d_out))
         why = magic == kTableMagic + 2u ? CMPQ_STATUS_NONFINITE : CMPQ_STATUS_ARRANGEMENT;
-    float c0 = INFINITY;
-    if (a.start_given) {  // the caller's levels, in level order; -0 is taken as +0
-        if (p < K) c0 = crow[p];
-        const uint64_t odd = __ballot(p < K && !isfinite(c0));
-        if (((odd >> (lane & 48)) & 0xffffu) && !why) why = CMPQ_STATUS_NONFINITE;
-        c0 = c0 == 0.0f ? 0.0f : c0;
-    }
+    const float c0 = given_level(a, i, K, why);
     const int K_out = K;
     if (why) K = 0;
     const uint32_t M = K ? kept_all - n_rem : 0u;
     __syncthreads();
     const long long s_all = K ? ch.base()[64] : 0ll;
-    if (!a.start_given) {
-        const float start = quantile_start<R, LB, AHEAD, REM>(ch, K, M, r);
-        c0 = p < K ? start : INFINITY;
-    }
-
-    // lane p of a row: the level at sorted position p, which level that is, the next distinct level above it
-    // (there is none for have_hi = false) and whether a weight half way belongs to the upper one
-    float c_sorted, hi;
-    int own;
-    bool have_hi, tie_up;
-    auto rank = [&](float c_level) {
-        int owner_lo, owner_hi;
-        rank_levels_in_rows(c_level, K, c_sorted, own, hi, owner_lo, owner_hi, have_hi);
-        tie_up = owner_hi < owner_lo;
-    };
-    {
-        // starting levels that ascend strictly (the usual outcome of the quantile start) are
-        // in sorted order already: each level's upper neighbour sits one lane up
-        const float c0_up = __uint_as_float(row_from_above(__float_as_uint(c0)));
-        if (__ballot(p < K - 1 && !(c0 < c0_up)) == 0ull) {
-            c_sorted = c0;
-            own = p;
-            hi = c0_up;
-            have_hi = p < K - 1;
-            tie_up = false;
-        } else {
-            rank(c0);
-        }
-    }
-    uint32_t tk = 0xffffffffu;
-#pragma unroll 1
-    for (int round = 0;; ++round) {
-        const uint32_t tk_prev = tk;
-        tk = boundary_key(c_sorted, hi, __ballot(have_hi && tie_up) != 0ull && tie_up);
-        if (!have_hi) tk = kKeyInf;
-        // no boundary moved: the iteration sits on its fixed point
-        if (round == a.iters || __ballot(p < K - 1 && tk != tk_prev) == 0ull) break;
-        // cumulative count and sum at each boundary; the last position takes everything
-        uint32_t n_below;
-        long long s_below;
-        below_key<R, LB, AHEAD, REM>(ch, tk, have_hi, r, n_below, s_below);
-        if (!have_hi) {
-            n_below = M;
-            s_below = s_all;
-        }
-        // sorted positions live in one DPP row: neighbours come by row shifts
-        const uint32_t n_cell = n_below - row_from_below(n_below);
-        const long long s_cell = s_below - (long long)(((unsigned long long)row_from_below((uint32_t)((unsigned long long)s_below >> 32)) << 32) |
-                                                       row_from_below((uint32_t)s_below));
-        const float mean = mean_of_cell(s_cell, n_cell);
-        const float c = p < K && n_cell > 0 ? mean : c_sorted;
-        // usual case: the levels are still strictly ascending in the old order
-        const float c_up = __uint_as_float(row_from_above(__float_as_uint(c)));
-        const int own_up = (int)row_from_above((uint32_t)own);
-        if (__ballot(p < K - 1 && !(c < c_up)) == 0ull) {
-            c_sorted = c;
-            hi = c_up;
-            have_hi = p < K - 1;
-            tie_up = own_up < own;
-        } else {
-            // bring the values back to level order and rank them again
-            float c_level = INFINITY;
-#pragma unroll 1
-            for (int l = 0; l < CMPQ_KMAX; ++l) {
-                const int ol = from_row_lane(own, l);
-                const float cl = from_row_lane(c, l);
-                if (ol == p) c_level = cl;
-            }
-            rank(c_level);
-        }
-    }
+    const Rounds res = run_rounds<R, AHEAD>(ch, K, M, s_all, a.start_given, c0, a.iters, r);
     if (!exists || r != 0) return;
-    if (why && p == 0 && a.status) atomicOr(a.status, (int)why);
-    if (p >= K_out) crow[p] = INFINITY;
-    else if (why) crow[p] = 0.0f;
-    else crow[own] = c_sorted;
-    if (fin && coded) {
-        fin[j].tk[p] = (uint16_t)tk;
-        fin[j].code_of[p] = (uint8_t)own;
-        if (p == 0) fin[j].ok = why == 0;
+    store_levels(a, i, K_out, why, res);
+    if (fin && coded) store_final(fin[j], why, res);
+}
+
+// The same of a channel whose tables lie in LDS as they were built, nothing taken off.
+template <int LB>
+struct LocalView {
+    static constexpr int kLB = LB;
+    static constexpr bool kRem = false;
+    static constexpr uint32_t kBuckets = ChannelView<LB, false>::kBuckets, kFirst = ChannelView<LB, false>::kFirst,
+                              kLast = ChannelView<LB, false>::kLast;
+    const TableHead *head;
+    const uint32_t *arr, *fill;
+    __device__ __forceinline__ const long long *base() const { return head->base; }
+    __device__ __forceinline__ const uint2 *rec() const { return reinterpret_cast<const uint2 *>(head + 1) + kFirst; }
+};
+
+// Tables, start-up and rounds of a channel in one workgroup, nothing but its levels (and tables to be kept) to
+// memory: for calls whose scratch is too small for the tables of many channels.  Kept tables are not taken: a channel's
+// own are built without the removed entries, which gives the same.
+template <int G, int T, int LB, bool MASKED, bool RAGGED>
+__global__ __launch_bounds__(T) void kmeans_channel_kernel(KmArgs a, int64_t i0, int64_t stride, ChannelFinal *fin) {
+    // dynamic LDS: what build_tables wants | head | records
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ BuildShared<T> sm;
+    constexpr int kBuckets = 1 << (16 - LB);
+    const int64_t i = i0 + blockIdx.x;
+    const int tid = threadIdx.x, b = a.bits[i];
+    if (b < 1 || b > 4) {
+        if (tid < CMPQ_KMAX) a.centroids[i * CMPQ_KMAX + tid] = INFINITY;
+        return;
     }
+    const int d_out = (int)a.d_out, n_words = MASKED ? (d_out + 31) >> 5 : 0;
+    TableHead *head = reinterpret_cast<TableHead *>(dyn + place_area_bytes<G, T, LB>(d_out) + (size_t)((n_words + 3) & ~3) * 4 +
+                                                    (size_t)kBuckets * 4);
+    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
+    uint32_t why = 0;  // the same for all lanes
+    if (a.arr_reuse) {
+        const TableHead *kept = reinterpret_cast<const TableHead *>(static_cast<const unsigned char *>(a.arr_reuse) + i * stride);
+        if (kept->magic != kTableMagic + 1u || kept->d_out != (uint32_t)d_out)
+            why = kept->magic == kTableMagic + 2u ? CMPQ_STATUS_NONFINITE : CMPQ_STATUS_ARRANGEMENT;
+    }
+    if (!why) {
+        const int bytes = build_tables<G, T, LB, MASKED, RAGGED>(a, i, dyn, sm, head, rec);
+        if (bytes < 0) why = CMPQ_STATUS_NONFINITE;
+        __syncthreads();
+        if (a.arr_keep) {
+            unsigned char *to = static_cast<unsigned char *>(a.arr_keep) + i * stride;
+            const int quads = (int)((why ? sizeof(TableHead) : sizeof(TableHead) + 8 * kBuckets) / 16);
+            for (int s = tid; s < quads; s += T) reinterpret_cast<uint4 *>(to)[s] = reinterpret_cast<const uint4 *>(head)[s];
+            if (!why) store_places<T>(to + sizeof(TableHead) + 8 * kBuckets, dyn, bytes, bucket_arr_bytes(d_out, LB));
+        }
+    }
+    if (tid >= CMPQ_WAVE) return;
+    const int K_out = 1 << b;
+    const float c0 = given_level(a, i, K_out, why);
+    const int K = why ? 0 : K_out;
+    const LocalView<LB> ch = {head, reinterpret_cast<const uint32_t *>(dyn), head->fill};
+    const Rounds res = run_rounds<4, 4>(ch, K, K ? head->kept : 0u, K ? head->base[64] : 0ll, a.start_given, c0, a.iters,
+                                        (uint32_t)(tid >> 4));
+    if (tid >= 16) return;
+    store_levels(a, i, K_out, why, res);
+    if (fin) store_final(fin[blockIdx.x], why, res);
 }
 
 // The coding table over the buckets (many levels, long channels): a bucket with no boundary
@@ -1279,6 +1390,8 @@ int allow_lds(Kern kern, size_t lds) {
 // quantization, us: 1024 x 8192 52 + 74 -> 40 + 66, 1024 x 4096 38 + 58 -> 33 + 57, 2048 x 4608 48 + 74 -> 45 + 73,
 // 2048 x 2048 43 + 68 -> 40 + 64; past it the order turns: 3000 x 4099 69 + 96 with 2 rows, 82 + 113 with 4.
 constexpr int64_t kFewChannels = 2048;
+// Parts of fewer channels than this leave the chip idle between their launches: the tables stay in LDS then.
+constexpr int64_t kLeastPart = 2048;
 template <int R, int LB, int AHEAD>
 int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *tables, int64_t stride,
                    const unsigned char *removed, ChannelFinal *fin, hipStream_t s) {
@@ -1291,27 +1404,40 @@ int launch_rounds(const KmArgs &a, int64_t i0, int64_t n, const unsigned char *t
     return CMPQ_OK;
 }
 
-// One quantization, a run of channels at a time (as many as the scratch holds tables for).
+// Codes of channels i0 .. i0 + n from what the rounds left.
+template <int G, int T, int LB>
+int launch_codes(const KmArgs &a, int64_t i0, int64_t n, const ChannelFinal *fin, hipStream_t s) {
+    auto kern = a.fused ? (a.ragged ? kmeans_code_kernel<G, T, LB, true, true> : kmeans_code_kernel<G, T, LB, true, false>)
+                        : (a.ragged ? kmeans_code_kernel<G, T, LB, false, true> : kmeans_code_kernel<G, T, LB, false, false>);
+    size_t lds = (size_t)code_table_words(T, G, LB) * 4;
+    if (a.fused) lds += (size_t)((((a.d_out + 31) >> 5) + 3) & ~3) * 4 + (size_t)(a.d_out / 2 + 16);
+    if (const int rc = allow_lds(kern, lds)) return rc;
+    kern<<<(unsigned)n, T, lds, s>>>(a, i0, fin);
+    CMPQ_LAUNCH_CHECK();
+    return CMPQ_OK;
+}
+
+bool wants_codes(const KmArgs &a) { return a.codes || a.fused; }
+// The removed entries have tables of their own where those of all weights are kept ones.
+bool wants_removed(const KmArgs &a) { return a.arr_reuse && a.n_out > 0; }
+// Scratch per channel: tables of all weights, or of the removed ones beside kept tables; what the rounds leave.
+size_t scratch_per_channel(const KmArgs &a, size_t stride) {
+    return ((!a.arr_keep && !a.arr_reuse) || wants_removed(a) ? stride : 0) + (wants_codes(a) ? sizeof(ChannelFinal) : 0);
+}
+
+// One quantization, `step` channels at a time.
 template <int G, int T, int LB, int R>
-int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes, hipStream_t s) {
+int launch_variant(const KmArgs &a, unsigned char *scratch, int64_t step, hipStream_t s) {
     const int64_t stride = (int64_t)table_bytes(a.d_out, LB);
-    const bool want_codes = a.codes || a.fused;
-    // scratch per channel: tables of all weights, or of the removed ones beside kept tables; what the rounds leave
-    const bool own_tables = !a.arr_keep && !a.arr_reuse, rem_tables = a.arr_reuse && a.n_out > 0;
-    const int64_t per_chan = (own_tables || rem_tables ? stride : 0) + (want_codes ? (int64_t)sizeof(ChannelFinal) : 0);
-    int64_t step = a.d_in;
-    if (per_chan > 0 && (int64_t)(scratch_bytes / per_chan) < step) step = (int64_t)(scratch_bytes / per_chan);
-    if (step < 1) return CMPQ_EWORKSPACE;
-    ChannelFinal *fin = want_codes ? reinterpret_cast<ChannelFinal *>(scratch) : nullptr;
-    unsigned char *side = scratch + (want_codes ? step * (int64_t)sizeof(ChannelFinal) : 0);
-    cmpq_timing_before(CMPQ_KERNEL_KMEANS, s);
+    ChannelFinal *fin = wants_codes(a) ? reinterpret_cast<ChannelFinal *>(scratch) : nullptr;
+    unsigned char *side = scratch + (fin ? step * (int64_t)sizeof(ChannelFinal) : 0);
     for (int64_t i0 = 0; i0 < a.d_in; i0 += step) {
         const int64_t n = a.d_in - i0 < step ? a.d_in - i0 : step;
         unsigned char *tables = a.arr_keep ? static_cast<unsigned char *>(a.arr_keep) + i0 * stride : side;
         const unsigned char *src = tables;
         if (a.arr_reuse) {
             src = static_cast<const unsigned char *>(a.arr_reuse) + i0 * stride;
-            if (rem_tables) {
+            if (wants_removed(a)) {
                 kmeans_removed_kernel<LB><<<(unsigned)n, kRemovedLanes, 0, s>>>(a, i0, side, stride);
                 CMPQ_LAUNCH_CHECK();
             }
@@ -1324,18 +1450,31 @@ int launch_variant(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes
             kern<<<(unsigned)n, T, lds, s>>>(a, i0, tables, stride);
             CMPQ_LAUNCH_CHECK();
         }
-        if (const int rc = launch_rounds<R, LB, G == 16 ? 8 : 4>(a, i0, n, src, stride, rem_tables ? side : nullptr, fin, s)) return rc;
-        if (want_codes) {
-            auto kern = a.fused ? (a.ragged ? kmeans_code_kernel<G, T, LB, true, true> : kmeans_code_kernel<G, T, LB, true, false>)
-                                : (a.ragged ? kmeans_code_kernel<G, T, LB, false, true> : kmeans_code_kernel<G, T, LB, false, false>);
-            size_t lds = (size_t)code_table_words(T, G, LB) * 4;
-            if (a.fused) lds += (size_t)((((a.d_out + 31) >> 5) + 3) & ~3) * 4 + (size_t)(a.d_out / 2 + 16);
-            if (const int rc = allow_lds(kern, lds)) return rc;
-            kern<<<(unsigned)n, T, lds, s>>>(a, i0, fin);
-            CMPQ_LAUNCH_CHECK();
-        }
+        if (const int rc = launch_rounds<R, LB, G == 16 ? 8 : 4>(a, i0, n, src, stride, wants_removed(a) ? side : nullptr, fin, s)) return rc;
+        if (!fin) continue;
+        if (const int rc = launch_codes<G, T, LB>(a, i0, n, fin, s)) return rc;
     }
-    cmpq_timing_after(CMPQ_KERNEL_KMEANS, s);
+    return CMPQ_OK;
+}
+
+// The same with a channel's tables in LDS alone.
+template <int G, int T, int LB>
+int launch_channels(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes, hipStream_t s) {
+    const int64_t room = (int64_t)(scratch_bytes / sizeof(ChannelFinal)), step = !wants_codes(a) || room > a.d_in ? a.d_in : room;
+    if (step < 1) return CMPQ_EWORKSPACE;
+    ChannelFinal *fin = wants_codes(a) ? reinterpret_cast<ChannelFinal *>(scratch) : nullptr;
+    const bool masked = a.n_out > 0 || a.ragged;
+    auto kern = a.ragged ? kmeans_channel_kernel<G, T, LB, true, true>
+                         : (masked ? kmeans_channel_kernel<G, T, LB, true, false> : kmeans_channel_kernel<G, T, LB, false, false>);
+    const size_t lds = build_lds<G, T, LB>(a.d_out, masked) + sizeof(TableHead) + ((size_t)8 << (16 - LB));
+    if (const int rc = allow_lds(kern, lds)) return rc;
+    for (int64_t i0 = 0; i0 < a.d_in; i0 += step) {
+        const int64_t n = a.d_in - i0 < step ? a.d_in - i0 : step;
+        kern<<<(unsigned)n, T, lds, s>>>(a, i0, (int64_t)table_bytes(a.d_out, LB), fin);
+        CMPQ_LAUNCH_CHECK();
+        if (!fin) continue;
+        if (const int rc = launch_codes<G, T, LB>(a, i0, n, fin, s)) return rc;
+    }
     return CMPQ_OK;
 }
 
@@ -1407,7 +1546,7 @@ extern "C" int cmpq_kmeans_build_shape(int64_t d_in, int64_t d_out, int64_t *sha
         shape[2] = s.LB;
         shape[3] = (int64_t)bucket_arr_bytes(d_out, s.LB);
         shape[4] = (int64_t)build_lds<s.G, s.T, s.LB>(d_out, true);
-        shape[5] = (int64_t)(sizeof(PrefixShared<s.T>) + s.T / CMPQ_WAVE * sizeof(uint32_t));
+        shape[5] = (int64_t)sizeof(BuildShared<s.T>);
         shape[6] = (int64_t)place_area_bytes<s.G, s.T, s.LB>(d_out);
         shape[7] = count_shift<s.G, s.T>();
         return CMPQ_OK;
@@ -1423,7 +1562,14 @@ extern "C" int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape) {
 }
 
 int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hipStream_t s) {
-    return with_shape(a.d_in, a.d_out, [&](auto shape) {
-        return launch_variant<shape.G, shape.T, shape.LB, shape.R>(a, static_cast<unsigned char *>(scratch), scratch_bytes, s);
-    });
+    unsigned char *sc = static_cast<unsigned char *>(scratch);
+    const size_t stride = table_bytes_of(a.d_out), per = scratch_per_channel(a, stride);
+    if (!stride) return CMPQ_ESHAPE;
+    const int64_t room = per ? (int64_t)(scratch_bytes / per) : a.d_in, step = room < a.d_in ? room : a.d_in;
+    cmpq_timing_before(CMPQ_KERNEL_KMEANS, s);
+    const int rc = step < a.d_in && step < kLeastPart
+                       ? with_shape(1, a.d_out, [&](auto v) { return launch_channels<v.G, v.T, v.LB>(a, sc, scratch_bytes, s); })
+                       : with_shape(a.d_in, a.d_out, [&](auto v) { return launch_variant<v.G, v.T, v.LB, v.R>(a, sc, step, s); });
+    cmpq_timing_after(CMPQ_KERNEL_KMEANS, s);
+    return rc;
 }

@@ -69,11 +69,11 @@ class _Limited:
         return self.buf
 
 
-@pytest.mark.parametrize("d_out", [1024, 4098, 8192])
-def test_scratch_for_a_few_channels_gives_the_same_bits(env, d_out):
+@pytest.mark.parametrize("d_in,d_out,rooms", [(23, 1024, (1, 5, 22)), (23, 4098, (1, 22)), (23, 8192, (22,)),
+                                              (4200, 64, (2047, 2048, 2049, 4199)), (2060, 1031, (2049,))])
+def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out, rooms):
     B, ws = env["B"], env["ws"]
     rng = np.random.default_rng(3)
-    d_in = 23
     W = rng.normal(0, 0.02, (d_in, d_out)).astype(np.float16)
     bits = rng.choice(np.array([2, 3, 4, 16], np.uint8), d_in)
     excl = _dev(np.sort(rng.choice(d_in * d_out, d_in * d_out // 80, replace=False)).astype(np.int32))
@@ -82,13 +82,67 @@ def test_scratch_for_a_few_channels_gives_the_same_bits(env, d_out):
     codes = torch.empty((d_in, d_out), dtype=torch.uint8, device=DEV)
     B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, ws)
     full = B.workspace_bytes(B.OP_KMEANS, d_in, d_out)
-    one = (full - B.workspace_bytes(B.OP_KMEANS, 1, d_out)) // (d_in - 1)
-    for channels in (1, 5, d_in - 1):
+    one = (B.workspace_bytes(B.OP_KMEANS, 1 << 20, d_out) - B.workspace_bytes(B.OP_KMEANS, 1 << 19, d_out)) >> 19
+    for channels in rooms:
         c2, k2 = torch.full_like(cent, 7.0), torch.full_like(codes, 255)
         B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, c2, k2, _Limited(full - (d_in - channels) * one + 512))
         assert torch.equal(c2, cent) and torch.equal(k2, codes)
     with pytest.raises(B.CmpqError):
         B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, _Limited(256))
+
+
+@pytest.mark.parametrize("d_in,d_out", [(1, 4), (7, 64), (3, 1028), (9, 1999), (5, 2052), (3, 4099), (2, 8192), (300, 1500),
+                                        (3, 16384), (2, 28672), (2, 32768), (2, 32767)])
+def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
+    """The size that holds for rows of any length (asked for without one): every form of the call, bit for bit what
+    it leaves with room for the tables of all channels."""
+    B, ws = env["B"], env["ws"]
+    rng = np.random.default_rng(d_out)
+    W = _crowded(rng, d_in, d_out)
+    if d_in > 1:
+        W[-1, -1] = np.inf
+    bits = np.resize(np.array([4, 3, 2, 16, 1], np.uint8), d_in)
+    n_out = d_in * d_out // 40
+    excl = _dev(np.sort(rng.choice(d_in * d_out, n_out, replace=False)).astype(np.int32)) if n_out else None
+    dW, db = _dev(W), _dev(bits)
+    widths = [b for b in (1, 2, 3, 4) if b in bits]
+    counts = [int((bits == b).sum()) for b in widths]
+    sumsq = torch.ones(d_in, device=DEV)
+    least = B.workspace_bytes(B.OP_KMEANS, d_in, 0)
+    whole = d_out % 4 == 0
+
+    def forms(space):
+        out = []
+
+        def run(n, codes, init, use, tables):
+            cent = torch.linspace(-0.1, 0.1, 16, device=DEV).repeat(d_in, 1)
+            st = torch.zeros(1, dtype=torch.int32, device=DEV)
+            B.kmeans_quantize(dW, db, excl if n else None, n, None, 5, cent, codes, space(), st, init=init, arrangement=tables,
+                              arrangement_use=use)
+            out.extend([cent, st] + ([codes] if codes is not None else []))
+
+        codes = lambda: torch.full((d_in, d_out), 255, dtype=torch.uint8, device=DEV)
+        for n in {0, n_out}:
+            for init in (B.INIT_QUANTILE, B.INIT_GIVEN):
+                run(n, codes(), init, B.ARRANGEMENT_NONE, None)
+        if whole:
+            run(n_out, None, B.INIT_QUANTILE, B.ARRANGEMENT_NONE, None)
+            tables = torch.zeros(B.arrangement_bytes(d_in, d_out), dtype=torch.uint8, device=DEV)
+            run(0, None, B.INIT_QUANTILE, B.ARRANGEMENT_KEEP, tables)
+            run(n_out, codes(), B.INIT_QUANTILE, B.ARRANGEMENT_REUSE, tables)
+            tables.zero_()
+            run(n_out, codes(), B.INIT_QUANTILE, B.ARRANGEMENT_REUSE, tables)
+            assert out[-2].item() & B.STATUS_ARRANGEMENT and not out[-1].any()
+        cent, k = torch.empty((d_in, 16), device=DEV), codes()
+        packed = [torch.full((c, (d_out * b + 31) // 32), -1, dtype=torch.int32, device=DEV) for b, c in zip(widths, counts)]
+        idx = [torch.full((c,), -1, dtype=torch.int32, device=DEV) for c in counts]
+        lut = [torch.full((c, 1 << b), 7.0, dtype=torch.float16, device=DEV) for b, c in zip(widths, counts)]
+        err, tot = torch.empty(d_in, dtype=torch.float64, device=DEV), torch.empty(2, dtype=torch.float64, device=DEV)
+        B.kmeans_quantize_pack(dW, db, excl, n_out, 5, cent, k, widths, counts, packed, idx, lut, sumsq, err, tot, space())
+        return out + [cent, k, *packed, *idx, *lut, err.view(torch.int64), tot.view(torch.int64)]
+
+    for a, b in zip(forms(lambda: ws), forms(lambda: _Limited(least))):
+        assert torch.equal(a, b)
 
 
 def test_tables_of_another_row_length_are_flagged(env):
