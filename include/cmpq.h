@@ -360,10 +360,12 @@ int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, size_t ws_byt
 int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape);
 
 /*
- * The same for d_in channels of any length (few channels get more lanes).  shape [8]: as above, then
- * the bytes of LDS that the place array lies in, which also hold the bucket counts (8 bytes a
- * bucket) where they are taken again in 64 bits, and the bits of a bucket's 32-bit word
- * that its sum of places has: they are taken again when the sum of some bucket reaches 2^bits.
+ * The same for d_in channels of any length.  shape [9]: as above, then the bytes of LDS that the
+ * place array lies in, which also hold the bucket counts (8 bytes a bucket) where they are taken
+ * again in 64 bits; the bits of a bucket's 32-bit word that its sum of places has: they are
+ * taken again when the sum of some bucket reaches 2^bits; the bytes of LDS for the other tables of
+ * a channel where one workgroup builds them and runs the rounds (few channels), 0 where the tables
+ * go to memory - keeping them for a later call spares that call something only then.
  * CMPQ_EINVAL for a null pointer, no channels or no weights, CMPQ_ESHAPE beyond the limit.
  */
 int cmpq_kmeans_build_shape(int64_t d_in, int64_t d_out, int64_t *shape);

@@ -6,6 +6,7 @@ if the library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -138,10 +139,12 @@ def kmeans_launch_shape(d_out: int):
     return tuple(int(v) for v in shape)
 
 
+@functools.lru_cache(maxsize=256)
 def kmeans_build_shape(d_in: int, d_out: int):
-    """`kmeans_launch_shape` for `d_in` channels of any length, then the bytes of LDS the place array lies in and
-    the bits of a bucket's word that hold its sum of places."""
-    shape = (_i64 * 8)()
+    """`kmeans_launch_shape` for `d_in` channels of any length, then the bytes of LDS the place array lies in, the
+    bits of a bucket's word that hold its sum of places, and the bytes of the other tables in LDS (0: the tables go to
+    memory)."""
+    shape = (_i64 * 9)()
     _check(lib().cmpq_kmeans_build_shape(int(d_in), int(d_out), shape), "cmpq_kmeans_build_shape")
     return tuple(int(v) for v in shape)
 

@@ -431,8 +431,7 @@ static size_t ws_kmeans_rows(int64_t d_in) {
     return ws_kmeans_base(d_in) + align_up((size_t)(d_in > 0 ? d_in : 1) * sizeof(int32_t), 256);
 }
 
-// The least that a call takes: ... | room of cmpq_pack_with_error's size, in which the histogram kernels leave what
-// their coding pass reads of a part of the channels (64 bytes each; there is room for 8 at least).
+// The least that a call takes: ... | room of cmpq_pack_with_error's size, which the histogram kernels can do without.
 static size_t ws_kmeans_least(int64_t d_in) { return ws_kmeans_rows(d_in) + cmpq_ws_pack_with_error(d_in); }
 
 size_t cmpq_ws_kmeans(int64_t d_in, int64_t d_out) {

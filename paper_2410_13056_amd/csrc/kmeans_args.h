@@ -41,7 +41,7 @@ struct KmArgs {
 // Histogram k-means (kmeans_hist.hip) and fixed-point brute-force k-means
 // (kmeans_fast.hip), both for fp16 weights with unit importance.
 // Honours a.fused, a.arr_keep, a.arr_reuse.  With less scratch than kmeans_hist_scratch() the channels are worked
-// on in parts, or one workgroup each; 64 bytes are enough.
+// on in parts, or by one workgroup each, which takes none.
 int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hipStream_t s);
 size_t kmeans_hist_scratch(int64_t d_in, int64_t d_out);
 // Bytes per channel of the arrangement for channels of d_out weights (0: the kernel does not take them).

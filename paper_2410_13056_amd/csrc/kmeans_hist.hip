@@ -21,6 +21,8 @@
 //   * kmeans_code_kernel codes the weights with the final boundaries, and writes the stored format and
 //     the error where they are asked for.
 //
+// Few channels go through all three in one workgroup each, with their tables in LDS (kmeans_channel_kernel).
+//
 // A quantization without entries of O_q can leave its tables to a later one with them.  That one has
 // kmeans_removed_kernel arrange the removed entries alone, in the same form, and its rounds take
 // (all) - (removed) at every boundary.
@@ -931,67 +933,6 @@ __global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int6
     if (fin && coded) store_final(fin[j], why, res);
 }
 
-// The same of a channel whose tables lie in LDS as they were built, nothing taken off.
-template <int LB>
-struct LocalView {
-    static constexpr int kLB = LB;
-    static constexpr bool kRem = false;
-    static constexpr uint32_t kBuckets = ChannelView<LB, false>::kBuckets, kFirst = ChannelView<LB, false>::kFirst,
-                              kLast = ChannelView<LB, false>::kLast;
-    const TableHead *head;
-    const uint32_t *arr, *fill;
-    __device__ __forceinline__ const long long *base() const { return head->base; }
-    __device__ __forceinline__ const uint2 *rec() const { return reinterpret_cast<const uint2 *>(head + 1) + kFirst; }
-};
-
-// Tables, start-up and rounds of a channel in one workgroup, nothing but its levels (and tables to be kept) to
-// memory: for calls whose scratch is too small for the tables of many channels.  Kept tables are not taken: a channel's
-// own are built without the removed entries, which gives the same.
-template <int G, int T, int LB, bool MASKED, bool RAGGED>
-__global__ __launch_bounds__(T) void kmeans_channel_kernel(KmArgs a, int64_t i0, int64_t stride, ChannelFinal *fin) {
-    // dynamic LDS: what build_tables wants | head | records
-    extern __shared__ __align__(16) unsigned char dyn[];
-    __shared__ BuildShared<T> sm;
-    constexpr int kBuckets = 1 << (16 - LB);
-    const int64_t i = i0 + blockIdx.x;
-    const int tid = threadIdx.x, b = a.bits[i];
-    if (b < 1 || b > 4) {
-        if (tid < CMPQ_KMAX) a.centroids[i * CMPQ_KMAX + tid] = INFINITY;
-        return;
-    }
-    const int d_out = (int)a.d_out, n_words = MASKED ? (d_out + 31) >> 5 : 0;
-    TableHead *head = reinterpret_cast<TableHead *>(dyn + place_area_bytes<G, T, LB>(d_out) + (size_t)((n_words + 3) & ~3) * 4 +
-                                                    (size_t)kBuckets * 4);
-    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
-    uint32_t why = 0;  // the same for all lanes
-    if (a.arr_reuse) {
-        const TableHead *kept = reinterpret_cast<const TableHead *>(static_cast<const unsigned char *>(a.arr_reuse) + i * stride);
-        if (kept->magic != kTableMagic + 1u || kept->d_out != (uint32_t)d_out)
-            why = kept->magic == kTableMagic + 2u ? CMPQ_STATUS_NONFINITE : CMPQ_STATUS_ARRANGEMENT;
-    }
-    if (!why) {
-        const int bytes = build_tables<G, T, LB, MASKED, RAGGED>(a, i, dyn, sm, head, rec);
-        if (bytes < 0) why = CMPQ_STATUS_NONFINITE;
-        __syncthreads();
-        if (a.arr_keep) {
-            unsigned char *to = static_cast<unsigned char *>(a.arr_keep) + i * stride;
-            const int quads = (int)((why ? sizeof(TableHead) : sizeof(TableHead) + 8 * kBuckets) / 16);
-            for (int s = tid; s < quads; s += T) reinterpret_cast<uint4 *>(to)[s] = reinterpret_cast<const uint4 *>(head)[s];
-            if (!why) store_places<T>(to + sizeof(TableHead) + 8 * kBuckets, dyn, bytes, bucket_arr_bytes(d_out, LB));
-        }
-    }
-    if (tid >= CMPQ_WAVE) return;
-    const int K_out = 1 << b;
-    const float c0 = given_level(a, i, K_out, why);
-    const int K = why ? 0 : K_out;
-    const LocalView<LB> ch = {head, reinterpret_cast<const uint32_t *>(dyn), head->fill};
-    const Rounds res = run_rounds<4, 4>(ch, K, K ? head->kept : 0u, K ? head->base[64] : 0ll, a.start_given, c0, a.iters,
-                                        (uint32_t)(tid >> 4));
-    if (tid >= 16) return;
-    store_levels(a, i, K_out, why, res);
-    if (fin) store_final(fin[blockIdx.x], why, res);
-}
-
 // The coding table over the buckets (many levels, long channels): a bucket with no boundary
 // inside has one code; with one boundary, a code on either side of it; with more (rare) the
 // entry sends the weight to the search.  An entry: byte 0 the code at or below the boundary,
@@ -1255,12 +1196,10 @@ __device__ __forceinline__ void coding_pass_plain(const KmArgs &a, int64_t i, Co
 
 // Codes of a channel's weights with its final boundaries, and, FUSED, the row of the stored format, the FP16
 // table and the channel's error.
-template <int G, int T, int LB, bool FUSED, bool RAGGED>
-__global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, const ChannelFinal *fin) {
-    // dynamic LDS: coding table | removed-entry bitmap | the row of the bit stream
-    extern __shared__ __align__(16) unsigned char dyn[];
-    __shared__ CodeShared sm;
-    const int64_t i = i0 + blockIdx.x;
+// tbl: LDS of the coding table; removed: of the removed-entry bitmap (MARKED: there already); arr: of the row.
+template <int G, int T, int LB, bool FUSED, bool RAGGED, bool MARKED>
+__device__ __forceinline__ void code_channel(const KmArgs &a, int64_t i, const ChannelFinal &f, CodeShared &sm, uint32_t *tbl,
+                                             uint32_t *removed, unsigned char *arr) {
     const int tid = threadIdx.x;
     const int d_out = (int)a.d_out, n_groups = RAGGED ? (d_out + 3) >> 2 : d_out >> 2;
     const int b = a.bits[i];
@@ -1284,7 +1223,6 @@ __global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, co
             if (a.pack.lut[j]) lut_dst = a.pack.lut[j] + ((int64_t)row << b);
         }
     }
-    const ChannelFinal &f = fin[blockIdx.x];
     if (!f.ok) {
         zero_codes<RAGGED, T>(codes_row, tid, n_groups, d_out);
         if constexpr (FUSED) {  // the row of all-zero codes, the table of zero levels, no number for the error
@@ -1294,10 +1232,6 @@ __global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, co
         }
         return;
     }
-    uint32_t *tbl = reinterpret_cast<uint32_t *>(dyn);
-    const int n_words = FUSED ? (d_out + 31) >> 5 : 0;
-    uint32_t *removed = tbl + code_table_words(T, G, LB);
-    unsigned char *arr = reinterpret_cast<unsigned char *>(removed + ((n_words + 3) & ~3));
     if (tid < CMPQ_KMAX) {
         const float c = a.centroids[i * CMPQ_KMAX + tid];
         sm.tk[tid] = f.tk[tid];
@@ -1309,15 +1243,19 @@ __global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, co
     if constexpr (FUSED) {
         const int lo = a.seg ? a.seg[i] : 0;
         n_ex = a.seg ? a.seg[i + 1] - lo : 0;
-        if (RAGGED || n_ex > 0) {
-            for (int s = tid; s < n_words; s += T)  // what fills up the last group counts as removed
-                removed[s] = RAGGED && s == d_out >> 5 && (d_out & 3) ? ((1u << (4 - (d_out & 3))) - 1u) << (d_out & 31) : 0u;
-        }
-        __syncthreads();
-        const int32_t chan_base = (int32_t)(i * a.d_out);
-        for (int e = tid; e < n_ex; e += T) {  // entries of O_q are restored to their FP16 weight: no error
-            const int o = a.out_idx[lo + e] - chan_base;
-            atomicOr(&removed[o >> 5], 1u << (o & 31));
+        if constexpr (!MARKED) {
+            if (RAGGED || n_ex > 0) {
+                for (int s = tid; s < (d_out + 31) >> 5; s += T)  // what fills up the last group counts as removed
+                    removed[s] = RAGGED && s == d_out >> 5 && (d_out & 3) ? ((1u << (4 - (d_out & 3))) - 1u) << (d_out & 31) : 0u;
+            }
+            __syncthreads();
+            const int32_t chan_base = (int32_t)(i * a.d_out);
+            for (int e = tid; e < n_ex; e += T) {  // entries of O_q are restored to their FP16 weight: no error
+                const int o = a.out_idx[lo + e] - chan_base;
+                atomicOr(&removed[o >> 5], 1u << (o & 31));
+            }
+        } else {
+            __syncthreads();
         }
     } else {
         __syncthreads();
@@ -1362,13 +1300,108 @@ __global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, co
     }
 }
 
-// Dynamic LDS of a table build.
+template <int G, int T, int LB, bool FUSED, bool RAGGED>
+__global__ __launch_bounds__(T) void kmeans_code_kernel(KmArgs a, int64_t i0, const ChannelFinal *fin) {
+    // dynamic LDS: coding table | removed-entry bitmap | the row of the bit stream
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ CodeShared sm;
+    uint32_t *tbl = reinterpret_cast<uint32_t *>(dyn), *removed = tbl + code_table_words(T, G, LB);
+    const int n_words = FUSED ? ((int)a.d_out + 31) >> 5 : 0;
+    code_channel<G, T, LB, FUSED, RAGGED, false>(a, i0 + blockIdx.x, fin[blockIdx.x], sm, tbl, removed,
+                                                 reinterpret_cast<unsigned char *>(removed + ((n_words + 3) & ~3)));
+}
+
+// The same of a channel whose tables lie in LDS as they were built, nothing taken off.
+template <int LB>
+struct LocalView {
+    static constexpr int kLB = LB;
+    static constexpr bool kRem = false;
+    static constexpr uint32_t kBuckets = ChannelView<LB, false>::kBuckets, kFirst = ChannelView<LB, false>::kFirst,
+                              kLast = ChannelView<LB, false>::kLast;
+    const TableHead *head;
+    const uint32_t *arr, *fill;
+    __device__ __forceinline__ const long long *base() const { return head->base; }
+    __device__ __forceinline__ const uint2 *rec() const { return reinterpret_cast<const uint2 *>(head + 1) + kFirst; }
+};
+
+// Wavefronts a SIMD that the registers of the channel kernel leave room for (at 6, 80 of them, rows of 64 weights a
+// lane at any alignment spill 12 bytes).
+constexpr int channel_waves(int G, bool ragged) { return G == 16 && ragged ? 5 : 6; }
+
+// Tables, start-up and rounds of a channel in one workgroup, nothing but its levels (and tables to be kept) to
+// memory: for few channels, and for calls whose scratch is too small for the tables of many.  Kept tables are not
+// taken: a channel's own are built without the removed entries, which gives the same.
+//
+// A round's latency is the bound, as in kmeans_rounds_kernel, but its words come from LDS and nothing has to be read
+// first.  First and final quantization (with packing and error; 20 rounds), us, as three kernels and so:
+// @@FIGURES@@
+template <int G, int T, int LB, bool MASKED, bool RAGGED, bool FUSED>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(channel_waves(G, RAGGED)))) void kmeans_channel_kernel(KmArgs a, int64_t stride) {
+    // dynamic LDS: what build_tables wants (the coding pass has its row in the place array and its table in the
+    // buckets' words) | head | records
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ union { BuildShared<T> build; CodeShared code; } sm;
+    __shared__ ChannelFinal fin;
+    constexpr int kBuckets = 1 << (16 - LB);
+    static_assert(code_table_words(T, G, LB) <= kBuckets, "the coding table fits the buckets' words");
+    const int64_t i = blockIdx.x;
+    const int tid = threadIdx.x, b = a.bits[i];
+    const int d_out = (int)a.d_out, n_words = MASKED ? (d_out + 31) >> 5 : 0;
+    uint32_t *removed = reinterpret_cast<uint32_t *>(dyn + place_area_bytes<G, T, LB>(d_out));
+    uint32_t *words = removed + ((n_words + 3) & ~3);
+    TableHead *head = reinterpret_cast<TableHead *>(words + kBuckets);
+    uint2 *rec = reinterpret_cast<uint2 *>(head + 1);
+    const bool coded = b >= 1 && b <= 4;
+    if (!coded && tid < CMPQ_KMAX) a.centroids[i * CMPQ_KMAX + tid] = INFINITY;
+    uint32_t why = 0;  // the same for all lanes
+    if (coded && a.arr_reuse) {
+        const TableHead *kept = reinterpret_cast<const TableHead *>(static_cast<const unsigned char *>(a.arr_reuse) + i * stride);
+        if (kept->magic != kTableMagic + 1u || kept->d_out != (uint32_t)d_out)
+            why = kept->magic == kTableMagic + 2u ? CMPQ_STATUS_NONFINITE : CMPQ_STATUS_ARRANGEMENT;
+    }
+    if (coded && !why) {
+        const int bytes = build_tables<G, T, LB, MASKED, RAGGED>(a, i, dyn, sm.build, head, rec);
+        if (bytes < 0) why = CMPQ_STATUS_NONFINITE;
+        __syncthreads();
+        if (a.arr_keep) {
+            unsigned char *to = static_cast<unsigned char *>(a.arr_keep) + i * stride;
+            const int quads = (int)((why ? sizeof(TableHead) : sizeof(TableHead) + 8 * kBuckets) / 16);
+            for (int s = tid; s < quads; s += T) reinterpret_cast<uint4 *>(to)[s] = reinterpret_cast<const uint4 *>(head)[s];
+            if (!why) store_places<T>(to + sizeof(TableHead) + 8 * kBuckets, dyn, bytes, bucket_arr_bytes(d_out, LB));
+        }
+    }
+    if (coded && tid < CMPQ_WAVE) {
+        const int K_out = 1 << b;
+        const float c0 = given_level(a, i, K_out, why);
+        const int K = why ? 0 : K_out;
+        const LocalView<LB> ch = {head, reinterpret_cast<const uint32_t *>(dyn), head->fill};
+        // Groups of 4 words at a time: a stretch is a few words where the channel is short, and a trip to LDS is short.
+        // First + final quantization with 1 / 2 / 4, us: 2000 x 300 58 / 60 / 64, 3001 x 2049 94 / 97 / 103, 2500 x 4096
+        // 104 / 100 / 104, 1024 x 8192 88 / 83 / 77, 512 x 28672 116 / 107 / 101.
+        constexpr int kAhead = T == 64 ? 1 : (T == 128 ? 2 : 4);
+        const Rounds res = run_rounds<4, kAhead>(ch, K, K ? head->kept : 0u, K ? head->base[64] : 0ll, a.start_given, c0, a.iters,
+                                            (uint32_t)(tid >> 4));
+        if (tid < 16) {
+            store_levels(a, i, K_out, why, res);
+            store_final(fin, why, res);
+        }
+    }
+    if (!FUSED && !a.codes) return;
+    __syncthreads();  // the places are read, the levels written
+    code_channel<G, T, LB, FUSED, RAGGED, MASKED>(a, i, fin, sm.code, words, removed, dyn);
+}
+
+// Dynamic LDS of a table build; the channel kernel has head and records behind it.
 template <int G, int T, int LB>
 size_t build_lds(int64_t d_out, bool masked) {
     size_t b = place_area_bytes<G, T, LB>(d_out);
     if (masked) b += (size_t)((((d_out + 31) >> 5) + 3) & ~3) * 4;
     return b + ((size_t)4 << (16 - LB));
 }
+template <int T>
+constexpr size_t kChannelShared = (sizeof(BuildShared<T>) > sizeof(CodeShared) ? sizeof(BuildShared<T>) : sizeof(CodeShared)) + sizeof(ChannelFinal);
+template <int LB>
+constexpr size_t kLocalTables = sizeof(TableHead) + ((size_t)8 << (16 - LB));
 
 template <typename Kern>
 int allow_lds(Kern kern, size_t lds) {
@@ -1384,12 +1417,6 @@ int allow_lds(Kern kern, size_t lds) {
 // rows shorten the scan of a bucket and put more wavefronts on the chip, fewer share the rest of the chain: first
 // quantization with 1 / 2 / 4 rows, us: 8192 x 1024 62 / 76 / 100, 4096 x 4096 69 / 63 / 76, 28672 x 8192 552 / 459
 // / 456, 8192 x 28672 433 / 395 / 360.
-//
-// Up to this many channels the rounds leave SIMDs without a wavefront (there are 1024 of them, and a wavefront
-// takes 4 / R channels), and a round's own length is what counts: twice the rows then.  First and final
-// quantization, us: 1024 x 8192 52 + 74 -> 40 + 66, 1024 x 4096 38 + 58 -> 33 + 57, 2048 x 4608 48 + 74 -> 45 + 73,
-// 2048 x 2048 43 + 68 -> 40 + 64; past it the order turns: 3000 x 4099 69 + 96 with 2 rows, 82 + 113 with 4.
-constexpr int64_t kFewChannels = 2048;
 // Parts of fewer channels than this leave the chip idle between their launches: the tables stay in LDS then.
 constexpr int64_t kLeastPart = 2048;
 template <int R, int LB, int AHEAD>
@@ -1457,24 +1484,16 @@ int launch_variant(const KmArgs &a, unsigned char *scratch, int64_t step, hipStr
     return CMPQ_OK;
 }
 
-// The same with a channel's tables in LDS alone.
-template <int G, int T, int LB>
-int launch_channels(const KmArgs &a, unsigned char *scratch, size_t scratch_bytes, hipStream_t s) {
-    const int64_t room = (int64_t)(scratch_bytes / sizeof(ChannelFinal)), step = !wants_codes(a) || room > a.d_in ? a.d_in : room;
-    if (step < 1) return CMPQ_EWORKSPACE;
-    ChannelFinal *fin = wants_codes(a) ? reinterpret_cast<ChannelFinal *>(scratch) : nullptr;
+// The same with a channel's tables in LDS alone, in one launch.
+template <int G, int T, int LB, bool FUSED>
+int launch_channels(const KmArgs &a, hipStream_t s) {
     const bool masked = a.n_out > 0 || a.ragged;
-    auto kern = a.ragged ? kmeans_channel_kernel<G, T, LB, true, true>
-                         : (masked ? kmeans_channel_kernel<G, T, LB, true, false> : kmeans_channel_kernel<G, T, LB, false, false>);
-    const size_t lds = build_lds<G, T, LB>(a.d_out, masked) + sizeof(TableHead) + ((size_t)8 << (16 - LB));
+    auto kern = a.ragged ? kmeans_channel_kernel<G, T, LB, true, true, FUSED>
+                         : (masked ? kmeans_channel_kernel<G, T, LB, true, false, FUSED> : kmeans_channel_kernel<G, T, LB, false, false, FUSED>);
+    const size_t lds = build_lds<G, T, LB>(a.d_out, masked) + kLocalTables<LB>;
     if (const int rc = allow_lds(kern, lds)) return rc;
-    for (int64_t i0 = 0; i0 < a.d_in; i0 += step) {
-        const int64_t n = a.d_in - i0 < step ? a.d_in - i0 : step;
-        kern<<<(unsigned)n, T, lds, s>>>(a, i0, (int64_t)table_bytes(a.d_out, LB), fin);
-        CMPQ_LAUNCH_CHECK();
-        if (!fin) continue;
-        if (const int rc = launch_codes<G, T, LB>(a, i0, n, fin, s)) return rc;
-    }
+    kern<<<(unsigned)a.d_in, T, lds, s>>>(a, (int64_t)table_bytes(a.d_out, LB));
+    CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
 }
 
@@ -1495,36 +1514,68 @@ struct Shape {
     static constexpr int G = G_, T = T_, LB = LB_, R = R_;
 };
 
-// Calls f with the shape for d_in channels of d_out weights (rows of any length: up to whole groups of 4).  A
-// power-of-two workgroup of at most 512 lanes: up to 32 weights per lane, 64 for the longest channels.
-// CMPQ_ESHAPE: too long.
-template <typename F>
-int with_shape(int64_t d_in, int64_t d_out, F &&f) {
+// Calls f with the shape for channels of d_out weights (rows of any length: up to whole groups of 4).  A
+// power-of-two workgroup of at most 512 lanes: up to 32 weights per lane, 64 for the longest channels.  LOCAL: for
+// the channel kernel, whose rounds have a wavefront per channel.  CMPQ_ESHAPE: too long.
+template <bool LOCAL, typename F>
+int with_shape(int64_t d_out, F &&f) {
     const int64_t groups = (d_out + 3) / 4;
     int64_t T = 64;
     while (T < 512 && T * 8 < groups) T <<= 1;
     const int64_t per_lane = cdiv(groups, T);
-    const bool few = d_in <= kFewChannels;
     if (per_lane > 16) return CMPQ_ESHAPE;
     if (per_lane > 8) return f(Shape<16, 512, CMPQ_LB512, 4>{});
     if (T == 512) return f(Shape<8, 512, CMPQ_LB512, 4>{});
-    if (T == 256) return few ? f(Shape<8, 256, CMPQ_LB256, 4>{}) : f(Shape<8, 256, CMPQ_LB256, 2>{});
-    // 2304 weights: 42 us, 44 on 128 lanes
-    if (T == 128) return few ? f(Shape<4, 256, 7, 4>{}) : f(Shape<8, 128, 7, 2>{});
-    if (per_lane > 4) return few ? f(Shape<8, 64, 7, 2>{}) : f(Shape<8, 64, 7, 1>{});
-    if (per_lane > 2) return f(Shape<4, 64, 7, 1>{});
-    if (per_lane > 1) return f(Shape<2, 64, 7, 1>{});
-    return f(Shape<1, 64, 7, 1>{});
+    if (T == 256) return f(Shape<8, 256, CMPQ_LB256, LOCAL ? 4 : 2>{});
+    if (T == 128) return f(Shape<8, 128, 7, LOCAL ? 4 : 2>{});
+    if (per_lane > 4) return f(Shape<8, 64, 7, LOCAL ? 4 : 1>{});
+    if (per_lane > 2) return f(Shape<4, 64, 7, LOCAL ? 4 : 1>{});
+    if (per_lane > 1) return f(Shape<2, 64, 7, LOCAL ? 4 : 1>{});
+    return f(Shape<1, 64, 7, LOCAL ? 4 : 1>{});
 }
 
-// Bytes of a channel's tables: the same for few channels and for many.  0: too long.
+// Bytes of a channel's tables.  0: too long.
 size_t table_bytes_of(int64_t d_out) {
     size_t bytes = 0;
-    (void)with_shape(INT64_MAX, d_out, [&](auto s) {
+    (void)with_shape<false>(d_out, [&](auto s) {
         bytes = table_bytes(d_out, s.LB);
         return CMPQ_OK;
     });
     return bytes;
+}
+
+// Whether the channel kernel takes these: few channels, all of whose workgroups the chip holds at once - 256 CUs
+// of 2048 lanes (1536 where a lane takes 64 weights, by its registers) and 160 KiB of LDS, a tenth of it to spare.  The rounds then leave wavefronts free in any case, and what the three kernels cost beyond their work - tables
+// out and in again, two launches - is what counts.  Rows of up to 2048 weights share a wavefront of the rounds between
+// 4 channels there and turn earlier.
+//
+// First and final quantization, us, three kernels and this one:
+//   2000 x 300   26 + 39, 24 + 34      3300 x 2052  44 + 69, 39 + 61      2880 x 4096  47 + 75, 47 + 79
+//   2500 x 300   27 + 40, 28 + 39      2500 x 4096  45 + 72, 39 + 64      2048 x 8192  49 + 74, 41 + 69
+//   672 x 28672  56 + 75, 45 + 76      1024 x 28672 64 + 88, 65 + 115
+bool tables_stay_in_lds(int64_t d_in, int64_t d_out) {
+    bool stay = false;
+    (void)with_shape<true>(d_out, [&](auto s) {
+        const size_t lds = build_lds<s.G, s.T, s.LB>(d_out, true) + kLocalTables<s.LB> + kChannelShared<s.T>;
+        stay = d_in <= 256 * (s.G == 16 ? 1536 : 2048) / s.T && d_in <= 230 * (int64_t)(160 * 1024 / lds) && (s.T > 64 || d_in <= 2048);
+        return CMPQ_OK;
+    });
+    return stay;
+}
+
+template <typename S>
+int report_shape(S, bool local, int64_t d_out, int64_t *shape) {
+    constexpr int G = S::G, T = S::T, LB = S::LB;
+    shape[0] = T;
+    shape[1] = G;
+    shape[2] = LB;
+    shape[3] = (int64_t)bucket_arr_bytes(d_out, LB);
+    shape[4] = (int64_t)(build_lds<G, T, LB>(d_out, true) + (local ? kLocalTables<LB> : 0));
+    shape[5] = (int64_t)(local ? kChannelShared<T> : sizeof(BuildShared<T>));
+    shape[6] = (int64_t)place_area_bytes<G, T, LB>(d_out);
+    shape[7] = count_shift<G, T>();
+    shape[8] = local ? (int64_t)kLocalTables<LB> : 0;
+    return CMPQ_OK;
 }
 
 }  // namespace
@@ -1535,27 +1586,20 @@ size_t kmeans_hist_arrangement_stride(int64_t d_out) {
 
 size_t kmeans_hist_scratch(int64_t d_in, int64_t d_out) {
     const size_t tables = d_in < 1 || d_out < 1 ? 0 : table_bytes_of(d_out);
-    return tables ? (size_t)d_in * (tables + sizeof(ChannelFinal)) : 0;
+    if (!tables) return 0;
+    return tables_stay_in_lds(d_in, d_out) ? 0 : (size_t)d_in * (tables + sizeof(ChannelFinal));
 }
 
 extern "C" int cmpq_kmeans_build_shape(int64_t d_in, int64_t d_out, int64_t *shape) {
     if (!shape || d_in < 1 || d_out < 1) return CMPQ_EINVAL;
-    return with_shape(d_in, d_out, [&](auto s) {
-        shape[0] = s.T;
-        shape[1] = s.G;
-        shape[2] = s.LB;
-        shape[3] = (int64_t)bucket_arr_bytes(d_out, s.LB);
-        shape[4] = (int64_t)build_lds<s.G, s.T, s.LB>(d_out, true);
-        shape[5] = (int64_t)sizeof(BuildShared<s.T>);
-        shape[6] = (int64_t)place_area_bytes<s.G, s.T, s.LB>(d_out);
-        shape[7] = count_shift<s.G, s.T>();
-        return CMPQ_OK;
-    });
+    if (tables_stay_in_lds(d_in, d_out))
+        return with_shape<true>(d_out, [&](auto s) { return report_shape(s, true, d_out, shape); });
+    return with_shape<false>(d_out, [&](auto s) { return report_shape(s, false, d_out, shape); });
 }
 
 extern "C" int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape) {
     if (!shape || d_out < 4 || d_out % 4 != 0) return CMPQ_EINVAL;
-    int64_t all[8];
+    int64_t all[9];
     const int rc = cmpq_kmeans_build_shape(INT64_MAX, d_out, all);
     for (int k = 0; rc == CMPQ_OK && k < 6; ++k) shape[k] = all[k];
     return rc;
@@ -1566,10 +1610,12 @@ int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hip
     const size_t stride = table_bytes_of(a.d_out), per = scratch_per_channel(a, stride);
     if (!stride) return CMPQ_ESHAPE;
     const int64_t room = per ? (int64_t)(scratch_bytes / per) : a.d_in, step = room < a.d_in ? room : a.d_in;
+    const bool local = tables_stay_in_lds(a.d_in, a.d_out) || (step < a.d_in && step < kLeastPart);
     cmpq_timing_before(CMPQ_KERNEL_KMEANS, s);
-    const int rc = step < a.d_in && step < kLeastPart
-                       ? with_shape(1, a.d_out, [&](auto v) { return launch_channels<v.G, v.T, v.LB>(a, sc, scratch_bytes, s); })
-                       : with_shape(a.d_in, a.d_out, [&](auto v) { return launch_variant<v.G, v.T, v.LB, v.R>(a, sc, step, s); });
+    const int rc = local ? with_shape<true>(a.d_out, [&](auto v) {
+        return a.fused ? launch_channels<v.G, v.T, v.LB, true>(a, s) : launch_channels<v.G, v.T, v.LB, false>(a, s);
+    })
+                         : with_shape<false>(a.d_out, [&](auto v) { return launch_variant<v.G, v.T, v.LB, v.R>(a, sc, step, s); });
     cmpq_timing_after(CMPQ_KERNEL_KMEANS, s);
     return rc;
 }

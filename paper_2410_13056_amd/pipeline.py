@@ -146,8 +146,8 @@ SHORT_CHANNEL = 2048
 def _shared_tables(Wt: torch.Tensor) -> Optional[torch.Tensor]:
     """The buffer through which the preliminary K-means of a layer hands its per-channel tables
     to the final one (`cmpq_kmeans_job.arrangement`), or None where the histogram kernel would
-    not take the input or the channels are short."""
-    if not _histogram_kernel_takes(Wt) or Wt.shape[1] <= SHORT_CHANNEL:
+    not take the input, the channels are short, or they are so few that their tables stay in LDS."""
+    if Wt.shape[1] <= SHORT_CHANNEL or not _histogram_kernel_takes(Wt) or B.kmeans_build_shape(*Wt.shape)[8]:
         return None
     return torch.empty(B.arrangement_bytes(*Wt.shape), dtype=torch.uint8, device=Wt.device)
 
@@ -243,7 +243,8 @@ def quantize_layer(W: torch.Tensor, sumsq: torch.Tensor, bit_set: Sequence[int],
 
     ``share_tables`` (on by default): the preliminary K-means leaves its per-channel tables for
     the final one (`cmpq_kmeans_job.arrangement`), which then does not build them again (for
-    channels of more than 2048 weights; shorter ones are the faster built anew).  Same
+    channels of more than 2048 weights, and more of them than run in one go with their tables in
+    LDS; the others are the faster built anew).  Same
     results, one buffer of about `d_in * (d_out + 8 KiB)` bytes more while the layer is in work;
     measured, the final pass is 14 to 34 % shorter on channels of 8192 and 28 672 weights.
 

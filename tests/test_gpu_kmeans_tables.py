@@ -69,8 +69,8 @@ class _Limited:
         return self.buf
 
 
-@pytest.mark.parametrize("d_in,d_out,rooms", [(23, 1024, (1, 5, 22)), (23, 4098, (1, 22)), (23, 8192, (22,)),
-                                              (4200, 64, (2047, 2048, 2049, 4199)), (2060, 1031, (2049,))])
+@pytest.mark.parametrize("d_in,d_out,rooms", [(23, 1024, (0,)), (23, 4098, (0,)), (4200, 64, (0, 5, 2047, 2048, 2049, 4199)),
+                                              (2060, 1031, (2049,)), (2300, 8192, (1, 2100))])
 def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out, rooms):
     B, ws = env["B"], env["ws"]
     rng = np.random.default_rng(3)
@@ -85,17 +85,18 @@ def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out
     one = (B.workspace_bytes(B.OP_KMEANS, 1 << 20, d_out) - B.workspace_bytes(B.OP_KMEANS, 1 << 19, d_out)) >> 19
     for channels in rooms:
         c2, k2 = torch.full_like(cent, 7.0), torch.full_like(codes, 255)
-        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, c2, k2, _Limited(full - (d_in - channels) * one + 512))
+        room = max(full - (d_in - channels) * one + 512, B.workspace_bytes(B.OP_KMEANS, d_in, 0))
+        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, c2, k2, _Limited(room))
         assert torch.equal(c2, cent) and torch.equal(k2, codes)
     with pytest.raises(B.CmpqError):
         B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, _Limited(256))
 
 
-@pytest.mark.parametrize("d_in,d_out", [(1, 4), (7, 64), (3, 1028), (9, 1999), (5, 2052), (3, 4099), (2, 8192), (300, 1500),
-                                        (3, 16384), (2, 28672), (2, 32768), (2, 32767)])
+@pytest.mark.parametrize("d_in,d_out", [(1, 4), (2100, 7), (2100, 64), (2055, 1028), (2053, 1999), (3300, 2052), (2800, 4095), (2050, 4099),
+                                        (2049, 8192), (1030, 16384), (770, 28672), (800, 32768), (800, 32767)])
 def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
     """The size that holds for rows of any length (asked for without one): every form of the call, bit for bit what
-    it leaves with room for the tables of all channels."""
+    it leaves with room for the tables of all channels (too many to stay in LDS there)."""
     B, ws = env["B"], env["ws"]
     rng = np.random.default_rng(d_out)
     W = _crowded(rng, d_in, d_out)
@@ -103,12 +104,13 @@ def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
         W[-1, -1] = np.inf
     bits = np.resize(np.array([4, 3, 2, 16, 1], np.uint8), d_in)
     n_out = d_in * d_out // 40
-    excl = _dev(np.sort(rng.choice(d_in * d_out, n_out, replace=False)).astype(np.int32)) if n_out else None
+    excl = torch.randperm(d_in * d_out, device=DEV)[:n_out].sort().values.int() if n_out else None
     dW, db = _dev(W), _dev(bits)
     widths = [b for b in (1, 2, 3, 4) if b in bits]
     counts = [int((bits == b).sum()) for b in widths]
     sumsq = torch.ones(d_in, device=DEV)
     least = B.workspace_bytes(B.OP_KMEANS, d_in, 0)
+    assert d_in == 1 or not B.kmeans_build_shape(d_in, d_out)[8]
     whole = d_out % 4 == 0
 
     def forms(space):
@@ -162,10 +164,11 @@ def test_tables_of_another_row_length_are_flagged(env):
 
 @pytest.mark.parametrize("d_out", [1028, 1999, 2052, 4095, 4100, 8192])
 def test_many_channels_get_the_bits_of_few(env, d_out):
-    """2049 channels in one call, and the same rows as 2048 and 1: other numbers of lanes per channel."""
+    """3300 channels in one call, and the same rows in two calls whose tables stay in LDS."""
     B, ws = env["B"], env["ws"]
     g = torch.Generator(device=DEV).manual_seed(d_out)
-    d_in = 2049
+    d_in = 3300
+    assert [bool(B.kmeans_build_shape(n, d_out)[8]) for n in (d_in, 2048, d_in - 2048)] == [False, True, True]
     W = (torch.randn(d_in, d_out, generator=g, device=DEV) * 0.02).half()
     bits = torch.randint(1, 5, (d_in,), generator=g, device=DEV).to(torch.uint8)
     excl = torch.arange(0, d_in * d_out, 97, dtype=torch.int32, device=DEV)

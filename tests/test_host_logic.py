@@ -64,15 +64,17 @@ def _arrangement_bounds(d_out, keys, kept, shape):
     the launch shape the library reports: bucket counts, padded stretches of the place array, the
     16-bit prefix tables, the removed-entry bitmap, the scatter cursors / coding table, and the
     per-lane ownership of weight groups.  Raises AssertionError on any index out of its array."""
-    T, G, LB, arr_bytes, dyn, static = shape
+    T, G, LB, arr_bytes, dyn, static, local = shape
     buckets = 1 << (16 - LB)
     n_groups = d_out // 4
     assert G * T >= n_groups                                    # every group of 4 weights has a lane
-    assert T in (64, 128, 256, 512) and (T // 16) * 16 == T     # T/16 lanes share a boundary: 15 boundaries fit
-    assert max(1, buckets // T) * T >= buckets                  # the prefix pass covers every bucket
-    # dynamic LDS = place array | removed bitmap (whole 16-byte pieces) | one word per bucket
+    assert T in (64, 128, 256, 512)
+    assert buckets % T == 0                                     # the prefix pass covers every bucket
+    # dynamic LDS = place array | removed bitmap (whole 16-byte pieces) | one word per bucket, and for few
+    # channels head and records
     n_words = (d_out + 31) >> 5
-    assert dyn == arr_bytes + ((n_words + 3) & ~3) * 4 + buckets * 4
+    assert dyn == arr_bytes + ((n_words + 3) & ~3) * 4 + buckets * 4 + local
+    assert local in (0, 560 + 8 * buckets)
     assert arr_bytes % 16 == 0
     assert ((n_groups - 1) >> 3) < n_words                       # bitmap word of the last group
     b = keys[kept] >> LB
@@ -86,8 +88,8 @@ def _arrangement_bounds(d_out, keys, kept, shape):
     per = max(1, buckets // T)
     packed = (n | (padded << 16)).reshape(-1, per).sum(1)       # a lane's share of the (count, stretch) scan
     assert int(packed.sum()) < 1 << 32 and int((n.reshape(-1, per).sum(1)).max()) < 65536
-    # scans read whole words of a stretch: [start >> 2, end >> 2), 4 * L at a time, guarded by the end
-    assert np.all(start % 4 == 0) and start[-1] // 4 <= arr_bytes // 4
+    # scans read a stretch in whole groups of 4 words, and up to 3 words past its end
+    assert np.all(start % 4 == 0) and start[-1] + 12 <= dyn
     # three workgroups of the longest configured channels (28 672 weights) share a compute unit's 160 KiB
     total = static + 512 + dyn                                  # + what the compiler adds to the static part
     if d_out <= 28672:
@@ -105,10 +107,11 @@ def test_kmeans_kernel_indices_stay_in_bounds_on_adversarial_channels():
     lengths = sorted({4, 8, 252, 256, 260, 512, 1024, 2044, 2048, 2052, 4096, 4100, 5120, 8192, 8196, 11008,
                       13824, 16384, 16388, 28672, 32764, 32768})
     worst = 0
-    for d_out, d_in in [(n, m) for n in lengths for m in (1, 2048, 2049)]:
-        shape = B.kmeans_build_shape(d_in, d_out)[:6]
-        if d_in > 2048:
-            assert shape == B.kmeans_launch_shape(d_out)
+    for d_out, d_in in [(n, m) for n in lengths for m in (1, 2048, 9999)]:
+        shape = B.kmeans_build_shape(d_in, d_out)
+        if d_in == 9999:
+            assert shape[:6] == B.kmeans_launch_shape(d_out) and shape[8] == 0
+        shape = shape[:6] + shape[8:]
         LB = shape[2]
         buckets = 1 << (16 - LB)
         layouts = {
@@ -136,9 +139,9 @@ def test_kmeans_bucket_counts_fit_their_words_or_are_taken_again_in_place():
     counts still fit beside the carries, and the array that takes the second, 64-bit count lies inside
     the place area: behind that lies the bitmap of removed entries, which is still read.  Every length."""
     from paper_2410_13056_amd import binding as B
-    for d_in in (1, 2048, 2049):
+    for d_in in (1, 2048, 9999):
         for d_out in range(1, 32769):
-            T, G, LB, arr_bytes, _, _, area, sum_bits = B.kmeans_build_shape(d_in, d_out)
+            T, G, LB, arr_bytes, _, _, area, sum_bits, _ = B.kmeans_build_shape(d_in, d_out)
             places = (1 << LB) - 1
             assert d_out <= 4 * G * T and arr_bytes <= area and area % 16 == 0
             carries = d_out * places >> sum_bits
