@@ -627,8 +627,10 @@ struct BucketPlaces {
             const uint32_t len = in ? v1 - v0 : 0u;
             any_rem = __ballot(len != 0) != 0ull;
             rem.fetch(ch.rem_arr + (len ? v0 : 0u), len, r, ch.fill);
-            rem.wait();
         }
+        // a copy of what was loaded first, moved up among the loads, would wait for it before the rest go out
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (REM) rem.wait();
         all.wait();
     }
     // N + D = twice the number of places at or below pl; A as in below_key.
@@ -841,6 +843,9 @@ __device__ __forceinline__ float given_level(const KmArgs &a, int64_t i, int K, 
     return c;
 }
 
+// Wavefronts a SIMD that this much LDS each leaves room for (160 KiB a CU): registers are not saved for more.
+constexpr int rounds_waves(uint32_t lds) { return (int)((160 * 1024 / lds + 3) / 4); }
+
 // Start-up and rounds of 4 / R channels on one wavefront.  A channel has R rows of 16 lanes; lane p of a
 // row carries the level at sorted position p and the boundary above it.  All rows of a channel hold the same
 // state; they share out the words of a boundary's bucket.  Sharing a wavefront is what makes a round
@@ -849,7 +854,7 @@ __device__ __forceinline__ float given_level(const KmArgs &a, int64_t i, int K, 
 // Bound by that chain: about 1400 cycles of instructions and a trip to memory for the words of a bucket (800
 // cycles; the records come from LDS, 150).
 template <int R, int LB, int AHEAD, bool REM>
-__global__ __launch_bounds__(CMPQ_WAVE) void kmeans_rounds_kernel(KmArgs a, int64_t i0, int64_t n_chan,
+__global__ __launch_bounds__(CMPQ_WAVE) __attribute__((amdgpu_waves_per_eu(1, rounds_waves(4 / R * ChannelView<LB, REM>::kBytes)))) void kmeans_rounds_kernel(KmArgs a, int64_t i0, int64_t n_chan,
                                                                  const unsigned char *tables, int64_t stride,
                                                                  const unsigned char *removed, ChannelFinal *fin) {
     const int lane = threadIdx.x;
