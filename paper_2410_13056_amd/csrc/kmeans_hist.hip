@@ -176,6 +176,16 @@ __device__ __forceinline__ void count_buckets(const uint32_t (&keys)[2 * G], con
     }
 }
 
+// Keeps what one pass over the keys works out (bucket and bitmap addresses) from being held for the next: of 64
+// registers, the 32 keys of a lane of the longest channels leave no room for it.
+template <int G>
+__device__ __forceinline__ int next_pass(uint32_t (&keys)[2 * G], int tid) {
+#pragma unroll
+    for (int k = 0; k < 2 * G; ++k) asm("" : "+v"(keys[k]));
+    asm("" : "+v"(tid));
+    return tid;
+}
+
 // Puts the place of every kept weight into its bucket's stretch of the byte array.
 template <int G, int T, int LB, bool MASKED>
 __device__ __forceinline__ void scatter_places(const uint32_t (&keys)[2 * G], const uint32_t *removed,
@@ -226,11 +236,14 @@ __device__ __forceinline__ uint32_t write_records(PrefixShared<T> &sm, const uin
     }
     // sums inside a run of equal sign and exponent (its kSeg lanes are neighbours)
     int u_incl = u_loc;
-#pragma unroll
-    for (int d = 1; d < kSeg; d <<= 1) {
-        const int up = __shfl_up(u_incl, d, CMPQ_WAVE);
+    static_assert(kSeg <= 8, "inside a row of 16 lanes");
+    auto from_below = [&](auto d) {
+        const int up = __builtin_amdgcn_update_dpp(0, u_incl, 0x110 + d, 0xF, 0xF, true);  // row_shr:d
         if ((lane & (kSeg - 1)) >= d) u_incl += up;
-    }
+    };
+    if constexpr (kSeg > 1) from_below(std::integral_constant<int, 1>{});
+    if constexpr (kSeg > 2) from_below(std::integral_constant<int, 2>{});
+    if constexpr (kSeg > 4) from_below(std::integral_constant<int, 4>{});
     if ((lane & (kSeg - 1)) == kSeg - 1) {
         bucket_scale<LB>((uint32_t)b0, mant, sh);
         sm.run[(b0 << LB) >> 10] = (long long)((unsigned long long)(long long)u_incl << sh);
@@ -330,7 +343,7 @@ __device__ __forceinline__ int build_tables(const KmArgs &a, int64_t i, unsigned
         }
         __syncthreads();
     }
-    count_buckets<G, T, LB, MASKED, kShift>(keys, removed, cursor, tid, n_groups);
+    count_buckets<G, T, LB, MASKED, kShift>(keys, removed, cursor, next_pass<G>(keys, tid), n_groups);
     __syncthreads();
     uint32_t n[kPer], l[kPer], start[kPer], total;
 #pragma unroll
@@ -346,7 +359,7 @@ __device__ __forceinline__ int build_tables(const KmArgs &a, int64_t i, unsigned
             __syncthreads();
             for (int s = tid; s < kBuckets; s += T) wide[s] = 0;
             __syncthreads();
-            count_buckets<G, T, LB, MASKED, 32>(keys, removed, wide, tid, n_groups);
+            count_buckets<G, T, LB, MASKED, 32>(keys, removed, wide, next_pass<G>(keys, tid), n_groups);
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < kPer; ++r) {
@@ -362,7 +375,7 @@ __device__ __forceinline__ int build_tables(const KmArgs &a, int64_t i, unsigned
 #pragma unroll
     for (int r = 0; r < kPer; ++r) cursor[tid * kPer + r] = start[r];
     __syncthreads();
-    scatter_places<G, T, LB, MASKED>(keys, removed, cursor, arr, tid, n_groups);
+    scatter_places<G, T, LB, MASKED>(keys, removed, cursor, arr, next_pass<G>(keys, tid), n_groups);
     __syncthreads();
     if (tid == 0) {
         head->magic = kTableMagic + 1u;
@@ -382,9 +395,10 @@ __device__ __forceinline__ void store_places(void *to, const unsigned char *arr,
 
 // The tables of one channel, built in LDS.  Bound by LDS (an atomic, a returning atomic and a byte store to
 // scattered addresses per weight: 6.7 clocks a wavefront instruction, two thirds of them bank conflicts) and
-// by what it reads and writes: 2 B a weight in, 1.1 B and 8 B a bucket out.  8192 x 28672 in 219 us = 3.9 TB/s,
-// LDS busy 61 % of the time.  64 registers: 8 wavefronts a SIMD, so that one workgroup's fetch runs beside the
-// others' LDS passes.  Counting in 32 bits where that is enough halves the LDS words of a count.
+// by what it reads and writes: 2 B a weight in, 1.1 B and 8 B a bucket out.  8192 x 28672 in 208 us, 220 with removed
+// entries.  64 registers: 8 wavefronts a SIMD, so that one workgroup's fetch runs beside the others' LDS passes; nothing
+// may spill (231 and 307 us with 32 and 80 bytes of scratch a lane, written and read with the tables).  Counting in 32
+// bits where that is enough halves the LDS words of a count.
 template <int G, int T, int LB, bool MASKED, bool RAGGED>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8, 8))) void kmeans_build_kernel(KmArgs a, int64_t i0, unsigned char *tables, int64_t stride) {
     extern __shared__ __align__(16) unsigned char dyn[];

@@ -154,6 +154,31 @@ def test_kmeans_bucket_counts_fit_their_words_or_are_taken_again_in_place():
         B.kmeans_build_shape(0, 64)
 
 
+def test_kmeans_kernels_use_no_scratch_memory():
+    """The table build is held to 64 registers; what does not fit would go out to memory with the tables.
+    Read from the metadata of the code objects built here."""
+    import re
+    import tempfile
+
+    import pytest
+    from paper_2410_13056_amd import binding as B
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        pytest.skip("llvm-readelf is not there")
+    B.lib()
+    blob = open(B.LIB_PATH, "rb").read()
+    scratch = {}
+    for m in list(re.finditer(rb"\x7fELF", blob))[1:]:
+        with tempfile.NamedTemporaryFile() as f:
+            f.write(blob[m.start():])
+            f.flush()
+            notes = subprocess.run([readelf, "--notes", f.name], capture_output=True, text=True).stdout
+        for name, size in re.findall(r"\.name:\s+(\S+)\n(?:.*\n)*?.*\.private_segment_fixed_size:\s+(\d+)", notes):
+            scratch[name] = int(size)
+    ours = {n: s for n, s in scratch.items() if re.search(r"kmeans_(build|removed|rounds|code|channel)_kernel", n)}
+    assert len(ours) > 50 and not any(ours.values()), {n: s for n, s in ours.items() if s}
+
+
 def test_bare_barriers_state_both_waits():
     """A bare s_barrier (unlike __syncthreads) waits for nothing: where buffers change hands at one, the
     line before it has to wait for the wavefront's loads into LDS and for its reads from LDS."""
