@@ -279,6 +279,13 @@ def extract_weight_outliers(W: torch.Tensor, centroids: Optional[torch.Tensor], 
            "cmpq_extract_outliers(weights)")
 
 
+def _kmeans_workspace_bytes(W: torch.Tensor, d_in: int, d_out: int, elem_weight: Optional[torch.Tensor], init: int,
+                            algorithm: Optional[int]) -> int:
+    """What a K-means call works in: room for tables only where the histogram kernels run."""
+    tables = W.dtype == torch.float16 and elem_weight is None and (algorithm != KMEANS_DIRECT or init == INIT_GIVEN)
+    return workspace_bytes(OP_KMEANS, d_in, d_out if tables else 0)
+
+
 def kmeans_quantize(W: torch.Tensor, bits: torch.Tensor, out_idx: Optional[torch.Tensor], n_out: int,
                     elem_weight: Optional[torch.Tensor], iters: int, centroids: torch.Tensor,
                     codes: torch.Tensor, ws: Workspace, status: Optional[torch.Tensor] = None,
@@ -286,7 +293,7 @@ def kmeans_quantize(W: torch.Tensor, bits: torch.Tensor, out_idx: Optional[torch
                     arrangement: Optional[torch.Tensor] = None, arrangement_use: int = ARRANGEMENT_NONE) -> None:
     """`cmpq_kmeans_quantize`; with `algorithm` or `arrangement` given, `cmpq_kmeans_quantize_job`."""
     d_in, d_out, ldw = _rows(W)
-    buf = ws.get(workspace_bytes(OP_KMEANS, d_in, d_out))
+    buf = ws.get(_kmeans_workspace_bytes(W, d_in, d_out, elem_weight, init, algorithm))
     if algorithm is None and arrangement is None:
         _check(lib().cmpq_kmeans_quantize(_ptr(W), _dtype(W), d_in, d_out, ldw, _ptr(bits), _ptr(out_idx),
                                           int(n_out), _ptr(elem_weight), int(iters), int(init), _ptr(centroids),
@@ -324,7 +331,7 @@ def kmeans_quantize_pack(W: torch.Tensor, bits: torch.Tensor, out_idx: Optional[
     pk = (_vp * n)(*[_ptr(t) for t in packed])
     ci = (_vp * n)(*[_ptr(t) for t in chan_idx])
     lt = (_vp * n)(*[_ptr(t) for t in lut])
-    buf = ws.get(workspace_bytes(OP_KMEANS, d_in, d_out))
+    buf = ws.get(_kmeans_workspace_bytes(W, d_in, d_out, elem_weight, init, algorithm))
     c = ctypes.cast
     job = KmeansJob(_ptr(W), _dtype(W), d_in, d_out, ldw, _ptr(bits), _ptr(out_idx), int(n_out),
                     _ptr(elem_weight), int(iters), int(init), _ptr(centroids), _ptr(codes), _ptr(status),

@@ -244,9 +244,10 @@ def quantize_layer(W: torch.Tensor, sumsq: torch.Tensor, bit_set: Sequence[int],
     ``share_tables`` (on by default): the preliminary K-means leaves its per-channel tables for
     the final one (`cmpq_kmeans_job.arrangement`), which then does not build them again (for
     channels of more than 2048 weights, and more of them than run in one go with their tables in
-    LDS; the others are the faster built anew).  Same
-    results, one buffer of about `d_in * (d_out + 8 KiB)` bytes more while the layer is in work;
-    measured, the final pass is 14 to 34 % shorter on channels of 8192 and 28 672 weights.
+    LDS; the others are the faster built anew).  Same results; the final pass is 14 to 34 % shorter on
+    channels of 8192 and 28 672 weights.  It costs one buffer of `d_in * (d_out + 5 to 12 KiB)` bytes while the
+    layer is in work (0.41 GB for 28672 channels of 8192 weights, 0.33 for 8192 of 28672), beside a workspace of
+    that size, which either route needs and which stays with ``ws``.
 
     ``iters_final_from_prelim`` (a variant; the paper names no start for either K-means of
     Sec. 3.2.2): the final quantization starts from the levels of the preliminary one and runs

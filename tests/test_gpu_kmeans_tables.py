@@ -218,3 +218,30 @@ def test_counts_that_run_over_with_entries_removed(env, d_out):
         B.kmeans_quantize(dW, db, out_idx, 0 if out_idx is None else len(excl), None, 6, cent, codes, ws)
         oc, ok = orc.kmeans(W, bits, out_idx=None if out_idx is None else excl.astype(np.int64), iters=6)
         assert np.array_equal(_np(cent), oc) and np.array_equal(_np(codes), ok)
+
+
+def test_calls_without_tables_ask_for_no_room_for_them(env):
+    """fp32 weights, importance weights and the direct algorithm run on kernels that keep no tables."""
+    B = env["B"]
+
+    class Asked(B.Workspace):
+        def get(self, nbytes):
+            self.asked = nbytes
+            return super().get(nbytes)
+
+    d_in, d_out = 2100, 1024
+    W = torch.randn(d_in, d_out, device=DEV)
+    bits = torch.full((d_in,), 2, dtype=torch.uint8, device=DEV)
+    cent, codes = torch.empty((d_in, 16), device=DEV), torch.empty((d_in, d_out), dtype=torch.uint8, device=DEV)
+    ws = Asked(DEV)
+
+    def asked(Wx, **kw):
+        B.kmeans_quantize(Wx, bits, None, 0, kw.pop("elem_weight", None), 2, cent, codes, ws, **kw)
+        return ws.asked
+
+    least, tables = B.workspace_bytes(B.OP_KMEANS, d_in, 0), B.workspace_bytes(B.OP_KMEANS, d_in, d_out)
+    assert least < 64 * d_in < tables
+    assert asked(W) == asked(W.half(), elem_weight=torch.ones_like(W)) == asked(W.half(), algorithm=B.KMEANS_DIRECT) == least
+    assert asked(W.half()) == tables
+    cent.copy_(torch.linspace(-1, 1, 16, device=DEV).repeat(d_in, 1))
+    assert asked(W.half(), algorithm=B.KMEANS_DIRECT, init=B.INIT_GIVEN) == tables
