@@ -245,3 +245,55 @@ def test_calls_without_tables_ask_for_no_room_for_them(env):
     assert asked(W.half()) == tables
     cent.copy_(torch.linspace(-1, 1, 16, device=DEV).repeat(d_in, 1))
     assert asked(W.half(), algorithm=B.KMEANS_DIRECT, init=B.INIT_GIVEN) == tables
+
+
+def _level_pairs(rng, n):
+    """Two different levels: neighbours of FP16 values, sums that meet an FP16 value exactly, subnormals, both sides
+    of zero, means of a few weights, far outside FP16."""
+    half = rng.integers(0, 0x7800, n).astype(np.uint16).view(np.float16).astype(np.float64) * rng.choice([-1.0, 1.0], n)
+    step = np.spacing(half.astype(np.float16)).astype(np.float64)
+    k = rng.integers(0, 8, n)
+    lo = half.copy()
+    hi = np.select([k == 0, k == 1, k == 2, k == 3, k == 4, k == 5, k == 6],
+                   [half + step,                                                  # half way between neighbours
+                    half + step * rng.integers(1, 40, n),                         # meets a value or the middle of two
+                    half + step * rng.integers(1, 4000, n) / 1024,                # close together
+                    -half * rng.integers(0, 5, n) / 4,                            # the other side of zero, or zero
+                    rng.integers(-2000, 2000, n) * 2.0 ** -24 / rng.integers(1, 9, n),  # about the smallest values
+                    half * rng.uniform(1.0, 3.0, n),
+                    rng.normal(0, 1, n) * 10.0 ** rng.integers(-8, 8, n)], rng.normal(0, 3e5, n))
+    lo = np.where(k == 4, rng.integers(-2000, 2000, n) * 2.0 ** -24 / rng.integers(1, 9, n), lo)
+    lo, hi = lo.astype(np.float32), hi.astype(np.float32)
+    hi = np.where(lo == hi, np.nextafter(hi, np.float32(np.inf), dtype=np.float32), hi)
+    swap = rng.random(n) < 0.5                                                    # either may have the smaller index
+    return np.where(swap, hi, lo), np.where(swap, lo, hi)
+
+
+@pytest.mark.parametrize("d_in", [2048, 40000])
+def test_boundaries_lie_at_the_exact_middle(env, d_in):
+    """No rounds from two given levels: the codes of the FP16 values about their middle tell where the boundary lies.
+    The reference compares 2 w with the levels' sum, exact in fp64 (pairs whose sum is not are left out)."""
+    B, ws = env["B"], env["ws"]
+    rng = np.random.default_rng(d_in)
+    c0, c1 = _level_pairs(rng, d_in)
+    a, b = c0.astype(np.float64), c1.astype(np.float64)
+    total = a + b
+    part = total - a
+    exact = (a - (total - part)) + (b - part) == 0.0
+    assert exact.mean() > 0.9
+    mid = np.clip(total / 2, -65504, 65504).astype(np.float16).view(np.uint16).astype(np.int32)
+    key = np.where(mid & 0x8000, 0x8000 - (mid & 0x7fff), 0x8000 + mid)           # value order
+    near = np.clip(key[:, None] + np.arange(-12, 12)[None, :], 0x8000 - 0x7bff, 0x8000 + 0x7bff)
+    near = np.where(near >= 0x8000, near - 0x8000, 0x8000 | (0x8000 - near)).astype(np.uint16)
+    W = np.concatenate([near.view(np.float16), rng.normal(0, 1, (d_in, 4)).astype(np.float16),
+                        np.tile(np.array([0.0, -0.0, 65504.0, -65504.0], np.float16), (d_in, 1))], axis=1)
+    start = torch.full((d_in, 16), 9.0, device=DEV)
+    start[:, 0], start[:, 1] = _dev(c0), _dev(c1)
+    codes = torch.empty(W.shape, dtype=torch.uint8, device=DEV)
+    B.kmeans_quantize(_dev(W), _dev(np.ones(d_in, np.uint8)), None, 0, None, 0, start, codes, ws, init=B.INIT_GIVEN)
+    twice = 2.0 * W.astype(np.float64) - total[:, None]
+    upper = np.where(b > a, 1, 0).astype(np.uint8)[:, None]                       # index of the larger level
+    want = np.where(twice > 0, upper, np.where(twice < 0, 1 - upper, 0))
+    got = _np(codes)
+    assert np.array_equal(got[exact], want[exact])
+    assert (twice[exact] == 0).any(1).mean() > 0.1                                # ties are among them
