@@ -185,9 +185,16 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# The handle alone: as torch.cuda.current_stream().cuda_stream each call takes the host about 2 us longer.  The two
+# functions are not part of torch's documented interface; without them, that is how the handle is found.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the handle alone: as torch.cuda.current_stream().cuda_stream each call takes the host about 2 us longer
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _rows(t: torch.Tensor):

@@ -484,7 +484,6 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
     a.err_ch = nullptr;
     a.arr_keep = nullptr;
     a.arr_reuse = nullptr;
-    a.arr_stride = 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (!ws || reinterpret_cast<uintptr_t>(ws) % 256 != 0 || ws_bytes < ws_kmeans_least(d_in))
         return CMPQ_EWORKSPACE;
@@ -503,7 +502,6 @@ extern "C" int cmpq_kmeans_quantize_job(const cmpq_kmeans_job *job, void *ws, si
         // only the histogram kernel builds and reads arrangements; one is kept from all weights
         if (!j.arrangement || !hist_takes_it || reinterpret_cast<uintptr_t>(j.arrangement) % 16 != 0) return CMPQ_EINVAL;
         if (j.arrangement_use == CMPQ_ARRANGEMENT_KEEP && j.n_out > 0) return CMPQ_EINVAL;
-        a.arr_stride = (int64_t)kmeans_hist_arrangement_stride(d_out);
         if (j.arrangement_use == CMPQ_ARRANGEMENT_KEEP) a.arr_keep = j.arrangement;
         else a.arr_reuse = j.arrangement;
     }

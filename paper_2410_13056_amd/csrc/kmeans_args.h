@@ -32,10 +32,9 @@ struct KmArgs {
     double *err_ch;
     // The bucket kernels' per-channel arrangement (bucket table and place array built from all
     // weights of a channel): written for a later run (arr_keep) or taken from an earlier one
-    // instead of building it again (arr_reuse).  arr_stride bytes per channel.
+    // instead of building it again (arr_reuse).
     void *arr_keep;
     const void *arr_reuse;
-    int64_t arr_stride;
 };
 
 // Histogram k-means (kmeans_hist.hip) and fixed-point brute-force k-means

@@ -728,10 +728,10 @@ __device__ __forceinline__ float quantile_start(const View &ch, int K, uint32_t 
     return c == 0.0f ? 0.0f : c;  // a level never starts as -0
 }
 
-// (s * 2^-24) / n in fp64, rounded once more to fp32.  The quotient is IEEE's: the reciprocal refined twice, one
-// correction of the quotient by its exact remainder - the steps of the compiler's own division without its
-// rescaling, which no |s| < 2^56 and 1 <= n <= 32768 asks for (with n = 0 the value is not used).  The reciprocal
-// is ready before the sum is.
+// (s * 2^-24) / n in fp64, rounded once more to fp32.  The quotient by Markstein's method (Computation of elementary
+// functions on the IBM RISC System/6000 processor, 1990): the reciprocal by two Newton steps from an estimate, the
+// quotient from it, corrected by its remainder, exact in a fused multiply-add.  No |s| < 2^56 and 1 <= n <= 32768
+// leaves the normal range (with n = 0 the value is not used).  The reciprocal is ready before the sum is.
 __device__ __forceinline__ float mean_of_cell(long long s, uint32_t n) {
     const double d = ldexp((double)n, 24);
     double r = __builtin_amdgcn_rcp(d);
@@ -1043,7 +1043,6 @@ __device__ __forceinline__ void coding_prepare(const KmArgs &a, CodeShared &sm, 
                                                int tid, int n_groups) {
     if constexpr (FUSED) {
         constexpr int B = K == 2 ? 1 : (K == 4 ? 2 : (K == 8 ? 3 : 4));
-        if (tid < CMPQ_KMAX) sm.cent64[tid] = (double)sm.cent[tid];
         const int row_bytes = (int)(((int64_t)a.d_out * B + 31) / 32) * 4;
         const int coded = B == 4 ? 2 * n_groups : (B == 2 ? n_groups : (B == 3 ? 3 * ((n_groups + 1) >> 1) : (n_groups + 1) >> 1));
         for (int x = coded + tid; x < row_bytes; x += T) arr[x] = 0;

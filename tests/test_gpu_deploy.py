@@ -414,3 +414,13 @@ def test_products_replayed_from_a_hip_graph_equal_eager_launches(env):
         torch.cuda.synchronize()
         for g, w in zip(got, want):
             assert torch.equal(g, w), it
+
+
+def test_launches_go_to_the_current_stream(env, monkeypatch):
+    """The handle handed to the library is the current stream's, with torch's short cut to it and without."""
+    B = env["B"]
+    for cut in (B._raw_stream, None):
+        monkeypatch.setattr(B, "_raw_stream", cut)
+        assert B._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(torch.cuda.Stream()):
+            assert B._stream() == torch.cuda.current_stream().cuda_stream != torch.cuda.default_stream().cuda_stream
