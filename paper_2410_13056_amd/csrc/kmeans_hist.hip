@@ -504,49 +504,52 @@ __device__ __forceinline__ int from_row_lane(int v, int l) {
     return __shfl(v, (threadIdx.x & 48) | l, CMPQ_WAVE);
 }
 
+// Value of lane L of the caller's row of 16 lanes, on the DPP path.
+template <int L>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x150 + L, 0xF, 0xF, true));  // row_newbcast:L
+}
+// Hands v to lane `to` of the caller's row; the lanes of a row name different ones.
+__device__ __forceinline__ int to_row_lane(int v, int to) {
+    return __builtin_amdgcn_ds_permute(((threadIdx.x & 48) | to) << 2, v);
+}
+__device__ __forceinline__ float to_row_lane(float v, int to) {
+    return __uint_as_float((uint32_t)to_row_lane((int)__float_as_uint(v), to));
+}
+
+// Number of lanes of the row before lane j in the order (value, lane): lanes L on.
+template <int L>
+__device__ __forceinline__ int rank_in_row(float c, int j) {
+    const float cl = row_bcast<L>(c);
+    const int before = (cl < c) || (cl == c && L < j) ? 1 : 0;
+    if constexpr (L + 1 < CMPQ_KMAX) return before + rank_in_row<L + 1>(c, j);
+    else return before;
+}
+
 // Levels by level index (lane j of a row of 16 lanes holds c for j < K, infinity above) -> per sorted
 // position p (lane p): value, owning level, next distinct value above and the owners for the tie rule.
-// Handles repeated values and any order.  K may differ from row to row.
+// Handles repeated values and any order.  K may differ from row to row.  Levels that no weight is nearest to repeat
+// one another round after round where a channel has few different values, so this counts: as 48 exchanges through
+// LDS one after the other, 3000 channels of 8 weights took 53 us (26 now, in the three kernels), 4096 x 4096 with all of
+// one row's weights removed 149 (73).
 __device__ __forceinline__ void rank_levels_in_rows(float c, int K, float &sorted, int &own, float &hi, int &owner_lo,
                                                     int &owner_hi, bool &have_hi) {
     const int j = threadIdx.x & 15;
-    int rank = 0;
-#pragma unroll 1
-    for (int l = 0; l < CMPQ_KMAX; ++l) {
-        const float cl = from_row_lane(c, l);
-        rank += (cl < c) || (cl == c && l < j);
-    }
-    sorted = INFINITY;
-    own = j;
-#pragma unroll 1
-    for (int l = 0; l < CMPQ_KMAX; ++l) {
-        const int rl = from_row_lane(rank, l);
-        const float cl = from_row_lane(c, l);
-        if (rl == j) {
-            sorted = cl;
-            own = l;
-        }
-    }
-    hi = INFINITY;
-    owner_lo = own;
-    owner_hi = 0;
-    bool have_lo = false;
-    have_hi = false;
-#pragma unroll 1
-    for (int l = 0; l < CMPQ_KMAX; ++l) {
-        const float sl = from_row_lane(sorted, l);
-        const int pl = from_row_lane(own, l);
-        if (!have_lo && sl == sorted) {
-            owner_lo = pl;
-            have_lo = true;
-        }
-        if (!have_hi && l > j && l < K && sl > sorted) {
-            hi = sl;
-            owner_hi = pl;
-            have_hi = true;
-        }
-    }
-    if (j >= K - 1) have_hi = false;
+    const int rank = rank_in_row<0>(c, j);
+    sorted = to_row_lane(c, rank);
+    own = to_row_lane(j, rank);
+    // positions whose neighbour above is larger: the next of them from j on, and the one before j, end j's run of
+    // equal values
+    const float above = __uint_as_float(row_from_above(__float_as_uint(sorted)));
+    const uint64_t ends = __ballot(j < K - 1 && sorted < above);
+    const uint32_t mine = (uint32_t)(ends >> (threadIdx.x & 48)) & 0xffffu;
+    const uint32_t up = mine >> j, down = mine & ((1u << j) - 1u);
+    have_hi = up != 0;
+    const int next = (j + __ffs(up)) & 15, first = 32 - __clz(down);
+    const float larger = from_row_lane(sorted, next);  // (by all lanes: one left out would have nothing to give)
+    hi = have_hi ? larger : INFINITY;
+    owner_hi = from_row_lane(own, next);
+    owner_lo = from_row_lane(own, first);
 }
 
 __device__ __forceinline__ uint4 load_words4(const uint32_t *p) {  // 4-byte aligned
@@ -815,13 +818,7 @@ __device__ __forceinline__ Rounds run_rounds(const View &ch, int K, uint32_t M, 
             tie_up = own_up < own;
         } else {
             // bring the values back to level order and rank them again
-            float c_level = INFINITY;
-#pragma unroll 1
-            for (int l = 0; l < CMPQ_KMAX; ++l) {
-                const int ol = from_row_lane(own, l);
-                const float cl = from_row_lane(c, l);
-                if (ol == p) c_level = cl;
-            }
+            const float c_level = to_row_lane(c, own);
             rank(c_level);
         }
     }
@@ -882,6 +879,10 @@ __global__ __launch_bounds__(CMPQ_WAVE) __attribute__((amdgpu_waves_per_eu(1, ro
     const int64_t j = exists ? at : n_chan - 1, i = i0 + j;
     const int b = exists ? a.bits[i] : 0;
     const bool coded = b >= 1 && b <= 4;
+    if (__ballot(coded) == 0ull) {  // all kept whole in FP16
+        if (exists && r == 0) a.centroids[i * CMPQ_KMAX + (lane & 15)] = INFINITY;
+        return;
+    }
     const TableHead *head = reinterpret_cast<const TableHead *>(tables + j * stride);
     const TableHead *rem = reinterpret_cast<const TableHead *>(REM ? removed + j * stride : nullptr);
     // ---- sums per run and records into LDS, what the removed entries add taken off.  All loads go out before
@@ -1342,19 +1343,16 @@ struct LocalView {
     __device__ __forceinline__ const uint2 *rec() const { return reinterpret_cast<const uint2 *>(head + 1) + kFirst; }
 };
 
-// Wavefronts a SIMD that the registers of the channel kernel leave room for (at 6, 80 of them, rows of 64 weights a
-// lane at any alignment spill 12 bytes).
-constexpr int channel_waves(int G, bool ragged) { return G == 16 && ragged ? 5 : 6; }
-
 // Tables, start-up and rounds of a channel in one workgroup, nothing but its levels (and tables to be kept) to
 // memory: for few channels, and for calls whose scratch is too small for the tables of many.  Kept tables are not
 // taken: a channel's own are built without the removed entries, which gives the same.
 //
 // A round's latency is the bound, as in kmeans_rounds_kernel, but its words come from LDS and nothing has to be read
-// first.  First and final quantization (with packing and error; 20 rounds), us, as three kernels and so:
-// @@FIGURES@@
+// first.  First and final quantization (with packing and error; 20 rounds), us, as three kernels and so: 1024 x 8192
+// 35 + 61 -> 29 + 48, 1031 x 4099 40 + 53 -> 35 + 46, 3001 x 2049 49 + 63 -> 41 + 54, 1024 x 11008 40 + 69 -> 31 + 57,
+// 512 x 28672 49 + 67 -> 38 + 65.
 template <int G, int T, int LB, bool MASKED, bool RAGGED, bool FUSED>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(channel_waves(G, RAGGED)))) void kmeans_channel_kernel(KmArgs a, int64_t stride) {
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(6))) void kmeans_channel_kernel(KmArgs a, int64_t stride) {
     // dynamic LDS: what build_tables wants (the coding pass has its row in the place array and its table in the
     // buckets' words) | head | records
     extern __shared__ __align__(16) unsigned char dyn[];
