@@ -364,8 +364,8 @@ int cmpq_kmeans_launch_shape(int64_t d_out, int64_t *shape);
  * place array lies in, which also hold the bucket counts (8 bytes a bucket) where they are taken
  * again in 64 bits; the bits of a bucket's 32-bit word that its sum of places has: they are
  * taken again when the sum of some bucket reaches 2^bits; the bytes of LDS for the other tables of
- * a channel where one workgroup builds them and runs the rounds (few channels), 0 where the tables
- * go to memory - keeping them for a later call spares that call something only then.
+ * a channel where one workgroup builds them and runs the rounds (few channels, short rows), 0 where
+ * the tables go to memory - keeping them for a later call spares that call something only then.
  * CMPQ_EINVAL for a null pointer, no channels or no weights, CMPQ_ESHAPE beyond the limit.
  */
 int cmpq_kmeans_build_shape(int64_t d_in, int64_t d_out, int64_t *shape);

@@ -21,7 +21,8 @@
 //   * kmeans_code_kernel codes the weights with the final boundaries, and writes the stored format and
 //     the error where they are asked for.
 //
-// Few channels go through all three in one workgroup each, with their tables in LDS (kmeans_channel_kernel).
+// Few channels, short ones and few rounds go through all three in one workgroup each, with their tables in LDS
+// (kmeans_channel_kernel).
 //
 // A quantization without entries of O_q can leave its tables to a later one with them.  That one has
 // kmeans_removed_kernel arrange the removed entries alone, in the same form, and its rounds take
@@ -1344,7 +1345,7 @@ struct LocalView {
 };
 
 // Tables, start-up and rounds of a channel in one workgroup, nothing but its levels (and tables to be kept) to
-// memory: for few channels, and for calls whose scratch is too small for the tables of many.  Kept tables are not
+// memory: for few channels or rounds, short rows, and scratch too small for the tables of many.  Kept tables are not
 // taken: a channel's own are built without the removed entries, which gives the same.
 //
 // A round's latency is the bound, as in kmeans_rounds_kernel, but its words come from LDS and nothing has to be read
@@ -1560,6 +1561,10 @@ size_t table_bytes_of(int64_t d_out) {
     return bytes;
 }
 
+// Rows of up to this many weights are shorter than their tables' records: 262144 x 128 1121 us in three kernels, 1001 in
+// the channel kernel, x 64 963 and 734, x 16 807 and 531; x 256 1309 and 1311.
+constexpr int64_t kShortRow = 128;
+
 // Whether the channel kernel takes these: few channels, all of whose workgroups the chip holds at once - 256 CUs
 // of 2048 lanes (1536 where a lane takes 64 weights, by its registers) and 160 KiB of LDS, a tenth of it to spare.  The rounds then leave wavefronts free in any case, and what the three kernels cost beyond their work - tables
 // out and in again, two launches - is what counts.  Rows of up to 2048 weights share a wavefront of the rounds between
@@ -1576,8 +1581,15 @@ bool tables_stay_in_lds(int64_t d_in, int64_t d_out) {
         stay = d_in <= 256 * (s.G == 16 ? 1536 : 2048) / s.T && d_in <= 230 * (int64_t)(160 * 1024 / lds) && (s.T > 64 || d_in <= 2048);
         return CMPQ_OK;
     });
-    return stay;
+    return stay || d_out <= kShortRow;
 }
+
+// And, where tables are neither kept nor taken, up to this many rounds: what a round costs less in the three kernels
+// has to make up for the tables' way out and in.  Final quantization, us, three kernels and the channel kernel:
+//   4096 x 4096   5 rounds 58, 55; 10: 64, 65        4000 x 6000   10 rounds 82, 77; 20: 99, 100
+//   8192 x 2048   2 rounds 65, 63;  5: 69, 72        8192 x 8192   10 rounds 163, 144; 20: 186, 188; 60: 277, 322
+//   8192 x 11008  2 rounds 195, 185; 5: 206, 210     28672 x 8192   5 rounds 471, 387; 20: 584, 584
+int64_t few_rounds(int64_t d_out) { return d_out > 4096 && d_out <= 8192 ? d_out / 400 : 5; }
 
 template <typename S>
 int report_shape(S, bool local, int64_t d_out, int64_t *shape) {
@@ -1626,7 +1638,8 @@ int launch_kmeans_hist(const KmArgs &a, void *scratch, size_t scratch_bytes, hip
     const size_t stride = table_bytes_of(a.d_out), per = scratch_per_channel(a, stride);
     if (!stride) return CMPQ_ESHAPE;
     const int64_t room = per ? (int64_t)(scratch_bytes / per) : a.d_in, step = room < a.d_in ? room : a.d_in;
-    const bool local = tables_stay_in_lds(a.d_in, a.d_out) || (step < a.d_in && step < kLeastPart);
+    const bool local = tables_stay_in_lds(a.d_in, a.d_out) || (step < a.d_in && step < kLeastPart) ||
+                       (!a.arr_keep && !a.arr_reuse && a.iters <= few_rounds(a.d_out));
     cmpq_timing_before(CMPQ_KERNEL_KMEANS, s);
     const int rc = local ? with_shape<true>(a.d_out, [&](auto v) {
         return a.fused ? launch_channels<v.G, v.T, v.LB, true>(a, s) : launch_channels<v.G, v.T, v.LB, false>(a, s);

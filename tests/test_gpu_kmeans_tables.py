@@ -69,7 +69,7 @@ class _Limited:
         return self.buf
 
 
-@pytest.mark.parametrize("d_in,d_out,rooms", [(23, 1024, (0,)), (23, 4098, (0,)), (4200, 64, (0, 5, 2047, 2048, 2049, 4199)),
+@pytest.mark.parametrize("d_in,d_out,rooms", [(23, 1024, (0,)), (23, 4098, (0,)), (4200, 132, (0, 5, 2047, 2048, 2049, 4199)),
                                               (2060, 1031, (2049,)), (2300, 8192, (1, 2100))])
 def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out, rooms):
     B, ws = env["B"], env["ws"]
@@ -80,19 +80,19 @@ def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out
     dW, db = _dev(W), _dev(bits)
     cent = torch.empty((d_in, 16), dtype=torch.float32, device=DEV)
     codes = torch.empty((d_in, d_out), dtype=torch.uint8, device=DEV)
-    B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, ws)
+    B.kmeans_quantize(dW, db, excl, excl.numel(), None, 21, cent, codes, ws)
     full = B.workspace_bytes(B.OP_KMEANS, d_in, d_out)
     one = (B.workspace_bytes(B.OP_KMEANS, 1 << 20, d_out) - B.workspace_bytes(B.OP_KMEANS, 1 << 19, d_out)) >> 19
     for channels in rooms:
         c2, k2 = torch.full_like(cent, 7.0), torch.full_like(codes, 255)
         room = max(full - (d_in - channels) * one + 512, B.workspace_bytes(B.OP_KMEANS, d_in, 0))
-        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, c2, k2, _Limited(room))
+        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 21, c2, k2, _Limited(room))
         assert torch.equal(c2, cent) and torch.equal(k2, codes)
     with pytest.raises(B.CmpqError):
-        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 5, cent, codes, _Limited(256))
+        B.kmeans_quantize(dW, db, excl, excl.numel(), None, 21, cent, codes, _Limited(256))
 
 
-@pytest.mark.parametrize("d_in,d_out", [(1, 4), (2100, 7), (2100, 64), (2055, 1028), (2053, 1999), (3300, 2052), (2800, 4095), (2050, 4099),
+@pytest.mark.parametrize("d_in,d_out", [(1, 4), (2100, 131), (2100, 132), (2055, 1028), (2053, 1999), (3300, 2052), (2800, 4095), (2050, 4099),
                                         (2049, 8192), (1030, 16384), (770, 28672), (800, 32768), (800, 32767)])
 def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
     """The size that holds for rows of any length (asked for without one): every form of the call, bit for bit what
@@ -119,7 +119,7 @@ def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
         def run(n, codes, init, use, tables):
             cent = torch.linspace(-0.1, 0.1, 16, device=DEV).repeat(d_in, 1)
             st = torch.zeros(1, dtype=torch.int32, device=DEV)
-            B.kmeans_quantize(dW, db, excl if n else None, n, None, 5, cent, codes, space(), st, init=init, arrangement=tables,
+            B.kmeans_quantize(dW, db, excl if n else None, n, None, 21, cent, codes, space(), st, init=init, arrangement=tables,
                               arrangement_use=use)
             out.extend([cent, st] + ([codes] if codes is not None else []))
 
@@ -140,7 +140,7 @@ def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
         idx = [torch.full((c,), -1, dtype=torch.int32, device=DEV) for c in counts]
         lut = [torch.full((c, 1 << b), 7.0, dtype=torch.float16, device=DEV) for b, c in zip(widths, counts)]
         err, tot = torch.empty(d_in, dtype=torch.float64, device=DEV), torch.empty(2, dtype=torch.float64, device=DEV)
-        B.kmeans_quantize_pack(dW, db, excl, n_out, 5, cent, k, widths, counts, packed, idx, lut, sumsq, err, tot, space())
+        B.kmeans_quantize_pack(dW, db, excl, n_out, 21, cent, k, widths, counts, packed, idx, lut, sumsq, err, tot, space())
         return out + [cent, k, *packed, *idx, *lut, err.view(torch.int64), tot.view(torch.int64)]
 
     for a, b in zip(forms(lambda: ws), forms(lambda: _Limited(least))):
@@ -162,9 +162,10 @@ def test_tables_of_another_row_length_are_flagged(env):
     assert st.item() == B.STATUS_ARRANGEMENT and not codes.any() and not cent[:, :8].any()
 
 
-@pytest.mark.parametrize("d_out", [1028, 1999, 2052, 4095, 4100, 8192])
-def test_many_channels_get_the_bits_of_few(env, d_out):
-    """3300 channels in one call, and the same rows in two calls whose tables stay in LDS."""
+@pytest.mark.parametrize("iters", [4, 24])
+@pytest.mark.parametrize("d_out", [132, 1028, 1999, 2052, 4095, 4100, 8192])
+def test_many_channels_get_the_bits_of_few(env, d_out, iters):
+    """3300 channels in one call, and the same rows in two calls whose tables stay in LDS; few rounds and many."""
     B, ws = env["B"], env["ws"]
     g = torch.Generator(device=DEV).manual_seed(d_out)
     d_in = 3300
@@ -176,7 +177,7 @@ def test_many_channels_get_the_bits_of_few(env, d_out):
     def run(lo, hi, out_idx, use, tables):
         cent = torch.full((hi - lo, 16), 7.0, device=DEV)
         codes = torch.full((hi - lo, d_out), 255, dtype=torch.uint8, device=DEV)
-        B.kmeans_quantize(W[lo:hi], bits[lo:hi], out_idx, out_idx.numel() if out_idx is not None else 0, None, 4, cent, codes,
+        B.kmeans_quantize(W[lo:hi], bits[lo:hi], out_idx, out_idx.numel() if out_idx is not None else 0, None, iters, cent, codes,
                           ws, arrangement=tables, arrangement_use=use)
         return cent, codes
 
