@@ -1568,17 +1568,17 @@ constexpr int64_t kShortRow = 128;
 // Whether the channel kernel takes these: few channels, all of whose workgroups the chip holds at once - 256 CUs
 // of 2048 lanes (1536 where a lane takes 64 weights, by its registers) and 160 KiB of LDS, a tenth of it to spare.  The rounds then leave wavefronts free in any case, and what the three kernels cost beyond their work - tables
 // out and in again, two launches - is what counts.  Rows of up to 2048 weights share a wavefront of the rounds between
-// 4 channels there and turn earlier.
+// 4 channels there and turn at 3 wavefronts a SIMD here.
 //
 // First and final quantization, us, three kernels and this one:
-//   2000 x 300   26 + 39, 24 + 34      3300 x 2052  44 + 69, 39 + 61      2880 x 4096  47 + 75, 47 + 79
-//   2500 x 300   27 + 40, 28 + 39      2500 x 4096  45 + 72, 39 + 64      2048 x 8192  49 + 74, 41 + 69
-//   672 x 28672  56 + 75, 45 + 76      1024 x 28672 64 + 88, 65 + 115
+//   3000 x 300   27 + 41, 28 + 40      3300 x 2052  44 + 69, 39 + 61      2880 x 4096  47 + 75, 47 + 79
+//   3500 x 300   28 + 43, 33 + 47      2500 x 4096  45 + 72, 39 + 64      2048 x 8192  49 + 74, 41 + 69
+//   3000 x 1024  30 + 48, 30 + 44      672 x 28672  56 + 75, 45 + 76      1024 x 28672 64 + 88, 65 + 115
 bool tables_stay_in_lds(int64_t d_in, int64_t d_out) {
     bool stay = false;
     (void)with_shape<true>(d_out, [&](auto s) {
         const size_t lds = build_lds<s.G, s.T, s.LB>(d_out, true) + kLocalTables<s.LB> + kChannelShared<s.T>;
-        stay = d_in <= 256 * (s.G == 16 ? 1536 : 2048) / s.T && d_in <= 230 * (int64_t)(160 * 1024 / lds) && (s.T > 64 || d_in <= 2048);
+        stay = d_in <= 256 * (s.G == 16 ? 1536 : 2048) / s.T && d_in <= 230 * (int64_t)(160 * 1024 / lds) && (s.T > 64 || d_in <= 3072);
         return CMPQ_OK;
     });
     return stay || d_out <= kShortRow;

@@ -70,7 +70,7 @@ class _Limited:
 
 
 @pytest.mark.parametrize("d_in,d_out,rooms", [(23, 1024, (0,)), (23, 4098, (0,)), (4200, 132, (0, 5, 2047, 2048, 2049, 4199)),
-                                              (2060, 1031, (2049,)), (2300, 8192, (1, 2100))])
+                                              (3090, 1031, (2049,)), (2300, 8192, (1, 2100))])
 def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out, rooms):
     B, ws = env["B"], env["ws"]
     rng = np.random.default_rng(3)
@@ -92,7 +92,7 @@ def test_scratch_for_a_part_of_the_channels_gives_the_same_bits(env, d_in, d_out
         B.kmeans_quantize(dW, db, excl, excl.numel(), None, 21, cent, codes, _Limited(256))
 
 
-@pytest.mark.parametrize("d_in,d_out", [(1, 4), (2100, 131), (2100, 132), (2055, 1028), (2053, 1999), (3300, 2052), (2800, 4095), (2050, 4099),
+@pytest.mark.parametrize("d_in,d_out", [(1, 4), (3100, 131), (3100, 132), (3080, 1028), (3080, 1999), (3300, 2052), (2800, 4095), (2050, 4099),
                                         (2049, 8192), (1030, 16384), (770, 28672), (800, 32768), (800, 32767)])
 def test_the_least_scratch_gives_the_same_bits(env, d_in, d_out):
     """The size that holds for rows of any length (asked for without one): every form of the call, bit for bit what
@@ -230,7 +230,7 @@ def test_calls_without_tables_ask_for_no_room_for_them(env):
             self.asked = nbytes
             return super().get(nbytes)
 
-    d_in, d_out = 2100, 1024
+    d_in, d_out = 3100, 1024
     W = torch.randn(d_in, d_out, device=DEV)
     bits = torch.full((d_in,), 2, dtype=torch.uint8, device=DEV)
     cent, codes = torch.empty((d_in, 16), device=DEV), torch.empty((d_in, d_out), dtype=torch.uint8, device=DEV)
