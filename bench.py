@@ -33,8 +33,8 @@ HBM_PEAK_GBS = 8000.0
 # Constants taken from the kept rocprofv3 --pmc summaries (bench.py cannot collect counters):
 # mean HBM bytes per k-means call, all its kernels (FETCH_SIZE + WRITE_SIZE scaled by a plain copy of known
 # size) and vector-ALU instructions of the k-means calls of a step (SQ_INSTS_VALU, per wavefront).
-KMEANS_TRAFFIC_BYTES = {"block70b": 778.8e6}
-KMEANS_VALU_WAVE_INSTS_PER_STEP = {"block70b": 1.302e9}     # 14 calls
+KMEANS_TRAFFIC_BYTES = {"block70b": 743.3e6}
+KMEANS_VALU_WAVE_INSTS_PER_STEP = {"block70b": 1.319e9}     # 14 calls
 KMEANS_COUNTERS_FILE = "profiles/kmeans_block70b_counters.txt"
 
 

@@ -32,12 +32,12 @@
 // times over, which one wavefront can run for several channels at once - while a channel's tables take
 // 5 to 36 KB to build in LDS.  In one kernel the rounds, half of a channel's time, hold that LDS and all
 // wavefronts of the channel, and leave a compute unit with 3 to 16 channels to hide the chain behind (2400
-// cycles a round at 28672 weights, where a wavefront alone needs 1400).  On their own they hold 4 to 9 KB a
+// cycles a round at 28672 weights, where a wavefront alone needs 1400).  On their own they hold 4.4 to 10.2 KB a
 // channel and one wavefront for 1 to 4.  Both quantizations of a layer, widths 2 to 4 at 3.5 on average, 1 %
 // in O_q, us in one kernel -> now (first + final):
-//   8192 x 28672  471 + 594 -> 360 + 459      4096 x 11008  192 + 244 -> 99 + 169
-//   28672 x 8192  574 + 751 -> 459 + 606      8192 x 1024    98 + 133 -> 62 + 124
-//   4096 x 4096    82 + 112 ->  63 + 100
+//   8192 x 28672  471 + 594 -> 318 + 411      4096 x 11008  192 + 244 -> 102 + 156
+//   28672 x 8192  574 + 751 -> 446 + 578      8192 x 1024    98 + 133 ->  58 + 95
+//   4096 x 4096    82 + 112 ->  64 + 94
 // Tried on the way, same results: rounds of 4 / 2 / 1 channels on one wavefront inside the one kernel (1024
 // weights 98 -> 70, 8192 weights 574 -> 630), all tables of the rounds in LDS (28672 x 8192 528: too few
 // channels at a time), none of them (gate-shaped 373, the records' lines do not stay in L2).

@@ -138,8 +138,8 @@ def _histogram_kernel_takes(Wt: torch.Tensor) -> bool:
 
 # Up to this many weights a channel the final K-means builds its tables again: taking the removed entries from
 # kept ones means a second set of tables per channel, which costs more than counting so few weights twice.  Final
-# quantization from kept and from new tables, us: 8192 x 1024 118 and 94, 8192 x 2048 130 and 116, 4096 x 2048 82
-# and 82, 4096 x 4096 93 and 98, 28672 x 8192 595 and 692.
+# quantization from kept and from new tables, us: 8192 x 1024 103 and 83, 8192 x 2048 119 and 104, 4096 x 2048 73
+# and 68, 4096 x 4096 86 and 88, 28672 x 8192 593 and 633, 8192 x 28672 413 and 510.
 SHORT_CHANNEL = 2048
 
 
@@ -244,7 +244,7 @@ def quantize_layer(W: torch.Tensor, sumsq: torch.Tensor, bit_set: Sequence[int],
     ``share_tables`` (on by default): the preliminary K-means leaves its per-channel tables for
     the final one (`cmpq_kmeans_job.arrangement`), which then does not build them again (for
     channels of more than 2048 weights, and more of them than run in one go with their tables in
-    LDS; the others are the faster built anew).  Same results; the final pass is 14 to 34 % shorter on
+    LDS; the others are the faster built anew).  Same results; the final pass is 6 to 19 % shorter on
     channels of 8192 and 28 672 weights.  It costs one buffer of `d_in * (d_out + 5 to 12 KiB)` bytes while the
     layer is in work (0.41 GB for 28672 channels of 8192 weights, 0.33 for 8192 of 28672), beside a workspace of
     that size, which either route needs and which stays with ``ws``.
