@@ -1566,9 +1566,10 @@ size_t table_bytes_of(int64_t d_out) {
 constexpr int64_t kShortRow = 128;
 
 // Whether the channel kernel takes these: few channels, all of whose workgroups the chip holds at once - 256 CUs
-// of 2048 lanes (1536 where a lane takes 64 weights, by its registers) and 160 KiB of LDS, a tenth of it to spare.  The rounds then leave wavefronts free in any case, and what the three kernels cost beyond their work - tables
-// out and in again, two launches - is what counts.  Rows of up to 2048 weights share a wavefront of the rounds between
-// 4 channels there and turn at 3 wavefronts a SIMD here.
+// of 2048 lanes (1536 where a lane takes 64 weights, by its registers) and 160 KiB of LDS, a tenth of it to spare.
+// The rounds then leave wavefronts free in any case, and what the three kernels cost beyond their work - tables
+// out and in again, two launches - is what counts.  Rows of up to 2048 weights share a wavefront of the rounds
+// between 4 channels there and turn at 3 wavefronts a SIMD here.
 //
 // First and final quantization, us, three kernels and this one:
 //   3000 x 300   27 + 41, 28 + 40      3300 x 2052  44 + 69, 39 + 61      2880 x 4096  47 + 75, 47 + 79
