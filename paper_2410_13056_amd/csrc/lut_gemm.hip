@@ -21,15 +21,18 @@
 // sends that layer token by token).
 //
 // Measured against one token after the other (us per call): two 13824x5120 layers, 16 tokens 281 ->
-// 56, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 312, of which, under
+// 45, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 312, of which, under
 // the profiler, the product 226 (636 TFLOP/s of the 1144 that a large library product reaches here),
 // decoding 65 (4.3 TB/s written).  The error against 64 bits is the same within a few per cent
-// (1.0e-7 to 1.4e-7).  What bounds the few-token kernel is its decoding (of its 37 us at 16 tokens 39 %
-// is issue of vector instructions, a quarter LDS look-ups, 7 % matrix cores; they overlap poorly with
-// 3 wavefronts per SIMD) and, for small layers, the first pass through its code: 52 to 85 KB, a body
-// for each width.  Registers
-// are all in use: the variants of 4, 8 and 16 tokens keep one vector register in memory, those of
-// 16 and 32 move 28 and 303 scalar registers through lanes of vector registers.
+// (1.0e-7 to 1.4e-7).  What bounds the few-token kernel is its decoding: an LDS look-up a weight at 3
+// and 4 bits (2.6 clocks of a compute unit each, measured; 4 of the 5 thousand clocks that a step of
+// 32 rows takes 12 wavefronts) and 2.3 vector instructions; at 2 bits half of either.  Of its 26 us at
+// 16 tokens (37 with a fourth instruction a weight, the parts split without regard to their cost
+// and a second round of workgroups) the first 3 go by before the codes are there and the last 2 in
+// adding up.  For small layers it is the launches and the first pass through the code, 53 to 65
+// KB, two bodies for each width: steps that are there whole, which need no bounds, and others.
+// Registers are all in use: the variants of up to 16 tokens keep 9 to 12 vector registers in
+// memory outside the loops.
 #include "lut_gemm.h"
 #include <limits.h>
 
@@ -53,7 +56,7 @@ struct Seg {
     const uint16_t *lut;
     const int32_t *chan;
     int rows, words_per_row, bits, step0;    // step0: first step among all steps of the layer
-    int steps, slabs;                        // few tokens: slabs that share the steps
+    int steps, part0, parts;                 // few tokens: the parts (one a wavefront) that share the steps
 };
 
 struct Layer {
@@ -69,8 +72,7 @@ struct Layer {
     int32_t *pos;       // [channel]: its row among all steps (many tokens)
     float *partial;     // [slab][token][d_out]
     uint4 *dense;       // [step][tile][operand][lane]: W_hat in operand order (many tokens)
-    int d_in, d_out, n_seg, steps, tiles, slabs, act_vec_ok;
-    int slab0[kMaxSegs];  // few tokens: first slab of each segment
+    int d_in, d_out, n_seg, steps, tiles, slabs, act_vec_ok;  // slabs: kWaves parts each
 };
 
 constexpr int kMaxLayers = CMPQ_MAX_GROUP;
@@ -158,10 +160,14 @@ struct TileArgs {
 
 // ---- decoding one step: 32 rows x 256 outputs -> 16 operands
 
-// LDS of a wavefront: the level tables of a step's 32 rows, twice.  Widths 1, 3, 4:
+// LDS of a wavefront: the level tables of a step's 32 rows, twice.  Widths 1 and 4:
 // [row % 8][row / 8][16 levels]; width 2: pairs of rows, [row / 2 % 4][row / 8][16 pairs of codes],
-// an entry the two rows' levels side by side, so that one look-up decodes two weights.  The tables
-// that a half-wavefront reads at once lie in different banks.
+// an entry the two rows' levels side by side, so that one look-up decodes two weights; width 3: the
+// tables twice over, [row % 8][row / 8][8 levels] with a level every 2 bytes and
+// [row / 2 % 4][8 levels][row / 8][row % 2] with one every 16, so that two neighbouring codes of a
+// shifted word are both in place as the bits of an address (bits 1-3 and 4-6): three instructions
+// for two weights instead of four.  The tables that a half-wavefront reads at once lie in different
+// banks.
 constexpr int kTableBytes = kRowsPerStep * 16 * 2;
 
 // (v << 1) + base in one instruction.
@@ -199,13 +205,17 @@ struct Decoder {
     static constexpr int kLevels = kAct ? 0 : 1 << B;
     static constexpr int kEntries = kLevels / 2;               // levels a lane fetches per step (not for pairs)
     static constexpr int kRaw = kPairs ? 4 : 8;                // look-ups per operand
+    static constexpr int kTable3 = kTableBytes / 2;            // width 3: the tables with a level every 16 bytes
     uint32_t w[8][kWords];
     uint32_t e[4];
 
     // The words of this lane's outputs in its 8 rows of the step that starts at `row`, and its share
     // of the step's tables.  Rows past the end are read again from the last one; their tables are
     // zero, so they add nothing.
-    __device__ __forceinline__ void fetch(const TileArgs &L, const Seg &s, int row, int out0, bool full, int half = 0) {
+    // WHOLE (uniform): all 32 rows and all 256 outputs are there.
+    template <bool WHOLE>
+    __device__ __forceinline__ void fetch(const TileArgs &L, const Seg &s, int row, int out0, int half = 0) {
+        const bool full = WHOLE || out0 + kTileOuts <= L.d_out;
         const int lane = threadIdx.x & 63, kg = lane >> 4;
         const int unit = (out0 >> 4) + (lane & 15);        // which 16 outputs of a row
         if constexpr (kAct) {
@@ -234,24 +244,26 @@ struct Decoder {
             // a uniform base and a 32-bit offset per lane (the packed rows of a width stay below 2^30 bytes)
             const char *base = reinterpret_cast<const char *>(s.packed) + (uint64_t)row * wpr * 4u;
             typedef uint32_t WordsN __attribute__((ext_vector_type(kWords), aligned(4)));
-            if (full && row + kRowsPerStep <= s.rows) {
+            if (WHOLE || (full && row + kRowsPerStep <= s.rows)) {
                 const uint32_t at = ((uint32_t)(8 * kg) * wpr + (uint32_t)first) * 4u;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const WordsN v = __builtin_nontemporal_load(reinterpret_cast<const WordsN *>(base + (uint64_t)(at + j * wpr * 4u)));
+                    const WordsN v = __builtin_nontemporal_load(reinterpret_cast<const WordsN *>(base + (uint64_t)(j * wpr) * 4u + at));
 #pragma unroll
                     for (int q = 0; q < kWords; ++q) w[j][q] = v[q];
                 }
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const uint32_t *p = reinterpret_cast<const uint32_t *>(base) + (uint64_t)min(8 * kg + j, s.rows - 1 - row) * wpr + first;
+                    // past the end of a row its last word again: outputs that are not there are not written
+                    const uint32_t r = (uint32_t)min(8 * kg + j, s.rows - 1 - row) * wpr;
 #pragma unroll
-                    for (int q = 0; q < kWords; ++q) w[j][q] = first + q < s.words_per_row ? p[q] : 0u;
+                    for (int q = 0; q < kWords; ++q)
+                        w[j][q] = *reinterpret_cast<const uint32_t *>(base + (uint64_t)((r + min((uint32_t)(first + q), wpr - 1u)) * 4u));
                 }
             }
             const uint16_t *lut = s.lut + (int64_t)row * kLevels;
-            const int left = s.rows - row;                 // rows of the step
+            const int left = WHOLE ? kRowsPerStep : s.rows - row;  // rows of the step
             if constexpr (kPairs) {
                 // lane: rows 2 p, 2 p + 1 with p = lane / 4; the upper row's code lane % 4
                 const int r0 = lane >> 2 << 1;
@@ -282,9 +294,13 @@ struct Decoder {
             *reinterpret_cast<uint4 *>(buf + (p & 3) * 256 + (p >> 2) * 64 + (lane & 3) * 16) = make_uint4(e[0], e[1], e[2], e[3]);
         } else if constexpr (!kAct) {
             const int row = lane >> 1;
-            unsigned char *p = buf + ((row & 7) * 4 + (row >> 3)) * 32 + (lane & 1) * kEntries * 2;
+            unsigned char *p = buf + ((row & 7) * 4 + (row >> 3)) * (B == 3 ? 16 : 32) + (lane & 1) * kEntries * 2;
             if constexpr (B == 4) *reinterpret_cast<uint4 *>(p) = make_uint4(e[0], e[1], e[2], e[3]);
-            else if constexpr (B == 3) *reinterpret_cast<uint2 *>(p) = make_uint2(e[0], e[1]);
+            else if constexpr (B == 3) {
+                *reinterpret_cast<uint2 *>(p) = make_uint2(e[0], e[1]);
+                uint16_t *q = reinterpret_cast<uint16_t *>(buf + kTable3 + ((row >> 1) & 3) * 128 + (lane & 1) * 64 + (row >> 3) * 4 + (row & 1) * 2);
+                q[0] = (uint16_t)e[0], q[8] = (uint16_t)(e[0] >> 16), q[16] = (uint16_t)e[1], q[24] = (uint16_t)(e[1] >> 16);
+            }
             else *reinterpret_cast<uint16_t *>(p) = (uint16_t)e[0];
             const int shift = 16 * (lane & 1);  // out0 is a whole number of units of 16 outputs, an even one
 #pragma unroll
@@ -300,7 +316,7 @@ struct Decoder {
 
     // LDS address of this lane's tables.
     static __device__ __forceinline__ uint32_t tables_at(const unsigned char *tables) {
-        return (uint32_t)reinterpret_cast<uintptr_t>(tables) + ((threadIdx.x & 63) >> 4) * (kPairs ? 64 : 32);
+        return (uint32_t)reinterpret_cast<uintptr_t>(tables) + ((threadIdx.x & 63) >> 4) * (kPairs ? 64 : (B == 3 ? 16 : 32));
     }
 
     // What operand k (output k of this lane in its 8 rows) is made of, and the operand.  Two parts,
@@ -324,6 +340,16 @@ struct Decoder {
                 // every other code, times 2, a byte each
                 const uint32_t t = (k & 1 ? w[j][k >> 3] >> 3 : w[j][k >> 3] << 1) & 0x1e1e1e1eu;
                 r.v[j] = lds_read<uint16_t>(add_byte(at, t, (k & 7) >> 1) + j * 128);
+            } else if constexpr (B == 3) {
+                // codes k (even) and k + 1 at bits 1-3 and 4-6 of the row's words, shifted
+                const int sh = 3 * (k & ~1) - 1;
+                const uint32_t u = sh < 0 ? w[j][0] << 1 : (sh < 32 ? __builtin_amdgcn_alignbit(w[j][1], w[j][0], sh) : w[j][1] >> (sh - 32));
+                if (k & 1) {
+                    const uint32_t at3 = at + kTable3 - ((threadIdx.x & 63) >> 4) * 12;  // bits 2-3: row / 8
+                    r.v[j] = lds_read<uint16_t>(((u & 0x70u) | at3) + (j >> 1) * 128 + (j & 1) * 2);
+                } else {
+                    r.v[j] = lds_read<uint16_t>(((u & 0xeu) | at) + j * 64);
+                }
             } else {
                 r.v[j] = lds_read<uint16_t>(shl1_add(code(j, k), at) + j * 128);
             }
@@ -353,9 +379,6 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Whether all 16 outputs of every lane of a tile lie inside the rows.
-__device__ __forceinline__ bool tile_is_full(const TileArgs &L, int out0) { return out0 + kTileOuts <= L.d_out; }
-
 // ---- few tokens: decode and multiply
 
 __device__ __forceinline__ Float4 mfma(Half8 a, Half8 b, Float4 c) {
@@ -369,16 +392,25 @@ constexpr int kTablesBytes = kWaves * 2 * kTableBytes;
 constexpr int kSlabLds = kWaves * (kOuts / 2) * 4 * CMPQ_WAVE * 4;   // 32 KB: tables and inputs, then sums
 constexpr int direct_steps(int nd) { return ((kSlabLds - kTablesBytes) / (nd * 2) - 8) / kRowsPerStep; }  // most steps of a slab
 
-// The steps a part of a width's slabs covers.
-__device__ __forceinline__ int part_step(const Seg &s, int part) { return s.step0 + (int)((int64_t)s.steps * part / (s.slabs * kWaves)); }
+// The steps of a part, and its segment.  A slab is kWaves parts, one a wavefront; a part is of one
+// width, and at the end of the last slab there may be parts that are empty.
+__device__ __forceinline__ int part_of(const Layer &L, int part, int &lo, int &hi) {
+    int j = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxSegs; ++i) j += i < L.n_seg && part >= L.seg[i].part0;
+    const Seg &s = L.seg[j];
+    const int p = min(part - s.part0, s.parts);
+    lo = s.step0 + (int)((uint32_t)s.steps * (uint32_t)p / (uint32_t)s.parts);
+    hi = s.step0 + (int)((uint32_t)s.steps * (uint32_t)min(p + 1, s.parts) / (uint32_t)s.parts);
+    return j;
+}
 
-template <int B, int MT, int ND>
+template <int B, int MT, int ND, bool WHOLE>
 __device__ __forceinline__ void multiply_steps(const TileArgs &L, const Seg &s, int lo, int hi, int out0, int tt,
                                                unsigned char *tables, const __half *xs, int xs_step0, int xs_rows,
                                                Float4 (&acc)[MT][kOuts]) {
     using D = Decoder<B>;
     const int lane = threadIdx.x & 63;
-    const bool full = tile_is_full(L, out0);
     const uint32_t at0 = D::tables_at(tables);
     const uint4 *xf = L.xf + ((int64_t)tt * L.steps) * CMPQ_WAVE + lane;
     auto load_x = [&](int step, Word4 (&x)[MT]) {
@@ -403,7 +435,7 @@ __device__ __forceinline__ void multiply_steps(const TileArgs &L, const Seg &s, 
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 D d;
-                d.fetch(L, s, (step - s.step0) * kRowsPerStep, out0, full, h);
+                d.template fetch<false>(L, s, (step - s.step0) * kRowsPerStep, out0, h);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const Half8 a = D::operand(d.look_up(k, 0), k);
@@ -417,7 +449,7 @@ __device__ __forceinline__ void multiply_steps(const TileArgs &L, const Seg &s, 
     }
     D cur, nxt;
     Word4 x[MT], xn[MT];
-    cur.fetch(L, s, (lo - s.step0) * kRowsPerStep, out0, full);
+    cur.template fetch<WHOLE>(L, s, (lo - s.step0) * kRowsPerStep, out0);
     load_x(lo, x);
     cur.settle(tables);
     wave_fence();
@@ -426,7 +458,7 @@ __device__ __forceinline__ void multiply_steps(const TileArgs &L, const Seg &s, 
     for (int step = lo; step < hi; ++step) {
         // the last step fetches itself again, which nothing uses
         const int ahead = step + 1 < hi ? step + 1 : step;
-        nxt.fetch(L, s, (ahead - s.step0) * kRowsPerStep, out0, full);
+        nxt.template fetch<WHOLE>(L, s, (ahead - s.step0) * kRowsPerStep, out0);
         load_x(ahead, xn);
         const uint32_t at = at0 + buf * kTableBytes;
         // Look-ups run one operand ahead of the products.  The fences keep the compiler from starting
@@ -452,11 +484,11 @@ __device__ __forceinline__ void multiply_steps(const TileArgs &L, const Seg &s, 
     }
 }
 
-// One slab: 256 outputs x MT * 16 tokens x a share of a width's steps, which 4 wavefronts split.
-// The whole body is instantiated per width: with the widths in one loop, the sums would change
-// registers between them.
-template <int B, int MT, int ND>
-__device__ __forceinline__ void multiply_slab(const TileArgs &L, const Seg &s, int at, int slab, int tile, int tt, int m,
+// One slab: 256 outputs x MT * 16 tokens x a share of the layer's steps, which 4 wavefronts split.  A
+// wavefront's steps are of one width: with the widths one after the other in one wavefront, the sums
+// would change registers between them.
+template <int MT, int ND>
+__device__ __forceinline__ void multiply_slab(const TileArgs &L, const Layer &layer, int slab, int tile, int tt, int m,
                                               unsigned char *smem) {
     const int lane = threadIdx.x & 63, wave = wave_index();
     const int out0 = tile * kTileOuts;
@@ -465,24 +497,47 @@ __device__ __forceinline__ void multiply_slab(const TileArgs &L, const Seg &s, i
     for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int k = 0; k < kOuts; ++k) acc[t][k] = Float4{0.f, 0.f, 0.f, 0.f};
-    const int lo = part_step(s, at * kWaves + wave), hi = part_step(s, at * kWaves + wave + 1);
+    int lo, hi;
+    const Seg s = layer.seg[part_of(layer, slab * kWaves + wave, lo, hi)];
     __half *xs = reinterpret_cast<__half *>(smem + kTablesBytes);
-    const int first = part_step(s, at * kWaves), rows = (part_step(s, at * kWaves + kWaves) - first) * kRowsPerStep;
+    int first = 0, rows = 0;
     if constexpr (ND > 0) {
-        const int row0 = (first - s.step0) * kRowsPerStep;
+        int last, other;
+        part_of(layer, slab * kWaves, first, other);
+        part_of(layer, slab * kWaves + kWaves - 1, other, last);
+        rows = (last - first) * kRowsPerStep;
         for (int r = threadIdx.x; r < rows; r += kThreads) {
-            const bool ok = row0 + r < s.rows;
-            const int chan = ok ? s.chan[row0 + r] : 0;
+            int chan = -1;
+#pragma unroll
+            for (int j = 0; j < kMaxSegs; ++j) {  // segments that are not there have no rows
+                const int row = first * kRowsPerStep + r - layer.seg[j].step0 * kRowsPerStep;
+                if (row >= 0 && row < layer.seg[j].rows) chan = layer.seg[j].chan[row];
+            }
             __half v[ND];
 #pragma unroll
-            for (int t = 0; t < ND; ++t) v[t] = ok && t < m ? L.X[(int64_t)t * L.ldx + chan] : __ushort_as_half(0);
+            for (int t = 0; t < ND; ++t) v[t] = chan >= 0 && t < m ? L.X[(int64_t)t * L.ldx + chan] : __ushort_as_half(0);
 #pragma unroll
             for (int t = 0; t < ND; ++t) xs[t * (rows + 8) + r] = v[t];
         }
         __syncthreads();
     }
-    if (lo < hi) multiply_steps<B, MT, ND>(L, s, lo, hi, out0, tt, smem + wave * 2 * kTableBytes, xs, first, rows, acc);
-    // The four wavefronts' sums, added in order.  Wavefront w takes the operands 4 w .. 4 w + 3, for a
+    if (lo < hi) {
+        unsigned char *tables = smem + wave * 2 * kTableBytes;
+        if (s.bits == kActBits) {
+            multiply_steps<kActBits, MT, ND, false>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+        } else if (out0 + kTileOuts <= L.d_out && (hi - s.step0) * kRowsPerStep <= s.rows) {
+            if (s.bits == 1) multiply_steps<1, MT, ND, true>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+            else if (s.bits == 2) multiply_steps<2, MT, ND, true>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+            else if (s.bits == 3) multiply_steps<3, MT, ND, true>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+            else multiply_steps<4, MT, ND, true>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+        } else {
+            if (s.bits == 1) multiply_steps<1, MT, ND, false>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+            else if (s.bits == 2) multiply_steps<2, MT, ND, false>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+            else if (s.bits == 3) multiply_steps<3, MT, ND, false>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+            else multiply_steps<4, MT, ND, false>(L, s, lo, hi, out0, tt, tables, xs, first, rows, acc);
+        }
+    }
+    // The four wavefronts' sums, added in pairs.  Wavefront w takes the operands 4 w .. 4 w + 3, for a
     // lane four neighbouring outputs of one token in each of the 4 components; two of them at a time,
     // so that 32 KB do.
     Float4 *red = reinterpret_cast<Float4 *>(smem);
@@ -498,10 +553,9 @@ __device__ __forceinline__ void multiply_slab(const TileArgs &L, const Seg &s, i
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                Float4 v = red[(2 * wave + k) * CMPQ_WAVE + lane];
-#pragma unroll
-                for (int u = 1; u < kWaves; ++u) v += red[(u * (kOuts / 2) + 2 * wave + k) * CMPQ_WAVE + lane];
-                y[2 * h + k] = v;
+                const Float4 *v = red + (2 * wave + k) * CMPQ_WAVE + lane;
+                constexpr int kNext = (kOuts / 2) * CMPQ_WAVE;
+                y[2 * h + k] = (v[0] + v[kNext]) + (v[2 * kNext] + v[3 * kNext]);
             }
         }
         const int token = (tt + t) * kTok + (lane & 15);
@@ -524,25 +578,16 @@ __device__ __forceinline__ void multiply_slab(const TileArgs &L, const Seg &s, i
 
 template <int MT, int ND>
 __global__ __launch_bounds__(kThreads, MT == 1 ? 3 : 2) void lut_tokens_kernel(Group g) {
-    __shared__ __align__(16) unsigned char smem[kSlabLds];
+    __shared__ __align__(kTableBytes) unsigned char smem[kSlabLds];
     int wg;
     const Layer &L = layer_of(g, wg);
     wg = xcd_order(wg, L.tiles * L.slabs * (g.token_tiles / MT));
-    const int tile = wg % L.tiles, rest = wg / L.tiles, tt = (rest / L.slabs) * MT;
-    const int slab = rest % L.slabs;
-    int j = 0;
-#pragma unroll
-    for (int i = 1; i < kMaxSegs; ++i) j += slab >= L.slab0[i];
-    const Seg s = L.seg[j];
+    // the slabs of a tile one after the other, so that every XCD and compute unit gets slabs of all
+    // widths (two 13824x5120 layers, 16 tokens: with the tiles innermost those of the widest codes took
+    // 25 us, the others 15)
+    const int slab = wg % L.slabs, rest = wg / L.slabs, tile = rest % L.tiles, tt = (rest / L.tiles) * MT;
     const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out, L.act_vec_ok};
-    const int at = slab - L.slab0[j];
-    switch (s.bits) {
-        case 1: multiply_slab<1, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
-        case 2: multiply_slab<2, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
-        case 3: multiply_slab<3, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
-        case 4: multiply_slab<4, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
-        default: multiply_slab<kActBits, MT, ND>(a, s, at, slab, tile, tt, g.m, smem); break;
-    }
+    multiply_slab<MT, ND>(a, L, slab, tile, tt, g.m, smem);
 }
 
 // Slabs and entries of O_q: 16 outputs x NT tokens per workgroup.  16 lanes per column take its
@@ -649,7 +694,7 @@ __device__ __forceinline__ void decode_step(const TileArgs &L, const Seg &s, Wor
 #pragma unroll
     for (int h = 0; h < kHalves; ++h) {
         Decoder<B> d;
-        d.fetch(L, s, (step - s.step0) * kRowsPerStep, out0, tile_is_full(L, out0), h);
+        d.template fetch<false>(L, s, (step - s.step0) * kRowsPerStep, out0, h);
         d.settle(tables);
         wave_fence();
 #pragma unroll
@@ -659,7 +704,7 @@ __device__ __forceinline__ void decode_step(const TileArgs &L, const Seg &s, Wor
 
 // A wavefront: one step of one tile.
 __global__ __launch_bounds__(kThreads) void lut_decode_kernel(Group g) {
-    __shared__ __align__(16) unsigned char smem[kWaves * kTableBytes];
+    __shared__ __align__(kTableBytes) unsigned char smem[kWaves * kTableBytes];
     int wg;
     const Layer &L = layer_of(g, wg);
     const int wave = wave_index();
@@ -815,7 +860,7 @@ __global__ __launch_bounds__(kThreads, 2) void weight_gemm_kernel(Group g) {
 
 // ---- host
 
-constexpr int kMaxSlabs = 16, kMaxRun = 8;
+constexpr int kMaxSlabs = 16, kMaxRun = 8, kLeastCost = 6;
 constexpr int64_t kDirectWeights = 4 << 20;
 
 int64_t max_steps(int64_t d_in) { return cdiv(d_in, (int64_t)kRowsPerStep) + kMaxSegs; }
@@ -824,33 +869,43 @@ int64_t max_steps(int64_t d_in) { return cdiv(d_in, (int64_t)kRowsPerStep) + kMa
 int tiles_at_once(int64_t m) { return m > kTok ? 2 : 1; }
 int64_t padded_token_tiles(int64_t m) { return align_up((size_t)cdiv(m, (int64_t)kTok), tiles_at_once(m)); }
 
-// Slabs of a width's steps per tile and token tile: over all widths 384 workgroups (three for every
-// two compute units; 192 to 512 differ by less than 5 %), at least 2 steps per wavefront and at most
-// 8: longer runs of fp32 sums lose more than the token-by-token kernel.  Depends on the layer and m
+// Slabs of a tile and token tile: up to 384 workgroups in all, half of what the chip holds at once of
+// them, so that two layers of that size run side by side in one go (two 13824x5120 layers in 756
+// workgroups; 972 left a second round with a quarter of the chip busy).  Depends on the layer and m
 // alone, so that a layer gives the same bits in any group.
 int64_t wanted_slabs(int64_t d_out, int64_t m) {
-    const int64_t want = cdiv((int64_t)384, cdiv(d_out, (int64_t)kTileOuts) * (padded_token_tiles(m) / tiles_at_once(m)));
-    return want < kMaxSlabs ? want : kMaxSlabs;
+    const int64_t want = 384 / (cdiv(d_out, (int64_t)kTileOuts) * (padded_token_tiles(m) / tiles_at_once(m)));
+    return want < 1 ? 1 : (want < kMaxSlabs ? want : kMaxSlabs);
+}
+// Each width's steps in parts of even cost, the cheapest that need no more slabs than wanted.  A step of
+// width 2 takes a wavefront two thirds of the time of one of width 3 or 4 (1.4 and 2.2 us with 3
+// wavefronts a SIMD; half as many look-ups).  A part has at most 8 steps: longer runs of fp32 sums lose
+// more than the token-by-token kernel.
+int64_t part_steps(int bits, int64_t cost) {
+    const int64_t n = bits <= 2 ? cost / 2 : cost / 3;
+    return n < kMaxRun ? n : kMaxRun;
 }
 void choose_slabs(Layer &L, int64_t m) {
-    const int64_t want = wanted_slabs(L.d_out, m);
-    L.slabs = 0;
-    for (int j = 0; j < L.n_seg; ++j) {
-        Seg &s = L.seg[j];
-        int64_t n = (want * s.steps + L.steps / 2) / L.steps;
-        if (n > s.steps / (2 * kWaves)) n = s.steps / (2 * kWaves);
-        const int64_t least = cdiv(s.steps, (int64_t)kMaxRun * kWaves);
-        if (n < least) n = least;
-        L.slab0[j] = L.slabs;
-        s.slabs = (int)n;
-        L.slabs += s.slabs;
+    const int64_t want = kWaves * wanted_slabs(L.d_out, m);
+    int64_t cost = kLeastCost, parts = 0;
+    for (;; ++cost) {
+        parts = 0;
+        for (int j = 0; j < L.n_seg; ++j) parts += cdiv(L.seg[j].steps, part_steps(L.seg[j].bits, cost));
+        if (parts <= want || cost == 3 * kMaxRun) break;
     }
-    for (int j = L.n_seg; j < kMaxSegs; ++j) L.slab0[j] = INT_MAX;
+    int part = 0;
+    for (int j = 0; j < L.n_seg; ++j) {
+        L.seg[j].part0 = part;
+        L.seg[j].parts = (int)cdiv(L.seg[j].steps, part_steps(L.seg[j].bits, cost));
+        part += L.seg[j].parts;
+    }
+    L.slabs = (int)cdiv(parts, (int64_t)kWaves);
 }
 
-// At least what choose_slabs gives for any widths: the shares of `want`, rounded, and the least of each.
+// At least what choose_slabs gives for any widths.
 int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
-    return wanted_slabs(d_out, m) + kMaxSegs + cdiv(max_steps(d_in), (int64_t)kMaxRun * kWaves) + kMaxSegs;
+    const int64_t n = wanted_slabs(d_out, m), least = cdiv(cdiv(max_steps(d_in), (int64_t)kMaxRun) + kMaxSegs, (int64_t)kWaves);
+    return n < least ? least : n;
 }
 
 // Whether to decode the weight once into memory and multiply from there.  That costs 4 bytes of
@@ -947,7 +1002,9 @@ size_t plan_layer(const cmpq_deployed_layer &S, int64_t m, bool dense, char *bas
         g.steps = (int)cdiv(rows, (int64_t)kRowsPerStep);
         steps += g.steps;
     };
-    for (int j = 0; j < S.n_set; ++j) add(S.packed[j], S.lut[j], S.chan_idx[j], S.counts_host[j], S.bit_set[j]);
+    for (int b = 1; b <= 4; ++b)  // ascending widths
+        for (int j = 0; j < S.n_set; ++j)
+            if (S.bit_set[j] == b) add(S.packed[j], S.lut[j], S.chan_idx[j], S.counts_host[j], b);
     add(nullptr, nullptr, S.act_idx, S.k_act, kActBits);
     L.X = static_cast<const __half *>(S.X);
     L.ldx = S.ldx;
@@ -1042,8 +1099,7 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
         bool direct = G == &few && m <= 32;
         for (int i = 0; direct && i < n; ++i) {
             if (nd > 4 && (int64_t)G->l[i].d_in * G->l[i].d_out > kDirectWeights) direct = false;
-            for (int j = 0; j < G->l[i].n_seg; ++j)
-                if (cdiv(G->l[i].seg[j].steps, G->l[i].seg[j].slabs) >= direct_steps(nd)) direct = false;
+            if (cdiv(G->l[i].steps, G->l[i].slabs > 0 ? G->l[i].slabs : 1) >= direct_steps(nd)) direct = false;
         }
         if (wx && !direct) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
         if (G == &few) {
