@@ -14,3 +14,31 @@ size_t lut_gemm_need(const cmpq_deployed_layer &layer, int64_t m);
 // Enqueues the products of `layers` (checked by the caller, d_out > 0, m > 0).  `ws` holds the
 // sum of lut_gemm_need over the layers.
 int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int64_t m, void *ws, hipStream_t s);
+
+// What both kinds of product use of LDS tables.
+
+// base + byte q of t in one instruction (written out: the compiler takes the byte out first).
+template <int Q>
+__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t t) {
+    uint32_t r;
+    if constexpr (Q == 0) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(base), "v"(t));
+    else if constexpr (Q == 1) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(base), "v"(t));
+    else if constexpr (Q == 2) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(base), "v"(t));
+    else asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(base), "v"(t));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t t, int q) {  // q known at compile time
+    return q == 0 ? add_byte<0>(base, t) : (q == 1 ? add_byte<1>(base, t) : (q == 2 ? add_byte<2>(base, t) : add_byte<3>(base, t)));
+}
+
+template <typename T>
+__device__ __forceinline__ T lds_read(uint32_t at) {
+    typedef const T __attribute__((address_space(3))) *P;
+    return *(P)(uintptr_t)at;
+}
+
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}

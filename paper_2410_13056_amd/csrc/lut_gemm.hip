@@ -177,27 +177,6 @@ __device__ __forceinline__ uint32_t shl1_add(uint32_t v, uint32_t base) {
     return r;
 }
 
-// base + byte q of t in one instruction (written out: the compiler takes the byte out first).
-template <int Q>
-__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t t) {
-    uint32_t r;
-    if constexpr (Q == 0) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(base), "v"(t));
-    else if constexpr (Q == 1) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(base), "v"(t));
-    else if constexpr (Q == 2) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(base), "v"(t));
-    else asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(base), "v"(t));
-    return r;
-}
-
-__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t t, int q) {  // q known at compile time
-    return q == 0 ? add_byte<0>(base, t) : (q == 1 ? add_byte<1>(base, t) : (q == 2 ? add_byte<2>(base, t) : add_byte<3>(base, t)));
-}
-
-template <typename T>
-__device__ __forceinline__ uint32_t lds_read(uint32_t at) {
-    typedef const T __attribute__((address_space(3))) *P;
-    return *(P)(uintptr_t)at;
-}
-
 template <int B>
 struct Decoder {
     static constexpr bool kAct = B == kActBits, kPairs = B == 2;
@@ -373,11 +352,6 @@ struct Decoder {
         return __builtin_amdgcn_alignbit(w[j][q + 1 < kWords ? q + 1 : q], w[j][q], sh) & ((1u << B) - 1u);
     }
 };
-
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // ---- few tokens: decode and multiply
 

@@ -8,27 +8,23 @@
 // (lut_gemm.hip) wherever that is faster.
 //
 // The packed rows are input channels, so a row contributes X[t,i] * lut_i[code] to every
-// output: the 2^b products X[t,i] * lut_i[c] are formed once per row and the rest is table
-// look-ups and additions.  HBM bound: b/8 bytes per weight are read once per token.
+// output: tables of levels are formed once per row (or pair of rows) and the rest is table
+// look-ups and additions.  b/8 bytes per weight are read once per token.
 //
-//   * lut_matvec_kernel: one launch, two kinds of workgroup, each leaving one partial row
-//     per token:
-//       - a slab of 128 packed rows of one width times 2048 outputs (a lane 32 consecutive
-//         outputs: exactly B words of a row; 32 rows per wavefront).  The per-row tables of
-//         4 rows at a time sit in LDS (one entry per lane to fill); a code becomes the
-//         address of its table entry with two instructions.  The 16 entries of a table lie
-//         in 16 banks, so the look-ups of a wavefront never collide.
-//         Width 2 looks two neighbouring codes up at once (pair tables).
-//       - a slab of 32 rows of O_act (FP16 rows) times 2048 outputs.
-//     The four wavefronts' sums are added in order.  A launch serves up to 8 products
-//     (cmpq_lut_matvec_group): every layer owns a range of blockIdx.y.
-//   * lut_matvec_finish_kernel: per output, the partial rows in order (packed slabs, O_act
-//     slabs), then the column's O_q entries - every sum in a fixed order, so the result is
-//     reproducible bit for bit.
+//   * lut_matvec_kernel: a wavefront adds up a part, up to 48 rows of one width (or 8 of O_act), for a tile
+//     of 2048 outputs (a lane 32 consecutive outputs: exactly B words of a row); a workgroup is
+//     four parts, whose sums are added in pairs, and leaves one partial row per token.  Up to 3 bits two
+//     rows are looked up at once (lut_part).  A launch serves up to 8 products (cmpq_lut_matvec_group).
+//   * lut_matvec_finish_kernel: per output, the partial rows in order, then the column's O_q entries -
+//     every sum in a fixed order, so the result is reproducible bit for bit.
+//     One token through the seven products of a 70B-shaped block, four groups: 193 -> 158 us (main
+//     kernels 158 -> 120 under the profiler: 3.9 TB/s on the largest; the finish kernels 43 -> 38).
+//   * lut_matvec_half_kernel: the variant with FP16 sums, in slabs of four times 8, 16 or 32 rows.
 //   * cmpq_outliers_by_column / cmpq_gather_channels prepare O_q and O_act for this once,
 //     at quantization time.
 #include "common.h"
 #include "lut_gemm.h"
+#include <limits.h>
 
 namespace {
 
@@ -36,8 +32,8 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / CMPQ_WAVE;
 constexpr int kOutPerLane = 32;                        // 32 codes = B whole words
 constexpr int kTileOut = CMPQ_WAVE * kOutPerLane;      // outputs per workgroup
-constexpr int kMaxRowsPerWave = 32;                    // a workgroup's slab: 4 wavefronts x 8, 16 or 32 rows
-constexpr int kGroup = 4;                              // rows whose tables are in LDS at once
+constexpr int kMaxRowsPerWave = 32;                    // FP16 sums: a workgroup's slab is 4 wavefronts x 8, 16 or 32 rows
+constexpr int kGroup = 4;                              // FP16 sums: rows whose tables are in LDS at once
 constexpr int kMaxWidths = 4;
 
 struct LmWidth {
@@ -49,7 +45,7 @@ struct LmWidth {
     int bits;
 };
 
-// One product of a launch, as the kernels see it.
+// One product of a launch, as the kernel with FP16 sums sees it.
 struct LmArgs {
     LmWidth w[kMaxWidths];
     const __half *X;
@@ -77,12 +73,12 @@ constexpr int kRedStride = CMPQ_WAVE + 1;  // sums of output k of all lanes: 64 
 constexpr int kRedHalf = kOutPerLane / 2;  // the sums meet in LDS in two halves of 16 outputs per lane
 constexpr int kRedFloats = kRedHalf * kRedStride;
 
-// The four wavefronts' sums of a 2048-output tile, added in wavefront order, into a partial
-// row.  Called once by every lane of the workgroup.  Lanes write with stride 1 and read with
+// The four wavefronts' sums of a 2048-output tile (from output o_tile on), added in pairs, into a
+// partial row.  Called once by every lane of the workgroup.  Lanes write with stride 1 and read with
 // stride 65: no bank is hit twice by a half-wavefront either way.  Two halves, so that the
 // LDS of a workgroup stays small enough for five workgroups per compute unit.
 __device__ __forceinline__ void store_partial(const float (&acc)[kOutPerLane], float (*red)[kRedFloats],
-                                              float *__restrict__ prow, int64_t d_out) {
+                                              float *__restrict__ prow, int64_t o_tile, int64_t d_out) {
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -93,25 +89,14 @@ __device__ __forceinline__ void store_partial(const float (&acc)[kOutPerLane], f
         // lane l holds outputs 32 l .. 32 l + 31 of the tile; this half covers k = 16 h .. 16 h + 15
         for (int c = threadIdx.x; c < kTileOut / 2; c += kThreads) {
             const int l = c / kRedHalf, k = c % kRedHalf;
-            const int64_t o = (int64_t)blockIdx.x * kTileOut + l * kOutPerLane + h * kRedHalf + k;
+            const int64_t o = o_tile + l * kOutPerLane + h * kRedHalf + k;
             if (o < d_out) {
                 const int at = k * kRedStride + l;
-                float t = red[0][at];
-#pragma unroll
-                for (int wv = 1; wv < kWaves; ++wv) t += red[wv][at];
-                prow[o] = t;
+                static_assert(kWaves == 4, "");
+                prow[o] = (red[0][at] + red[1][at]) + (red[2][at] + red[3][at]);
             }
         }
     }
-}
-
-// Code k of a lane's 32 codes held in w[0..B-1] (one bit-field extract, two instructions
-// where the code straddles two words).
-template <int B>
-__device__ __forceinline__ uint32_t code_at(const uint32_t (&w)[B], int k) {
-    const int bit = k * B, idx = bit >> 5, sh = bit & 31;
-    if (sh + B <= 32) return __builtin_amdgcn_ubfe(w[idx], sh, B);
-    return __builtin_amdgcn_alignbit(w[idx + 1 < B ? idx + 1 : idx], w[idx], sh) & ((1u << B) - 1u);
 }
 
 // (code << 2) + base in one instruction.  Written out because the compiler otherwise turns
@@ -122,94 +107,6 @@ __device__ __forceinline__ uint32_t entry_offset(uint32_t code, uint32_t base) {
     return r;
 }
 
-template <int B>
-__device__ __forceinline__ void lut_slab(const LmArgs &a, const LmWidth &wd, int slab,
-                                         float (*tbl_all)[2][kGroup * 16], float (*red)[kRedFloats]) {
-    const __half *__restrict__ X = a.X;
-    const int64_t ldx = a.ldx, d_out = a.d_out;
-    const int rows_per_wave = a.rows_per_wave, n_rows_total = a.n_rows_total;
-    float *__restrict__ partial = a.partial;
-    constexpr int K = 1 << B;
-    // per wavefront: two buffers of kGroup row tables (K floats each)
-    float(*tbl)[2][kGroup * 16] = tbl_all;
-    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    const int64_t token = blockIdx.z;
-    const __half *x = X + token * ldx;
-    const int64_t word0 = (int64_t)blockIdx.x * (kTileOut / 32) * B + (int64_t)lane * B;
-    const int64_t r0 = ((int64_t)slab * kWaves + wave) * rows_per_wave;
-    const int64_t r1 = min(wd.rows, r0 + rows_per_wave);
-    float acc[kOutPerLane];
-#pragma unroll
-    for (int k = 0; k < kOutPerLane; ++k) acc[k] = 0.f;
-
-    // entry (row g, level c) of a group's tables is filled by lane g*K + c
-    const int fill_g = lane / K, fill_c = lane % K;
-    auto table_entry = [&](int64_t r) -> float {
-        if (fill_g >= kGroup || r + fill_g >= r1) return 0.f;
-        const int64_t row = r + fill_g;
-        const float xi = __half2float(x[wd.chan_idx[row]]);
-        return xi * __half2float(__ushort_as_half(wd.lut[row * K + fill_c]));
-    };
-    // a lane's B words of a row: one vector load when they all exist
-    const bool full = word0 + B <= wd.words_per_row;
-    auto load_words = [&](int64_t r, uint32_t (&w)[kGroup][B]) {
-#pragma unroll
-        for (int g = 0; g < kGroup; ++g) {
-            const uint32_t *p = wd.packed + (r + g) * wd.words_per_row + word0;
-            if (r + g < r1 && full) {
-                typedef uint32_t WordsB __attribute__((ext_vector_type(B), aligned(4)));
-                const WordsB v = __builtin_nontemporal_load(reinterpret_cast<const WordsB *>(p));  // dword-aligned vector load; a token reads the codes once
-#pragma unroll
-                for (int j = 0; j < B; ++j) w[g][j] = v[j];
-            } else {
-#pragma unroll
-                for (int j = 0; j < B; ++j) w[g][j] = (r + g < r1 && word0 + j < wd.words_per_row) ? p[j] : 0u;
-            }
-        }
-    };
-
-    if (r0 < r1) {
-        // The tables of a group are written one group ahead, into the buffer the look-ups of the
-        // group before have just left, so that the write has a whole group of look-ups to land
-        // in; the table entries themselves are fetched two groups ahead, the words one.
-        uint32_t w[kGroup][B], wn[kGroup][B];
-        const bool fills = kGroup * K >= CMPQ_WAVE || lane < kGroup * K;
-        if (fills) tbl[wave][0][lane % (kGroup * K)] = table_entry(r0);
-        float e = r0 + kGroup < r1 ? table_entry(r0 + kGroup) : 0.f, en = 0.f;
-        load_words(r0, w);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        int buf = 0;
-        for (int64_t r = r0; r < r1; r += kGroup) {
-            if (r + kGroup < r1) {
-                if (fills) tbl[wave][buf ^ 1][lane % (kGroup * K)] = e;
-                load_words(r + kGroup, wn);
-            }
-            if (r + 2 * kGroup < r1) en = table_entry(r + 2 * kGroup);
-            // byte offset of this wavefront's current buffer; code * 4 is added to it with one
-            // shift-and-add
-            const char *base = reinterpret_cast<const char *>(&tbl[0][0][0]);
-            const uint32_t wb = (uint32_t)((wave * 2 + buf) * (kGroup * 16 * 4));
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g) {
-                // rows past the end have all-zero tables: their look-ups add 0
-#pragma unroll
-                for (int k = 0; k < kOutPerLane; ++k)
-                    acc[k] += *reinterpret_cast<const float *>(base + g * K * 4 + entry_offset(code_at<B>(w[g], k), wb));
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            buf ^= 1;
-            e = en;
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-                for (int j = 0; j < B; ++j) w[g][j] = wn[g][j];
-        }
-    }
-    store_partial(acc, red, partial + (token * n_rows_total + wd.slab0 + slab) * d_out, d_out);
-}
-
 // Field p of `bits` bits of a lane's words (two instructions where it straddles two words).
 template <int B, int PB>
 __device__ __forceinline__ uint32_t field_at(const uint32_t (&w)[B], int p) {
@@ -218,122 +115,201 @@ __device__ __forceinline__ uint32_t field_at(const uint32_t (&w)[B], int p) {
     return __builtin_amdgcn_alignbit(w[idx + 1 < B ? idx + 1 : idx], w[idx], sh) & ((1u << PB) - 1u);
 }
 
-// Width 2: two neighbouring codes are looked up at once.  Per row two tables indexed by the
-// pair (c0 | c1 << B): A[pair] = x * lut[c0] for the even output, B[pair] = x * lut[c1] for the
-// odd one, read by one two-address LDS load.  One extract and one shift-and-add serve two
-// weights, so a weight costs 2 instead of 3 vector instructions; the sums are the same
-// products added in the same order.  A table of 16 entries lies in 16 banks: no conflicts.
-// (Written for any width whose pair table fits a wavefront; with width 3 the 64-entry tables
-// wrap around the LDS banks, the look-ups of a wavefront collide and the kernel is slower than
-// with single look-ups, so width 3 does not use it.)  Same slab shape, prefetch and double
-// buffering as lut_slab.
-template <int B>
-__device__ __forceinline__ void lut_slab_pairs(const LmArgs &a, const LmWidth &wd, int slab, float *smem,
-                                               float (*red)[kRedFloats]) {
-    constexpr int K = 1 << B, PB = 2 * B, KP = 1 << PB;   // levels, bits of a pair, entries of a pair table
-    constexpr int kRowsPerFill = CMPQ_WAVE / KP < kGroup ? CMPQ_WAVE / KP : kGroup;  // rows one pass over the lanes fills
-    constexpr int kFills = kGroup / kRowsPerFill;
-    constexpr int kRowFloats = 2 * KP;                     // A then B
-    constexpr int kBufFloats = kGroup * kRowFloats;
-    static_assert(KP <= CMPQ_WAVE && kGroup % kRowsPerFill == 0, "pair tables are filled by whole wavefronts");
-    const __half *__restrict__ X = a.X;
-    const int64_t d_out = a.d_out;
-    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    const int64_t token = blockIdx.z;
-    const __half *x = X + token * a.ldx;
-    const int64_t word0 = (int64_t)blockIdx.x * (kTileOut / 32) * B + (int64_t)lane * B;
-    const int64_t r0 = ((int64_t)slab * kWaves + wave) * a.rows_per_wave;
-    const int64_t r1 = min(wd.rows, r0 + a.rows_per_wave);
-    float acc[kOutPerLane];
-#pragma unroll
-    for (int k = 0; k < kOutPerLane; ++k) acc[k] = 0.f;
+// ---- fp32 sums: a wavefront's part
 
-    // pass f over the lanes fills the tables of row f * kRowsPerFill + lane / KP, entry lane % KP
-    const int fill_row = lane / KP, fill_e = lane % KP;
-    auto table_entries = [&](int64_t r, float (&ea)[kFills], float (&eb)[kFills]) {
+// A layer's rows of one width (or of O_act, bits = 16), in parts of about even cost: a wavefront adds up
+// one part for a tile of 2048 outputs, a workgroup four parts.
+struct MvWidth {
+    const uint32_t *packed;
+    const int32_t *chan;
+    const uint16_t *lut;
+    int rows, words_per_row, bits, part0, parts;
+};
+constexpr int kActBits = 16;
+struct MvLayer {
+    MvWidth w[kMaxWidths + 1];
+    const __half *X, *W_act;
+    int64_t ldx, ld_act;
+    float *partial;                // [tokens][slabs][d_out]
+    int d_out, n_w, slabs, act_vec_ok;
+};
+struct MvGroup {
+    int wg0[kMaxLayers];  // first workgroup of each layer (past the last layer: INT_MAX)
+    MvLayer l[kMaxLayers];
+};
+static_assert(sizeof(MvGroup) <= 4096, "travels in the kernel arguments");
+
+// Widths 1 to 3: the rows of a pair are looked up at once.  Their codes of one output make an index into
+// a table of 4^B sums x0 * level0 + x1 * level1 (products exact, sum rounded once), so an output costs
+// one extract, one address, one LDS read and one addition for two weights.
+template <int B>
+struct PairWords {
+    static constexpr uint32_t mask(int q) {  // word q: the fields of even outputs
+        uint32_t m = 0;
+        for (int p = 0; p < 32; ++p) m |= (uint32_t)((32 * q + p) % (2 * B) < B) << p;
+        return m;
+    }
+    uint32_t even[B], odd[B];  // pairs of codes of the even / odd outputs: pair i at bit 2 B i
+    __device__ __forceinline__ PairWords(const uint32_t (&a)[B], const uint32_t (&b)[B]) {
 #pragma unroll
-        for (int f = 0; f < kFills; ++f) {
-            const int64_t row = r + f * kRowsPerFill + fill_row;
-            ea[f] = 0.f;
-            eb[f] = 0.f;
-            if (fill_row < kRowsPerFill && row < r1) {
-                const float xi = __half2float(x[wd.chan_idx[row]]);
-                ea[f] = xi * __half2float(__ushort_as_half(wd.lut[row * K + (fill_e & (K - 1))]));
-                eb[f] = xi * __half2float(__ushort_as_half(wd.lut[row * K + (fill_e >> B)]));
+        for (int q = 0; q < B; ++q) {
+            const uint32_t up = q ? __builtin_amdgcn_alignbit(b[q], b[q - 1], 32 - B) : b[0] << B;
+            const uint32_t down = q + 1 < B ? __builtin_amdgcn_alignbit(a[q + 1], a[q], B) : a[q] >> B;
+            even[q] = (a[q] & mask(q)) | (up & ~mask(q));
+            odd[q] = (down & mask(q)) | (b[q] & ~mask(q));
+        }
+    }
+};
+
+// base + 4 * (nibble I of n), t the even or odd nibbles of n times 4, a byte each.
+__device__ __forceinline__ uint32_t nibbles4(uint32_t n, bool odd) { return (odd ? n >> 2 : n << 2) & 0x3c3c3c3cu; }
+
+// Rows whose tables are in LDS at once, LDS of a wavefront: two such groups.
+template <int B>
+constexpr int kPartGroup = B <= 2 ? 8 : 4;
+constexpr int kPartTable = 512;  // bytes of a group's tables: 16 entries for each of 4 rows or pairs, 64 for each of 2 pairs
+constexpr int kMaxPartRows = CMPQ_WAVE;  // a lane keeps the input of one row
+
+// What bounds it: vector instructions - 1.9 a weight at 3 bits, 2.6 at 4, 1.5 at 2 - and LDS reads (half
+// a read a weight up to 3 bits, with two-way conflicts at 3).  With one table a row at 3 bits, extracts
+// of single codes at 4 and pairs of outputs at 2 it were 3.1, 3.1 and 2.1.
+template <int B>
+__device__ __forceinline__ void lut_part(const MvLayer &a, const MvWidth &wd, const __half *__restrict__ x, int r0, int n,
+                                         int tile, unsigned char *tables, float (&acc)[kOutPerLane]) {
+    constexpr int K = 1 << B, G = kPartGroup<B>;
+    constexpr bool kPairs = B <= 3;
+    constexpr int KP = kPairs ? K * K : K, kTables = kPairs ? G / 2 : G;  // entries of a table, tables of a group
+    constexpr int kPasses = kTables * KP > CMPQ_WAVE ? kTables * KP / CMPQ_WAVE : 1, kPerPass = kTables / kPasses;
+    static_assert(kTables * KP * 4 <= kPartTable && kPerPass * KP <= CMPQ_WAVE, "");
+    const int lane = threadIdx.x & (CMPQ_WAVE - 1);
+    const float x_mine = lane < n ? __half2float(x[wd.chan[r0 + lane]]) : 0.f;
+    // entry `fe` of table `ft` of a pass
+    const int ft = lane / KP, fe = lane % KP;
+    const uint16_t *lut = wd.lut + (int64_t)r0 * K;
+    // levels of a group's tables (past the end those of the last row again, dropped when they are written)
+    struct Levels {
+        uint16_t lo[kPasses], hi[kPasses];
+    };
+    auto fetch_levels = [&](int r, Levels &v) {
+#pragma unroll
+        for (int f = 0; f < kPasses; ++f) {
+            if constexpr (kPairs) {
+                const int row = r + 2 * (f * kPerPass + ft);
+                v.lo[f] = lut[min(row, n - 1) * K + (fe & (K - 1))];
+                v.hi[f] = lut[min(row + 1, n - 1) * K + ((fe >> B) & (K - 1))];
+            } else {
+                v.lo[f] = lut[min(r + ft, n - 1) * K + fe];
             }
         }
     };
-    const bool full = word0 + B <= wd.words_per_row;
-    auto load_words = [&](int64_t r, uint32_t (&w)[kGroup][B]) {
+    auto write_tables = [&](int r, const Levels &v, unsigned char *buf) {
 #pragma unroll
-        for (int g = 0; g < kGroup; ++g) {
-            const uint32_t *p = wd.packed + (r + g) * wd.words_per_row + word0;
-            if (r + g < r1 && full) {
+        for (int f = 0; f < kPasses; ++f) {
+            const int row = r + (kPairs ? 2 : 1) * (f * kPerPass + ft);
+            float e = row < n ? __half2float(__ushort_as_half(v.lo[f])) : 0.f;
+            if constexpr (kPairs) {
+                const float x0 = __shfl(x_mine, row & (CMPQ_WAVE - 1), CMPQ_WAVE), x1 = __shfl(x_mine, (row + 1) & (CMPQ_WAVE - 1), CMPQ_WAVE);
+                e = fmaf(x0, e, x1 * (row + 1 < n ? __half2float(__ushort_as_half(v.hi[f])) : 0.f));
+            }
+            if (kPerPass * KP == CMPQ_WAVE || lane < kPerPass * KP) reinterpret_cast<float *>(buf)[f * CMPQ_WAVE + lane] = e;
+        }
+    };
+    // A lane's B words of a row: one vector load where the tile is whole, else word by word, past the end of
+    // the row its last one again (outputs that are not there are not written).  Past the last row that one
+    // again: its tables are zero.
+    const int64_t wpr = wd.words_per_row;
+    const bool whole = (tile + 1) * (kTileOut / 32) * B <= wd.words_per_row;
+    const uint32_t *packed = wd.packed + (int64_t)r0 * wpr + (whole ? tile * (kTileOut / 32) * B : 0);
+    const uint32_t word0 = (uint32_t)((whole ? 0 : tile * (kTileOut / 32) * B) + lane * B);
+    auto load_words = [&](int r, uint32_t (&w)[G][B]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const uint32_t *p = packed + (int64_t)min(r + g, n - 1) * wpr;  // uniform
+            if (whole) {
                 typedef uint32_t WordsB __attribute__((ext_vector_type(B), aligned(4)));
-                const WordsB v = __builtin_nontemporal_load(reinterpret_cast<const WordsB *>(p));
+                // (a uniform base and a 32-bit offset; a token reads the codes once)
+                const WordsB v = __builtin_nontemporal_load(reinterpret_cast<const WordsB *>(reinterpret_cast<const char *>(p) + word0 * 4u));
 #pragma unroll
                 for (int j = 0; j < B; ++j) w[g][j] = v[j];
             } else {
 #pragma unroll
-                for (int j = 0; j < B; ++j) w[g][j] = (r + g < r1 && word0 + j < wd.words_per_row) ? p[j] : 0u;
+                for (int j = 0; j < B; ++j)
+                    w[g][j] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(p) + min(word0 + j, (uint32_t)wpr - 1u) * 4u);
             }
         }
     };
-
-    if (r0 < r1) {
-        uint32_t w[kGroup][B], wn[kGroup][B];
-        float ea[kFills], eb[kFills], ean[kFills], ebn[kFills];
-        table_entries(r0, ea, eb);
-        load_words(r0, w);
-        int buf = 0;
-        for (int64_t r = r0; r < r1; r += kGroup) {
-            float *mine = smem + (wave * 2 + buf) * kBufFloats;
+    auto add_up = [&](int r, const uint32_t (&w)[G][B], uint32_t at) {
 #pragma unroll
-            for (int f = 0; f < kFills; ++f) {
-                if (fill_row < kRowsPerFill) {
-                    float *row_tbl = mine + (f * kRowsPerFill + fill_row) * kRowFloats;
-                    row_tbl[fill_e] = ea[f];
-                    row_tbl[KP + fill_e] = eb[f];
+        for (int t = 0; t < kTables; ++t) {
+            if constexpr (B == 4) {
+                // (the input multiplies here, not in the table: no lane needs another row's)
+                const float xi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x_mine), (r + t) & (CMPQ_WAVE - 1)));
+#pragma unroll
+                for (int q = 0; q < B; ++q)
+#pragma unroll
+                    for (int odd = 0; odd < 2; ++odd) {
+                        const uint32_t n4 = nibbles4(w[t][q], odd);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float &y = acc[8 * q + 2 * i + odd];
+                            y = fmaf(xi, lds_read<float>(add_byte(at, n4, i) + t * KP * 4), y);
+                        }
+                    }
+            } else {
+                const PairWords<B> pw(w[2 * t], w[2 * t + 1]);
+                if constexpr (B == 2) {
+#pragma unroll
+                    for (int q = 0; q < B; ++q)
+#pragma unroll
+                        for (int odd = 0; odd < 2; ++odd) {
+                            const uint32_t ne = nibbles4(pw.even[q], odd), no = nibbles4(pw.odd[q], odd);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int o = 16 * q + 2 * (2 * i + odd);
+                                acc[o] += lds_read<float>(add_byte(at, ne, i) + t * KP * 4);
+                                acc[o + 1] += lds_read<float>(add_byte(at, no, i) + t * KP * 4);
+                            }
+                        }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kOutPerLane / 2; ++i) {
+                        acc[2 * i] += lds_read<float>(entry_offset(field_at<B, 2 * B>(pw.even, i), at) + t * KP * 4);
+                        acc[2 * i + 1] += lds_read<float>(entry_offset(field_at<B, 2 * B>(pw.odd, i), at) + t * KP * 4);
+                    }
                 }
             }
-            if (r + kGroup < r1) {
-                table_entries(r + kGroup, ean, ebn);
-                load_words(r + kGroup, wn);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const char *base = reinterpret_cast<const char *>(smem);
-            const uint32_t wb = (uint32_t)((wave * 2 + buf) * (kBufFloats * 4));
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g) {
-                // rows past the end have all-zero tables: their look-ups add 0
-#pragma unroll
-                for (int p = 0; p < kOutPerLane / 2; ++p) {
-                    const char *at = base + g * (kRowFloats * 4) + entry_offset(field_at<B, PB>(w[g], p), wb);
-                    acc[2 * p] += *reinterpret_cast<const float *>(at);
-                    acc[2 * p + 1] += *reinterpret_cast<const float *>(at + KP * 4);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            buf ^= 1;
-#pragma unroll
-            for (int f = 0; f < kFills; ++f) {
-                ea[f] = ean[f];
-                eb[f] = ebn[f];
-            }
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-                for (int j = 0; j < B; ++j) w[g][j] = wn[g][j];
         }
+    };
+    // Words are fetched one group ahead, levels two; a group's tables are written while the group
+    // before is worked on, into the buffer its predecessor has left.
+    uint32_t w0[G][B], w1[G][B];
+    Levels v;
+    const uint32_t at = (uint32_t)reinterpret_cast<uintptr_t>(tables);
+    fetch_levels(0, v);
+    load_words(0, w0);
+    write_tables(0, v, tables);
+    fetch_levels(G, v);
+    wave_fence();
+#pragma unroll 1
+    for (int r = 0; r < n; r += 2 * G) {
+        write_tables(r + G, v, tables + kPartTable);
+        load_words(r + G, w1);
+        fetch_levels(r + 2 * G, v);
+        add_up(r, w0, at);
+        wave_fence();
+        if (r + G >= n) break;
+        write_tables(r + 2 * G, v, tables);
+        load_words(r + 2 * G, w0);
+        fetch_levels(r + 3 * G, v);
+        add_up(r + G, w1, at + kPartTable);
+        wave_fence();
     }
-    store_partial(acc, red, a.partial + (token * a.n_rows_total + wd.slab0 + slab) * d_out, d_out);
 }
 
 // The variant that adds up in FP16 (the paper's product keeps FP16 throughout, Sec. 6): the
 // products x * level are rounded to FP16, and a wavefront adds those of its run of at most 32
 // rows of a slab in FP16, two outputs per packed addition; the run's sums are then widened
-// to fp32 and take the same way as in lut_slab (added over wavefronts, slabs, O_act and O_q in
+// to fp32 and take the same way as the fp32 parts' (added over wavefronts, slabs, O_act and O_q in
 // fp32, in a fixed order).  Every width looks two neighbouring codes up at once: per row a
 // table of 2^(2B) pairs (product of the even output's code, product of the odd one's), 4
 // bytes an entry, built from the row's 2^B products with two LDS reads per entry (for width
@@ -341,8 +317,8 @@ __device__ __forceinline__ void lut_slab_pairs(const LmArgs &a, const LmWidth &w
 // store).  A weight then costs half an extract, half a shift-and-add, half an LDS read and
 // half a packed addition.  Tables of 64 and 256 entries wrap around the LDS banks, so their
 // reads collide; with 4-byte entries that costs less than the instructions saved (with the
-// 8-byte entries of fp32 pairs it did not).  Same slab shape, prefetch and double buffering
-// as lut_slab.
+// 8-byte entries of fp32 pairs it did not).  Words and levels are
+// fetched a group ahead, tables are double-buffered.
 constexpr int kHalfPairBytes = kGroup * 256 * 4;               // pair tables of a group of rows at width 4
 constexpr int kHalfBufBytes = kHalfPairBytes + kGroup * 16 * 2;  // + the rows' own products
 constexpr int kHalfLdsBytes = kWaves * 2 * kHalfBufBytes;
@@ -455,29 +431,21 @@ __device__ __forceinline__ void lut_slab_half(const LmArgs &a, const LmWidth &wd
         acc[2 * p] = __low2float(acc2[p]);
         acc[2 * p + 1] = __high2float(acc2[p]);
     }
-    store_partial(acc, red, a.partial + (token * a.n_rows_total + wd.slab0 + slab) * d_out, d_out);
+    store_partial(acc, red, a.partial + (token * a.n_rows_total + wd.slab0 + slab) * d_out, (int64_t)blockIdx.x * kTileOut, d_out);
 }
 
-// A slab of O_act: 8 rows of FP16 weights per wavefront times their inputs (few rows, so
-// short slabs: the loop over rows is bound by latency).  A lane reads its 32 outputs of a
+// Rows of O_act: up to 8 rows of FP16 weights per wavefront times their inputs (few rows, so
+// short parts: the loop over rows is bound by latency).  A lane reads its 32 outputs of a
 // row as four 16-byte pieces, two rows in flight; the rows' inputs are fetched up front,
 // one per lane.
 constexpr int kActRowsPerWave = 8;
 
-__device__ __forceinline__ void act_slab(const LmArgs &a, int slab, float (*red)[kRedFloats]) {
-    const __half *__restrict__ X = a.X;
-    const int64_t ldx = a.ldx, d_out = a.d_out;
-    float *__restrict__ partial = a.partial;
-    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    const int64_t token = blockIdx.z;
-    const __half *x = X + token * ldx;
-    const int64_t o0 = (int64_t)blockIdx.x * kTileOut + (int64_t)lane * kOutPerLane;
-    const int64_t r0 = ((int64_t)slab * kWaves + wave) * kActRowsPerWave;
-    const int n = (int)max((int64_t)0, min(a.k_act - r0, (int64_t)kActRowsPerWave));
-    float acc[kOutPerLane];
-#pragma unroll
-    for (int k = 0; k < kOutPerLane; ++k) acc[k] = 0.f;
-    const float x_mine = lane < n ? __half2float(x[a.act_idx[r0 + lane]]) : 0.f;
+template <typename Args>
+__device__ __forceinline__ void act_rows(const Args &a, const int32_t *__restrict__ act_idx, const __half *__restrict__ x,
+                                         int64_t r0, int n, int64_t o0, float (&acc)[kOutPerLane]) {
+    const int lane = threadIdx.x & (CMPQ_WAVE - 1);
+    const int64_t d_out = a.d_out;
+    const float x_mine = lane < n ? __half2float(x[act_idx[r0 + lane]]) : 0.f;
     // every row's input in a scalar register (rows past the count: 0), read before lanes part ways
     float xs[kActRowsPerWave];
 #pragma unroll
@@ -520,41 +488,68 @@ __device__ __forceinline__ void act_slab(const LmArgs &a, int slab, float (*red)
                 if (o0 + k < d_out) acc[k] = fmaf(xi, __half2float(wrow[k]), acc[k]);
         }
     }
-    store_partial(acc, red, partial + (token * a.n_rows_total + a.n_lut_slabs + slab) * d_out, d_out);
 }
 
-// grid: (tiles of 2048 outputs of the widest layer; per layer its O_act slabs, then its packed
-// slabs of all widths one after the other; tokens)
-__global__ __launch_bounds__(kThreads) void lut_matvec_kernel(LmGroup g) {
+__device__ __forceinline__ void act_slab(const LmArgs &a, int slab, float (*red)[kRedFloats]) {
+    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
+    const int64_t token = blockIdx.z, o_tile = (int64_t)blockIdx.x * kTileOut;
+    const int64_t r0 = ((int64_t)slab * kWaves + wave) * kActRowsPerWave;
+    float acc[kOutPerLane];
+#pragma unroll
+    for (int k = 0; k < kOutPerLane; ++k) acc[k] = 0.f;
+    act_rows(a, a.act_idx, a.X + token * a.ldx, r0, (int)max((int64_t)0, min(a.k_act - r0, (int64_t)kActRowsPerWave)),
+             o_tile + (int64_t)lane * kOutPerLane, acc);
+    store_partial(acc, red, a.partial + (token * a.n_rows_total + a.n_lut_slabs + slab) * a.d_out, o_tile, a.d_out);
+}
+
+// Workgroups of a layer: per tile of 2048 outputs its slabs of four parts, side by side, so that every
+// compute unit gets parts of all widths; blockIdx.y: token.
+__global__ __launch_bounds__(kThreads) void lut_matvec_kernel(MvGroup g) {
     // the tables of the look-ups and, after them, the wavefronts' sums share one piece of LDS
-    __shared__ float smem[kWaves * kRedFloats];
-    float(*tbl)[2][kGroup * 16] = reinterpret_cast<float(*)[2][kGroup * 16]>(smem);
+    __shared__ __align__(16) float smem[kWaves * kRedFloats];
+    static_assert(kWaves * 2 * kPartTable <= kWaves * kRedFloats * (int)sizeof(float), "the tables fit the shared piece");
     float(*red)[kRedFloats] = reinterpret_cast<float(*)[kRedFloats]>(smem);
-    static_assert(kWaves * 2 * kGroup * 2 * 16 <= kWaves * kRedFloats, "pair tables fit the shared piece");
     int l = 0;
-    while (l + 1 < g.n_layers && (int)blockIdx.y >= g.l[l + 1].y0) ++l;
-    const LmArgs &a = g.l[l];
-    if ((int)blockIdx.x >= a.tiles) return;
-    int y = (int)blockIdx.y - a.y0;
-    if (y < a.n_act_slabs) {
-        act_slab(a, y, red);
-        return;
-    }
-    y -= a.n_act_slabs;
+#pragma unroll
+    for (int i = 1; i < kMaxLayers; ++i) l += (int)blockIdx.x >= g.wg0[i];
+    const MvLayer &a = g.l[l];
+    const int wg = (int)blockIdx.x - g.wg0[l], slab = wg % a.slabs, tile = wg / a.slabs;
+    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
+    const int64_t token = blockIdx.y, o_tile = (int64_t)tile * kTileOut;
+    const int part = slab * kWaves + wave;
     int j = 0;
-    while (j + 1 < a.n_widths && y >= a.w[j + 1].slab0) ++j;
-    const LmWidth &wd = a.w[j];
-    const int slab = y - wd.slab0;
-    switch (wd.bits) {
-        case 1: lut_slab<1>(a, wd, slab, tbl, red); break;
-        case 2: lut_slab_pairs<2>(a, wd, slab, smem, red); break;
-        case 3: lut_slab<3>(a, wd, slab, tbl, red); break;
-        default: lut_slab<4>(a, wd, slab, tbl, red); break;
+#pragma unroll
+    for (int i = 1; i <= kMaxWidths; ++i) j += i < a.n_w && part >= a.w[i].part0;
+    const MvWidth &wd = a.w[j];
+    const __half *x = a.X + token * a.ldx;
+    const int p = part - wd.part0;  // parts past the last one of the last slab are empty
+    int r0, n;
+    if (wd.bits == kActBits) {
+        r0 = p * kActRowsPerWave;
+        n = min(wd.rows - r0, kActRowsPerWave);
+    } else {  // even shares of the row groups
+        const uint32_t group = wd.bits <= 2 ? 8 : 4, groups = ((uint32_t)wd.rows + group - 1) / group, parts = (uint32_t)wd.parts;
+        r0 = (int)(groups * min((uint32_t)p, parts) / parts * group);
+        n = min((int)(groups * min((uint32_t)p + 1u, parts) / parts * group), wd.rows) - r0;
     }
+    float acc[kOutPerLane];
+#pragma unroll
+    for (int k = 0; k < kOutPerLane; ++k) acc[k] = 0.f;
+    if (n > 0) {
+        unsigned char *tables = reinterpret_cast<unsigned char *>(smem) + wave * 2 * kPartTable;
+        switch (wd.bits) {
+            case 1: lut_part<1>(a, wd, x, r0, n, tile, tables, acc); break;
+            case 2: lut_part<2>(a, wd, x, r0, n, tile, tables, acc); break;
+            case 3: lut_part<3>(a, wd, x, r0, n, tile, tables, acc); break;
+            case 4: lut_part<4>(a, wd, x, r0, n, tile, tables, acc); break;
+            default: act_rows(a, wd.chan, x, r0, n, o_tile + (int64_t)lane * kOutPerLane, acc); break;
+        }
+    }
+    store_partial(acc, red, a.partial + (token * a.slabs + slab) * a.d_out, o_tile, a.d_out);
 }
 
-// The same launch with the packed rows added up in FP16 (lut_slab_half); the O_act slabs are
-// the fp32 ones.
+// The packed rows added up in FP16 (lut_slab_half); grid: (tiles of 2048 outputs of the widest layer; per
+// layer its O_act slabs, then its packed slabs of all widths one after the other; tokens).
 __global__ __launch_bounds__(kThreads) void lut_matvec_half_kernel(LmGroup g) {
     __shared__ __align__(16) unsigned char smem[kHalfLdsBytes];
     static_assert(kHalfLdsBytes >= kWaves * kRedFloats * (int)sizeof(float), "the wavefronts' sums fit the shared piece");
@@ -585,10 +580,10 @@ constexpr int kFinCols = 16;  // outputs per workgroup
 constexpr int kFinRuns = kThreads / kFinCols;
 
 // 16 consecutive outputs per workgroup of 256 lanes.
+//   * partial rows: cut into 16 runs of consecutive rows; lane (run, output) adds its run up in eights,
+//     each in pairs; the loads of the first eight are on their way before anything else.
 //   * O_q: 16 lanes per column; lane l takes the column's entries l, l+16, ... (8 in flight)
 //     and adds them in that order.
-//   * partial rows: cut into 16 runs of consecutive rows; lane (run, output) adds its run in
-//     row order (4 loads in flight).
 // Per output, the 16 run sums are added in run order, then the 16 O_q sums in lane order.
 struct FinArgs {
     const __half *X;
@@ -607,28 +602,34 @@ struct FinGroup {
     int n_layers;
 };
 
-__global__ __launch_bounds__(kThreads) void lut_matvec_finish_kernel(FinGroup g) {
+__global__ __launch_bounds__(kThreads, 8) void lut_matvec_finish_kernel(FinGroup g) {
     int l = 0;
     while (l + 1 < g.n_layers && (int)blockIdx.x >= g.l[l + 1].x0) ++l;
     const FinArgs &a = g.l[l];
-    const __half *__restrict__ X = a.X;
-    const int64_t ldx = a.ldx, d_out = a.d_out, ldy = a.ldy;
-    const float *__restrict__ partial = a.partial;
-    const int n_rows_total = a.n_rows_total;
-    const int32_t *__restrict__ colptr = a.colptr;
-    const int32_t *__restrict__ row_idx = a.row_idx;
-    const float *__restrict__ delta = a.delta;
-    float *__restrict__ Y = a.Y;
-    constexpr int U = 8;
+    constexpr int U = 8, kInFlight = 8;
     __shared__ float part[kFinRuns][kFinCols + 1];
     __shared__ float sp[kFinCols][kFinRuns + 1];
     const int hi = threadIdx.x / kFinCols, lo = threadIdx.x % kFinCols;
-    const int64_t token = blockIdx.y;
-    const int64_t o0 = (int64_t)((int)blockIdx.x - a.x0) * kFinCols;
-    const __half *x = X + token * ldx;
+    const int64_t d_out = a.d_out, token = blockIdx.y, o0 = (int64_t)((int)blockIdx.x - a.x0) * kFinCols;
+    const int n_rows = a.n_rows_total;
+    // partial rows of output o0 + lo, run hi
+    const int per = (n_rows + kFinRuns - 1) / kFinRuns, r0 = hi * per, r1 = o0 + lo < d_out ? min(n_rows, r0 + per) : 0;
+    const float *p = a.partial + token * n_rows * d_out + o0 + lo;
+    float v[kInFlight];
+    auto fetch = [&](int r) {
+#pragma unroll
+        for (int q = 0; q < kInFlight; ++q) v[q] = r + q < r1 ? p[(int64_t)(r + q) * d_out] : 0.f;
+    };
+    auto pairwise = [&] { return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])); };
+    static_assert(kInFlight == 8, "");
+    fetch(r0);
     // O_q of column o0 + hi, entries lo, lo + 16, ...
+    const int32_t *__restrict__ colptr = a.colptr;
     float t = 0.f;
     if (colptr && o0 + hi < d_out) {
+        const int32_t *__restrict__ row_idx = a.row_idx;
+        const float *__restrict__ delta = a.delta;
+        const __half *x = a.X + token * a.ldx;
         const int e1 = colptr[o0 + hi + 1];
         for (int e = colptr[o0 + hi] + lo; e < e1; e += 16 * U) {
             int32_t r[U];
@@ -647,21 +648,10 @@ __global__ __launch_bounds__(kThreads) void lut_matvec_finish_kernel(FinGroup g)
         }
     }
     sp[hi][lo] = t;
-    // partial rows of output o0 + lo, run hi
-    float y = 0.f;
-    if (o0 + lo < d_out) {
-        const int per = (n_rows_total + kFinRuns - 1) / kFinRuns;
-        const int r0 = hi * per, r1 = min(n_rows_total, r0 + per);
-        const float *p = partial + token * n_rows_total * d_out + o0 + lo;
-        int r = r0;
-        for (; r + 4 <= r1; r += 4) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = p[(int64_t)(r + u) * d_out];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) y += v[u];
-        }
-        for (; r < r1; ++r) y += p[(int64_t)r * d_out];
+    float y = pairwise();
+    for (int r = r0 + kInFlight; r < r1; r += kInFlight) {
+        fetch(r);
+        y += pairwise();
     }
     part[hi][lo] = y;
     __syncthreads();
@@ -671,7 +661,7 @@ __global__ __launch_bounds__(kThreads) void lut_matvec_finish_kernel(FinGroup g)
         for (int q = 0; q < kFinRuns; ++q) dense += part[q][threadIdx.x];
 #pragma unroll
         for (int q = 0; q < 16; ++q) sparse += sp[threadIdx.x][q];
-        Y[token * ldy + o0 + threadIdx.x] = dense + sparse;
+        a.Y[token * a.ldy + o0 + threadIdx.x] = dense + sparse;
     }
 }
 
@@ -902,19 +892,60 @@ int check_layer(const cmpq_deployed_layer &L, int64_t m) {
 // The token-by-token launch of the layers order[0..n), `tokens` of the call's m at a time: arguments
 // of its two kernels, grid and scratch.
 struct Plan {
-    LmGroup g;
+    LmGroup g;    // FP16 sums
+    MvGroup mv;   // fp32 sums
     FinGroup f;
     size_t ws_used;
-    int64_t y_total, x_total, max_tiles;
+    int64_t y_total, x_total, max_tiles, wgs;
 };
 
+// Parts of a layer for fp32 sums: up to 512 workgroups in all, two per compute unit, of 8 rows a
+// wavefront or more; larger layers in more, of 32 rows at width 4 (40 at 3, 48 at 2; with fewer the partial rows would need
+// more scratch than calls had to bring before).  A width's rows
+// count by what one costs (vector instructions a weight, see lut_part).  Kernel times of an earlier build,
+// us: query, key and value of 8192 channels in 978 workgroups 20.6, in 1370 24.9; 8192 outputs of 28672
+// channels in 496 39.8, in 740 34.6, in 976 32.5; twice 28672 of 8192 in 1008 56.1, in 1484 62.3, in 1960 57.5.
+// (Bounds checks taken out of the loops, now: 17.5 in 978, 33.3 in 820, 53.1 in 1652.)
+constexpr int64_t kMostCost = 160;
+int part_rows(int bits, int64_t cost) {
+    static const int kCost[5] = {0, 3, 3, 4, 5};
+    const int group = bits <= 2 ? kPartGroup<1> : kPartGroup<4>;
+    int64_t n = cost / kCost[bits] / group * group;
+    return (int)(n < 8 ? 8 : (n > kMaxPartRows ? kMaxPartRows : n));
+}
+void choose_parts(MvLayer &a, int64_t tiles, int64_t tokens) {
+    int64_t want = 512 / (tiles * tokens) * kWaves, act = 0, cost = 0;
+    for (int j = 0; j < a.n_w; ++j) {
+        if (a.w[j].bits == kActBits) act = cdiv(a.w[j].rows, (int64_t)kActRowsPerWave);
+        else cost += (int64_t)a.w[j].rows * (a.w[j].bits + 1);  // no more than what the parts will cost
+    }
+    want = want > act + kWaves ? want - act : kWaves;
+    cost /= want;
+    cost = cost < 16 ? 16 : (cost > kMostCost ? kMostCost : cost);
+    for (;; cost += 4) {
+        int64_t parts = 0;
+        for (int j = 0; j < a.n_w; ++j)
+            if (a.w[j].bits != kActBits) parts += cdiv(a.w[j].rows, (int64_t)part_rows(a.w[j].bits, cost));
+        if (parts <= want || cost >= kMostCost) break;
+    }
+    int part = 0;
+    for (int j = 0; j < a.n_w; ++j) {
+        MvWidth &w = a.w[j];
+        w.part0 = part;
+        w.parts = (int)cdiv(w.rows, (int64_t)(w.bits == kActBits ? kActRowsPerWave : part_rows(w.bits, cost)));
+        part += w.parts;
+    }
+    a.slabs = (int)cdiv((int64_t)part, (int64_t)kWaves);
+}
+
 void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, int n, int64_t m, int64_t tokens, void *ws,
-                         Plan &p) {
+                         Plan &p, bool half_sums) {
     LmGroup &g = p.g;
     FinGroup &f = p.f;
     g.n_layers = f.n_layers = n;
     p.ws_used = 0;
-    p.y_total = p.x_total = p.max_tiles = 0;
+    p.y_total = p.x_total = p.max_tiles = p.wgs = 0;
+    for (int s = 0; s < kMaxLayers; ++s) p.mv.wg0[s] = INT_MAX;
     for (int s = 0; s < n; ++s) {
         const cmpq_deployed_layer &L = layers[order[s]];
         LmArgs &a = g.l[s];
@@ -966,6 +997,26 @@ void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, in
         fa.Y = L.Y;
         fa.ldy = L.ldy;
         fa.n_rows_total = (int)n_rows;
+        if (!half_sums) {
+            // (fewer parts than what the scratch is reserved for, which a caller may count on)
+            MvLayer &v = p.mv.l[s];
+            v.n_w = 0;
+            for (int j = 0; j < a.n_widths; ++j)
+                v.w[v.n_w++] = MvWidth{a.w[j].packed, a.w[j].chan_idx, a.w[j].lut, (int)a.w[j].rows, (int)a.w[j].words_per_row, a.w[j].bits, 0, 0};
+            if (L.k_act > 0) v.w[v.n_w++] = MvWidth{nullptr, L.act_idx, nullptr, (int)L.k_act, 0, kActBits, 0, 0};
+            for (int j = v.n_w; j <= kMaxWidths; ++j) v.w[j] = MvWidth{};
+            v.X = a.X;
+            v.W_act = a.W_act;
+            v.ldx = L.ldx;
+            v.ld_act = L.ld_act;
+            v.partial = a.partial;
+            v.d_out = (int)L.d_out;
+            v.act_vec_ok = a.act_vec_ok;
+            choose_parts(v, tiles, m);
+            fa.n_rows_total = v.slabs;
+            p.mv.wg0[s] = (int)p.wgs;
+            p.wgs += tiles * v.slabs;
+        }
         fa.x0 = (int)p.x_total;
         p.ws_used += align_up((size_t)tokens * (size_t)n_rows * (size_t)L.d_out * sizeof(float), 256);
         p.y_total += n_rows;
@@ -975,15 +1026,14 @@ void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, in
     for (int s = n; s < kMaxLayers; ++s) {
         g.l[s] = g.l[0];
         f.l[s] = f.l[0];
+        p.mv.l[s] = p.mv.l[0];
     }
 }
 
 int launch_token_by_token(const Plan &p, int64_t tokens, bool half_sums, hipStream_t st) {
-    if (p.y_total > 0) {
-        const dim3 grid((unsigned)p.max_tiles, (unsigned)p.y_total, (unsigned)tokens);
-        if (half_sums) lut_matvec_half_kernel<<<grid, kThreads, 0, st>>>(p.g);
-        else lut_matvec_kernel<<<grid, kThreads, 0, st>>>(p.g);
-    }
+    if (half_sums && p.y_total > 0)
+        lut_matvec_half_kernel<<<dim3((unsigned)p.max_tiles, (unsigned)p.y_total, (unsigned)tokens), kThreads, 0, st>>>(p.g);
+    if (!half_sums && p.wgs > 0) lut_matvec_kernel<<<dim3((unsigned)p.wgs, (unsigned)tokens), kThreads, 0, st>>>(p.mv);
     const dim3 fgrid((unsigned)p.x_total, (unsigned)tokens);
     lut_matvec_finish_kernel<<<fgrid, kThreads, 0, st>>>(p.f);
     CMPQ_LAUNCH_CHECK();
@@ -1015,17 +1065,17 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t have = ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 ? ws_bytes : 0;
     Plan p;
-    plan_token_by_token(layers, order, n_live, m, m, ws, p);
+    plan_token_by_token(layers, order, n_live, m, m, ws, p, half_sums);
     if (p.y_total > 65535 || p.x_total > 0x7fffffff) return CMPQ_ESHAPE;
     if (half_sums) {
         // as many tokens at a time as the workspace holds, the same numbers however many
         int64_t tokens = m;
         if (p.ws_used > have) {
-            plan_token_by_token(layers, order, n_live, m, 1, ws, p);
+            plan_token_by_token(layers, order, n_live, m, 1, ws, p, true);
             if (p.ws_used > have) return CMPQ_EWORKSPACE;
             // (a token's rows fill whole 256 bytes at most once over; parts of even size)
             tokens = cdiv(m, cdiv(m, (int64_t)(have / p.ws_used)));
-            plan_token_by_token(layers, order, n_live, m, tokens, ws, p);
+            plan_token_by_token(layers, order, n_live, m, tokens, ws, p, true);
         }
         for (int64_t t = 0; t < m; t += tokens) {
             const int rc = launch_token_by_token(p, m - t < tokens ? m - t : tokens, true, st);
@@ -1055,7 +1105,7 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
     if (n_rest == n_live) return p.ws_used > have ? CMPQ_EWORKSPACE : launch_token_by_token(p, m, false, st);
     if (p.ws_used > have) {
         if (sum > have) return CMPQ_EWORKSPACE;
-        if (n_rest > 0) plan_token_by_token(layers, rest, n_rest, m, m, ws, p);
+        if (n_rest > 0) plan_token_by_token(layers, rest, n_rest, m, m, ws, p, false);
         if (n_rest > 0 && p.ws_used > have) return CMPQ_EWORKSPACE;
     }
     const cmpq_deployed_layer *batch[kMaxLayers];
@@ -1080,7 +1130,7 @@ int launch_group(const cmpq_deployed_layer *layers, int n_layers, int64_t m, voi
         }
     }
     if (n_rest == 0) return CMPQ_OK;
-    plan_token_by_token(layers, rest, n_rest, m, m, ws, p);
+    plan_token_by_token(layers, rest, n_rest, m, m, ws, p, false);
     return launch_token_by_token(p, m, false, st);
 }
 
