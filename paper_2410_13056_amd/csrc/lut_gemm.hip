@@ -9,7 +9,7 @@
 // operands, one per output, of 8 rows each: operand e of the wavefront covers the outputs
 // 16 i + e.  No code passes between lanes.
 //
-//   * tokens_kernel     X in operand order (rows as the steps take them), and channel by channel
+//   * order_tokens      X in operand order (rows as the steps take them), and channel by channel
 //                       for the entries of O_q;
 //   * few tokens: lut_tokens_kernel multiplies while it decodes - a weight is decoded once per
 //     16 or 32 tokens and never stored - and leaves one partial result per slab of rows;
@@ -81,15 +81,19 @@ struct Group {
     int n_layers, m, token_tiles;
     Layer l[kMaxLayers];
 };
-static_assert(sizeof(Group) <= 4096, "travels in the kernel arguments");
+static_assert(sizeof(Group) + 64 <= 4096, "travels in the kernel arguments");
 
-// The layer a workgroup belongs to, and its number among that layer's workgroups.
-__device__ __forceinline__ const Layer &layer_of(const Group &g, int &wg) {
+// The layer that workgroup `wg` of the launch belongs to; `wg` becomes its number among that layer's.
+__device__ __forceinline__ const Layer &layer_of(const Group &g, const int (&wg0)[kMaxLayers], int &wg) {
     int l = 0;
 #pragma unroll
-    for (int i = 1; i < kMaxLayers; ++i) l += (int)blockIdx.x >= g.wg0[i];
-    wg = (int)blockIdx.x - g.wg0[l];
+    for (int i = 1; i < kMaxLayers; ++i) l += wg >= wg0[i];
+    wg -= wg0[l];
     return g.l[l];
+}
+__device__ __forceinline__ const Layer &layer_of(const Group &g, int &wg) {
+    wg = (int)blockIdx.x;
+    return layer_of(g, g.wg0, wg);
 }
 
 // Workgroups are dealt out to the 8 XCDs in turn.  This renumbering gives each XCD a contiguous
@@ -104,9 +108,8 @@ __device__ __forceinline__ int xcd_order(int i, int n) {
 
 // Workgroups of a layer: per token tile, blocks of 256 rows (8 steps) of the operand order, then
 // blocks of 256 channels.
-__global__ __launch_bounds__(kThreads) void tokens_kernel(Group g) {
-    int b;
-    const Layer &L = layer_of(g, b);
+constexpr int kTokensLds = kTok * (kThreads + 8) * 2;
+__device__ __forceinline__ void order_tokens(const Group &g, const Layer &L, int b, unsigned char *smem) {
     const int tid = threadIdx.x;
     const int row_blocks = (L.steps + 7) / 8, chan_blocks = L.xt ? (L.d_in + kThreads - 1) / kThreads : 0;
     const int tt = b / (row_blocks + chan_blocks);
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void tokens_kernel(Group g) {
         dst[1] = reinterpret_cast<const uint4 *>(v)[1];
         return;
     }
-    __shared__ __align__(16) __half s[kTok][kThreads + 8];
+    __half(*s)[kThreads + 8] = reinterpret_cast<__half(*)[kThreads + 8]>(smem);
     const int k = b * kThreads + tid, step = k / kRowsPerStep;
     int chan = -1;
     if (step < L.steps) {
@@ -146,6 +149,13 @@ __global__ __launch_bounds__(kThreads) void tokens_kernel(Group g) {
             L.xf[((int64_t)tt * L.steps + b * 8 + st) * CMPQ_WAVE + lane] =
                 *reinterpret_cast<const uint4 *>(&s[lane % 16][st * kRowsPerStep + (lane / 16) * 8]);
     }
+}
+
+__global__ __launch_bounds__(kThreads) void tokens_kernel(Group g) {
+    __shared__ __align__(16) unsigned char smem[kTokensLds];
+    int b;
+    const Layer &L = layer_of(g, b);
+    order_tokens(g, L, b, smem);
 }
 
 // What the decoding of a tile needs of its layer, copied out of the kernel arguments once.
@@ -676,11 +686,23 @@ __device__ __forceinline__ void decode_step(const TileArgs &L, const Seg &s, Wor
     }
 }
 
-// A wavefront: one step of one tile.
-__global__ __launch_bounds__(kThreads) void lut_decode_kernel(Group g) {
-    __shared__ __align__(kTableBytes) unsigned char smem[kWaves * kTableBytes];
-    int wg;
-    const Layer &L = layer_of(g, wg);
+// X in operand order (the first workgroups) and W_hat in operand order, a wavefront for one step of one
+// tile: neither needs the other, and as launches of their own the inputs took 13 us beside the 41 of
+// the decoding (a 4096-wide group of two MLP layers, 512 tokens).
+struct DecodeWgs {
+    int wg0[kMaxLayers];  // first workgroup of each layer among those that decode
+    int first;            //   and the first of those in the launch
+};
+__global__ __launch_bounds__(kThreads) void lut_decode_kernel(Group g, DecodeWgs d) {
+    __shared__ __align__(kTableBytes) unsigned char smem[kTokensLds > kWaves * kTableBytes ? kTokensLds : kWaves * kTableBytes];
+    int wg = (int)blockIdx.x;
+    if (wg < d.first) {
+        const Layer &L = layer_of(g, g.wg0, wg);
+        order_tokens(g, L, wg, smem);
+        return;
+    }
+    wg -= d.first;
+    const Layer &L = layer_of(g, d.wg0, wg);
     const int wave = wave_index();
     const int unit = wg * kWaves + wave, tiles = L.tiles;
     const int step = unit / tiles, tile = unit - step * tiles;
@@ -1075,7 +1097,7 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
             if (nd > 4 && (int64_t)G->l[i].d_in * G->l[i].d_out > kDirectWeights) direct = false;
             if (cdiv(G->l[i].steps, G->l[i].slabs > 0 ? G->l[i].slabs : 1) >= direct_steps(nd)) direct = false;
         }
-        if (wx && !direct) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
+        if (wx && !direct && G == &few) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
         if (G == &few) {
             const unsigned w = number([&](const Layer &L) { return (int64_t)L.tiles * L.slabs * (tts / MT); });
             if (w > 0) {
@@ -1094,8 +1116,14 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
             else if (m <= 8) tokens_finish_kernel<8, false><<<f, kThreads, 0, s>>>(*G);
             else tokens_finish_kernel<16, false><<<f, kThreads, 0, s>>>(*G);
         } else {
-            const unsigned w = number([&](const Layer &L) { return cdiv((int64_t)L.steps * L.tiles, (int64_t)kWaves); });
-            lut_decode_kernel<<<w, kThreads, 0, s>>>(*G);
+            DecodeWgs d;
+            int64_t w = 0;
+            for (int i = 0; i < kMaxLayers; ++i) {
+                d.wg0[i] = i < n ? (int)w : INT_MAX;
+                if (i < n) w += cdiv((int64_t)G->l[i].steps * G->l[i].tiles, (int64_t)kWaves);
+            }
+            d.first = (int)wx;
+            lut_decode_kernel<<<(unsigned)(wx + w), kThreads, 0, s>>>(*G, d);
             bool any = false;
             for (int i = 0; i < n; ++i) any = any || G->l[i].colptr;
             if (any) {
