@@ -178,6 +178,15 @@ int cmpq_allocate_bits(const float *sumsq, int64_t d_in, const uint8_t *chan_mas
                        void *stream);
 
 /*
+ * O_act and Algorithm 1 in one call: cmpq_extract_outliers(CMPQ_OUTLIER_CHANNELS, k = k_act) into act_idx
+ * [k_act] and chan_mask [d_in], then cmpq_allocate_bits with that mask.  The same results; up to 8192
+ * channels in one launch.  No workspace.
+ */
+int cmpq_rank_channels(const float *sumsq, int64_t d_in, int64_t k_act, const int32_t *bit_set, int n_set,
+                       double avg_bits, int32_t *act_idx, uint8_t *chan_mask, uint8_t *bits,
+                       int64_t *counts_host, void *stream);
+
+/*
  * The two outlier extractions of Sec. 3.2.2.  Both pick the k largest keys under the
  * order "larger key first, equal keys by smaller index" and return indices ascending.
  *

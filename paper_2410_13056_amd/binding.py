@@ -41,7 +41,7 @@ EXPORTS = ("cmpq_workspace_bytes", "cmpq_strerror", "cmpq_count_ppm", "cmpq_act_
            "cmpq_gather_channels", "cmpq_outliers_by_column", "cmpq_lut_matvec", "cmpq_act_stats_norm",
            "cmpq_rtn_quantize", "cmpq_select_by_width", "cmpq_lut_matvec_group", "cmpq_lut4_quantize",
            "cmpq_pack_with_error", "cmpq_time_kernel", "cmpq_act_stats_static", "cmpq_kmeans_launch_shape",
-           "cmpq_shader_clock_probe", "cmpq_lut_matvec_group_fp16acc", "cmpq_kmeans_build_shape")
+           "cmpq_shader_clock_probe", "cmpq_lut_matvec_group_fp16acc", "cmpq_kmeans_build_shape", "cmpq_rank_channels")
 
 _i64, _i32, _int, _vp, _dbl, _sz = (ctypes.c_int64, ctypes.c_int32, ctypes.c_int, ctypes.c_void_p,
                                     ctypes.c_double, ctypes.c_size_t)
@@ -92,6 +92,7 @@ def lib() -> ctypes.CDLL:
         L.cmpq_act_stats.argtypes = [_vp, _int, _i64, _i64, _i64, _vp, _vp, _int, _vp, _sz, _vp, _vp]
         L.cmpq_transpose.argtypes = [_vp, _int, _i64, _i64, _i64, _vp, _i64, _vp]
         L.cmpq_allocate_bits.argtypes = [_vp, _i64, _vp, _i64, _vp, _int, _dbl, _vp, _vp, _vp, _sz, _vp]
+        L.cmpq_rank_channels.argtypes = [_vp, _i64, _i64, _vp, _int, _dbl, _vp, _vp, _vp, _vp, _vp]
         L.cmpq_extract_outliers.argtypes = [_int, _int, _int, _vp, _vp, _int, _i64, _i64, _i64, _vp, _vp,
                                             _vp, _i64, _vp, _vp, _vp, _vp, _sz, _vp]
         L.cmpq_kmeans_quantize.argtypes = [_vp, _int, _i64, _i64, _i64, _vp, _vp, _i64, _vp, _int,
@@ -260,6 +261,17 @@ def allocate_bits(sumsq: torch.Tensor, chan_mask: Optional[torch.Tensor], n_prot
                                     float(avg_bits), _ptr(bits), counts, _ptr(buf), buf.numel(), _stream()),
            "cmpq_allocate_bits")
     return [int(c) for c in counts]
+
+
+def rank_channels(sumsq: torch.Tensor, k_act: int, bit_set: Sequence[int], avg_bits: float, act_idx: torch.Tensor,
+                  chan_mask: torch.Tensor, bits: torch.Tensor):
+    """O_act (the `k_act` largest statistics), then the widths of the other channels; channels per width."""
+    bs = (_i32 * len(bit_set))(*bit_set)
+    counts = (_i64 * len(bit_set))()
+    _check(lib().cmpq_rank_channels(_ptr(sumsq), sumsq.numel(), int(k_act), bs, len(bit_set), float(avg_bits),
+                                    _ptr(act_idx), _ptr(chan_mask), _ptr(bits), counts, _stream()),
+           "cmpq_rank_channels")
+    return list(counts)
 
 
 def extract_channel_outliers(sumsq: torch.Tensor, k: int, idx_out: torch.Tensor,

@@ -320,6 +320,120 @@ __global__ __launch_bounds__(kRankThreads) void allocate_bits_reg_kernel(
     store_bytes<PER>(bits, w, d_in);
 }
 
+// Both rankings in one launch (d_in <= 8192).  O_act, the channels of the wider width and those of the middle
+// one are the first k[0], k[1] and k[2] channels of one order (larger key first, equal keys by index), so
+// the three threshold keys come out of the same three digit passes: one histogram for the first digit, one for
+// each rank after that.  A pass is a chain of barriers, so what counts is their number: 5120 channels, 1.6 us a
+// digit; as two launches of three and three passes 6.2 + 7.0 us, 13.4 with the gap, now 7.9.
+struct MultiShared {
+    uint32_t hist[3][2048];
+    uint32_t scan[34];
+    uint32_t prefix[3], rem[3];
+};
+
+// RANKS = 2: every channel that is not of the wider width is of the middle one.
+template <int PER, int RANKS>
+__global__ __launch_bounds__(kRankThreads) void rank_channels_kernel(const float *__restrict__ sumsq, int d_in, uint3 k,
+                                                                     int w_hi, int w_mid, int w_lo, int32_t *__restrict__ idx_out,
+                                                                     uint8_t *__restrict__ mask_out, uint8_t *__restrict__ bits) {
+    __shared__ MultiShared sh;
+    RankKeys<PER> a;
+    a.load(sumsq, nullptr, d_in);
+    const uint32_t kk[3] = {k.x, k.y, k.z};
+    uint32_t T[RANKS], need[RANKS], have = 0;
+#pragma unroll
+    for (int h = 0; h < RANKS; ++h) T[h] = 0, need[h] = kk[h];
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+        const uint32_t digit_mask = pass == 2 ? 1023u : 2047u;
+        constexpr int kBinsPer = 2048 / kRankThreads;
+        const int hists = pass == 0 ? 1 : RANKS;
+#pragma unroll
+        for (int h = 0; h < hists; ++h)
+#pragma unroll
+            for (int q = 0; q < kBinsPer; ++q) sh.hist[h][threadIdx.x + q * kRankThreads] = 0;
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int h = 0; h < RANKS; ++h) sh.rem[h] = need[h], sh.prefix[h] = T[h];  // (a rank of 0 falls in no digit)
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            const uint32_t digit = (a.key[r] >> shift) & digit_mask;
+#pragma unroll
+            for (int h = 0; h < hists; ++h)
+                if (((a.live >> r) & 1u) && (a.key[r] & have) == T[h]) atomicAdd(&sh.hist[h][digit], 1u);
+        }
+        __syncthreads();
+        // thread t looks at the digits 2047 - 2 t and 2046 - 2 t, and owns the one a rank falls in.  Counts
+        // stay below 2^16: two ranks to a word of the scan.
+        const int top = 2047 - kBinsPer * (int)threadIdx.x;
+        uint32_t v[RANKS][kBinsPer], before[RANKS], sum[3] = {0, 0, 0};
+#pragma unroll
+        for (int h = 0; h < RANKS; ++h)
+#pragma unroll
+            for (int q = 0; q < kBinsPer; ++q) sum[h] += v[h][q] = h < hists ? sh.hist[h][top - q] : v[0][q];
+        if constexpr (RANKS == 2) {
+            uint32_t total;
+            const uint32_t both = block_scan_excl_u32(sum[0] | (sum[1] << 16), sh.scan, &total);
+            before[0] = both & 0xffffu, before[1] = both >> 16;
+        } else {
+            uint32_t both, total, total2;
+            block_scan_excl_2xu32(sum[0] | (sum[1] << 16), sum[2], sh.scan, both, before[2], total, total2);
+            before[0] = both & 0xffffu, before[1] = both >> 16;
+        }
+#pragma unroll
+        for (int h = 0; h < RANKS; ++h)
+#pragma unroll
+            for (int q = 0; q < kBinsPer; ++q) {
+                if (before[h] < need[h] && need[h] <= before[h] + v[h][q]) {
+                    sh.rem[h] = need[h] - before[h];
+                    sh.prefix[h] = T[h] | ((uint32_t)(top - q) << shift);
+                }
+                before[h] += v[h][q];
+            }
+        have |= digit_mask << shift;
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < RANKS; ++h) T[h] = sh.prefix[h], need[h] = sh.rem[h];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int h = 0; h < RANKS; ++h)
+        if (kk[h] == 0) T[h] = 0xffffffffu, need[h] = 0;  // nothing: no key exceeds the all-ones pattern
+    uint32_t gt = 0, eq[3] = {0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const uint32_t in = (a.live >> r) & 1u;
+        gt += in && a.key[r] > T[0];
+#pragma unroll
+        for (int h = 0; h < RANKS; ++h) eq[h] += in && a.key[r] == T[h];
+    }
+    uint32_t x, y, all_x, all_y;
+    block_scan_excl_2xu32(gt | (eq[0] << 16), eq[1] | (eq[2] << 16), sh.scan, x, y, all_x, all_y);
+    uint32_t ties[3] = {x >> 16, y & 0xffffu, y >> 16};
+    uint32_t pos = (x & 0xffffu) + min(ties[0], need[0]);
+    __align__(8) uint8_t taken[PER], w[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const bool in = (a.live >> r) & 1u;
+        bool first[RANKS];  // among the first kk[h] channels: equal keys are taken in index order until `need` are in
+#pragma unroll
+        for (int h = 0; h < RANKS; ++h) {
+            const bool tie = in && a.key[r] == T[h];
+            first[h] = (in && a.key[r] > T[h]) || (tie && ties[h] < need[h]);
+            ties[h] += tie;
+        }
+        if (first[0] && idx_out) idx_out[pos] = (int)threadIdx.x * PER + r;
+        pos += first[0];
+        taken[r] = first[0];
+        w[r] = (uint8_t)(first[0] ? CMPQ_PROTECTED : (first[1] ? w_hi : (RANKS < 3 || first[RANKS - 1] ? w_mid : w_lo)));
+    }
+    if (mask_out) store_bytes<PER>(mask_out, taken, d_in);
+    store_bytes<PER>(bits, w, d_in);
+}
+
 // ------------------------------------------------------------------ whole layer, d_in*d_out keys
 //
 // Top-k of the scores of a whole layer, written in ascending linear index.  The data is
@@ -1937,16 +2051,16 @@ size_t cmpq_ws_outlier_weights(int64_t d_in, int64_t d_out, int64_t k) {
     return layer > channel ? layer : channel;
 }
 
-extern "C" int cmpq_allocate_bits(const float *sumsq, int64_t d_in, const uint8_t *chan_mask,
-                                  int64_t n_protected, const int32_t *bit_set, int n_set,
-                                  double avg_bits, uint8_t *bits, int64_t *counts_host, void *ws,
-                                  size_t ws_bytes, void *stream) {
-    (void)ws;
-    (void)ws_bytes;
-    if (!sumsq || !bits || !bit_set || d_in < 0 || n_protected < 0 || n_protected > d_in)
-        return CMPQ_EINVAL;
-    if (!chan_mask && n_protected != 0) return CMPQ_EINVAL;
-    if (d_in >= (int64_t)1 << 31) return CMPQ_ESHAPE;
+namespace {
+
+// Algorithm 1's integer budget: the k_hi channels with the largest statistic get w_hi, the next up to k_mid
+// w_mid, the rest w_lo (all_mid: every other one w_mid).
+struct Budget {
+    int64_t k_hi, k_mid;
+    int w_hi, w_mid, w_lo, all_mid;
+};
+int channel_budget(int64_t d_in, int64_t n_protected, const int32_t *bit_set, int n_set, double avg_bits,
+                   int64_t *counts_host, Budget &p) {
     if (n_set < 1 || n_set > 4) return CMPQ_EBUDGET;
     for (int j = 0; j < n_set; ++j) {
         if (bit_set[j] < 1 || bit_set[j] > 4) return CMPQ_EBUDGET;
@@ -1955,9 +2069,6 @@ extern "C" int cmpq_allocate_bits(const float *sumsq, int64_t d_in, const uint8_
     const int lo = bit_set[0], hi = bit_set[n_set - 1];
     if (!(avg_bits >= lo - 1e-9 && avg_bits <= hi + 1e-9)) return CMPQ_EBUDGET;
     const int64_t d_eff = d_in - n_protected;
-    // the integer budget
-    int64_t k_hi, k_mid;
-    int w_hi, w_mid, w_lo, all_mid;
     const double nearest = (double)(int64_t)(avg_bits + 0.5);
     const double gap = avg_bits - nearest;
     if ((gap < 0 ? -gap : gap) < 1e-9) {
@@ -1970,36 +2081,77 @@ extern "C" int cmpq_allocate_bits(const float *sumsq, int64_t d_in, const uint8_
             if (m < 0) m = 0;
             if (2 * m > d_eff) m = d_eff / 2;
         }
-        k_hi = m;
-        k_mid = d_eff - m;
-        w_hi = s + 1;
-        w_mid = s;
-        w_lo = s - 1;
-        all_mid = m == 0;
+        p = Budget{m, d_eff - m, s + 1, s, s - 1, m == 0};
     } else {
         const int s = (int)avg_bits;  // floor, avg_bits > 0
         const int64_t T = (int64_t)(avg_bits * (double)d_eff + 1e-9);
-        k_hi = T - (int64_t)s * d_eff;
-        k_mid = d_eff;
-        w_hi = s + 1;
-        w_mid = s;
-        w_lo = s;
-        all_mid = 1;
+        p = Budget{T - (int64_t)s * d_eff, d_eff, s + 1, s, s, 1};
     }
     if (counts_host) {
         for (int j = 0; j < n_set; ++j) counts_host[j] = 0;
-        if (k_hi > 0) counts_host[w_hi - lo] += k_hi;
-        if (k_mid - k_hi > 0) counts_host[w_mid - lo] += k_mid - k_hi;
-        if (d_eff - k_mid > 0) counts_host[w_lo - lo] += d_eff - k_mid;
+        if (p.k_hi > 0) counts_host[p.w_hi - lo] += p.k_hi;
+        if (p.k_mid - p.k_hi > 0) counts_host[p.w_mid - lo] += p.k_mid - p.k_hi;
+        if (d_eff - p.k_mid > 0) counts_host[p.w_lo - lo] += d_eff - p.k_mid;
     }
+    return CMPQ_OK;
+}
+
+void launch_top_channels(const float *sumsq, int64_t d_in, int64_t k, int32_t *idx_out, uint8_t *mask_out, hipStream_t s) {
+    if (d_in <= kRankPer * kRankThreads)
+        top_channels_reg_kernel<kRankPer><<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, (uint32_t)k, idx_out, mask_out);
+    else
+        top_channels_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, (uint32_t)k, idx_out, mask_out);
+}
+
+void launch_allocate_bits(const float *sumsq, int64_t d_in, const uint8_t *chan_mask, const Budget &p, uint8_t *bits, hipStream_t s) {
+    if (d_in <= kRankPer * kRankThreads)
+        allocate_bits_reg_kernel<kRankPer><<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, chan_mask, (uint32_t)p.k_hi,
+                                                                       (uint32_t)p.k_mid, p.all_mid, p.w_hi, p.w_mid, p.w_lo, bits);
+    else
+        allocate_bits_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, chan_mask, (uint32_t)p.k_hi, (uint32_t)p.k_mid, p.all_mid,
+                                                       p.w_hi, p.w_mid, p.w_lo, bits);
+}
+
+}  // namespace
+
+extern "C" int cmpq_allocate_bits(const float *sumsq, int64_t d_in, const uint8_t *chan_mask,
+                                  int64_t n_protected, const int32_t *bit_set, int n_set,
+                                  double avg_bits, uint8_t *bits, int64_t *counts_host, void *ws,
+                                  size_t ws_bytes, void *stream) {
+    (void)ws;
+    (void)ws_bytes;
+    if (!sumsq || !bits || !bit_set || d_in < 0 || n_protected < 0 || n_protected > d_in)
+        return CMPQ_EINVAL;
+    if (!chan_mask && n_protected != 0) return CMPQ_EINVAL;
+    if (d_in >= (int64_t)1 << 31) return CMPQ_ESHAPE;
+    Budget p;
+    const int rc = channel_budget(d_in, n_protected, bit_set, n_set, avg_bits, counts_host, p);
+    if (rc != CMPQ_OK) return rc;
+    if (d_in == 0) return CMPQ_OK;
+    launch_allocate_bits(sumsq, d_in, chan_mask, p, bits, static_cast<hipStream_t>(stream));
+    CMPQ_LAUNCH_CHECK();
+    return CMPQ_OK;
+}
+
+extern "C" int cmpq_rank_channels(const float *sumsq, int64_t d_in, int64_t k_act, const int32_t *bit_set, int n_set,
+                                  double avg_bits, int32_t *act_idx, uint8_t *chan_mask, uint8_t *bits,
+                                  int64_t *counts_host, void *stream) {
+    if (!sumsq || !bits || !bit_set || !chan_mask || d_in < 0 || k_act < 0 || (k_act > 0 && !act_idx)) return CMPQ_EINVAL;
+    if (d_in >= (int64_t)1 << 31) return CMPQ_ESHAPE;
+    if (k_act > d_in) return CMPQ_ECOUNT;
+    Budget p;
+    const int rc = channel_budget(d_in, k_act, bit_set, n_set, avg_bits, counts_host, p);
+    if (rc != CMPQ_OK) return rc;
     if (d_in == 0) return CMPQ_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (d_in <= kRankPer * kRankThreads)
-        allocate_bits_reg_kernel<kRankPer><<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, chan_mask, (uint32_t)k_hi,
-                                                                       (uint32_t)k_mid, all_mid, w_hi, w_mid, w_lo, bits);
-    else
-        allocate_bits_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, chan_mask, (uint32_t)k_hi, (uint32_t)k_mid, all_mid,
-                                                       w_hi, w_mid, w_lo, bits);
+    if (d_in <= kRankPer * kRankThreads) {
+        const uint3 k = make_uint3((uint32_t)k_act, (uint32_t)(k_act + p.k_hi), (uint32_t)(k_act + p.k_mid));
+        auto kern = p.all_mid ? rank_channels_kernel<kRankPer, 2> : rank_channels_kernel<kRankPer, 3>;
+        kern<<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, k, p.w_hi, p.w_mid, p.w_lo, act_idx, chan_mask, bits);
+    } else {
+        launch_top_channels(sumsq, d_in, k_act, act_idx, chan_mask, s);
+        launch_allocate_bits(sumsq, d_in, chan_mask, p, bits, s);
+    }
     CMPQ_LAUNCH_CHECK();
     return CMPQ_OK;
 }
@@ -2017,10 +2169,7 @@ extern "C" int cmpq_extract_outliers(int mode, int score, int scope, const float
         if (d_in >= (int64_t)1 << 31) return CMPQ_ESHAPE;
         if (k > d_in) return CMPQ_ECOUNT;
         if (d_in == 0) return CMPQ_OK;
-        if (d_in <= kRankPer * kRankThreads)
-            top_channels_reg_kernel<kRankPer><<<1, kRankThreads, 0, s>>>(sumsq, (int)d_in, (uint32_t)k, idx_out, chan_mask_out);
-        else
-            top_channels_kernel<<<1, kSelThreads, 0, s>>>(sumsq, d_in, (uint32_t)k, idx_out, chan_mask_out);
+        launch_top_channels(sumsq, d_in, k, idx_out, chan_mask_out, s);
         CMPQ_LAUNCH_CHECK();
         return CMPQ_OK;
     }

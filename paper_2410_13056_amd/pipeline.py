@@ -111,18 +111,16 @@ def _oriented(W: torch.Tensor, transposed: bool, timer):
     return Wt
 
 
-def _channels_and_widths(sumsq, d_in, bit_set, avg_bits, rho_act_ppm, ws, timer):
+def _channels_and_widths(sumsq, d_in, bit_set, avg_bits, rho_act_ppm, timer):
     """O_act (Sec. 3.2.2), then Algorithm 1 on W' = W - O_act.  Both depend on the statistic of
     the layer's input only, not on its weights."""
     dev = sumsq.device
     k_act = B.count_ppm(rho_act_ppm, d_in)
     act_idx = torch.empty(k_act, dtype=torch.int32, device=dev)
     chan_mask = torch.empty(d_in, dtype=torch.uint8, device=dev)
-    with _stage(timer, "outlier_channels"):
-        B.extract_channel_outliers(sumsq, k_act, act_idx, chan_mask, ws)
     bits = torch.empty(d_in, dtype=torch.uint8, device=dev)
-    with _stage(timer, "allocate_bits"):
-        counts = B.allocate_bits(sumsq, chan_mask, k_act, bit_set, avg_bits, bits, ws)
+    with _stage(timer, "rank_channels"):
+        counts = B.rank_channels(sumsq, k_act, bit_set, avg_bits, act_idx, chan_mask, bits)
     return act_idx, chan_mask, bits, counts
 
 
@@ -257,7 +255,7 @@ def quantize_layer(W: torch.Tensor, sumsq: torch.Tensor, bit_set: Sequence[int],
     Wt = _oriented(W, transposed, timer)
     d_in, d_out = Wt.shape
     if widths is None:
-        widths = _channels_and_widths(sumsq, d_in, bit_set, avg_bits, rho_act_ppm, ws, timer)
+        widths = _channels_and_widths(sumsq, d_in, bit_set, avg_bits, rho_act_ppm, timer)
     act_idx, chan_mask, bits, counts = widths
     # preliminary quantization W'_q.  Only its levels are needed further on: O_q ranks
     # |w - nearest level|, which is |W' - W'_q| (Sec. 3 eq. Q(x)), so where the kernel can leave
@@ -321,7 +319,7 @@ def quantize_layer_from_cache(cache: WidthCache, sumsq: torch.Tensor, avg_bits: 
     dev = cache.W_t.device
     d_in, d_out = cache.W_t.shape
     act_idx, chan_mask, bits, counts = _channels_and_widths(sumsq, d_in, cache.bit_set, avg_bits, rho_act_ppm,
-                                                            ws, timer)
+                                                            timer)
     cent1 = torch.empty((d_in, B.KMAX), dtype=torch.float32, device=dev)
     codes1 = torch.empty((d_in, d_out), dtype=torch.uint8, device=dev)
     with _stage(timer, "select_by_width"):
@@ -396,7 +394,7 @@ def quantize_layer_rtn(W: torch.Tensor, sumsq: torch.Tensor, bit_set: Sequence[i
     dev = W.device
     Wt = _oriented(W, transposed, timer)
     d_in, d_out = Wt.shape
-    act_idx, chan_mask, bits, counts = _channels_and_widths(sumsq, d_in, bit_set, avg_bits, rho_act_ppm, ws, timer)
+    act_idx, chan_mask, bits, counts = _channels_and_widths(sumsq, d_in, bit_set, avg_bits, rho_act_ppm, timer)
     n_groups = -(-d_out // group)
     codes = torch.empty((d_in, d_out), dtype=torch.uint8, device=dev)
     scale = torch.empty((d_in, n_groups), dtype=torch.float32, device=dev)
@@ -550,7 +548,7 @@ def quantize_block(weights: Dict[str, torch.Tensor], acts: Dict[str, torch.Tenso
             if x_key not in stats:
                 sumsq = activation_stats(acts[x_key], ws, status=status, timer=timer)[1]
                 stats[x_key] = (sumsq, _channels_and_widths(sumsq, sumsq.numel(), bit_set, avg_bits, rho_act_ppm,
-                                                            ws, timer))
+                                                            timer))
             sumsq, widths = stats[x_key]
             out[name] = quantize_layer(weights[name], sumsq, bit_set, avg_bits, rho_act_ppm,
                                        rho_q_ppm, iters, ws, with_error=with_error, status=status,
@@ -574,7 +572,7 @@ def quantize_block(weights: Dict[str, torch.Tensor], acts: Dict[str, torch.Tenso
             if x_key not in stats:
                 sumsq = activation_stats(acts[x_key], ws[j], status=status, timer=timer)[1]
                 # O_act and the widths follow from the statistic alone: once per input, not per layer
-                widths = _channels_and_widths(sumsq, sumsq.numel(), bit_set, avg_bits, rho_act_ppm, ws[j], timer)
+                widths = _channels_and_widths(sumsq, sumsq.numel(), bit_set, avg_bits, rho_act_ppm, timer)
                 ev = torch.cuda.Event()
                 ev.record()
                 stats[x_key] = (sumsq, widths, ev, j)
