@@ -463,10 +463,10 @@ __global__ __launch_bounds__(kRankThreads) void rank_channels_kernel(const float
 // exact chain 178; keys near the guess 73.)
 //
 // What bounds the chain beside the one pass over the data is its launches, 4.5 us each, and counters
-// that many workgroups add to.  Ten launches: one sample pass, two of the list and no scan of the
-// units' counts in a kernel of its own, where it were thirteen; 4096x4096 weights, k = 0.5 %, all
-// kernels but the pass over the data: 102 -> 64 us (sample 31 -> 11, list 25 -> 13, counts and
-// output 29 -> 15).
+// that many workgroups add to.  Nine launches: one sample pass, two of the list, the second of which is
+// the exact chain's first where that one runs, and no scan of the units' counts in a kernel of its own, where
+// it were thirteen; 4096x4096 weights, k = 0.5 %, all kernels but the pass over the data: 102 -> 56 us
+// (sample 31 -> 11, list 25 -> 15, counts and output 29 -> 12).
 
 constexpr int kWThreads = 256;
 constexpr int kWaves = kWThreads / CMPQ_WAVE;
@@ -760,10 +760,12 @@ __device__ __forceinline__ void for_each_raw_chunk(const WselArgs &a, int64_t q0
     int64_t i = uniform_i64(q0 / a.wc_per_channel);
     int c = __builtin_amdgcn_readfirstlane((int)(q0 % a.wc_per_channel));  // a channel has at most 2^31 / 512 wave-chunks
     const int wc_per_channel = (int)a.wc_per_channel, lane0 = lane * kWPerLane;
-    bool live = channel_live(a, i);
-    float cent = live && a.centroids ? a.centroids[i * CMPQ_KMAX + (lane & 15)] : 0.f;
-    Raw8<TW> cur = {}, nxt = {};
-    if (live) fetch8(a, i, c * kWaveChunk + lane0, cur);
+    // (all loads at once: a channel of O_act is fetched and then dropped)
+    const uint32_t bits = a.bits[i];
+    float cent = a.centroids ? a.centroids[i * CMPQ_KMAX + (lane & 15)] : 0.f;
+    Raw8<TW> cur, nxt = {};
+    fetch8(a, i, c * kWaveChunk + lane0, cur);
+    bool live = bits >= 1 && bits <= 4;
     for (int64_t q = q0; q < q1; ++q) {
         int64_t ni = i;
         int nc = c + 1;
@@ -999,16 +1001,21 @@ __device__ __forceinline__ SafeIntervals safe_intervals(float cent, int K, float
     // rank by counting, send to the lane of the rank
     const uint32_t cb = __float_as_uint(cent);
     const uint32_t key = valid ? cb ^ ((cb >> 31) ? 0xffffffffu : 0x80000000u) : 0xffffffffu;
-    uint32_t rank = 0;
-    for (int j = 0; j < K; ++j) {  // (lanes past K hold the largest key and keep their places)
-        const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
-        rank += (kj < key || (kj == key && j < k)) ? 1u : 0u;
+    uint32_t sf = valid ? first : 0x10000u, sl = valid ? last : 0u;
+    float sc = cent;
+    const uint32_t key_up = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x101, 0xF, 0xF, true);  // row_shl:1
+    if (__ballot(lane < 16 && k < K - 1 && key > key_up) != 0ull) {  // (levels that ascend are in place: the usual case)
+        uint32_t rank = 0;
+        for (int j = 0; j < K; ++j) {  // (lanes past K hold the largest key and keep their places)
+            const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+            rank += (kj < key || (kj == key && j < k)) ? 1u : 0u;
+        }
+        if (k >= K) rank = (uint32_t)k;
+        const int to = (lane < 16 ? (int)rank : lane) << 2;  // a permutation of the lanes
+        sf = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)sf);
+        sl = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)sl);
+        sc = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(cent)));
     }
-    if (k >= K) rank = (uint32_t)k;
-    const int to = (lane < 16 ? (int)rank : lane) << 2;  // a permutation of the lanes
-    const uint32_t sf = (uint32_t)__builtin_amdgcn_ds_permute(to, valid ? (int)first : 0x10000);
-    const uint32_t sl = (uint32_t)__builtin_amdgcn_ds_permute(to, valid ? (int)last : 0);
-    const float sc = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(cent)));
     const bool svalid = lane < 16 && sf <= 0xffffu;
     // running largest last position; a run starts a new interval when an FP16 value lies between
     uint32_t run_max = svalid ? sl : 0u;
@@ -1265,15 +1272,15 @@ __device__ __forceinline__ void list_key(const uint32_t *__restrict__ hist, uint
     T = first_key + ((8 * bin + (uint32_t)pick_of_8(hist + kHistList2Fine + 8 * bin, (uint32_t)rem8, need)) << shift);
 }
 
-// Calls body(key) for the listed entries of this workgroup's share of the units.
+// Calls body(key) for the listed entries of this workgroup's share of the units, one of `blocks`.
 template <typename F>
-__device__ __forceinline__ void for_each_listed(const WselArgs &a, int nunits, F &&body) {
+__device__ __forceinline__ void for_each_listed(const WselArgs &a, int nunits, int blocks, F &&body) {
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
     // 8 lanes per unit: units hold a few entries to a few hundred
     constexpr int kShare = 8;
     const int sub = lane & (kShare - 1);
     for (int64_t unit = ((int64_t)blockIdx.x * kWaves + wave) * (CMPQ_WAVE / kShare) + lane / kShare; unit < nunits;
-         unit += (int64_t)gridDim.x * (kWThreads / kShare)) {
+         unit += (int64_t)blocks * (kWThreads / kShare)) {
         const unsigned long long *ik = a.stage_ik + unit * a.cap;
         const uint32_t n = a.stage_cnt[unit];
 #pragma unroll 4
@@ -1438,12 +1445,12 @@ template <typename TW, bool NEAR>
 __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_num_sgpr(80))) void wsel_stage_kernel(WselArgs a, WselState *st,
                                                                 const uint32_t *__restrict__ hist) {
     __shared__ PickShared ps;
-    const uint32_t reach = sample_guess(hist, a.sample_rank, ps);
-    if (blockIdx.x == 0 && threadIdx.x == 0) st->reach = reach;
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
     const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
     const int64_t q0 = unit * a.wc_per_unit;
     const int64_t q1 = min(a.total_wc, q0 + a.wc_per_unit);
+    const uint32_t reach = sample_guess(hist, a.sample_rank, ps);
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->reach = reach;
     uint32_t n_staged = 0;
     bool over = false;
     unsigned long long *stage_ik = a.stage_ik + unit * a.cap;
@@ -1497,12 +1504,88 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_num_sgpr(80))) voi
     }
 }
 
+// Exact chain, a pass over the data.  PASS 0: digit = key >> 21 (11 bits), PASS 1: (key >> 10) & 2047, PASS 2:
+// key & 1023.  The last pass also stages the entries whose top 22 bits reach the prefix and leaves,
+// per workgroup, how many of its keys lie above the 22-bit prefix and its own histogram
+// of the last digit (what the full path needs to place its output without counting again).
+// Usually there is none, so it is launched with few workgroups, each of which takes the shares
+// blk = blockIdx.x, + gridDim.x, ... of the nblocks in turn.  `lh` holds kCopies * kBins counters.
+template <int PASS>
+constexpr int kCopies = PASS == 0 ? 4 : 1;  // the first digit is the same for most keys: copies, chosen by lane
+template <typename TW, int PASS>
+__device__ __forceinline__ void exact_pass(const WselArgs &a, WselState *st, uint64_t k, int nblocks, uint32_t *__restrict__ hist,
+                                           uint32_t *__restrict__ above, uint32_t *__restrict__ local_last, uint32_t *lh,
+                                           uint32_t *red, PickShared &ps) {
+    uint32_t prefix = 0;
+    {
+        uint64_t rem;
+        bool all;
+        exact_prefix(hist, k, PASS, ps, prefix, rem, all);  // the digits the passes before this one fixed
+    }
+    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
+    for (int blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        __syncthreads();  // the counters of the share before are no longer read
+        for (int b = threadIdx.x; b < kCopies<PASS> * kBins; b += kWThreads) lh[b] = 0;
+        __syncthreads();
+        uint32_t *lh0 = lh + (lane & (kCopies<PASS> - 1)) * kBins;
+        const int64_t unit = (int64_t)blk * kWaves + wave;
+        const int64_t q0 = unit * a.wc_per_unit;
+        const int64_t q1 = min(a.total_wc, q0 + a.wc_per_unit);
+        uint32_t n_above = 0, n_staged = 0;
+        bool over = false;
+        unsigned long long *stage_ik = a.stage_ik + unit * a.cap;
+        uint16_t *stage_val = a.stage_val + unit * a.cap;
+        for_each_wave_chunk<TW>(a, q0, q1, [&](int64_t i, int o0, const uint32_t (&key)[8], const float (&wv)[8], uint32_t valid) {
+            uint32_t cand = 0;  // bit j: entry j reaches the 22-bit prefix
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (!((valid >> j) & 1u)) continue;
+                if (PASS == 0) {
+                    atomicAdd(&lh0[key[j] >> 21], 1u);
+                } else if (PASS == 1) {
+                    if ((key[j] >> 21) == (prefix >> 21)) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
+                } else {
+                    if ((key[j] >> 10) == (prefix >> 10)) atomicAdd(&lh[key[j] & 1023u], 1u);
+                    n_above += (key[j] >> 10) > (prefix >> 10);
+                    cand |= (uint32_t)((key[j] >> 10) >= (prefix >> 10)) << j;
+                }
+            }
+            if (PASS == 2) stage_chunk(cand, i, o0, a.d_out, key, wv, stage_ik, stage_val, a.cap, n_staged, over);
+        });
+        __syncthreads();
+        for (int b = threadIdx.x; b < kBins; b += kWThreads) {
+            uint32_t n = lh[b];
+#pragma unroll
+            for (int r = 1; r < kCopies<PASS>; ++r) n += lh[r * kBins + b];
+            if (n) atomicAdd(&hist[PASS * kBins + b], n);
+        }
+        if (PASS == 2) {
+            if (lane == 0) {
+                a.stage_cnt[unit] = over ? 0u : n_staged;
+                if (over) st->overflow = 1u;
+            }
+            for (int b = threadIdx.x; b < 1024; b += kWThreads) local_last[(int64_t)blk * 1024 + b] = lh[b];
+            n_above = wave_sum_u32(n_above);
+            if (lane == 0) red[wave] = n_above;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                uint32_t t = 0;
+                for (int w = 0; w < kWaves; ++w) t += red[w];
+                above[blk] = t;
+            }
+        }
+    }
+}
+
 // Fast chain, passes over the list: its first two histograms.  The second pass also settles whether
 // the list holds the answer at all: it does unless it overflowed or is shorter than k.
-template <int PASS>
-__global__ __launch_bounds__(kWThreads) void wsel_list_kernel(WselArgs a, WselState *st, int nunits,
+// Where it does not, the second pass is the exact chain's first instead: in a kernel of its own that one was
+// a launch of 4 us that nearly always returned at once.  The first list_blocks workgroups go over the list.
+template <typename TW, int PASS>
+__global__ __launch_bounds__(kWThreads) void wsel_list_kernel(WselArgs a, WselState *st, int nunits, int list_blocks,
                                                                uint32_t *__restrict__ hist, uint64_t k) {
     constexpr int kWords = PASS == 0 ? kBins : kListFine;
+    static_assert(PASS == 0 || kCopies<0> * kBins == kListFine, "both passes' counters fit");
     __shared__ uint32_t lh[kWords];
     __shared__ PickShared ps;
     for (int b = threadIdx.x; b < kWords; b += kWThreads) lh[b] = 0;
@@ -1518,12 +1601,16 @@ __global__ __launch_bounds__(kWThreads) void wsel_list_kernel(WselArgs a, WselSt
             st->list_shift = shift;
             st->rem = rem;
         }
-        if (failed) return;
+        if (failed) {
+            exact_pass<TW, 0>(a, st, k, nunits / kWaves, hist, nullptr, nullptr, lh, nullptr, ps);
+            return;
+        }
+        if ((int)blockIdx.x >= list_blocks) return;
     } else if (overflowed) {
         return;
     }
     __syncthreads();
-    for_each_listed(a, nunits, [&](uint32_t key) {
+    for_each_listed(a, nunits, list_blocks, [&](uint32_t key) {
         if (PASS == 0) {
             atomicAdd(&lh[list_bin_of(key, reach)], 1u);
         } else {
@@ -1565,99 +1652,33 @@ __global__ void wsel_init_kernel(WselState *st, uint32_t *hist) {
     }
 }
 
-// PASS 0: digit = key >> 21 (11 bits), PASS 1: (key >> 10) & 2047, PASS 2: key & 1023.
-// The last pass also stages the entries whose top 22 bits reach the prefix and leaves,
-// per workgroup, how many of its keys lie above the 22-bit prefix and its own histogram
-// of the last digit (what the full path needs to place its output without counting again).
-// Usually it returns at once, so it is launched with few workgroups, each of which takes the shares
-// blk = blockIdx.x, + gridDim.x, ... of the nblocks in turn.  Where the fast chain found the k-th key
-// in a coarse bin, PASS 0 counts the list's last 8 bits instead.
+// The exact chain's second and third pass, where the fast chain does not hold the answer.  Where it found the
+// k-th key in a coarse bin, PASS 1 counts the list's last 8 bits instead.
 template <typename TW, int PASS>
 __global__ __launch_bounds__(kWThreads) void wsel_hist_kernel(WselArgs a, WselState *st, uint64_t k, int nblocks,
                                                                uint32_t *__restrict__ hist,
                                                                uint32_t *__restrict__ above,
                                                                uint32_t *__restrict__ local_last) {
-    // the first digit is the same for most keys: its histogram is kept in 4 copies, chosen
-    // by lane, so that fewer lanes collide on one counter
-    constexpr int kCopies = PASS == 0 ? 4 : 1;
-    __shared__ uint32_t lh[kCopies * kBins];
+    __shared__ uint32_t lh[kCopies<PASS> * kBins];
     __shared__ uint32_t red[kWaves];
     __shared__ PickShared ps;
     if (!st->fast_failed) {  // the fast chain settles the answer
         const uint32_t shift = st->list_shift;
-        if (PASS != 0 || shift == 0) return;
+        if (PASS != 1 || shift == 0) return;
         uint32_t first;
         uint64_t rem;
         list_key(hist, st->first_key, shift, st->rem, ps, first, rem);
         static_assert(1 << kListFarShift == kWThreads, "a bin per thread");
         lh[threadIdx.x] = 0;
         __syncthreads();
-        for_each_listed(a, nblocks * kWaves, [&](uint32_t key) {
+        for_each_listed(a, nblocks * kWaves, (int)gridDim.x, [&](uint32_t key) {
             if (key - first < 1u << kListFarShift) atomicAdd(&lh[key - first], 1u);
         });
         __syncthreads();
         if (lh[threadIdx.x]) atomicAdd(&hist[kHistList3 + threadIdx.x], lh[threadIdx.x]);
         return;
     }
-    uint32_t prefix = 0;
-    {
-        uint64_t rem;
-        bool all;
-        exact_prefix(hist, k, PASS, ps, prefix, rem, all);  // the digits the passes before this one fixed
-    }
-    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    for (int blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        __syncthreads();  // the counters of the share before are no longer read
-        for (int b = threadIdx.x; b < kCopies * kBins; b += kWThreads) lh[b] = 0;
-        __syncthreads();
-        uint32_t *lh0 = lh + (lane & (kCopies - 1)) * kBins;
-        const int64_t unit = (int64_t)blk * kWaves + wave;
-        const int64_t q0 = unit * a.wc_per_unit;
-        const int64_t q1 = min(a.total_wc, q0 + a.wc_per_unit);
-        uint32_t n_above = 0, n_staged = 0;
-        bool over = false;
-        unsigned long long *stage_ik = a.stage_ik + unit * a.cap;
-        uint16_t *stage_val = a.stage_val + unit * a.cap;
-        for_each_wave_chunk<TW>(a, q0, q1, [&](int64_t i, int o0, const uint32_t (&key)[8], const float (&wv)[8], uint32_t valid) {
-            uint32_t cand = 0;  // bit j: entry j reaches the 22-bit prefix
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (!((valid >> j) & 1u)) continue;
-                if (PASS == 0) {
-                    atomicAdd(&lh0[key[j] >> 21], 1u);
-                } else if (PASS == 1) {
-                    if ((key[j] >> 21) == (prefix >> 21)) atomicAdd(&lh[(key[j] >> 10) & 2047u], 1u);
-                } else {
-                    if ((key[j] >> 10) == (prefix >> 10)) atomicAdd(&lh[key[j] & 1023u], 1u);
-                    n_above += (key[j] >> 10) > (prefix >> 10);
-                    cand |= (uint32_t)((key[j] >> 10) >= (prefix >> 10)) << j;
-                }
-            }
-            if (PASS == 2) stage_chunk(cand, i, o0, a.d_out, key, wv, stage_ik, stage_val, a.cap, n_staged, over);
-        });
-        __syncthreads();
-        for (int b = threadIdx.x; b < kBins; b += kWThreads) {
-            uint32_t n = lh[b];
-#pragma unroll
-            for (int r = 1; r < kCopies; ++r) n += lh[r * kBins + b];
-            if (n) atomicAdd(&hist[PASS * kBins + b], n);
-        }
-        if (PASS == 2) {
-            if (lane == 0) {
-                a.stage_cnt[unit] = over ? 0u : n_staged;
-                if (over) st->overflow = 1u;
-            }
-            for (int b = threadIdx.x; b < 1024; b += kWThreads) local_last[(int64_t)blk * 1024 + b] = lh[b];
-            n_above = wave_sum_u32(n_above);
-            if (lane == 0) red[wave] = n_above;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                uint32_t t = 0;
-                for (int w = 0; w < kWaves; ++w) t += red[w];
-                above[blk] = t;
-            }
-        }
-    }
+    exact_pass<TW, PASS>(a, st, k, nblocks, hist, above, local_last, lh, red, ps);
 }
 
 // Keys above the threshold and keys equal to it, per workgroup (4 units) and, from the staging list,
@@ -1673,6 +1694,10 @@ __global__ __launch_bounds__(kWThreads) void wsel_count_kernel(WselState *st, Ws
     __shared__ uint2 red[kWaves];
     __shared__ PickShared ps;
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
+    // the unit's first entries, on their way while the threshold is worked out (`cap` is 256 or more)
+    const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
+    const unsigned long long *ik = a.stage_ik + unit * a.cap;
+    const uint32_t n = a.stage_cnt[unit], first = (uint32_t)ik[lane];
     const bool exact = st->fast_failed != 0;
     uint32_t T;
     uint64_t need;
@@ -1696,11 +1721,8 @@ __global__ __launch_bounds__(kWThreads) void wsel_count_kernel(WselState *st, Ws
     }
     uint32_t gt = 0, eq = 0;
     if (!exact || !st->overflow) {
-        const int64_t unit = (int64_t)blockIdx.x * kWaves + wave;
-        const unsigned long long *ik = a.stage_ik + unit * a.cap;
-        const uint32_t n = a.stage_cnt[unit];
         for (uint32_t e = lane; e < n; e += CMPQ_WAVE) {
-            const uint32_t key = (uint32_t)ik[e];
+            const uint32_t key = e < CMPQ_WAVE ? first : (uint32_t)ik[e];
             gt += key > T;
             eq += key == T;
         }
@@ -1773,27 +1795,41 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
 
 // Writes the answer from the staging list: a wavefront per unit, 64 staged entries a step.  `ties`
 // and `outp`: the equal keys and the taken entries before the workgroup's units.
-__device__ __forceinline__ void emit_from_list(const WselArgs &a, uint32_t T, uint64_t need,
-                                               const uint2 *__restrict__ cnt_unit, uint32_t gt_before,
+struct UnitList {  // what is on its way while the counts before the unit are added up
+    const unsigned long long *ik;
+    const uint16_t *sv;
+    uint32_t n;
+    unsigned long long ik0;
+    uint16_t sv0;
+    uint2 cnt[kWaves - 1];  // of the workgroup's units
+    __device__ __forceinline__ void fetch(const WselArgs &a, const uint2 *__restrict__ cnt_unit) {
+        const int lane = threadIdx.x & (CMPQ_WAVE - 1);
+        const int64_t unit0 = (int64_t)blockIdx.x * kWaves, unit = unit0 + wave_index();
+        ik = a.stage_ik + unit * a.cap;
+        sv = a.stage_val + unit * a.cap;
+        n = a.stage_cnt[unit];
+        ik0 = ik[lane], sv0 = sv[lane];  // (`cap` is 256 or more)
+#pragma unroll
+        for (int w = 0; w < kWaves - 1; ++w) cnt[w] = cnt_unit[unit0 + w];
+    }
+};
+__device__ __forceinline__ void emit_from_list(const UnitList &l, uint32_t T, uint64_t need, uint32_t gt_before,
                                                uint32_t eq_before, int64_t k,
                                                int32_t *__restrict__ idx_out, uint16_t *__restrict__ val_out) {
     const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
-    const int64_t unit0 = (int64_t)blockIdx.x * kWaves, unit = unit0 + wave;
+#pragma unroll
     for (int w = 0; w < kWaves - 1; ++w) {
-        const uint2 c = cnt_unit[unit0 + w];
         if (w < wave) {
-            gt_before += c.x;
-            eq_before += c.y;
+            gt_before += l.cnt[w].x;
+            eq_before += l.cnt[w].y;
         }
     }
-    const unsigned long long *ik = a.stage_ik + unit * a.cap;
-    const uint16_t *sv = a.stage_val + unit * a.cap;
-    const uint32_t n = a.stage_cnt[unit];
+    const uint32_t n = l.n;
     // equal keys are taken in index order until `need` are in
     uint64_t ties = eq_before, outp = gt_before + (ties < need ? ties : need);
     for (uint32_t e0 = 0; e0 < n; e0 += CMPQ_WAVE) {
         const uint32_t e = e0 + lane;
-        const unsigned long long v = e < n ? ik[e] : 0ull;
+        const unsigned long long v = e0 == 0 ? l.ik0 : (e < n ? l.ik[e] : 0ull);
         const uint32_t key = (uint32_t)v;
         const bool is_eq = e < n && key == T, is_gt = e < n && key > T;
         const unsigned long long eq_mask = __ballot(is_eq);
@@ -1802,7 +1838,7 @@ __device__ __forceinline__ void emit_from_list(const WselArgs &a, uint32_t T, ui
         const uint64_t pos = outp + lanes_below(sel_mask);
         if (sel && (int64_t)pos < k) {
             idx_out[pos] = (int32_t)(v >> 32);
-            if (val_out) val_out[pos] = sv[e];
+            if (val_out) val_out[pos] = e0 == 0 ? l.sv0 : l.sv[e];
         }
         ties += __popcll(eq_mask);
         outp += __popcll(sel_mask);
@@ -1884,13 +1920,15 @@ __global__ __launch_bounds__(kWThreads) void wsel_emit_kernel(WselArgs a, const 
     __shared__ uint32_t red[kWaves][4];
     const uint32_t T = st->T;
     const uint64_t need = st->need;
+    UnitList list;
+    list.fetch(a, cnt_unit);
     const Before c = counts_before(cnt_block, red);
     if (st->fast_failed && st->overflow) {
         const int64_t q0 = (int64_t)blockIdx.x * kWaves * a.wc_per_unit;
         const int64_t q1 = min(a.total_wc, q0 + kWaves * a.wc_per_unit);
         write_chunks<TW>(a, T, need, c.eq, c.gt + (c.eq < need ? (uint64_t)c.eq : need), q0, q1, k, idx_out, val_out, scan);
     } else {
-        emit_from_list(a, T, need, cnt_unit, c.gt, c.eq, k, idx_out, val_out);
+        emit_from_list(list, T, need, c.gt, c.eq, k, idx_out, val_out);
     }
     const uint64_t found = c.all_gt + (c.all_eq < need ? (uint64_t)c.all_eq : need);
     for (int64_t j = (int64_t)found + (int64_t)blockIdx.x * kWThreads + threadIdx.x; j < k; j += (int64_t)gridDim.x * kWThreads)
@@ -2020,16 +2058,16 @@ int launch_weight_select(WselArgs a, const WselPlan &p, int64_t k, int32_t *idx_
         wsel_stage_kernel<TW, false><<<p.nblocks, kWThreads, 0, s>>>(a, w.st, w.hist);
     cmpq_timing_after(CMPQ_KERNEL_OUTLIER_STAGE, s);
     const int list_blocks = (int)cdiv(p.nunits, 32) < 256 ? (int)cdiv(p.nunits, 32) : 256;  // a unit per 8 lanes
-    wsel_list_kernel<0><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
-    wsel_list_kernel<1><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, w.hist, (uint64_t)k);
-    // exact chain: these return at once unless the fast chain raised its flag
+    // exact chain: its passes return at once, or are not there, unless the fast chain raised its flag
     // (Workgroups that return at once still cost: three launches of 1024 0.1 us, of 1536 0.5 us more than
     // of 512.  Where they do work they hide its latency: channels of different scale, 8192x28672
     // weights, 512 workgroups 1300 us for the call, 1024 1067, 1536 988, 2048 999; 4096x4096 186, 168,
     // 163, 167.)
     const int most_blocks = p.wc_per_unit >= 16 ? 1536 : 1024;
     const int hist_blocks = p.nblocks < most_blocks ? p.nblocks : most_blocks;
-    wsel_hist_kernel<TW, 0><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
+    const int second_blocks = hist_blocks < 1024 ? (hist_blocks > list_blocks ? hist_blocks : list_blocks) : 1024;
+    wsel_list_kernel<TW, 0><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, list_blocks, w.hist, (uint64_t)k);
+    wsel_list_kernel<TW, 1><<<second_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, list_blocks, w.hist, (uint64_t)k);
     wsel_hist_kernel<TW, 1><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     wsel_hist_kernel<TW, 2><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     // threshold, placement and output, from whichever chain holds the answer
