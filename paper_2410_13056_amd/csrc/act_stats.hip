@@ -126,7 +126,18 @@ __global__ __launch_bounds__(kThreads) void act_stats_any_kernel(const T *__rest
     const int64_t r_begin = (int64_t)blockIdx.y * rows_per_split;
     const int64_t r_end = min(n, r_begin + rows_per_split);
     double s = 0.0;
-    for (int64_t r = r_begin; r < r_end; ++r) s = fold<NORM>(s, load_as_f32<T>(X, r * ldx + col));
+    // 16 rows on their way at a time, added in row order all the same (3001 columns, 1031 rows: 16.6 us
+    // one after the other, 6.8 so)
+    constexpr int U = 16;
+    int64_t r = r_begin;
+    for (; r + U <= r_end; r += U) {
+        T x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = X[(r + u) * ldx + col];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s = fold<NORM>(s, load_as_f32<T>(x, u));
+    }
+    for (; r < r_end; ++r) s = fold<NORM>(s, load_as_f32<T>(X, r * ldx + col));
     partial[(int64_t)blockIdx.y * d_in + col] = s;
 }
 
