@@ -571,6 +571,19 @@ def select_by_width(bits: torch.Tensor, bit_set: Sequence[int], centroids_by_wid
            "cmpq_select_by_width")
 
 
+def select_levels_by_width(bits: torch.Tensor, bit_set: Sequence[int], centroids_by_width: Sequence[torch.Tensor],
+                           codes_by_width: Sequence[torch.Tensor], centroids: torch.Tensor) -> None:
+    """`select_by_width` without the codes (rows of no length)."""
+    d_in, n = bits.numel(), len(bit_set)
+    for c in (*centroids_by_width, centroids):
+        if tuple(c.shape) != (d_in, KMAX) or not c.is_contiguous() or c.dtype != torch.float32:
+            raise ValueError("levels must be contiguous [d_in,16] fp32")
+    _check(lib().cmpq_select_by_width(_ptr(bits), d_in, 0, (_i32 * n)(*bit_set), n,
+                                      (_vp * n)(*[_ptr(t) for t in centroids_by_width]),
+                                      (_vp * n)(*[_ptr(t) for t in codes_by_width]), _ptr(centroids), None, _stream()),
+           "cmpq_select_by_width")
+
+
 def lut4_quantize(centroids: torch.Tensor, bits: torch.Tensor, codes4: torch.Tensor, table: torch.Tensor,
                   centroids_q: torch.Tensor, ws: Workspace, mode: int = LUT4_CODEBOOK, iters: int = 20) -> None:
     """Sec. 5.1 / Tab. 7: the tables of a layer in 4 bits - codes into one 16-level table per layer

@@ -305,6 +305,12 @@ def build_width_cache(W: torch.Tensor, bit_set: Sequence[int], iters: int = 20,
     return WidthCache(tuple(bit_set), iters, Wt, cents, codes)
 
 
+# From this many weights on a layer takes only its levels from the kept runs: O_q ranks the distance to the nearest
+# level itself (the same score), which costs its pass a start of some 20 us and saves copying the codes and reading
+# them back.  Copy and pass, us: 13824 x 5120 26 + 47 with codes, 5 + 59 without; 4096 x 4096 9 + 17 and 4 + 29.
+LEVELS_ONLY = 1 << 25
+
+
 def quantize_layer_from_cache(cache: WidthCache, sumsq: torch.Tensor, avg_bits: float,
                               rho_act_ppm: int = 4500, rho_q_ppm: int = 500,
                               ws: Optional[B.Workspace] = None, score: int = B.SCORE_RESIDUAL,
@@ -321,9 +327,13 @@ def quantize_layer_from_cache(cache: WidthCache, sumsq: torch.Tensor, avg_bits: 
     act_idx, chan_mask, bits, counts = _channels_and_widths(sumsq, d_in, cache.bit_set, avg_bits, rho_act_ppm,
                                                             timer)
     cent1 = torch.empty((d_in, B.KMAX), dtype=torch.float32, device=dev)
-    codes1 = torch.empty((d_in, d_out), dtype=torch.uint8, device=dev)
+    codes1 = None
     with _stage(timer, "select_by_width"):
-        B.select_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1, codes1)
+        if keep_prelim or d_in * d_out < LEVELS_ONLY or not _histogram_kernel_takes(cache.W_t):
+            codes1 = torch.empty((d_in, d_out), dtype=torch.uint8, device=dev)
+            B.select_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1, codes1)
+        else:
+            B.select_levels_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1)
     return _after_first_pass(cache.W_t, sumsq, cache.bit_set, counts, act_idx, chan_mask, bits, cent1, codes1,
                              rho_q_ppm, cache.iters, ws, score, with_error, keep_prelim, status, timer,
                              iters_final_from_prelim, False, fused)
