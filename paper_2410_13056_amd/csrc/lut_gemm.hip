@@ -576,7 +576,7 @@ __global__ __launch_bounds__(kThreads, MT == 1 ? 3 : 2) void lut_tokens_kernel(G
 
 // Slabs and entries of O_q: 16 outputs x NT tokens per workgroup.  16 lanes per column take its
 // entries l, l + 16, ... with all NT tokens of the entry's channel at once; per output and token the
-// slabs are added in eights, each in pairs, then the 16 lanes' sums in lane order.
+// slabs are added in 64 bits, then the 16 lanes' sums in lane order.
 constexpr int kFinCols = 16;
 template <int NT, bool DIRECT>
 __global__ __launch_bounds__(kThreads) void tokens_finish_kernel(Group g) {
@@ -650,13 +650,19 @@ __global__ __launch_bounds__(kThreads) void tokens_finish_kernel(Group g) {
         __syncthreads();
     }
     if (!mine) return;
-    auto pairwise = [&] { return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])); };
+    // (in 64 bits: what the longer runs of width 2 lose this gains back.  Widened no earlier than here, or the
+    // entries of O_q would wait for the slabs)
+    auto sum = [&] {
+#pragma unroll
+        for (int q = 0; q < kInFlight; ++q) asm volatile("" : "+v"(v[q]));
+        return (((double)v[0] + v[1]) + ((double)v[2] + v[3])) + (((double)v[4] + v[5]) + ((double)v[6] + v[7]));
+    };
     static_assert(kInFlight == 8, "");
-    float y = pairwise();
+    double y = sum();
     for (int s = kInFlight; s < slabs; s += kInFlight) {
 #pragma unroll
         for (int q = 0; q < kInFlight; ++q) v[q] = s + q < slabs ? p[(int64_t)(s + q) * m * d_out] : 0.f;
-        y += pairwise();
+        y += sum();
     }
     if (colptr) {
         float z = 0.f;
@@ -664,7 +670,7 @@ __global__ __launch_bounds__(kThreads) void tokens_finish_kernel(Group g) {
         for (int u = 0; u < 16; ++u) z += sp[lo * kCol + u * kLane + hi];
         y += z;
     }
-    L.Y[(int64_t)token * L.ldy + o] = y;
+    L.Y[(int64_t)token * L.ldy + o] = (float)y;
 }
 
 // ---- many tokens: decode once, then multiply
@@ -882,7 +888,8 @@ int64_t part_steps(int bits, int64_t cost) {
     return n < kMaxRun ? n : kMaxRun;
 }
 void choose_slabs(Layer &L, int64_t m) {
-    const int64_t want = kWaves * wanted_slabs(L.d_out, m);
+    // (where there are few tiles, widths with few rows get their parts on top)
+    const int64_t slabs = wanted_slabs(L.d_out, m), want = kWaves * (slabs + (slabs == kMaxSlabs && L.n_seg > 1 ? L.n_seg - 1 : 0));
     int64_t cost = kLeastCost, parts = 0;
     for (;; ++cost) {
         parts = 0;
@@ -900,7 +907,7 @@ void choose_slabs(Layer &L, int64_t m) {
 
 // At least what choose_slabs gives for any widths.
 int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
-    const int64_t n = wanted_slabs(d_out, m), least = cdiv(cdiv(max_steps(d_in), (int64_t)kMaxRun) + kMaxSegs, (int64_t)kWaves);
+    const int64_t n = wanted_slabs(d_out, m) + kMaxSegs - 1, least = cdiv(cdiv(max_steps(d_in), (int64_t)kMaxRun) + kMaxSegs, (int64_t)kWaves);
     return n < least ? least : n;
 }
 
@@ -1089,12 +1096,16 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
         const unsigned wx = number([&](const Layer &L) {
             return G->token_tiles * (cdiv(L.steps, 8) + (L.xt ? cdiv(L.d_in, (int64_t)kThreads) : 0)); });
         // Inputs straight from X where a launch less is worth more than the scattered reads: up to 4
-        // tokens always (13824x5120 twice, 4 tokens: 41 against 45 us), up to 32 in small layers
-        // (900x700, 6 tokens: 17 against 20 us).  Either way the same numbers in the same order.
+        // tokens always (13824x5120 twice, 4 tokens: 41 against 45 us), up to 8 in layers of up to 64 million
+        // weights (4099 and 513 of 3001, 5 tokens: 18 against 23; 4096x4096, 6 tokens: 17 and 20; 4096 -> 11008
+        // twice, 8 tokens: level; 8192x28672: 65 and 62), up to 16 in those of up to 16 million and 4096 channels
+        // (3001x4099: 24.8 and 26.0; 8192 -> 1024 twice: 30 and 27), up to 32 in small ones (900x700, 6 tokens: 17
+        // against 20 us).  Either way the same numbers in the same order.
         const int nd = m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32));
         bool direct = G == &few && m <= 32;
         for (int i = 0; direct && i < n; ++i) {
-            if (nd > 4 && (int64_t)G->l[i].d_in * G->l[i].d_out > kDirectWeights) direct = false;
+            const int64_t most = kDirectWeights * (nd <= 8 ? 16 : (nd == 16 && G->l[i].d_in <= 4096 ? 4 : 1));
+            if (nd > 4 && (int64_t)G->l[i].d_in * G->l[i].d_out > most) direct = false;
             if (cdiv(G->l[i].steps, G->l[i].slabs > 0 ? G->l[i].slabs : 1) >= direct_steps(nd)) direct = false;
         }
         if (wx && !direct && G == &few) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
