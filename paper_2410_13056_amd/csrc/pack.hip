@@ -9,16 +9,16 @@
 
 namespace {
 
-// row_of[i] = row of channel i inside its width group, -1 when it stores no row.  A step covers 8 x 1024
-// channels: what a wavefront counts of each width by a ballot, for each of the 8, goes to LDS; four wavefronts add
-// those counts up, one a width.  (A step of 1024 with a scan over the workgroup took 0.7 us, eight of them for 8192
-// channels.)
+// row_of[i] = row of channel i inside its width group, -1 when it stores no row.  One pass: the
+// flags of up to four widths are scanned together, two 16-bit fields to a word (a step covers
+// 1024 channels, so no field overflows).
 //
 // That is the first workgroup.  Those behind it, if any, find the slices of an ascending list of entries, a
 // channel a lane, on as many compute units as that makes: scattered reads (5120 channels, 354 000 entries: 10.7 us
-// with 1024 channels a workgroup, 7.1 with 64).  The two jobs share nothing, and a launch of its own cost a layer
-// some 5 us.
-constexpr int kSlices = 64, kIndexSteps = 8, kIndexWaves = 1024 / CMPQ_WAVE;
+// with 1024 channels a workgroup, 7.6 with 256).  The two jobs share nothing, and a launch of its own cost a layer
+// some 5 us.  (Numbered by ballots, 8192 channels to a step, the first workgroup alone takes 7.0 us instead of 8.8, but
+// the step of a 70B-shaped block on three streams 0.6 % longer, and by 256 lanes 18.)
+constexpr int kSlices = 256;
 __global__ __launch_bounds__(1024) void pack_index_kernel(const uint8_t *__restrict__ bits,
                                                           int64_t d_in, PackPtrs p,
                                                           int32_t *__restrict__ row_of,
@@ -29,63 +29,30 @@ __global__ __launch_bounds__(1024) void pack_index_kernel(const uint8_t *__restr
         if ((int)threadIdx.x < kSlices && i <= d_in) seg[i] = entries_below(out_idx, n_out, i * d_out);
         return;
     }
-    constexpr int kCounts = kIndexSteps * kIndexWaves;
-    __shared__ uint32_t before[4][kCounts], total[4];
-    const int lane = threadIdx.x & (CMPQ_WAVE - 1), wave = wave_index();
+    __shared__ uint32_t scan[34];
     uint32_t run[4] = {0, 0, 0, 0};
-    for (int64_t base = 0; base < d_in; base += (int64_t)blockDim.x * kIndexSteps) {
-        int w[kIndexSteps], below[kIndexSteps];
-        const int steps = (int)min((d_in - base + 1023) / 1024, (int64_t)kIndexSteps);
-#pragma unroll
-        for (int e = 0; e < kIndexSteps; ++e) {
-            const int64_t i = base + e * 1024 + threadIdx.x;
-            w[e] = i < d_in ? bits[i] : 0;
+    for (int64_t base = 0; base < d_in; base += blockDim.x) {
+        const int64_t i = base + threadIdx.x;
+        int j = -1;
+        if (i < d_in) {
+            const int w = bits[i];
+            for (int t = 0; t < p.n_set; ++t)
+                if (w == p.width[t]) j = t;
         }
-#pragma unroll
-        for (int e = 0; e < kIndexSteps; ++e) {
-            if (e >= steps) break;
-            int j = -1;
-            below[e] = 0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const bool mine = t < p.n_set && w[e] == p.width[t] && w[e] != 0;
-                const uint64_t m = __ballot(mine);
-                if (lane == 0) before[t][e * kIndexWaves + wave] = (uint32_t)__popcll(m);
-                if (mine) {
-                    j = t;
-                    below[e] = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                }
-            }
-            w[e] = j;
+        const uint32_t a = j == 0 ? 1u : (j == 1 ? 0x10000u : 0u), b = j == 2 ? 1u : (j == 3 ? 0x10000u : 0u);
+        uint32_t a_excl, b_excl, a_total, b_total;
+        block_scan_excl_2xu32(a, b, scan, a_excl, b_excl, a_total, b_total);
+        if (j >= 0) {
+            const uint32_t field = j < 2 ? a_excl : b_excl;
+            const uint32_t before = j == 0 ? run[0] : (j == 1 ? run[1] : (j == 2 ? run[2] : run[3]));
+            const uint32_t row = before + ((j & 1) ? field >> 16 : field & 0xffffu);
+            int32_t *list = j == 0 ? p.chan_idx[0] : (j == 1 ? p.chan_idx[1] : (j == 2 ? p.chan_idx[2] : p.chan_idx[3]));
+            row_of[i] = (int32_t)row;
+            if (list) list[row] = (int32_t)i;
+        } else if (i < d_in) {
+            row_of[i] = -1;
         }
-        __syncthreads();
-        if (wave < 4) {
-            static_assert(kCounts == 2 * CMPQ_WAVE, "two counts a lane");
-            const bool there = 2 * lane < steps * kIndexWaves;
-            const uint32_t c0 = there ? before[wave][2 * lane] : 0u, c1 = there ? before[wave][2 * lane + 1] : 0u;
-            const uint32_t incl = wave_scan_incl_u32(c0 + c1);
-            before[wave][2 * lane] = incl - c0 - c1;
-            before[wave][2 * lane + 1] = incl - c1;
-            if (lane == CMPQ_WAVE - 1) total[wave] = incl;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < kIndexSteps; ++e) {
-            if (e >= steps) break;
-            const int64_t i = base + e * 1024 + threadIdx.x;
-            const int j = w[e];
-            int32_t row = -1;
-            if (j >= 0) {
-                const uint32_t start = j == 0 ? run[0] : (j == 1 ? run[1] : (j == 2 ? run[2] : run[3]));
-                row = (int32_t)(start + before[j][e * kIndexWaves + wave]) + below[e];
-                int32_t *list = j == 0 ? p.chan_idx[0] : (j == 1 ? p.chan_idx[1] : (j == 2 ? p.chan_idx[2] : p.chan_idx[3]));
-                if (list) list[row] = (int32_t)i;
-            }
-            if (i < d_in) row_of[i] = row;
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) run[t] += total[t];
-        __syncthreads();
+        run[0] += a_total & 0xffffu, run[1] += a_total >> 16, run[2] += b_total & 0xffffu, run[3] += b_total >> 16;
     }
 }
 
