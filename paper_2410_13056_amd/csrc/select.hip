@@ -463,7 +463,7 @@ __global__ __launch_bounds__(kRankThreads) void rank_channels_kernel(const float
 // exact chain 178; keys near the guess 73.)
 //
 // What bounds the chain beside the one pass over the data is its launches, 4.5 us each, and counters
-// that many workgroups add to.  Nine launches: one sample pass, two of the list, the second of which is
+// that many workgroups add to.  Nine launches (ten in large layers): one sample pass, two of the list, the second of which is
 // the exact chain's first where that one runs, and no scan of the units' counts in a kernel of its own, where
 // it were thirteen; 4096x4096 weights, k = 0.5 %, all kernels but the pass over the data: 102 -> 56 us
 // (sample 31 -> 11, list 25 -> 15, counts and output 29 -> 12).
@@ -1579,11 +1579,12 @@ __device__ __forceinline__ void exact_pass(const WselArgs &a, WselState *st, uin
 
 // Fast chain, passes over the list: its first two histograms.  The second pass also settles whether
 // the list holds the answer at all: it does unless it overflowed or is shorter than k.
-// Where it does not, the second pass is the exact chain's first instead: in a kernel of its own that one was
-// a launch of 4 us that nearly always returned at once.  The first list_blocks workgroups go over the list.
+// Where it does not, the second pass is the exact chain's first instead if `exact_here`: in a kernel of its own
+// that one was a launch of 4 us that nearly always returned at once.  The first list_blocks workgroups go over the
+// list.
 template <typename TW, int PASS>
 __global__ __launch_bounds__(kWThreads) void wsel_list_kernel(WselArgs a, WselState *st, int nunits, int list_blocks,
-                                                               uint32_t *__restrict__ hist, uint64_t k) {
+                                                               int exact_here, uint32_t *__restrict__ hist, uint64_t k) {
     constexpr int kWords = PASS == 0 ? kBins : kListFine;
     static_assert(PASS == 0 || kCopies<0> * kBins == kListFine, "both passes' counters fit");
     __shared__ uint32_t lh[kWords];
@@ -1602,7 +1603,7 @@ __global__ __launch_bounds__(kWThreads) void wsel_list_kernel(WselArgs a, WselSt
             st->rem = rem;
         }
         if (failed) {
-            exact_pass<TW, 0>(a, st, k, nunits / kWaves, hist, nullptr, nullptr, lh, nullptr, ps);
+            if (exact_here) exact_pass<TW, 0>(a, st, k, nunits / kWaves, hist, nullptr, nullptr, lh, nullptr, ps);
             return;
         }
         if ((int)blockIdx.x >= list_blocks) return;
@@ -1652,7 +1653,7 @@ __global__ void wsel_init_kernel(WselState *st, uint32_t *hist) {
     }
 }
 
-// The exact chain's second and third pass, where the fast chain does not hold the answer.  Where it found the
+// The exact chain's passes, where the fast chain does not hold the answer.  Where that one found the
 // k-th key in a coarse bin, PASS 1 counts the list's last 8 bits instead.
 template <typename TW, int PASS>
 __global__ __launch_bounds__(kWThreads) void wsel_hist_kernel(WselArgs a, WselState *st, uint64_t k, int nblocks,
@@ -2065,9 +2066,15 @@ int launch_weight_select(WselArgs a, const WselPlan &p, int64_t k, int32_t *idx_
     // 163, 167.)
     const int most_blocks = p.wc_per_unit >= 16 ? 1536 : 1024;
     const int hist_blocks = p.nblocks < most_blocks ? p.nblocks : most_blocks;
-    const int second_blocks = hist_blocks < 1024 ? (hist_blocks > list_blocks ? hist_blocks : list_blocks) : 1024;
-    wsel_list_kernel<TW, 0><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, list_blocks, w.hist, (uint64_t)k);
-    wsel_list_kernel<TW, 1><<<second_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, list_blocks, w.hist, (uint64_t)k);
+    // The first of them is part of the list's second pass in layers of up to 67 million weights.  Larger ones keep it
+    // apart: it wants more workgroups than the list, whose second pass takes 9.7 us instead of 7.6 with that many,
+    // beside other streams' kernels more.
+    const bool apart = p.wc_per_unit >= 16;
+    const int second_blocks = apart || hist_blocks < list_blocks ? list_blocks : hist_blocks;
+    wsel_list_kernel<TW, 0><<<list_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, list_blocks, 0, w.hist, (uint64_t)k);
+    wsel_list_kernel<TW, 1><<<second_blocks, kWThreads, 0, s>>>(a, w.st, p.nunits, list_blocks, !apart, w.hist, (uint64_t)k);
+    if (apart)
+        wsel_hist_kernel<TW, 0><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     wsel_hist_kernel<TW, 1><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     wsel_hist_kernel<TW, 2><<<hist_blocks, kWThreads, 0, s>>>(a, w.st, (uint64_t)k, p.nblocks, w.hist, w.above, w.local_last);
     // threshold, placement and output, from whichever chain holds the answer
