@@ -606,6 +606,21 @@ int cmpq_lut_matvec_group_fp16acc(const cmpq_deployed_layer *layers, int n_layer
                                   size_t ws_bytes, void *stream);
 
 /*
+ * Introspection for host-side checks: how cmpq_lut_matvec cuts up the product of `m` tokens with a layer, where
+ * the workspace holds its plan.  Of `layer` it reads d_in, d_out, bit_set, n_set, counts_host and k_act.
+ *   shape [6], host, out: 0 token by token, 1 several tokens multiplied while the codes are decoded, 2 the weight
+ *         decoded once; tokens at a time; workgroups that share the rows of a tile of outputs (2: tiles); parts of
+ *         the rows, one a wavefront, four a workgroup (2: 0); bytes of LDS that the inputs of the rows of the fullest
+ *         workgroup take where they come straight from X (else 0); bytes there are for them (1 alone).
+ *   parts [room][3], host, out: of the first `room` parts the width (16: O_act), the first row among those of
+ *         that width, and the rows.
+ * Launches nothing.  CMPQ_EINVAL for a null pointer, no tokens, channels or outputs, or counts that do not fit
+ * the channels; CMPQ_ESHAPE beyond the limits of cmpq_lut_matvec.
+ */
+int cmpq_lut_matvec_shape(const cmpq_deployed_layer *layer, int64_t m, int64_t *shape, int64_t *parts,
+                          int64_t room);
+
+/*
  * Measurement hook (for a benchmark that wants the duration of one kernel rather than of an
  * entry point, which may launch several).  Arms the CALLING THREAD: the next launch of the
  * named kernel from this thread records event_begin (a hipEvent_t passed as void*) on the

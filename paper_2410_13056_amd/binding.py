@@ -41,7 +41,8 @@ EXPORTS = ("cmpq_workspace_bytes", "cmpq_strerror", "cmpq_count_ppm", "cmpq_act_
            "cmpq_gather_channels", "cmpq_outliers_by_column", "cmpq_lut_matvec", "cmpq_act_stats_norm",
            "cmpq_rtn_quantize", "cmpq_select_by_width", "cmpq_lut_matvec_group", "cmpq_lut4_quantize",
            "cmpq_pack_with_error", "cmpq_time_kernel", "cmpq_act_stats_static", "cmpq_kmeans_launch_shape",
-           "cmpq_shader_clock_probe", "cmpq_lut_matvec_group_fp16acc", "cmpq_kmeans_build_shape", "cmpq_rank_channels")
+           "cmpq_shader_clock_probe", "cmpq_lut_matvec_group_fp16acc", "cmpq_kmeans_build_shape", "cmpq_rank_channels",
+           "cmpq_lut_matvec_shape")
 
 _i64, _i32, _int, _vp, _dbl, _sz = (ctypes.c_int64, ctypes.c_int32, ctypes.c_int, ctypes.c_void_p,
                                     ctypes.c_double, ctypes.c_size_t)
@@ -106,6 +107,7 @@ def lib() -> ctypes.CDLL:
         L.cmpq_time_kernel.argtypes = [_int, _vp, _vp]
         L.cmpq_kmeans_launch_shape.argtypes = [_i64, _vp]
         L.cmpq_kmeans_build_shape.argtypes = [_i64, _i64, _vp]
+        L.cmpq_lut_matvec_shape.argtypes = [_vp, _i64, _vp, _vp, _i64]
         L.cmpq_shader_clock_probe.argtypes = [_int, _int, _vp, _vp, _vp]
         L.cmpq_act_stats_static.argtypes = [_vp, _int, _i64, _i64, _i64, _vp, _vp, _int, _vp, _vp]
         L.cmpq_act_stats_norm.argtypes = [_vp, _int, _i64, _i64, _i64, _int, _vp, _vp, _int, _vp, _sz, _vp, _vp]
@@ -148,6 +150,19 @@ def kmeans_build_shape(d_in: int, d_out: int):
     shape = (_i64 * 9)()
     _check(lib().cmpq_kmeans_build_shape(int(d_in), int(d_out), shape), "cmpq_kmeans_build_shape")
     return tuple(int(v) for v in shape)
+
+
+def lut_matvec_shape(d_in: int, d_out: int, bit_set: Sequence[int], counts: Sequence[int], k_act: int, m: int):
+    """How `lut_matvec` cuts up a layer (`cmpq_lut_matvec_shape`): (way, tokens at a time, workgroups, parts, bytes of
+    LDS that inputs take straight from X, bytes there are), [(width, first row, rows), ...]."""
+    n = len(bit_set)
+    bs, cn, shape = (_i32 * n)(*bit_set), (_i64 * n)(*counts), (_i64 * 6)()
+    L = DeployedLayer(d_in=int(d_in), d_out=int(d_out), bit_set=ctypes.addressof(bs), n_set=n,
+                      counts_host=ctypes.addressof(cn), k_act=int(k_act))
+    _check(lib().cmpq_lut_matvec_shape(ctypes.byref(L), int(m), shape, None, 0), "cmpq_lut_matvec_shape")
+    parts = (_i64 * (3 * shape[3]))()
+    _check(lib().cmpq_lut_matvec_shape(ctypes.byref(L), int(m), shape, parts, shape[3]), "cmpq_lut_matvec_shape")
+    return tuple(shape), [tuple(parts[3 * i:3 * i + 3]) for i in range(shape[3])]
 
 
 def time_kernel(kernel: int, event_begin: Optional[int], event_end: Optional[int]) -> None:

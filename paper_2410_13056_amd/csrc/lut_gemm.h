@@ -15,6 +15,9 @@ size_t lut_gemm_need(const cmpq_deployed_layer &layer, int64_t m);
 // sum of lut_gemm_need over the layers.
 int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int64_t m, void *ws, hipStream_t s);
 
+// How that cuts a layer up: see cmpq_lut_matvec_shape.
+void lut_gemm_shape(const cmpq_deployed_layer &layer, int64_t m, int64_t *shape, int64_t *parts, int64_t room);
+
 // What both kinds of product use of LDS tables.
 
 // base + byte q of t in one instruction (written out: the compiler takes the byte out first).

@@ -73,6 +73,7 @@ struct Layer {
     float *partial;     // [slab][token][d_out]
     uint4 *dense;       // [step][tile][operand][lane]: W_hat in operand order (many tokens)
     int d_in, d_out, n_seg, steps, tiles, slabs, act_vec_ok;  // slabs: kWaves parts each
+    int span;           // steps of the fullest slab
 };
 
 constexpr int kMaxLayers = CMPQ_MAX_GROUP;
@@ -378,14 +379,14 @@ constexpr int direct_steps(int nd) { return ((kSlabLds - kTablesBytes) / (nd * 2
 
 // The steps of a part, and its segment.  A slab is kWaves parts, one a wavefront; a part is of one
 // width, and at the end of the last slab there may be parts that are empty.
-__device__ __forceinline__ int part_of(const Layer &L, int part, int &lo, int &hi) {
+__host__ __device__ __forceinline__ int part_of(const Layer &L, int part, int &lo, int &hi) {
     int j = 0;
 #pragma unroll
     for (int i = 1; i < kMaxSegs; ++i) j += i < L.n_seg && part >= L.seg[i].part0;
     const Seg &s = L.seg[j];
-    const int p = min(part - s.part0, s.parts);
+    const int p = part - s.part0 < s.parts ? part - s.part0 : s.parts, next = p < s.parts ? p + 1 : p;
     lo = s.step0 + (int)((uint32_t)s.steps * (uint32_t)p / (uint32_t)s.parts);
-    hi = s.step0 + (int)((uint32_t)s.steps * (uint32_t)min(p + 1, s.parts) / (uint32_t)s.parts);
+    hi = s.step0 + (int)((uint32_t)s.steps * (uint32_t)next / (uint32_t)s.parts);
     return j;
 }
 
@@ -903,7 +904,29 @@ void choose_slabs(Layer &L, int64_t m) {
         part += L.seg[j].parts;
     }
     L.slabs = (int)cdiv(parts, (int64_t)kWaves);
+    L.span = 0;
+    for (int s = 0; s < L.slabs; ++s) {
+        int first, last, other;
+        part_of(L, s * kWaves, first, other);
+        part_of(L, s * kWaves + kWaves - 1, other, last);
+        if (last - first > L.span) L.span = last - first;
+    }
 }
+
+// Whether the workgroups of a layer take the inputs of up to `nd` tokens straight from X.  They keep those of all
+// their rows in LDS, so the fullest slab decides, not the mean: parts are of even cost, and four of width 2 hold up
+// to 1.8 times the mean.  It is done where a launch less is worth more than the scattered reads: up to 4 tokens
+// always (13824x5120 twice, 4 tokens: 41 against 45 us), up to 8 in layers of up to 64 million weights (4099 and 513
+// of 3001, 5 tokens: 18 against 23; 4096x4096, 6 tokens: 17 and 20; 4096 -> 11008 twice, 8 tokens: level;
+// 8192x28672: 65 and 62), up to 16 in those of up to 16 million and 4096 channels (3001x4099: 24.8 and 26.0; 8192 ->
+// 1024 twice: 30 and 27), up to 32 in small ones (900x700, 6 tokens: 17 against 20 us).  Either way the same numbers
+// in the same order.
+bool direct_inputs(const Layer &L, int nd) {
+    const int64_t most = kDirectWeights * (nd <= 8 ? 16 : (nd == 16 && L.d_in <= 4096 ? 4 : 1));
+    if (nd > 4 && (int64_t)L.d_in * L.d_out > most) return false;
+    return L.span <= direct_steps(nd);
+}
+int direct_tokens(int64_t m) { return m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32)); }
 
 // At least what choose_slabs gives for any widths.
 int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
@@ -1054,6 +1077,29 @@ size_t lut_gemm_need(const cmpq_deployed_layer &S, int64_t m) {
     return first > last ? first : last;
 }
 
+void lut_gemm_shape(const cmpq_deployed_layer &S, int64_t m, int64_t *shape, int64_t *parts, int64_t room) {
+    Layer L;
+    if (many_tokens(S, m)) {
+        plan_layer(S, m, true, nullptr, L);
+        shape[0] = 2, shape[1] = m, shape[2] = L.tiles;
+        return;
+    }
+    const int64_t at_once = part_tokens(S.d_in, S.d_out, m);
+    plan_layer(S, at_once, false, nullptr, L);
+    shape[0] = 1, shape[1] = at_once, shape[2] = L.slabs;
+    const int nd = direct_tokens(at_once), n = L.n_seg ? L.seg[L.n_seg - 1].part0 + L.seg[L.n_seg - 1].parts : 0;
+    for (int part = 0; part < n && part < room; ++part) {
+        int lo, hi;
+        const Seg &s = L.seg[part_of(L, part, lo, hi)];
+        const int64_t row = (int64_t)(lo - s.step0) * kRowsPerStep, rows = (int64_t)(hi - lo) * kRowsPerStep;
+        parts[3 * part] = s.bits, parts[3 * part + 1] = row;
+        parts[3 * part + 2] = row + rows < s.rows ? rows : s.rows - row;
+    }
+    shape[3] = n;
+    shape[4] = at_once <= 32 && direct_inputs(L, nd) ? (int64_t)nd * (L.span * kRowsPerStep + 8) * (int64_t)sizeof(__half) : 0;
+    shape[5] = kSlabLds - kTablesBytes;
+}
+
 int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int64_t m, void *ws, hipStream_t s) {
     Group few, many;
     few.n_layers = many.n_layers = 0;
@@ -1095,19 +1141,9 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
         };
         const unsigned wx = number([&](const Layer &L) {
             return G->token_tiles * (cdiv(L.steps, 8) + (L.xt ? cdiv(L.d_in, (int64_t)kThreads) : 0)); });
-        // Inputs straight from X where a launch less is worth more than the scattered reads: up to 4
-        // tokens always (13824x5120 twice, 4 tokens: 41 against 45 us), up to 8 in layers of up to 64 million
-        // weights (4099 and 513 of 3001, 5 tokens: 18 against 23; 4096x4096, 6 tokens: 17 and 20; 4096 -> 11008
-        // twice, 8 tokens: level; 8192x28672: 65 and 62), up to 16 in those of up to 16 million and 4096 channels
-        // (3001x4099: 24.8 and 26.0; 8192 -> 1024 twice: 30 and 27), up to 32 in small ones (900x700, 6 tokens: 17
-        // against 20 us).  Either way the same numbers in the same order.
-        const int nd = m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32));
+        const int nd = direct_tokens(m);
         bool direct = G == &few && m <= 32;
-        for (int i = 0; direct && i < n; ++i) {
-            const int64_t most = kDirectWeights * (nd <= 8 ? 16 : (nd == 16 && G->l[i].d_in <= 4096 ? 4 : 1));
-            if (nd > 4 && (int64_t)G->l[i].d_in * G->l[i].d_out > most) direct = false;
-            if (cdiv(G->l[i].steps, G->l[i].slabs > 0 ? G->l[i].slabs : 1) >= direct_steps(nd)) direct = false;
-        }
+        for (int i = 0; direct && i < n; ++i) direct = direct_inputs(G->l[i], nd);
         if (wx && !direct && G == &few) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
         if (G == &few) {
             const unsigned w = number([&](const Layer &L) { return (int64_t)L.tiles * L.slabs * (tts / MT); });

@@ -502,6 +502,20 @@ __device__ __forceinline__ void act_slab(const LmArgs &a, int slab, float (*red)
     store_partial(acc, red, a.partial + (token * a.n_rows_total + a.n_lut_slabs + slab) * a.d_out, o_tile, a.d_out);
 }
 
+// The rows of part `p` of a width: even shares of its row groups (of O_act: kActRowsPerWave rows).  Past the last part: none.
+__host__ __device__ __forceinline__ void rows_of_part(const MvWidth &wd, int p, int &r0, int &n) {
+    if (wd.bits == kActBits) {
+        r0 = p * kActRowsPerWave;
+        n = wd.rows - r0 < kActRowsPerWave ? wd.rows - r0 : kActRowsPerWave;
+        return;
+    }
+    const uint32_t group = wd.bits <= 2 ? 8 : 4, groups = ((uint32_t)wd.rows + group - 1) / group, parts = (uint32_t)wd.parts;
+    const uint32_t at = (uint32_t)p < parts ? (uint32_t)p : parts, next = at < parts ? at + 1 : parts;
+    r0 = (int)(groups * at / parts * group);
+    const int r1 = (int)(groups * next / parts * group);
+    n = (r1 < wd.rows ? r1 : wd.rows) - r0;
+}
+
 // Workgroups of a layer: per tile of 2048 outputs its slabs of four parts, side by side, so that every
 // compute unit gets parts of all widths; blockIdx.y: token.
 __global__ __launch_bounds__(kThreads) void lut_matvec_kernel(MvGroup g) {
@@ -524,14 +538,7 @@ __global__ __launch_bounds__(kThreads) void lut_matvec_kernel(MvGroup g) {
     const __half *x = a.X + token * a.ldx;
     const int p = part - wd.part0;  // parts past the last one of the last slab are empty
     int r0, n;
-    if (wd.bits == kActBits) {
-        r0 = p * kActRowsPerWave;
-        n = min(wd.rows - r0, kActRowsPerWave);
-    } else {  // even shares of the row groups
-        const uint32_t group = wd.bits <= 2 ? 8 : 4, groups = ((uint32_t)wd.rows + group - 1) / group, parts = (uint32_t)wd.parts;
-        r0 = (int)(groups * min((uint32_t)p, parts) / parts * group);
-        n = min((int)(groups * min((uint32_t)p + 1u, parts) / parts * group), wd.rows) - r0;
-    }
+    rows_of_part(wd, p, r0, n);
     float acc[kOutPerLane];
 #pragma unroll
     for (int k = 0; k < kOutPerLane; ++k) acc[k] = 0.f;
@@ -1175,4 +1182,45 @@ extern "C" int cmpq_lut_matvec(const void *X, int64_t m, int64_t d_in, int64_t l
     L.ldy = ldy;
     if (m < 0) return CMPQ_EINVAL;
     return launch_group(&L, 1, m, ws, ws_bytes, stream);
+}
+
+extern "C" int cmpq_lut_matvec_shape(const cmpq_deployed_layer *layer, int64_t m, int64_t *shape, int64_t *parts,
+                                     int64_t room) {
+    if (!layer || !shape || room < 0 || (room > 0 && !parts)) return CMPQ_EINVAL;
+    // sizes alone: what check_layer asks of the pointers is not looked at
+    static const uint32_t *const packed[kMaxWidths] = {};
+    static const int32_t *const chan_idx[kMaxWidths] = {};
+    static const uint16_t *const lut[kMaxWidths] = {};
+    cmpq_deployed_layer L = {};
+    L.d_in = L.ldx = layer->d_in;
+    L.d_out = L.ldy = L.ld_act = layer->d_out;
+    L.bit_set = layer->bit_set, L.n_set = layer->n_set, L.counts_host = layer->counts_host, L.k_act = layer->k_act;
+    L.packed = packed, L.chan_idx = chan_idx, L.lut = lut;
+    if (m < 1 || L.d_in < 1 || L.d_out < 1 || L.k_act < 0 || L.n_set < 0 || L.n_set > kMaxWidths) return CMPQ_EINVAL;
+    if (L.n_set > 0 && (!L.bit_set || !L.counts_host)) return CMPQ_EINVAL;
+    int64_t rows = L.k_act;
+    for (int j = 0; j < L.n_set; ++j) {
+        if (L.bit_set[j] < 1 || L.bit_set[j] > 4 || L.counts_host[j] < 0) return CMPQ_EINVAL;
+        rows += L.counts_host[j];
+    }
+    if (rows > L.d_in) return CMPQ_EINVAL;
+    const int order = 0;
+    Plan p;
+    plan_token_by_token(&L, &order, 1, m, m, nullptr, p, false);
+    if (m > 65535 || L.d_out >= (1 << 20) || p.y_total > 65535) return CMPQ_ESHAPE;
+    for (int i = 0; i < 6; ++i) shape[i] = 0;
+    if (m > 1 && lut_gemm_takes(L.d_in, L.d_out, m)) {
+        lut_gemm_shape(L, m, shape, parts, room);
+        return CMPQ_OK;
+    }
+    const MvLayer &v = p.mv.l[0];
+    shape[1] = m, shape[2] = v.slabs;
+    for (int j = 0; j < v.n_w; ++j)
+        for (int i = 0; i < v.w[j].parts; ++i) {
+            int r0, n;
+            rows_of_part(v.w[j], i, r0, n);
+            const int64_t at = shape[3]++;
+            if (at < room) parts[3 * at] = v.w[j].bits, parts[3 * at + 1] = r0, parts[3 * at + 2] = n;
+        }
+    return CMPQ_OK;
 }

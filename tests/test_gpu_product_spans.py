@@ -1,0 +1,31 @@
+"""Products of 16 and 32 tokens whose workgroups are at, and past, the most rows of which they can keep the inputs in
+LDS (tests/test_product_plan.py has the rule itself on the host).
+
+Bar: per output and token, the fp32 rounding of the sums - 2e-6 of the sum of the terms' magnitudes -
+against the product in 64 bits with the weight rebuilt from W, levels, codes and outlier indices."""
+import pytest
+import torch
+
+from test_gpu_deploy import DEV, env  # noqa: F401
+from test_gpu_product_tokens import _check, _layer
+
+pytestmark = pytest.mark.gpu
+
+
+# the fullest workgroup holds the inputs of exactly as many rows as fit (2064, 8528), 1 step too many, 5 too many;
+# one step is 32 rows
+@pytest.mark.parametrize("d_in,d_out,bit_set,avg,m", [
+    (2064, 256, (2, 3), 2.75, 32), (4096, 512, (2, 3), 2.5, 32), (5696, 512, (2, 3), 2.5, 32),
+    (5120, 640, (2, 3, 4), 2.75, 32), (8528, 256, (2, 3), 2.5, 16), (9824, 256, (2, 3), 2.8, 16)])
+def test_inputs_of_full_workgroups(env, d_in, d_out, bit_set, avg, m):
+    P, ws = env["P"], env["ws"]
+    dep, What = _layer(env, d_in, d_in, d_out, bit_set, avg, 4500)
+    wide, _ = _layer(env, d_out, d_in, 8500, bit_set, avg, 4500)      # too large for inputs straight from X
+    X = torch.randn((m, d_in), generator=torch.Generator(device=DEV).manual_seed(m), device=DEV).to(torch.float16)
+    Y = P.lut_matvec(dep, X, ws)
+    _check(Y, X, What)
+    for n in (m, m - 1, m // 2 + 1):
+        Ys = [torch.full((n, d.d_out), float("nan"), device=DEV) for d in (wide, dep)]
+        P.group_products([wide, dep])([X[:n], X[:n]], Ys, ws)
+        assert torch.equal(Ys[1], P.lut_matvec(dep, X[:n], ws))
+        _check(Ys[1], X[:n], What)
