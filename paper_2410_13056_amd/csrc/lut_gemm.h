@@ -18,6 +18,14 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
 // How that cuts a layer up: see cmpq_lut_matvec_shape.
 void lut_gemm_shape(const cmpq_deployed_layer &layer, int64_t m, int64_t *shape, int64_t *parts, int64_t room);
 
+// Where share `i` of `n` things in `parts` even shares begins: floor(n * i / parts).  The product passes 32 bits from
+// 741 441 rows of width 4 on, and a division in 64 bits is 100 instructions, in fp64 a tenth of that.  Exact: n and
+// parts stay below 2^22 (limit of 65535 slabs of 128 rows), so the product does below 2^44, and a quotient below
+// 2^22 that is no whole number lies further than 2^-22 from the next, its rounding less than 2^-30.
+__host__ __device__ __forceinline__ int share_of(int n, int i, int parts) {
+    return (int)((double)n * (double)i / (double)parts);
+}
+
 // What both kinds of product use of LDS tables.
 
 // base + byte q of t in one instruction (written out: the compiler takes the byte out first).

@@ -385,8 +385,8 @@ __host__ __device__ __forceinline__ int part_of(const Layer &L, int part, int &l
     for (int i = 1; i < kMaxSegs; ++i) j += i < L.n_seg && part >= L.seg[i].part0;
     const Seg &s = L.seg[j];
     const int p = part - s.part0 < s.parts ? part - s.part0 : s.parts, next = p < s.parts ? p + 1 : p;
-    lo = s.step0 + (int)((uint32_t)s.steps * (uint32_t)p / (uint32_t)s.parts);
-    hi = s.step0 + (int)((uint32_t)s.steps * (uint32_t)next / (uint32_t)s.parts);
+    lo = s.step0 + share_of(s.steps, p, s.parts);
+    hi = s.step0 + share_of(s.steps, next, s.parts);
     return j;
 }
 

@@ -509,10 +509,10 @@ __host__ __device__ __forceinline__ void rows_of_part(const MvWidth &wd, int p, 
         n = wd.rows - r0 < kActRowsPerWave ? wd.rows - r0 : kActRowsPerWave;
         return;
     }
-    const uint32_t group = wd.bits <= 2 ? 8 : 4, groups = ((uint32_t)wd.rows + group - 1) / group, parts = (uint32_t)wd.parts;
-    const uint32_t at = (uint32_t)p < parts ? (uint32_t)p : parts, next = at < parts ? at + 1 : parts;
-    r0 = (int)(groups * at / parts * group);
-    const int r1 = (int)(groups * next / parts * group);
+    const int shift = wd.bits <= 2 ? 3 : 2, groups = (wd.rows + (1 << shift) - 1) >> shift;
+    const int at = p < wd.parts ? p : wd.parts, next = at < wd.parts ? at + 1 : at;
+    r0 = share_of(groups, at, wd.parts) << shift;
+    const int r1 = share_of(groups, next, wd.parts) << shift;
     n = (r1 < wd.rows ? r1 : wd.rows) - r0;
 }
 

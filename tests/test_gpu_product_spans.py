@@ -29,3 +29,19 @@ def test_inputs_of_full_workgroups(env, d_in, d_out, bit_set, avg, m):
         P.group_products([wide, dep])([X[:n], X[:n]], Ys, ws)
         assert torch.equal(Ys[1], P.lut_matvec(dep, X[:n], ws))
         _check(Ys[1], X[:n], What)
+
+
+@pytest.mark.parametrize("b", [3, 4])
+def test_rows_whose_product_with_the_parts_passes_32_bits(env, b):
+    B, ws, n, d_out = env["B"], env["ws"], 900001, 8
+    gen = torch.Generator(device=DEV).manual_seed(b)
+    codes = torch.randint(0, 1 << b, (n, d_out), generator=gen, device=DEV)
+    packed = (codes << (b * torch.arange(d_out, device=DEV))).sum(1, keepdim=True)
+    packed = torch.where(packed >= 1 << 31, packed - (1 << 32), packed).to(torch.int32)
+    lut = torch.randn((n, 1 << b), generator=gen, device=DEV).to(torch.float16)
+    X = torch.randn((1, n), generator=gen, device=DEV).to(torch.float16)
+    call = B.LutMatvecCall(n, d_out, (b,), [n], [packed], [torch.arange(n, dtype=torch.int32, device=DEV)], [lut],
+                           None, None, None, None, None)
+    Y = torch.full((1, d_out), float("nan"), device=DEV)
+    call(X, Y, ws)
+    _check(Y, X, lut.gather(1, codes).double())

@@ -47,3 +47,25 @@ def test_inputs_of_the_fullest_workgroup_fit_into_lds():
         assert tokens * (32 * most + 8) * 2 == used <= there, (d_in, d_out, m, bit_set, counts, k_act, most)
         taken[tokens] += 1
     assert min(taken.values()) > 50, taken                      # (the rule still takes layers)
+
+
+def test_parts_cover_every_row_once():
+    """For one token and for several: the parts of a width follow each other without gap or overlap, none is longer
+    than the sums of one wavefront may run, and their partial results fit the workspace.  Up to row counts at which
+    rows times parts leaves 32 bits."""
+    large = [(n, 8, m, (1, 2, 3, 4), counts, 0) for n in (741441, 800000, 8000000) for m in (1, 2)
+             for counts in ([0, 0, 0, n], [0, 0, n, 0], [0, n, 0, 0], [n // 2, 0, 0, n // 2])]
+    some = list(_layers(2, 400))
+    for d_in, d_out, m, bit_set, counts, k_act in large + some + [(*c[:2], 1, *c[3:]) for c in some]:
+        case = (d_in, d_out, m, bit_set, counts, k_act)
+        (way, tokens, groups, n, _, _), parts = B.lut_matvec_shape(*case[:2], bit_set, counts, k_act, m)
+        assert way < 2 and tokens == m and groups == -(-n // 4), case
+        assert groups * m * d_out * 4 <= B.workspace_bytes(B.OP_LUT_MATVEC, d_in, d_out, m), case
+        most = {b: 256 if way else (64 if b <= 4 else 8) for b in (1, 2, 3, 4, 16)}
+        left = dict(zip(bit_set, counts))
+        left[16] = k_act
+        at = dict.fromkeys(left, 0)
+        for width, row, rows in parts:
+            assert row == at[width] and 0 < rows <= most[width], (case, width, row, rows)
+            at[width] += rows
+        assert at == left, case
