@@ -1,6 +1,7 @@
 // The product of several tokens with deployed layers (lut_gemm.hip), as lut_matvec.hip calls it.
 #pragma once
 #include "common.h"
+#include <type_traits>
 
 // Whether a layer's product with m tokens runs here (otherwise token by token in lut_matvec.hip).
 // Depends on nothing but these sizes, so that a layer gives the same bits in any group.
@@ -47,6 +48,39 @@ template <typename T>
 __device__ __forceinline__ T lds_read(uint32_t at) {
     typedef const T __attribute__((address_space(3))) *P;
     return *(P)(uintptr_t)at;
+}
+
+// Outputs o .. o + 7 of a row of O_act, from any even address.  In the last tile of a row the last eight are read
+// instead where not all are there, and shifted into place; what is not there is not written.  One load, no branch
+// between lanes: with a branch for every output the last tile (or, where rows are not 16 bytes apart, every one of
+// the product with one token) waited for its loads one after the other.  Kernel times, us: 7872 -> 476, 24 tokens
+// 19.1, now 13.4; 2048 -> 2006, 5 tokens 14.1 and 9.5; 832 -> 5118, one token 15.8 and 8.4.
+// MODE, the same in all lanes: all lanes have all of their outputs; some do not; rows of fewer than eight.
+enum { kActFull, kActShifted, kActFew };
+template <int MODE>
+__device__ __forceinline__ uint4 act_outputs8(const __half *row, int o, int d_out) {
+    const char *p = reinterpret_cast<const char *>(row);
+    if constexpr (MODE == kActFew) {
+        uint32_t h[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) h[e] = reinterpret_cast<const uint16_t *>(p)[min(e, d_out - 1)];
+        return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+    }
+    typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(2)));
+    const Words4 v = *reinterpret_cast<const Words4 *>(p + (uint32_t)(MODE == kActFull ? o : min(o, d_out - 8)) * 2u);
+    if constexpr (MODE == kActFull) return make_uint4(v[0], v[1], v[2], v[3]);
+    const int s = max(o + 8 - d_out, 0);  // that many of the eight are not there (8 and more: none is)
+    const uint32_t a0 = s & 4 ? v[2] : v[0], a1 = s & 4 ? v[3] : v[1];
+    const uint32_t b0 = s & 2 ? a1 : a0, b1 = s & 2 ? v[2] : a1, b2 = s & 2 ? v[3] : v[2];
+    const uint32_t bits = (s & 1) * 16;
+    return make_uint4(__builtin_amdgcn_alignbit(b1, b0, bits), __builtin_amdgcn_alignbit(b2, b1, bits),
+                      __builtin_amdgcn_alignbit(v[3], b2, bits), v[3] >> bits);
+}
+template <typename F>
+__device__ __forceinline__ void with_act_mode(int d_out, bool full, F &&f) {
+    if (full) f(std::integral_constant<int, kActFull>());
+    else if (d_out >= 8) f(std::integral_constant<int, kActShifted>());
+    else f(std::integral_constant<int, kActFew>());
 }
 
 __device__ __forceinline__ void wave_fence() {

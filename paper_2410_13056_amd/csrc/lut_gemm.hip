@@ -72,7 +72,7 @@ struct Layer {
     int32_t *pos;       // [channel]: its row among all steps (many tokens)
     float *partial;     // [slab][token][d_out]
     uint4 *dense;       // [step][tile][operand][lane]: W_hat in operand order (many tokens)
-    int d_in, d_out, n_seg, steps, tiles, slabs, act_vec_ok;  // slabs: kWaves parts each
+    int d_in, d_out, n_seg, steps, tiles, slabs;  // slabs: kWaves parts each
     int span;           // steps of the fullest slab
 };
 
@@ -166,7 +166,7 @@ struct TileArgs {
     int64_t ldx;
     int64_t ld_act;
     float *partial;
-    int steps, d_out, act_vec_ok;
+    int steps, d_out;
 };
 
 // ---- decoding one step: 32 rows x 256 outputs -> 16 operands
@@ -210,24 +210,15 @@ struct Decoder {
         const int unit = (out0 >> 4) + (lane & 15);        // which 16 outputs of a row
         if constexpr (kAct) {
             const int o = unit * kOuts + half * 8;
+            with_act_mode(L.d_out, full, [&](auto mode) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int r = row + 8 * kg + j;
-                const bool ok = r < s.rows;
-                const __half *p = L.W_act + (int64_t)min(r, s.rows - 1) * L.ld_act + o;
-                if (full && L.act_vec_ok) {
-                    const uint4 a = *reinterpret_cast<const uint4 *>(p);
+                for (int j = 0; j < 8; ++j) {
+                    const int r = row + 8 * kg + j;
+                    const uint4 a = act_outputs8<decltype(mode)::value>(L.W_act + (int64_t)min(r, s.rows - 1) * L.ld_act, o, L.d_out);
+                    const bool ok = r < s.rows;
                     w[j][0] = ok ? a.x : 0, w[j][1] = ok ? a.y : 0, w[j][2] = ok ? a.z : 0, w[j][3] = ok ? a.w : 0;
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        uint32_t v = 0;
-                        if (ok && o + 2 * q < L.d_out) v = __half_as_ushort(p[2 * q]);
-                        if (ok && o + 2 * q + 1 < L.d_out) v |= (uint32_t)__half_as_ushort(p[2 * q + 1]) << 16;
-                        w[j][q] = v;
-                    }
                 }
-            }
+            });
         } else {
             const int first = B == 4 ? 2 * unit : (B == 3 ? 3 * (unit >> 1) + (unit & 1) : (B == 2 ? unit : unit >> 1));
             const uint32_t wpr = (uint32_t)s.words_per_row;
@@ -571,7 +562,7 @@ __global__ __launch_bounds__(kThreads, MT == 1 ? 3 : 2) void lut_tokens_kernel(G
     // widths (two 13824x5120 layers, 16 tokens: with the tiles innermost those of the widest codes took
     // 25 us, the others 15)
     const int slab = wg % L.slabs, rest = wg / L.slabs, tile = rest % L.tiles, tt = (rest / L.tiles) * MT;
-    const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out, L.act_vec_ok};
+    const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out};
     multiply_slab<MT, ND>(a, L, slab, tile, tt, g.m, smem);
 }
 
@@ -700,7 +691,8 @@ struct DecodeWgs {
     int wg0[kMaxLayers];  // first workgroup of each layer among those that decode
     int first;            //   and the first of those in the launch
 };
-__global__ __launch_bounds__(kThreads) void lut_decode_kernel(Group g, DecodeWgs d) {
+// (Held to 6 wavefronts a SIMD, 79 registers: the rows of O_act alone would have it take 101.)
+__global__ __launch_bounds__(kThreads, 6) void lut_decode_kernel(Group g, DecodeWgs d) {
     __shared__ __align__(kTableBytes) unsigned char smem[kTokensLds > kWaves * kTableBytes ? kTokensLds : kWaves * kTableBytes];
     int wg = (int)blockIdx.x;
     if (wg < d.first) {
@@ -719,7 +711,7 @@ __global__ __launch_bounds__(kThreads) void lut_decode_kernel(Group g, DecodeWgs
 #pragma unroll
     for (int i = 1; i < kMaxSegs; ++i) j += i < L.n_seg && step >= L.seg[i].step0;
     const Seg s = L.seg[j];
-    const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out, L.act_vec_ok};
+    const TileArgs a{L.xf, L.X, L.W_act, L.ldx, L.ld_act, L.partial, L.steps, L.d_out};
     Word4 *dense = reinterpret_cast<Word4 *>(L.dense) + (int64_t)unit * kOuts * CMPQ_WAVE;
     switch (s.bits) {
         case 1: decode_step<1>(a, s, dense, step, tile * kTileOuts, tables); break;
@@ -1036,7 +1028,6 @@ size_t plan_layer(const cmpq_deployed_layer &S, int64_t m, bool dense, char *bas
     L.ldx = S.ldx;
     L.W_act = reinterpret_cast<const __half *>(S.W_act);
     L.ld_act = S.ld_act;
-    L.act_vec_ok = reinterpret_cast<uintptr_t>(S.W_act) % 16 == 0 && S.ld_act % 8 == 0;
     L.colptr = S.colptr;
     L.row_idx = S.row_idx;
     L.delta = S.delta;

@@ -57,7 +57,6 @@ struct LmArgs {
     int n_widths, rows_per_wave;
     int n_lut_slabs, n_act_slabs;  // a layer's blockIdx.y range: O_act slabs first, then the packed slabs
     int n_rows_total;              // partial rows per token: packed slabs, then O_act slabs
-    int act_vec_ok;                // W_act rows may be read 16 bytes at a time
     int tiles;                     // tiles of 2048 outputs
     int y0;                        // first blockIdx.y of this layer
 };
@@ -131,7 +130,7 @@ struct MvLayer {
     const __half *X, *W_act;
     int64_t ldx, ld_act;
     float *partial;                // [tokens][slabs][d_out]
-    int d_out, n_w, slabs, act_vec_ok;
+    int d_out, n_w, slabs;
 };
 struct MvGroup {
     int wg0[kMaxLayers];  // first workgroup of each layer (past the last layer: INT_MAX)
@@ -444,50 +443,38 @@ template <typename Args>
 __device__ __forceinline__ void act_rows(const Args &a, const int32_t *__restrict__ act_idx, const __half *__restrict__ x,
                                          int64_t r0, int n, int64_t o0, float (&acc)[kOutPerLane]) {
     const int lane = threadIdx.x & (CMPQ_WAVE - 1);
-    const int64_t d_out = a.d_out;
     const float x_mine = lane < n ? __half2float(x[act_idx[r0 + lane]]) : 0.f;
     // every row's input in a scalar register (rows past the count: 0), read before lanes part ways
     float xs[kActRowsPerWave];
 #pragma unroll
     for (int j = 0; j < kActRowsPerWave; ++j)
         xs[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x_mine), j));
-    const bool vec = a.act_vec_ok && o0 + kOutPerLane <= d_out;
-    if (vec) {
+    const int d_out = (int)a.d_out;
+    with_act_mode(d_out, o0 - lane * kOutPerLane + kTileOut <= d_out, [&](auto mode) {
 #pragma unroll
         for (int j = 0; j < kActRowsPerWave; j += 2) {
             if (j >= n) break;
             uint4 raw[2][4];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                // the second row of an odd count is read again from the first: its input is 0
-                const int64_t r = r0 + (j + u < n ? j + u : j);
+                // (a second row that is not there is read again from the first, and left out)
+                const __half *row = a.W_act + (r0 + (j + u < n ? j + u : j)) * a.ld_act;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    raw[u][q] = reinterpret_cast<const uint4 *>(a.W_act + r * a.ld_act + o0)[q];
+                for (int q = 0; q < 4; ++q) raw[u][q] = act_outputs8<decltype(mode)::value>(row, (int)o0 + 8 * q, d_out);
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const float xi = xs[j + u];
+                if (j + u >= n) break;
                 const __half2 *h = reinterpret_cast<const __half2 *>(raw[u]);
 #pragma unroll
                 for (int k = 0; k < kOutPerLane / 2; ++k) {
                     const float2 wv = __half22float2(h[k]);
-                    acc[2 * k] = fmaf(xi, wv.x, acc[2 * k]);
-                    acc[2 * k + 1] = fmaf(xi, wv.y, acc[2 * k + 1]);
+                    acc[2 * k] = fmaf(xs[j + u], wv.x, acc[2 * k]);
+                    acc[2 * k + 1] = fmaf(xs[j + u], wv.y, acc[2 * k + 1]);
                 }
             }
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kActRowsPerWave; ++j) {
-            if (j >= n) break;
-            const float xi = xs[j];
-            const __half *wrow = a.W_act + (r0 + j) * a.ld_act + o0;
-#pragma unroll
-            for (int k = 0; k < kOutPerLane; ++k)
-                if (o0 + k < d_out) acc[k] = fmaf(xi, __half2float(wrow[k]), acc[k]);
-        }
-    }
+    });
 }
 
 __device__ __forceinline__ void act_slab(const LmArgs &a, int slab, float (*red)[kRedFloats]) {
@@ -978,7 +965,6 @@ void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, in
         a.W_act = reinterpret_cast<const __half *>(L.W_act);
         a.k_act = L.k_act;
         a.ld_act = L.ld_act;
-        a.act_vec_ok = reinterpret_cast<uintptr_t>(L.W_act) % 16 == 0 && L.ld_act % 8 == 0;
         int slab0 = 0;
         for (int j = 0; j < L.n_set; ++j) {
             if (L.counts_host[j] == 0) continue;
@@ -1018,7 +1004,6 @@ void plan_token_by_token(const cmpq_deployed_layer *layers, const int *order, in
             v.ld_act = L.ld_act;
             v.partial = a.partial;
             v.d_out = (int)L.d_out;
-            v.act_vec_ok = a.act_vec_ok;
             choose_parts(v, tiles, m);
             fa.n_rows_total = v.slabs;
             p.mv.wg0[s] = (int)p.wgs;
