@@ -107,6 +107,17 @@ __device__ __forceinline__ int xcd_order(int i, int n) {
 
 // ---- X as the product reads it
 
+// Inputs of channel `chan` (-1: none) of the tokens t0 .. t0 + 15, zero past the last token.  What is not there is
+// read from channel 0 or the last token and dropped: loads under a condition each waited for the one before
+// (8000 channels, 16 tokens: 8.6 us for the launch, now 4.8).
+__device__ __forceinline__ void load_tokens(const __half *__restrict__ X, int64_t ldx, int chan, int t0, int m, __half (&v)[kTok]) {
+    const __half *x = X + max(chan, 0);
+#pragma unroll
+    for (int t = 0; t < kTok; ++t) v[t] = x[(int64_t)min(t0 + t, m - 1) * ldx];
+#pragma unroll
+    for (int t = 0; t < kTok; ++t) v[t] = chan >= 0 && t0 + t < m ? v[t] : __ushort_as_half(0);
+}
+
 // Workgroups of a layer: per token tile, blocks of 256 rows (8 steps) of the operand order, then
 // blocks of 256 channels.
 constexpr int kTokensLds = kTok * (kThreads + 8) * 2;
@@ -120,9 +131,7 @@ __device__ __forceinline__ void order_tokens(const Group &g, const Layer &L, int
         const int c = (b - row_blocks) * kThreads + tid;
         if (c >= L.d_in) return;
         __half v[kTok];
-#pragma unroll
-        for (int t = 0; t < kTok; ++t)
-            v[t] = t0 + t < g.m ? L.X[(int64_t)(t0 + t) * L.ldx + c] : __ushort_as_half(0);
+        load_tokens(L.X, L.ldx, c, t0, g.m, v);
         uint4 *dst = reinterpret_cast<uint4 *>(L.xt + ((int64_t)tt * L.d_in + c) * kTok);
         dst[0] = reinterpret_cast<const uint4 *>(v)[0];
         dst[1] = reinterpret_cast<const uint4 *>(v)[1];
@@ -139,9 +148,10 @@ __device__ __forceinline__ void order_tokens(const Group &g, const Layer &L, int
         }
     }
     if (L.pos && tt == 0 && chan >= 0) L.pos[chan] = k;
+    __half v[kTok];
+    load_tokens(L.X, L.ldx, chan, t0, g.m, v);
 #pragma unroll
-    for (int t = 0; t < kTok; ++t)
-        s[t][tid] = chan >= 0 && t0 + t < g.m ? L.X[(int64_t)(t0 + t) * L.ldx + chan] : __ushort_as_half(0);
+    for (int t = 0; t < kTok; ++t) s[t][tid] = v[t];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
