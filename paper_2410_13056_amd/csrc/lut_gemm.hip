@@ -1144,7 +1144,11 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
             return G->token_tiles * (cdiv(L.steps, 8) + (L.xt ? cdiv(L.d_in, (int64_t)kThreads) : 0)); });
         const int nd = direct_tokens(m);
         bool direct = G == &few && m <= 32;
-        for (int i = 0; direct && i < n; ++i) direct = direct_inputs(G->l[i], nd);
+        // (past 8 tokens by the weights of all layers: the launch left out is one, the scattered reads are each layer's;
+        // 542 -> three times 13568, 12 tokens: 28.9 us with inputs straight from X, 24.1 without)
+        int64_t weights = 0;
+        for (int i = 0; i < n; ++i) weights += (int64_t)G->l[i].d_in * G->l[i].d_out;
+        for (int i = 0; direct && i < n; ++i) direct = direct_inputs(G->l[i], nd) && (nd <= 8 || weights <= 4 * kDirectWeights);
         if (wx && !direct && G == &few) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
         if (G == &few) {
             const unsigned w = number([&](const Layer &L) { return (int64_t)L.tiles * L.slabs * (tts / MT); });
