@@ -890,6 +890,17 @@ int64_t part_steps(int bits, int64_t cost) {
     const int64_t n = bits <= 2 ? cost / 2 : cost / 3;
     return n < kMaxRun ? n : kMaxRun;
 }
+// At least what choose_slabs gives for any widths.
+int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
+    const int64_t n = wanted_slabs(d_out, m) + kMaxSegs - 1, least = cdiv(cdiv(max_steps(d_in), (int64_t)kMaxRun) + kMaxSegs, (int64_t)kWaves);
+    return n < least ? least : n;
+}
+// Up to 8 tokens a part has at most 5 steps of width 3 or 4 where the scratch for that is there, whatever is
+// wanted: longer ones are a chain of latencies in a workgroup, with a third of the chip's places taken (5535 ->
+// 12608, 2 tokens 31.4 us in 343 workgroups of up to 7 steps, 26.5 in 441; 7808 -> 8768 and 2487, 4 tokens 34.2 and 31.2).
+// With more tokens two layers of that size side by side lose more (5756 -> 11456 twice, 16 tokens 51.0 us with 6
+// steps, 54.9 with 5) than one alone gains.
+constexpr int64_t kShortCost = 17, kShortTokens = 8;
 void choose_slabs(Layer &L, int64_t m) {
     // (where there are few tiles, widths with few rows get their parts on top)
     const int64_t slabs = wanted_slabs(L.d_out, m), want = kWaves * (slabs + (slabs == kMaxSlabs && L.n_seg > 1 ? L.n_seg - 1 : 0));
@@ -898,6 +909,7 @@ void choose_slabs(Layer &L, int64_t m) {
         parts = 0;
         for (int j = 0; j < L.n_seg; ++j) parts += cdiv(L.seg[j].steps, part_steps(L.seg[j].bits, cost));
         if (parts <= want || cost == 3 * kMaxRun) break;
+        if (m <= kShortTokens && cost == kShortCost && parts <= kWaves * most_slabs(L.d_in, L.d_out, m)) break;
     }
     int part = 0;
     for (int j = 0; j < L.n_seg; ++j) {
@@ -929,12 +941,6 @@ bool direct_inputs(const Layer &L, int nd) {
     return L.span <= direct_steps(nd);
 }
 int direct_tokens(int64_t m) { return m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32)); }
-
-// At least what choose_slabs gives for any widths.
-int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
-    const int64_t n = wanted_slabs(d_out, m) + kMaxSegs - 1, least = cdiv(cdiv(max_steps(d_in), (int64_t)kMaxRun) + kMaxSegs, (int64_t)kWaves);
-    return n < least ? least : n;
-}
 
 // Whether to decode the weight once into memory and multiply from there.  That costs 4 bytes of
 // traffic per weight and two launches, multiplying while decoding costs a decoding per 32 tokens;
