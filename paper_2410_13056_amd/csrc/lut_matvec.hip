@@ -578,7 +578,7 @@ constexpr int kFinRuns = kThreads / kFinCols;
 //     each in pairs; the loads of the first eight are on their way before anything else.
 //   * O_q: 16 lanes per column; lane l takes the column's entries l, l+16, ... (8 in flight)
 //     and adds them in that order.
-// Per output, the 16 run sums are added in run order, then the 16 O_q sums in lane order.
+// Per output, the 16 run sums are added in pairs, then the 16 O_q sums in lane order.
 struct FinArgs {
     const __half *X;
     int64_t ldx, d_out;
@@ -650,12 +650,16 @@ __global__ __launch_bounds__(kThreads, 8) void lut_matvec_finish_kernel(FinGroup
     part[hi][lo] = y;
     __syncthreads();
     if (threadIdx.x < kFinCols && o0 + threadIdx.x < d_out) {
-        float dense = 0.f, sparse = 0.f;
+        float dense[kFinRuns], sparse = 0.f;
 #pragma unroll
-        for (int q = 0; q < kFinRuns; ++q) dense += part[q][threadIdx.x];
+        for (int q = 0; q < kFinRuns; ++q) dense[q] = part[q][threadIdx.x];
+#pragma unroll
+        for (int n = kFinRuns / 2; n > 0; n /= 2)
+#pragma unroll
+            for (int q = 0; q < n; ++q) dense[q] = dense[2 * q] + dense[2 * q + 1];
 #pragma unroll
         for (int q = 0; q < 16; ++q) sparse += sp[threadIdx.x][q];
-        a.Y[token * a.ldy + o0 + threadIdx.x] = dense + sparse;
+        a.Y[token * a.ldy + o0 + threadIdx.x] = dense[0] + sparse;
     }
 }
 
