@@ -568,15 +568,20 @@ def rtn_quantize(W: torch.Tensor, bits: torch.Tensor, group: int, codes: torch.T
            "cmpq_rtn_quantize")
 
 
+def _check_kept_runs(d_in: int, d_out: int, centroids_by_width: Sequence[torch.Tensor],
+                     codes_by_width: Sequence[torch.Tensor]) -> None:
+    for c, k in zip(centroids_by_width, codes_by_width):
+        if tuple(c.shape) != (d_in, KMAX) or tuple(k.shape) != (d_in, d_out) or not c.is_contiguous() \
+                or not k.is_contiguous() or c.dtype != torch.float32 or k.dtype != torch.uint8:
+            raise ValueError("kept runs must be contiguous [d_in,16] fp32 levels and [d_in,d_out] uint8 codes")
+
+
 def select_by_width(bits: torch.Tensor, bit_set: Sequence[int], centroids_by_width: Sequence[torch.Tensor],
                     codes_by_width: Sequence[torch.Tensor], centroids: torch.Tensor, codes: torch.Tensor) -> None:
     """The first K-means pass for the allocation `bits`, chosen row by row from one kept run per width."""
     d_in, d_out = codes.shape
     n = len(bit_set)
-    for c, k in zip(centroids_by_width, codes_by_width):
-        if tuple(c.shape) != (d_in, KMAX) or tuple(k.shape) != (d_in, d_out) or not c.is_contiguous() \
-                or not k.is_contiguous() or c.dtype != torch.float32 or k.dtype != torch.uint8:
-            raise ValueError("kept runs must be contiguous [d_in,16] fp32 levels and [d_in,d_out] uint8 codes")
+    _check_kept_runs(d_in, d_out, centroids_by_width, codes_by_width)
     if not codes.is_contiguous() or not centroids.is_contiguous() or tuple(centroids.shape) != (d_in, KMAX):
         raise ValueError("outputs must be contiguous [d_in,16] and [d_in,d_out]")
     _check(lib().cmpq_select_by_width(_ptr(bits), d_in, d_out, (_i32 * n)(*bit_set), n,
@@ -587,12 +592,12 @@ def select_by_width(bits: torch.Tensor, bit_set: Sequence[int], centroids_by_wid
 
 
 def select_levels_by_width(bits: torch.Tensor, bit_set: Sequence[int], centroids_by_width: Sequence[torch.Tensor],
-                           codes_by_width: Sequence[torch.Tensor], centroids: torch.Tensor) -> None:
-    """`select_by_width` without the codes (rows of no length)."""
+                           codes_by_width: Sequence[torch.Tensor], centroids: torch.Tensor, d_out: int) -> None:
+    """`select_by_width` without the codes (rows of no length).  Takes and refuses the same kept runs."""
     d_in, n = bits.numel(), len(bit_set)
-    for c in (*centroids_by_width, centroids):
-        if tuple(c.shape) != (d_in, KMAX) or not c.is_contiguous() or c.dtype != torch.float32:
-            raise ValueError("levels must be contiguous [d_in,16] fp32")
+    _check_kept_runs(d_in, d_out, centroids_by_width, codes_by_width)
+    if not centroids.is_contiguous() or tuple(centroids.shape) != (d_in, KMAX):
+        raise ValueError("levels must be contiguous [d_in,16]")
     _check(lib().cmpq_select_by_width(_ptr(bits), d_in, 0, (_i32 * n)(*bit_set), n,
                                       (_vp * n)(*[_ptr(t) for t in centroids_by_width]),
                                       (_vp * n)(*[_ptr(t) for t in codes_by_width]), _ptr(centroids), None, _stream()),

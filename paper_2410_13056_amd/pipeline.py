@@ -333,7 +333,7 @@ def quantize_layer_from_cache(cache: WidthCache, sumsq: torch.Tensor, avg_bits: 
             codes1 = torch.empty((d_in, d_out), dtype=torch.uint8, device=dev)
             B.select_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1, codes1)
         else:
-            B.select_levels_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1)
+            B.select_levels_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1, d_out)
     return _after_first_pass(cache.W_t, sumsq, cache.bit_set, counts, act_idx, chan_mask, bits, cent1, codes1,
                              rho_q_ppm, cache.iters, ws, score, with_error, keep_prelim, status, timer,
                              iters_final_from_prelim, False, fused)
