@@ -150,8 +150,9 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t *__rest
 
 // 2-byte elements: a lane moves 4 elements (8 bytes) per access on both sides of an LDS tile of T x T.  RAGGED: any
 // dimensions and alignment, 8 bytes from any even address, the last 1 to 3 elements of a row one by one.  The rows
-// of a tile begin and end inside lines of memory there, so its tiles are of 128 and its loads leave the lines
-// they share in the cache (4099 x 3001: 13.2 us; tiles of 64 15.9, streamed loads 18.5, element by element 18.5).
+// of a tile begin and end inside lines of memory there, so its tiles are of 128 where they fill the chip and its loads
+// leave the lines they share in the cache (4099 x 3001: 13.2 us; tiles of 64 15.9, streamed loads 18.5, element by
+// element 18.5).
 // Else every dimension and leading dimension is a multiple of 4 and the bases are 8-byte aligned.
 template <int T, bool RAGGED>
 __global__ __launch_bounds__(256) void transpose16_vec_kernel(const uint16_t *__restrict__ src,
@@ -234,8 +235,15 @@ extern "C" int cmpq_transpose(const void *src, int dtype, int64_t rows, int64_t 
             transpose16_vec_kernel<kTile, false><<<grid, 256, 0, st>>>(from, rows, cols, ld_src, to, ld_dst);
             cmpq_timing_after(CMPQ_KERNEL_TRANSPOSE, st);
         } else {
+            // Tiles of 128 where they make 704 workgroups; with fewer, below three a compute unit, their longer way shows.
+            // Us, tiles of 128 and of 64: 33 x 70000 (547 of 128) 6.2 and 5.4, 1024 x 8190 (512) 10.9 and 6.7, 2500 x
+            // 2501 (400) 9.7 and 6.1, 3201 x 3200 (650) 11.7 and 10.0, 3333 x 3333 (729) 12.2 and 13.3, 4099 x 3001
+            // (792) 12.4 and 15.0.
             const dim3 wide((unsigned)cdiv(cols, 2 * kTile), (unsigned)cdiv(rows, 2 * kTile));
-            transpose16_vec_kernel<2 * kTile, true><<<wide, 256, 0, st>>>(from, rows, cols, ld_src, to, ld_dst);
+            if ((int64_t)wide.x * wide.y >= 704)
+                transpose16_vec_kernel<2 * kTile, true><<<wide, 256, 0, st>>>(from, rows, cols, ld_src, to, ld_dst);
+            else
+                transpose16_vec_kernel<kTile, true><<<grid, 256, 0, st>>>(from, rows, cols, ld_src, to, ld_dst);
         }
     } else {
         transpose32_kernel<<<grid, 256, 0, st>>>(static_cast<const uint32_t *>(src), rows, cols, ld_src,

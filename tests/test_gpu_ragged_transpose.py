@@ -7,7 +7,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 1), (3, 5), (4, 7), (63, 65), (64, 66), (129, 67), (257, 1031), (1030, 259)])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (3, 5), (4, 7), (63, 65), (64, 66), (129, 67), (257, 1031), (1030, 259),
+                                       (40, 70001), (3331, 3363)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
 def test_orientation_of_any_rows(rows, cols, dtype):
     if not torch.cuda.is_available():
