@@ -1911,8 +1911,10 @@ __device__ __forceinline__ void write_chunks(const WselArgs &a, uint32_t T, uint
 // The last kernel of a call: from the list, unless the exact chain ran and its list overflowed: then
 // with one more pass over the data, a workgroup per run of 4 units.  Where there are fewer
 // candidates than asked for, the rest of idx_out is filled with -1.
+// (Held to 8 wavefronts a SIMD: what is on its way for the list takes more than 96 scalar registers, which leaves 7, and
+// the pass over the data then takes 331 us instead of 316 for 8192x28672 weights.)
 template <typename TW>
-__global__ __launch_bounds__(kWThreads) void wsel_emit_kernel(WselArgs a, const WselState *st,
+__global__ __launch_bounds__(kWThreads, 8) void wsel_emit_kernel(WselArgs a, const WselState *st,
                                                                const uint2 *__restrict__ cnt_unit,
                                                                const uint2 *__restrict__ cnt_block,
                                                                int64_t k, int32_t *__restrict__ idx_out,
