@@ -308,6 +308,9 @@ def build_width_cache(W: torch.Tensor, bit_set: Sequence[int], iters: int = 20,
 # From this many weights on a layer takes only its levels from the kept runs: O_q ranks the distance to the nearest
 # level itself (the same score), which costs its pass a start of some 20 us and saves copying the codes and reading
 # them back.  Copy and pass, us: 13824 x 5120 26 + 47 with codes, 5 + 59 without; 4096 x 4096 9 + 17 and 4 + 29.
+# The more channels of 16 levels, the dearer the search: above 3.5 bits on average only from four times as many on.
+# The call with levels | with codes, us: 11008 x 4096 325 | 324 at 3.6 bits, 311 | 306 at 4; 13824 x 5120 430 | 437 at 2.6,
+# 426 | 419 at 4; 28672 x 8192 966 | 1014 at 4; 4096 x 8192 209 | 201 at 3.1.
 LEVELS_ONLY = 1 << 25
 
 
@@ -328,8 +331,9 @@ def quantize_layer_from_cache(cache: WidthCache, sumsq: torch.Tensor, avg_bits: 
                                                             timer)
     cent1 = torch.empty((d_in, B.KMAX), dtype=torch.float32, device=dev)
     codes1 = None
+    line = LEVELS_ONLY if avg_bits <= 3.5 else 4 * LEVELS_ONLY
     with _stage(timer, "select_by_width"):
-        if keep_prelim or d_in * d_out < LEVELS_ONLY or not _histogram_kernel_takes(cache.W_t):
+        if keep_prelim or d_in * d_out < line or not _histogram_kernel_takes(cache.W_t):
             codes1 = torch.empty((d_in, d_out), dtype=torch.uint8, device=dev)
             B.select_by_width(bits, cache.bit_set, cache.centroids, cache.codes, cent1, codes1)
         else:
