@@ -901,10 +901,15 @@ int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
 // With more tokens two layers of that size side by side lose more (5756 -> 11456 twice, 16 tokens 51.0 us with 6
 // steps, 54.9 with 5) than one alone gains.
 constexpr int64_t kShortCost = 17, kShortTokens = 8;
+// Parts of one step instead of at least two of width 3 or 4 (three of width 2) in layers of up to 16 steps and 32 tokens,
+// which have few workgroups otherwise: 256x15296, 10 tokens 16.7 us, now 14.9; 450x6000 15.6 and 13.8; 256x4096, 24 tokens 19.2 and
+// 16.5; smaller ones level.  (Many outputs and tokens lose, 480x16384, 32 tokens 22.7 and 24.2; past 16 steps many more do:
+// 512x16384, 16 tokens 18.3 and 19.4; 1024x8192 17.2 and 18.7.)
+constexpr int kThinSteps = 16;
 void choose_slabs(Layer &L, int64_t m) {
     // (where there are few tiles, widths with few rows get their parts on top)
     const int64_t slabs = wanted_slabs(L.d_out, m), want = kWaves * (slabs + (slabs == kMaxSlabs && L.n_seg > 1 ? L.n_seg - 1 : 0));
-    int64_t cost = kLeastCost, parts = 0;
+    int64_t cost = L.steps <= kThinSteps && m <= 2 * kTok ? 3 : kLeastCost, parts = 0;
     for (;; ++cost) {
         parts = 0;
         for (int j = 0; j < L.n_seg; ++j) parts += cdiv(L.seg[j].steps, part_steps(L.seg[j].bits, cost));

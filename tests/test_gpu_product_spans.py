@@ -13,10 +13,11 @@ pytestmark = pytest.mark.gpu
 
 
 # the fullest workgroup holds the inputs of exactly as many rows as fit (2064, 8528), 1 step too many, 5 too many;
-# one step is 32 rows
+# one step is 32 rows; thin layers of 15 and 17 steps, whose parts are cut otherwise
 @pytest.mark.parametrize("d_in,d_out,bit_set,avg,m", [
     (2064, 256, (2, 3), 2.75, 32), (4096, 512, (2, 3), 2.5, 32), (5696, 512, (2, 3), 2.5, 32),
-    (5120, 640, (2, 3, 4), 2.75, 32), (8528, 256, (2, 3), 2.5, 16), (9824, 256, (2, 3), 2.8, 16)])
+    (5120, 640, (2, 3, 4), 2.75, 32), (8528, 256, (2, 3), 2.5, 16), (9824, 256, (2, 3), 2.8, 16),
+    (440, 8200, (2, 3), 2.5, 16), (480, 8192, (2, 3), 2.5, 32), (440, 8192, (2, 3), 2.5, 32), (440, 8193, (2, 3), 2.5, 32)])
 def test_inputs_of_full_workgroups(env, d_in, d_out, bit_set, avg, m):
     P, ws = env["P"], env["ws"]
     dep, What = _layer(env, d_in, d_in, d_out, bit_set, avg, 4500)
