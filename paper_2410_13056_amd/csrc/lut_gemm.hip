@@ -932,20 +932,28 @@ void choose_slabs(Layer &L, int64_t m) {
     }
 }
 
-// Whether the workgroups of a layer take the inputs of up to `nd` tokens straight from X.  They keep those of all
+// Whether the workgroups of a layer take the inputs of m tokens straight from X.  They keep those of all
 // their rows in LDS, so the fullest slab decides, not the mean: parts are of even cost, and four of width 2 hold up
-// to 1.8 times the mean.  It is done where a launch less is worth more than the scattered reads: up to 4 tokens
-// always (13824x5120 twice, 4 tokens: 41 against 45 us), up to 8 in layers of up to 64 million weights (4099 and 513
-// of 3001, 5 tokens: 18 against 23; 4096x4096, 6 tokens: 17 and 20; 4096 -> 11008 twice, 8 tokens: level;
-// 8192x28672: 65 and 62), up to 16 in those of up to 16 million and 4096 channels (3001x4099: 24.8 and 26.0; 8192 ->
-// 1024 twice: 30 and 27), up to 32 in small ones (900x700, 6 tokens: 17 against 20 us).  Either way the same numbers
-// in the same order.
-bool direct_inputs(const Layer &L, int nd) {
-    const int64_t most = kDirectWeights * (nd <= 8 ? 16 : (nd == 16 && L.d_in <= 4096 ? 4 : 1));
-    if (nd > 4 && (int64_t)L.d_in * L.d_out > most) return false;
-    return L.span <= direct_steps(nd);
-}
+// to 1.8 times the mean.  It is done where a launch less (3 to 4 us of the host's time, which bounds calls of less than
+// 20 us) is worth more than the scattered reads, which grow with the tokens and the entries of O_q in a column.
+// Straight | in order, us a call:
+//   * up to 4 tokens always (13824x5120 twice, 4 tokens: 41 | 45), up to 8 in layers of up to 64 million weights (4099 and
+//     513 of 3001, 5 tokens: 18 | 23; 4096x4096, 6 tokens: 17 | 20; 4096 -> 11008 twice, 8 tokens: level; 8192x28672: 65 | 62);
+//   * up to 16 in layers of up to 4 million weights (4096x1024, 0.5 % of the weights in O_q, 12 tokens 17.8 | 18.7; 1 %, 16
+//     tokens 21.4 | 19.5), and of up to 12 million up to 40960 tokens times channels (1024x8192, 1 %, 10 tokens 16.0 | 16.9; 2048x4096, 16
+//     tokens 19.6 | 18.1 to 19.6, as fast as the host is; 4096x2048, 9 tokens 18.8 | 19.8; 3072x3072, 16 tokens 21.1 | 18.2 to 19.3;
+//     4096x4096, 10 tokens 22.7 | 20.0);
+//   * up to 32 in layers of up to 16 steps with up to 8192 outputs in the call, more than which the finish kernel takes in two rounds
+//     (256x4096, 24 tokens 16.5 | 17.2 to 18.7; 340x9000 22.2 | 18.7; 1000x1000, 32 tokens 19.5 | 19.3; 4000x1000, 1 % 24.8 | 20.4).
+// Either way the same numbers in the same order.
+constexpr int64_t kDirectReads = 40 << 10, kThinOutputs = 8192;
 int direct_tokens(int64_t m) { return m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32)); }
+bool direct_inputs(const Layer &L, int64_t m) {
+    if (m > 32 || (m > 16 && (L.steps > kThinSteps || L.d_out > kThinOutputs))) return false;
+    const int64_t most = kDirectWeights * (m <= 8 ? 16 : (m * L.d_in <= kDirectReads ? 3 : 1));
+    if (m > 4 && (int64_t)L.d_in * L.d_out > most) return false;
+    return L.span <= direct_steps(direct_tokens(m));
+}
 
 // Whether to decode the weight once into memory and multiply from there.  That costs 4 bytes of
 // traffic per weight and two launches, multiplying while decoding costs a decoding per 32 tokens;
@@ -1108,7 +1116,7 @@ void lut_gemm_shape(const cmpq_deployed_layer &S, int64_t m, int64_t *shape, int
         parts[3 * part + 2] = row + rows < s.rows ? rows : s.rows - row;
     }
     shape[3] = n;
-    shape[4] = at_once <= 32 && direct_inputs(L, nd) ? (int64_t)nd * (L.span * kRowsPerStep + 8) * (int64_t)sizeof(__half) : 0;
+    shape[4] = direct_inputs(L, at_once) ? (int64_t)nd * (L.span * kRowsPerStep + 8) * (int64_t)sizeof(__half) : 0;
     shape[5] = kSlabLds - kTablesBytes;
 }
 
@@ -1154,12 +1162,14 @@ int launch_lut_gemm(const cmpq_deployed_layer *const *layers, int n_layers, int6
         const unsigned wx = number([&](const Layer &L) {
             return G->token_tiles * (cdiv(L.steps, 8) + (L.xt ? cdiv(L.d_in, (int64_t)kThreads) : 0)); });
         const int nd = direct_tokens(m);
-        bool direct = G == &few && m <= 32;
+        bool direct = G == &few;
         // (past 8 tokens by the weights of all layers: the launch left out is one, the scattered reads are each layer's;
         // 542 -> three times 13568, 12 tokens: 28.9 us with inputs straight from X, 24.1 without)
-        int64_t weights = 0;
-        for (int i = 0; i < n; ++i) weights += (int64_t)G->l[i].d_in * G->l[i].d_out;
-        for (int i = 0; direct && i < n; ++i) direct = direct_inputs(G->l[i], nd) && (nd <= 8 || weights <= 4 * kDirectWeights);
+        int64_t weights = 0, outputs = 0;
+        for (int i = 0; i < n; ++i) weights += (int64_t)G->l[i].d_in * G->l[i].d_out, outputs += G->l[i].d_out;
+        if (m > 8 && weights > 4 * kDirectWeights) direct = false;
+        if (m > 16 && outputs > kThinOutputs) direct = false;
+        for (int i = 0; direct && i < n; ++i) direct = direct_inputs(G->l[i], m);
         if (wx && !direct && G == &few) tokens_kernel<<<wx, kThreads, 0, s>>>(*G);
         if (G == &few) {
             const unsigned w = number([&](const Layer &L) { return (int64_t)L.tiles * L.slabs * (tts / MT); });

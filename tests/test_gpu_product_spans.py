@@ -1,5 +1,6 @@
-"""Products of 16 and 32 tokens whose workgroups are at, and past, the most rows of which they can keep the inputs in
-LDS (tests/test_product_plan.py has the rule itself on the host).
+"""Products of 9 to 32 tokens around the lines up to which workgroups keep the inputs of their rows in LDS, and in
+layers whose fullest workgroups have more rows than LDS could hold them of (tests/test_product_plan.py has the rule
+itself on the host).
 
 Bar: per output and token, the fp32 rounding of the sums - 2e-6 of the sum of the terms' magnitudes -
 against the product in 64 bits with the weight rebuilt from W, levels, codes and outlier indices."""
@@ -12,11 +13,13 @@ from test_gpu_product_tokens import _check, _layer
 pytestmark = pytest.mark.gpu
 
 
-# the fullest workgroup holds the inputs of exactly as many rows as fit (2064, 8528), 1 step too many, 5 too many;
-# one step is 32 rows; thin layers of 15 and 17 steps, whose parts are cut otherwise
+# the inputs of the fullest workgroup's rows would just fit into LDS (2064, 8528), are 1 step too many, 5 too many (one step
+# is 32 rows); tokens times channels at the line and past it; thin layers of 15 and 17 steps, whose parts are cut otherwise,
+# with as many outputs as their line and one more
 @pytest.mark.parametrize("d_in,d_out,bit_set,avg,m", [
     (2064, 256, (2, 3), 2.75, 32), (4096, 512, (2, 3), 2.5, 32), (5696, 512, (2, 3), 2.5, 32),
     (5120, 640, (2, 3, 4), 2.75, 32), (8528, 256, (2, 3), 2.5, 16), (9824, 256, (2, 3), 2.8, 16),
+    (2560, 1000, (2, 3), 2.5, 16), (2561, 1700, (2, 3), 2.5, 16), (1536, 300, (2, 3, 4), 3.0, 17),
     (440, 8200, (2, 3), 2.5, 16), (480, 8192, (2, 3), 2.5, 32), (440, 8192, (2, 3), 2.5, 32), (440, 8193, (2, 3), 2.5, 32)])
 def test_inputs_of_full_workgroups(env, d_in, d_out, bit_set, avg, m):
     P, ws = env["P"], env["ws"]

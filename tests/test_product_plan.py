@@ -36,11 +36,11 @@ def test_inputs_of_the_fullest_workgroup_fit_into_lds():
     more between tokens, behind the tables of levels.  Its rows are those of four neighbouring parts, and parts
     are of even cost, not of even length."""
     taken = {4: 0, 8: 0, 16: 0, 32: 0}
-    for d_in, d_out, m, bit_set, counts, k_act in _layers(1, 6000):
+    for d_in, d_out, m, bit_set, counts, k_act in _layers(1, 12000):
         (way, _, groups, n, used, there), parts = B.lut_matvec_shape(d_in, d_out, bit_set, counts, k_act, m)
         if way != 1 or not used:
             continue
-        tokens = next(t for t in (4, 8, 16, 32) if m <= t)
+        tokens = next(t for t in taken if m <= t)
         steps = [-(-rows // 32) for _, _, rows in parts]
         assert groups == -(-n // 4)
         most = max(sum(steps[i:i + 4]) for i in range(0, n, 4))
