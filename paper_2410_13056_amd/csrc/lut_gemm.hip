@@ -895,12 +895,13 @@ int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
     const int64_t n = wanted_slabs(d_out, m) + kMaxSegs - 1, least = cdiv(cdiv(max_steps(d_in), (int64_t)kMaxRun) + kMaxSegs, (int64_t)kWaves);
     return n < least ? least : n;
 }
-// Up to 8 tokens a part has at most 5 steps of width 3 or 4 where the scratch for that is there, whatever is
-// wanted: longer ones are a chain of latencies in a workgroup, with a third of the chip's places taken (5535 ->
-// 12608, 2 tokens 31.4 us in 343 workgroups of up to 7 steps, 26.5 in 441; 7808 -> 8768 and 2487, 4 tokens 34.2 and 31.2).
-// With more tokens two layers of that size side by side lose more (5756 -> 11456 twice, 16 tokens 51.0 us with 6
-// steps, 54.9 with 5) than one alone gains.
-constexpr int64_t kShortCost = 17, kShortTokens = 8;
+// Up to 8 tokens a part has at most 4 steps of width 3 or 4, or as few more as the scratch of most_slabs takes, whatever is
+// wanted: longer ones are a chain of latencies in a workgroup, with a third of the chip's places taken (widths 3 and 4 at
+// 3.3 bits, 2 tokens: 8192 -> 10240 34.9 us in 360 workgroups of 8 steps, 29.2 in 480 of 6; 7936 -> 10821 35.2 and 30.3;
+// 4096 -> 11008 24.5 with 5 steps, 21.8 with 4; 5248 -> 10496 25.2 and 21.9).  Two layers of that size side by side lose the
+// round that they shared (4617 -> twice 10583 31.1 and 36.1; 4096 -> twice 11008 30.4 and 32.2; 5535 -> twice 12608 level), and with
+// more tokens they would lose more (5756 -> 11456 twice, 16 tokens 51.0 us with 6 steps, 54.9 with 5) than one alone gains.
+constexpr int64_t kShortCost = 12, kShortTokens = 8;
 // Parts of one step instead of at least two of width 3 or 4 (three of width 2) in layers of up to 16 steps and 32 tokens,
 // which have few workgroups otherwise: 256x15296, 10 tokens 16.7 us, now 14.9; 450x6000 15.6 and 13.8; 256x4096, 24 tokens 19.2 and
 // 16.5; smaller ones level.  (Many outputs and tokens lose, 480x16384, 32 tokens 22.7 and 24.2; past 16 steps many more do:
@@ -914,7 +915,7 @@ void choose_slabs(Layer &L, int64_t m) {
         parts = 0;
         for (int j = 0; j < L.n_seg; ++j) parts += cdiv(L.seg[j].steps, part_steps(L.seg[j].bits, cost));
         if (parts <= want || cost == 3 * kMaxRun) break;
-        if (m <= kShortTokens && cost == kShortCost && parts <= kWaves * most_slabs(L.d_in, L.d_out, m)) break;
+        if (m <= kShortTokens && cost >= kShortCost && parts <= kWaves * most_slabs(L.d_in, L.d_out, m)) break;
     }
     int part = 0;
     for (int j = 0; j < L.n_seg; ++j) {

@@ -69,3 +69,13 @@ def test_parts_cover_every_row_once():
             assert row == at[width] and 0 < rows <= most[width], (case, width, row, rows)
             at[width] += rows
         assert at == left, case
+
+
+def test_parts_of_few_tokens_are_short():
+    """Up to 8 tokens a part of width 3 or 4 has at most 4 steps of 32 rows, or as few more as the workspace takes, though
+    fewer workgroups than the chip has places for would do: long parts are chains of latencies."""
+    for d_in, d_out, most in [(4096, 11008, 4), (5248, 10496, 4), (8192, 10240, 6), (7936, 10821, 6), (5535, 12608, 5)]:
+        for m in (2, 4, 5, 8):
+            k_act = B.count_ppm(4500, d_in)
+            _, parts = B.lut_matvec_shape(d_in, d_out, (3, 4), _widths(d_in, (3, 4), 3.3, k_act), k_act, m)
+            assert max(rows for width, _, rows in parts if width <= 4) <= 32 * most, (d_in, d_out, m)
