@@ -21,10 +21,10 @@
 // sends that layer token by token).
 //
 // Measured against one token after the other (us per call): two 13824x5120 layers, 16 tokens 281 ->
-// 44, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 297, of which, under
-// the profiler, the product 231 (622 TFLOP/s of the 1144 that a large library product reaches here),
-// decoding with the inputs put in order beside it 85 (in launches of their own 65 + 26).  The error against 64 bits is the same within a few per cent
-// (1.0e-7 to 1.4e-7).  What bounds the few-token kernel is its decoding: an LDS look-up a weight at 3
+// 41, 96 tokens -> 160; a 4096-wide attention and MLP group, 512 tokens 9183 -> 303, of which, under
+// the profiler, the product 233 (618 TFLOP/s of the 1144 that a large library product reaches here),
+// decoding with the inputs put in order beside it 75 (in launches of their own 65 + 26).  The error against 64 bits is
+// 0.8e-7 to 1.4e-7, no larger than token by token.  What bounds the few-token kernel is its decoding: an LDS look-up a weight at 3
 // and 4 bits (2.6 clocks of a compute unit each, measured; 4 of the 5 thousand clocks that a step of
 // 32 rows takes 12 wavefronts) and 2.3 vector instructions; at 2 bits half of either.  Of its 26 us at
 // 16 tokens (37 with a fourth instruction a weight, the parts split without regard to their cost

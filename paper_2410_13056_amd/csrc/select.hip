@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kRankThreads) void allocate_bits_reg_kernel(
 // one are the first k[0], k[1] and k[2] channels of one order (larger key first, equal keys by index), so
 // the three threshold keys come out of the same three digit passes: one histogram for the first digit, one for
 // each rank after that.  A pass is a chain of barriers, so what counts is their number: 5120 channels, 1.6 us a
-// digit; as two launches of three and three passes 6.2 + 7.0 us, 13.4 with the gap, now 7.9.
+// digit; as two launches of three and three passes 5.9 + 6.7 us and the gap between them, now 8.1.
 struct MultiShared {
     uint32_t hist[3][2048];
     uint32_t scan[34];

@@ -26,7 +26,10 @@ class StageTimer:
 
     With ``kernels=True`` the library's measurement hook also brackets the one kernel that
     dominates the stage (`cmpq_time_kernel`: events recorded right before and after that launch,
-    on its stream); `kernel_totals()` returns the same shape for those."""
+    on its stream); `kernel_totals()` returns the same shape for those.
+
+    O_act and the widths of the other channels come out of one call and are one stage, `rank_channels`; there is no
+    `outlier_channels` or `allocate_bits` beside it."""
 
     def __init__(self, kernels: bool = False):
         self.pairs: Dict[str, list] = {}
