@@ -899,13 +899,14 @@ int64_t most_slabs(int64_t d_in, int64_t d_out, int64_t m) {
 // wanted: longer ones are a chain of latencies in a workgroup, with a third of the chip's places taken (widths 3 and 4 at
 // 3.3 bits, 2 tokens: 8192 -> 10240 34.9 us in 360 workgroups of 8 steps, 29.2 in 480 of 6; 7936 -> 10821 35.2 and 30.3;
 // 4096 -> 11008 24.5 with 5 steps, 21.8 with 4; 5248 -> 10496 25.2 and 21.9).  Two layers of that size side by side lose the
-// round that they shared (4617 -> twice 10583 31.1 and 36.1; 4096 -> twice 11008 30.4 and 32.2; 5535 -> twice 12608 level), and with
-// more tokens they would lose more (5756 -> 11456 twice, 16 tokens 51.0 us with 6 steps, 54.9 with 5) than one alone gains.
+// round that they shared (4617 -> twice 10583 31.1 and 36.1; 4096 -> twice 11008 30.4 and 32.2; 5535 -> twice 12608
+// level), and with more tokens they would lose more (5756 -> 11456 twice, 16 tokens 51.0 us with 6 steps, 54.9 with 5)
+// than one alone gains.
 constexpr int64_t kShortCost = 12, kShortTokens = 8;
 // Parts of one step instead of at least two of width 3 or 4 (three of width 2) in layers of up to 16 steps and 32 tokens,
-// which have few workgroups otherwise: 256x15296, 10 tokens 16.7 us, now 14.9; 450x6000 15.6 and 13.8; 256x4096, 24 tokens 19.2 and
-// 16.5; smaller ones level.  (Many outputs and tokens lose, 480x16384, 32 tokens 22.7 and 24.2; past 16 steps many more do:
-// 512x16384, 16 tokens 18.3 and 19.4; 1024x8192 17.2 and 18.7.)
+// which have few workgroups otherwise: 256x15296, 10 tokens 16.7 us, now 14.9; 450x6000 15.6 and 13.8; 256x4096, 24 tokens
+// 19.2 and 16.5; smaller ones level.  (Many outputs and tokens lose, 480x16384, 32 tokens 22.7 and 24.2; past 16 steps
+// many more do: 512x16384, 16 tokens 18.3 and 19.4; 1024x8192 17.2 and 18.7.)
 constexpr int kThinSteps = 16;
 void choose_slabs(Layer &L, int64_t m) {
     // (where there are few tiles, widths with few rows get their parts on top)
@@ -941,11 +942,12 @@ void choose_slabs(Layer &L, int64_t m) {
 //   * up to 4 tokens always (13824x5120 twice, 4 tokens: 41 | 45), up to 8 in layers of up to 64 million weights (4099 and
 //     513 of 3001, 5 tokens: 18 | 23; 4096x4096, 6 tokens: 17 | 20; 4096 -> 11008 twice, 8 tokens: level; 8192x28672: 65 | 62);
 //   * up to 16 in layers of up to 4 million weights (4096x1024, 0.5 % of the weights in O_q, 12 tokens 17.8 | 18.7; 1 %, 16
-//     tokens 21.4 | 19.5), and of up to 12 million up to 40960 tokens times channels (1024x8192, 1 %, 10 tokens 16.0 | 16.9; 2048x4096, 16
-//     tokens 19.6 | 18.1 to 19.6, as fast as the host is; 4096x2048, 9 tokens 18.8 | 19.8; 3072x3072, 16 tokens 21.1 | 18.2 to 19.3;
-//     4096x4096, 10 tokens 22.7 | 20.0);
-//   * up to 32 in layers of up to 16 steps with up to 8192 outputs in the call, more than which the finish kernel takes in two rounds
-//     (256x4096, 24 tokens 16.5 | 17.2 to 18.7; 340x9000 22.2 | 18.7; 1000x1000, 32 tokens 19.5 | 19.3; 4000x1000, 1 % 24.8 | 20.4).
+//     tokens 21.4 | 19.5), and of up to 12 million up to 40960 tokens times channels (1024x8192, 1 %, 10 tokens 16.0 |
+//     16.9; 2048x4096, 16 tokens 19.6 | 18.1 to 19.6, as fast as the host is; 4096x2048, 9 tokens 18.8 | 19.8;
+//     3072x3072, 16 tokens 21.1 | 18.2 to 19.3; 4096x4096, 10 tokens 22.7 | 20.0);
+//   * up to 32 in layers of up to 16 steps with up to 8192 outputs in the call, more than which the finish kernel takes in
+//     two rounds (256x4096, 24 tokens 16.5 | 17.2 to 18.7; 340x9000 22.2 | 18.7; 1000x1000, 32 tokens 19.5 | 19.3;
+//     4000x1000, 1 % 24.8 | 20.4).
 // Either way the same numbers in the same order.
 constexpr int64_t kDirectReads = 40 << 10, kThinOutputs = 8192;
 int direct_tokens(int64_t m) { return m <= 4 ? 4 : (m <= 8 ? 8 : (m <= 16 ? 16 : 32)); }
